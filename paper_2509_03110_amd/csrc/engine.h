@@ -62,9 +62,11 @@ int launch_gram_dot(const float* G1, const float* G2, int64_t stride, int64_t n,
 // the tree are fixed-order, so the result is run-to-run deterministic).
 // `restart` (may be null): the per-replica marks described at launch_center; this kernel, which
 // runs once per step before anything touches the iterate sums, counts every mark down by one.
+// `nonfinite` (may be null): the plane writers' flag, lowered here, between the two passes (each
+// pass writes all the planes it reads).
 void launch_norm_finish(const double* partials, int nblk, int64_t partials_stride, int K, float rho, float gamma,
                         float* norms, float* scale, const float* loss_rows, int B,
-                        float* loss_out, hipStream_t s, int32_t* restart = nullptr);
+                        float* loss_out, hipStream_t s, int32_t* restart = nullptr, int* nonfinite = nullptr);
 // x~ = x + scale[k] * g.  Writes fp32 (xt_f32), or, if xt_bf16 is non-null, the bf16 operand
 // copy of the weight matrices in the blocked layout described by `map` (replica stride
 // `shadow_stride` elements).
@@ -186,6 +188,55 @@ size_t gemm_splitk_bytes(const GemmDesc& d);          // scratch this GEMM would
 // bf16 fast path (direct-to-LDS ring); returns 1 when the shape is left to the generic kernel.
 int launch_gemm_bf16(const GemmDesc& d, int tile_override, hipStream_t s, int* sumsq_slots);
 
+// Adds the `splits` partial results of a split contraction ([M][ldP] per replica, split_stride
+// floats apart) in a fixed order and finishes them as `d` says (C, epilogue, bias, mask, sumsq;
+// its operands are ignored).  Returns the sum-of-squares slots written per replica.
+int launch_splitk_reduce(const GemmDesc& d, const float* partial, int splits, int64_t split_stride, int ldP, hipStream_t s);
+
+// ---- convolution products on plane tensors (kernels_conv_gemm.hip) ------------------------
+// A plane tensor holds every fp32 value as np bfloat16 values, `plane` elements apart: np = 1 the
+// rounded value, np = 3 an exact split.
+struct PlaneImage {
+  const uint16_t* p; int64_t stride, plane;      // replica and plane strides (elements, multiples of 8)
+  int C, oH, oW, sH, sW, st;                     // images [sH][sW][C], C % 8 == 0; output pixels [oH][oW]
+  int nu, nv, du0, dv0;                          // tap (a, c) of nu x nv reads pixel (st i + du0 + a, st j + dv0 + c)
+};
+// wgrad = 0: C[m, n] = sum over (tap, c) of image(pixel m, tap, c) * other[n][(tap, c)], M output
+//   pixels, Kd = taps * C, other [N][ld] with zeros from Kd to the next multiple of 32.
+// wgrad = 1: C[m, (tap, c)] = sum over output pixels k of other[k][m] * image(k, tap, c), other
+//   [Kd][M] (ld = M), N = taps * C.
+// Epilogues as in GemmDesc (bias, mask: fp32).  `nonfinite`: the flag the plane writers raise.
+struct ConvGemmDesc {
+  int np, wgrad;
+  PlaneImage image;
+  const uint16_t* other; int64_t other_stride, other_plane; int ld;
+  float* C; int64_t strideC; int ldC;
+  int M, N, Kd, batch;
+  int epilogue;
+  const float* bias; int64_t strideBias;
+  const float* mask; int64_t strideMask; int ldMask;
+  float* splitk_ws; size_t splitk_bytes;
+  double* sumsq; int64_t sumsq_stride;
+  const int* nonfinite;
+};
+int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots = nullptr);   // 0, or -1: not served
+size_t conv_gemm_splitk_bytes(const ConvGemmDesc& d);
+// Planes of n consecutive floats (n % 4 == 0).  *nonfinite is set to 1 when np = 3 and a value is infinite.
+int launch_split_planes(const float* src, uint16_t* dst, int np, int64_t plane, int64_t n, int* nonfinite, hipStream_t s);
+// One filter bank [rows][cols] (row pitch ldw) at `src` of every replica's parameters as the plane
+// products read it, `dst` elements into every plane.  taps = 0: [K][rows][ldp], zeros from cols on
+// (cols, ldw, ldp multiples of 4); taps = 1 or 9: mirrored and transposed, `cols` counting one tap's
+// columns: [K][cols][ldp], value (c, tap * rows + o) = W[o][(taps - 1 - tap) * cols + c], zeros beyond.
+struct FilterBank {
+  int64_t src, dst;
+  int32_t rows, cols, ldw, ldp, taps;
+  int32_t first;            // first workgroup that serves the bank
+};
+int filter_bank_blocks(const FilterBank& f);
+// All n banks of the table (device memory) for K replicas; blocks: workgroups of all of them.
+int launch_filters(const float* params, int64_t strideParams, const FilterBank* banks, int n, int blocks, uint16_t* dst,
+                   int np, int64_t plane, int K, int* nonfinite, hipStream_t s);
+
 // Softmax cross-entropy, forward and backward.  logits [K,B,ld] fp32; labels [K,B];
 // dz = (softmax - onehot)/B: fp32 [K,B,ld_dz] row-major with zeros in the padded columns, or
 // (dz_bf16) bf16 in the blocked layout, ld_dz then being one replica's stored size in elements;
@@ -220,11 +271,12 @@ int launch_head_weight_grad(const float* dz, int ld_dz, const float* A, int ldA,
 // when the shape does not fit the kernel (pitches and channel counts that are not multiples
 // of 4 where stated).
 // col[k][(b,i,j)][(u,v,c)] = X[k][b][i+u-1][j+v-1][c], zero outside the image and in the
-// padding columns 9C..ld-1 (ld % 4 == 0; any C).
+// padding columns 9C..ld-1 (ld % 4 == 0; any C): np = 0 as floats, otherwise as np bfloat16 planes
+// `plane` elements apart (np = 3 raises *nonfinite on an infinite value).
 // `stride` 1 or 2: the image is [stride H][stride W][C] and col row (b,i,j) holds the window
 // around pixel (stride i, stride j); H x W is the convolution's output.
-int launch_unfold3x3(const float* X, int64_t strideX, float* col, int64_t strideCol, int ld, int K,
-                     int B, int H, int W, int C, int stride, hipStream_t s);
+int launch_unfold3x3(const float* X, int64_t strideX, void* col, int np, int64_t plane, int ld, int K,
+                     int B, int H, int W, int C, int stride, int* nonfinite, hipStream_t s);
 // dX[k][b][i][j][c] = sum_{u,v} dcol[k][(b,i-u+1,j-v+1)][(u,v,c)], taps added in (u,v) order,
 // set to zero where mask (same shape as dX, may be null) is not positive.  C % 4 == 0.
 int launch_fold3x3(const float* dcol, int64_t strideCol, int ld, float* dX, const float* mask,
@@ -256,8 +308,12 @@ int launch_first_conv_wgrad(const float* X, const float* dout, float* partial, f
 // bn_chunks(rows, C, K) * C floats.  Backward: launch_bn_backward_partials leaves chunk sums
 // part[k][chunk][0..C) = sum dY Xh and [C..2C) = sum dY (returns the chunk count; launch_bias_grad
 // over them gives dgamma and dbeta); launch_bn_backward_apply then writes
-// dZ = gamma stats[1] (dY - dbeta/rows - Xh dgamma/rows) to `dZ`, which may be dY itself or Z,
-// dgamma and dbeta read from grad + k * strideParams at the same offsets.  -1: shape not supported.
+// dZ = gamma stats[1] (dY - dbeta/rows - Xh dgamma/rows) [+ add] to `dZ`, which may be dY itself or Z
+// (or null: planes only), dgamma and dbeta read from grad + k * strideParams at the same offsets.  -1: shape not supported.
+// Where a kernel also writes its fp32 result as plane tensors (np = 0: it does not).
+struct PlaneOut {
+  uint16_t* p = nullptr; int np = 0; int64_t plane = 0; int* nonfinite = nullptr;
+};
 // Shortcut of a residual block (He et al., CIFAR variant, parameter-free): the block input
 // src [K][B][step H][step W][Cs] (replica stride `stride` floats) enters the block output
 // [B][H][W][C] as src[b][step i][step j][c] for c < Cs and 0 for the channels beyond.  Cs % 4 == 0.
@@ -281,7 +337,8 @@ int bn_chunks(int64_t rows, int C, int K);
 // `shortcut` (may be null): added to the normalised output before the ReLU.
 int launch_bn_forward(const float* Z, float* scratch, float* stats, const float* params,
                       int64_t strideParams, int64_t gam_off, int64_t bet_off, float* out, int K,
-                      int64_t rows, int C, float eps, const ShortcutDesc* shortcut, hipStream_t s);
+                      int64_t rows, int C, float eps, const ShortcutDesc* shortcut, const PlaneOut& planes,
+                      hipStream_t s);
 // dIn (shape of d.src) += the gradient dY [K][rows][C] of the block output, through the shortcut,
 // kept only where mask (shape of dIn, the ReLU output the block read; may be null) is positive.
 int launch_shortcut_backward(const float* dY, float* dIn, const float* mask, const ShortcutDesc& d, int K,
@@ -295,7 +352,8 @@ int launch_bn_backward_partials(const float* Z, const float* dY, const float* st
                                 int64_t rows, int C, hipStream_t s);
 void launch_bn_backward_apply(const float* Z, const float* dY, float* dZ, const float* stats,
                               const float* params, const float* grad, int64_t strideParams,
-                              int64_t gam_off, int64_t bet_off, int K, int64_t rows, int C, hipStream_t s);
+                              int64_t gam_off, int64_t bet_off, int K, int64_t rows, int C, const float* add,
+                              const PlaneOut& planes, hipStream_t s);
 // Wt[k][c][(u,v,o)] = W[k][o][(2-u,2-v,c)] for K filter banks W [Cout][3][3][Cin] (row pitch ldw,
 // replica stride strideW); Wt is dense, [K][Cin][9 Cout].  Cout must be a multiple of 32.
 void launch_flip_filters(const float* W, int64_t strideW, int ldw, float* Wt, int K, int Cout, int Cin,
@@ -309,7 +367,7 @@ int launch_colsum_partials(const float* A, int64_t rows, int N, int K, float* pa
 // 2x2/stride-2 max-pool over `images` contiguous [H][W][C] images, and the backward pass of
 // ReLU-then-pool: dA = dP at the first maximum of each window if it is positive, else 0
 // (A: the ReLU output that was pooled).  C % 4 == 0, H and W even.
-int launch_maxpool2(const float* A, float* P, int64_t images, int H, int W, int C, hipStream_t s);
+int launch_maxpool2(const float* A, float* P, int64_t images, int H, int W, int C, const PlaneOut& planes, hipStream_t s);
 int launch_maxpool2_backward(const float* A, const float* dP, float* dA, int64_t images, int H,
                              int W, int C, hipStream_t s);
 

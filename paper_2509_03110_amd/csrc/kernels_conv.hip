@@ -9,12 +9,34 @@
 // All tensors are fp32, [K][B][H][W][C] with C contiguous; all four kernels are bandwidth
 // bound and move 128-bit words, consecutive lanes on consecutive words.
 #include "engine.h"
+#include "planes.h"
 
 namespace lsam {
 namespace {
 
 constexpr int kThreads = 256;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
+
+// Writes 4 values as planes at element `at` of each.
+template <int NP>
+__device__ __forceinline__ void put_planes(unsigned short* p, long long plane, long long at, const f32x4& v,
+                                           int* nonfinite) {
+  if constexpr (NP > 0) {
+    u16x4 w[NP];
+    bool inf = false;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      unsigned short t[NP];
+      inf |= split_planes<NP>(v[r], t);
+#pragma unroll
+      for (int q = 0; q < NP; ++q) w[q][r] = t[q];
+    }
+#pragma unroll
+    for (int q = 0; q < NP; ++q) *reinterpret_cast<u16x4*>(p + q * plane + at) = w[q];
+    if (NP > 1 && inf) *nonfinite = 1;
+  }
+}
 
 struct ImgShape {
   int H, W, C;     // one output image of the convolution (H x W positions), C input channels
@@ -24,11 +46,13 @@ struct ImgShape {
   int st;          // stride: the input image is [st H][st W][C]
 };
 
-// One thread per 16-byte word of col.  VEC: C % 4 == 0, a word then lies inside one tap.
-template <bool VEC>
+// One thread per 4 values of col.  VEC: C % 4 == 0, they then lie inside one tap.  NP: col is written
+// as that many bfloat16 planes, `plane` elements apart (replicas contiguous); 0: as floats.
+template <bool VEC, int NP>
 __global__ __launch_bounds__(kThreads) void unfold3x3_kernel(const float* __restrict__ X,
-                                                             float* __restrict__ col, ImgShape sh,
-                                                             long long strideX, long long strideCol) {
+                                                             void* __restrict__ col, ImgShape sh,
+                                                             long long strideX, long long plane,
+                                                             int* __restrict__ nonfinite) {
   const long long idx = (long long)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= sh.total) return;
   const int words = sh.ld / 4;
@@ -62,7 +86,8 @@ __global__ __launch_bounds__(kThreads) void unfold3x3_kernel(const float* __rest
       }
     }
   }
-  *reinterpret_cast<f32x4*>(col + (long long)k * strideCol + m * sh.ld + 4 * q) = o;
+  if constexpr (NP == 0) *reinterpret_cast<f32x4*>(static_cast<float*>(col) + idx * 4) = o;
+  else put_planes<NP>(static_cast<unsigned short*>(col), plane, idx * 4, o, nonfinite);
 }
 
 // Adjoint of the unfold: dX[b,y,x,c] = sum over the taps (u,v) and output positions (i,j) with
@@ -113,8 +138,11 @@ struct PoolShape {
 };
 
 // P[b,i,j,c] = max over the 2x2 window of A.  One thread per 16-byte word of P.
+template <int NP>
 __global__ __launch_bounds__(kThreads) void maxpool2_kernel(const float* __restrict__ A,
-                                                            float* __restrict__ P, PoolShape sh) {
+                                                            float* __restrict__ P, PoolShape sh,
+                                                            unsigned short* __restrict__ planes, long long plane,
+                                                            int* __restrict__ nonfinite) {
   const long long idx = (long long)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= sh.cells) return;
   const int words = sh.C / 4;
@@ -136,6 +164,7 @@ __global__ __launch_bounds__(kThreads) void maxpool2_kernel(const float* __restr
     m[r] = v3[r] > m[r] ? v3[r] : m[r];
   }
   *reinterpret_cast<f32x4*>(P + cell * sh.C + c) = m;
+  put_planes<NP>(planes, plane, cell * sh.C + c, m, nonfinite);
 }
 
 // Backward of ReLU followed by the pool: dA[window] = dP where A is the window's first
@@ -570,14 +599,17 @@ struct Shortcut {
   long long pgam_off, pbet_off;
 };
 
-// out = relu(gamma (Z - mean) inv_std + beta [+ shortcut]).  One thread per 16-byte word.
+// out = relu(gamma (Z - mean) inv_std + beta [+ shortcut]), and its planes for the layer that reads it.
+// One thread per 16-byte word.
+template <int NP>
 __global__ __launch_bounds__(kThreads) void bn_apply_kernel(const float* __restrict__ Z,
                                                             const float* __restrict__ stats,
                                                             const float* __restrict__ params,
                                                             long long strideParams, long long gam_off,
                                                             long long bet_off, float* __restrict__ out,
                                                             long long rows, int C, long long total,
-                                                            Shortcut sc) {
+                                                            Shortcut sc, unsigned short* __restrict__ planes,
+                                                            long long plane, int* __restrict__ nonfinite) {
   const long long idx = (long long)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= total) return;
   const int words = C / 4;
@@ -605,6 +637,7 @@ __global__ __launch_bounds__(kThreads) void bn_apply_kernel(const float* __restr
 #pragma unroll
   for (int r = 0; r < 4; ++r) y[r] = y[r] > 0.f ? y[r] : 0.f;
   *reinterpret_cast<f32x4*>(out + idx * 4) = y;
+  put_planes<NP>(planes, plane, idx * 4, y, nonfinite);
 }
 
 // The shortcut's share of the block input's gradient: dIn[b][st i][st j][c] += dY[b][i][j][c]
@@ -729,12 +762,14 @@ __global__ __launch_bounds__(kThreads) void bn_backward_partial_kernel(const flo
   }
 }
 
-// dZ = gamma inv_std (dY - dbeta / N - Xh dgamma / N), written to dZ, which may be dY itself or Z
-// (every thread reads its own word of both before it writes).
+// dZ = gamma inv_std (dY - dbeta / N - Xh dgamma / N) [+ add], written to dZ (null: not at all), which may
+// be dY itself or Z (every thread reads its own word of both before it writes), and to its planes.
+template <int NP>
 __global__ __launch_bounds__(kThreads) void bn_backward_apply_kernel(
     const float* Z, const float* dY, float* dZ, const float* __restrict__ stats,
     const float* __restrict__ params, const float* __restrict__ grad, long long strideParams,
-    long long gam_off, long long bet_off, long long rows, int C, long long total) {
+    long long gam_off, long long bet_off, long long rows, int C, long long total, const float* add,
+    unsigned short* __restrict__ planes, long long plane, int* __restrict__ nonfinite) {
   const long long idx = (long long)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= total) return;
   const int words = C / 4;
@@ -748,23 +783,28 @@ __global__ __launch_bounds__(kThreads) void bn_backward_apply_kernel(
   const float inv_n = 1.f / (float)rows;
   const f32x4 xh = (*reinterpret_cast<const f32x4*>(Z + idx * 4) - mu) * inv;
   const f32x4 dy = *reinterpret_cast<const f32x4*>(dY + idx * 4);
-  *reinterpret_cast<f32x4*>(dZ + idx * 4) = ga * inv * (dy - dbe * inv_n - xh * (dga * inv_n));
+  f32x4 o = ga * inv * (dy - dbe * inv_n - xh * (dga * inv_n));
+  if (add != nullptr) o += *reinterpret_cast<const f32x4*>(add + idx * 4);
+  if (dZ != nullptr) *reinterpret_cast<f32x4*>(dZ + idx * 4) = o;
+  put_planes<NP>(planes, plane, idx * 4, o, nonfinite);
 }
 
 unsigned blocks_for(long long total) { return (unsigned)((total + kThreads - 1) / kThreads); }
 
 }  // namespace
 
-int launch_unfold3x3(const float* X, int64_t strideX, float* col, int64_t strideCol, int ld, int K,
-                     int B, int H, int W, int C, int stride, hipStream_t s) {
+int launch_unfold3x3(const float* X, int64_t strideX, void* col, int np, int64_t plane, int ld, int K,
+                     int B, int H, int W, int C, int stride, int* nonfinite, hipStream_t s) {
   ImgShape sh{H, W, C, ld, (long long)B * H * W, 0, stride};
   sh.total = (long long)K * sh.rows * (ld / 4);
   if (ld % 4 || ld < 9 * C || sh.total <= 0 || sh.total >= (1ll << 31) * kThreads || stride < 1 || stride > 2)
     return -1;
+  const unsigned grid = blocks_for(sh.total);
+  auto run = [&](auto kernel) { kernel<<<grid, kThreads, 0, s>>>(X, col, sh, strideX, plane, nonfinite); };
   if (C % 4 == 0)
-    unfold3x3_kernel<true><<<blocks_for(sh.total), kThreads, 0, s>>>(X, col, sh, strideX, strideCol);
+    run(np == 0 ? unfold3x3_kernel<true, 0> : np == 1 ? unfold3x3_kernel<true, 1> : unfold3x3_kernel<true, 3>);
   else
-    unfold3x3_kernel<false><<<blocks_for(sh.total), kThreads, 0, s>>>(X, col, sh, strideX, strideCol);
+    run(np == 0 ? unfold3x3_kernel<false, 0> : np == 1 ? unfold3x3_kernel<false, 1> : unfold3x3_kernel<false, 3>);
   return 0;
 }
 
@@ -855,7 +895,7 @@ int launch_subsample2(const float* src, float* dst, int64_t images, int H, int W
 
 int launch_bn_forward(const float* Z, float* scratch, float* stats, const float* params,
                       int64_t strideParams, int64_t gam_off, int64_t bet_off, float* out, int K,
-                      int64_t rows, int C, float eps, const ShortcutDesc* shortcut, hipStream_t s) {
+                      int64_t rows, int C, float eps, const ShortcutDesc* shortcut, const PlaneOut& o, hipStream_t s) {
   if (C % 4 || C < 4 || C > 4 * kThreads || rows < 1) return -1;
   Shortcut sc{nullptr, 0, 1, 1, 0, 1, nullptr, nullptr, 0, 0};
   if (shortcut != nullptr && shortcut->pz != nullptr) {
@@ -878,8 +918,11 @@ int launch_bn_forward(const float* Z, float* scratch, float* stats, const float*
   bn_stats_finish_kernel<<<dim3((unsigned)((C + 63) / 64), (unsigned)K), 64 * kBnChains, 0, s>>>(
       pmean, pm2, stats, rows, C, chunks, pl.chunk_rows, eps);
   const long long total = (long long)K * rows * (C / 4);
-  bn_apply_kernel<<<blocks_for(total), kThreads, 0, s>>>(Z, stats, params, strideParams, gam_off, bet_off,
-                                                        out, rows, C, total, sc);
+  auto run = [&](auto kernel) {
+    kernel<<<blocks_for(total), kThreads, 0, s>>>(Z, stats, params, strideParams, gam_off, bet_off, out, rows, C, total, sc,
+                                                  o.p, o.plane, o.nonfinite);
+  };
+  run(o.np == 0 ? bn_apply_kernel<0> : o.np == 1 ? bn_apply_kernel<1> : bn_apply_kernel<3>);
   return 0;
 }
 
@@ -916,10 +959,14 @@ int launch_bn_backward_partials(const float* Z, const float* dY, const float* st
 
 void launch_bn_backward_apply(const float* Z, const float* dY, float* dZ, const float* stats,
                               const float* params, const float* grad, int64_t strideParams,
-                              int64_t gam_off, int64_t bet_off, int K, int64_t rows, int C, hipStream_t s) {
+                              int64_t gam_off, int64_t bet_off, int K, int64_t rows, int C, const float* add,
+                              const PlaneOut& o, hipStream_t s) {
   const long long total = (long long)K * rows * (C / 4);
-  bn_backward_apply_kernel<<<blocks_for(total), kThreads, 0, s>>>(Z, dY, dZ, stats, params, grad, strideParams,
-                                                                 gam_off, bet_off, rows, C, total);
+  auto run = [&](auto kernel) {
+    kernel<<<blocks_for(total), kThreads, 0, s>>>(Z, dY, dZ, stats, params, grad, strideParams, gam_off, bet_off, rows, C,
+                                                  total, add, o.p, o.plane, o.nonfinite);
+  };
+  run(o.np == 0 ? bn_backward_apply_kernel<0> : o.np == 1 ? bn_backward_apply_kernel<1> : bn_backward_apply_kernel<3>);
 }
 
 int colsum_chunks(int64_t rows, int N, int K) { return chunk_plan(rows, N, K).chunks; }
@@ -932,10 +979,11 @@ int launch_colsum_partials(const float* A, int64_t rows, int N, int K, float* pa
   return pl.chunks;
 }
 
-int launch_maxpool2(const float* A, float* P, int64_t images, int H, int W, int C, hipStream_t s) {
+int launch_maxpool2(const float* A, float* P, int64_t images, int H, int W, int C, const PlaneOut& o, hipStream_t s) {
   PoolShape sh{H / 2, W / 2, C, images * (H / 2) * (W / 2) * (C / 4)};
   if (C % 4 || H % 2 || W % 2 || sh.cells <= 0 || sh.cells >= (1ll << 31) * kThreads) return -1;
-  maxpool2_kernel<<<blocks_for(sh.cells), kThreads, 0, s>>>(A, P, sh);
+  auto run = [&](auto kernel) { kernel<<<blocks_for(sh.cells), kThreads, 0, s>>>(A, P, sh, o.p, o.plane, o.nonfinite); };
+  run(o.np == 0 ? maxpool2_kernel<0> : o.np == 1 ? maxpool2_kernel<1> : maxpool2_kernel<3>);
   return 0;
 }
 

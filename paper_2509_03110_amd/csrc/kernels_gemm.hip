@@ -834,6 +834,17 @@ Plan make_plan(const GemmDesc& d, int tile_override) {
   return pl;
 }
 
+// Launches the reduce; returns the sum-of-squares slots it writes per replica.
+int reduce_splits(const GemmParams& p, hipStream_t s) {
+  const long long per_rep = (long long)p.M * (p.ldP / 4);
+  const int slots = (int)((per_rep + kThreads - 1) / kThreads);
+  if (p.splits >= 8)
+    splitk_reduce_kernel<4><<<dim3((unsigned)slots, (unsigned)p.batch), kThreads * 4, 0, s>>>(p);
+  else
+    splitk_reduce_kernel<1><<<dim3((unsigned)slots, (unsigned)p.batch), kThreads, 0, s>>>(p);
+  return slots;
+}
+
 template <typename T, typename TC, int BM, int BN, int BKU, bool AK, bool BK_, int CONV = 0,
           bool BF16MATH = false>
 int launch_one(const GemmParams& p0, hipStream_t s, int* sumsq_slots) {
@@ -856,15 +867,7 @@ int launch_one(const GemmParams& p0, hipStream_t s, int* sumsq_slots) {
     attr_set.store(true, std::memory_order_relaxed);
   }
   kern<<<p.chunks * 8, kThreads, smem, s>>>(p);
-  int slots = p.tilesM * p.tilesN;
-  if (p.splits > 1) {
-    const long long per_rep = (long long)p.M * (p.ldP / 4);
-    slots = (int)((per_rep + kThreads - 1) / kThreads);
-    if (p.splits >= 8)
-      splitk_reduce_kernel<4><<<dim3((unsigned)slots, (unsigned)p.batch), kThreads * 4, 0, s>>>(p);
-    else
-      splitk_reduce_kernel<1><<<dim3((unsigned)slots, (unsigned)p.batch), kThreads, 0, s>>>(p);
-  }
+  const int slots = p.splits > 1 ? reduce_splits(p, s) : p.tilesM * p.tilesN;
   if (sumsq_slots) *sumsq_slots = slots;
   return 0;
 }
@@ -920,12 +923,24 @@ int launch_layout(const GemmDesc& d, const GemmParams& p, const Plan& pl, hipStr
 
 }  // namespace
 
+int launch_splitk_reduce(const GemmDesc& d, const float* partial, int splits, int64_t split_stride, int ldP, hipStream_t s) {
+  GemmParams p{};
+  p.C = (char*)d.C; p.strideC = d.strideC; p.ldC = d.ldC;
+  p.M = d.M; p.N = d.N; p.batch = d.batch;
+  p.epilogue = d.epilogue;
+  p.bias = d.bias; p.strideBias = d.strideBias;
+  p.mask = (const char*)d.mask; p.strideMask = d.strideMask; p.ldMask = d.ldMask;
+  p.partial = const_cast<float*>(partial); p.strideSplit = split_stride; p.ldP = ldP; p.splits = splits;
+  p.sumsq = d.sumsq; p.strideSumsq = d.sumsq_stride;
+  return reduce_splits(p, s);
+}
+
 size_t gemm_splitk_bytes(const GemmDesc& d) { return make_plan(d, 0).ws_bytes; }
 
-// Smallest tiles are 64x64; a split-K reduce uses one workgroup per 256 vector words of
-// [M][N rounded up to 4].
+// Smallest tiles are 32x64 (plane products) and 64x64; a split-K reduce uses one workgroup per 256
+// vector words of [M][N rounded up to 4].
 int gemm_sumsq_capacity(int M, int N) {
-  const long long tiles = (long long)((M + 63) / 64) * ((N + 63) / 64);
+  const long long tiles = (long long)((M + 31) / 32) * ((N + 63) / 64);
   const long long words = ((long long)M * ((N + 3) / 4) + kThreads - 1) / kThreads;
   return (int)(tiles > words ? tiles : words);
 }

@@ -138,21 +138,34 @@ struct ConvLayer {
   bool skip;           // closes a residual block: the input of the layer below is added before the ReLU
   int skip_C, skip_step;   // channels of that block input; 2 if the block halved the image, else 1
   bool proj;           // that shortcut is a projection (1x1 convolution + batch normalisation)
-  size_t psub, pz, pstats; // its input pixels [K][rows][skip_C] (later: their gradient), its
-                           // convolution output [K][rows][Cout] (later: that output's gradient), its statistics
+  size_t psub, pz, pstats; // gradient of its input pixels [K][rows][skip_C], its convolution
+                           // output [K][rows][Cout] (later: that output's gradient), its statistics
   int64_t rows;        // B H W: rows of the unfolded image and of the layer's output
   int ldc;             // pitch of the unfolded image, 9 Cin rounded up to 8
-  // The GEMM kernels can read an unfolded image straight from the image when its channel
-  // count is a multiple of 32: `direct_in` for the layer's input (forward and dW), `direct_dx`
-  // for its output gradient (dX, with the mirrored filters `wt`).  Otherwise the unfolded
-  // image (`col`) resp. its gradient (the shared `dcol`) is stored.
+  // Which products serve the layer.  `fast`: the bf16 matrix units on plane tensors
+  // (kernels_conv_gemm.hip); otherwise the fp32-storage GEMM (small layers, plane_products_pay).
+  // Both can read an unfolded image straight from the image: `direct_in` for the layer's input
+  // (forward and dW), `direct_dx` for its output gradient (dX, with the mirrored filters, `wt` for
+  // the fp32-storage GEMM).  Otherwise the unfolded image (`col`, planes if fast) resp. its gradient
+  // (the shared `dcol`) is stored.
   // `first`: layer 0 with 1..3 input channels runs its forward pass and its weight gradient
   // in kernels of their own (no unfolded image at all).
-  bool direct_in, direct_dx, first;
+  bool fast, direct_in, direct_dx, first;
   size_t first_partial;   // scratch of the first layer's weight gradient
   bool bn;                // batch-normalised: `z` keeps the convolution's output, `stats` the
   size_t z, stats;        // per-channel mean and 1/sqrt(var + eps) of each replica
   size_t col, out, pooled, dout, dpooled, wt;   // workspace offsets ([K] contiguous replicas each)
+  // plane tensors (kernels_conv_gemm.hip): the image this layer reads, kept from the forward pass
+  // for the weight gradient; `plane_elems` elements per plane (all replicas).  Present if the layer
+  // itself (fast and direct_in) or the fast projection of the block it opens reads it.
+  bool planes;
+  bool planes_above;   // they are written by the kernel that writes the image (normalisation or pool of the layer below)
+  size_t xp;
+  int64_t plane_elems;
+  // filters as the plane products read them, elements into a plane of lo.wp: forward and dX, the
+  // same of the projection
+  int64_t wf, wx, pwf, pwx;
+  int in_H, in_W;      // that image
 };
 
 struct Layout {
@@ -161,6 +174,13 @@ struct Layout {
   bool preact = false;         // residual blocks sum un-normalised convolution outputs (wide residual networks)
   std::vector<ConvLayer> conv;
   size_t dcol = 0;             // gradient of an unfolded image (largest layer that needs one)
+  int np = 0;                  // planes per plane tensor: 1 with bf16 products, 3 (exact split) without
+  size_t wp = 0, dzp = 0;      // planes of all filters, and of one layer's output gradient (reused layer by layer)
+  int64_t wp_elems = 0, dzp_elems = 0;   // per plane
+  std::vector<FilterBank> banks;         // the filters in wp; their device copy and the workgroups they take
+  size_t banks_at = 0;
+  int bank_blocks = 0;
+  size_t nonfinite = 0;        // flag the plane writers raise on an infinite value
   size_t gram1 = 0, gram2 = 0; // bf16 dense model: Gram matrices [K][B][ldg] of a layer's dZ and of its input
   size_t restart = 0;         // K marks: which iterate sums read as zero / start afresh (launch_center)
   int ldg = 0;
@@ -313,6 +333,24 @@ int gram_pieces(int K, int B, int kd) {
   return (int)std::max<int64_t>(1, std::min<int64_t>({want, deep, 8}));
 }
 
+// Whether the plane products serve a convolution (rows: output pixels per replica).  They take a
+// launch a pass for all filters, and planes of every image and gradient, and pay from about 1e8
+// multiply-adds over all replicas, 3e8 with more than 32 channels (fewer, larger workgroups).
+// Time of a step of three equal layers, as a fraction of the fp32-storage GEMM's: 32 channels 0.98
+// at 9e6, 0.90 at 1.5e8, 0.74 at 2.4e9; 16 channels 0.93 at 2e7, 0.60 at 6e8; 64 channels 1.13 at
+// 7.5e7, 0.98 at 6e8; 128 channels 0.87 at 1.2e9 (fp32 arithmetic; with bf16 products 1.0, 0.94, 0.78;
+// 0.92, 0.59; 1.02, 0.90; 0.91).  One plane leaves little to gain on few, small images: 256 channels on
+// 2048 pixels 0.95 in fp32, 1.07 with bf16 products, which therefore want 4096.  Channel counts that
+// need a stored unfolded image move nine times the image either way: with three planes that stays
+// slower at every size (24 channels: 1.06 to 1.16), with one plane it pays from 3e8 (0.88).
+bool plane_products_pay(int np, int K, int64_t rows, int Cin, int Cout) {
+  auto fits = [](int C) { return C % 32 == 0 || C == 8 || C == 16; };
+  const double macs = (double)K * (double)rows * 9.0 * Cin * Cout;
+  if (np == 1 && K * rows < 4096) return false;
+  if (fits(Cin) && fits(Cout)) return macs >= (std::max(Cin, Cout) <= 32 ? 1e8 : 3e8);
+  return np == 1 && macs >= 3e8;
+}
+
 void build_layout(const lsam_config& c, Layout& lo) {
   lo.K = c.K;
   lo.L = c.n_layers;
@@ -320,6 +358,7 @@ void build_layout(const lsam_config& c, Layout& lo) {
   lo.B = lo.raw ? 0 : c.batch;
   lo.bf16 = !lo.raw && c.gemm_dtype == LSAM_GEMM_BF16 && c.n_conv == 0;
   lo.bf16_math = !lo.raw && c.gemm_dtype == LSAM_GEMM_BF16 && c.n_conv > 0;
+  lo.np = lo.bf16_math ? 1 : 3;
   int64_t off = 0, flat = 0;
   if (lo.raw) {
     lo.d = c.d_raw;
@@ -467,15 +506,45 @@ void build_layout(const lsam_config& c, Layout& lo) {
     for (int l = 0; l < lo.n_conv; ++l) {
       ConvLayer& cv = lo.conv[l];
       const size_t full = (size_t)lo.K * cv.rows * cv.Cout * 4;
-      const bool small = cv.rows < (1 << 24);      // pixel indices exact in fp32
-      // the kernels that unfold on the fly, and the first layer's own, know stride 1 only
-      cv.direct_in = small && cv.Cin % 32 == 0 && cv.stride == 1;
-      cv.direct_dx = small && l > 0 && cv.Cout % 32 == 0 && cv.stride == 1;
+      const bool small = cv.rows < (1 << 24);      // (first-layer kernels: pixel indices exact in fp32)
+      cv.fast = plane_products_pay(lo.np, lo.K, cv.rows, cv.Cin, cv.Cout);
+      // unfolding by address: whole taps or parts of one tap make up a 32-deep k-step; the
+      // fp32-storage GEMM knows stride 1 and parts of taps only
+      auto fits = [&](int C) { return C % 32 == 0 || (cv.fast && (C == 8 || C == 16)); };
+      cv.direct_in = small && fits(cv.Cin) && (cv.fast || cv.stride == 1);
+      cv.direct_dx = small && l > 0 && fits(cv.Cout) && cv.stride == 1;
       cv.first = l == 0 && cv.stride == 1 && first_conv_fits(cv.Cin, cv.Cout, cv.rows);
       if (cv.first)
         cv.first_partial = take(cur, (size_t)lo.K * first_conv_chunks(cv.rows) * cv.Cout * 32 * 4);
-      else if (!cv.direct_in) cv.col = take(cur, (size_t)lo.K * cv.rows * cv.ldc * 4);
-      if (cv.direct_dx) cv.wt = take(cur, (size_t)lo.K * cv.Cin * 9 * cv.Cout * 4);
+      else if (!cv.direct_in) cv.col = take(cur, (size_t)lo.K * cv.rows * cv.ldc * (cv.fast ? 2 * lo.np : 4));
+      if (cv.direct_dx && !cv.fast) cv.wt = take(cur, (size_t)lo.K * cv.Cin * 9 * cv.Cout * 4);
+      cv.in_H = cv.H * cv.stride; cv.in_W = cv.W * cv.stride;
+      cv.planes = (cv.fast && cv.direct_in && !cv.first) || (l + 1 < lo.n_conv && lo.conv[l + 1].proj &&
+                  plane_products_pay(lo.np, lo.K, lo.conv[l + 1].rows, lo.conv[l + 1].Cin, lo.conv[l + 1].Cout));
+      cv.planes_above = cv.planes && l > 0 && (lo.conv[l - 1].pool || lo.conv[l - 1].bn);
+      if (cv.planes) {
+        cv.plane_elems = (int64_t)lo.K * lo.B * cv.in_H * cv.in_W * cv.Cin;
+        cv.xp = take(cur, (size_t)cv.plane_elems * 2 * lo.np);
+      }
+      if (cv.fast) {
+        const Layer& ly = lo.layers[l];
+        auto bank = [&](int64_t src, int rows, int cols, int ldw, int taps) {
+          FilterBank f{src, lo.wp_elems, rows, cols, ldw, 0, taps, lo.bank_blocks};
+          f.ldp = (int)round_up(taps ? taps * rows : cols, 32);
+          lo.wp_elems += (int64_t)lo.K * (taps ? cols : rows) * f.ldp;
+          lo.bank_blocks += filter_bank_blocks(f);
+          lo.banks.push_back(f);
+          return f.dst;
+        };
+        // (a stored unfolded image has the filters' row pitch, zeros in the padding of both)
+        if (!cv.first) cv.wf = bank(ly.w_off, cv.Cout, cv.direct_in ? ly.in : ly.ldw, ly.ldw, 0);
+        if (l > 0) cv.wx = cv.direct_dx ? bank(ly.w_off, cv.Cout, cv.Cin, ly.ldw, 9) : bank(ly.w_off, cv.Cout, cv.ldc, ly.ldw, 1);
+        if (cv.proj) {
+          cv.pwf = bank(ly.pw_off, cv.Cout, ly.proj_in, ly.proj_in, 0);
+          cv.pwx = bank(ly.pw_off, cv.Cout, ly.proj_in, ly.proj_in, 1);
+        }
+        lo.dzp_elems = std::max(lo.dzp_elems, (int64_t)lo.K * cv.rows * cv.Cout);
+      }
       cv.out = take(cur, full);
       cv.dout = take(cur, full);
       cv.bn = lo.layers[l].bn;
@@ -495,6 +564,12 @@ void build_layout(const lsam_config& c, Layout& lo) {
       if (l > 0 && !cv.direct_dx) dcol_bytes = std::max(dcol_bytes, (size_t)lo.K * cv.rows * cv.ldc * 4);
     }
     if (dcol_bytes) lo.dcol = take(cur, dcol_bytes);
+    if (lo.wp_elems) {
+      lo.wp = take(cur, (size_t)lo.wp_elems * 2 * lo.np);
+      lo.banks_at = take(cur, lo.banks.size() * sizeof(FilterBank));
+    }
+    if (lo.dzp_elems) lo.dzp = take(cur, (size_t)lo.dzp_elems * 2 * lo.np);
+    if (lo.n_conv > 0) lo.nonfinite = take(cur, 4);
     if (lo.n_conv > 0) {
       size_t most = 0;
       for (const ConvLayer& cv : lo.conv)
@@ -529,27 +604,48 @@ void build_layout(const lsam_config& c, Layout& lo) {
       d.batch = lo.K; d.in_bf16 = lo.bf16; d.bf16_math = lo.bf16_math;
       const ConvLayer* cv = l < lo.n_conv ? &lo.conv[l] : nullptr;
       const int rows = cv ? (int)cv->rows : lo.B;
-      d.M = rows; d.N = ly.out; d.Kd = ly.in; d.a_kmajor = 1; d.b_kmajor = 1;     // forward
-      d.out_bf16 = lo.bf16 && l + 1 < lo.L;
-      d.unfold = cv && cv->direct_in ? 1 : 0;
-      need = std::max(need, gemm_splitk_bytes(d));
-      d.M = rows; d.N = ly.in; d.Kd = ly.out; d.a_kmajor = 1; d.b_kmajor = 0;     // dX
-      d.out_bf16 = lo.bf16;
-      d.unfold = 0;
-      if (cv && cv->direct_dx) { d.N = cv->Cin; d.Kd = 9 * cv->Cout; d.b_kmajor = 1; d.unfold = 1; }
-      if (l > 0) need = std::max(need, gemm_splitk_bytes(d));
-      d.M = ly.out; d.N = ly.in; d.Kd = rows; d.a_kmajor = 0; d.b_kmajor = 0;     // dW
-      d.out_bf16 = 0;
-      d.unfold = cv && cv->direct_in ? 2 : 0;
-      need = std::max(need, gemm_splitk_bytes(d));
-      if (ly.proj) {       // the projection's three products
+      if (!cv || !cv->fast) {
+        d.M = rows; d.N = ly.out; d.Kd = ly.in; d.a_kmajor = 1; d.b_kmajor = 1;     // forward
+        d.unfold = cv && cv->direct_in ? 1 : 0;
+        need = std::max(need, gemm_splitk_bytes(d));
+        d.M = rows; d.N = ly.in; d.Kd = ly.out; d.a_kmajor = 1; d.b_kmajor = 0;     // dX
         d.unfold = 0;
-        d.M = rows; d.N = ly.out; d.Kd = ly.proj_in; d.a_kmajor = 1; d.b_kmajor = 1;
+        if (cv && cv->direct_dx) { d.N = cv->Cin; d.Kd = 9 * cv->Cout; d.b_kmajor = 1; d.unfold = 1; }
+        if (l > 0) need = std::max(need, gemm_splitk_bytes(d));
+        d.M = ly.out; d.N = ly.in; d.Kd = rows; d.a_kmajor = 0; d.b_kmajor = 0;     // dW
+        d.unfold = cv && cv->direct_in ? 2 : 0;
         need = std::max(need, gemm_splitk_bytes(d));
-        d.M = rows; d.N = ly.proj_in; d.Kd = ly.out; d.a_kmajor = 1; d.b_kmajor = 0;
-        need = std::max(need, gemm_splitk_bytes(d));
-        d.M = ly.out; d.N = ly.proj_in; d.Kd = rows; d.a_kmajor = 0; d.b_kmajor = 0;
-        need = std::max(need, gemm_splitk_bytes(d));
+        if (ly.proj) {       // the projection's three products
+          d.unfold = 0;
+          d.M = rows; d.N = ly.out; d.Kd = ly.proj_in; d.a_kmajor = 1; d.b_kmajor = 1;
+          need = std::max(need, gemm_splitk_bytes(d));
+          d.M = rows; d.N = ly.proj_in; d.Kd = ly.out; d.a_kmajor = 1; d.b_kmajor = 0;
+          need = std::max(need, gemm_splitk_bytes(d));
+          d.M = ly.out; d.N = ly.proj_in; d.Kd = rows; d.a_kmajor = 0; d.b_kmajor = 0;
+          need = std::max(need, gemm_splitk_bytes(d));
+        }
+        continue;
+      }
+      auto planes = [&](int wgrad, int C, int stride, int side, int M, int N, int Kd) {
+        ConvGemmDesc q{};
+        q.np = lo.np; q.wgrad = wgrad; q.batch = lo.K;
+        q.image = PlaneImage{nullptr, 0, 0, C, cv->H, cv->W, cv->H * stride, cv->W * stride, stride, side, side, 0, 0};
+        q.M = M; q.N = N; q.Kd = Kd;
+        need = std::max(need, conv_gemm_splitk_bytes(q));
+      };
+      if (cv->direct_in) {
+        planes(0, cv->Cin, cv->stride, 3, rows, ly.out, ly.in);
+        planes(1, cv->Cin, cv->stride, 3, ly.out, ly.in, rows);
+      } else if (!cv->first) {
+        planes(0, cv->ldc, 1, 1, rows, ly.out, cv->ldc);
+        planes(1, cv->ldc, 1, 1, ly.out, cv->ldc, rows);
+      }
+      if (cv->direct_dx) planes(0, cv->Cout, 1, 3, rows, cv->Cin, 9 * cv->Cout);
+      else if (l > 0) planes(0, cv->Cout, 1, 1, rows, cv->ldc, cv->Cout);
+      if (ly.proj) {           // the projection's three products
+        planes(0, ly.proj_in, cv->skip_step, 1, rows, ly.out, ly.proj_in);
+        planes(0, ly.out, 1, 1, rows, ly.proj_in, ly.out);
+        planes(1, ly.proj_in, cv->skip_step, 1, ly.out, ly.proj_in, rows);
       }
     }
     lo.splitk_bytes = need;
@@ -682,16 +778,85 @@ void split(const lsam_ctx* c, GemmDesc& d) {
   d.bf16_math = c->lo.bf16_math;     // every GEMM of a step shares the arithmetic mode, too
 }
 
+// ---- plane products (kernels_conv_gemm.hip) ----
+// The image layer `cv` reads as the operand of its 3x3 convolution ...
+PlaneImage layer_image(const lsam_ctx* c, const ConvLayer& cv) {
+  return PlaneImage{c->at<uint16_t>(cv.xp), cv.plane_elems / c->lo.K, cv.plane_elems, cv.Cin, cv.H, cv.W, cv.in_H, cv.in_W,
+                    cv.stride, 3, 3, -1, -1};
+}
+// ... or, where the unfolded image is stored, that image under a single tap;
+PlaneImage stored_image(const lsam_ctx* c, const ConvLayer& cv) {
+  return PlaneImage{c->at<uint16_t>(cv.col), cv.rows * cv.ldc, (int64_t)c->lo.K * cv.rows * cv.ldc, cv.ldc, cv.H, cv.W,
+                    cv.H, cv.W, 1, 1, 1, 0, 0};
+}
+// ... and, as the input of the block that convolution `top` (one above) closes, of its projection:
+// every skip_step-th pixel.
+PlaneImage projection_image(const lsam_ctx* c, const ConvLayer& below, const ConvLayer& top) {
+  return PlaneImage{c->at<uint16_t>(below.xp), below.plane_elems / c->lo.K, below.plane_elems, below.Cin, top.H, top.W,
+                    below.in_H, below.in_W, top.skip_step, 1, 1, 0, 0};
+}
+// A layer's output gradient (the planes in dzp) as a stride-1 image under `taps` = 3 x 3 or 1 x 1 taps.
+PlaneImage gradient_image(const lsam_ctx* c, const ConvLayer& cv, int side) {
+  return PlaneImage{c->at<uint16_t>(c->lo.dzp), cv.rows * cv.Cout, c->lo.dzp_elems, cv.Cout, cv.H, cv.W, cv.H, cv.W, 1,
+                    side, side, side == 3 ? -1 : 0, side == 3 ? -1 : 0};
+}
+// `filters`: where in wp the launch's filters lie (unused for a weight gradient).
+ConvGemmDesc plane_desc(const lsam_ctx* c, const PlaneImage& im, int wgrad, int64_t filters, int M, int N, int Kd) {
+  const Layout& lo = c->lo;
+  ConvGemmDesc d{};
+  d.np = lo.np; d.wgrad = wgrad; d.image = im;
+  d.M = M; d.N = N; d.Kd = Kd; d.batch = lo.K;
+  d.epilogue = EPI_PLAIN;
+  d.splitk_ws = lo.splitk_bytes ? c->at<float>(lo.splitk) : nullptr;
+  d.splitk_bytes = lo.splitk_bytes;
+  d.nonfinite = c->at<int>(lo.nonfinite);
+  if (wgrad) {     // contraction with the output gradient in dzp
+    d.other = c->at<uint16_t>(lo.dzp);
+    d.other_stride = (int64_t)Kd * M; d.other_plane = lo.dzp_elems; d.ld = M;
+  } else {         // filters in wp, rows padded to whole k-steps
+    d.other = c->at<uint16_t>(lo.wp) + filters;
+    d.ld = (int)round_up(Kd, 32);
+    d.other_stride = (int64_t)N * d.ld; d.other_plane = lo.wp_elems;
+  }
+  return d;
+}
+int split_gradient(const lsam_ctx* c, const float* dz, const ConvLayer& cv) {
+  const Layout& lo = c->lo;
+  return launch_split_planes(dz, c->at<uint16_t>(lo.dzp), lo.np, lo.dzp_elems, (int64_t)lo.K * cv.rows * cv.Cout,
+                             c->at<int>(lo.nonfinite), c->stream);
+}
+
+// The planes of convolution l's input, for the kernel that writes that image.
+PlaneOut input_planes(const lsam_ctx* c, int l) {
+  const Layout& lo = c->lo;
+  PlaneOut o;
+  if (l < lo.n_conv && lo.conv[l].planes_above) {
+    const ConvLayer& cv = lo.conv[l];
+    o.p = c->at<uint16_t>(cv.xp); o.np = lo.np; o.plane = cv.plane_elems; o.nonfinite = c->at<int>(lo.nonfinite);
+  }
+  return o;
+}
+
 // Forward pass of the convolution layers: unfold, GEMM with bias + ReLU, pool.  `params`: x or
 // the perturbed copy (fp32).  The result is the dense layers' input, lo.act[n_conv].
 int conv_forward(lsam_ctx* c, const float* X, const float* params) {
   const Layout& lo = c->lo;
   hipStream_t s = c->stream;
   const float* in = X;
+  if (!lo.banks.empty()) {
+    LaunchTimer t(c, KC_MISC);
+    if (launch_filters(params, lo.d_pad, c->at<FilterBank>(lo.banks_at), (int)lo.banks.size(), lo.bank_blocks,
+                       c->at<uint16_t>(lo.wp), lo.np, lo.wp_elems, lo.K, c->at<int>(lo.nonfinite), s) != 0)
+      return fail(LSAM_EINVAL, "planes of the filters rejected");
+  }
   for (int l = 0; l < lo.n_conv; ++l) {
     const ConvLayer& cv = lo.conv[l];
     const Layer& ly = lo.layers[l];
-    float* col = cv.direct_in ? nullptr : c->at<float>(cv.col);
+    if (cv.planes && !cv.planes_above) {
+      LaunchTimer t(c, KC_UNFOLD);
+      if (launch_split_planes(in, c->at<uint16_t>(cv.xp), lo.np, cv.plane_elems, cv.plane_elems, c->at<int>(lo.nonfinite), s) != 0)
+        return fail(LSAM_EINVAL, "planes of the input of convolution %d rejected", l);
+    }
     if (cv.first) {
       LaunchTimer t(c, KC_CONV_FIRST);
       if (launch_first_conv_forward(in, params, lo.d_pad, ly.w_off, ly.b_off, ly.ldw,
@@ -701,13 +866,24 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
         return fail(LSAM_EINVAL, "first convolution rejected");
     } else if (!cv.direct_in) {
       LaunchTimer t(c, KC_UNFOLD);
-      if (launch_unfold3x3(in, cv.rows * cv.stride * cv.stride * cv.Cin, col, cv.rows * cv.ldc, cv.ldc,
-                           lo.K, lo.B, cv.H, cv.W, cv.Cin, cv.stride, s) != 0)
+      if (launch_unfold3x3(in, cv.rows * cv.stride * cv.stride * cv.Cin, c->at<char>(cv.col), cv.fast ? lo.np : 0,
+                           (int64_t)lo.K * cv.rows * cv.ldc, cv.ldc, lo.K, lo.B, cv.H, cv.W, cv.Cin, cv.stride,
+                           c->at<int>(lo.nonfinite), s) != 0)
         return fail(LSAM_EINVAL, "unfold of convolution %d rejected", l);
     }
-    if (!cv.first) {
+    if (!cv.first && cv.fast) {
+      // filters of ldw columns: 9 C_in, and zeros up to the unfolded image's pitch where that is stored
+      LaunchTimer t(c, KC_GEMM_FWD);
+      const int cols = cv.direct_in ? ly.in : ly.ldw;
+      ConvGemmDesc d = plane_desc(c, cv.direct_in ? layer_image(c, cv) : stored_image(c, cv), 0, cv.wf, (int)cv.rows, cv.Cout, cols);
+      d.C = c->at<float>(cv.bn ? cv.z : cv.out); d.strideC = cv.rows * cv.Cout; d.ldC = cv.Cout;
+      d.epilogue = cv.bn ? EPI_BIAS : EPI_BIAS_RELU;
+      d.bias = params + ly.b_off; d.strideBias = lo.d_pad;
+      if (launch_conv_gemm(d, s) != 0)
+        return fail(LSAM_EINVAL, "forward product of convolution %d rejected", l);
+    } else if (!cv.first) {
       GemmDesc d{};
-      d.A = col; d.strideA = cv.rows * cv.ldc; d.ldA = cv.ldc; d.a_kmajor = 1;
+      d.A = c->at<float>(cv.col); d.strideA = cv.rows * cv.ldc; d.ldA = cv.ldc; d.a_kmajor = 1;
       if (cv.direct_in) {
         d.A = in; d.strideA = cv.rows * cv.Cin; d.ldA = cv.Cin;
         d.unfold = 1; d.unfold_C = cv.Cin; d.unfold_H = cv.H; d.unfold_W = cv.W;
@@ -724,25 +900,35 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
     if (cv.proj) {
       // projection shortcut: the block input's pixels (every second one if the block halved
       // the image) through a 1x1 convolution, then that output's own statistics
-      const ConvLayer& src = lo.conv[l - 2];
-      const float* sub = c->at<float>(src.out);
-      if (cv.skip_step == 2) {
-        LaunchTimer t(c, KC_UNFOLD);
-        if (launch_subsample2(sub, c->at<float>(cv.psub), (int64_t)lo.K * lo.B, cv.H, cv.W, cv.skip_C, s) != 0)
-          return fail(LSAM_EINVAL, "projection of convolution %d: gather rejected", l);
-        sub = c->at<float>(cv.psub);
-      }
-      GemmDesc d{};
-      d.A = sub; d.strideA = cv.rows * cv.skip_C; d.ldA = cv.skip_C; d.a_kmajor = 1;
-      d.B = params + ly.pw_off; d.strideB = lo.d_pad; d.ldB = ly.proj_in; d.b_kmajor = 1;
-      d.C = c->at<float>(cv.pz); d.strideC = cv.rows * cv.Cout; d.ldC = cv.Cout;
-      d.M = (int)cv.rows; d.N = cv.Cout; d.Kd = ly.proj_in; d.batch = lo.K;
-      d.epilogue = EPI_BIAS;
-      d.bias = params + ly.pb_off; d.strideBias = lo.d_pad;
-      split(c, d);
-      {
+      if (cv.fast) {
         LaunchTimer t(c, KC_GEMM_FWD);
-        if (launch_gemm(d, s) != 0) return fail(LSAM_EINVAL, "projection of convolution %d rejected", l);
+        ConvGemmDesc d = plane_desc(c, projection_image(c, lo.conv[l - 1], cv), 0, cv.pwf, (int)cv.rows, cv.Cout, ly.proj_in);
+        d.C = c->at<float>(cv.pz); d.strideC = cv.rows * cv.Cout; d.ldC = cv.Cout;
+        d.epilogue = EPI_BIAS;
+        d.bias = params + ly.pb_off; d.strideBias = lo.d_pad;
+        if (launch_conv_gemm(d, s) != 0)
+          return fail(LSAM_EINVAL, "projection of convolution %d rejected", l);
+      } else {
+        const ConvLayer& src = lo.conv[l - 2];
+        const float* sub = c->at<float>(src.out);
+        if (cv.skip_step == 2) {
+          LaunchTimer t(c, KC_UNFOLD);
+          if (launch_subsample2(sub, c->at<float>(cv.psub), (int64_t)lo.K * lo.B, cv.H, cv.W, cv.skip_C, s) != 0)
+            return fail(LSAM_EINVAL, "projection of convolution %d: gather rejected", l);
+          sub = c->at<float>(cv.psub);
+        }
+        GemmDesc d{};
+        d.A = sub; d.strideA = cv.rows * cv.skip_C; d.ldA = cv.skip_C; d.a_kmajor = 1;
+        d.B = params + ly.pw_off; d.strideB = lo.d_pad; d.ldB = ly.proj_in; d.b_kmajor = 1;
+        d.C = c->at<float>(cv.pz); d.strideC = cv.rows * cv.Cout; d.ldC = cv.Cout;
+        d.M = (int)cv.rows; d.N = cv.Cout; d.Kd = ly.proj_in; d.batch = lo.K;
+        d.epilogue = EPI_BIAS;
+        d.bias = params + ly.pb_off; d.strideBias = lo.d_pad;
+        split(c, d);
+        {
+          LaunchTimer t(c, KC_GEMM_FWD);
+          if (launch_gemm(d, s) != 0) return fail(LSAM_EINVAL, "projection of convolution %d rejected", l);
+        }
       }
       if (lo.preact) {
         // the bare projection joins the convolution's output in front of the normalisation
@@ -777,13 +963,15 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
       }
       if (launch_bn_forward(c->at<float>(cv.z), c->at<float>(lo.colsum), c->at<float>(cv.stats), params,
                             lo.d_pad, ly.gam_off, ly.bet_off, c->at<float>(cv.out), lo.K, cv.rows,
-                            cv.Cout, c->cfg.bn_eps, post_sum ? &sc : nullptr, s) != 0)
+                            cv.Cout, c->cfg.bn_eps, post_sum ? &sc : nullptr,
+                            cv.pool ? PlaneOut{} : input_planes(c, l + 1), s) != 0)
         return fail(LSAM_EINVAL, "batch normalisation of convolution %d rejected", l);
     }
     in = c->at<float>(cv.out);
     if (cv.pool) {
       LaunchTimer t(c, KC_POOL);
-      if (launch_maxpool2(in, c->at<float>(cv.pooled), (int64_t)lo.K * lo.B, cv.H, cv.W, cv.Cout, s) != 0)
+      if (launch_maxpool2(in, c->at<float>(cv.pooled), (int64_t)lo.K * lo.B, cv.H, cv.W, cv.Cout,
+                          input_planes(c, l + 1), s) != 0)
         return fail(LSAM_EINVAL, "pool of convolution %d rejected", l);
       in = c->at<float>(cv.pooled);
     }
@@ -830,6 +1018,25 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
                                    (int64_t)lo.K * lo.B, cv.H, cv.W, cv.Cout, s) != 0)
         return fail(LSAM_EINVAL, "pool backward of convolution %d rejected", l);
     }
+    // A block's closing convolution keeps dY: it is also the gradient of the shortcut, added
+    // to the block input's gradient further down.  Its dZ goes where Z was (Z is not needed again).
+    float* dz = (cv.bn && cv.skip && !lo.preact) ? c->at<float>(cv.z) : dout;
+    // In a pre-activation network this convolution's sum may be the identity shortcut of the block
+    // above: that block's sum hands its gradient (complete since its own backward pass) down unchanged
+    const float* handed = lo.preact && l + 2 < lo.n_conv && lo.conv[l + 2].skip && !lo.conv[l + 2].proj
+                              ? c->at<float>(lo.conv[l + 2].dout) : nullptr;
+    PlaneOut po;                 // fast layers: dZ as planes, for dW and dX
+    if (cv.fast && !cv.first) {
+      po.p = c->at<uint16_t>(lo.dzp); po.np = lo.np; po.plane = lo.dzp_elems; po.nonfinite = c->at<int>(lo.nonfinite);
+    }
+    auto own_gradient = [&]() {
+      // nothing reads the floats of a fast layer's dZ but the convolution its sum is handed down to
+      const bool floats = !po.p || (lo.preact && cv.skip && !cv.proj);
+      launch_bn_backward_apply(c->at<float>(cv.z), dout, floats ? dz : nullptr, c->at<float>(cv.stats), params, g,
+                               lo.d_pad, ly.gam_off, ly.bet_off, lo.K, cv.rows, cv.Cout, cv.fast ? handed : nullptr, po, s);
+    };
+    // The projection of a post-activation block goes first: its planes take the same place
+    const bool own_last = cv.proj && !lo.preact;
     if (cv.bn) {
       // dout holds the gradient behind the ReLU; turn it into the gradient of the convolution's
       // output and leave dgamma, dbeta in g
@@ -851,11 +1058,7 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
                                 cv.Cout, ssq ? ssq + *slots : nullptr, lo.nblk, s);
         if (ssq) *slots += used;
       }
-      // A block's closing convolution keeps dY: it is also the gradient of the shortcut, added
-      // to the block input's gradient further down.  Its dZ goes where Z was (Z is not needed again).
-      float* dz = (cv.skip && !lo.preact) ? c->at<float>(cv.z) : dout;
-      launch_bn_backward_apply(c->at<float>(cv.z), dout, dz, c->at<float>(cv.stats), params, g, lo.d_pad,
-                               ly.gam_off, ly.bet_off, lo.K, cv.rows, cv.Cout, s);
+      if (!own_last) own_gradient();
       if (cv.proj && !lo.preact) {
         // the same gradient dY enters the projection's normalisation: dgamma_p, dbeta_p, then
         // the gradient of the 1x1 convolution's output, which takes that output's place
@@ -869,49 +1072,71 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
         used = launch_bias_grad(part + cv.Cout, 2 * cv.Cout, 0, g + ly.pbet_off, lo.d_pad, lo.K, pchunks,
                                 cv.Cout, ssq ? ssq + *slots : nullptr, lo.nblk, s);
         if (ssq) *slots += used;
-        launch_bn_backward_apply(pz, dout, pz, c->at<float>(cv.pstats), params, g, lo.d_pad, ly.pgam_off,
-                                 ly.pbet_off, lo.K, cv.rows, cv.Cout, s);
+        launch_bn_backward_apply(pz, dout, po.p ? nullptr : pz, c->at<float>(cv.pstats), params, g, lo.d_pad, ly.pgam_off,
+                                 ly.pbet_off, lo.K, cv.rows, cv.Cout, nullptr, po, s);
       }
-      dout = dz;
     }
-    if (lo.preact && l + 2 < lo.n_conv && lo.conv[l + 2].skip && !lo.conv[l + 2].proj) {
-      // this convolution's sum is the identity shortcut of the block above: that block's sum
-      // hands its gradient (complete since its own backward pass) down unchanged
+    if (handed && !cv.fast) {
       LaunchTimer t(c, KC_POOL);
-      if (launch_add_into(dout, c->at<float>(lo.conv[l + 2].dout), (int64_t)lo.K * cv.rows * cv.Cout, s) != 0)
+      if (launch_add_into(dz, handed, (int64_t)lo.K * cv.rows * cv.Cout, s) != 0)
         return fail(LSAM_EINVAL, "shortcut into convolution %d: sum rejected", l);
     }
     if (cv.proj) {
       // dW_p = dZ_p^T S and dS = dZ_p W_p; dS replaces the gathered pixels and reaches the block
       // input's gradient once the block's opening convolution has written that gradient.  In a
       // pre-activation block the projection's output gradient is the sum's own.
-      const float* dzp = lo.preact ? dout : c->at<float>(cv.pz);
+      const float* dzp = lo.preact ? dz : c->at<float>(cv.pz);
       float* psub = c->at<float>(cv.psub);
-      {
+      if (cv.fast) {
+        {
+          LaunchTimer t(c, KC_GEMM_DW);
+          ConvGemmDesc d = plane_desc(c, projection_image(c, lo.conv[l - 1], cv), 1, 0, cv.Cout, ly.proj_in, (int)cv.rows);
+          d.C = g + ly.pw_off; d.strideC = lo.d_pad; d.ldC = ly.proj_in;
+          if (ssq) { d.sumsq = ssq + *slots; d.sumsq_stride = lo.nblk; }
+          int used = 0;
+          if (launch_conv_gemm(d, s, &used) != 0) return fail(LSAM_EINVAL, "projection of convolution %d: dW rejected", l);
+          if (ssq) *slots += used;
+        }
+        LaunchTimer t(c, KC_GEMM_DX);
+        ConvGemmDesc d = plane_desc(c, gradient_image(c, cv, 1), 0, cv.pwx, (int)cv.rows, ly.proj_in, cv.Cout);
+        d.C = psub; d.strideC = cv.rows * cv.skip_C; d.ldC = cv.skip_C;
+        if (launch_conv_gemm(d, s) != 0)
+          return fail(LSAM_EINVAL, "projection of convolution %d: dX rejected", l);
+      } else {
+        {
+          GemmDesc d{};
+          d.A = dzp; d.strideA = cv.rows * cv.Cout; d.ldA = cv.Cout; d.a_kmajor = 0;
+          d.B = cv.skip_step == 2 ? psub : c->at<float>(lo.conv[l - 2].out);
+          d.strideB = cv.rows * cv.skip_C; d.ldB = cv.skip_C; d.b_kmajor = 0;
+          d.C = g + ly.pw_off; d.strideC = lo.d_pad; d.ldC = ly.proj_in;
+          d.M = cv.Cout; d.N = ly.proj_in; d.Kd = (int)cv.rows; d.batch = lo.K;
+          d.epilogue = EPI_PLAIN;
+          split(c, d);
+          if (ssq) { d.sumsq = ssq + *slots; d.sumsq_stride = lo.nblk; }
+          int used = 0;
+          LaunchTimer t(c, KC_GEMM_DW);
+          if (launch_gemm(d, s, &used) != 0) return fail(LSAM_EINVAL, "projection of convolution %d: dW rejected", l);
+          if (ssq) *slots += used;
+        }
         GemmDesc d{};
-        d.A = dzp; d.strideA = cv.rows * cv.Cout; d.ldA = cv.Cout; d.a_kmajor = 0;
-        d.B = cv.skip_step == 2 ? psub : c->at<float>(lo.conv[l - 2].out);
-        d.strideB = cv.rows * cv.skip_C; d.ldB = cv.skip_C; d.b_kmajor = 0;
-        d.C = g + ly.pw_off; d.strideC = lo.d_pad; d.ldC = ly.proj_in;
-        d.M = cv.Cout; d.N = ly.proj_in; d.Kd = (int)cv.rows; d.batch = lo.K;
+        d.A = dzp; d.strideA = cv.rows * cv.Cout; d.ldA = cv.Cout; d.a_kmajor = 1;
+        d.B = params + ly.pw_off; d.strideB = lo.d_pad; d.ldB = ly.proj_in; d.b_kmajor = 0;
+        d.C = psub; d.strideC = cv.rows * cv.skip_C; d.ldC = cv.skip_C;
+        d.M = (int)cv.rows; d.N = ly.proj_in; d.Kd = cv.Cout; d.batch = lo.K;
         d.epilogue = EPI_PLAIN;
         split(c, d);
-        if (ssq) { d.sumsq = ssq + *slots; d.sumsq_stride = lo.nblk; }
-        int used = 0;
-        LaunchTimer t(c, KC_GEMM_DW);
-        if (launch_gemm(d, s, &used) != 0) return fail(LSAM_EINVAL, "projection of convolution %d: dW rejected", l);
-        if (ssq) *slots += used;
+        LaunchTimer t(c, KC_GEMM_DX);
+        if (launch_gemm(d, s) != 0) return fail(LSAM_EINVAL, "projection of convolution %d: dX rejected", l);
       }
-      GemmDesc d{};
-      d.A = dzp; d.strideA = cv.rows * cv.Cout; d.ldA = cv.Cout; d.a_kmajor = 1;
-      d.B = params + ly.pw_off; d.strideB = lo.d_pad; d.ldB = ly.proj_in; d.b_kmajor = 0;
-      d.C = psub; d.strideC = cv.rows * cv.skip_C; d.ldC = cv.skip_C;
-      d.M = (int)cv.rows; d.N = ly.proj_in; d.Kd = cv.Cout; d.batch = lo.K;
-      d.epilogue = EPI_PLAIN;
-      split(c, d);
-      LaunchTimer t(c, KC_GEMM_DX);
-      if (launch_gemm(d, s) != 0) return fail(LSAM_EINVAL, "projection of convolution %d: dX rejected", l);
     }
+    if (own_last) {
+      LaunchTimer t(c, KC_BATCHNORM);
+      own_gradient();
+    } else if (po.p && !cv.bn) {
+      LaunchTimer t(c, KC_UNFOLD);
+      if (split_gradient(c, dout, cv) != 0) return fail(LSAM_EINVAL, "planes of the gradient of convolution %d rejected", l);
+    }
+    dout = dz;
     if (cv.first) {
       LaunchTimer t(c, KC_CONV_FIRST);
       const int used = launch_first_conv_wgrad(X, dout, c->at<float>(cv.first_partial), g, lo.d_pad,
@@ -923,8 +1148,16 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
       if (ssq) *slots += used;
       if (!lo.bf16_math) continue;    // otherwise the bias gradient is still to come, below
     }
-    if (!cv.first)
-    {
+    if (!cv.first && cv.fast) {
+      LaunchTimer t(c, KC_GEMM_DW);
+      ConvGemmDesc d = cv.direct_in ? plane_desc(c, layer_image(c, cv), 1, 0, cv.Cout, ly.in, (int)cv.rows)
+                                    : plane_desc(c, stored_image(c, cv), 1, 0, cv.Cout, ly.ldw, (int)cv.rows);
+      d.C = g + ly.w_off; d.strideC = lo.d_pad; d.ldC = ly.ldw;
+      if (ssq) { d.sumsq = ssq + *slots; d.sumsq_stride = lo.nblk; }
+      int used = 0;
+      if (launch_conv_gemm(d, s, &used) != 0) return fail(LSAM_EINVAL, "dW product of convolution %d rejected", l);
+      if (ssq) *slots += used;
+    } else if (!cv.first) {
       GemmDesc d{};
       d.A = dout; d.strideA = cv.rows * cv.Cout; d.ldA = cv.Cout; d.a_kmajor = 0;
       d.B = c->at<float>(cv.col); d.strideB = cv.rows * cv.ldc; d.ldB = cv.ldc; d.b_kmajor = 0;
@@ -961,29 +1194,48 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
       // into the gradient of the image this layer read (masked by the ReLU output it came
       // from when no pool sits in between; a pool's backward pass applies the mask itself)
       const ConvLayer& below = lo.conv[l - 1];
-      float* wt = c->at<float>(cv.wt);
-      {
-        LaunchTimer t(c, KC_MISC);
-        launch_flip_filters(params + ly.w_off, lo.d_pad, ly.ldw, wt, lo.K, cv.Cout, cv.Cin, s);
+      if (cv.fast) {
+        LaunchTimer t(c, KC_GEMM_DX);
+        ConvGemmDesc d = plane_desc(c, gradient_image(c, cv, 3), 0, cv.wx, (int)cv.rows, cv.Cin, 9 * cv.Cout);
+        d.C = c->at<float>(below.pool ? below.dpooled : below.dout);
+        d.strideC = cv.rows * cv.Cin; d.ldC = cv.Cin;
+        d.epilogue = below.pool ? EPI_PLAIN : EPI_MASK;
+        if (!below.pool) {
+          d.mask = c->at<float>(below.out); d.strideMask = cv.rows * cv.Cin; d.ldMask = cv.Cin;
+        }
+        if (launch_conv_gemm(d, s) != 0)
+          return fail(LSAM_EINVAL, "dX product of convolution %d rejected", l);
+      } else {
+        float* wt = c->at<float>(cv.wt);
+        {
+          LaunchTimer t(c, KC_MISC);
+          launch_flip_filters(params + ly.w_off, lo.d_pad, ly.ldw, wt, lo.K, cv.Cout, cv.Cin, s);
+        }
+        GemmDesc d{};
+        d.A = dout; d.strideA = cv.rows * cv.Cout; d.ldA = cv.Cout; d.a_kmajor = 1;
+        d.unfold = 1; d.unfold_C = cv.Cout; d.unfold_H = cv.H; d.unfold_W = cv.W;
+        d.B = wt; d.strideB = (int64_t)cv.Cin * 9 * cv.Cout; d.ldB = 9 * cv.Cout; d.b_kmajor = 1;
+        d.C = c->at<float>(below.pool ? below.dpooled : below.dout);
+        d.strideC = cv.rows * cv.Cin; d.ldC = cv.Cin;
+        d.M = (int)cv.rows; d.N = cv.Cin; d.Kd = 9 * cv.Cout; d.batch = lo.K;
+        d.epilogue = below.pool ? EPI_PLAIN : EPI_MASK;
+        if (!below.pool) {
+          d.mask = c->at<float>(below.out); d.strideMask = cv.rows * cv.Cin; d.ldMask = cv.Cin;
+        }
+        split(c, d);
+        LaunchTimer t(c, KC_GEMM_DX);
+        if (launch_gemm(d, s) != 0) return fail(LSAM_EINVAL, "dX GEMM of convolution %d rejected", l);
       }
-      GemmDesc d{};
-      d.A = dout; d.strideA = cv.rows * cv.Cout; d.ldA = cv.Cout; d.a_kmajor = 1;
-      d.unfold = 1; d.unfold_C = cv.Cout; d.unfold_H = cv.H; d.unfold_W = cv.W;
-      d.B = wt; d.strideB = (int64_t)cv.Cin * 9 * cv.Cout; d.ldB = 9 * cv.Cout; d.b_kmajor = 1;
-      d.C = c->at<float>(below.pool ? below.dpooled : below.dout);
-      d.strideC = cv.rows * cv.Cin; d.ldC = cv.Cin;
-      d.M = (int)cv.rows; d.N = cv.Cin; d.Kd = 9 * cv.Cout; d.batch = lo.K;
-      d.epilogue = below.pool ? EPI_PLAIN : EPI_MASK;
-      if (!below.pool) {
-        d.mask = c->at<float>(below.out); d.strideMask = cv.rows * cv.Cin; d.ldMask = cv.Cin;
-      }
-      split(c, d);
-      LaunchTimer t(c, KC_GEMM_DX);
-      if (launch_gemm(d, s) != 0) return fail(LSAM_EINVAL, "dX GEMM of convolution %d rejected", l);
     } else if (l > 0) {
       const ConvLayer& below = lo.conv[l - 1];
       float* dcol = c->at<float>(lo.dcol);
-      {
+      if (cv.fast) {
+        LaunchTimer t(c, KC_GEMM_DX);
+        ConvGemmDesc d = plane_desc(c, gradient_image(c, cv, 1), 0, cv.wx, (int)cv.rows, cv.ldc, cv.Cout);
+        d.C = dcol; d.strideC = cv.rows * cv.ldc; d.ldC = cv.ldc;
+        if (launch_conv_gemm(d, s) != 0)
+          return fail(LSAM_EINVAL, "dX product of convolution %d rejected", l);
+      } else {
         GemmDesc d{};
         d.A = dout; d.strideA = cv.rows * cv.Cout; d.ldA = cv.Cout; d.a_kmajor = 1;
         d.B = params + ly.w_off; d.strideB = lo.d_pad; d.ldB = ly.ldw; d.b_kmajor = 0;
@@ -1287,7 +1539,7 @@ int update_tail_first(lsam_ctx* c, const float* g1, int64_t g_stride, int64_t n,
                        c->at<float>(lo.norms), c->at<float>(lo.scale),
                        lo.raw ? nullptr : c->at<float>(lo.loss_rows), lo.B,
                        lo.raw ? nullptr : (loss ? loss : c->at<float>(lo.loss)), s,
-                       c->at<int32_t>(lo.restart));
+                       c->at<int32_t>(lo.restart), lo.n_conv > 0 ? c->at<int>(lo.nonfinite) : nullptr);
   }
   if (c->rho != 0.f && perturb) {
     LaunchTimer t(c, KC_PERTURB);
@@ -1534,6 +1786,9 @@ int lsam_init(const lsam_config* cfg, const float* init_params, int64_t n_init, 
     c->noise.seg = c->at<NoiseSeg>(lo.noise_segs);
     c->noise.n = (int)segs.size();
   }
+  if (!lo.banks.empty() &&
+      (rc = to_device(c, c->at<char>(lo.banks_at), lo.banks.data(), lo.banks.size() * sizeof(FilterBank))) != LSAM_OK)
+    return bail(rc);
   float* x = c->at<float>(lo.x);
   float* y = c->at<float>(lo.y);
   if (n_init == lo.d) {

@@ -1,0 +1,144 @@
+"""The convolution products on plane tensors (one bfloat16 plane, or the exact three-plane split of
+fp32) against the CPU oracle, at the edges of their tiles: patches that touch several images, image
+widths that do and do not divide a tile, ragged tile rows, channel counts with a tap per k-step,
+several taps per k-step and odd remainders, one and several column tiles, split contractions,
+strides, 1x1 projections, and infinite operands.
+
+The layers are large enough for the plane products (3e8 multiply-adds each, 1e8 up to 32 channels).
+Normalisation parameters keep ReLU decisions away from zero, so the network is all but linear and a
+group's gradient cancels below its normalisation (its norm is 1e-2 to 1e-5 of the whole); errors are
+bounded by the whole gradient's norm: an fp32 sum of n = 4e4 terms is good to sqrt(n) 2^-24 = 1.2e-5 of
+the norm of its terms, which lie below the whole (bound 3e-6; the fp32-storage products measure up to
+6e-7).  A tile, row, tap or channel left out changes 1e-2 to 1 of a group.  With bf16 products each
+operand is rounded at the product on both sides, and what differs is where a last fp32 bit decides
+a bfloat16 neighbour: 2^-8 of an operand, on few of them (bound 1e-3)."""
+import numpy as np
+import pytest
+import torch
+
+import workloads
+from paper_2509_03110_amd import lsam
+from util import bn_away_from_zero, oracle_from, rel_l2
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def net(dims, side, batch, K=2, stride=0, skip=0, proj=0, preact=0, bf16=0, pool=0):
+    n = len(dims) - 2
+    return workloads.Workload("planes", K=K, dims=dims, batch=batch, n_conv=n, img_h=side[0], img_w=side[1],
+                              bn_mask=(1 << n) - 1, stride_mask=stride, skip_mask=skip, proj_mask=proj, preact=preact,
+                              pool_mask=pool, global_avg_pool=1, gemm_dtype=bf16, tau=(2,) * K, rho=0.05, lr=0.02,
+                              n_classes=dims[-1], data_seed=77)
+
+
+def groups(w):
+    """(first, last) of every parameter group of the flat vector."""
+    at, out = 0, []
+    for l, (fan_in, fo) in enumerate(w.layer_shapes):
+        sizes = [fan_in * fo, fo]
+        if l < w.n_conv:
+            sizes += [fo, fo]
+            if (w.proj_mask >> l) & 1:
+                sizes += [fo * w.dims[l - 1], fo] + ([] if w.preact else [fo, fo])
+        for n in sizes:
+            out.append((at, at + n))
+            at += n
+    assert at == w.d
+    return out
+
+
+def step_both(w, X=None):
+    init = spread(w)
+    cfg, keep = lsam.config_from_workload(w)
+    g, o = lsam.Lsam(cfg, init, device=DEV, keep=keep), oracle_from(w, init)
+    Xb, lab = workloads.batch(w, 0)
+    X = Xb if X is None else X(Xb)
+    loss = torch.zeros(w.K, device=DEV)
+    g.lsam_step(torch.from_numpy(X).to(DEV), torch.from_numpy(lab).to(DEV), loss)
+    with np.errstate(all="ignore"):
+        ol = o.step(X, lab)
+    return g, o, loss.cpu().numpy(), np.asarray(ol)
+
+
+def spread(w):
+    """Initial parameters whose normalised layers keep three channels of four positive everywhere and
+    the fourth negative everywhere (gamma 0.25, beta +-1.5; shortcuts agree in sign)."""
+    init = bn_away_from_zero(w, workloads.init_params(w))
+    model = oracle_from(w.scaled(K=1, tau=(1,)), init).model
+    ranges = [(b1, b2) for b0, b1, b2 in model.bn_offsets.values()]
+    ranges += [(p[3], p[4]) for p in model.proj_offsets.values()]
+    for lo, hi in ranges:
+        init[lo:hi] = np.where(np.arange(hi - lo) % 4 == 3, -1.5, 1.5)
+    return init
+
+
+NETS = {
+    # a 32-wide image: tiles of whole rows; 20 rows: a tile may end one image and begin the next
+    "32 wide, 64 channels": dict(dims=(3, 64, 64, 64, 10), side=(20, 32), batch=7),
+    # 16-wide: several images per patch, ragged last tile; one 32-channel block, two column tiles
+    "16 wide, 32 to 96 channels": dict(dims=(3, 32, 96, 32, 10), side=(16, 16), batch=23),
+    # widths that do not divide a tile, odd heights
+    "28 wide": dict(dims=(3, 32, 64, 64, 10), side=(7, 28), batch=43),
+    "33 wide": dict(dims=(3, 64, 64, 10), side=(5, 33), batch=27),
+    # images smaller than a tile row: many per patch, or (2 x 2) too many: the ring
+    "4 wide": dict(dims=(3, 64, 128, 64, 10), side=(4, 4), batch=131),
+    "2 wide": dict(dims=(3, 64, 128, 64, 10), side=(2, 2), batch=521),
+    "8 wide, 160 channels": dict(dims=(3, 32, 160, 160, 10), side=(8, 8), batch=53),
+    # four and two taps per k-step, an unfolded first layer of 45 values, small column tiles
+    "8 and 16 channels": dict(dims=(5, 8, 16, 16, 10), side=(32, 32), batch=45),
+    # a channel count that needs a stored unfolded image (taken with one plane only)
+    "24 channels": dict(dims=(3, 24, 64, 24, 10), side=(16, 32), batch=22),
+    # stride 2 forward and dW by address, dX through a stored gradient; both kinds of shortcut
+    "stride and projection": dict(dims=(3, 32, 64, 64, 10), side=(32, 32), batch=33, stride=0b010, skip=0b100, proj=0b100),
+    "parameter-free shortcut": dict(dims=(3, 64, 64, 64, 10), side=(16, 16), batch=17, skip=0b100),
+    # sums in front of the normalisation: a projection and an identity, pools
+    "pre-activation": dict(dims=(3, 32, 64, 64, 64, 64, 10), side=(16, 32), batch=65, stride=0b00010, skip=0b10100,
+                           proj=0b00100, preact=1),
+    "pools": dict(dims=(3, 32, 64, 64, 10), side=(16, 32), batch=129, pool=0b011),
+}
+
+
+@pytest.mark.parametrize("bf16", [0, 1])
+@pytest.mark.parametrize("name", sorted(NETS))
+def test_plane_products_match_oracle(name, bf16):
+    w = net(bf16=bf16, **NETS[name])
+    g, o, loss, ol = step_both(w)
+    assert np.allclose(loss, ol, rtol=2e-2 if bf16 else 1e-5)
+    worst = 0.0
+    for i in range(w.K):
+        g2, ref = g.lsam_get_buffer(lsam.BUF_GRAD, i), o.last_g2[i]
+        worst = max([worst] + [np.linalg.norm(g2[lo:hi] - ref[lo:hi]) / np.linalg.norm(ref) for lo, hi in groups(w)])
+        assert rel_l2(g.lsam_get_params(i), o.get_params(i)) <= (1e-4 if bf16 else 1e-6)
+    print("%s bf16=%d: worst group %.2e" % (name, bf16, worst))
+    assert worst <= (1e-3 if bf16 else 3e-6)
+    g.close()
+
+
+@pytest.mark.parametrize("name", ["32 wide, 64 channels", "8 and 16 channels", "2 wide"])
+def test_infinite_operands(name):
+    """An infinite pixel does not split into planes: launches that meet one form their results from
+    the values, as the sums of products they are.  Without normalisation, with positive weights, it
+    stays infinite (never infinity less infinity) up to the loss; the other replica is computed as
+    ever, and so is the step after the state is restored."""
+    net_of = dict(NETS[name])
+    w = net(**net_of).scaled(bn_mask=0)
+    init = np.abs(workloads.init_params(w)) * 0.1
+    cfg, keep = lsam.config_from_workload(w)
+    g, o = lsam.Lsam(cfg, init, device=DEV, keep=keep), oracle_from(w, init)
+    X, lab = workloads.batch(w, 0)
+    bad = X.copy()
+    bad.reshape(w.K, -1)[0, 0] = np.inf
+    loss = torch.zeros(w.K, device=DEV)
+    ol = o.step(X, lab)
+    for pixels in (bad, X):
+        for i in range(w.K):
+            g.lsam_set_buffer(lsam.BUF_PARAMS, i, init)
+            g.lsam_set_buffer(lsam.BUF_VELOCITY, i, np.zeros(w.d, np.float32))
+        g.lsam_step(torch.from_numpy(pixels).to(DEV), torch.from_numpy(lab).to(DEV), loss)
+        first = 1 if pixels is bad else 0
+        assert np.isfinite(loss.cpu().numpy()).tolist() == [pixels is X, True]
+        for i in range(first, w.K):
+            assert np.isclose(loss[i].item(), ol[i], rtol=1e-5)
+            assert rel_l2(g.lsam_get_buffer(lsam.BUF_GRAD, i), o.last_g2[i]) <= 3e-6
+    g.close()

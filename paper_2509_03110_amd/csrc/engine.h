@@ -249,6 +249,10 @@ void launch_softmax_ce(const float* logits, int ld, const int32_t* labels, void*
 // results to sumsq[k * sumsq_stride + j]; returns the number of such slots per replica.
 int launch_bias_grad(const void* dz, int64_t ld, int dz_bf16, float* db, int64_t strideDb, int K,
                      int B, int N, double* sumsq, int64_t sumsq_stride, hipStream_t s);
+// dgamma and dbeta (at gam_off and bet_off of each replica's gradient) from the chunk sums that
+// launch_bn_backward_partials left; returns the sum-of-squares slots written per replica.
+int launch_norm_param_grads(const float* part, float* grad, int64_t strideGrad, int64_t gam_off, int64_t bet_off,
+                            int K, int chunks, int C, double* sumsq, int64_t sumsq_stride, hipStream_t s);
 
 // Narrow classifier head in fp32 (head_fits: few classes, an input row that fits LDS, a
 // moderate batch): forward of the last layer, loss, dZ and the masked dX in one kernel (A: the
@@ -306,7 +310,7 @@ int launch_first_conv_wgrad(const float* X, const float* dout, float* partial, f
 // 1/sqrt(biased variance + eps); out = relu(gamma Xh + beta), Xh = (Z - mean) stats[1], gamma
 // and beta read from params + k * strideParams at gam_off / bet_off.  `scratch`: 2 * K *
 // bn_chunks(rows, C, K) * C floats.  Backward: launch_bn_backward_partials leaves chunk sums
-// part[k][chunk][0..C) = sum dY Xh and [C..2C) = sum dY (returns the chunk count; launch_bias_grad
+// part[k][chunk][0..C) = sum dY Xh and [C..2C) = sum dY (returns the chunk count; launch_norm_param_grads
 // over them gives dgamma and dbeta); launch_bn_backward_apply then writes
 // dZ = gamma stats[1] (dY - dbeta/rows - Xh dgamma/rows) [+ add] to `dZ`, which may be dY itself or Z
 // (or null: planes only), dgamma and dbeta read from grad + k * strideParams at the same offsets.  -1: shape not supported.

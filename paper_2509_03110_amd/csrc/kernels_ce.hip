@@ -76,16 +76,23 @@ template <> __device__ __forceinline__ float get<__bf16>(const __bf16* p) {
   return static_cast<float>(*p);
 }
 
-// db[k][n] = sum_b dz[k][b][n].  A workgroup owns 64 adjacent columns of one replica; its four
-// wavefronts take every fourth row (lane = column, so a row is one coalesced read), each lane
+// db[k][n] = sum_b dz[k][b][n].  A workgroup owns 64 adjacent columns of one replica; its WAVES
+// wavefronts take every WAVES-th row (lane = column, so a row is one coalesced read), each lane
 // keeps four partial sums, and the partials are combined in a fixed order through LDS.
-template <typename TD>
-__global__ __launch_bounds__(kThreads) void bias_grad_kernel(const TD* __restrict__ dz, long long ld,
+// blockIdx.z: one of several sums side by side, `zin` columns and `zout` results apart.
+// What bounds it is the chain of loads a wavefront waits for; sixteen wavefronts from 256 rows on
+// (512 rows of 64 columns, four replicas: 7.2 us with four wavefronts, 4 us with sixteen; below
+// 256 rows a wavefront has at most one round of loads more and the smaller launch is as fast).
+template <typename TD, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void bias_grad_kernel(const TD* __restrict__ dz, long long ld,
                                                             float* __restrict__ db,
                                                             long long strideDb, int B, int N,
                                                             double* __restrict__ sumsq,
-                                                            long long strideSumsq) {
-  __shared__ float part[kWaves][64];
+                                                            long long strideSumsq, int zin,
+                                                            long long zout) {
+  __shared__ float part[WAVES][64];
+  dz += (long long)blockIdx.z * zin;
+  db += blockIdx.z * zout;
   const int k = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = blockIdx.x * 64 + lane;
@@ -98,27 +105,29 @@ __global__ __launch_bounds__(kThreads) void bias_grad_kernel(const TD* __restric
       return get<TD>(blocked ? base + b32s_offset(b, n, cb) : base + (long long)b * ld);
     };
     int b = wave;
-    for (; b + 3 * kWaves < B; b += 4 * kWaves) {
+    for (; b + 3 * WAVES < B; b += 4 * WAVES) {
       s0 += at(b);
-      s1 += at(b + kWaves);
-      s2 += at(b + 2 * kWaves);
-      s3 += at(b + 3 * kWaves);
+      s1 += at(b + WAVES);
+      s2 += at(b + 2 * WAVES);
+      s3 += at(b + 3 * WAVES);
     }
-    for (; b < B; b += kWaves) s0 += at(b);
+    for (; b < B; b += WAVES) s0 += at(b);
   }
   part[wave][lane] = (s0 + s1) + (s2 + s3);
   __syncthreads();
   if (wave == 0) {
     float r = 0.f;
     if (n < N) {
-      r = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
+#pragma unroll
+      for (int w = 0; w < WAVES; w += 4)
+        r += (part[w][lane] + part[w + 1][lane]) + (part[w + 2][lane] + part[w + 3][lane]);
       db[(long long)k * strideDb + n] = r;
     }
     if (sumsq != nullptr) {        // sum of the squares of this workgroup's 64 results
       double q = (double)r * (double)r;
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) q += __shfl_xor(q, off, 64);
-      if (lane == 0) sumsq[(long long)k * strideSumsq + blockIdx.x] = q;
+      if (lane == 0) sumsq[(long long)k * strideSumsq + blockIdx.z * gridDim.x + blockIdx.x] = q;
     }
   }
 }
@@ -410,6 +419,15 @@ void launch_softmax_ce(const float* logits, int ld, const int32_t* labels, void*
                                                        loss_rows, rows, B, C);
 }
 
+static void run_bias_grad(const float* dz, int64_t ld, float* db, int64_t strideDb, int B, int N, double* sumsq,
+                          int64_t sumsq_stride, int zin, int64_t zout, dim3 grid, hipStream_t s) {
+  if (B >= 256)
+    bias_grad_kernel<float, 16><<<grid, 1024, 0, s>>>(dz, ld, db, strideDb, B, N, sumsq, sumsq_stride, zin, zout);
+  else
+    bias_grad_kernel<float, kWaves><<<grid, kThreads, 0, s>>>(dz, ld, db, strideDb, B, N, sumsq, sumsq_stride, zin,
+                                                              zout);
+}
+
 int launch_bias_grad(const void* dz, int64_t ld, int dz_bf16, float* db, int64_t strideDb, int K,
                      int B, int N, double* sumsq, int64_t sumsq_stride, hipStream_t s) {
   dim3 grid((N + 63) / 64, K);
@@ -417,9 +435,15 @@ int launch_bias_grad(const void* dz, int64_t ld, int dz_bf16, float* db, int64_t
     bias_grad_blocked_kernel<<<grid, kThreads, 0, s>>>((const __bf16*)dz, ld, db, strideDb, B, N,
                                                        sumsq, sumsq_stride);
   else
-    bias_grad_kernel<float><<<grid, kThreads, 0, s>>>((const float*)dz, ld, db, strideDb, B, N,
-                                                      sumsq, sumsq_stride);
+    run_bias_grad((const float*)dz, ld, db, strideDb, B, N, sumsq, sumsq_stride, 0, 0, grid, s);
   return (int)grid.x;
+}
+
+int launch_norm_param_grads(const float* part, float* grad, int64_t strideGrad, int64_t gam_off, int64_t bet_off,
+                            int K, int chunks, int C, double* sumsq, int64_t sumsq_stride, hipStream_t s) {
+  const dim3 grid((C + 63) / 64, K, 2);
+  run_bias_grad(part, 2 * C, grad + gam_off, strideGrad, chunks, C, sumsq, sumsq_stride, C, bet_off - gam_off, grid, s);
+  return 2 * (int)grid.x;
 }
 
 }  // namespace lsam

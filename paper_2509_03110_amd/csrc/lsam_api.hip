@@ -1045,17 +1045,9 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
       const int chunks = launch_bn_backward_partials(c->at<float>(cv.z), dout, c->at<float>(cv.stats),
                                                      part, lo.K, cv.rows, cv.Cout, s);
       if (chunks < 0) return fail(LSAM_EINVAL, "batch normalisation of convolution %d rejected", l);
-      if (ly.bet_off == ly.gam_off + cv.Cout) {
-        // gamma and beta are neighbours in the layout (64 | C_out): one sum over both halves
-        const int used = launch_bias_grad(part, 2 * cv.Cout, 0, g + ly.gam_off, lo.d_pad, lo.K, chunks,
-                                          2 * cv.Cout, ssq ? ssq + *slots : nullptr, lo.nblk, s);
-        if (ssq) *slots += used;
-      } else {
-        int used = launch_bias_grad(part, 2 * cv.Cout, 0, g + ly.gam_off, lo.d_pad, lo.K, chunks,
-                                    cv.Cout, ssq ? ssq + *slots : nullptr, lo.nblk, s);
-        if (ssq) *slots += used;
-        used = launch_bias_grad(part + cv.Cout, 2 * cv.Cout, 0, g + ly.bet_off, lo.d_pad, lo.K, chunks,
-                                cv.Cout, ssq ? ssq + *slots : nullptr, lo.nblk, s);
+      {
+        const int used = launch_norm_param_grads(part, g, lo.d_pad, ly.gam_off, ly.bet_off, lo.K, chunks, cv.Cout,
+                                                 ssq ? ssq + *slots : nullptr, lo.nblk, s);
         if (ssq) *slots += used;
       }
       if (!own_last) own_gradient();
@@ -1066,11 +1058,8 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
         const int pchunks = launch_bn_backward_partials(pz, dout, c->at<float>(cv.pstats), part, lo.K,
                                                         cv.rows, cv.Cout, s);
         if (pchunks < 0) return fail(LSAM_EINVAL, "projection of convolution %d: normalisation rejected", l);
-        int used = launch_bias_grad(part, 2 * cv.Cout, 0, g + ly.pgam_off, lo.d_pad, lo.K, pchunks, cv.Cout,
-                                    ssq ? ssq + *slots : nullptr, lo.nblk, s);
-        if (ssq) *slots += used;
-        used = launch_bias_grad(part + cv.Cout, 2 * cv.Cout, 0, g + ly.pbet_off, lo.d_pad, lo.K, pchunks,
-                                cv.Cout, ssq ? ssq + *slots : nullptr, lo.nblk, s);
+        const int used = launch_norm_param_grads(part, g, lo.d_pad, ly.pgam_off, ly.pbet_off, lo.K, pchunks, cv.Cout,
+                                                 ssq ? ssq + *slots : nullptr, lo.nblk, s);
         if (ssq) *slots += used;
         launch_bn_backward_apply(pz, dout, po.p ? nullptr : pz, c->at<float>(cv.pstats), params, g, lo.d_pad, ly.pgam_off,
                                  ly.pbet_off, lo.K, cv.rows, cv.Cout, nullptr, po, s);

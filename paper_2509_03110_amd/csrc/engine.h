@@ -218,6 +218,11 @@ struct ConvGemmDesc {
   float* splitk_ws; size_t splitk_bytes;
   double* sumsq; int64_t sumsq_stride;
   const int* nonfinite;
+  // 2: the input gradient of a stride-2 convolution.  The image is the output gradient [oH][oW], C and
+  // the mask are images of [2 oH][2 oW].  An input pixel meets the taps of its row's and its
+  // column's parity only: four classes of pixels, each a convolution of 1, 2, 2 or 4 taps whose filters
+  // follow each other in `other` (see FilterBank); M counts one class's pixels, Kd all nine taps.
+  int out_step = 1;
 };
 int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots = nullptr);   // 0, or -1: not served
 size_t conv_gemm_splitk_bytes(const ConvGemmDesc& d);
@@ -227,10 +232,13 @@ int launch_split_planes(const float* src, uint16_t* dst, int np, int64_t plane, 
 // products read it, `dst` elements into every plane.  taps = 0: [K][rows][ldp], zeros from cols on
 // (cols, ldw, ldp multiples of 4); taps = 1 or 9: mirrored and transposed, `cols` counting one tap's
 // columns: [K][cols][ldp], value (c, tap * rows + o) = W[o][(taps - 1 - tap) * cols + c], zeros beyond.
+// With stride 2 the nine taps come class by class instead, as the input pixels of even / odd row and
+// column read them: (1,1) | (1,2) (1,0) | (2,1) (0,1) | (2,2) (2,0) (0,2) (0,0).
 struct FilterBank {
   int64_t src, dst;
   int32_t rows, cols, ldw, ldp, taps;
   int32_t first;            // first workgroup that serves the bank
+  int32_t stride;
 };
 int filter_bank_blocks(const FilterBank& f);
 // All n banks of the table (device memory) for K replicas; blocks: workgroups of all of them.

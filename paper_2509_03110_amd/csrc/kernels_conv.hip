@@ -544,7 +544,7 @@ __global__ __launch_bounds__(kThreads) void bn_stats_partial_kernel(const float*
 // over the chunks i, in double, in a fixed order.  Next to nothing is read, so what bounds this is
 // the chain of loads a thread has to wait for: workgroup (block, k) serves 16 columns with 64 chains
 // each (chain q takes chunks q, q + 64, ...), eight loads in flight per chain.  512 chunks of 64
-// columns, four replicas: 18 us with 16 chains and a load at a time, 5.5 us so.
+// columns, four replicas: 18 us with 16 chains and a load at a time, 11 us so; 128 chunks 14 and 7.
 constexpr int kBnCols = 16, kBnChains = 64, kBnDepth = 8;
 __device__ __forceinline__ double chain_total(double v, double (*buf)[kBnCols], int col) {
   v += __shfl_xor(v, 16, 64);
@@ -720,7 +720,7 @@ __global__ __launch_bounds__(kThreads) void add_into_kernel(float* __restrict__ 
 // dA[k][b][i][j][c] = dP[k][b][c] / (H W) where A > 0 (mask null: everywhere).  A workgroup sums
 // the positions of 16 words of one image in 16 groups (position p in group p mod 16, the groups
 // added in order); a thread per word alone walks the image with a load at a time: 128 channels,
-// 16 x 16 positions, 512 images took 76 us, 13 us so (5.2 TB/s).
+// 16 x 16 positions, 512 images took 76 us, 12 us so (5.5 TB/s).
 __global__ __launch_bounds__(kThreads) void avgpool_kernel(const float* __restrict__ A, float* __restrict__ P,
                                                            int HW, int C, int ldp) {
   __shared__ f32x4 buf[kThreads];

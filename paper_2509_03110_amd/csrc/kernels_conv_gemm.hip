@@ -61,6 +61,7 @@ struct Params {
   const float* bias; long long strideBias;
   const float* mask; long long strideMask; int ldMask;
   double* sumsq; long long strideSumsq;
+  int out_step, out_i, out_j;                          // see ConvGemmDesc
   int ksplit, steps_per_piece; float* partial; long long stridePartial; int ldP;
   const int* nonfinite;
 };
@@ -452,17 +453,23 @@ __device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[
           }
         }
         v += bv;
+        int row = m;
+        if (p.out_step > 1) {
+          int b, oi, oj;
+          decode(m, p.g, b, oi, oj);
+          row = ((b * p.g.oH + oi) * 2 + p.out_i) * (2 * p.g.oW) + 2 * oj + p.out_j;
+        }
         if (relu) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) v[r] = v[r] > 0.f ? v[r] : 0.f;
         }
         if (masked) {
-          const f32x4 mk = *reinterpret_cast<const f32x4*>(mask + (long long)m * p.ldMask + n);
+          const f32x4 mk = *reinterpret_cast<const f32x4*>(mask + (long long)row * p.ldMask + n);
 #pragma unroll
           for (int r = 0; r < 4; ++r)
             if (!(mk[r] > 0.f)) v[r] = 0.f;
         }
-        *reinterpret_cast<f32x4*>(C + (long long)m * ldC + n) = v;
+        *reinterpret_cast<f32x4*>(C + (long long)row * ldC + n) = v;
         ssq += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
       }
     }
@@ -508,8 +515,22 @@ __global__ __launch_bounds__(kThreads, OCC) void conv_gemm_kernel(Params p) {
   const int logical = (blockIdx.x % 8) * p.chunks + blockIdx.x / 8;
   if (logical >= p.total) return;
   const int per_rep = p.tilesM * p.tilesN;
-  int rest = logical / per_rep;
-  const int t_in = logical - rest * per_rep;
+  int index = logical;
+  if constexpr (KIND != kWeightGrad) {
+    if (p.out_step == 2) {
+      // four classes of pixels (see ConvGemmDesc), side by side: neighbours read the same pixels,
+      // and every part of the grid has the same mix of one to four taps
+      const int cls = 3 - (logical & 3), odd_i = cls >> 1, odd_j = cls & 1;
+      index = logical >> 2;
+      const int before = cls == 0 ? 0 : 2 * cls - 1;   // taps of the classes in front: 0, 1, 3, 5
+      p.g.nu = 1 + odd_i; p.g.nv = 1 + odd_j; p.g.du0 = p.g.dv0 = 0;
+      p.Kd = p.g.nu * p.g.nv * p.g.C;
+      p.B += before * p.g.C; p.bytesB -= (unsigned)(before * p.g.C * 2);
+      p.out_i = odd_i; p.out_j = odd_j;
+    }
+  }
+  int rest = index / per_rep;
+  const int t_in = index - rest * per_rep;
   const int piece = rest % p.ksplit;
   const int bat = rest / p.ksplit;
   constexpr int GROUP_M = 8;
@@ -1142,7 +1163,8 @@ __global__ __launch_bounds__(kThreads) void split_kernel(const float* __restrict
 // Planes of all filter banks of a model, one launch (a launch per bank and pass cost more than
 // the copies).  Workgroups are dealt out bank by bank (FilterBank::first); a bank is copied with its
 // rows padded to pitch ldp by zeros, or mirrored and transposed for the input gradient:
-//   dst[c][tap * rows + o] = W[o][(taps - 1 - tap) * cols + c]
+//   dst[c][tap * rows + o] = W[o][source(tap) * cols + c],
+// source(tap) = taps - 1 - tap, or the order in which the classes of a stride-2 gradient follow each other,
 // in 32 x 32 (o, c) tiles of one tap, transposed through LDS so that reads and writes are both rows.
 template <int NP>
 __global__ __launch_bounds__(kThreads) void filters_kernel(const float* __restrict__ params, long long strideParams,
@@ -1185,7 +1207,9 @@ __global__ __launch_bounds__(kThreads) void filters_kernel(const float* __restri
     const int tap = block % f.taps, ot = block / f.taps / cblocks, ct = block / f.taps % cblocks;
     const int ob = ot * 32, cb = ct * 32;
     const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
-    const float* src = W + (long long)(f.taps - 1 - tap) * f.cols;
+    // (stride 2: the centre; its row's and its column's other two; the corners)
+    const int from = f.taps == 9 && f.stride == 2 ? (int)(0x026817354ull >> (4 * tap) & 15) : f.taps - 1 - tap;
+    const float* src = W + (long long)from * f.cols;
 #pragma unroll
     for (int r = 0; r < 32; r += 8)
       tile[y + r][x] = (cb + x < f.cols && ob + y + r < f.rows) ? src[(long long)(ob + y + r) * f.ldw + cb + x] : 0.f;
@@ -1219,7 +1243,7 @@ struct Tile { int bm, bn; };
 int tiled(Params& p, int bm, int bn) {
   p.tilesM = (p.M + bm - 1) / bm;
   p.tilesN = (p.N + bn - 1) / bn;
-  p.total = p.tilesM * p.tilesN * p.batch * p.ksplit;
+  p.total = p.tilesM * p.tilesN * p.batch * p.ksplit * (p.out_step == 2 ? 4 : 1);
   p.chunks = (p.total + 7) / 8;
   return p.tilesM * p.tilesN;
 }
@@ -1300,7 +1324,7 @@ ConvPlan conv_plan(const ConvGemmDesc& d) {
     pl.tile = d.M > 64 && d.np == 1 ? Tile{128, 128} : d.M > 32 ? Tile{64, 128} : Tile{32, 128};
   }
   const PlaneImage& im = d.image;
-  if (!d.wgrad && im.nu == 3 && im.nv == 3 && im.st == 1 && im.C % (d.np == 1 ? 32 : 16) == 0 && d.N > 32) {
+  if (!d.wgrad && im.nu == 3 && im.nv == 3 && im.st == 1 && d.out_step == 1 && im.C % (d.np == 1 ? 32 : 16) == 0 && d.N > 32) {
     const int s256 = patch_slots(256, im.oH, im.oW), s128 = patch_slots(128, im.oH, im.oW);
     if (d.np == 1) pl.patch = s256 <= 22 * 16 ? kPatch22 : s256 <= 26 * 16 ? kPatch26 : kNoPatch;
     else pl.patch = s256 <= 11 * 32 ? kSplitPatch256 : s128 <= 10 * 32 ? kSplitPatch128 : kNoPatch;
@@ -1311,7 +1335,7 @@ ConvPlan conv_plan(const ConvGemmDesc& d) {
   const long long tiles = count(pl.tile.bm, pl.tile.bn);
   const int target = 512;                                   // workgroups that fit the chip
   pl.steps = all;
-  if (tiles < target && all >= (pl.patch ? 4 : 16)) {
+  if (tiles < target && all >= (pl.patch ? 4 : 16) && d.out_step == 1) {
     long long want = (target + tiles - 1) / tiles;
     long long cap = pl.patch ? all / 2 : all / 8;
     long long sp = want < cap ? want : cap;
@@ -1346,6 +1370,9 @@ int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots) {
   // the other operand: filters [N][ld] resp. output gradient [Kd][ld]
   const long long rows = d.wgrad ? d.Kd : d.N;
   if (d.ld % 8 || (d.wgrad ? d.ld != d.M : d.ld < (d.Kd + 31) / 32 * 32)) return -1;
+  if (d.out_step != 1 && (d.out_step != 2 || d.wgrad || im.st != 1 || taps != 9 || im.oH != im.sH || im.oW != im.sW ||
+                          d.sumsq != nullptr || out_px >= (1 << 29)))
+    return -1;
   // 32-bit byte offsets; a k-step may reach up to 32 rows past the end
   if (img_elems * 2 >= 0x7FFF0000LL || (rows + 32) * d.ld * 2 >= 0x7FFF0000LL) return -1;
   if (((uintptr_t)im.p & 15) || ((uintptr_t)d.other & 15) || (im.stride % 8) || (im.plane % 8) || (d.other_stride % 8) ||
@@ -1368,6 +1395,7 @@ int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots) {
   p.g = Geometry{im.C, im.oH, im.oW, im.sH, im.sW, im.st, im.nu, im.nv, im.du0, im.dv0,
                  (unsigned)((1ull << 32) / (unsigned)im.C + 1)};
   p.epilogue = d.epilogue;
+  p.out_step = d.out_step;
   p.bias = d.bias; p.strideBias = d.strideBias;
   p.mask = d.mask; p.strideMask = d.strideMask; p.ldMask = d.ldMask;
   p.sumsq = d.sumsq; p.strideSumsq = d.sumsq_stride;

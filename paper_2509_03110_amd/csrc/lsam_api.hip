@@ -512,7 +512,10 @@ void build_layout(const lsam_config& c, Layout& lo) {
       // fp32-storage GEMM knows stride 1 and parts of taps only
       auto fits = [&](int C) { return C % 32 == 0 || (cv.fast && (C == 8 || C == 16)); };
       cv.direct_in = small && fits(cv.Cin) && (cv.fast || cv.stride == 1);
-      cv.direct_dx = small && l > 0 && fits(cv.Cout) && cv.stride == 1;
+      // (stride 2: with three planes the classes lose against the product with a stored gradient where
+      // their columns fill the 64-wide tiles badly: 160 channels, a step 0.35 ms slower of 27)
+      cv.direct_dx = small && l > 0 && fits(cv.Cout) &&
+                     (cv.stride == 1 || (cv.fast && (lo.np == 1 || cv.Cin <= 32 || (cv.Cin + 63) / 64 * 64 * 8 <= cv.Cin * 9)));
       cv.first = l == 0 && cv.stride == 1 && first_conv_fits(cv.Cin, cv.Cout, cv.rows);
       if (cv.first)
         cv.first_partial = take(cur, (size_t)lo.K * first_conv_chunks(cv.rows) * cv.Cout * 32 * 4);
@@ -529,7 +532,7 @@ void build_layout(const lsam_config& c, Layout& lo) {
       if (cv.fast) {
         const Layer& ly = lo.layers[l];
         auto bank = [&](int64_t src, int rows, int cols, int ldw, int taps) {
-          FilterBank f{src, lo.wp_elems, rows, cols, ldw, 0, taps, lo.bank_blocks};
+          FilterBank f{src, lo.wp_elems, rows, cols, ldw, 0, taps, lo.bank_blocks, cv.stride};
           f.ldp = (int)round_up(taps ? taps * rows : cols, 32);
           lo.wp_elems += (int64_t)lo.K * (taps ? cols : rows) * f.ldp;
           lo.bank_blocks += filter_bank_blocks(f);
@@ -640,7 +643,8 @@ void build_layout(const lsam_config& c, Layout& lo) {
         planes(0, cv->ldc, 1, 1, rows, ly.out, cv->ldc);
         planes(1, cv->ldc, 1, 1, ly.out, cv->ldc, rows);
       }
-      if (cv->direct_dx) planes(0, cv->Cout, 1, 3, rows, cv->Cin, 9 * cv->Cout);
+      if (cv->direct_dx && cv->stride == 1) planes(0, cv->Cout, 1, 3, rows, cv->Cin, 9 * cv->Cout);
+      else if (cv->direct_dx) {}          // one launch per class of pixels, never split
       else if (l > 0) planes(0, cv->Cout, 1, 1, rows, cv->ldc, cv->Cout);
       if (ly.proj) {           // the projection's three products
         planes(0, ly.proj_in, cv->skip_step, 1, rows, ly.out, ly.proj_in);
@@ -1185,12 +1189,18 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
       const ConvLayer& below = lo.conv[l - 1];
       if (cv.fast) {
         LaunchTimer t(c, KC_GEMM_DX);
+        // (stride 2: in four classes of pixels, the multiply-adds of a product with a stored gradient of
+        // the unfolded image without that gradient, nine values written and read per pixel: a step of
+        // 64 / 128-channel residual blocks with bf16 products 4.93 -> 4.72 ms, of 16 / 32 / 64 channels in
+        // fp32 2.84 -> 2.76; 4 replicas of 128 images of 32 x 32)
         ConvGemmDesc d = plane_desc(c, gradient_image(c, cv, 3), 0, cv.wx, (int)cv.rows, cv.Cin, 9 * cv.Cout);
+        d.out_step = cv.stride;
+        const int64_t image = (int64_t)lo.B * cv.in_H * cv.in_W * cv.Cin;
         d.C = c->at<float>(below.pool ? below.dpooled : below.dout);
-        d.strideC = cv.rows * cv.Cin; d.ldC = cv.Cin;
+        d.strideC = image; d.ldC = cv.Cin;
         d.epilogue = below.pool ? EPI_PLAIN : EPI_MASK;
         if (!below.pool) {
-          d.mask = c->at<float>(below.out); d.strideMask = cv.rows * cv.Cin; d.ldMask = cv.Cin;
+          d.mask = c->at<float>(below.out); d.strideMask = image; d.ldMask = cv.Cin;
         }
         if (launch_conv_gemm(d, s) != 0)
           return fail(LSAM_EINVAL, "dX product of convolution %d rejected", l);

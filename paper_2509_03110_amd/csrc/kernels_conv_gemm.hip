@@ -1112,6 +1112,286 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_patch_kernel(Params p)
                                                                   Bb, first * 16, nblk * 16, true);
 }
 
+// ---- weight gradient of 3x3 layers with stride 1, three planes, image patches in LDS ------------------
+// The ring forms 64 x 128 results from operands that pass through LDS once per 64 rows resp. per
+// tap, 1152 bytes a pixel, and waits for the caches that deliver them (160 channels at 32 x 32,
+// 4 replicas of 128: 9.6 TB/s out of L2 at 106 TFLOP/s).  Here a workgroup takes 32 OB output channels x 32
+// input channels x all nine taps: PX pixels of the gradient and the patch of the zero-rimmed
+// image they touch (NCHUNK x 16 slots of 64 bytes a plane, a tap a constant shift of the slot) feed
+// nine products, 790 bytes a pixel for 64 x 288 results.  Eight wavefronts, two to a matrix unit:
+// each owns one 32-channel block of the gradient, every PG-th matrix depth of 16 pixels and five or
+// four of the taps, and the two that share a unit have nine between them (all nine in one
+// wavefront are 288 accumulators, more than its 256 registers for them).  Three stages in LDS, the
+// loads of the one after the next under the products of the current one (with two stages they
+// have to wait for a second barrier, and the matrix units for them: 45 % busy).  The PG sums are added through LDS at the end and the launch leaves one partial
+// result per piece of the contraction.  4 replicas of 128, ring -> here: 64 channels at 32 x 32 320 ->
+// 218 us (177 TFLOP/s), 160 channels 2270 -> 1440, 320 channels at 16 x 16 1400 -> 1020.
+template <int NLA>
+__device__ __forceinline__ void patch_offsets(const Geometry& g, int px0, int images, const int (&row)[NLA],
+                                              const int (&col)[NLA], unsigned (&off)[NLA]) {
+  const int H2 = g.oH + 2;
+  int b0, i0, j0;
+  decode(px0, g, b0, i0, j0);
+  const int pr0 = __builtin_amdgcn_readfirstlane(b0 * H2 + i0);
+#pragma unroll
+  for (int l = 0; l < NLA; ++l) {
+    const int pr = pr0 + row[l], b = pr / H2, i = pr - b * H2 - 1;
+    const bool ok = (unsigned)i < (unsigned)g.oH && b < images && col[l] >= 0;
+    off[l] = ok ? (unsigned)(b * g.oH + i) * (unsigned)(g.oW * g.C * 2) + (unsigned)col[l] : kOob;
+  }
+}
+// Load x of a stage: planes of the patch (NLA each), then of the gradient; `ahead`: bytes in front of the
+// stage's first row of the gradient.
+template <int OB, int PX, int NCHUNK, int NLA>
+__device__ __forceinline__ void issue_wgrad(const Params& p, const unsigned short* Ab, const unsigned short* Bb, lds_byte* buf,
+                                            lds_byte* spill, bool live, const unsigned (&off)[NLA], unsigned zoff, unsigned ahead,
+                                            int wave, int x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if (x < 3 * NLA) {
+    const int q = x / NLA, l = x % NLA, chunk = wave + 8 * l;
+    lds_byte* dst = chunk < NCHUNK ? buf + (q * NCHUNK + chunk) * 1024 : spill;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(Bb + q * p.planeB, live ? p.bytesB : 0u),
+                                             (__attribute__((address_space(3))) void*)dst, 16, off[l], 0, 0, 0);
+  } else {
+    const int q = x - 3 * NLA;
+    lds_byte* dst = wave < OB * PX / 16 ? buf + 3 * NCHUNK * 1024 + q * (OB * PX * 64) + wave * 1024 : spill;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(Ab + q * p.planeA, live ? p.bytesA : 0u),
+                                             (__attribute__((address_space(3))) void*)dst, 16,
+                                             zoff == kOob ? kOob : zoff + ahead, 0, 0, 0);
+  }
+#endif
+}
+
+__device__ __forceinline__ u32x4 read_transposed(const lds_byte* at0, const lds_byte* at1) {
+  u32x4 f = {0u, 0u, 0u, 0u};
+#if defined(__HIP_DEVICE_COMPILE__)
+  const u32x2 l2 = __builtin_bit_cast(
+      u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)at0));
+  const u32x2 h2 = __builtin_bit_cast(
+      u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)at1));
+  f[0] = l2[0]; f[1] = l2[1]; f[2] = h2[0]; f[3] = h2[1];
+#endif
+  return f;
+}
+
+template <int OB, int PX, int NCHUNK>
+__global__ __launch_bounds__(512, 2) void conv_split_wgrad_kernel(Params p) {
+  constexpr int NP = 3, PG = 4 / OB, CH = PX / 16 / PG, NT = 5;   // CH: matrix depths per wavefront and stage
+  constexpr int NLA = (NCHUNK + 7) / 8, NL = NP * (NLA + 1);
+  constexpr int X_BYTES = NP * NCHUNK * 1024, Z_PLANE = OB * PX * 64, USED = X_BYTES + NP * Z_PLANE;
+  constexpr int SUMS = NT * 16 * 64;                       // floats of a wavefront's sums
+  constexpr int STAGE = USED > 2 * SUMS * 4 ? USED : 2 * SUMS * 4;
+  static_assert(OB * PX <= 128, "a load of the gradient per wavefront and plane");
+  __shared__ __attribute__((aligned(1024))) unsigned char st0[STAGE];
+  __shared__ __attribute__((aligned(1024))) unsigned char st1[STAGE];
+  __shared__ __attribute__((aligned(1024))) unsigned char st2[STAGE];
+  __shared__ __attribute__((aligned(1024))) unsigned char spill[1024];
+
+  const int logical = (blockIdx.x % 8) * p.chunks + blockIdx.x / 8;
+  if (logical >= p.total) return;
+  const int per_rep = p.tilesM * p.tilesN;
+  const int rest = __builtin_amdgcn_readfirstlane(logical / per_rep);
+  const int t_in = logical - rest * per_rep;
+  const int bat = __builtin_amdgcn_readfirstlane(rest / p.ksplit);
+  const int piece = rest - bat * p.ksplit;
+  const int t_row = __builtin_amdgcn_readfirstlane(t_in / p.tilesN);
+  const int m0 = t_row * (OB * 32), c0 = (t_in - t_row * p.tilesN) * 32;
+
+  const unsigned short* Ab = p.A + (long long)bat * p.strideA;
+  const unsigned short* Bb = p.B + (long long)bat * p.strideB;
+  const Geometry& g = p.g;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ob = wave % OB, pg = wave / OB % PG, tg = wave / 4;   // output channels, pixels, taps
+  const int H2 = g.oH + 2, W2 = g.oW + 2;
+  const int images = p.Kd / (g.oH * g.oW);
+
+  const int all = (p.Kd + PX - 1) / PX;                    // stages of the whole contraction
+  const int first = piece * p.steps_per_piece;
+  const int n = all - first < p.steps_per_piece ? all - first : p.steps_per_piece;
+
+  int row[NLA], col[NLA];                                  // this lane's patch slots: rimmed row, byte offset in the row
+#pragma unroll
+  for (int l = 0; l < NLA; ++l) {
+    const int slot = (wave + 8 * l) * 16 + (lane >> 2);
+    row[l] = slot / W2;
+    const int x = slot - row[l] * W2 - 1;
+    col[l] = (unsigned)x < (unsigned)g.oW && wave + 8 * l < NCHUNK ? (x * g.C + c0 + (lane & 3) * 8) * 2 : -1;
+  }
+  unsigned zoff;
+  {
+    const int blk = wave / (PX / 16), r = wave % (PX / 16) * 16 + (lane >> 2);
+    const int c = m0 + blk * 32 + (lane & 3) * 8;
+    zoff = blk < OB && c < p.ldA ? ((unsigned)r * p.ldA + c) * 2u : kOob;
+  }
+  lds_byte* s0 = (lds_byte*)st0;
+  lds_byte* s1 = (lds_byte*)st1;
+  lds_byte* s2 = (lds_byte*)st2;
+  lds_byte* sp = (lds_byte*)spill;
+
+  // transposing reads: lane -> pixel kr (+ 4) of the depth, four channels from colb / 2 on
+  const int il = lane & 15, gq = lane >> 4;
+  const int kr = (gq >> 1) * 8 + (il >> 2);
+  const int colb = ((gq & 1) * 16 + 4 * (il & 3)) * 2;
+  int shift[NT];                                           // of this wavefront's taps, in bytes (the tenth: unused)
+#pragma unroll
+  for (int i = 0; i < NT; ++i) {
+    const int tap = tg * NT + i < 9 ? tg * NT + i : 8;
+    shift[i] = (tap / 3 * W2 + tap % 3) * 64;
+  }
+
+  f32x16 acc[NT], low[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[t][e] = low[t][e] = 0.f;
+
+  // What a stage needs in addresses is worked out under the products of the stages before it: the
+  // offsets of its patch two stages ahead, its pixels' slots (of tap (0, 0)) one.
+  unsigned off[NLA];
+  int xs[CH][2], zs[CH][2];
+  auto slots_of = [&](int px0) {
+    int b, y, x;
+    decode(px0, g, b, y, x);
+    const int pr0 = b * H2 + y;
+#pragma unroll
+    for (int cc = 0; cc < CH; ++cc)
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        decode(px0 + (pg + PG * cc) * 16 + kr + kk * 4, g, b, y, x);
+        xs[cc][kk] = ((b * H2 + y - pr0) * W2 + x) * 64 + colb;
+      }
+  };
+#pragma unroll
+  for (int cc = 0; cc < CH; ++cc)
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) zs[cc][kk] = X_BYTES + (ob * PX + (pg + PG * cc) * 16 + kr + kk * 4) * 64 + colb;
+  const unsigned step = (unsigned)(p.ldA * 2) * PX;        // bytes of a stage's rows of the gradient
+  patch_offsets(g, first * PX, images, row, col, off);
+#pragma unroll
+  for (int x = 0; x < NL; ++x) issue_wgrad<OB, PX, NCHUNK>(p, Ab, Bb, s0, sp, true, off, zoff, first * step, wave, x);
+  patch_offsets(g, (first + 1) * PX, images, row, col, off);
+#pragma unroll
+  for (int x = 0; x < NL; ++x) issue_wgrad<OB, PX, NCHUNK>(p, Ab, Bb, s1, sp, 1 < n, off, zoff, (first + 1) * step, wave, x);
+  patch_offsets(g, (first + 2) * PX, images, row, col, off);
+  slots_of(first * PX);
+  constexpr int LPS = (NL + CH * (NT - 1) - 1) / (CH * (NT - 1));   // loads under a step's products
+
+  auto compute = [&](const lds_byte* buf, lds_byte* fill, int st) {
+    u32x4 fa[2][NP], fb[2][NP];
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      fa[0][q] = read_transposed(buf + zs[0][0] + q * Z_PLANE, buf + zs[0][1] + q * Z_PLANE);
+      fb[0][q] = read_transposed(buf + xs[0][0] + shift[0] + q * NCHUNK * 1024, buf + xs[0][1] + shift[0] + q * NCHUNK * 1024);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x100, 4 * NP, 0);
+#pragma unroll
+    for (int t = 0; t < CH * NT; ++t) {
+      const int cc = t / NT, i = t % NT, nt = t + 1, nc = nt / NT;
+      if (nt < CH * NT) {
+        if (nc != cc)
+#pragma unroll
+          for (int q = 0; q < NP; ++q)
+            fa[nc & 1][q] = read_transposed(buf + zs[nc][0] + q * Z_PLANE, buf + zs[nc][1] + q * Z_PLANE);
+#pragma unroll
+        for (int q = 0; q < NP; ++q)
+          fb[nt & 1][q] = read_transposed(buf + xs[nc][0] + shift[nt % NT] + q * NCHUNK * 1024,
+                                          buf + xs[nc][1] + shift[nt % NT] + q * NCHUNK * 1024);
+      }
+      const int x0 = (cc * (NT - 1) + i) * LPS;
+      if (i < NT - 1)
+#pragma unroll
+        for (int x = x0; x < x0 + LPS; ++x)
+          if (x < NL)
+            issue_wgrad<OB, PX, NCHUNK>(p, Ab, Bb, fill, sp, st + 2 < n, off, zoff, (first + st + 2) * step, wave, x);
+      constexpr int xa[6] = {2, 0, 1, 1, 0, 0}, xb[6] = {0, 2, 1, 0, 1, 0};
+      if (i < NT - 1 || tg == 0) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+          f32x16& to = q < 5 ? low[i] : acc[i];
+          to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb[t & 1][xb[q]]),
+                                                       __builtin_bit_cast(bf16x8, fa[cc & 1][xa[q]]), to, 0, 0, 0);
+        }
+        if (i < NT - 1) Interleave<0x120, 2 * NP + LPS, 6, 0>::run();
+      }
+    }
+  };
+
+  // After a stage's barrier every wavefront is through with the stage before, whose place the one
+  // after the next takes.
+#define LSAM_WGRAD_STAGE(CUR, FILL)                                                                                   \
+  {                                                                                                                   \
+    __builtin_amdgcn_s_waitcnt(waitcnt(NL, 0));                                                                       \
+    asm volatile("" ::: "memory");                                                                                    \
+    __builtin_amdgcn_s_barrier();                                                                                     \
+    asm volatile("" ::: "memory");                                                                                    \
+    compute(CUR, FILL, st);                                                                                           \
+    slots_of((first + st + 1) * PX);                                                                                  \
+    patch_offsets(g, (first + st + 3) * PX, images, row, col, off);                                                   \
+    if (++st >= n) break;                                                                                             \
+  }
+  for (int st = 0;;) {
+    LSAM_WGRAD_STAGE(s0, s2)
+    LSAM_WGRAD_STAGE(s1, s0)
+    LSAM_WGRAD_STAGE(s2, s1)
+  }
+#undef LSAM_WGRAD_STAGE
+  __builtin_amdgcn_s_waitcnt(waitcnt(0, 0));            // nothing may still be writing LDS
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[t][e] += low[t][e];
+  // the sums of pixel groups half.. to those of groups 0..half - 1
+#pragma unroll
+  for (int half = PG / 2; half >= 1; half /= 2) {
+    const int slot = (pg % half * OB + ob) * 2 + tg;       // at most four
+    float* at = reinterpret_cast<float*>(slot & 1 ? st1 : st0) + (slot >> 1) * SUMS + lane;
+    if (pg >= half && pg < 2 * half) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) at[(t * 16 + e) * 64] = acc[t][e];
+    }
+    __syncthreads();
+    if (pg < half) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[t][e] += at[(t * 16 + e) * 64];
+    }
+    __syncthreads();
+  }
+  const int m = m0 + ob * 32 + (lane & 31);
+  if (pg == 0 && m < p.M) {
+    const bool slow = *p.nonfinite != 0;
+    float* C = p.partial + (long long)piece * p.stridePartial + ((long long)bat * p.M + m) * p.ldP;
+    const int kbeg = first * PX, kend = (first + n) * PX < p.Kd ? (first + n) * PX : p.Kd;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      if (tg * NT + t >= 9) continue;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int c = (tg * NT + t) * g.C + c0 + q * 8 + (lane >> 5) * 4;
+        f32x4 v = {acc[t][q * 4], acc[t][q * 4 + 1], acc[t][q * 4 + 2], acc[t][q * 4 + 3]};
+        if (__builtin_expect(slow, 0)) {
+#pragma unroll 1
+          for (int r = 0; r < 4; ++r) {
+            float sum = 0.f;
+#pragma unroll 1
+            for (int k = kbeg; k < kend; ++k)
+              sum = __builtin_fmaf(MatM<64, NP>::value(p, Ab, m, k), ImgM<128, NP>::value(p, Bb, c + r, k), sum);
+            if (r == 0) v[0] = sum; else if (r == 1) v[1] = sum; else if (r == 2) v[2] = sum; else v[3] = sum;
+          }
+        }
+        *reinterpret_cast<f32x4*>(C + c) = v;
+      }
+    }
+  }
+}
+
 // Every specialisation that is launched is instantiated explicitly (the compiler does not emit the
 // host-side launch stubs of all implicit instantiations of such a kernel).
 #define LSAM_CONV_KERNEL(...) template __global__ void conv_gemm_kernel<__VA_ARGS__>(Params);
@@ -1137,6 +1417,8 @@ template __global__ void conv_patch_kernel<22>(Params);
 template __global__ void conv_patch_kernel<26>(Params);
 template __global__ void conv_split_patch_kernel<2, 11>(Params);
 template __global__ void conv_split_patch_kernel<1, 10>(Params);
+template __global__ void conv_split_wgrad_kernel<2, 64, 9>(Params);
+template __global__ void conv_split_wgrad_kernel<1, 64, 9>(Params);
 
 // ---- planes --------------------------------------------------------------------------------------
 // dst planes of n values (a multiple of 4), 4 to a thread.  Bound by its (4 + 2 NP) bytes a value.
@@ -1276,8 +1558,15 @@ int run_weight_grad(Params& p, const Tile& t, int np, hipStream_t s) {
   return run<3, kWeightGrad, 32, 128, 1, 2, 2>(p, s);
 }
 
-enum PatchKind { kNoPatch = 0, kPatch22, kPatch26, kSplitPatch256, kSplitPatch128 };
+enum PatchKind { kNoPatch = 0, kPatch22, kPatch26, kSplitPatch256, kSplitPatch128, kSplitWgrad64, kSplitWgrad32 };
 int run_patch(Params& p, int kind, hipStream_t s) {
+  if (kind == kSplitWgrad64 || kind == kSplitWgrad32) {
+    tiled(p, kind == kSplitWgrad64 ? 64 : 32, 9 * 32);       // N = 9 C, C a multiple of 32
+    const unsigned grid = (unsigned)p.chunks * 8;
+    if (kind == kSplitWgrad64) conv_split_wgrad_kernel<2, 64, 9><<<grid, 512, 0, s>>>(p);
+    else conv_split_wgrad_kernel<1, 64, 9><<<grid, 512, 0, s>>>(p);
+    return 0;                                                // partial sums only
+  }
   const int slots = tiled(p, kind == kSplitPatch128 ? 128 : 256, 64);
   const unsigned grid = (unsigned)p.chunks * 8;
   if (kind == kPatch22) conv_patch_kernel<22><<<grid, kThreads, 0, s>>>(p);
@@ -1329,6 +1618,31 @@ ConvPlan conv_plan(const ConvGemmDesc& d) {
     if (d.np == 1) pl.patch = s256 <= 22 * 16 ? kPatch22 : s256 <= 26 * 16 ? kPatch26 : kNoPatch;
     else pl.patch = s256 <= 11 * 32 ? kSplitPatch256 : s128 <= 10 * 32 ? kSplitPatch128 : kNoPatch;
     if (pl.patch) pl.tile = Tile{pl.patch == kSplitPatch128 ? 128 : 256, 64};
+  }
+  // Weight gradients: the patch kernel always leaves partial sums.  Its workgroups have a compute unit to
+  // themselves and equal work, so the contraction is cut for one, two or four full rounds of 256,
+  // the first that keeps 93 % of the units busy.
+  if (d.wgrad && d.np == 3 && im.nu == 3 && im.nv == 3 && im.st == 1 && im.C % 32 == 0) {
+    const bool wide = d.M > 32;
+    const int px = 64;
+    const long long tiles = (long long)((d.M + (wide ? 63 : 31)) / (wide ? 64 : 32)) * (im.C / 32) * d.batch;
+    const int stages = (d.Kd + px - 1) / px;
+    long long pieces = 0;
+    for (int r = 1; r <= 4; r *= 2) {
+      pieces = 256LL * r / tiles;
+      if (pieces * tiles >= 238LL * r) break;
+    }
+    if (pieces > 64) pieces = 64;
+    if (pieces > stages / 4) pieces = stages / 4;
+    if (patch_slots(px, im.oH, im.oW) <= 9 * 16 && pieces >= 2) {
+      pl.patch = wide ? kSplitWgrad64 : kSplitWgrad32;
+      pl.steps = (int)((stages + pieces - 1) / pieces);
+      pl.splits = (stages + pl.steps - 1) / pl.steps;
+      pl.ldP = d.N;
+      pl.ws_bytes = (size_t)pl.splits * d.batch * d.M * pl.ldP * 4;
+      if (pl.splits >= 2) return pl;
+      pl = ConvPlan{pl.tile, 0, 1, 0, 0, 0};
+    }
   }
   const int per_block = pl.patch ? (d.np == 1 ? 32 : 16) : 0;
   const int all = pl.patch ? im.C / per_block : (d.Kd + 31) / 32;
@@ -1400,9 +1714,11 @@ int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots) {
   p.mask = d.mask; p.strideMask = d.strideMask; p.ldMask = d.ldMask;
   p.sumsq = d.sumsq; p.strideSumsq = d.sumsq_stride;
   p.nonfinite = d.nonfinite;
-  const ConvPlan pl = conv_plan(d);
+  ConvPlan pl = conv_plan(d);
+  const bool room = d.splitk_ws != nullptr && d.splitk_bytes >= pl.ws_bytes && ((uintptr_t)d.splitk_ws & 15) == 0;
+  if (d.wgrad && pl.patch && !room) pl.patch = kNoPatch, pl.splits = 1, pl.steps = (d.Kd + 31) / 32;
   p.ksplit = 1; p.steps_per_piece = pl.steps * pl.splits;     // all of it
-  if (pl.splits > 1 && d.splitk_ws != nullptr && d.splitk_bytes >= pl.ws_bytes && ((uintptr_t)d.splitk_ws & 15) == 0) {
+  if (pl.splits > 1 && room) {
     p.ksplit = pl.splits; p.steps_per_piece = pl.steps;
     p.partial = d.splitk_ws; p.ldP = pl.ldP;
     p.stridePartial = (long long)d.batch * d.M * pl.ldP;

@@ -919,9 +919,12 @@ __global__ __launch_bounds__(kThreads, 2) void conv_patch_kernel(Params p) {
 // LDS: 276 against 222 us on 64 channels at 32 x 32).  A 16-byte unit of slot t lies at position
 // u ^ (t / 8) % 2: 16 consecutive slots read without bank conflicts at any shift.
 // Per stage and wavefront: 6 TM x 4 products, 3 (TM + 2) fragment reads.
-template <int TM, int NCHUNK>
+// TN = 1 serves layers of up to 32 columns (half of the filter rows it requests do not exist and
+// cost no traffic): 16 channels at 32 x 32, 4 replicas of 128: 38 us,
+// 56 by the ring (which fetches every pixel nine times).
+template <int TM, int TN, int NCHUNK>
 __global__ __launch_bounds__(kThreads, 2) void conv_split_patch_kernel(Params p) {
-  constexpr int NP = 3, TN = 2, BM = TM * 128, BN = 64, S = 9;
+  constexpr int NP = 3, BM = TM * 128, BN = TN * 32, S = 9;
   constexpr int NLA = (NCHUNK + 3) / 4, NA = NLA * NP, AG = (NA + S - 2) / (S - 1);
   constexpr int A_BYTES = NP * NCHUNK * 1024, B_BYTES = NP * 2048;
   constexpr int EPI_PITCH = BN + 4;
@@ -980,7 +983,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_patch_kernel(Params p)
   {
     const int row = (wave & 1) * 32 + (lane >> 1);
     const int u = (lane & 1) ^ ((row >> 3) & 1);
-    boff = n0 + row < p.N ? ((unsigned)(n0 + row) * p.ldB + u * 8) * 2u : kOob;
+    boff = row < BN && n0 + row < p.N ? ((unsigned)(n0 + row) * p.ldB + u * 8) * 2u : kOob;
   }
   lds_byte* a0 = (lds_byte*)pa0;
   lds_byte* a1 = (lds_byte*)pa1;
@@ -1415,8 +1418,10 @@ LSAM_CONV_KERNEL(3, kWeightGrad, 32, 128, 1, 2, 2)
 
 template __global__ void conv_patch_kernel<22>(Params);
 template __global__ void conv_patch_kernel<26>(Params);
-template __global__ void conv_split_patch_kernel<2, 11>(Params);
-template __global__ void conv_split_patch_kernel<1, 10>(Params);
+template __global__ void conv_split_patch_kernel<2, 2, 11>(Params);
+template __global__ void conv_split_patch_kernel<1, 2, 10>(Params);
+template __global__ void conv_split_patch_kernel<2, 1, 11>(Params);
+template __global__ void conv_split_patch_kernel<1, 1, 10>(Params);
 template __global__ void conv_split_wgrad_kernel<2, 64, 9>(Params);
 template __global__ void conv_split_wgrad_kernel<1, 64, 9>(Params);
 
@@ -1558,7 +1563,7 @@ int run_weight_grad(Params& p, const Tile& t, int np, hipStream_t s) {
   return run<3, kWeightGrad, 32, 128, 1, 2, 2>(p, s);
 }
 
-enum PatchKind { kNoPatch = 0, kPatch22, kPatch26, kSplitPatch256, kSplitPatch128, kSplitWgrad64, kSplitWgrad32 };
+enum PatchKind { kNoPatch = 0, kPatch22, kPatch26, kSplitPatch256, kSplitPatch128, kSplitNarrow256, kSplitNarrow128, kSplitWgrad64, kSplitWgrad32 };
 int run_patch(Params& p, int kind, hipStream_t s) {
   if (kind == kSplitWgrad64 || kind == kSplitWgrad32) {
     tiled(p, kind == kSplitWgrad64 ? 64 : 32, 9 * 32);       // N = 9 C, C a multiple of 32
@@ -1567,12 +1572,15 @@ int run_patch(Params& p, int kind, hipStream_t s) {
     else conv_split_wgrad_kernel<1, 64, 9><<<grid, 512, 0, s>>>(p);
     return 0;                                                // partial sums only
   }
-  const int slots = tiled(p, kind == kSplitPatch128 ? 128 : 256, 64);
+  const int slots = tiled(p, kind == kSplitPatch128 || kind == kSplitNarrow128 ? 128 : 256,
+                          kind == kSplitNarrow256 || kind == kSplitNarrow128 ? 32 : 64);
   const unsigned grid = (unsigned)p.chunks * 8;
   if (kind == kPatch22) conv_patch_kernel<22><<<grid, kThreads, 0, s>>>(p);
   else if (kind == kPatch26) conv_patch_kernel<26><<<grid, kThreads, 0, s>>>(p);
-  else if (kind == kSplitPatch256) conv_split_patch_kernel<2, 11><<<grid, kThreads, 0, s>>>(p);
-  else conv_split_patch_kernel<1, 10><<<grid, kThreads, 0, s>>>(p);
+  else if (kind == kSplitPatch256) conv_split_patch_kernel<2, 2, 11><<<grid, kThreads, 0, s>>>(p);
+  else if (kind == kSplitPatch128) conv_split_patch_kernel<1, 2, 10><<<grid, kThreads, 0, s>>>(p);
+  else if (kind == kSplitNarrow256) conv_split_patch_kernel<2, 1, 11><<<grid, kThreads, 0, s>>>(p);
+  else conv_split_patch_kernel<1, 1, 10><<<grid, kThreads, 0, s>>>(p);
   return slots;
 }
 
@@ -1613,11 +1621,14 @@ ConvPlan conv_plan(const ConvGemmDesc& d) {
     pl.tile = d.M > 64 && d.np == 1 ? Tile{128, 128} : d.M > 32 ? Tile{64, 128} : Tile{32, 128};
   }
   const PlaneImage& im = d.image;
-  if (!d.wgrad && im.nu == 3 && im.nv == 3 && im.st == 1 && d.out_step == 1 && im.C % (d.np == 1 ? 32 : 16) == 0 && d.N > 32) {
+  if (!d.wgrad && im.nu == 3 && im.nv == 3 && im.st == 1 && d.out_step == 1 &&
+      im.C % (d.np == 1 ? 32 : 16) == 0 && (d.np == 3 || d.N > 32)) {
     const int s256 = patch_slots(256, im.oH, im.oW), s128 = patch_slots(128, im.oH, im.oW);
     if (d.np == 1) pl.patch = s256 <= 22 * 16 ? kPatch22 : s256 <= 26 * 16 ? kPatch26 : kNoPatch;
-    else pl.patch = s256 <= 11 * 32 ? kSplitPatch256 : s128 <= 10 * 32 ? kSplitPatch128 : kNoPatch;
-    if (pl.patch) pl.tile = Tile{pl.patch == kSplitPatch128 ? 128 : 256, 64};
+    else if (d.N > 32) pl.patch = s256 <= 11 * 32 ? kSplitPatch256 : s128 <= 10 * 32 ? kSplitPatch128 : kNoPatch;
+    else pl.patch = s256 <= 11 * 32 ? kSplitNarrow256 : s128 <= 10 * 32 ? kSplitNarrow128 : kNoPatch;
+    if (pl.patch)
+      pl.tile = Tile{pl.patch == kSplitPatch128 || pl.patch == kSplitNarrow128 ? 128 : 256, d.N > 32 ? 64 : 32};
   }
   // Weight gradients: the patch kernel always leaves partial sums.  Its workgroups have a compute unit to
   // themselves and equal work, so the contraction is cut for one, two or four full rounds of 256,

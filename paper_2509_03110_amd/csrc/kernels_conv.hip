@@ -393,9 +393,12 @@ __global__ __launch_bounds__(kThreads) void first_conv_forward_kernel(const floa
 // Weight and bias gradient, first stage: workgroup (chunk, k) covers kFirstChunk pixels, 128 per
 // wavefront; partial[k][chunk][o][t] = sum over its pixels of dout[p][o] unfolded(p, t), with
 // t = 9 C standing for the constant 1 (that column is the bias gradient).  The four
-// wavefronts' sums are added in wave order through LDS.
+// wavefronts' sums are added in wave order through LDS.  What bounds it is the work per pixel in
+// front of the matrix instruction (its row and column, the gather of its 27 neighbours), so two
+// blocks of 32 output channels share it where there are two: 64 channels at 32 x 32, 4 replicas of 128,
+// 87 us with one at a time, 57 with two.
 constexpr int kFirstChunk = 512;
-template <int C>
+template <int C, int OB>
 __global__ __launch_bounds__(kThreads) void first_conv_wgrad_kernel(const float* __restrict__ X,
                                                                     const float* __restrict__ dout,
                                                                     float* __restrict__ partial,
@@ -412,10 +415,12 @@ __global__ __launch_bounds__(kThreads) void first_conv_wgrad_kernel(const float*
   const int tap = t / C, c = t - tap * C;
   const int du = tap / 3 - 1, dv = tap % 3 - 1;
   const int shift = (du * f.W + dv) * C + c;
-  for (int ob = 0; ob < f.Cout; ob += 32) {
-    f32x16 acc;
+  for (int ob = 0; ob < f.Cout; ob += 32 * OB) {
+    f32x16 acc[OB];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    for (int q = 0; q < OB; ++q)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[q][e] = 0.f;
     // loads are issued unconditionally (from a clamped pixel) and zeroed afterwards, so that the
     // unrolled loop can have many of them in flight
     const int last = (int)f.rows - 1;
@@ -426,34 +431,44 @@ __global__ __launch_bounds__(kThreads) void first_conv_wgrad_kernel(const float*
       int i, j;
       pixel_rc(pc, f, i, j);
       const bool in_img = t < 9 * C && (unsigned)(i + du) < (unsigned)f.H && (unsigned)(j + dv) < (unsigned)f.W;
-      float a = dz[(long long)pc * f.Cout + ob + l32];
+      float a[OB];
+#pragma unroll
+      for (int q = 0; q < OB; ++q) a[q] = dz[(long long)pc * f.Cout + ob + 32 * q + l32];
       float b = img[in_img ? (long long)pc * C + shift : 0];
       b = in_img ? b : (t == 9 * C ? 1.f : 0.f);
-      if (p > last) { a = 0.f; b = 0.f; }
-      if (round) { a = to_bf16(a); b = to_bf16(b); }
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b, a, acc, 0, 0, 0);
-    }
-    // acc[e]: o = ob + l32, t = (e/4)*8 + h*4 + e%4
-    if (wave > 0) {
+      if (p > last) b = 0.f;
+      if (round) b = to_bf16(b);
 #pragma unroll
-      for (int e = 0; e < 16; ++e) red[wave - 1][l32 * 32 + (e / 4) * 8 + h * 4 + e % 4] = acc[e];
-    }
-    __syncthreads();
-    if (wave == 0) {
-      float* dst = partial + (((long long)k * chunks + blockIdx.x) * f.Cout + ob + l32) * 32;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int tt = q * 8 + h * 4;
-        f32x4 v;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int at = l32 * 32 + tt + r;
-          v[r] = ((acc[q * 4 + r] + red[0][at]) + red[1][at]) + red[2][at];
-        }
-        *reinterpret_cast<f32x4*>(dst + tt) = v;
+      for (int q = 0; q < OB; ++q) {
+        if (p > last) a[q] = 0.f;
+        if (round) a[q] = to_bf16(a[q]);
+        acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(b, a[q], acc[q], 0, 0, 0);
       }
     }
-    __syncthreads();
+    // acc[q][e]: o = ob + 32 q + l32, t = (e/4)*8 + h*4 + e%4
+#pragma unroll
+    for (int q = 0; q < OB; ++q) {
+      if (wave > 0) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) red[wave - 1][l32 * 32 + (e / 4) * 8 + h * 4 + e % 4] = acc[q][e];
+      }
+      __syncthreads();
+      if (wave == 0) {
+        float* dst = partial + (((long long)k * chunks + blockIdx.x) * f.Cout + ob + 32 * q + l32) * 32;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int tt = u * 8 + h * 4;
+          f32x4 v;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int at = l32 * 32 + tt + r;
+            v[r] = ((acc[q][u * 4 + r] + red[0][at]) + red[1][at]) + red[2][at];
+          }
+          *reinterpret_cast<f32x4*>(dst + tt) = v;
+        }
+      }
+      __syncthreads();
+    }
   }
 }
 
@@ -886,9 +901,13 @@ int launch_first_conv_wgrad(const float* X, const float* dout, float* partial, f
   const FirstConv f = first_shape(H, W, Cout, rows, strideParams, ldw);
   const int chunks = first_conv_chunks(rows);
   const dim3 grid((unsigned)chunks, (unsigned)K);
-  if (C == 1) first_conv_wgrad_kernel<1><<<grid, kThreads, 0, s>>>(X, dout, partial, chunks, f, round);
-  else if (C == 2) first_conv_wgrad_kernel<2><<<grid, kThreads, 0, s>>>(X, dout, partial, chunks, f, round);
-  else first_conv_wgrad_kernel<3><<<grid, kThreads, 0, s>>>(X, dout, partial, chunks, f, round);
+  auto run = [&](auto one, auto two) {
+    if (Cout % 64 == 0) two<<<grid, kThreads, 0, s>>>(X, dout, partial, chunks, f, round);
+    else one<<<grid, kThreads, 0, s>>>(X, dout, partial, chunks, f, round);
+  };
+  if (C == 1) run(first_conv_wgrad_kernel<1, 1>, first_conv_wgrad_kernel<1, 2>);
+  else if (C == 2) run(first_conv_wgrad_kernel<2, 1>, first_conv_wgrad_kernel<2, 2>);
+  else run(first_conv_wgrad_kernel<3, 1>, first_conv_wgrad_kernel<3, 2>);
   first_conv_wgrad_finish_kernel<<<dim3((unsigned)(Cout / 2), (unsigned)K), 1024, 0, s>>>(
       partial, chunks, C, grad, w_off, b_off, sumsq, sumsq_stride, f, skip_bias);
   return Cout / 2;     // sum-of-squares slots written per replica

@@ -25,6 +25,7 @@ import workloads  # noqa: E402
 
 PEAK_HBM_GBS = 8000.0
 PEAK_TFLOPS = {0: 157.3, 1: 2500.0}   # dense MFMA: fp32, bf16
+PEAK_TFLOPS_SPLIT = 2500.0 / 6        # fp32 as six products of exact bf16 pieces: the ceiling of a convolutional model
 
 
 # HBM bytes per launch of each kernel class, from two `rocprofv3 --pmc` runs of this script
@@ -92,7 +93,7 @@ def kernel_sources_digest():
     # the files that hold device code (the host engine, lsam_api.hip and engine.h, launches
     # these kernels but does not change what one launch of them moves)
     files = sorted(glob.glob(os.path.join(ROOT, "paper_2509_03110_amd", "csrc", "kernels_*.hip")) +
-                   [os.path.join(ROOT, "paper_2509_03110_amd", "csrc", h) for h in ("b32s.h", "langevin.h")])
+                   [os.path.join(ROOT, "paper_2509_03110_amd", "csrc", h) for h in ("b32s.h", "langevin.h", "planes.h")])
     for f in files:
         with open(f, "rb") as fh:
             h.update(fh.read())
@@ -140,7 +141,7 @@ def conv_bytes(w, layers):
     from paper_2509_03110_amd import lsam
     unfold = pool = bn = 0.0
     for l in range(w.n_conv):
-        kind, dx_stored, _, rows, _, _, proj_c, proj_step = layers[l]
+        kind, dx_stored, _, rows, _, _, proj_c, _ = layers[l]
         cin, cout = w.dims[l], w.dims[l + 1]
         st2 = 4 if (w.stride_mask >> l) & 1 else 1    # pixels of the image read per output pixel
         if kind == lsam.LAYER_CONV_STORED:
@@ -149,8 +150,8 @@ def conv_bytes(w, layers):
             unfold += rows * (9 * cin + st2 * cin) * 4.0
         if proj_c:
             # projection: its normalisation costs what the layer's own does (below), and its
-            # output is read once more where the two branches meet; the gather for a strided
-            # one reads and writes the pixels it keeps; backward, the gradient of those pixels
+            # output is read once more where the two branches meet (the pixels a strided one
+            # keeps are read in place); backward, the gradient of those pixels
             # is added to the block input's gradient under that input's mask (3 reads, 1 write)
             # (a pre-activation block's bare projection is added to the convolution's output
             # instead: two reads and a write)
@@ -158,8 +159,6 @@ def conv_bytes(w, layers):
                 pool += rows * cout * 4.0 * 3
             else:
                 bn += rows * cout * 4.0 * (1 + 1 + 2 + 3)
-            if proj_step == 2:
-                unfold += rows * proj_c * 4.0 * 2
             pool += rows * proj_c * 4.0 * 4
         elif (w.skip_mask >> l) & 1 and w.preact:
             # identity shortcut of a pre-activation block: the sum two convolutions below is added
@@ -360,7 +359,8 @@ def run_workload(w, steps, warmup, kernel_timing=True):
                          mfma_tflops=flops[name] * steps / (tot * 1e-3) / 1e12)
             elif name in flops and tot > 0:
                 k.update(bound="mfma", achieved=flops[name] * steps / (tot * 1e-3) / 1e12,
-                         peak=PEAK_TFLOPS[w.gemm_dtype], unit="TFLOP/s",
+                         peak=PEAK_TFLOPS_SPLIT if w.n_conv and w.gemm_dtype == 0 and name != "conv_first"
+                         else PEAK_TFLOPS[w.gemm_dtype], unit="TFLOP/s",
                          algorithmic_flops_per_launch=flops[name] * steps / cnt)
             elif name in nbytes and tot > 0:
                 k.update(bound="hbm", achieved=nbytes[name] * steps / (tot * 1e-3) / 1e9,

@@ -259,7 +259,7 @@ int lsam_set_fused_step(lsam_ctx* ctx, int32_t on);
  *   [4], [5] columns of its weight matrix (fan-in) and its outputs
  *   [6] channels its projection shortcut reads (0: the layer closes no block with a projection;
  *       then three more products of [3] rows, [6] columns and [5] outputs belong to the layer)
- *   [7] pixel step of that projection (2: it reads every second pixel, through a gather) */
+ *   [7] pixel step of that projection (2: it reads every second pixel) */
 #define LSAM_LAYER_INFO_FIELDS 8
 #define LSAM_LAYER_DENSE 0
 #define LSAM_LAYER_HEAD 1

@@ -24,10 +24,10 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def net(dims, side, batch, K=2, stride=0, skip=0, proj=0, preact=0, bf16=0, pool=0):
+def net(dims, side, batch, K=2, stride=0, skip=0, proj=0, preact=0, bf16=0, pool=0, bn=1):
     n = len(dims) - 2
     return workloads.Workload("planes", K=K, dims=dims, batch=batch, n_conv=n, img_h=side[0], img_w=side[1],
-                              bn_mask=(1 << n) - 1, stride_mask=stride, skip_mask=skip, proj_mask=proj, preact=preact,
+                              bn_mask=(1 << n) - 1 if bn else 0, stride_mask=stride, skip_mask=skip, proj_mask=proj, preact=preact,
                               pool_mask=pool, global_avg_pool=1, gemm_dtype=bf16, tau=(2,) * K, rho=0.05, lr=0.02,
                               n_classes=dims[-1], data_seed=77)
 
@@ -38,7 +38,8 @@ def groups(w):
     for l, (fan_in, fo) in enumerate(w.layer_shapes):
         sizes = [fan_in * fo, fo]
         if l < w.n_conv:
-            sizes += [fo, fo]
+            if (w.bn_mask >> l) & 1:
+                sizes += [fo, fo]
             if (w.proj_mask >> l) & 1:
                 sizes += [fo * w.dims[l - 1], fo] + ([] if w.preact else [fo, fo])
         for n in sizes:
@@ -63,9 +64,17 @@ def step_both(w, X=None):
 
 def spread(w):
     """Initial parameters whose normalised layers keep three channels of four positive everywhere and
-    the fourth negative everywhere (gamma 0.25, beta +-1.5; shortcuts agree in sign)."""
+    the fourth negative everywhere (gamma 0.25, beta +-1.5; shortcuts agree in sign).  Without
+    normalisation: weights a fifth of their size and biases +-1, eight spreads from zero."""
     init = bn_away_from_zero(w, workloads.init_params(w))
     model = oracle_from(w.scaled(K=1, tau=(1,)), init).model
+    if not w.bn_mask:
+        at = 0
+        for fan_in, fo in w.layer_shapes[:w.n_conv]:
+            init[at:at + fan_in * fo] *= 0.2
+            at += fan_in * fo
+            init[at:at + fo] = np.where(np.arange(fo) % 4 == 3, -1.0, 1.0)
+            at += fo
     ranges = [(b1, b2) for b0, b1, b2 in model.bn_offsets.values()]
     ranges += [(p[3], p[4]) for p in model.proj_offsets.values()]
     for lo, hi in ranges:
@@ -98,6 +107,8 @@ NETS = {
     "pre-activation": dict(dims=(3, 32, 64, 64, 64, 64, 10), side=(16, 32), batch=65, stride=0b00010, skip=0b10100,
                            proj=0b00100, preact=1),
     "pools": dict(dims=(3, 32, 64, 64, 10), side=(16, 32), batch=129, pool=0b011),
+    # no normalisation: a kernel of its own writes the gradient's planes, below a pool and elsewhere
+    "pools, no normalisation": dict(dims=(3, 32, 64, 64, 64, 10), side=(16, 32), batch=129, pool=0b0011, bn=0),
 }
 
 

@@ -82,7 +82,7 @@ template <> __device__ __forceinline__ float get<__bf16>(const __bf16* p) {
 // blockIdx.z: one of several sums side by side, `zin` columns and `zout` results apart.
 // What bounds it is the chain of loads a wavefront waits for; sixteen wavefronts from 256 rows on
 // (512 rows of 64 columns, four replicas: 7.3 us with four wavefronts, 5.1 us with sixteen; below
-// 256 rows a wavefront has at most one round of loads more and the smaller launch is as fast).
+// 256 rows four wavefronts have at most sixteen loads each, four at a time, and stay).
 template <typename TD, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void bias_grad_kernel(const TD* __restrict__ dz, long long ld,
                                                             float* __restrict__ db,

@@ -380,6 +380,14 @@ struct Reader {
   }
 };
 
+// A result with three planes from its two sums, the products of the leading pieces and the other
+// five.  An infinite or NaN leading sum is the result: the leading piece of a finite number is finite,
+// of an infinite one the number itself, so these products overflow, or are infinite or NaN, where the
+// products of the numbers are, while the small ones may then be infinite with the other sign.
+__device__ __forceinline__ float joined_sums(float leading, float small) {
+  return __builtin_isfinite(leading) ? leading + small : leading;
+}
+
 template <int MASK, int N, int M, int I>
 struct Interleave {
   static __device__ __forceinline__ void run() {
@@ -664,7 +672,7 @@ __global__ __launch_bounds__(kThreads, OCC) void conv_gemm_kernel(Params p) {
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] += low[i][j][e];
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = joined_sums(acc[i][j][e], low[i][j][e]);
   }
 
   float* stage = reinterpret_cast<float*>((wave >> 1) ? st1 : st0) + (wave & 1) * (32 * EPI_PITCH);
@@ -1109,7 +1117,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_patch_kernel(Params p)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] += low[i][j][e];
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = joined_sums(acc[i][j][e], low[i][j][e]);
   float* stage = reinterpret_cast<float*>((wave >> 1) ? pa1 : pa0) + (wave & 1) * (32 * EPI_PITCH);
   store_tile<NP, TM, TN, ImgK<BM, NP, true>, MatK<BN, NP, false>>(p, acc, stage, m0 + wave * (TM * 32), n0, bat, piece, t_in, Ab,
                                                                   Bb, first * 16, nblk * 16, true);
@@ -1346,7 +1354,7 @@ __global__ __launch_bounds__(512, 2) void conv_split_wgrad_kernel(Params p) {
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[t][e] += low[t][e];
+    for (int e = 0; e < 16; ++e) acc[t][e] = joined_sums(acc[t][e], low[t][e]);
   // the sums of pixel groups half.. to those of groups 0..half - 1
 #pragma unroll
   for (int half = PG / 2; half >= 1; half /= 2) {

@@ -155,3 +155,59 @@ def test_infinite_operands(name):
             assert np.isclose(loss[i].item(), ol[i], rtol=1e-5)
             assert rel_l2(g.lsam_get_buffer(lsam.BUF_GRAD, i), o.last_g2[i]) <= 3e-6
     g.close()
+
+
+# x = m 2^e with a rounding to bfloat16 that goes up, so that the product of the leading pieces of two
+# such numbers is too large and the small products are negative
+M = 1 + 2.0**-7 - 2.0**-10
+
+
+@pytest.mark.parametrize("product", ["forward", "input gradient", "weight gradient"])
+@pytest.mark.parametrize("c0,c1,side,batch,stride", [
+    (32, 64, 16, 32, 0),         # patches, 64-wide
+    (32, 32, 16, 64, 0),         # patches, up to 32 columns
+    (16, 16, 32, 64, 0),         # 16 channels: weight gradient through the ring
+    (64, 64, 2, 1100, 0),        # images too small for a patch: the ring
+    (8, 8, 32, 90, 0),           # several taps per k-step
+    (64, 64, 32, 32, 0b10),      # stride 2, input gradient in pixel classes
+])
+def test_finite_operands_whose_products_overflow(c0, c1, side, batch, stride, product):
+    """Every term of the overflowing sums is positive and above the largest float, so each result is
+    +infinity, in the forward products (an infinite activation reaches the loss; NaN would end as the
+    ReLU's zero), in the input gradient (seen in the bias gradient of the layer below) and in the
+    weight gradient.  The other replica, of ordinary numbers, stays finite."""
+    w = net((c0, c1, c1, 10), (side, side), batch, stride=stride, bn=0).scaled(rho=0.0)
+    lab = np.ones((w.K, batch), np.int32)
+    ones = np.ones((w.K, batch, side, side, c0), np.float32)
+    shapes, rows = w.layer_shapes, batch * (side // (2 if stride else 1))**2
+
+    def run(x, w1, w2, w3):
+        """Gradient of replica 0 by layer, and the losses, with constant data and weights."""
+        X = ones * np.float32(M)
+        X[0] *= np.float32(x)
+        init = np.concatenate([np.concatenate([np.full(fi * fo, v, np.float32), np.zeros(fo, np.float32)])
+                               for (fi, fo), v in zip(shapes, (w1 * M, w2 * M, 0.0))])
+        init[-shapes[2][0] * 10 - 10:][:shapes[2][0]] = w3 * M      # class 0 of the dense layer
+        cfg, keep = lsam.config_from_workload(w)
+        g = lsam.Lsam(cfg, init, device=DEV, keep=keep)
+        loss = torch.zeros(w.K, device=DEV)
+        g.lsam_step(torch.from_numpy(X).to(DEV), torch.from_numpy(lab).to(DEV), loss)
+        grad = g.lsam_get_buffer(lsam.BUF_GRAD, 0)
+        g.close()
+        out, at = [], 0
+        for fi, fo in shapes:
+            out.append((grad[at:at + fi * fo].reshape(fo, fi), grad[at + fi * fo:at + fi * fo + fo]))
+            at += fi * fo + fo
+        return out, loss.cpu().numpy()
+
+    # the second layer's output is ordinary, its gradient comes down at 2^70 a pixel
+    up = 2.0**70 * rows
+    if product == "forward":             # 9 c0 terms of 2^140 in the first layer, of 2^70 in the other replica
+        _, loss = run(2.0**70, 2.0**70, 2.0**-80, 2.0**-10)
+        assert not np.isfinite(loss[0]) and np.isfinite(loss[1])
+    elif product == "input gradient":    # 2^70 2^70
+        grads, _ = run(1.0, 2.0**-70, 2.0**70, up)
+        assert np.all(grads[0][1] == np.inf)
+    else:                                # 2^70 2^70, activations of the first layer at 2^70
+        grads, _ = run(1.0, 2.0**70, 2.0**-70, up)
+        assert np.all(grads[1][0] == np.inf)

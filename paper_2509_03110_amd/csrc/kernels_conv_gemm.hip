@@ -184,27 +184,33 @@ struct ImgK {
   }
 };
 
-template <int R, int NP, bool IS_A>
+// TAIL: Kd may end inside a k-step with more values of the row behind it (a class of pixels of a stride-2
+// input gradient, followed by the next class's filters): they read as zeros.  The image's side is zero
+// there as well, but zero times an infinite filter is not.
+template <int R, int NP, bool TAIL>
 struct MatK {
   static constexpr bool KMAJOR = true;
   static constexpr int NLOAD = Shape<R>::NLOAD, BYTES = Shape<R>::BYTES;
   unsigned off[NLOAD];
+  int e;                                               // contraction index of this lane's unit
   __device__ __forceinline__ void init(const Params& p, int row0, int first_step, int tid) {
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int ld = IS_A ? p.ldA : p.ldB, rows = IS_A ? p.M : p.N;
+    const int u = (lane & 3) ^ ((lane >> 4) & 3);
+    e = first_step * 32 + u * 8;
 #pragma unroll
     for (int l = 0; l < NLOAD; ++l) {
       const int row = (wave * NLOAD + l) * 16 + (lane >> 2);
-      const int u = (lane & 3) ^ ((row >> 2) & 3);
-      off[l] = (row < R && row0 + row < rows) ? ((unsigned)(row0 + row) * ld + first_step * 32 + u * 8) * 2u : kOob;
+      off[l] = (row < R && row0 + row < p.N) ? ((unsigned)(row0 + row) * p.ldB + e) * 2u : kOob;
     }
   }
-  __device__ __forceinline__ void issue(const Params&, const __amdgpu_buffer_rsrc_t (&rs)[NP], lds_byte* tile, bool live) {
+  __device__ __forceinline__ void issue(const Params& p, const __amdgpu_buffer_rsrc_t (&rs)[NP], lds_byte* tile, bool live) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     lds_byte* dst = tile + wave * NLOAD * 1024;
+    const bool ok = live && (!TAIL || e < p.Kd);
+    if (TAIL) e += 32;
 #pragma unroll
     for (int l = 0; l < NLOAD; ++l) {
-      const unsigned at = live ? off[l] : kOob;
+      const unsigned at = ok ? off[l] : kOob;
 #pragma unroll
       for (int q = 0; q < NP; ++q)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rs[q], (__attribute__((address_space(3))) void*)(dst + q * BYTES + l * 1024),
@@ -213,7 +219,7 @@ struct MatK {
     }
   }
   static __device__ __forceinline__ float value(const Params& p, const unsigned short* base, int n, int k) {
-    return joined<NP>(base, (long long)n * (IS_A ? p.ldA : p.ldB) + k, IS_A ? p.planeA : p.planeB);
+    return joined<NP>(base, (long long)n * p.ldB + k, p.planeB);
   }
 };
 
@@ -497,7 +503,7 @@ enum Kind { kForward = 0, kForwardAnyC = 1, kWeightGrad = 2 };
 
 template <int NP, int KIND, int BM> struct PickA { typedef ImgK<BM, NP, KIND == kForward> type; };
 template <int NP, int BM> struct PickA<NP, kWeightGrad, BM> { typedef MatM<BM, NP> type; };
-template <int NP, int KIND, int BN> struct PickB { typedef MatK<BN, NP, false> type; };
+template <int NP, int KIND, int BN> struct PickB { typedef MatK<BN, NP, KIND == kForwardAnyC> type; };
 template <int NP, int BN> struct PickB<NP, kWeightGrad, BN> { typedef ImgM<BN, NP> type; };
 
 template <int NP, int KIND, int BM, int BN, int WM, int NSTAGE, int OCC>

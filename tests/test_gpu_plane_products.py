@@ -211,3 +211,37 @@ def test_finite_operands_whose_products_overflow(c0, c1, side, batch, stride, pr
     else:                                # 2^70 2^70, activations of the first layer at 2^70
         grads, _ = run(1.0, 2.0**70, 2.0**-70, up)
         assert np.all(grads[1][0] == np.inf)
+
+
+@pytest.mark.parametrize("bf16", [0, 1])
+@pytest.mark.parametrize("c,batch", [(8, 350), (16, 90)])
+def test_infinite_filter_stays_in_its_class_of_pixels(c, batch, bf16):
+    """An infinite filter of a stride-2 layer enters the input gradient of the pixels its tap meets and of
+    no other (with 8 or 16 channels the classes of pixels share k-steps).  The filter, -infinity at
+    row 1, column 2, belongs to an output that is dead, and the pixels it meets are dead in the
+    layer below, whose ReLU drops the NaN of 0 times infinity: every gradient is what it is with a
+    filter of zeros."""
+    w = net((c, c, c, 10), (32, 32), batch, stride=0b10, bf16=bf16, bn=0).scaled(rho=0.0)
+    X = np.ones((w.K, batch, 32, 32, c), np.float32)
+    X[:, :, 0::2, 1::2] = -1.0                                     # seen by (1, 2): even rows, odd columns
+    lab = np.zeros((w.K, batch), np.int32)
+    n = 9 * c * c
+    grads = []
+    for filt in (0.0, -np.inf):
+        rng = np.random.default_rng(3)
+        init = rng.uniform(0.01, 0.1, w.d).astype(np.float32)
+        first, second = init[:n].reshape(c, 9, c), init[n + c:2 * n + c].reshape(c, 9, c)
+        first[:, [0, 1, 2, 3, 5, 6, 7, 8]] = 0.0                   # the pixel itself only
+        init[n:n + c] = 0.0
+        second[0] = 0.0
+        second[0, 5] = filt
+        init[2 * n + c] = -1.0                                     # output 0: dead
+        cfg, keep = lsam.config_from_workload(w)
+        g = lsam.Lsam(cfg, init, device=DEV, keep=keep)
+        loss = torch.zeros(w.K, device=DEV)
+        g.lsam_step(torch.from_numpy(X).to(DEV), torch.from_numpy(lab).to(DEV), loss)
+        assert np.all(np.isfinite(loss.cpu().numpy()))
+        grads.append(g.lsam_get_buffer(lsam.BUF_GRAD, 0))
+        g.close()
+    # (sums of 9e4 terms in another order, sqrt(9e4) 2^-24, where infinite operands take the slow path)
+    assert np.any(grads[0][:n]) and rel_l2(grads[1], grads[0]) <= 2e-5

@@ -62,11 +62,9 @@ int launch_gram_dot(const float* G1, const float* G2, int64_t stride, int64_t n,
 // the tree are fixed-order, so the result is run-to-run deterministic).
 // `restart` (may be null): the per-replica marks described at launch_center; this kernel, which
 // runs once per step before anything touches the iterate sums, counts every mark down by one.
-// `nonfinite` (may be null): the plane writers' flag, lowered here, between the two passes (each
-// pass writes all the planes it reads).
 void launch_norm_finish(const double* partials, int nblk, int64_t partials_stride, int K, float rho, float gamma,
                         float* norms, float* scale, const float* loss_rows, int B,
-                        float* loss_out, hipStream_t s, int32_t* restart = nullptr, int* nonfinite = nullptr);
+                        float* loss_out, hipStream_t s, int32_t* restart = nullptr);
 // x~ = x + scale[k] * g.  Writes fp32 (xt_f32), or, if xt_bf16 is non-null, the bf16 operand
 // copy of the weight matrices in the blocked layout described by `map` (replica stride
 // `shadow_stride` elements).
@@ -205,7 +203,7 @@ struct PlaneImage {
 //   pixels, Kd = taps * C, other [N][ld] with zeros from Kd to the next multiple of 32.
 // wgrad = 1: C[m, (tap, c)] = sum over output pixels k of other[k][m] * image(k, tap, c), other
 //   [Kd][M] (ld = M), N = taps * C.
-// Epilogues as in GemmDesc (bias, mask: fp32).  `nonfinite`: the flag the plane writers raise.
+// Epilogues as in GemmDesc (bias, mask: fp32).
 struct ConvGemmDesc {
   int np, wgrad;
   PlaneImage image;
@@ -217,7 +215,6 @@ struct ConvGemmDesc {
   const float* mask; int64_t strideMask; int ldMask;
   float* splitk_ws; size_t splitk_bytes;
   double* sumsq; int64_t sumsq_stride;
-  const int* nonfinite;
   // 2: the input gradient of a stride-2 convolution.  The image is the output gradient [oH][oW], C and
   // the mask are images of [2 oH][2 oW].  An input pixel meets the taps of its row's and its
   // column's parity only: four classes of pixels, each a convolution of 1, 2, 2 or 4 taps whose filters
@@ -226,8 +223,8 @@ struct ConvGemmDesc {
 };
 int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots = nullptr);   // 0, or -1: not served
 size_t conv_gemm_splitk_bytes(const ConvGemmDesc& d);
-// Planes of n consecutive floats (n % 4 == 0).  *nonfinite is set to 1 when np = 3 and a value is infinite.
-int launch_split_planes(const float* src, uint16_t* dst, int np, int64_t plane, int64_t n, int* nonfinite, hipStream_t s);
+// Planes of n consecutive floats (n % 4 == 0).
+int launch_split_planes(const float* src, uint16_t* dst, int np, int64_t plane, int64_t n, hipStream_t s);
 // One filter bank [rows][cols] (row pitch ldw) at `src` of every replica's parameters as the plane
 // products read it, `dst` elements into every plane.  taps = 0: [K][rows][ldp], zeros from cols on
 // (cols, ldw, ldp multiples of 4); taps = 1 or 9: mirrored and transposed, `cols` counting one tap's
@@ -243,7 +240,7 @@ struct FilterBank {
 int filter_bank_blocks(const FilterBank& f);
 // All n banks of the table (device memory) for K replicas; blocks: workgroups of all of them.
 int launch_filters(const float* params, int64_t strideParams, const FilterBank* banks, int n, int blocks, uint16_t* dst,
-                   int np, int64_t plane, int K, int* nonfinite, hipStream_t s);
+                   int np, int64_t plane, int K, hipStream_t s);
 
 // Softmax cross-entropy, forward and backward.  logits [K,B,ld] fp32; labels [K,B];
 // dz = (softmax - onehot)/B: fp32 [K,B,ld_dz] row-major with zeros in the padded columns, or
@@ -284,11 +281,11 @@ int launch_head_weight_grad(const float* dz, int ld_dz, const float* A, int ldA,
 // of 4 where stated).
 // col[k][(b,i,j)][(u,v,c)] = X[k][b][i+u-1][j+v-1][c], zero outside the image and in the
 // padding columns 9C..ld-1 (ld % 4 == 0; any C): np = 0 as floats, otherwise as np bfloat16 planes
-// `plane` elements apart (np = 3 raises *nonfinite on an infinite value).
+// `plane` elements apart.
 // `stride` 1 or 2: the image is [stride H][stride W][C] and col row (b,i,j) holds the window
 // around pixel (stride i, stride j); H x W is the convolution's output.
 int launch_unfold3x3(const float* X, int64_t strideX, void* col, int np, int64_t plane, int ld, int K,
-                     int B, int H, int W, int C, int stride, int* nonfinite, hipStream_t s);
+                     int B, int H, int W, int C, int stride, hipStream_t s);
 // dX[k][b][i][j][c] = sum_{u,v} dcol[k][(b,i-u+1,j-v+1)][(u,v,c)], taps added in (u,v) order,
 // set to zero where mask (same shape as dX, may be null) is not positive.  C % 4 == 0.
 int launch_fold3x3(const float* dcol, int64_t strideCol, int ld, float* dX, const float* mask,
@@ -324,7 +321,7 @@ int launch_first_conv_wgrad(const float* X, const float* dout, float* partial, f
 // (or null: planes only), dgamma and dbeta read from grad + k * strideParams at the same offsets.  -1: shape not supported.
 // Where a kernel also writes its fp32 result as plane tensors (np = 0: it does not).
 struct PlaneOut {
-  uint16_t* p = nullptr; int np = 0; int64_t plane = 0; int* nonfinite = nullptr;
+  uint16_t* p = nullptr; int np = 0; int64_t plane = 0;
 };
 // Shortcut of a residual block (He et al., CIFAR variant, parameter-free): the block input
 // src [K][B][step H][step W][Cs] (replica stride `stride` floats) enters the block output

@@ -20,21 +20,18 @@ typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
 
 // Writes 4 values as planes at element `at` of each.
 template <int NP>
-__device__ __forceinline__ void put_planes(unsigned short* p, long long plane, long long at, const f32x4& v,
-                                           int* nonfinite) {
+__device__ __forceinline__ void put_planes(unsigned short* p, long long plane, long long at, const f32x4& v) {
   if constexpr (NP > 0) {
     u16x4 w[NP];
-    bool inf = false;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       unsigned short t[NP];
-      inf |= split_planes<NP>(v[r], t);
+      split_planes<NP>(v[r], t);
 #pragma unroll
       for (int q = 0; q < NP; ++q) w[q][r] = t[q];
     }
 #pragma unroll
     for (int q = 0; q < NP; ++q) *reinterpret_cast<u16x4*>(p + q * plane + at) = w[q];
-    if (NP > 1 && inf) *nonfinite = 1;
   }
 }
 
@@ -51,8 +48,7 @@ struct ImgShape {
 template <bool VEC, int NP>
 __global__ __launch_bounds__(kThreads) void unfold3x3_kernel(const float* __restrict__ X,
                                                              void* __restrict__ col, ImgShape sh,
-                                                             long long strideX, long long plane,
-                                                             int* __restrict__ nonfinite) {
+                                                             long long strideX, long long plane) {
   const long long idx = (long long)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= sh.total) return;
   const int words = sh.ld / 4;
@@ -87,7 +83,7 @@ __global__ __launch_bounds__(kThreads) void unfold3x3_kernel(const float* __rest
     }
   }
   if constexpr (NP == 0) *reinterpret_cast<f32x4*>(static_cast<float*>(col) + idx * 4) = o;
-  else put_planes<NP>(static_cast<unsigned short*>(col), plane, idx * 4, o, nonfinite);
+  else put_planes<NP>(static_cast<unsigned short*>(col), plane, idx * 4, o);
 }
 
 // Adjoint of the unfold: dX[b,y,x,c] = sum over the taps (u,v) and output positions (i,j) with
@@ -141,8 +137,7 @@ struct PoolShape {
 template <int NP>
 __global__ __launch_bounds__(kThreads) void maxpool2_kernel(const float* __restrict__ A,
                                                             float* __restrict__ P, PoolShape sh,
-                                                            unsigned short* __restrict__ planes, long long plane,
-                                                            int* __restrict__ nonfinite) {
+                                                            unsigned short* __restrict__ planes, long long plane) {
   const long long idx = (long long)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= sh.cells) return;
   const int words = sh.C / 4;
@@ -164,7 +159,7 @@ __global__ __launch_bounds__(kThreads) void maxpool2_kernel(const float* __restr
     m[r] = v3[r] > m[r] ? v3[r] : m[r];
   }
   *reinterpret_cast<f32x4*>(P + cell * sh.C + c) = m;
-  put_planes<NP>(planes, plane, cell * sh.C + c, m, nonfinite);
+  put_planes<NP>(planes, plane, cell * sh.C + c, m);
 }
 
 // Backward of ReLU followed by the pool: dA[window] = dP where A is the window's first
@@ -644,7 +639,7 @@ __global__ __launch_bounds__(kThreads) void bn_apply_kernel(const float* __restr
                                                             long long bet_off, float* __restrict__ out,
                                                             long long rows, int C, long long total,
                                                             Shortcut sc, unsigned short* __restrict__ planes,
-                                                            long long plane, int* __restrict__ nonfinite) {
+                                                            long long plane) {
   const long long idx = (long long)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= total) return;
   const int words = C / 4;
@@ -672,7 +667,7 @@ __global__ __launch_bounds__(kThreads) void bn_apply_kernel(const float* __restr
 #pragma unroll
   for (int r = 0; r < 4; ++r) y[r] = y[r] > 0.f ? y[r] : 0.f;
   *reinterpret_cast<f32x4*>(out + idx * 4) = y;
-  put_planes<NP>(planes, plane, idx * 4, y, nonfinite);
+  put_planes<NP>(planes, plane, idx * 4, y);
 }
 
 // The shortcut's share of the block input's gradient: dIn[b][st i][st j][c] += dY[b][i][j][c]
@@ -814,7 +809,7 @@ __global__ __launch_bounds__(kThreads) void bn_backward_apply_kernel(
     const float* Z, const float* dY, float* dZ, const float* __restrict__ stats,
     const float* __restrict__ params, const float* __restrict__ grad, long long strideParams,
     long long gam_off, long long bet_off, long long rows, int C, long long total, const float* add,
-    unsigned short* __restrict__ planes, long long plane, int* __restrict__ nonfinite) {
+    unsigned short* __restrict__ planes, long long plane) {
   const long long idx = (long long)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= total) return;
   const int words = C / 4;
@@ -831,7 +826,7 @@ __global__ __launch_bounds__(kThreads) void bn_backward_apply_kernel(
   f32x4 o = ga * inv * (dy - dbe * inv_n - xh * (dga * inv_n));
   if (add != nullptr) o += *reinterpret_cast<const f32x4*>(add + idx * 4);
   if (dZ != nullptr) *reinterpret_cast<f32x4*>(dZ + idx * 4) = o;
-  put_planes<NP>(planes, plane, idx * 4, o, nonfinite);
+  put_planes<NP>(planes, plane, idx * 4, o);
 }
 
 unsigned blocks_for(long long total) { return (unsigned)((total + kThreads - 1) / kThreads); }
@@ -839,13 +834,13 @@ unsigned blocks_for(long long total) { return (unsigned)((total + kThreads - 1) 
 }  // namespace
 
 int launch_unfold3x3(const float* X, int64_t strideX, void* col, int np, int64_t plane, int ld, int K,
-                     int B, int H, int W, int C, int stride, int* nonfinite, hipStream_t s) {
+                     int B, int H, int W, int C, int stride, hipStream_t s) {
   ImgShape sh{H, W, C, ld, (long long)B * H * W, 0, stride};
   sh.total = (long long)K * sh.rows * (ld / 4);
   if (ld % 4 || ld < 9 * C || sh.total <= 0 || sh.total >= (1ll << 31) * kThreads || stride < 1 || stride > 2)
     return -1;
   const unsigned grid = blocks_for(sh.total);
-  auto run = [&](auto kernel) { kernel<<<grid, kThreads, 0, s>>>(X, col, sh, strideX, plane, nonfinite); };
+  auto run = [&](auto kernel) { kernel<<<grid, kThreads, 0, s>>>(X, col, sh, strideX, plane); };
   if (C % 4 == 0)
     run(np == 0 ? unfold3x3_kernel<true, 0> : np == 1 ? unfold3x3_kernel<true, 1> : unfold3x3_kernel<true, 3>);
   else
@@ -969,7 +964,7 @@ int launch_bn_forward(const float* Z, float* scratch, float* stats, const float*
   const long long total = (long long)K * rows * (C / 4);
   auto run = [&](auto kernel) {
     kernel<<<blocks_for(total), kThreads, 0, s>>>(Z, stats, params, strideParams, gam_off, bet_off, out, rows, C, total, sc,
-                                                  o.p, o.plane, o.nonfinite);
+                                                  o.p, o.plane);
   };
   run(o.np == 0 ? bn_apply_kernel<0> : o.np == 1 ? bn_apply_kernel<1> : bn_apply_kernel<3>);
   return 0;
@@ -1013,7 +1008,7 @@ void launch_bn_backward_apply(const float* Z, const float* dY, float* dZ, const 
   const long long total = (long long)K * rows * (C / 4);
   auto run = [&](auto kernel) {
     kernel<<<blocks_for(total), kThreads, 0, s>>>(Z, dY, dZ, stats, params, grad, strideParams, gam_off, bet_off, rows, C,
-                                                  total, add, o.p, o.plane, o.nonfinite);
+                                                  total, add, o.p, o.plane);
   };
   run(o.np == 0 ? bn_backward_apply_kernel<0> : o.np == 1 ? bn_backward_apply_kernel<1> : bn_backward_apply_kernel<3>);
 }
@@ -1031,7 +1026,7 @@ int launch_colsum_partials(const float* A, int64_t rows, int N, int K, float* pa
 int launch_maxpool2(const float* A, float* P, int64_t images, int H, int W, int C, const PlaneOut& o, hipStream_t s) {
   PoolShape sh{H / 2, W / 2, C, images * (H / 2) * (W / 2) * (C / 4)};
   if (C % 4 || H % 2 || W % 2 || sh.cells <= 0 || sh.cells >= (1ll << 31) * kThreads) return -1;
-  auto run = [&](auto kernel) { kernel<<<blocks_for(sh.cells), kThreads, 0, s>>>(A, P, sh, o.p, o.plane, o.nonfinite); };
+  auto run = [&](auto kernel) { kernel<<<blocks_for(sh.cells), kThreads, 0, s>>>(A, P, sh, o.p, o.plane); };
   run(o.np == 0 ? maxpool2_kernel<0> : o.np == 1 ? maxpool2_kernel<1> : maxpool2_kernel<3>);
   return 0;
 }

@@ -9,10 +9,10 @@
 //           nine cross products, smallest first; what is left out is below 2^-24 of |a||b|, under
 //           the rounding of the fp32 accumulation itself, so this is fp32 arithmetic on units that
 //           do 16 times the fp32 matrix rate (157 TFLOP/s nominal): six products leave 2.7 times.
-// Infinite operands do not split into a sum that multiplies like infinity (inf - inf); the
-// kernel that writes the planes raises a flag when it meets one, and a launch that finds the flag
-// raised forms its results from the re-joined fp32 values element by element (slow, and only
-// ever in the steps in which a diverging run overflows).
+// An infinite number, or NaN, is its own leading piece (the others are zero), so what infinite and
+// overflowing operands come to is in the sum of the leading products; see join_sums.
+// The split is exact from 2^-110 up: bfloat16 ends at 2^-133, so below that the last piece keeps
+// what lies above 2^-134 (an operand is then off by at most 2^-134; below 2^-134 it is zero).
 //
 // The kernel is the ring of the dense bf16 products: buffer_load ... lds straight into a ring of
 // NSTAGE k-steps of 32, one barrier per k-step, fragments read one half k-step ahead.  What differs
@@ -63,7 +63,6 @@ struct Params {
   double* sumsq; long long strideSumsq;
   int out_step, out_i, out_j;                          // see ConvGemmDesc
   int ksplit, steps_per_piece; float* partial; long long stridePartial; int ldP;
-  const int* nonfinite;
 };
 
 constexpr int waitcnt(int vm, int lgkm) {
@@ -84,15 +83,6 @@ __device__ __forceinline__ void decode(int p, const Geometry& g, int& b, int& i,
   j = p - q * g.oW;
   b = q / g.oH;
   i = q - b * g.oH;
-}
-
-// The value of element `at` of a plane tensor.
-template <int NP>
-__device__ __forceinline__ float joined(const unsigned short* p, long long at, long long plane) {
-  float v = 0.f;
-#pragma unroll
-  for (int q = NP - 1; q >= 0; --q) v += __builtin_bit_cast(float, (unsigned)p[at + q * plane] << 16);
-  return v;
 }
 
 // ---- operand loaders ------------------------------------------------------------------------------
@@ -173,15 +163,6 @@ struct ImgK {
       e0 += 32;
     }
   }
-  static __device__ __forceinline__ float value(const Params& p, const unsigned short* base, int m, int k) {
-    const Geometry& g = p.g;
-    int b, i, j;
-    decode(m, g, b, i, j);
-    const int tap = k / g.C, ch = k - tap * g.C;
-    const int y = g.st * i + g.du0 + tap / g.nv, x = g.st * j + g.dv0 + tap % g.nv;
-    if ((unsigned)y >= (unsigned)g.sH || (unsigned)x >= (unsigned)g.sW) return 0.f;
-    return joined<NP>(base, (((long long)b * g.sH + y) * g.sW + x) * g.C + ch, p.planeA);
-  }
 };
 
 // TAIL: Kd may end inside a k-step with more values of the row behind it (a class of pixels of a stride-2
@@ -218,9 +199,6 @@ struct MatK {
       if (off[l] != kOob) off[l] += 64;
     }
   }
-  static __device__ __forceinline__ float value(const Params& p, const unsigned short* base, int n, int k) {
-    return joined<NP>(base, (long long)n * p.ldB + k, p.planeB);
-  }
 };
 
 // A operand, k selects the row of a matrix [Kd][ldA].
@@ -253,9 +231,6 @@ struct MatM {
                                                  16, at, 0, 0, 0);
       if (off[l] != kOob) off[l] += (unsigned)p.ldA * 64u;
     }
-  }
-  static __device__ __forceinline__ float value(const Params& p, const unsigned short* base, int m, int k) {
-    return joined<NP>(base, (long long)k * p.ldA + m, p.planeA);
   }
 };
 
@@ -331,15 +306,6 @@ struct ImgM {
       b[q] += db + ci;
     }
   }
-  static __device__ __forceinline__ float value(const Params& p, const unsigned short* base, int n, int k) {
-    const Geometry& g = p.g;
-    int bb, ii, jj;
-    decode(k, g, bb, ii, jj);
-    const int tap = n / g.C, ch = n - tap * g.C;
-    const int y = g.st * ii + g.du0 + tap / g.nv, x = g.st * jj + g.dv0 + tap % g.nv;
-    if ((unsigned)y >= (unsigned)g.sH || (unsigned)x >= (unsigned)g.sW) return 0.f;
-    return joined<NP>(base, (((long long)bb * g.sH + y) * g.sW + x) * g.C + ch, p.planeB);
-  }
 };
 
 // Reads of one wavefront's fragments: T fragments of 32 rows x 16 k, of every plane.
@@ -386,12 +352,23 @@ struct Reader {
   }
 };
 
-// A result with three planes from its two sums, the products of the leading pieces and the other
-// five.  An infinite or NaN leading sum is the result: the leading piece of a finite number is finite,
-// of an infinite one the number itself, so these products overflow, or are infinite or NaN, where the
-// products of the numbers are, while the small ones may then be infinite with the other sign.
-__device__ __forceinline__ float joined_sums(float leading, float small) {
-  return __builtin_isfinite(leading) ? leading + small : leading;
+// Results with three planes from their two sums, the products of the leading pieces and the other
+// five: `leading` becomes both.  An infinite leading sum (or NaN) is the result: the leading piece of a
+// finite number is finite, of an infinite one the number itself, so these products overflow, or are
+// infinite or NaN, where the products of the numbers are, while the small ones may then be infinite
+// with the other sign.  (One look at the largest of sixteen: a compare and a choice for each value cost
+// 16-channel layers 1.3 %.)
+__device__ __forceinline__ void join_sums(f32x16& leading, f32x16& small) {
+  float most = 0.f;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) most = __builtin_fmaxf(most, __builtin_fabsf(leading[e]));
+  if (__builtin_expect(__builtin_isinf(most), 0)) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+      if (__builtin_isinf(leading[e])) small[e] = 0.f;
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) leading[e] += small[e];
 }
 
 template <int MASK, int N, int M, int I>
@@ -407,12 +384,9 @@ struct Interleave {
 // Writes a wavefront's TM x TN blocks of 32 x 32 results, rows m0.., columns n0.., as the launch asks:
 // the wavefront passes 32-row strips through its private piece of LDS, `stage`, and writes rows,
 // consecutive lanes on consecutive 16 bytes (bias and ReLU mask are read the same way).
-// kbeg, klen: the range of the contraction the results cover, for the slow path of infinite
-// operands; by_channel: that range counts channels (every tap of them) instead of (tap, channel).
-template <int NP, int TM, int TN, typename OpA, typename OpB>
+template <int TM, int TN>
 __device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[TM][TN], float* stage, int m0, int n0, int bat,
-                                           int piece, int t_in, const unsigned short* Ab, const unsigned short* Bb, int kbeg,
-                                           int klen, bool by_channel) {
+                                           int piece, int t_in) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, h = lane >> 5;
   const bool split_mode = p.ksplit > 1;
   float* C = split_mode ? p.partial + (long long)piece * p.stridePartial + (long long)bat * p.M * p.ldP
@@ -422,7 +396,6 @@ __device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[
   const bool relu = !split_mode && p.epilogue == EPI_BIAS_RELU;
   const bool masked = !split_mode && p.epilogue == EPI_MASK;
   const float* mask = masked ? p.mask + (long long)bat * p.strideMask : nullptr;
-  const bool slow = NP > 1 && *p.nonfinite != 0;
   constexpr int PITCH = TN * 32 + 4;
   constexpr int LANES_PER_ROW = TN * 8;
   constexpr int ROWS_PER_PASS = 64 / LANES_PER_ROW;
@@ -433,6 +406,10 @@ __device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[
   float ssq = 0.f;
   f32x4 bv = {0.f, 0.f, 0.f, 0.f};
   if (has_bias && n < p.N) bv = *reinterpret_cast<const f32x4*>(p.bias + (long long)bat * p.strideBias + n);
+  // Waited for here: a wait in front of the sum of every pass would also wait for the stores of the pass
+  // before (16 channels at 32 x 32 with three planes, 4 replicas of 128: 40.4 us a launch so, 37.9 us here;
+  // patches of 64 channels with one plane 12 % of the launch).
+  __builtin_amdgcn_s_waitcnt(waitcnt(0, 15));
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
 #pragma unroll
@@ -450,22 +427,6 @@ __device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[
       const int m = m0 + i * 32 + rr;
       if (rr < 32 && rsub < ROWS_PER_PASS && m < p.M && n < p.N) {       // N is a multiple of 4
         f32x4 v = *reinterpret_cast<const f32x4*>(stage + rr * PITCH + c4);
-        if constexpr (NP > 1) {
-          if (__builtin_expect(slow, 0)) {
-            const int taps = by_channel ? p.g.nu * p.g.nv : 1;
-            const int kend = kbeg + klen < p.Kd ? kbeg + klen : p.Kd;
-#pragma unroll 1
-            for (int r = 0; r < 4; ++r) {
-              float s = 0.f;
-#pragma unroll 1
-              for (int tap = 0; tap < taps; ++tap)
-#pragma unroll 1
-                for (int k = kbeg; k < kend; ++k)
-                  s = __builtin_fmaf(OpA::value(p, Ab, m, tap * p.g.C + k), OpB::value(p, Bb, n + r, tap * p.g.C + k), s);
-              if (r == 0) v[0] = s; else if (r == 1) v[1] = s; else if (r == 2) v[2] = s; else v[3] = s;
-            }
-          }
-        }
         v += bv;
         int row = m;
         if (p.out_step > 1) {
@@ -677,12 +638,11 @@ __global__ __launch_bounds__(kThreads, OCC) void conv_gemm_kernel(Params p) {
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = joined_sums(acc[i][j][e], low[i][j][e]);
+        join_sums(acc[i][j], low[i][j]);
   }
 
   float* stage = reinterpret_cast<float*>((wave >> 1) ? st1 : st0) + (wave & 1) * (32 * EPI_PITCH);
-  store_tile<NP, TM, TN, OpA, OpB>(p, acc, stage, m0 + wm0, n0 + wn0, bat, piece, t_in, Ab, Bb, first * 32, ksteps * 32, false);
+  store_tile(p, acc, stage, m0 + wm0, n0 + wn0, bat, piece, t_in);
 }
 
 // A uniform value the compiler may not compute with ahead of time: without it the addresses of all
@@ -922,8 +882,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_patch_kernel(Params p) {
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   float* stage = reinterpret_cast<float*>((wave >> 1) ? pa1 : pa0) + (wave & 1) * (32 * EPI_PITCH);
-  store_tile<NP, TM, TN, ImgK<BM, NP, true>, MatK<BN, NP, false>>(p, acc, stage, m0 + wm0, n0, bat, piece, t_in, Ab, Bb,
-                                                                  first * 32, nblk * 32, true);
+  store_tile(p, acc, stage, m0 + wm0, n0, bat, piece, t_in);
 }
 
 // The same with three planes.  A workgroup takes TM x 128 pixels and blocks of 16 channels (one
@@ -1122,11 +1081,9 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_patch_kernel(Params p)
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = joined_sums(acc[i][j][e], low[i][j][e]);
+      join_sums(acc[i][j], low[i][j]);
   float* stage = reinterpret_cast<float*>((wave >> 1) ? pa1 : pa0) + (wave & 1) * (32 * EPI_PITCH);
-  store_tile<NP, TM, TN, ImgK<BM, NP, true>, MatK<BN, NP, false>>(p, acc, stage, m0 + wave * (TM * 32), n0, bat, piece, t_in, Ab,
-                                                                  Bb, first * 16, nblk * 16, true);
+  store_tile(p, acc, stage, m0 + wave * (TM * 32), n0, bat, piece, t_in);
 }
 
 // ---- weight gradient of 3x3 layers with stride 1, three planes, image patches in LDS ------------------
@@ -1359,8 +1316,7 @@ __global__ __launch_bounds__(512, 2) void conv_split_wgrad_kernel(Params p) {
   asm volatile("" ::: "memory");
 #pragma unroll
   for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[t][e] = joined_sums(acc[t][e], low[t][e]);
+    join_sums(acc[t], low[t]);
   // the sums of pixel groups half.. to those of groups 0..half - 1
 #pragma unroll
   for (int half = PG / 2; half >= 1; half /= 2) {
@@ -1383,9 +1339,7 @@ __global__ __launch_bounds__(512, 2) void conv_split_wgrad_kernel(Params p) {
   }
   const int m = m0 + ob * 32 + (lane & 31);
   if (pg == 0 && m < p.M) {
-    const bool slow = *p.nonfinite != 0;
     float* C = p.partial + (long long)piece * p.stridePartial + ((long long)bat * p.M + m) * p.ldP;
-    const int kbeg = first * PX, kend = (first + n) * PX < p.Kd ? (first + n) * PX : p.Kd;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       if (tg * NT + t >= 9) continue;
@@ -1393,16 +1347,6 @@ __global__ __launch_bounds__(512, 2) void conv_split_wgrad_kernel(Params p) {
       for (int q = 0; q < 4; ++q) {
         const int c = (tg * NT + t) * g.C + c0 + q * 8 + (lane >> 5) * 4;
         f32x4 v = {acc[t][q * 4], acc[t][q * 4 + 1], acc[t][q * 4 + 2], acc[t][q * 4 + 3]};
-        if (__builtin_expect(slow, 0)) {
-#pragma unroll 1
-          for (int r = 0; r < 4; ++r) {
-            float sum = 0.f;
-#pragma unroll 1
-            for (int k = kbeg; k < kend; ++k)
-              sum = __builtin_fmaf(MatM<64, NP>::value(p, Ab, m, k), ImgM<128, NP>::value(p, Bb, c + r, k), sum);
-            if (r == 0) v[0] = sum; else if (r == 1) v[1] = sum; else if (r == 2) v[2] = sum; else v[3] = sum;
-          }
-        }
         *reinterpret_cast<f32x4*>(C + c) = v;
       }
     }
@@ -1443,22 +1387,20 @@ template __global__ void conv_split_wgrad_kernel<1, 64, 9>(Params);
 // dst planes of n values (a multiple of 4), 4 to a thread.  Bound by its (4 + 2 NP) bytes a value.
 template <int NP>
 __global__ __launch_bounds__(kThreads) void split_kernel(const float* __restrict__ src, unsigned short* __restrict__ dst,
-                                                         long long plane, long long words, int* __restrict__ nonfinite) {
+                                                         long long plane, long long words) {
   const long long idx = (long long)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= words) return;
   const f32x4 v = *reinterpret_cast<const f32x4*>(src + idx * 4);
   u16x4 o[NP];
-  bool inf = false;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     unsigned short t[NP];
-    inf |= split_planes<NP>(v[r], t);
+    split_planes<NP>(v[r], t);
 #pragma unroll
     for (int q = 0; q < NP; ++q) o[q][r] = t[q];
   }
 #pragma unroll
   for (int q = 0; q < NP; ++q) *reinterpret_cast<u16x4*>(dst + q * plane + idx * 4) = o[q];
-  if (NP > 1 && inf) *nonfinite = 1;
 }
 
 // Planes of all filter banks of a model, one launch (a launch per bank and pass cost more than
@@ -1470,8 +1412,7 @@ __global__ __launch_bounds__(kThreads) void split_kernel(const float* __restrict
 template <int NP>
 __global__ __launch_bounds__(kThreads) void filters_kernel(const float* __restrict__ params, long long strideParams,
                                                            const FilterBank* __restrict__ banks, int n,
-                                                           unsigned short* __restrict__ dst, long long plane, int K,
-                                                           int* __restrict__ nonfinite) {
+                                                           unsigned short* __restrict__ dst, long long plane) {
   int lo = 0, hi = n - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) / 2;
@@ -1482,7 +1423,6 @@ __global__ __launch_bounds__(kThreads) void filters_kernel(const float* __restri
   const int block = blockIdx.x - f.first;
   const long long k = blockIdx.y;
   const float* W = params + k * strideParams + f.src;
-  bool inf = false;
   if (f.taps == 0) {
     const int words = f.ldp / 4;
     const int idx = block * kThreads + threadIdx.x;
@@ -1494,7 +1434,7 @@ __global__ __launch_bounds__(kThreads) void filters_kernel(const float* __restri
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         unsigned short b[NP];
-        inf |= split_planes<NP>(v[r], b);
+        split_planes<NP>(v[r], b);
 #pragma unroll
         for (int q = 0; q < NP; ++q) t[q][r] = b[q];
       }
@@ -1520,7 +1460,7 @@ __global__ __launch_bounds__(kThreads) void filters_kernel(const float* __restri
       const int c = cb + y + r;
       if (c >= f.cols) continue;
       unsigned short b[NP];
-      inf |= split_planes<NP>(tile[x][y + r], b);
+      split_planes<NP>(tile[x][y + r], b);
       unsigned short* row = dst + f.dst + (k * f.cols + c) * f.ldp;
       if (ob + x < f.rows) {
 #pragma unroll
@@ -1534,7 +1474,6 @@ __global__ __launch_bounds__(kThreads) void filters_kernel(const float* __restri
       }
     }
   }
-  if (NP > 1 && inf) *nonfinite = 1;
 }
 
 unsigned blocks_for(long long n) { return (unsigned)((n + kThreads - 1) / kThreads); }
@@ -1719,7 +1658,6 @@ int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots) {
     return -1;
   if (d.epilogue == EPI_MASK && (d.ldMask % 4 || d.strideMask % 4 || ((uintptr_t)d.mask & 15))) return -1;
   if ((d.epilogue == EPI_BIAS || d.epilogue == EPI_BIAS_RELU) && (((uintptr_t)d.bias & 15) || d.strideBias % 4)) return -1;
-  if (d.np > 1 && d.nonfinite == nullptr) return -1;
   Params p{};
   const unsigned image_bytes = (unsigned)(img_elems * 2), other_bytes = (unsigned)(rows * d.ld * 2);
   if (!d.wgrad) {
@@ -1738,7 +1676,6 @@ int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots) {
   p.bias = d.bias; p.strideBias = d.strideBias;
   p.mask = d.mask; p.strideMask = d.strideMask; p.ldMask = d.ldMask;
   p.sumsq = d.sumsq; p.strideSumsq = d.sumsq_stride;
-  p.nonfinite = d.nonfinite;
   ConvPlan pl = conv_plan(d);
   const bool room = d.splitk_ws != nullptr && d.splitk_bytes >= pl.ws_bytes && ((uintptr_t)d.splitk_ws & 15) == 0;
   if (d.wgrad && pl.patch && !room) pl.patch = kNoPatch, pl.splits = 1, pl.steps = (d.Kd + 31) / 32;
@@ -1763,10 +1700,10 @@ int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots) {
   return 0;
 }
 
-int launch_split_planes(const float* src, uint16_t* dst, int np, int64_t plane, int64_t n, int* nonfinite, hipStream_t s) {
+int launch_split_planes(const float* src, uint16_t* dst, int np, int64_t plane, int64_t n, hipStream_t s) {
   if (n < 4 || n % 4 || plane % 8 || ((uintptr_t)src & 15) || ((uintptr_t)dst & 15)) return -1;
-  if (np == 1) split_kernel<1><<<blocks_for(n / 4), kThreads, 0, s>>>(src, dst, plane, n / 4, nonfinite);
-  else split_kernel<3><<<blocks_for(n / 4), kThreads, 0, s>>>(src, dst, plane, n / 4, nonfinite);
+  if (np == 1) split_kernel<1><<<blocks_for(n / 4), kThreads, 0, s>>>(src, dst, plane, n / 4);
+  else split_kernel<3><<<blocks_for(n / 4), kThreads, 0, s>>>(src, dst, plane, n / 4);
   return 0;
 }
 
@@ -1776,11 +1713,11 @@ int filter_bank_blocks(const FilterBank& f) {
 }
 
 int launch_filters(const float* params, int64_t strideParams, const FilterBank* banks, int n, int blocks, uint16_t* dst,
-                   int np, int64_t plane, int K, int* nonfinite, hipStream_t s) {
+                   int np, int64_t plane, int K, hipStream_t s) {
   if (n < 1 || blocks < 1) return -1;
   const dim3 grid((unsigned)blocks, (unsigned)K);
-  if (np == 1) filters_kernel<1><<<grid, kThreads, 0, s>>>(params, strideParams, banks, n, dst, plane, K, nonfinite);
-  else filters_kernel<3><<<grid, kThreads, 0, s>>>(params, strideParams, banks, n, dst, plane, K, nonfinite);
+  if (np == 1) filters_kernel<1><<<grid, kThreads, 0, s>>>(params, strideParams, banks, n, dst, plane);
+  else filters_kernel<3><<<grid, kThreads, 0, s>>>(params, strideParams, banks, n, dst, plane);
   return 0;
 }
 

@@ -171,9 +171,8 @@ __global__ __launch_bounds__(kThreads) void gram_dot_partials_kernel(
 __global__ __launch_bounds__(kThreads) void norm_finish_kernel(
     const double* __restrict__ partials, int nblk, int64_t pstride, float rho, float gamma,
     float* __restrict__ norms, float* __restrict__ scale, const float* __restrict__ loss_rows,
-    int B, float* __restrict__ loss_out, int32_t* __restrict__ restart, int* __restrict__ nonfinite) {
+    int B, float* __restrict__ loss_out, int32_t* __restrict__ restart) {
   const int k = blockIdx.x;
-  if (nonfinite != nullptr && k == 0 && threadIdx.x == 0) *nonfinite = 0;
   if (restart != nullptr && threadIdx.x == 0) {     // 2 (sum just served) -> 1 (restart it in this step) -> 0
     const int32_t m = restart[k];
     if (m > 0) restart[k] = m - 1;
@@ -462,9 +461,9 @@ int launch_gram_dot(const float* G1, const float* G2, int64_t stride, int64_t n,
 
 void launch_norm_finish(const double* partials, int nblk, int64_t partials_stride, int K, float rho,
                         float gamma, float* norms, float* scale, const float* loss_rows, int B,
-                        float* loss_out, hipStream_t s, int32_t* restart, int* nonfinite) {
+                        float* loss_out, hipStream_t s, int32_t* restart) {
   norm_finish_kernel<<<K, kThreads, 0, s>>>(partials, nblk, partials_stride, rho, gamma, norms,
-                                            scale, loss_rows, B, loss_out, restart, nonfinite);
+                                            scale, loss_rows, B, loss_out, restart);
 }
 
 void launch_perturb(const float* x, const float* g, int64_t g_stride, const float* scale,

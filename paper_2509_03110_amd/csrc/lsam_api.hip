@@ -180,7 +180,6 @@ struct Layout {
   std::vector<FilterBank> banks;         // the filters in wp; their device copy and the workgroups they take
   size_t banks_at = 0;
   int bank_blocks = 0;
-  size_t nonfinite = 0;        // flag the plane writers raise on an infinite value
   size_t gram1 = 0, gram2 = 0; // bf16 dense model: Gram matrices [K][B][ldg] of a layer's dZ and of its input
   size_t restart = 0;         // K marks: which iterate sums read as zero / start afresh (launch_center)
   int ldg = 0;
@@ -572,7 +571,6 @@ void build_layout(const lsam_config& c, Layout& lo) {
       lo.banks_at = take(cur, lo.banks.size() * sizeof(FilterBank));
     }
     if (lo.dzp_elems) lo.dzp = take(cur, (size_t)lo.dzp_elems * 2 * lo.np);
-    if (lo.n_conv > 0) lo.nonfinite = take(cur, 4);
     if (lo.n_conv > 0) {
       size_t most = 0;
       for (const ConvLayer& cv : lo.conv)
@@ -813,7 +811,6 @@ ConvGemmDesc plane_desc(const lsam_ctx* c, const PlaneImage& im, int wgrad, int6
   d.epilogue = EPI_PLAIN;
   d.splitk_ws = lo.splitk_bytes ? c->at<float>(lo.splitk) : nullptr;
   d.splitk_bytes = lo.splitk_bytes;
-  d.nonfinite = c->at<int>(lo.nonfinite);
   if (wgrad) {     // contraction with the output gradient in dzp
     d.other = c->at<uint16_t>(lo.dzp);
     d.other_stride = (int64_t)Kd * M; d.other_plane = lo.dzp_elems; d.ld = M;
@@ -826,8 +823,7 @@ ConvGemmDesc plane_desc(const lsam_ctx* c, const PlaneImage& im, int wgrad, int6
 }
 int split_gradient(const lsam_ctx* c, const float* dz, const ConvLayer& cv) {
   const Layout& lo = c->lo;
-  return launch_split_planes(dz, c->at<uint16_t>(lo.dzp), lo.np, lo.dzp_elems, (int64_t)lo.K * cv.rows * cv.Cout,
-                             c->at<int>(lo.nonfinite), c->stream);
+  return launch_split_planes(dz, c->at<uint16_t>(lo.dzp), lo.np, lo.dzp_elems, (int64_t)lo.K * cv.rows * cv.Cout, c->stream);
 }
 
 // The planes of convolution l's input, for the kernel that writes that image.
@@ -836,7 +832,7 @@ PlaneOut input_planes(const lsam_ctx* c, int l) {
   PlaneOut o;
   if (l < lo.n_conv && lo.conv[l].planes_above) {
     const ConvLayer& cv = lo.conv[l];
-    o.p = c->at<uint16_t>(cv.xp); o.np = lo.np; o.plane = cv.plane_elems; o.nonfinite = c->at<int>(lo.nonfinite);
+    o.p = c->at<uint16_t>(cv.xp); o.np = lo.np; o.plane = cv.plane_elems;
   }
   return o;
 }
@@ -850,7 +846,7 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
   if (!lo.banks.empty()) {
     LaunchTimer t(c, KC_MISC);
     if (launch_filters(params, lo.d_pad, c->at<FilterBank>(lo.banks_at), (int)lo.banks.size(), lo.bank_blocks,
-                       c->at<uint16_t>(lo.wp), lo.np, lo.wp_elems, lo.K, c->at<int>(lo.nonfinite), s) != 0)
+                       c->at<uint16_t>(lo.wp), lo.np, lo.wp_elems, lo.K, s) != 0)
       return fail(LSAM_EINVAL, "planes of the filters rejected");
   }
   for (int l = 0; l < lo.n_conv; ++l) {
@@ -858,7 +854,7 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
     const Layer& ly = lo.layers[l];
     if (cv.planes && !cv.planes_above) {
       LaunchTimer t(c, KC_UNFOLD);
-      if (launch_split_planes(in, c->at<uint16_t>(cv.xp), lo.np, cv.plane_elems, cv.plane_elems, c->at<int>(lo.nonfinite), s) != 0)
+      if (launch_split_planes(in, c->at<uint16_t>(cv.xp), lo.np, cv.plane_elems, cv.plane_elems, s) != 0)
         return fail(LSAM_EINVAL, "planes of the input of convolution %d rejected", l);
     }
     if (cv.first) {
@@ -871,8 +867,7 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
     } else if (!cv.direct_in) {
       LaunchTimer t(c, KC_UNFOLD);
       if (launch_unfold3x3(in, cv.rows * cv.stride * cv.stride * cv.Cin, c->at<char>(cv.col), cv.fast ? lo.np : 0,
-                           (int64_t)lo.K * cv.rows * cv.ldc, cv.ldc, lo.K, lo.B, cv.H, cv.W, cv.Cin, cv.stride,
-                           c->at<int>(lo.nonfinite), s) != 0)
+                           (int64_t)lo.K * cv.rows * cv.ldc, cv.ldc, lo.K, lo.B, cv.H, cv.W, cv.Cin, cv.stride, s) != 0)
         return fail(LSAM_EINVAL, "unfold of convolution %d rejected", l);
     }
     if (!cv.first && cv.fast) {
@@ -1031,7 +1026,7 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
                               ? c->at<float>(lo.conv[l + 2].dout) : nullptr;
     PlaneOut po;                 // fast layers: dZ as planes, for dW and dX
     if (cv.fast && !cv.first) {
-      po.p = c->at<uint16_t>(lo.dzp); po.np = lo.np; po.plane = lo.dzp_elems; po.nonfinite = c->at<int>(lo.nonfinite);
+      po.p = c->at<uint16_t>(lo.dzp); po.np = lo.np; po.plane = lo.dzp_elems;
     }
     auto own_gradient = [&]() {
       // nothing reads the floats of a fast layer's dZ but the convolution its sum is handed down to
@@ -1538,7 +1533,7 @@ int update_tail_first(lsam_ctx* c, const float* g1, int64_t g_stride, int64_t n,
                        c->at<float>(lo.norms), c->at<float>(lo.scale),
                        lo.raw ? nullptr : c->at<float>(lo.loss_rows), lo.B,
                        lo.raw ? nullptr : (loss ? loss : c->at<float>(lo.loss)), s,
-                       c->at<int32_t>(lo.restart), lo.n_conv > 0 ? c->at<int>(lo.nonfinite) : nullptr);
+                       c->at<int32_t>(lo.restart));
   }
   if (c->rho != 0.f && perturb) {
     LaunchTimer t(c, KC_PERTURB);

@@ -891,7 +891,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_patch_kernel(Params p) {
 // write-out run under the other's products (one workgroup of 32-channel blocks, all 160 KiB of
 // LDS: 276 against 222 us on 64 channels at 32 x 32).  A 16-byte unit of slot t lies at position
 // u ^ (t / 8) % 2: 16 consecutive slots read without bank conflicts at any shift.
-// Per stage and wavefront: 6 TM x 4 products, 3 (TM + 2) fragment reads.
+// Per stage (a tap at one matrix depth) and wavefront: 6 TM TN products, 3 (TM + TN) fragment reads.
 // TN = 1 serves layers of up to 32 columns (half of the filter rows it requests do not exist and
 // cost no traffic): 16 channels at 32 x 32, 4 replicas of 128: 38 us,
 // 56 by the ring (which fetches every pixel nine times).
@@ -1062,7 +1062,9 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_patch_kernel(Params p)
     LSAM_SPLIT_STAGE(CUR, NEXT, BY, BX, 7, (F) ^ 1)                                                                   \
     LSAM_SPLIT_STAGE(CUR, NEXT, BX, BY, 8, F)                                                                         \
   }
-  static_assert(AG * (S - 1) >= NA, "the patch is requested before the last stage");
+  // the barrier of the last stage, whose products read on into NEXT, leaves what the stage before it
+  // requested in flight: that must be none of the patch
+  static_assert(AG * (S - 2) >= NA, "the patch is requested before the last stage but one");
   int blk = 0;
   while (blk + 1 < nblk) {
     LSAM_SPLIT_BLOCK(a0, a1, b0, b1, 0)

@@ -310,6 +310,11 @@ int launch_first_conv_wgrad(const float* X, const float* dout, float* partial, f
                             int64_t strideParams, int64_t w_off, int64_t b_off, int ldw, int round,
                             int skip_bias, int K, int64_t rows, int H, int W, int C, int Cout,
                             double* sumsq, int64_t sumsq_stride, hipStream_t s);
+// Where a kernel also writes its fp32 result as plane tensors (np = 0: it does not).
+struct PlaneOut {
+  uint16_t* p = nullptr; int np = 0; int64_t plane = 0;
+};
+
 // Training-mode batch normalisation of K matrices Z [rows][C] (C % 4 == 0, C <= 1024), per
 // replica and column over the rows.  Forward: stats[k][0][c] = mean, stats[k][1][c] =
 // 1/sqrt(biased variance + eps); out = relu(gamma Xh + beta), Xh = (Z - mean) stats[1], gamma
@@ -319,10 +324,7 @@ int launch_first_conv_wgrad(const float* X, const float* dout, float* partial, f
 // over them gives dgamma and dbeta); launch_bn_backward_apply then writes
 // dZ = gamma stats[1] (dY - dbeta/rows - Xh dgamma/rows) [+ add] to `dZ`, which may be dY itself or Z
 // (or null: planes only), dgamma and dbeta read from grad + k * strideParams at the same offsets.  -1: shape not supported.
-// Where a kernel also writes its fp32 result as plane tensors (np = 0: it does not).
-struct PlaneOut {
-  uint16_t* p = nullptr; int np = 0; int64_t plane = 0;
-};
+
 // Shortcut of a residual block (He et al., CIFAR variant, parameter-free): the block input
 // src [K][B][step H][step W][Cs] (replica stride `stride` floats) enters the block output
 // [B][H][W][C] as src[b][step i][step j][c] for c < Cs and 0 for the channels beyond.  Cs % 4 == 0.

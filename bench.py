@@ -25,64 +25,67 @@ import workloads  # noqa: E402
 
 PEAK_HBM_GBS = 8000.0
 PEAK_TFLOPS = {0: 157.3, 1: 2500.0}   # dense MFMA: fp32, bf16
-PEAK_TFLOPS_SPLIT = 2500.0 / 6        # fp32 as six products of exact bf16 pieces: the ceiling of a convolutional model
+SPLIT_PRODUCTS = 6                    # bf16 products an fp32 product of exact pieces is formed from (plane tensors)
 
 
 # HBM bytes per launch of each kernel class, from two `rocprofv3 --pmc` runs of this script
 # (FETCH_SIZE, then WRITE_SIZE; KiB per dispatch scaled by what the same counter reads for a plain
 # 1 GiB device copy: x2.0 and x1.0), summed over the dispatches of a class and divided by its
-# launches (a split-K GEMM and its reduce count as one launch).  The figures belong to the
-# kernel sources whose digest is TRAFFIC_SOURCES; with any other sources `traffic` is null.
-TRAFFIC_SOURCES = "184631bf3fbaf3a4"
+# launches (a split-K GEMM and its reduce count as one launch; kernels that serve several classes
+# are told apart by empty marker kernels launched between the classes in a copy of the library).
+# The figures belong to the kernel sources whose digest is TRAFFIC_SOURCES; with any other sources
+# `traffic` is null.
+TRAFFIC_SOURCES = "16c3d0d4d047df78"
 TRAFFIC = {
-    "cfg2": {"bias_grad": 2148523, "center": 84162976, "descent": 538499328, "gemm_dw": 43632755,
-             "gemm_dx": 42127701, "gemm_fwd": 62107669, "perturb": 201932160},
-    "cfg3": {"bias_grad": 13690112, "center": 1393525408, "descent": 877295, "gemm_dw_ascend":
-             732954300, "gemm_dw_norm": 17543979, "gemm_dw_step": 2905857877, "gemm_dx":
-             250149963, "gemm_fwd": 144075458, "softmax_ce": 1429696},
-    "cfg4": {"center": 2400049184, "descent": 25600058581, "perturb": 9600045269,
-             "sumsq_partials": 3416877589},
-    "cfg5": {"bias_grad": 117981832, "descent": 3481941, "gemm_dw_ascend": 6219425829,
-             "gemm_dw_norm": 152019669, "gemm_dw_step": 27294712777, "gemm_dx": 2581714869,
-             "gemm_fwd": 1161916226, "softmax_ce": 96450869},
-    "cnn5": {"bias_grad": 17354844, "conv_first": 80453440, "descent": 79486763, "gemm_dw":
-             67376004, "gemm_dx": 34787669, "gemm_fwd": 38345732, "perturb": 29800448, "pool":
-             68586073},
-    "cnn5bn": {"batchnorm": 157826080, "bias_grad": 562773, "conv_first": 80449835, "descent":
-             79552597, "gemm_dw": 67362485, "gemm_dx": 34787669, "gemm_fwd": 38344209, "perturb":
-             29825024, "pool": 68585845},
-    "resnet18": {"batchnorm": 259997189, "conv_first": 155183819, "descent": 1431000491,
-             "gemm_dw": 308601196, "gemm_dx": 178777639, "gemm_fwd": 230439253, "perturb":
-             536618624, "pool": 183890665, "unfold_fold": 218021649},
-    "resnet18bf": {"batchnorm": 259998289, "bias_grad": 50432, "conv_first": 155182635, "descent":
-             1431003904, "gemm_dw": 268401223, "gemm_dx": 145274408, "gemm_fwd": 274711036,
-             "perturb": 536618453, "pool": 183890643, "softmax_ce": 124587, "unfold_fold":
-             218021620},
-    "resnet20": {"batchnorm": 86666182, "descent": 34874283, "gemm_dw": 212806394, "gemm_dx":
-             269469124, "gemm_fwd": 100369632, "perturb": 13073408, "pool": 64194118,
-             "unfold_fold": 328611381},
-    "resnet34": {"batchnorm": 244145097, "bias_grad": 347008, "conv_first": 155250368, "descent":
-             2731215403, "gemm_dw": 264940556, "gemm_dx": 153711067, "gemm_fwd": 215734746,
-             "perturb": 1024204416, "pool": 195406042, "softmax_ce": 485291, "unfold_fold":
-             218021544},
-    "vgg16": {"batchnorm": 175729217, "bias_grad": 1091675, "conv_first": 155189792, "descent":
-             1952575829, "gemm_dw": 140527392, "gemm_dx": 16961707, "gemm_fwd": 137751684,
-             "perturb": 732209579, "pool": 89627452},
-    "vgg16bf": {"batchnorm": 175695851, "bias_grad": 1011170, "conv_first": 155195029, "descent":
-             1952580053, "gemm_dw": 113747526, "gemm_dx": 12092075, "gemm_fwd": 169044908,
-             "perturb": 732209749, "pool": 89627526, "softmax_ce": 124587},
-    "wrn16x10": {"batchnorm": 736315405, "descent": 2191812864, "gemm_dw": 1854432135, "gemm_dx":
-             549450901, "gemm_fwd": 1184345296, "perturb": 821921621, "pool": 441879842,
-             "unfold_fold": 629743101},
-    "wrn16x10bf": {"batchnorm": 736315944, "bias_grad": 50048, "descent": 2191814955, "gemm_dw":
-             1114631144, "gemm_dx": 496001376, "gemm_fwd": 1400264620, "perturb": 821921707,
-             "pool": 441879842, "softmax_ce": 124587, "unfold_fold": 629743085},
-    "wrn28x10": {"batchnorm": 760367501, "bias_grad": 346880, "descent": 4678217856, "gemm_dw":
-             1943620653, "gemm_dx": 458547460, "gemm_fwd": 1271969861, "perturb": 1754327680,
-             "pool": 508961023, "softmax_ce": 485035, "unfold_fold": 629743043},
-    "wrn40x10": {"batchnorm": 768818096, "bias_grad": 346880, "descent": 7157244245, "gemm_dw":
-             2026127685, "gemm_dx": 458552949, "gemm_fwd": 1321328546, "perturb": 2683965739,
-             "pool": 533675103, "softmax_ce": 485376, "unfold_fold": 629742957},
+    "cfg2": {"bias_grad": 2149376, "center": 84162976, "descent": 538498858, "gemm_dw": 43629941,
+             "gemm_dx": 42136917, "gemm_fwd": 62116917, "perturb": 201932202},
+    "cfg3": {"bias_grad": 13693175, "center": 1393525408, "descent": 877124,
+             "gemm_dw_ascend": 732946210, "gemm_dw_norm": 81972736, "gemm_dw_step": 2906428433,
+             "gemm_dx": 250149957, "gemm_fwd": 233129047, "softmax_ce": 1429162},
+    "cfg4": {"center": 2400048672, "descent": 25600060288, "perturb": 9600046122,
+             "sumsq_partials": 3418530176},
+    "cfg5": {"bias_grad": 117984776, "descent": 3481947, "gemm_dw_ascend": 6215313852,
+             "gemm_dw_norm": 297865222, "gemm_dw_step": 27263005891, "gemm_dx": 2584827413,
+             "gemm_fwd": 2034599334, "softmax_ce": 96421056},
+    "cnn5": {"bias_grad": 17351488, "conv_first": 80450336, "descent": 79484928,
+             "gemm_dw": 68642698, "gemm_dx": 107690872, "gemm_fwd": 42498844, "perturb": 29800448,
+             "pool": 74873283, "unfold_fold": 62939306},
+    "cnn5bn": {"batchnorm": 162298769, "bias_grad": 563456, "conv_first": 80451221,
+             "descent": 79554176, "gemm_dw": 68648231, "gemm_dx": 107711089, "gemm_fwd": 42498744,
+             "perturb": 29825024, "pool": 74873230},
+    "resnet18": {"batchnorm": 316547992, "conv_first": 155199008, "descent": 1431000405,
+             "gemm_dw": 277736942, "gemm_dx": 342793625, "gemm_fwd": 314629414,
+             "perturb": 536618410, "pool": 183896249},
+    "resnet18bf": {"batchnorm": 260340954, "bias_grad": 50560, "conv_first": 155189941,
+             "descent": 1430995285, "gemm_dw": 123361473, "gemm_dx": 164009495,
+             "gemm_fwd": 109682539, "perturb": 536618581, "pool": 183896339, "softmax_ce": 124586},
+    "resnet20": {"batchnorm": 106351412, "descent": 34873642, "gemm_dw": 81757391,
+             "gemm_dx": 85113705, "gemm_fwd": 66717286, "perturb": 13073408, "pool": 64199994,
+             "unfold_fold": 85693952},
+    "resnet34": {"batchnorm": 298999596, "bias_grad": 347925, "conv_first": 154976458,
+             "descent": 2731212586, "gemm_dw": 250918070, "gemm_dx": 308537713,
+             "gemm_fwd": 278780092, "perturb": 1024203946, "pool": 195411535, "softmax_ce": 485589},
+    "vgg16": {"batchnorm": 202196419, "bias_grad": 1092224, "conv_first": 155099861,
+             "descent": 1952577493, "gemm_dw": 172316226, "gemm_dx": 197142470,
+             "gemm_fwd": 167721758, "perturb": 732209706, "pool": 99061013},
+    "vgg16bf": {"batchnorm": 173722171, "bias_grad": 745024, "conv_first": 155116000,
+             "descent": 1952581930, "gemm_dw": 87375335, "gemm_dx": 99479776, "gemm_fwd": 75919045,
+             "perturb": 732210346, "pool": 92560134, "softmax_ce": 124778},
+    "wrn16x10": {"batchnorm": 960026909, "descent": 2191810474, "gemm_dw": 1238102859,
+             "gemm_dx": 1651112258, "gemm_fwd": 1457835793, "perturb": 821921877, "pool": 402241043,
+             "unfold_fold": 740394848},
+    "wrn16x10bf": {"batchnorm": 781240953, "bias_grad": 50560, "descent": 2191808512,
+             "gemm_dw": 359387094, "gemm_dx": 553025112, "gemm_fwd": 349111386,
+             "perturb": 821921877, "pool": 402241029, "softmax_ce": 124650,
+             "unfold_fold": 85694037},
+    "wrn28x10": {"batchnorm": 1018028438, "bias_grad": 347904, "descent": 4678213376,
+             "gemm_dw": 1347396689, "gemm_dx": 1813427767, "gemm_fwd": 1519858703,
+             "perturb": 1754328064, "pool": 467526364, "softmax_ce": 485376,
+             "unfold_fold": 740394858},
+    "wrn40x10": {"batchnorm": 1038407155, "bias_grad": 347904, "descent": 7157262762,
+             "gemm_dw": 1427835705, "gemm_dx": 1909015397, "gemm_fwd": 1616510991,
+             "perturb": 2683965440, "pool": 498749897, "softmax_ce": 485034,
+             "unfold_fold": 740394624},
 }
 
 
@@ -104,6 +107,34 @@ def layer_table(eng, w):
     """What the library reports about each layer (`lsam_layer_info`): which kernels serve it, the
     rows of its matrix products, whether its gradients are stored."""
     return [eng.lsam_layer_info(l) for l in range(len(w.dims) - 1)]
+
+
+def plane_table(eng, w):
+    """bfloat16 values per number in the operands of each layer's products (0: stored fp32 numbers)."""
+    return [eng.lsam_layer_planes(l) for l in range(len(w.dims) - 1)]
+
+
+def matrix_units(w, layers, planes):
+    """Per product class: the share of its flops that each kind of product forms ("fp32", "bf16", or
+    "split": fp32 from exact bf16 pieces)."""
+    from paper_2509_03110_amd import lsam
+
+    def shares(lo):
+        out = {}
+        for (kind, _, _, rows, fi, fo, pc, _), np_ in list(zip(layers, planes))[lo:]:
+            if kind in (lsam.LAYER_HEAD, lsam.LAYER_CONV_FIRST):
+                continue
+            unit = "split" if np_ == 3 else "bf16" if np_ == 1 or w.gemm_dtype == 1 else "fp32"
+            out[unit] = out.get(unit, 0.0) + float(rows) * (fi + pc) * fo
+        total = sum(out.values())
+        return {k: v / total for k, v in out.items()}
+    return {name: s for name, s in (("gemm_fwd", shares(0)), ("gemm_dx", shares(1)), ("gemm_dw", shares(0))) if s}
+
+
+def mixed_rate(shares, fp32, bf16):
+    """The rate of a class whose flops are shared out like that among units of these rates."""
+    rate = {"fp32": fp32, "bf16": bf16, "split": bf16 / SPLIT_PRODUCTS}
+    return 1.0 / sum(v / rate[k] for k, v in shares.items())
 
 
 def gemm_flops(w, layers):
@@ -132,38 +163,65 @@ def gemm_flops(w, layers):
     return out
 
 
-def conv_bytes(w, layers):
+def conv_bytes(w, layers, planes):
     """Algorithmic bytes per all-replica step (both passes) of the kernels around the
     convolution GEMMs: where an unfolded image is stored it is written once (plus the image
     read), where its gradient is stored that is read once (plus the image gradient written);
     the pool reads its input and writes a quarter of it, its backward pass reads both and
-    writes the full-size gradient."""
+    writes the full-size gradient.  Where plane tensors serve a layer (`planes` values of 2 bytes
+    per number) its image's and its output gradient's planes are written by the kernels that form
+    them, or from the stored floats by one of their own; nothing then reads the gradient's floats
+    but an identity shortcut in front of a normalisation."""
     from paper_2509_03110_amd import lsam
     unfold = pool = bn = 0.0
     for l in range(w.n_conv):
-        kind, dx_stored, _, rows, _, _, proj_c, _ = layers[l]
+        kind, dx_stored, _, rows, _, _, proj_c, proj_step = layers[l]
+        np_ = planes[l]
+        skip, proj = (w.skip_mask >> l) & 1, bool(proj_c)
         cin, cout = w.dims[l], w.dims[l + 1]
         st2 = 4 if (w.stride_mask >> l) & 1 else 1    # pixels of the image read per output pixel
         if kind == lsam.LAYER_CONV_STORED:
-            unfold += rows * (st2 * cin + 9 * cin) * 4.0
+            unfold += rows * (st2 * cin * 4.0 + 9 * cin * (2.0 * np_ if np_ else 4.0))
+        # planes of the image it reads, also for the projection of the block it opens
+        image = np_ if kind == lsam.LAYER_CONV_DIRECT else 0
+        if l + 1 < w.n_conv and layers[l + 1][6]:
+            image = max(image, planes[l + 1])
+        if image and l > 0 and (w.pool_mask >> (l - 1)) & 1:
+            pool += rows * st2 * cin * 2.0 * image
+        elif image and l > 0 and (w.bn_mask >> (l - 1)) & 1:
+            bn += rows * st2 * cin * 2.0 * image
+        elif image:
+            unfold += rows * st2 * cin * (4.0 + 2.0 * image)
+        # what is written of the output gradient behind its normalisation, bytes a value
+        dz = 2.0 * np_ + (4.0 if w.preact and skip and not proj else 0.0) if np_ else 4.0
+        if np_ and not (w.bn_mask >> l) & 1:
+            unfold += rows * cout * (4.0 + 2.0 * np_)
         if dx_stored:
             unfold += rows * (9 * cin + st2 * cin) * 4.0
         if proj_c:
             # projection: its normalisation costs what the layer's own does (below), and its
-            # output is read once more where the two branches meet (the pixels a strided one
-            # keeps are read in place); backward, the gradient of those pixels
+            # output is read once more where the two branches meet; the pixels a strided one
+            # keeps are read in place on plane tensors, gathered (read and written) otherwise;
+            # backward, the gradient of those pixels
             # is added to the block input's gradient under that input's mask (3 reads, 1 write)
             # (a pre-activation block's bare projection is added to the convolution's output
             # instead: two reads and a write)
             if w.preact:
                 pool += rows * cout * 4.0 * 3
             else:
-                bn += rows * cout * 4.0 * (1 + 1 + 2 + 3)
+                bn += rows * cout * (4.0 * (1 + 1 + 2 + 2) + (2.0 * np_ if np_ else 4.0))
+            if proj_step == 2 and not np_:
+                unfold += rows * proj_c * 4.0 * 2
             pool += rows * proj_c * 4.0 * 4
         elif (w.skip_mask >> l) & 1 and w.preact:
             # identity shortcut of a pre-activation block: the sum two convolutions below is added
-            # to this one's (forward), this one's gradient to that one's (backward)
-            pool += rows * cout * 4.0 * (3 + 3)
+            # to this one's (forward), this one's gradient to that one's (backward; on plane
+            # tensors where that one's is formed)
+            pool += rows * cout * 4.0 * 3
+            if planes[l - 2]:
+                bn += rows * cout * 4.0
+            else:
+                pool += rows * cout * 4.0 * 3
         elif (w.skip_mask >> l) & 1:
             # shortcut: read with the normalisation (forward); backward reads dY, the mask and the
             # block input's gradient and writes the latter
@@ -173,7 +231,7 @@ def conv_bytes(w, layers):
         if (w.bn_mask >> l) & 1:
             # statistics read Z; normalise+ReLU reads Z, writes the activation; the backward
             # sums read Z and dY; the backward apply reads Z and dY and writes dZ
-            bn += rows * cout * 4.0 * (1 + 2 + 2 + 3)
+            bn += rows * cout * (4.0 * (1 + 2 + 2 + 2) + dz)
     out = {}
     if bn:
         out["batchnorm"] = 2 * bn * w.K
@@ -331,7 +389,8 @@ def run_workload(w, steps, warmup, kernel_timing=True):
             one(i)
         stats = eng.lsam_timing_read()
         eng.lsam_timing_enable(False)
-        layers = layer_table(eng, w) if w.dims else []
+        layers, planes = (layer_table(eng, w), plane_table(eng, w)) if w.dims else ([], [])
+        units = matrix_units(w, layers, planes) if w.dims else {}
         fused_step = any(r[2] for r in layers)
         flops = gemm_flops(w, layers) if w.dims else {}
         # center update: 4 B/param per due replica (S read; starting it again from zero costs
@@ -342,7 +401,7 @@ def run_workload(w, steps, warmup, kernel_timing=True):
         nd = due[first:].sum(axis=1)
         restarts = float(due[first - 1:-1].sum()) / steps     # served one tick earlier
         nbytes = stream_bytes(w, fused_step, restarts)
-        nbytes.update(conv_bytes(w, layers))
+        nbytes.update(conv_bytes(w, layers, planes))
         nbytes["center"] = float(np.sum((4.0 * nd + 16.0) * (nd > 0))) * w.d / steps
         traffic = TRAFFIC.get(w.name, {}) if kernel_sources_digest() == TRAFFIC_SOURCES else {}
         for name, (cnt, tot) in stats.items():
@@ -359,7 +418,7 @@ def run_workload(w, steps, warmup, kernel_timing=True):
                          mfma_tflops=flops[name] * steps / (tot * 1e-3) / 1e12)
             elif name in flops and tot > 0:
                 k.update(bound="mfma", achieved=flops[name] * steps / (tot * 1e-3) / 1e12,
-                         peak=PEAK_TFLOPS_SPLIT if w.n_conv and w.gemm_dtype == 0 and name != "conv_first"
+                         peak=mixed_rate(units[name], PEAK_TFLOPS[0], PEAK_TFLOPS[1]) if name in units
                          else PEAK_TFLOPS[w.gemm_dtype], unit="TFLOP/s",
                          algorithmic_flops_per_launch=flops[name] * steps / cnt)
             elif name in nbytes and tot > 0:
@@ -368,6 +427,8 @@ def run_workload(w, steps, warmup, kernel_timing=True):
                          algorithmic_bytes_per_launch=nbytes[name] * steps / cnt)
             if "achieved" in k:
                 k["frac"] = k["achieved"] / k["peak"]
+            if name in units and k.get("bound") == "mfma" and "split" in units[name]:
+                k["units"] = units[name]
             k["traffic"] = traffic.get(name)
             kernels[name] = k
         ranked = [n for n in sorted(kernels, key=lambda n: -kernels[n]["ms_per_step"])
@@ -377,6 +438,8 @@ def run_workload(w, steps, warmup, kernel_timing=True):
             roof = {"kernel": ranked[0], "bound": top["bound"], "achieved": top["achieved"],
                     "peak": top["peak"], "unit": top["unit"], "frac": top["frac"],
                     "traffic": top["traffic"], "avg_launch_ms": top["avg_launch_ms"]}
+            if "units" in top:
+                roof["units"] = top["units"]
 
     out = {
         "metric": metric, "value": value, "unit": unit, "n_gpus": 1, "steps": steps,
@@ -404,7 +467,7 @@ def add_measured_fractions(out, w, peaks):
     mfma_meas = bf16_tf if w.gemm_dtype == 1 else f32_tf
     for k in list(out["kernels"].values()) + ([out["roofline"]] if out["roofline"] else []):
         if k.get("bound") == "mfma":
-            k["frac_of_measured"] = k["achieved"] / mfma_meas
+            k["frac_of_measured"] = k["achieved"] / (mixed_rate(k["units"], f32_tf, bf16_tf) if "units" in k else mfma_meas)
         elif k.get("bound") == "hbm":
             k["frac_of_measured"] = k["achieved"] / copy_gbs
 

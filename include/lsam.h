@@ -247,7 +247,7 @@ int lsam_set_fused_step(lsam_ctx* ctx, int32_t on);
 
 /* Which kernels serve layer `layer` (0-based) of this context, for reports that attribute time
  * and work to kernel classes without restating the library's choices.  `info` [host] gets
- * LSAM_LAYER_INFO_FIELDS (8) values, `n` its capacity:
+ * LSAM_LAYER_INFO_FIELDS (8) values, and one more if its capacity `n` is larger:
  *   [0] LSAM_LAYER_DENSE (GEMM kernels), LSAM_LAYER_HEAD (the two fused kernels of a narrow fp32
  *       classifier head), LSAM_LAYER_CONV_FIRST (first-layer convolution kernels),
  *       LSAM_LAYER_CONV_DIRECT (GEMM that unfolds the image on the fly), LSAM_LAYER_CONV_STORED
@@ -259,7 +259,10 @@ int lsam_set_fused_step(lsam_ctx* ctx, int32_t on);
  *   [4], [5] columns of its weight matrix (fan-in) and its outputs
  *   [6] channels its projection shortcut reads (0: the layer closes no block with a projection;
  *       then three more products of [3] rows, [6] columns and [5] outputs belong to the layer)
- *   [7] pixel step of that projection (2: it reads every second pixel) */
+ *   [7] pixel step of that projection (2: it reads every second pixel: in place where [8] is not 0,
+ *       through a gather otherwise)
+ *   [8] (if n > LSAM_LAYER_INFO_FIELDS) bfloat16 values per number in the operands of a convolution's
+ *       products and its projection's: 1 (rounded), 3 (exact split), 0: stored fp32 numbers */
 #define LSAM_LAYER_INFO_FIELDS 8
 #define LSAM_LAYER_DENSE 0
 #define LSAM_LAYER_HEAD 1

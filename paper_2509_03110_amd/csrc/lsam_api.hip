@@ -143,7 +143,8 @@ struct ConvLayer {
   int64_t rows;        // B H W: rows of the unfolded image and of the layer's output
   int ldc;             // pitch of the unfolded image, 9 Cin rounded up to 8
   // Which products serve the layer.  `fast`: the bf16 matrix units on plane tensors
-  // (kernels_conv_gemm.hip); otherwise the fp32-storage GEMM (small layers, plane_products_pay).
+  // (kernels_conv_gemm.hip); otherwise the fp32-storage GEMM (small layers and, in fp32 arithmetic, channel
+  // counts other than 8, 16 and multiples of 32; plane_products_pay).
   // Both can read an unfolded image straight from the image: `direct_in` for the layer's input
   // (forward and dW), `direct_dx` for its output gradient (dX, with the mirrored filters, `wt` for
   // the fp32-storage GEMM).  Otherwise the unfolded image (`col`, planes if fast) resp. its gradient
@@ -339,9 +340,11 @@ int gram_pieces(int K, int B, int kd) {
 // at 9e6, 0.90 at 1.5e8, 0.74 at 2.4e9; 16 channels 0.93 at 2e7, 0.60 at 6e8; 64 channels 1.13 at
 // 7.5e7, 0.98 at 6e8; 128 channels 0.87 at 1.2e9 (fp32 arithmetic; with bf16 products 1.0, 0.94, 0.78;
 // 0.92, 0.59; 1.02, 0.90; 0.91).  One plane leaves little to gain on few, small images: 256 channels on
-// 2048 pixels 0.95 in fp32, 1.07 with bf16 products, which therefore want 4096.  Channel counts that
-// need a stored unfolded image move nine times the image either way: with three planes that stays
-// slower at every size (24 channels: 1.06 to 1.16), with one plane it pays from 3e8 (0.88).
+// 2048 pixels 0.95 in fp32, 1.07 with bf16 products, which therefore want 4096.  Other channel counts
+// (multiples of 8, but neither 8, 16 nor multiples of 32) are taken with a stored unfolded image here, nine
+// times the image either way: with three planes that was slower at every size (24 channels: 1.06 to
+// 1.16), with one plane it pays from 3e8 (0.88).  The loaders could unfold them by address as well; that
+// has not been measured.
 bool plane_products_pay(int np, int K, int64_t rows, int Cin, int Cout) {
   auto fits = [](int C) { return C % 32 == 0 || C == 8 || C == 16; };
   const double macs = (double)K * (double)rows * 9.0 * Cin * Cout;
@@ -2044,6 +2047,7 @@ int lsam_layer_info(lsam_ctx* c, int32_t layer, int32_t* info, int32_t n) {
   info[5] = ly.out;
   info[6] = ly.proj ? ly.proj_in : 0;
   info[7] = ly.proj ? lo.conv[layer].skip_step : 0;
+  if (n > LSAM_LAYER_INFO_FIELDS) info[8] = layer < lo.n_conv && lo.conv[layer].fast && !lo.conv[layer].first ? lo.np : 0;
   return LSAM_OK;
 }
 

@@ -300,6 +300,12 @@ class Lsam:
         _check(lib().lsam_layer_info(self._h, layer, out.ctypes.data, out.size))
         return tuple(int(v) for v in out)
 
+    def lsam_layer_planes(self, layer):
+        """bfloat16 values per number in the operands of convolution `layer`'s products (0: fp32)."""
+        out = np.zeros(9, dtype=np.int32)
+        _check(lib().lsam_layer_info(self._h, layer, out.ctypes.data, out.size))
+        return int(out[8])
+
     def lsam_set_fused_step(self, on):
         return _check(lib().lsam_set_fused_step(self._h, 1 if on else 0))
 

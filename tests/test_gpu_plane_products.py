@@ -161,6 +161,21 @@ def test_plane_products_match_oracle(name, bf16):
     g.close()
 
 
+def test_layer_info_reports_planes():
+    """Layers that the plane products serve say so: by size, and in fp32 arithmetic by channel count."""
+    def table(w):
+        cfg, keep = lsam.config_from_workload(w)
+        g = lsam.Lsam(cfg, workloads.init_params(w), device=DEV, keep=keep)
+        out = [g.lsam_layer_planes(l) for l in range(len(w.dims) - 1)]
+        assert all(len(g.lsam_layer_info(l)) == 8 for l in range(len(w.dims) - 1))
+        g.close()
+        return out
+    over = dict(dims=(3, 32, 64, 24, 64, 10), side=(16, 32), batch=40)
+    assert table(net(**over)) == [0, 3, 0, 0, 0]
+    assert table(net(bf16=1, **over)) == [0, 1, 1, 1, 0]
+    assert table(net(**dict(over, batch=2))) == [0, 0, 0, 0, 0]
+
+
 @pytest.mark.parametrize("name", ["32 wide, 64 channels", "8 and 16 channels", "2 wide"])
 def test_infinite_operands(name):
     """An infinite pixel, without normalisation and with positive weights, stays infinite (never infinity

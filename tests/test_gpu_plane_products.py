@@ -347,3 +347,43 @@ def test_infinite_filter_stays_in_its_class_of_pixels(c, batch, bf16):
         grads.append(g.lsam_get_buffer(lsam.BUF_GRAD, 0))
         g.close()
     assert np.any(grads[0][:n]) and np.array_equal(grads[1], grads[0])
+
+
+@pytest.mark.parametrize("bf16", [0, 1])
+@pytest.mark.parametrize("name", ["8 and 16 channels", "stride and projection", "pre-activation", "pools, no normalisation"])
+def test_captured_and_concurrent_steps(name, bf16):
+    """Four steps of a captured graph, with eager work and synchronisations between the replays, and four
+    steps of each of two contexts on streams of their own, side by side, leave what four eager steps
+    leave, bit for bit."""
+    w = net(bf16=bf16, **NETS[name]).scaled(tau=(100, 100))
+    init = spread(w)
+    X, lab = (torch.from_numpy(t).to(DEV) for t in workloads.batch(w, 0))
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(device=DEV) for _ in range(4)]
+    cfg, keep = lsam.config_from_workload(w)
+    eager, captured, one, two = (lsam.Lsam(cfg, init, device=DEV, keep=keep, stream=st) for st in streams)
+    losses = [torch.zeros(w.K, device=DEV) for _ in range(4)]
+    torch.cuda.synchronize()
+    for _ in range(4):
+        eager.lsam_step(X, lab, losses[0])
+    torch.cuda.synchronize()
+    with torch.cuda.stream(streams[1]):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=streams[1]):
+            captured.lsam_step(X, lab, losses[1])
+        scratch = torch.zeros(1 << 20, device=DEV)
+        for _ in range(4):
+            graph.replay()
+            scratch.add_(1.0)
+            streams[1].synchronize()
+    for _ in range(4):
+        one.lsam_step(X, lab, losses[2])
+        two.lsam_step(X, lab, losses[3])
+    torch.cuda.synchronize()
+    for g, loss in zip((captured, one, two), losses[1:]):
+        assert torch.equal(loss, losses[0])
+        for i in range(w.K):
+            for which in (lsam.BUF_PARAMS, lsam.BUF_VELOCITY, lsam.BUF_ITER_SUM, lsam.BUF_GRAD):
+                assert np.array_equal(g.lsam_get_buffer(which, i), eager.lsam_get_buffer(which, i)), (i, which)
+    for g in (eager, captured, one, two):
+        g.close()

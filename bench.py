@@ -35,7 +35,7 @@ SPLIT_PRODUCTS = 6                    # bf16 products an fp32 product of exact p
 # are told apart by empty marker kernels launched between the classes in a copy of the library).
 # The figures belong to the kernel sources whose digest is TRAFFIC_SOURCES; with any other sources
 # `traffic` is null.
-TRAFFIC_SOURCES = "16c3d0d4d047df78"
+TRAFFIC_SOURCES = "19c3b54a836d85e0"
 TRAFFIC = {
     "cfg2": {"bias_grad": 2149376, "center": 84162976, "descent": 538498858, "gemm_dw": 43629941,
              "gemm_dx": 42136917, "gemm_fwd": 62116917, "perturb": 201932202},

@@ -527,7 +527,6 @@ __global__ __launch_bounds__(kThreads, OCC) void conv_gemm_kernel(Params p) {
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
-  const int l32 = lane & 31, h = lane >> 5;
 
   const int all = (p.Kd + 31) / 32;
   const int first = piece * p.steps_per_piece;

@@ -254,6 +254,10 @@ def stream_bytes(w, fused_step=False, restarts=0.0):
     out = {"sumsq_partials": 4 * n,
            "perturb": (10 if bf else 12) * n,
            "descent": (30 if bf else 28) * n + 4.0 * w.d - 4.0 * restarts * w.d}
+    if not w.dims and w.rho and w.algorithm == 0:
+        # both gradients are at hand: the descent's pass reads g1 and writes the perturbed point too
+        out["descent"] += 8 * n
+        del out["perturb"]
     if fused_step:
         # the weight matrices take their step where the second-pass gradient is produced: that
         # kernel reads x, v, S (12 B per parameter) and y once, writes x, v, S (12 B) and the

@@ -49,9 +49,17 @@ __device__ __forceinline__ float ascent_point(float x, float scale, float g) {
 // ---- streaming kernels (update path) ---------------------------------------------------
 
 // Sum of squares, pass 1: per (replica, block) partial sums in double.
-// g: [K] rows of `n` floats with row stride `g_stride`; partials: [K, nblk] doubles.
+// g: [K] rows of `n` floats with row stride `g_stride` (any n, stride and 4-byte alignment);
+// partials: [K, nblk] doubles.  `restart`: as in launch_norm_finish, which then gets none.
 void launch_sumsq_partials(const float* g, int64_t g_stride, int64_t n, int K, double* partials,
-                           int nblk, hipStream_t s);
+                           int nblk, hipStream_t s, int32_t* restart = nullptr);
+// How many partial sums a row of n values is cut into: pieces of 4096 values, up to
+// kProloguePartials of them, while that leaves a piece at most 16384 values (four rounds of four
+// loads per lane), otherwise pieces of 16384 and more, at most kMaxPartials.
+// Pieces of 65536 left most of the chip idle in short rows: 18 us for 4 x 270410 values.
+constexpr int kProloguePartials = 128;
+constexpr int kMaxPartials = 1024;
+int sumsq_blocks(int64_t n);
 // Inner product of K pairs of matrices G1, G2 (each `n` floats, replica stride `stride`, both
 // multiples of 4, 16-byte aligned): partials[k * pstride + j] for j < the returned count (<= 64).
 // G1 (G2) is the sum of pieces1 (pieces2) >= 1 partial matrices lying piece_stride elements apart.
@@ -80,6 +88,22 @@ void launch_descent(float* x, const float* g, int64_t g_stride, float* v, float*
                     const float* y, uint16_t* shadow, const ShadowMap* map, int64_t shadow_stride,
                     int64_t stride, int64_t n, int K, const ReplicaScalars& lam, float lr, float mu,
                     int nesterov, const NoiseMap* noise, hipStream_t s, const int32_t* restart = nullptr);
+// A step on gradients that are both at hand, in two launches: the norm of g1, then one pass for x~ =
+// x + scale g1 (xt null: not wanted) and the descent on g2.  A third adds the norm's partial sums up
+// where the descent does not.  n, the strides of g1 and g2 and their 4-byte alignment are the caller's;
+// x, v, S, xt, y as in launch_descent, xt over none of the others.  nblk: sumsq_blocks(n).
+struct AscentPass {
+  const float* g1 = nullptr; int64_t g1_stride = 0;
+  float* xt = nullptr;
+  double* partials = nullptr; int nblk = 0;
+  float rho = 0.f, gamma = 0.f;
+  float* norms = nullptr; float* scale = nullptr;
+  bool finish_in_descent() const { return xt != nullptr && nblk <= kProloguePartials; }
+};
+void launch_raw_norm(int64_t n, int K, hipStream_t s, int32_t* restart, const AscentPass& up);
+void launch_raw_descent(float* x, const float* g2, int64_t g_stride, float* v, float* S, const float* y,
+                        int64_t stride, int64_t n, int K, const ReplicaScalars& lam, float lr, float mu,
+                        int nesterov, const NoiseMap* noise, hipStream_t s, const int32_t* restart, const AscentPass& up);
 // dst[c * dst_stride + i] = (1/K) sum_k src[k * src_stride + i] for c < copies, i < n; the K
 // terms are added in replica order.  dst may be src (each index is read in full before it is
 // written).

@@ -13,60 +13,59 @@ constexpr int kThreads = 256;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
 
-template <int VEC> struct Vec;
-template <> struct Vec<4> { typedef f32x4 type; };
-template <> struct Vec<1> { typedef float type; };
+// A row of a gradient that a caller hands in starts wherever its length puts it: four floats that are
+// aligned as one (global memory takes 128-bit accesses at any multiple of 4 bytes).
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
 
-template <int VEC>
-__device__ __forceinline__ typename Vec<VEC>::type ldv(const float* p) {
-  return __builtin_nontemporal_load(reinterpret_cast<const typename Vec<VEC>::type*>(p));
+__device__ __forceinline__ f32x4 ldv(const float* p) {
+  return __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
 }
-template <int VEC>
-__device__ __forceinline__ void stv(float* p, typename Vec<VEC>::type v) {
-  __builtin_nontemporal_store(v, reinterpret_cast<typename Vec<VEC>::type*>(p));
+template <bool STREAM>
+__device__ __forceinline__ f32x4 ld_any(const float* p) {
+  if constexpr (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(p));
+  else return *reinterpret_cast<const f32x4_any*>(p);
+}
+__device__ __forceinline__ void stv(float* p, f32x4 v) {
+  __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(p));
 }
 // Parameters that the next kernels read back: streamed past the caches when all replicas
 // together are far larger than they are (K d floats; measured at 3.2 GB: +5-9 % for the two
 // kernels with streaming stores), left in them when they fit (at 67 MB the following forward
 // GEMMs and the next descent find them there: -2 % per step).
 constexpr int64_t kCacheResidentBytes = 96ll << 20;
-template <int VEC, bool STREAM>
-__device__ __forceinline__ void st_param(float* p, typename Vec<VEC>::type v) {
-  if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<typename Vec<VEC>::type*>(p));
-  else *reinterpret_cast<typename Vec<VEC>::type*>(p) = v;
+template <bool STREAM>
+__device__ __forceinline__ void st_param(float* p, f32x4 v) {
+  if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(p));
+  else *reinterpret_cast<f32x4*>(p) = v;
 }
 // y / g'_prev are re-read by later kernels and other replicas: ordinary cached access.
-template <int VEC>
-__device__ __forceinline__ typename Vec<VEC>::type ldc(const float* p) {
-  return *reinterpret_cast<const typename Vec<VEC>::type*>(p);
-}
-
-__device__ __forceinline__ float elem(const f32x4& v, int i) { return v[i]; }
-__device__ __forceinline__ float elem(const float& v, int) { return v; }
-__device__ __forceinline__ void set_elem(f32x4& v, int i, float a) { v[i] = a; }
-__device__ __forceinline__ void set_elem(float& v, int, float a) { v = a; }
+__device__ __forceinline__ f32x4 ldc(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 
 __device__ __forceinline__ unsigned short bf16_bits(float f) {
   return __builtin_bit_cast(unsigned short, static_cast<__bf16>(f));
 }
-template <int VEC>
-__device__ __forceinline__ void store_bf16(uint16_t* p, const typename Vec<VEC>::type& v) {
-  if constexpr (VEC == 4) {
-    u16x4 o;
+__device__ __forceinline__ void store_bf16(uint16_t* p, const f32x4& v) {
+  u16x4 o;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = bf16_bits(v[i]);
-    // Plain store: a wavefront's 64-byte pieces of neighbouring blocks merge in L2 before they
-    // go out; the streaming hint measured no better once the copy became blocked.
-    *reinterpret_cast<u16x4*>(p) = o;
-  } else {
-    *p = bf16_bits(v);
-  }
+  for (int i = 0; i < 4; ++i) o[i] = bf16_bits(v[i]);
+  // Plain store: a wavefront's 64-byte pieces of neighbouring blocks merge in L2 before they
+  // go out; the streaming hint measured no better once the copy became blocked.
+  *reinterpret_cast<u16x4*>(p) = o;
 }
+
+enum Ascent { ASCENT_NONE = 0, ASCENT_SCALE, ASCENT_SUMS };   // see descent_kernel
 
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
   return v;
+}
+
+// One step further for a replica's mark (launch_center): 2 (sum just served) -> 1 (restart it in
+// this step) -> 0.
+__device__ __forceinline__ void count_mark(int32_t* mark) {
+  const int32_t m = *mark;
+  if (m > 0) *mark = m - 1;
 }
 
 // Sum over the block in a fixed order; result valid in thread 0.
@@ -86,36 +85,39 @@ __device__ __forceinline__ double block_sum(double v) {
 }
 
 // ---- gradient norm, pass 1 ------------------------------------------------------------------
-template <int VEC>
+// HBM-bound: 4 bytes per value, four 16-byte loads in flight per lane.  nv whole words of four and
+// `rem` values behind them; rows may start at any multiple of 4 bytes.
+template <bool STREAM>
 __global__ __launch_bounds__(kThreads) void sumsq_partials_kernel(
-    const float* __restrict__ g, int64_t g_stride, int64_t nv, double* __restrict__ partials,
-    int nblk) {
+    const float* __restrict__ g, int64_t g_stride, int64_t nv, int rem, double* __restrict__ partials,
+    int nblk, int32_t* __restrict__ restart) {
   const int k = blockIdx.y;
+  if (restart != nullptr && blockIdx.x == 0 && threadIdx.x == 0) count_mark(restart + k);
   const int64_t chunk = (nv + nblk - 1) / nblk;
   const int64_t beg = (int64_t)blockIdx.x * chunk;
   const int64_t end = beg + chunk < nv ? beg + chunk : nv;
   const float* gk = g + (int64_t)k * g_stride;
-  float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+  float a[4] = {0.f, 0.f, 0.f, 0.f};
   int64_t i = beg + threadIdx.x;
   for (; i + 3 * kThreads < end; i += 4 * kThreads) {
-    auto v0 = ldv<VEC>(gk + i * VEC);
-    auto v1 = ldv<VEC>(gk + (i + kThreads) * VEC);
-    auto v2 = ldv<VEC>(gk + (i + 2 * kThreads) * VEC);
-    auto v3 = ldv<VEC>(gk + (i + 3 * kThreads) * VEC);
+    f32x4 v[4];
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-      a0 += elem(v0, e) * elem(v0, e);
-      a1 += elem(v1, e) * elem(v1, e);
-      a2 += elem(v2, e) * elem(v2, e);
-      a3 += elem(v3, e) * elem(v3, e);
-    }
+    for (int j = 0; j < 4; ++j) v[j] = ld_any<STREAM>(gk + (i + j * kThreads) * 4);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[j] += v[j][e] * v[j][e];
   }
   for (; i < end; i += kThreads) {
-    auto v0 = ldv<VEC>(gk + i * VEC);
+    const f32x4 v0 = ld_any<STREAM>(gk + i * 4);
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) a0 += elem(v0, e) * elem(v0, e);
+    for (int e = 0; e < 4; ++e) a[0] += v0[e] * v0[e];
   }
-  double s = ((double)a0 + (double)a1) + ((double)a2 + (double)a3);
+  if (blockIdx.x == 0 && (int)threadIdx.x < rem) {
+    const float v0 = gk[nv * 4 + threadIdx.x];
+    a[1] += v0 * v0;
+  }
+  double s = ((double)a[0] + (double)a[1]) + ((double)a[2] + (double)a[3]);
   s = block_sum(s);
   if (threadIdx.x == 0) partials[(int64_t)k * nblk + blockIdx.x] = s;
 }
@@ -128,9 +130,9 @@ __global__ __launch_bounds__(kThreads) void sumsq_partials_kernel(
 // Gram matrix may arrive as several partial matrices (its contraction split over workgroups),
 // `piece_stride` elements apart, which are added up first, in order.
 __device__ __forceinline__ f32x4 gram_word(const float* p, int64_t i, int pieces, int64_t piece_stride) {
-  f32x4 u = ldc<4>(p + i * 4);
+  f32x4 u = ldc(p + i * 4);
   for (int j = 1; j < pieces; ++j) {
-    const f32x4 t = ldc<4>(p + (int64_t)j * piece_stride + i * 4);
+    const f32x4 t = ldc(p + (int64_t)j * piece_stride + i * 4);
 #pragma unroll
     for (int e = 0; e < 4; ++e) u[e] += t[e];
   }
@@ -173,10 +175,7 @@ __global__ __launch_bounds__(kThreads) void norm_finish_kernel(
     float* __restrict__ norms, float* __restrict__ scale, const float* __restrict__ loss_rows,
     int B, float* __restrict__ loss_out, int32_t* __restrict__ restart) {
   const int k = blockIdx.x;
-  if (restart != nullptr && threadIdx.x == 0) {     // 2 (sum just served) -> 1 (restart it in this step) -> 0
-    const int32_t m = restart[k];
-    if (m > 0) restart[k] = m - 1;
-  }
+  if (restart != nullptr && threadIdx.x == 0) count_mark(restart + k);
   double s = 0.0;
   for (int i = threadIdx.x; i < nblk; i += kThreads) s += partials[(int64_t)k * pstride + i];
   s = block_sum(s);
@@ -194,36 +193,30 @@ __global__ __launch_bounds__(kThreads) void norm_finish_kernel(
 }
 
 // ---- ascent perturbation ----------------------------------------------------------------------
-// BF16_OUT: x~ exists only as the bf16 operand copy of the weight matrices (blocked layout);
-// elements that belong to no weight matrix (biases, padding) are not stored at all -- the
-// perturbed biases are formed in the GEMM epilogue from x, g1 and scale.
-template <int VEC, bool BF16_OUT, bool STREAM>
+template <bool STREAM>
 __global__ __launch_bounds__(kThreads) void perturb_kernel(
     const float* __restrict__ x, const float* __restrict__ g, int64_t g_stride,
-    const float* __restrict__ scale, float* __restrict__ xt, uint16_t* __restrict__ xt16,
-    ShadowMap map, int64_t shadow_stride, int64_t stride, int64_t nv) {
+    const float* __restrict__ scale, float* __restrict__ xt, int64_t stride, int64_t nv, int rem) {
   const int k = blockIdx.y;
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i >= nv) return;
-  int64_t so = 0;
-  if constexpr (BF16_OUT) {
-    so = shadow_offset4(map, i * VEC);
-    if (so < 0) return;
-  }
   const float sc = scale[k];
-  auto xv = ldv<VEC>(x + (int64_t)k * stride + i * VEC);
-  auto gv = ldv<VEC>(g + (int64_t)k * g_stride + i * VEC);
-  typename Vec<VEC>::type o;
+  const float* xk = x + (int64_t)k * stride + i * 4;
+  const float* gk = g + (int64_t)k * g_stride + i * 4;
+  float* tk = xt + (int64_t)k * stride + i * 4;
+  if (i < nv) {
+    const f32x4 xv = ldv(xk), gv = ld_any<true>(gk);
+    f32x4 o;
 #pragma unroll
-  for (int e = 0; e < VEC; ++e) set_elem(o, e, ascent_point(elem(xv, e), sc, elem(gv, e)));
-  if constexpr (BF16_OUT) {
-    store_bf16<VEC>(xt16 + (int64_t)k * shadow_stride + so, o);
-  } else {
-    st_param<VEC, STREAM>(xt + (int64_t)k * stride + i * VEC, o);
+    for (int e = 0; e < 4; ++e) o[e] = ascent_point(xv[e], sc, gv[e]);
+    st_param<STREAM>(tk, o);
+  } else if (i == nv) {
+    for (int e = 0; e < rem; ++e) tk[e] = ascent_point(xk[e], sc, gk[e]);
   }
 }
 
-// The same for bf16 operands, walking the weight matrices in tiles instead of the flat vector: a
+// For bf16 operands x~ exists only as the operand copy of the weight matrices (blocked layout);
+// elements of no weight matrix (biases, padding) are not stored at all: the perturbed biases are
+// formed in the GEMM epilogue from x, g1 and scale.  This kernel walks the weight matrices in tiles: a
 // workgroup takes 8 rows x 128 columns of one matrix, a wavefront 8 rows x 32 columns, so that the
 // wavefront's 256 results are 512 consecutive bytes of one block of the copy (the flat walk
 // writes 64-byte pieces of 8 different blocks per wavefront and reached 67 % of HBM peak here
@@ -250,12 +243,12 @@ __global__ __launch_bounds__(kThreads) void perturb_tiled_kernel(
   if (r >= tiles.rows[s] || c >= map.ldw[s]) return;
   const int64_t flat = map.begin[s] + (int64_t)r * map.ldw[s] + c;
   const float sc = scale[k];
-  const auto xv = ldv<4>(x + (int64_t)k * stride + flat);
-  const auto gv = ldv<4>(g + (int64_t)k * g_stride + flat);
-  typename Vec<4>::type o;
+  const auto xv = ldv(x + (int64_t)k * stride + flat);
+  const auto gv = ldv(g + (int64_t)k * g_stride + flat);
+  f32x4 o;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) set_elem(o, e, ascent_point(elem(xv, e), sc, elem(gv, e)));
-  store_bf16<4>(xt16 + (int64_t)k * shadow_stride + map.shadow[s] + b32s_offset(r, c, map.cblocks[s]), o);
+  for (int e = 0; e < 4; ++e) o[e] = ascent_point(xv[e], sc, gv[e]);
+  store_bf16(xt16 + (int64_t)k * shadow_stride + map.shadow[s] + b32s_offset(r, c, map.cblocks[s]), o);
 }
 
 // ---- descent + coupling -------------------------------------------------------------------------
@@ -265,77 +258,155 @@ __global__ __launch_bounds__(kThreads) void perturb_tiled_kernel(
 // once, measured 8-12 % slower at K = 8 and 16; sending the K workgroups of a piece to the same
 // XCD, so that y misses only one L2, measured 4-9 % slower: the other XCDs' misses are served
 // by the memory-side cache, and the launch order here keeps each XCD on fewer DRAM pages.)
-template <int VEC, bool SHADOW, bool STREAM, typename NOISE>
+//
+// ASCENT: both gradients are at hand (nothing is computed at the perturbed point in between), and
+// x~ = x + scale g1 is written by the same pass, which reads x once: 36 instead of 12 + 28 bytes per
+// value.  Ten streams that miss the caches run faster the fewer bytes are in flight: one workgroup of 256
+// per compute unit (`room` keeps the others out), two words per lane, takes 4.76 ms for 8 x 10^8 values (6.05
+// TB/s), one word per lane 5.22; two workgroups with one word per lane 4.90, three 4.97, eight 5.27; four
+// words and as many workgroups as fit 5.35; a workgroup of 1024 4.91; the two kernels it replaces take 5.21.
+// ASCENT_SUMS: the norm pass left at most kProloguePartials partial sums per replica, and
+// every wavefront adds them up itself while its loads are under way, which saves the launch that
+// would do it (4 us of a step that takes 14 at 4 x 270410 values; 42 with four launches, norms by
+// 20 workgroups and single floats); the first workgroup of a replica writes norm and scale.
+template <int ASCENT, bool SHADOW, bool STREAM, typename NOISE> struct DescentShape {
+  static constexpr bool wide = ASCENT != 0 && STREAM;
+  static constexpr int words = wide ? 2 : 1;
+  static constexpr int room = wide ? 84 << 10 : 16;      // bytes of LDS
+};
+
+template <int ASCENT, bool SHADOW, bool STREAM, typename NOISE>
 __global__ __launch_bounds__(kThreads) void descent_kernel(
     float* __restrict__ x, const float* __restrict__ g, int64_t g_stride, float* __restrict__ v,
     float* __restrict__ S, const float* __restrict__ y, uint16_t* __restrict__ shadow,
-    ShadowMap map, int64_t shadow_stride, int64_t stride, int64_t nv, int K, ReplicaScalars lam,
-    float lr, float mu, int nesterov, NOISE noise, const int32_t* __restrict__ restart) {
-  const int64_t b = blockIdx.x;
-  const int k = (int)(b % K);
-  const int64_t i = (b / K) * kThreads + threadIdx.x;
-  if (i >= nv) return;
-  const auto yv = ldc<VEC>(y + i * VEC);
-  const int64_t o = (int64_t)k * stride + i * VEC;
-  auto xv = ldv<VEC>(x + o);
-  auto gv = ldv<VEC>(g + (int64_t)k * g_stride + i * VEC);
-  auto vv = ldv<VEC>(v + o);
-  typename Vec<VEC>::type sv;
-  if (restart != nullptr && restart[k] == 1) {       // the sum starts afresh: its memory is stale
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) set_elem(sv, e, 0.f);
-  } else {
-    sv = ldv<VEC>(S + o);
+    ShadowMap map, int64_t shadow_stride, int64_t stride, int64_t n, int K, ReplicaScalars lam,
+    float lr, float mu, int nesterov, NOISE noise, const int32_t* __restrict__ restart, AscentPass up) {
+  using Shape = DescentShape<ASCENT, SHADOW, STREAM, NOISE>;
+  constexpr int W = Shape::words;
+  constexpr bool ascend = ASCENT != ASCENT_NONE;
+  if constexpr (Shape::wide) {
+    __shared__ unsigned char room[Shape::room];
+    asm volatile("" ::"v"(room));      // allocated, never touched
   }
-  const float lk = lam.v[k];
-  float xi[4] = {0.f, 0.f, 0.f, 0.f};      // sigma sqrt(2 eta) xi of the Langevin sampler
-  if constexpr (!std::is_same<NOISE, NoNoise>::value) {
-    if constexpr (VEC == 4) {
-      langevin4(noise, k, i * 4, xi);
-    } else {
-      float grp[4];
-      langevin4(noise, k, i & ~(int64_t)3, grp);
-      xi[0] = grp[i & 3];
+  const int k = (int)(blockIdx.x % (unsigned)K);
+  const int64_t beg = (int64_t)(blockIdx.x / (unsigned)K) * (kThreads * W * 4);      // first value of the workgroup
+  const int lane = threadIdx.x & 63;
+  const unsigned at = ((threadIdx.x >> 6) * (64 * W) + lane) * 4;    // of the lane, relative to it
+  float* xk = x + (int64_t)k * stride + beg;
+  const float* gk = g + (int64_t)k * g_stride + beg;
+  const float* hk = ascend ? up.g1 + (int64_t)k * up.g1_stride + beg : nullptr;
+  float* vk = v + (int64_t)k * stride + beg;
+  float* Sk = S + (int64_t)k * stride + beg;
+  const float* yk = y + beg;
+  float* tk = ascend ? up.xt + (int64_t)k * stride + beg : nullptr;
+  const bool fresh = restart != nullptr && restart[k] == 1;      // the sum starts afresh: its memory is stale
+  const bool whole = beg + kThreads * W * 4 <= n;
+  f32x4 yv[W], xv[W], gv[W], vv[W], sv[W], hv[W];
+  if (whole) {
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      const unsigned o = at + w * 256;
+      yv[w] = ldc(yk + o);
+      xv[w] = ldv(xk + o);
+      gv[w] = ld_any<true>(gk + o);
+      vv[w] = ldv(vk + o);
+      if constexpr (ascend) hv[w] = ld_any<true>(hk + o);
+      sv[w] = f32x4{};
+    }
+    if (!fresh) {
+#pragma unroll
+      for (int w = 0; w < W; ++w) sv[w] = ldv(Sk + at + w * 256);
     }
   }
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) {
-    float xe = elem(xv, e), ve = elem(vv, e), se = elem(sv, e);
-    sampler_step(elem(gv, e), elem(yv, e), lk, lr, mu, nesterov, xi[e], xe, ve, se);
-    set_elem(vv, e, ve);
-    set_elem(xv, e, xe);
-    set_elem(sv, e, se);
+  float sc = 0.f;
+  if constexpr (ASCENT == ASCENT_SUMS) {
+    const double* part = up.partials + (int64_t)k * up.nblk;
+    double s = lane < up.nblk ? part[lane] : 0.0;
+    if (lane + 64 < up.nblk) s += part[lane + 64];
+    s = __shfl(wave_sum(s), 0, 64);
+    const double norm = sqrt(s);
+    sc = (float)((double)up.rho / (norm + (double)up.gamma));
+    if (beg == 0 && threadIdx.x == 0) {
+      up.norms[k] = (float)norm;
+      up.scale[k] = sc;
+    }
+  } else if constexpr (ASCENT == ASCENT_SCALE) {
+    sc = up.scale[k];
   }
-  st_param<VEC, STREAM>(x + o, xv);
-  stv<VEC>(v + o, vv);
-  stv<VEC>(S + o, sv);
-  if constexpr (SHADOW) {
-    const int64_t so = shadow_offset4(map, i * VEC);
-    if (so >= 0) store_bf16<VEC>(shadow + (int64_t)k * shadow_stride + so, xv);
+  const float lk = lam.v[k];
+  if (whole) {
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      const unsigned o = at + w * 256;
+      f32x4 tv = {};
+      float xi[4] = {0.f, 0.f, 0.f, 0.f};      // sigma sqrt(2 eta) xi of the Langevin sampler
+      if constexpr (!std::is_same<NOISE, NoNoise>::value) langevin4(noise, k, beg + o, xi);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float xe = xv[w][e], ve = vv[w][e], se = sv[w][e];
+        if constexpr (ascend) tv[e] = ascent_point(xe, sc, hv[w][e]);
+        sampler_step(gv[w][e], yv[w][e], lk, lr, mu, nesterov, xi[e], xe, ve, se);
+        vv[w][e] = ve;
+        xv[w][e] = xe;
+        sv[w][e] = se;
+      }
+      st_param<STREAM>(xk + o, xv[w]);
+      stv(vk + o, vv[w]);
+      stv(Sk + o, sv[w]);
+      if constexpr (ascend) st_param<STREAM>(tk + o, tv);
+      if constexpr (SHADOW) {
+        const int64_t so = shadow_offset4(map, beg + o);
+        if (so >= 0) store_bf16(shadow + (int64_t)k * shadow_stride + so, xv[w]);
+      }
+    }
+    return;
+  }
+  // a replica's last workgroup, value by value
+  for (int w = 0; w < W; ++w) {
+    const unsigned o = at + w * 256;
+    if (beg + o >= n) return;
+    const int m = n - beg - o < 4 ? (int)(n - beg - o) : 4;
+    float xi[4] = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (!std::is_same<NOISE, NoNoise>::value) langevin4(noise, k, beg + o, xi);
+    f32x4 nx = {};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (e >= m) continue;
+      float xe = xk[o + e], ve = vk[o + e], se = fresh ? 0.f : Sk[o + e];
+      if constexpr (ascend) tk[o + e] = ascent_point(xe, sc, hk[o + e]);
+      sampler_step(gk[o + e], yk[o + e], lk, lr, mu, nesterov, xi[e], xe, ve, se);
+      xk[o + e] = nx[e] = xe;
+      vk[o + e] = ve;
+      Sk[o + e] = se;
+    }
+    if constexpr (SHADOW) {
+      const int64_t so = shadow_offset4(map, beg + o);
+      if (so >= 0) store_bf16(shadow + (int64_t)k * shadow_stride + so, nx);
+    }
   }
 }
 
 // ---- average over replicas (synchronous data-parallel baseline) ---------------------------------
-template <int VEC>
 __global__ __launch_bounds__(kThreads) void grad_mean_kernel(
-    const float* src, int64_t src_stride, float* dst, int64_t dst_stride, int64_t nv, int K,
+    const float* src, int64_t src_stride, float* dst, int64_t dst_stride, int64_t nv, int rem, int K,
     int copies) {
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i >= nv) return;
-  auto acc = ldv<VEC>(src + i * VEC);
-  for (int k = 1; k < K; ++k) {
-    const auto gv = ldv<VEC>(src + (int64_t)k * src_stride + i * VEC);
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) set_elem(acc, e, elem(acc, e) + elem(gv, e));
-  }
   const float inv = 1.f / (float)K;
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) set_elem(acc, e, elem(acc, e) * inv);
-  for (int c = 0; c < copies; ++c) stv<VEC>(dst + (int64_t)c * dst_stride + i * VEC, acc);
+  if (i < nv) {
+    f32x4 acc = ld_any<true>(src + i * 4);
+    for (int k = 1; k < K; ++k) acc += ld_any<true>(src + (int64_t)k * src_stride + i * 4);
+    acc *= inv;
+    for (int c = 0; c < copies; ++c) stv(dst + (int64_t)c * dst_stride + i * 4, acc);
+  } else if (i == nv) {
+    for (int64_t j = i * 4; j < i * 4 + rem; ++j) {
+      float acc = src[j];
+      for (int k = 1; k < K; ++k) acc += src[(int64_t)k * src_stride + j];
+      for (int c = 0; c < copies; ++c) dst[(int64_t)c * dst_stride + j] = acc * inv;
+    }
+  }
 }
 
 // ---- center update ------------------------------------------------------------------------------
-template <int VEC>
 __global__ __launch_bounds__(kThreads) void center_kernel(
     float* __restrict__ S, float* __restrict__ y, float* __restrict__ gprev, int64_t stride,
     int64_t nv, DueList due, float inv_m, float beta, float lr_center, int has_prev,
@@ -345,38 +416,33 @@ __global__ __launch_bounds__(kThreads) void center_kernel(
   if (restart != nullptr && blockIdx.x == 0 && (int)threadIdx.x < due.n) restart[due.idx[threadIdx.x]] = 2;
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i >= nv) return;
-  typename Vec<VEC>::type tot, zero;
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) { set_elem(tot, e, 0.f); set_elem(zero, e, 0.f); }
+  f32x4 tot = {};
   for (int j = 0; j < due.n; ++j) {
-    float* p = S + (int64_t)due.idx[j] * stride + i * VEC;
-    auto sv = ldv<VEC>(p);
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) set_elem(tot, e, elem(tot, e) + elem(sv, e));
-    if (restart == nullptr) stv<VEC>(p, zero);
+    float* p = S + (int64_t)due.idx[j] * stride + i * 4;
+    tot += ldv(p);
+    if (restart == nullptr) stv(p, f32x4{});
   }
-  auto yv = ldc<VEC>(y + i * VEC);
-  auto pv = ldc<VEC>(gprev + i * VEC);
-  typename Vec<VEC>::type gp;
+  f32x4 yv = ldc(y + i * 4);
+  const f32x4 pv = ldc(gprev + i * 4);
+  f32x4 gp;
 #pragma unroll
-  for (int e = 0; e < VEC; ++e) {
-    const float gpe = elem(tot, e) * inv_m - elem(yv, e);
-    const float ge = has_prev ? gpe + beta * (gpe - elem(pv, e)) : gpe;
-    set_elem(gp, e, gpe);
-    set_elem(yv, e, elem(yv, e) + lr_center * ge);
+  for (int e = 0; e < 4; ++e) {
+    const float gpe = tot[e] * inv_m - yv[e];
+    const float ge = has_prev ? gpe + beta * (gpe - pv[e]) : gpe;
+    gp[e] = gpe;
+    yv[e] = yv[e] + lr_center * ge;
   }
-  *reinterpret_cast<typename Vec<VEC>::type*>(y + i * VEC) = yv;
-  *reinterpret_cast<typename Vec<VEC>::type*>(gprev + i * VEC) = gp;
+  *reinterpret_cast<f32x4*>(y + i * 4) = yv;
+  *reinterpret_cast<f32x4*>(gprev + i * 4) = gp;
 }
 
 // ---- small utility kernels ------------------------------------------------------------------------
-template <int VEC>
 __global__ __launch_bounds__(kThreads) void broadcast_kernel(
     const float* __restrict__ src, float* __restrict__ dst, int64_t stride, int64_t nv, int K) {
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i >= nv) return;
-  auto sv = ldc<VEC>(src + i * VEC);
-  for (int k = 0; k < K; ++k) stv<VEC>(dst + (int64_t)k * stride + i * VEC, sv);
+  const f32x4 sv = ldc(src + i * 4);
+  for (int k = 0; k < K; ++k) stv(dst + (int64_t)k * stride + i * 4, sv);
 }
 
 // bf16 operand copy of the weight matrices of replica blockIdx.y from its fp32 parameters.
@@ -388,7 +454,7 @@ __global__ __launch_bounds__(kThreads) void shadow_refresh_kernel(
   if (i >= nv) return;
   const int64_t so = shadow_offset4(map, i * 4);
   if (so < 0) return;
-  store_bf16<4>(shadow + (int64_t)k * shadow_stride + so, ldc<4>(x + (int64_t)k * stride + i * 4));
+  store_bf16(shadow + (int64_t)k * shadow_stride + so, ldc(x + (int64_t)k * stride + i * 4));
 }
 
 // Row-major bf16 matrix of replica blockIdx.y -> blocked layout; one thread per 8 elements.
@@ -429,7 +495,6 @@ __global__ __launch_bounds__(kThreads) void pad_rows_kernel(const T* __restrict_
   }
 }
 
-inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kThreads - 1) / kThreads); }
 inline unsigned capped_blocks(int64_t n) {
   int64_t b = (n + kThreads - 1) / kThreads;
@@ -438,14 +503,19 @@ inline unsigned capped_blocks(int64_t n) {
 
 }  // namespace
 
+int sumsq_blocks(int64_t n) {
+  const int64_t small = (n + 4095) / 4096, large = (n + 16383) / 16384;
+  if (large <= kProloguePartials) return (int)(small < 1 ? 1 : small < kProloguePartials ? small : kProloguePartials);
+  return (int)(large < kMaxPartials ? large : kMaxPartials);
+}
+
 void launch_sumsq_partials(const float* g, int64_t g_stride, int64_t n, int K, double* partials,
-                           int nblk, hipStream_t s) {
+                           int nblk, hipStream_t s, int32_t* restart) {
   dim3 grid(nblk, K);
-  if (n % 4 == 0 && g_stride % 4 == 0 && aligned16(g)) {
-    sumsq_partials_kernel<4><<<grid, kThreads, 0, s>>>(g, g_stride, n / 4, partials, nblk);
-  } else {
-    sumsq_partials_kernel<1><<<grid, kThreads, 0, s>>>(g, g_stride, n, partials, nblk);
-  }
+  if ((int64_t)K * n * 4 > kCacheResidentBytes)
+    sumsq_partials_kernel<true><<<grid, kThreads, 0, s>>>(g, g_stride, n / 4, (int)(n % 4), partials, nblk, restart);
+  else
+    sumsq_partials_kernel<false><<<grid, kThreads, 0, s>>>(g, g_stride, n / 4, (int)(n % 4), partials, nblk, restart);
 }
 
 int launch_gram_dot(const float* G1, const float* G2, int64_t stride, int64_t n, int K, int pieces1,
@@ -469,8 +539,6 @@ void launch_norm_finish(const double* partials, int nblk, int64_t partials_strid
 void launch_perturb(const float* x, const float* g, int64_t g_stride, const float* scale,
                     float* xt_f32, uint16_t* xt_bf16, const ShadowMap* map, int64_t shadow_stride,
                     int64_t stride, int64_t n, int K, hipStream_t s) {
-  const bool vec = n % 4 == 0 && g_stride % 4 == 0 && stride % 4 == 0 && aligned16(g);
-  ShadowMap none{};
   if (xt_bf16) {
     // bf16 mode only exists for the MLP layouts, which are always vector-aligned
     TileMap tm{};
@@ -486,88 +554,93 @@ void launch_perturb(const float* x, const float* g, int64_t g_stride, const floa
     dim3 grid(total, K);
     perturb_tiled_kernel<<<grid, kThreads, 0, s>>>(x, g, g_stride, scale, xt_bf16, *map, tm,
                                                    shadow_stride, stride);
-  } else if (vec) {
-    dim3 grid(blocks_for(n / 4), K);
-    if ((int64_t)K * n * 4 > kCacheResidentBytes)
-      perturb_kernel<4, false, true><<<grid, kThreads, 0, s>>>(x, g, g_stride, scale, xt_f32, nullptr,
-                                                               none, 0, stride, n / 4);
-    else
-      perturb_kernel<4, false, false><<<grid, kThreads, 0, s>>>(x, g, g_stride, scale, xt_f32,
-                                                                nullptr, none, 0, stride, n / 4);
   } else {
-    dim3 grid(blocks_for(n), K);
-    perturb_kernel<1, false, true><<<grid, kThreads, 0, s>>>(x, g, g_stride, scale, xt_f32, nullptr,
-                                                             none, 0, stride, n);
+    dim3 grid(blocks_for((n + 3) / 4), K);
+    if ((int64_t)K * n * 4 > kCacheResidentBytes)
+      perturb_kernel<true><<<grid, kThreads, 0, s>>>(x, g, g_stride, scale, xt_f32, stride, n / 4, (int)(n % 4));
+    else
+      perturb_kernel<false><<<grid, kThreads, 0, s>>>(x, g, g_stride, scale, xt_f32, stride, n / 4, (int)(n % 4));
   }
 }
 
-template <typename NOISE>
+template <int ASCENT, typename NOISE>
 void launch_descent_with(float* x, const float* g, int64_t g_stride, float* v, float* S,
                          const float* y, uint16_t* shadow, const ShadowMap* map,
                          int64_t shadow_stride, int64_t stride, int64_t n, int K,
                          const ReplicaScalars& lam, float lr, float mu, int nesterov,
-                         const NOISE& noise, hipStream_t s, const int32_t* restart) {
-  const bool vec = n % 4 == 0 && g_stride % 4 == 0 && stride % 4 == 0 && aligned16(g);
+                         const NOISE& noise, hipStream_t s, const int32_t* restart, const AscentPass& up) {
   ShadowMap none{};
-  if (shadow) {
-    const unsigned grid = blocks_for(n / 4) * (unsigned)K;
-    descent_kernel<4, true, true, NOISE><<<grid, kThreads, 0, s>>>(
-        x, g, g_stride, v, S, y, shadow, *map, shadow_stride, stride, n / 4, K, lam, lr, mu,
-        nesterov, noise, restart);
-  } else if (vec) {
-    const unsigned grid = blocks_for(n / 4) * (unsigned)K;
-    if ((int64_t)K * n * 4 > kCacheResidentBytes)
-      descent_kernel<4, false, true, NOISE><<<grid, kThreads, 0, s>>>(
-          x, g, g_stride, v, S, y, nullptr, none, 0, stride, n / 4, K, lam, lr, mu, nesterov, noise,
-          restart);
-    else
-      descent_kernel<4, false, false, NOISE><<<grid, kThreads, 0, s>>>(
-          x, g, g_stride, v, S, y, nullptr, none, 0, stride, n / 4, K, lam, lr, mu, nesterov, noise,
-          restart);
-  } else {
-    const unsigned grid = blocks_for(n) * (unsigned)K;
-    descent_kernel<1, false, true, NOISE><<<grid, kThreads, 0, s>>>(
-        x, g, g_stride, v, S, y, nullptr, none, 0, stride, n, K, lam, lr, mu, nesterov, noise, restart);
+  auto go = [&](auto kernel, auto shape, uint16_t* copy, const ShadowMap& m, int64_t copy_stride) {
+    using Shape = decltype(shape);
+    const unsigned grid = blocks_for(((n + 3) / 4 + Shape::words - 1) / Shape::words) * (unsigned)K;
+    kernel<<<grid, kThreads, 0, s>>>(x, g, g_stride, v, S, y, copy, m, copy_stride, stride, n, K, lam, lr,
+                                           mu, nesterov, noise, restart, up);
+  };
+  if constexpr (ASCENT == ASCENT_NONE) {
+    if (shadow) {
+      go(descent_kernel<ASCENT, true, true, NOISE>, DescentShape<ASCENT, true, true, NOISE>{}, shadow, *map, shadow_stride);
+      return;
+    }
   }
+  if ((int64_t)K * n * 4 > kCacheResidentBytes)
+    go(descent_kernel<ASCENT, false, true, NOISE>, DescentShape<ASCENT, false, true, NOISE>{}, nullptr, none, 0);
+  else
+    go(descent_kernel<ASCENT, false, false, NOISE>, DescentShape<ASCENT, false, false, NOISE>{}, nullptr, none, 0);
 }
 
 void launch_descent(float* x, const float* g, int64_t g_stride, float* v, float* S,
                     const float* y, uint16_t* shadow, const ShadowMap* map, int64_t shadow_stride,
                     int64_t stride, int64_t n, int K, const ReplicaScalars& lam, float lr, float mu,
                     int nesterov, const NoiseMap* noise, hipStream_t s, const int32_t* restart) {
+  const AscentPass none{};
   if (noise)
-    launch_descent_with<NoiseMap>(x, g, g_stride, v, S, y, shadow, map, shadow_stride, stride, n, K,
-                                  lam, lr, mu, nesterov, *noise, s, restart);
+    launch_descent_with<ASCENT_NONE, NoiseMap>(x, g, g_stride, v, S, y, shadow, map, shadow_stride, stride, n, K,
+                                               lam, lr, mu, nesterov, *noise, s, restart, none);
   else
-    launch_descent_with<NoNoise>(x, g, g_stride, v, S, y, shadow, map, shadow_stride, stride, n, K,
-                                 lam, lr, mu, nesterov, NoNoise{}, s, restart);
+    launch_descent_with<ASCENT_NONE, NoNoise>(x, g, g_stride, v, S, y, shadow, map, shadow_stride, stride, n, K,
+                                              lam, lr, mu, nesterov, NoNoise{}, s, restart, none);
+}
+
+void launch_raw_norm(int64_t n, int K, hipStream_t s, int32_t* restart, const AscentPass& up) {
+  launch_sumsq_partials(up.g1, up.g1_stride, n, K, up.partials, up.nblk, s, restart);
+  if (!up.finish_in_descent())
+    launch_norm_finish(up.partials, up.nblk, up.nblk, K, up.rho, up.gamma, up.norms, up.scale, nullptr, 0, nullptr, s);
+}
+
+void launch_raw_descent(float* x, const float* g2, int64_t g_stride, float* v, float* S, const float* y,
+                        int64_t stride, int64_t n, int K, const ReplicaScalars& lam, float lr, float mu,
+                        int nesterov, const NoiseMap* noise, hipStream_t s, const int32_t* restart, const AscentPass& up) {
+  auto step = [&](auto ascent, const auto& how) {
+    launch_descent_with<decltype(ascent)::value>(x, g2, g_stride, v, S, y, nullptr, nullptr, 0, stride, n, K, lam, lr,
+                                                 mu, nesterov, how, s, restart, up);
+  };
+  auto choose = [&](const auto& how) {
+    if (up.xt == nullptr) step(std::integral_constant<int, ASCENT_NONE>{}, how);
+    else if (up.finish_in_descent()) step(std::integral_constant<int, ASCENT_SUMS>{}, how);
+    else step(std::integral_constant<int, ASCENT_SCALE>{}, how);
+  };
+  if (noise) choose(*noise);
+  else choose(NoNoise{});
 }
 
 void launch_grad_mean(const float* src, int64_t src_stride, float* dst, int64_t dst_stride,
                       int64_t n, int K, int copies, hipStream_t s) {
-  if (n % 4 == 0 && src_stride % 4 == 0 && dst_stride % 4 == 0 && aligned16(src) && aligned16(dst))
-    grad_mean_kernel<4><<<blocks_for(n / 4), kThreads, 0, s>>>(src, src_stride, dst, dst_stride,
-                                                               n / 4, K, copies);
-  else
-    grad_mean_kernel<1><<<blocks_for(n), kThreads, 0, s>>>(src, src_stride, dst, dst_stride, n, K,
-                                                           copies);
+  // dst is this library's own: rows of whole words of four, 16-byte aligned
+  grad_mean_kernel<<<blocks_for((n + 3) / 4), kThreads, 0, s>>>(src, src_stride, dst, dst_stride, n / 4, (int)(n % 4), K,
+                                                                copies);
 }
 
 void launch_center(float* S, float* y, float* gprev, int64_t stride, int64_t n,
                    const DueList& due, float inv_m, float beta, float lr_center, int has_prev,
                    hipStream_t s, int32_t* restart) {
-  if (n % 4 == 0 && stride % 4 == 0) {
-    center_kernel<4><<<blocks_for(n / 4), kThreads, 0, s>>>(S, y, gprev, stride, n / 4, due, inv_m,
-                                                            beta, lr_center, has_prev, restart);
-  } else {
-    center_kernel<1><<<blocks_for(n), kThreads, 0, s>>>(S, y, gprev, stride, n, due, inv_m, beta,
-                                                        lr_center, has_prev, restart);
-  }
+  // this library's own rows, padded with zeros to 64 values: the last word is whole, and stays zero where it pads
+  center_kernel<<<blocks_for((n + 3) / 4), kThreads, 0, s>>>(S, y, gprev, stride, (n + 3) / 4, due, inv_m,
+                                                             beta, lr_center, has_prev, restart);
 }
 
 void launch_broadcast(const float* src, float* dst, int64_t stride, int64_t n, int K, hipStream_t s) {
   // internal buffers only: n and stride are multiples of 4 by construction
-  broadcast_kernel<4><<<blocks_for(n / 4), kThreads, 0, s>>>(src, dst, stride, n / 4, K);
+  broadcast_kernel<<<blocks_for(n / 4), kThreads, 0, s>>>(src, dst, stride, n / 4, K);
 }
 
 void launch_shadow_refresh(const float* x, uint16_t* shadow, const ShadowMap& map, int64_t stride,

@@ -468,8 +468,7 @@ void build_layout(const lsam_config& c, Layout& lo) {
     }
   }
   if (lo.raw) {
-    int64_t nb = (lo.d_pad + 65535) / 65536;
-    lo.nblk = (int)(nb < 1 ? 1 : (nb > 1024 ? 1024 : nb));
+    lo.nblk = sumsq_blocks(lo.d);
   } else {
     // the first backward pass leaves one partial sum of squares per workgroup that wrote a
     // piece of the gradient: room for the most any tile choice can produce
@@ -1524,7 +1523,7 @@ int update_tail_first(lsam_ctx* c, const float* g1, int64_t g_stride, int64_t n,
                       bool partials_ready, bool perturb = true) {
   const Layout& lo = c->lo;
   hipStream_t s = c->stream;
-  int nparts = partials_ready ? c->norm_slots : (lo.nblk < 1024 ? lo.nblk : 1024);
+  const int nparts = partials_ready ? c->norm_slots : std::min(lo.nblk, kMaxPartials);
   if (!partials_ready) {
     LaunchTimer t(c, KC_SUMSQ);
     launch_sumsq_partials(g1, g_stride, n, lo.K, c->at<double>(lo.partials), nparts, s);
@@ -1555,7 +1554,9 @@ bool can_fuse_step(const lsam_ctx* c) {
   return c->lo.bf16 && c->cfg.algorithm == LSAM_ALG_LSAM && !(c->cfg.noise_scale > 0.f) && c->fuse_step;
 }
 
-int update_tail_second(lsam_ctx* c, const float* g2, int64_t g_stride, int64_t n, bool already_stepped = false) {
+// `up`: the norm of g1 and the perturbed point are still to come as well (raw vectors).
+int update_tail_second(lsam_ctx* c, const float* g2, int64_t g_stride, int64_t n, bool already_stepped = false,
+                       const AscentPass* up = nullptr) {
   const Layout& lo = c->lo;
   if (already_stepped) {
     ++c->t_step;
@@ -1570,7 +1571,12 @@ int update_tail_second(lsam_ctx* c, const float* g2, int64_t g_stride, int64_t n
     c->noise.amp = (float)((double)c->cfg.noise_scale * std::sqrt(2.0 * (double)c->lr));
     noise = &c->noise;
   }
-  {
+  if (up) {
+    LaunchTimer t(c, KC_DESCENT);
+    launch_raw_descent(c->at<float>(lo.x), g2, g_stride, c->at<float>(lo.v), c->at<float>(lo.S), c->at<float>(lo.y),
+                       lo.d_pad, n, lo.K, lam, c->lr, c->cfg.momentum, c->cfg.nesterov, noise, c->stream,
+                       c->at<int32_t>(lo.restart), *up);
+  } else {
     LaunchTimer t(c, KC_DESCENT);
     launch_descent(c->at<float>(lo.x), g2, g_stride, c->at<float>(lo.v), c->at<float>(lo.S),
                    c->at<float>(lo.y), lo.bf16 ? c->at<uint16_t>(lo.xt) : nullptr, &lo.map,
@@ -1883,8 +1889,17 @@ int lsam_step_grads(lsam_ctx* c, const float* g1, const float* g2) {
     }
     return update_tail_second(c, m, 0, lo.d);
   }
-  if ((rc = update_tail_first(c, g1, lo.d, lo.d, nullptr, false)) != LSAM_OK) return rc;
-  return update_tail_second(c, g2, lo.d, lo.d);
+  AscentPass up;
+  up.g1 = g1; up.g1_stride = lo.d;
+  up.partials = c->at<double>(lo.partials); up.nblk = lo.nblk;
+  up.rho = c->rho; up.gamma = c->cfg.gamma;
+  up.norms = c->at<float>(lo.norms); up.scale = c->at<float>(lo.scale);
+  if (c->rho != 0.f) up.xt = c->at<float>(lo.xt);
+  {
+    LaunchTimer t(c, KC_SUMSQ);
+    launch_raw_norm(lo.d, lo.K, c->stream, c->at<int32_t>(lo.restart), up);
+  }
+  return update_tail_second(c, g2, lo.d, lo.d, false, &up);
 }
 
 int lsam_sync(lsam_ctx* c) {

@@ -11,9 +11,8 @@
 namespace lsam {
 namespace {
 
-constexpr int kMaxBlocks = 1024;                    // partial sums per replica at most
 constexpr int kMaxDevices = 64;
-constexpr size_t kPartialBytes = (size_t)kMaxK * kMaxBlocks * sizeof(double);   // 512 KiB
+constexpr size_t kPartialBytes = (size_t)kMaxK * kMaxPartials * sizeof(double);   // 512 KiB
 constexpr size_t kScratchBytes = kPartialBytes + 2 * kMaxK * sizeof(float);     // + norms, scales
 
 // Host code never passes this name to a kernel: it is a stand-in on the host side.  The device
@@ -57,6 +56,18 @@ int scratch_for_current_device(void** out) {
   return LSAM_OK;
 }
 
+// Whether x~ lies over any of the step's other arrays.
+bool shares_memory(const lsam_update_desc* u, const float* x, const float* v, const float* S, const float* y,
+                   const float* g1, const float* g2, const float* xt) {
+  auto meets = [&](const float* p, int64_t rows, int64_t stride) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(xt), b = reinterpret_cast<uintptr_t>(p);
+    const uintptr_t la = ((u->K - 1) * u->stride + u->d) * 4, lb = ((rows - 1) * stride + u->d) * 4;
+    return a < b + lb && b < a + la;
+  };
+  return meets(x, u->K, u->stride) || meets(v, u->K, u->stride) || meets(S, u->K, u->stride) || meets(y, 1, u->stride) ||
+         meets(g1, u->K, u->g_stride) || meets(g2, u->K, u->g_stride);
+}
+
 }  // namespace
 
 }  // namespace lsam
@@ -96,18 +107,27 @@ extern "C" int lsam_step_grads_static(const lsam_update_desc* u, float* x, float
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int K = u->K;
   const int64_t d = u->d;
-  // as many partial sums per replica as the context-based call uses for the same d
-  int64_t nb = ((d + 63) / 64 * 64 + 65535) / 65536;
-  const int nblk = (int)(nb < 1 ? 1 : (nb > kMaxBlocks ? kMaxBlocks : nb));
-  // every slot that is read below is written first, so nothing of an earlier call is seen
-  launch_sumsq_partials(g1, u->g_stride, d, K, partials, nblk, s);
-  launch_norm_finish(partials, nblk, nblk, K, u->rho, u->gamma, norms, scale, nullptr, 0, nullptr, s);
-  if (u->rho != 0.f)
-    launch_perturb(x, g1, u->g_stride, scale, xt, nullptr, nullptr, 0, u->stride, d, K, s);
   ReplicaScalars lam;
   for (int i = 0; i < K; ++i) lam.v[i] = u->lambda[i];
-  launch_descent(x, g2, u->g_stride, v, S, y, nullptr, nullptr, 0, u->stride, d, K, lam, u->lr,
-                 u->momentum, u->nesterov, nullptr, s);
+  // every slot that is read is written first, so nothing of an earlier call is seen
+  AscentPass up;
+  up.g1 = g1; up.g1_stride = u->g_stride;
+  up.partials = partials; up.nblk = sumsq_blocks(d);
+  up.rho = u->rho; up.gamma = u->gamma;
+  up.norms = norms; up.scale = scale;
+  if (u->rho != 0.f) up.xt = xt;
+  if (up.xt && shares_memory(u, x, v, S, y, g1, g2, xt)) {
+    // x~ takes the place of something that the descent reads: it has to be whole before that
+    launch_sumsq_partials(g1, u->g_stride, d, K, partials, up.nblk, s);
+    launch_norm_finish(partials, up.nblk, up.nblk, K, u->rho, u->gamma, norms, scale, nullptr, 0, nullptr, s);
+    launch_perturb(x, g1, u->g_stride, scale, xt, nullptr, nullptr, 0, u->stride, d, K, s);
+    launch_descent(x, g2, u->g_stride, v, S, y, nullptr, nullptr, 0, u->stride, d, K, lam, u->lr,
+                   u->momentum, u->nesterov, nullptr, s);
+  } else {
+    launch_raw_norm(d, K, s, nullptr, up);
+    launch_raw_descent(x, g2, u->g_stride, v, S, y, u->stride, d, K, lam, u->lr, u->momentum, u->nesterov, nullptr, s,
+                       nullptr, up);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     set_last_error(hipGetErrorString(e));

@@ -46,6 +46,12 @@ __device__ __forceinline__ float ascent_point(float x, float scale, float g) {
   return __builtin_fmaf(scale, g, x);
 }
 
+// Parameters that the next kernels read back: streamed past the caches when all replicas
+// together are far larger than they are (K d floats; measured at 3.2 GB: +5-9 % for the two
+// kernels with streaming stores), left in them when they fit (at 67 MB the following forward
+// GEMMs and the next descent find them there: -2 % per step).
+constexpr int64_t kCacheResidentBytes = 96ll << 20;
+
 // ---- streaming kernels (update path) ---------------------------------------------------
 
 // Sum of squares, pass 1: per (replica, block) partial sums in double.

@@ -55,6 +55,7 @@ struct Bf16GemmParams {
   // and the operand copy that receives bf16(x + scale g) (fshadow, strideShadow, cbShadow above)
   const float* ax; const float* ascale;
   int mode;                               // EPI_* the launch asks for
+  int cached;                             // EPI_STEP, EPI_ASCEND: of the .._CACHED kind
   // EPI_STORE with a plain fp32 result only: the contraction is cut into ksplit pieces, each
   // taken by a workgroup of its own; piece j of replica k writes its partial result at
   // C + k * strideC + j * strideSplit (elements)
@@ -199,14 +200,17 @@ template <> struct Out<__bf16> {
 //   EPI_SUMSQ   weight gradient of the first pass: only its sum of squares is wanted
 //   EPI_ASCEND  weight gradient of the first pass, recomputed once the norm is known: write
 //               the operand copy of the perturbed weights, bf16(x + scale * g)
-enum { EPI_STORE = 0, EPI_STEP = 1, EPI_SUMSQ = 2, EPI_ASCEND = 3 };
+//   .._CACHED   the same on a state that stays in the caches: its loads and stores are ordinary ones
+enum { EPI_STORE = 0, EPI_STEP = 1, EPI_SUMSQ = 2, EPI_ASCEND = 3, EPI_STEP_CACHED = 4, EPI_ASCEND_CACHED = 5 };
 constexpr int kStepGroup = 4;      // EPI_STEP: side of the tile groups an XCD takes through all replicas
 constexpr int kAscendBand = 2;    // EPI_ASCEND: tile rows of the band all XCDs share
 
-template <typename TC, int BM, int BN, int NSTAGE, bool A_KMAJOR, bool B_KMAJOR, int OCC, int MODE = EPI_STORE>
+template <typename TC, int BM, int BN, int NSTAGE, bool A_KMAJOR, bool B_KMAJOR, int OCC, int KIND = EPI_STORE>
 __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams p) {
+  constexpr bool CACHED = KIND == EPI_STEP_CACHED || KIND == EPI_ASCEND_CACHED;
+  constexpr int MODE = KIND == EPI_STEP_CACHED ? EPI_STEP : KIND == EPI_ASCEND_CACHED ? EPI_ASCEND : KIND;
   static_assert(MODE == EPI_STORE || sizeof(TC) == 4, "the fused epilogues work on fp32 results");
-  static_assert(NSTAGE == 3 || NSTAGE == 4, "ring of 3 or 4 stages");
+  static_assert(NSTAGE == 3 || NSTAGE == 4 || NSTAGE == 8, "ring of 3, 4 or 8 stages");
   constexpr int TM = BM / 64, TN = BN / 64;
   constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
   constexpr int EPI_PITCH = BN / 2 + 4;                       // epilogue staging pitch (floats)
@@ -215,7 +219,12 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams
   __shared__ __attribute__((aligned(1024))) unsigned char st0[STAGE_BYTES];
   __shared__ __attribute__((aligned(1024))) unsigned char st1[STAGE_BYTES];
   __shared__ __attribute__((aligned(1024))) unsigned char st2[STAGE_BYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char st3[NSTAGE == 4 ? STAGE_BYTES : 1024];
+  __shared__ __attribute__((aligned(1024))) unsigned char st3[NSTAGE >= 4 ? STAGE_BYTES : 1024];
+  constexpr int MORE_BYTES = NSTAGE == 8 ? STAGE_BYTES : 1024;
+  __shared__ __attribute__((aligned(1024))) unsigned char st4[MORE_BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char st5[MORE_BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char st6[MORE_BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char st7[MORE_BYTES];
 
   const int w = blockIdx.x;
   int bat, m0, n0, t_in = 0, piece = 0;
@@ -325,15 +334,25 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams
   lds_byte* s1 = (lds_byte*)st1;
   lds_byte* s2 = (lds_byte*)st2;
   lds_byte* s3 = (lds_byte*)st3;
+  lds_byte* s4 = (lds_byte*)st4;
+  lds_byte* s5 = (lds_byte*)st5;
+  lds_byte* s6 = (lds_byte*)st6;
+  lds_byte* s7 = (lds_byte*)st7;
 
   // Tiles past the last k-step are still requested (as zeros), which keeps the number of
   // loads in flight, and so the wait counts, the same in every step, and lets the loop run
-  // in whole rounds of the four stages.
+  // in whole rounds of the stages.
   oa.issue(rsrcA, s0, 0, ksteps); ob.issue(rsrcB, s0 + A_BYTES, 0, ksteps);
   oa.issue(rsrcA, s1, 1, ksteps); ob.issue(rsrcB, s1 + A_BYTES, 1, ksteps);
   oa.issue(rsrcA, s2, 2, ksteps); ob.issue(rsrcB, s2 + A_BYTES, 2, ksteps);
-  if constexpr (NSTAGE == 4) {
+  if constexpr (NSTAGE >= 4) {
     oa.issue(rsrcA, s3, 3, ksteps); ob.issue(rsrcB, s3 + A_BYTES, 3, ksteps);
+  }
+  if constexpr (NSTAGE == 8) {
+    oa.issue(rsrcA, s4, 4, ksteps); ob.issue(rsrcB, s4 + A_BYTES, 4, ksteps);
+    oa.issue(rsrcA, s5, 5, ksteps); ob.issue(rsrcB, s5 + A_BYTES, 5, ksteps);
+    oa.issue(rsrcA, s6, 6, ksteps); ob.issue(rsrcB, s6 + A_BYTES, 6, ksteps);
+    oa.issue(rsrcA, s7, 7, ksteps); ob.issue(rsrcB, s7 + A_BYTES, 7, ksteps);
   }
   __builtin_amdgcn_s_waitcnt(waitcnt((NSTAGE - 1) * NL, 15));   // tile 0 has landed (this wavefront's part)
   asm volatile("" ::: "memory");
@@ -368,9 +387,17 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams
     LSAM_GEMM_STEP(s1, s2)
     if constexpr (NSTAGE == 3) {
       LSAM_GEMM_STEP(s2, s0)
-    } else {
+    } else if constexpr (NSTAGE == 4) {
       LSAM_GEMM_STEP(s2, s3)
       LSAM_GEMM_STEP(s3, s0)
+    } else {
+      LSAM_GEMM_STEP(s2, s3)
+      LSAM_GEMM_STEP(s3, s4)
+      if (ks >= ksteps) break;
+      LSAM_GEMM_STEP(s4, s5)
+      LSAM_GEMM_STEP(s5, s6)
+      LSAM_GEMM_STEP(s6, s7)
+      LSAM_GEMM_STEP(s7, s0)
     }
   }
 #undef LSAM_GEMM_STEP
@@ -429,9 +456,10 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams
     // once per step: loads are non-temporal, stores non-temporal and written through at system
     // scope, the 8-byte stores of the operand copy as well.  Measured on 16 x [8192 x 8192]
     // layers: no hints 31.6 ms per step of the largest configuration, nt on loads and state
-    // stores 30.2, nt + write-through on every store 28.7 (sc0 alone 31.6, sc1 alone 28.8).
-    constexpr int NT = 2;
-    constexpr int WT = 2 | 1 | 16;
+    // stores 30.2, nt + write-through on every store 28.7 (sc0 alone 31.6, sc1 alone 28.8).  A state
+    // that stays in the caches is left there: 276 -> 251 us per step of 3 replicas 1000-1500-777-37, batch 100.
+    constexpr int NT = CACHED ? 0 : 2;
+    constexpr int WT = CACHED ? 0 : 2 | 1 | 16;
     const unsigned wbytes = (unsigned)p.M * (unsigned)p.ldC * 4u;
     const __amdgpu_buffer_rsrc_t rx = make_rsrc(p.fx + (long long)bat * p.strideC, wbytes);
     const __amdgpu_buffer_rsrc_t rv = make_rsrc(p.fv + (long long)bat * p.strideC, wbytes);
@@ -523,7 +551,7 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
           const unsigned off = col_ok ? off0 + (unsigned)(i * 32 + (pb + u) * ROWS_PER_PASS) * rowbytes : kOut;
-          xv[u] = __builtin_amdgcn_raw_buffer_load_b128(rx, off, 0, 2);
+          xv[u] = __builtin_amdgcn_raw_buffer_load_b128(rx, off, 0, CACHED ? 0 : 2);
         }
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
@@ -536,7 +564,7 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams
           const unsigned woff = (col_ok && m < p.M) ? (unsigned)b32s_offset(m, n, p.cbShadow) * 2u : kOut;
           // non-temporal and written through, like the step's stores of the same copy (with a
           // plain store here the step kernel that later overwrites the copy ran 4 % slower)
-          __builtin_amdgcn_raw_buffer_store_b64(Out<__bf16>::from(xe), rw, woff, 0, 2 | 1 | 16);
+          __builtin_amdgcn_raw_buffer_store_b64(Out<__bf16>::from(xe), rw, woff, 0, CACHED ? 0 : 2 | 1 | 16);
         }
       }
     }
@@ -620,7 +648,9 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams
 #define LSAM_INSTANTIATE(TC, AK, BK_)                                                         \
   template __global__ void gemm_bf16_kernel<TC, 256, 256, 4, AK, BK_, 1>(Bf16GemmParams);      \
   template __global__ void gemm_bf16_kernel<TC, 256, 128, 3, AK, BK_, 2>(Bf16GemmParams);      \
-  template __global__ void gemm_bf16_kernel<TC, 128, 128, 4, AK, BK_, 2>(Bf16GemmParams);
+  template __global__ void gemm_bf16_kernel<TC, 128, 128, 4, AK, BK_, 2>(Bf16GemmParams);      \
+  template __global__ void gemm_bf16_kernel<TC, 64, 64, 8, AK, BK_, 2>(Bf16GemmParams);        \
+  template __global__ void gemm_bf16_kernel<TC, 64, 64, 4, AK, BK_, 4>(Bf16GemmParams);
 LSAM_INSTANTIATE(float, true, true)
 LSAM_INSTANTIATE(float, true, false)
 LSAM_INSTANTIATE(float, false, false)
@@ -631,21 +661,24 @@ LSAM_INSTANTIATE(__bf16, false, false)
 #define LSAM_INSTANTIATE_MODE(M)                                                                         \
   template __global__ void gemm_bf16_kernel<float, 256, 256, 4, false, false, 1, M>(Bf16GemmParams);  \
   template __global__ void gemm_bf16_kernel<float, 256, 128, 3, false, false, 2, M>(Bf16GemmParams);  \
-  template __global__ void gemm_bf16_kernel<float, 128, 128, 4, false, false, 2, M>(Bf16GemmParams);
+  template __global__ void gemm_bf16_kernel<float, 128, 128, 4, false, false, 2, M>(Bf16GemmParams);  \
+  template __global__ void gemm_bf16_kernel<float, 64, 64, 4, false, false, 4, M>(Bf16GemmParams);
 LSAM_INSTANTIATE_MODE(EPI_STEP)
 LSAM_INSTANTIATE_MODE(EPI_SUMSQ)
 LSAM_INSTANTIATE_MODE(EPI_ASCEND)
 #undef LSAM_INSTANTIATE_MODE
+template __global__ void gemm_bf16_kernel<float, 64, 64, 4, false, false, 4, EPI_STEP_CACHED>(Bf16GemmParams);
+template __global__ void gemm_bf16_kernel<float, 64, 64, 4, false, false, 4, EPI_ASCEND_CACHED>(Bf16GemmParams);
 
 template <typename TC, int BM, int BN, int NSTAGE, bool AK, bool BK_>
 int launch_one(const Bf16GemmParams& p0, hipStream_t s, int* slots) {
-  constexpr int OCC = (BM * BN >= 256 * 256) ? 1 : 2;
+  constexpr int OCC = BM * BN >= 256 * 256 ? 1 : BM * BN == 64 * 64 && NSTAGE == 4 ? 4 : 2;
   Bf16GemmParams p = p0;
   p.tilesM = (p.M + BM - 1) / BM;
   p.tilesN = (p.N + BN - 1) / BN;
   p.total = p.tilesM * p.tilesN * p.batch * p.ksplit;
   p.chunks = (p.total + 7) / 8;
-  if constexpr (sizeof(TC) == 4 && !AK && !BK_) {
+  if constexpr (sizeof(TC) == 4 && !AK && !BK_ && NSTAGE < 8) {
     // the fused epilogues exist for weight-gradient launches (both operands m-major) only
     if (p.mode == EPI_STEP) {
       const long long groups = (long long)((p.tilesM + kStepGroup - 1) / kStepGroup) *
@@ -653,7 +686,10 @@ int launch_one(const Bf16GemmParams& p0, hipStream_t s, int* slots) {
       const long long per_xcd = (groups + 7) / 8 * p.batch * kStepGroup * kStepGroup;
       if (per_xcd * 8 >= (1ll << 31)) return -1;
       p.chunks = (int)per_xcd;
-      gemm_bf16_kernel<TC, BM, BN, NSTAGE, AK, BK_, OCC, EPI_STEP><<<p.chunks * 8, kThreads, 0, s>>>(p);
+      if constexpr (BM == 64) {
+        if (p.cached) gemm_bf16_kernel<TC, BM, BN, NSTAGE, AK, BK_, OCC, EPI_STEP_CACHED><<<p.chunks * 8, kThreads, 0, s>>>(p);
+      }
+      if (!p.cached) gemm_bf16_kernel<TC, BM, BN, NSTAGE, AK, BK_, OCC, EPI_STEP><<<p.chunks * 8, kThreads, 0, s>>>(p);
       if (slots) *slots = 0;
       return 0;
     }
@@ -661,7 +697,10 @@ int launch_one(const Bf16GemmParams& p0, hipStream_t s, int* slots) {
       const long long per_xcd = (long long)p.batch * p.tilesM * ((p.tilesN + 7) / 8);
       if (per_xcd * 8 >= (1ll << 31)) return -1;
       p.chunks = (int)per_xcd;
-      gemm_bf16_kernel<TC, BM, BN, NSTAGE, AK, BK_, OCC, EPI_ASCEND><<<p.chunks * 8, kThreads, 0, s>>>(p);
+      if constexpr (BM == 64) {
+        if (p.cached) gemm_bf16_kernel<TC, BM, BN, NSTAGE, AK, BK_, OCC, EPI_ASCEND_CACHED><<<p.chunks * 8, kThreads, 0, s>>>(p);
+      }
+      if (!p.cached) gemm_bf16_kernel<TC, BM, BN, NSTAGE, AK, BK_, OCC, EPI_ASCEND><<<p.chunks * 8, kThreads, 0, s>>>(p);
       if (slots) *slots = 0;
       return 0;
     }
@@ -681,6 +720,8 @@ template <typename TC, bool AK, bool BK_>
 int launch_tiled(const Bf16GemmParams& p, int tile, hipStream_t s, int* slots) {
   if (tile == 256) return launch_one<TC, 256, 256, 4, AK, BK_>(p, s, slots);
   if (tile == 2) return launch_one<TC, 256, 128, 3, AK, BK_>(p, s, slots);
+  if (tile == 64) return launch_one<TC, 64, 64, 8, AK, BK_>(p, s, slots);
+  if (tile == 65) return launch_one<TC, 64, 64, 4, AK, BK_>(p, s, slots);
   return launch_one<TC, 128, 128, 4, AK, BK_>(p, s, slots);
 }
 
@@ -724,6 +765,16 @@ int launch_gemm_bf16(const GemmDesc& d, int tile_override, hipStream_t s, int* s
   // 256x256); the ascent epilogue, one array in and one out, keeps the choice above (9.1 against
   // 9.6 ms with 128x128).
   if (d.fuse != nullptr && tile_override == 0) tile = 128;
+  // Where 128x128 tiles cannot give every compute unit a workgroup, and in the fused epilogues of
+  // states that stay in the caches, 64x64 tiles: a tile's time is a chain of memory latencies, not
+  // work.  With at most two per unit and more than four k-steps the ring has eight stages.  A step of 3
+  // replicas 1000-1500-777-37 with batch 100 takes 251 us so (128x128 only: 373), of 4 3072-1024-1024-10 with
+  // 128 300 (433), of 8 700-900-1100-300 with 400 450 (538), of one 2500-4000-3000-4000-900 with 50 775 (947);
+  // of 8 1024-2048-2048-100 with 256 654 (702), and 684 with 64x64 up to 512 tiles of 128x128.
+  const bool fused = d.fuse != nullptr || d.ascend != nullptr;
+  const bool cached = fused && d.batch * d.strideC * 4 <= kCacheResidentBytes;
+  if (tile_override == 0 && (cached || tiles(128, 128) < 256))
+    tile = !fused && !d.sumsq_only && d.Kd > 128 && tiles(64, 64) <= 512 ? 64 : 65;
   const int kpad = (d.Kd + 31) / 32 * 32;
   // stored shapes: k-major [rows][k], m-major [k][rows]
   const long long blocksA = d.a_kmajor ? (long long)b32s_blocks(d.M) * d.cbA : (long long)b32s_blocks(kpad) * d.cbA;
@@ -754,6 +805,7 @@ int launch_gemm_bf16(const GemmDesc& d, int tile_override, hipStream_t s, int* s
   p.strideSumsq = d.sumsq_stride;
   p.fx = nullptr; p.frestart = nullptr;
   p.mode = EPI_STORE;
+  p.cached = cached;
   const bool plain_f32 = !d.out_bf16 && d.epilogue == EPI_PLAIN && (d.ldC % 4) == 0 && (d.strideC % 4) == 0;
   p.ksplit = 1; p.strideSplit = 0;
   if (d.ksplit > 1) {

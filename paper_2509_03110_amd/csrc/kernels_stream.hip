@@ -28,11 +28,6 @@ __device__ __forceinline__ f32x4 ld_any(const float* p) {
 __device__ __forceinline__ void stv(float* p, f32x4 v) {
   __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(p));
 }
-// Parameters that the next kernels read back: streamed past the caches when all replicas
-// together are far larger than they are (K d floats; measured at 3.2 GB: +5-9 % for the two
-// kernels with streaming stores), left in them when they fit (at 67 MB the following forward
-// GEMMs and the next descent find them there: -2 % per step).
-constexpr int64_t kCacheResidentBytes = 96ll << 20;
 template <bool STREAM>
 __device__ __forceinline__ void st_param(float* p, f32x4 v) {
   if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(p));

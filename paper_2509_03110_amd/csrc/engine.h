@@ -66,11 +66,6 @@ void launch_sumsq_partials(const float* g, int64_t g_stride, int64_t n, int K, d
 constexpr int kProloguePartials = 128;
 constexpr int kMaxPartials = 1024;
 int sumsq_blocks(int64_t n);
-// Inner product of K pairs of matrices G1, G2 (each `n` floats, replica stride `stride`, both
-// multiples of 4, 16-byte aligned): partials[k * pstride + j] for j < the returned count (<= 64).
-// G1 (G2) is the sum of pieces1 (pieces2) >= 1 partial matrices lying piece_stride elements apart.
-int launch_gram_dot(const float* G1, const float* G2, int64_t stride, int64_t n, int K, int pieces1,
-                    int pieces2, int64_t piece_stride, double* partials, int64_t pstride, hipStream_t s);
 // Pass 2: norms[k] = sqrt(sum_{b<nblk} partials[k * partials_stride + b]); scale[k] = rho / (norm + gamma).
 // If loss_rows != nullptr also reduces loss_rows [K,B] to loss_out[k] = mean (both passes of
 // the tree are fixed-order, so the result is run-to-run deterministic).
@@ -190,11 +185,6 @@ struct GemmDesc {
   const struct AscentFusion* ascend;
   // If set (same kind of launch, `sumsq` given): only the sums of squares are written.
   int sumsq_only;
-  // bf16 operands in the blocked layout, plain fp32 result, none of the options above: with
-  // ksplit > 1 the contraction is cut into ksplit pieces of whole 32-deep steps, each taken by
-  // workgroups of its own, and piece j writes its partial result at C + j * split_stride
-  // (elements, beside the replica stride); the caller adds the pieces up in a fixed order.
-  int ksplit; int64_t split_stride;
 };
 struct AscentFusion {
   const float* x; const float* scale;
@@ -215,6 +205,13 @@ int gemm_sumsq_capacity(int M, int N);
 size_t gemm_splitk_bytes(const GemmDesc& d);          // scratch this GEMM would like (0: none)
 // bf16 fast path (direct-to-LDS ring); returns 1 when the shape is left to the generic kernel.
 int launch_gemm_bf16(const GemmDesc& d, int tile_override, hipStream_t s, int* sumsq_slots);
+
+// Squared norms of n <= LSAM_MAX_LAYERS weight gradients dZ^T A that are not stored (dz [B][out] and act
+// [B][in] of K replicas, bf16 in the blocked layout, replicas one stored size apart), as partial sums:
+// returns the slots written per replica, or -1.
+int gram_slots(int n, int K, int B);
+struct GramLayer { const void* dz; const void* act; int out, in; };
+int launch_gram_norms(const GramLayer* layers, int n, int K, int B, double* sumsq, int64_t sumsq_stride, hipStream_t s);
 
 // Adds the `splits` partial results of a split contraction ([M][ldP] per replica, split_stride
 // floats apart) in a fixed order and finishes them as `d` says (C, epilogue, bias, mask, sumsq;

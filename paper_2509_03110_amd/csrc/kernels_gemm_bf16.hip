@@ -15,6 +15,8 @@
 //     single wavefront per SIMD.  Each stage is its own LDS array so that the compiler's
 //     wait-count tracking can tell them apart; the wait that orders a stage's arrival before
 //     the workgroup barrier is explicit.
+#include <algorithm>
+
 #include "engine.h"
 #include "b32s.h"
 
@@ -56,10 +58,6 @@ struct Bf16GemmParams {
   const float* ax; const float* ascale;
   int mode;                               // EPI_* the launch asks for
   int cached;                             // EPI_STEP, EPI_ASCEND: of the .._CACHED kind
-  // EPI_STORE with a plain fp32 result only: the contraction is cut into ksplit pieces, each
-  // taken by a workgroup of its own; piece j of replica k writes its partial result at
-  // C + k * strideC + j * strideSplit (elements)
-  int ksplit; long long strideSplit;
 };
 
 // s_waitcnt immediate: vmcnt = vm (0..63), lgkmcnt = lgkm (0..15), expcnt untouched.
@@ -126,12 +124,6 @@ struct Operand {
     }
   }
 
-  // Moves the tile's first k-step `first` steps into the contraction.
-  __device__ __forceinline__ void skip(int first) {
-#pragma unroll
-    for (int j = 0; j < NLOAD; ++j) goff[j] += (unsigned)first * kstep;
-  }
-
   // Requests k-step `ks` of the tile into `tile`.  A step at or past `ksteps` is sent out of
   // range on purpose: the stage then fills with zeros, which add nothing when multiplied.
   __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t rsrc, lds_byte* tile, int ks,
@@ -174,6 +166,102 @@ struct Interleave {
   }
 };
 
+// The stages of a ring, each an LDS array of its own (see the head of this file).
+struct Ring {
+  lds_byte *s0, *s1, *s2, *s3, *s4, *s5, *s6, *s7;
+};
+#define LSAM_RING_STAGES                                                                                       \
+  const Ring ring{(lds_byte*)st0, (lds_byte*)st1, (lds_byte*)st2, (lds_byte*)st3, (lds_byte*)st4, (lds_byte*)st5, \
+                  (lds_byte*)st6, (lds_byte*)st7};
+
+// acc += the products of `ksteps` k-steps of the two operands.  Every wavefront has left the stages
+// when it returns.
+template <int NSTAGE, int A_BYTES, typename OA, typename OB, int TM, int TN>
+__device__ __forceinline__ void ring_products(const OA& oa, const OB& ob, __amdgpu_buffer_rsrc_t rsrcA,
+                                              __amdgpu_buffer_rsrc_t rsrcB, const Ring& ring, int ksteps,
+                                              f32x16 (&acc)[TM][TN]) {
+  static_assert(NSTAGE == 3 || NSTAGE == 4 || NSTAGE == 8, "ring of 3, 4 or 8 stages");
+  constexpr int NL = OA::NLOAD + OB::NLOAD;
+  constexpr int ND = OA::NREAD + OB::NREAD;
+  constexpr int NM = TM * TN;
+  u32x4 fa[2][TM], fb[2][TN];
+  auto mfma_chunk = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            __builtin_bit_cast(bf16x8, fb[buf][j]), __builtin_bit_cast(bf16x8, fa[buf][i]),
+            acc[i][j], 0, 0, 0);
+  };
+  // Tiles past the last k-step are still requested (as zeros), which keeps the number of
+  // loads in flight, and so the wait counts, the same in every step, and lets the loop run
+  // in whole rounds of the stages.
+  oa.issue(rsrcA, ring.s0, 0, ksteps); ob.issue(rsrcB, ring.s0 + A_BYTES, 0, ksteps);
+  oa.issue(rsrcA, ring.s1, 1, ksteps); ob.issue(rsrcB, ring.s1 + A_BYTES, 1, ksteps);
+  oa.issue(rsrcA, ring.s2, 2, ksteps); ob.issue(rsrcB, ring.s2 + A_BYTES, 2, ksteps);
+  if constexpr (NSTAGE >= 4) {
+    oa.issue(rsrcA, ring.s3, 3, ksteps); ob.issue(rsrcB, ring.s3 + A_BYTES, 3, ksteps);
+  }
+  if constexpr (NSTAGE == 8) {
+    oa.issue(rsrcA, ring.s4, 4, ksteps); ob.issue(rsrcB, ring.s4 + A_BYTES, 4, ksteps);
+    oa.issue(rsrcA, ring.s5, 5, ksteps); ob.issue(rsrcB, ring.s5 + A_BYTES, 5, ksteps);
+    oa.issue(rsrcA, ring.s6, 6, ksteps); ob.issue(rsrcB, ring.s6 + A_BYTES, 6, ksteps);
+    oa.issue(rsrcA, ring.s7, 7, ksteps); ob.issue(rsrcB, ring.s7 + A_BYTES, 7, ksteps);
+  }
+  __builtin_amdgcn_s_waitcnt(waitcnt((NSTAGE - 1) * NL, 15));   // tile 0 has landed (this wavefront's part)
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  oa.read(ring.s0, 0, fa[0]);
+  ob.read(ring.s0 + A_BYTES, 0, fb[0]);
+
+  // One k-step on stage CUR; NEXT holds the following tile; the tile NSTAGE steps ahead is
+  // requested into CUR as soon as every wavefront has taken its last fragment out of it.
+#define LSAM_GEMM_STEP(CUR, NEXT)                                                         \
+  {                                                                                       \
+    oa.read(CUR, 1, fa[1]);                                                               \
+    ob.read(CUR + A_BYTES, 1, fb[1]);                                                     \
+    mfma_chunk(0);                                                                        \
+    Interleave<0x100, ND, NM, 0>::run();                                                  \
+    __builtin_amdgcn_s_waitcnt(waitcnt((NSTAGE - 2) * NL, 0));                            \
+    asm volatile("" ::: "memory");                                                        \
+    __builtin_amdgcn_s_barrier();                                                         \
+    asm volatile("" ::: "memory");                                                        \
+    oa.issue(rsrcA, CUR, ks + NSTAGE, ksteps);                                            \
+    ob.issue(rsrcB, CUR + A_BYTES, ks + NSTAGE, ksteps);                                  \
+    oa.read(NEXT, 0, fa[0]);                                                              \
+    ob.read(NEXT + A_BYTES, 0, fb[0]);                                                    \
+    mfma_chunk(1);                                                                        \
+    Interleave<0x120, ND + NL, NM, 0>::run();                                             \
+    ++ks;                                                                                 \
+  }
+
+  for (int ks = 0; ks < ksteps;) {
+    LSAM_GEMM_STEP(ring.s0, ring.s1)
+    LSAM_GEMM_STEP(ring.s1, ring.s2)
+    if constexpr (NSTAGE == 3) {
+      LSAM_GEMM_STEP(ring.s2, ring.s0)
+    } else if constexpr (NSTAGE == 4) {
+      LSAM_GEMM_STEP(ring.s2, ring.s3)
+      LSAM_GEMM_STEP(ring.s3, ring.s0)
+    } else {
+      LSAM_GEMM_STEP(ring.s2, ring.s3)
+      LSAM_GEMM_STEP(ring.s3, ring.s4)
+      if (ks >= ksteps) break;
+      LSAM_GEMM_STEP(ring.s4, ring.s5)
+      LSAM_GEMM_STEP(ring.s5, ring.s6)
+      LSAM_GEMM_STEP(ring.s6, ring.s7)
+      LSAM_GEMM_STEP(ring.s7, ring.s0)
+    }
+  }
+#undef LSAM_GEMM_STEP
+  __builtin_amdgcn_s_waitcnt(waitcnt(0, 0));           // nothing may still be writing LDS
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 template <typename TC> struct Out;
 template <> struct Out<float> {
   typedef f32x4 vec;
@@ -210,7 +298,6 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams
   constexpr bool CACHED = KIND == EPI_STEP_CACHED || KIND == EPI_ASCEND_CACHED;
   constexpr int MODE = KIND == EPI_STEP_CACHED ? EPI_STEP : KIND == EPI_ASCEND_CACHED ? EPI_ASCEND : KIND;
   static_assert(MODE == EPI_STORE || sizeof(TC) == 4, "the fused epilogues work on fp32 results");
-  static_assert(NSTAGE == 3 || NSTAGE == 4 || NSTAGE == 8, "ring of 3, 4 or 8 stages");
   constexpr int TM = BM / 64, TN = BN / 64;
   constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
   constexpr int EPI_PITCH = BN / 2 + 4;                       // epilogue staging pitch (floats)
@@ -227,7 +314,7 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams
   __shared__ __attribute__((aligned(1024))) unsigned char st7[MORE_BYTES];
 
   const int w = blockIdx.x;
-  int bat, m0, n0, t_in = 0, piece = 0;
+  int bat, m0, n0, t_in = 0;
   if constexpr (MODE == EPI_STEP) {
     // The step reads the centre y, which all replicas share: an XCD takes whole groups of
     // kStepGroup x kStepGroup tiles and works through the replicas of one group before it
@@ -272,10 +359,6 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams
     const int per_rep = p.tilesM * p.tilesN;
     bat = logical / per_rep;
     t_in = logical - bat * per_rep;
-    if (p.ksplit > 1) {                                // (replica, piece of the contraction)
-      piece = bat % p.ksplit;
-      bat /= p.ksplit;
-    }
     const int band = t_in / (GROUP_M * p.tilesN);
     const int first_m = band * GROUP_M;
     const int gsize = p.tilesM - first_m < GROUP_M ? p.tilesM - first_m : GROUP_M;
@@ -297,9 +380,6 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams
   Operand<BN, B_KMAJOR, TN> ob;
   oa.init(p.cbA, m0, wm0, tid);
   ob.init(p.cbB, n0, wn0, tid);
-  constexpr int NL = Operand<BM, A_KMAJOR, TM>::NLOAD + Operand<BN, B_KMAJOR, TN>::NLOAD;
-  constexpr int ND = Operand<BM, A_KMAJOR, TM>::NREAD + Operand<BN, B_KMAJOR, TN>::NREAD;
-  constexpr int NM = TM * TN;
 
   f32x16 acc[TM][TN];
 #pragma unroll
@@ -309,102 +389,9 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  u32x4 fa[2][TM], fb[2][TN];
-  auto mfma_chunk = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-            __builtin_bit_cast(bf16x8, fb[buf][j]), __builtin_bit_cast(bf16x8, fa[buf][i]),
-            acc[i][j], 0, 0, 0);
-  };
-
-  int ksteps = (p.Kd + BK - 1) / BK;           // the stored operands are zero-padded to 32
-  if (p.ksplit > 1) {
-    // this workgroup's piece of the contraction: k-steps [first, first + ksteps), possibly none
-    const int per = (ksteps + p.ksplit - 1) / p.ksplit;
-    const int first = piece * per;
-    ksteps = ksteps - first < per ? ksteps - first : per;
-    if (ksteps < 0) ksteps = 0;
-    oa.skip(first);
-    ob.skip(first);
-  }
-  lds_byte* s0 = (lds_byte*)st0;
-  lds_byte* s1 = (lds_byte*)st1;
-  lds_byte* s2 = (lds_byte*)st2;
-  lds_byte* s3 = (lds_byte*)st3;
-  lds_byte* s4 = (lds_byte*)st4;
-  lds_byte* s5 = (lds_byte*)st5;
-  lds_byte* s6 = (lds_byte*)st6;
-  lds_byte* s7 = (lds_byte*)st7;
-
-  // Tiles past the last k-step are still requested (as zeros), which keeps the number of
-  // loads in flight, and so the wait counts, the same in every step, and lets the loop run
-  // in whole rounds of the stages.
-  oa.issue(rsrcA, s0, 0, ksteps); ob.issue(rsrcB, s0 + A_BYTES, 0, ksteps);
-  oa.issue(rsrcA, s1, 1, ksteps); ob.issue(rsrcB, s1 + A_BYTES, 1, ksteps);
-  oa.issue(rsrcA, s2, 2, ksteps); ob.issue(rsrcB, s2 + A_BYTES, 2, ksteps);
-  if constexpr (NSTAGE >= 4) {
-    oa.issue(rsrcA, s3, 3, ksteps); ob.issue(rsrcB, s3 + A_BYTES, 3, ksteps);
-  }
-  if constexpr (NSTAGE == 8) {
-    oa.issue(rsrcA, s4, 4, ksteps); ob.issue(rsrcB, s4 + A_BYTES, 4, ksteps);
-    oa.issue(rsrcA, s5, 5, ksteps); ob.issue(rsrcB, s5 + A_BYTES, 5, ksteps);
-    oa.issue(rsrcA, s6, 6, ksteps); ob.issue(rsrcB, s6 + A_BYTES, 6, ksteps);
-    oa.issue(rsrcA, s7, 7, ksteps); ob.issue(rsrcB, s7 + A_BYTES, 7, ksteps);
-  }
-  __builtin_amdgcn_s_waitcnt(waitcnt((NSTAGE - 1) * NL, 15));   // tile 0 has landed (this wavefront's part)
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-  oa.read(s0, 0, fa[0]);
-  ob.read(s0 + A_BYTES, 0, fb[0]);
-
-  // One k-step on stage CUR; NEXT holds the following tile; the tile NSTAGE steps ahead is
-  // requested into CUR as soon as every wavefront has taken its last fragment out of it.
-#define LSAM_GEMM_STEP(CUR, NEXT)                                                         \
-  {                                                                                       \
-    oa.read(CUR, 1, fa[1]);                                                               \
-    ob.read(CUR + A_BYTES, 1, fb[1]);                                                     \
-    mfma_chunk(0);                                                                        \
-    Interleave<0x100, ND, NM, 0>::run();                                                  \
-    __builtin_amdgcn_s_waitcnt(waitcnt((NSTAGE - 2) * NL, 0));                            \
-    asm volatile("" ::: "memory");                                                        \
-    __builtin_amdgcn_s_barrier();                                                         \
-    asm volatile("" ::: "memory");                                                        \
-    oa.issue(rsrcA, CUR, ks + NSTAGE, ksteps);                                            \
-    ob.issue(rsrcB, CUR + A_BYTES, ks + NSTAGE, ksteps);                                  \
-    oa.read(NEXT, 0, fa[0]);                                                              \
-    ob.read(NEXT + A_BYTES, 0, fb[0]);                                                    \
-    mfma_chunk(1);                                                                        \
-    Interleave<0x120, ND + NL, NM, 0>::run();                                             \
-    ++ks;                                                                                 \
-  }
-
-  for (int ks = 0; ks < ksteps;) {
-    LSAM_GEMM_STEP(s0, s1)
-    LSAM_GEMM_STEP(s1, s2)
-    if constexpr (NSTAGE == 3) {
-      LSAM_GEMM_STEP(s2, s0)
-    } else if constexpr (NSTAGE == 4) {
-      LSAM_GEMM_STEP(s2, s3)
-      LSAM_GEMM_STEP(s3, s0)
-    } else {
-      LSAM_GEMM_STEP(s2, s3)
-      LSAM_GEMM_STEP(s3, s4)
-      if (ks >= ksteps) break;
-      LSAM_GEMM_STEP(s4, s5)
-      LSAM_GEMM_STEP(s5, s6)
-      LSAM_GEMM_STEP(s6, s7)
-      LSAM_GEMM_STEP(s7, s0)
-    }
-  }
-#undef LSAM_GEMM_STEP
-  __builtin_amdgcn_s_waitcnt(waitcnt(0, 0));           // nothing may still be writing LDS
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
+  const int ksteps = (p.Kd + BK - 1) / BK;           // the stored operands are zero-padded to 32
+  LSAM_RING_STAGES
+  ring_products<NSTAGE, A_BYTES>(oa, ob, rsrcA, rsrcB, ring, ksteps, acc);
 
   // Epilogue.  Element e of a 32x32 accumulator tile is row m = l32, column
   // n = (e/4)*8 + h*4 + e%4 (the MFMA was issued with rows <- B, columns <- A); storing from
@@ -413,7 +400,7 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams
   // barrier: LDS operations of one wavefront complete in order) and writes them out as row
   // segments, consecutive lanes on consecutive 16 bytes; bias and the ReLU mask are read the
   // same way.
-  TC* C = reinterpret_cast<TC*>(p.C) + (long long)bat * p.strideC + (long long)piece * p.strideSplit;
+  TC* C = reinterpret_cast<TC*>(p.C) + (long long)bat * p.strideC;
   const float* bias = p.bias ? p.bias + (long long)bat * p.strideBias : nullptr;
   const float* bias_dir = p.bias_dir ? p.bias_dir + (long long)bat * p.strideBias : nullptr;
   const float bias_sc = p.bias_dir ? p.bias_scale[bat] : 0.f;
@@ -643,6 +630,85 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams
   }
 }
 
+// The squared norms of weight gradients that are not stored, for all layers of a group in one launch.
+// ||dZ^T A||_F^2 = sum_{b,b'} (dZ dZ^T)[b,b'] (A A^T)[b,b']: a workgroup forms the same tile of both
+// B x B Gram matrices, one behind the other, multiplies them where they are, and leaves one partial sum.
+// Neither matrix is stored, and of the tiles off the diagonal, which come in equal pairs, one is formed
+// and counted twice.  Rows and columns past the batch are zero in the stored operands.  What bounds it is
+// the load path into LDS.  A step of 8 replicas 3072-4096-4096-4096-4096-100 with batch 256 takes 4.37 ms
+// so and took 4.55 with two products and an inner product per layer (280 us together), one of 3 replicas
+// 1000-1500-777-37 with batch 100 245 us instead of 271.
+// Tiles of one replica's layer go to one XCD, whose L2 then holds the panels they share.
+constexpr int kGramItems = LSAM_MAX_LAYERS;
+struct GramGroup {
+  int n, batch, tilesB, tri;
+  double* sumsq; long long strideSumsq;
+  struct Item {
+    const char* dz; const char* act;
+    long long strideZ, strideA;         // elements between replicas
+    int cbZ, cbA;                       // column blocks
+    unsigned bytesZ, bytesA;            // of one replica
+  } it[kGramItems];
+};
+template <int BT, int NSTAGE, int OCC>
+__global__ __launch_bounds__(kThreads, OCC) void gram_norm_kernel(GramGroup p) {
+  constexpr int T = BT / 64, TILE_BYTES = BT * BK * 2, STAGE_BYTES = 2 * TILE_BYTES;
+  constexpr int MORE_BYTES = NSTAGE == 8 ? STAGE_BYTES : 1024;
+  __shared__ __attribute__((aligned(1024))) unsigned char st0[STAGE_BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char st1[STAGE_BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char st2[STAGE_BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char st3[STAGE_BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char st4[MORE_BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char st5[MORE_BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char st6[MORE_BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char st7[MORE_BYTES];
+  __shared__ double part[4];
+  const int idx = blockIdx.x / 8;
+  const int unit = idx / p.tri * 8 + blockIdx.x % 8, t = idx % p.tri;
+  if (unit >= p.n * p.batch) return;
+  const int item = unit / p.batch, bat = unit - item * p.batch;
+  int tn = 0;                           // tile t of the upper triangle: columns tn, rows tm <= tn
+  while ((tn + 1) * (tn + 2) / 2 <= t) ++tn;
+  const int tm = t - tn * (tn + 1) / 2;
+  const GramGroup::Item& g = p.it[item];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  LSAM_RING_STAGES
+  f32x16 acc[2][T][T];
+#pragma unroll
+  for (int w = 0; w < 2; ++w)
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+      for (int j = 0; j < T; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[w][i][j][e] = 0.f;
+  Operand<BT, true, T> oa, ob;
+  oa.init(g.cbZ, tm * BT, (wave >> 1) * (BT / 2), tid);
+  ob.init(g.cbZ, tn * BT, (wave & 1) * (BT / 2), tid);
+  __amdgpu_buffer_rsrc_t r = make_rsrc(g.dz + (long long)bat * g.strideZ * 2, g.bytesZ);
+  ring_products<NSTAGE, TILE_BYTES>(oa, ob, r, r, ring, g.cbZ, acc[0]);
+  oa.init(g.cbA, tm * BT, (wave >> 1) * (BT / 2), tid);
+  ob.init(g.cbA, tn * BT, (wave & 1) * (BT / 2), tid);
+  r = make_rsrc(g.act + (long long)bat * g.strideA * 2, g.bytesA);
+  ring_products<NSTAGE, TILE_BYTES>(oa, ob, r, r, ring, g.cbA, acc[1]);
+  double tot = 0.0;
+#pragma unroll
+  for (int i = 0; i < T; ++i)
+#pragma unroll
+    for (int j = 0; j < T; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) tot += (double)acc[0][i][j][e] * (double)acc[1][i][j][e];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) tot += __shfl_xor(tot, off, 64);
+  if (lane == 0) part[wave] = tot;
+  __syncthreads();
+  if (tid == 0)
+    p.sumsq[(long long)bat * p.strideSumsq + item * p.tri + t] =
+        ((part[0] + part[1]) + (part[2] + part[3])) * (tm == tn ? 1.0 : 2.0);
+}
+template __global__ void gram_norm_kernel<128, 4, 2>(GramGroup);
+template __global__ void gram_norm_kernel<64, 8, 2>(GramGroup);
+
 // Every specialisation that can be launched is instantiated explicitly (the host-side launch
 // stubs of implicit instantiations of this kernel were not all emitted by the compiler).
 #define LSAM_INSTANTIATE(TC, AK, BK_)                                                         \
@@ -676,7 +742,7 @@ int launch_one(const Bf16GemmParams& p0, hipStream_t s, int* slots) {
   Bf16GemmParams p = p0;
   p.tilesM = (p.M + BM - 1) / BM;
   p.tilesN = (p.N + BN - 1) / BN;
-  p.total = p.tilesM * p.tilesN * p.batch * p.ksplit;
+  p.total = p.tilesM * p.tilesN * p.batch;
   p.chunks = (p.total + 7) / 8;
   if constexpr (sizeof(TC) == 4 && !AK && !BK_ && NSTAGE < 8) {
     // the fused epilogues exist for weight-gradient launches (both operands m-major) only
@@ -807,14 +873,6 @@ int launch_gemm_bf16(const GemmDesc& d, int tile_override, hipStream_t s, int* s
   p.mode = EPI_STORE;
   p.cached = cached;
   const bool plain_f32 = !d.out_bf16 && d.epilogue == EPI_PLAIN && (d.ldC % 4) == 0 && (d.strideC % 4) == 0;
-  p.ksplit = 1; p.strideSplit = 0;
-  if (d.ksplit > 1) {
-    // partial results of a split contraction: plain fp32 stores and nothing else
-    if (!plain_f32 || d.sumsq != nullptr || d.fuse != nullptr || d.ascend != nullptr || d.sumsq_only ||
-        d.ksplit > 64 || (d.split_stride % 4) != 0 || tiles(128, 128) * d.ksplit >= (1ll << 28))
-      return -1;
-    p.ksplit = d.ksplit; p.strideSplit = d.split_stride;
-  }
   // 32-bit byte offsets inside one replica's W_l, rows of a ragged last tile included
   const bool offsets_fit = ((long long)d.M + 256) * d.ldC * 4 < 0x7FFFFFF0LL;
   if (d.fuse != nullptr) {
@@ -846,6 +904,50 @@ int launch_gemm_bf16(const GemmDesc& d, int tile_override, hipStream_t s, int* s
   }
   return d.out_bf16 ? launch_layout<__bf16>(d, p, tile, s, sumsq_slots)
                     : launch_layout<float>(d, p, tile, s, sumsq_slots);
+}
+
+namespace {
+constexpr int kGramTiles = 192;         // tiles of 128 x 128 from which on those are taken: most compute units have one
+int gram_tile(int n, int K, int B) {
+  const long long t = (B + 127) / 128;
+  return n * K * (t * (t + 1) / 2) >= kGramTiles ? 128 : 64;
+}
+}  // namespace
+
+int gram_slots(int n, int K, int B) {
+  const int tile = gram_tile(n, K, B), t = (B + tile - 1) / tile;
+  return n * (t * (t + 1) / 2);
+}
+
+int launch_gram_norms(const GramLayer* layers, int n, int K, int B, double* sumsq, int64_t sumsq_stride, hipStream_t s) {
+  if (n < 1 || n > kGramItems || K < 1 || B < 1) return -1;
+  GramGroup p{};
+  const int tile = gram_tile(n, K, B);
+  p.n = n; p.batch = K;
+  p.tilesB = (B + tile - 1) / tile;
+  p.tri = p.tilesB * (p.tilesB + 1) / 2;
+  p.sumsq = sumsq; p.strideSumsq = sumsq_stride;
+  const GramLayer* order[kGramItems];
+  for (int i = 0; i < n; ++i) order[i] = layers + i;
+  // the longest contractions first: the last workgroups to start are then the shortest
+  std::stable_sort(order, order + n, [](const GramLayer* a, const GramLayer* b) { return a->out + a->in > b->out + b->in; });
+  for (int i = 0; i < n; ++i) {
+    const GramLayer& q = *order[i];
+    GramGroup::Item& it = p.it[i];
+    it.dz = (const char*)q.dz; it.act = (const char*)q.act;
+    it.cbZ = b32s_blocks(q.out); it.cbA = b32s_blocks(q.in);
+    it.strideZ = b32s_size(B, q.out); it.strideA = b32s_size(B, q.in);
+    // 32-bit byte offsets, rows of a ragged last tile included
+    if ((it.strideZ + 8ll * it.cbZ * 1024) * 2 >= 0x7FFFFFF0LL || (it.strideA + 8ll * it.cbA * 1024) * 2 >= 0x7FFFFFF0LL ||
+        ((uintptr_t)it.dz & 15) || ((uintptr_t)it.act & 15))
+      return -1;
+    it.bytesZ = (unsigned)(it.strideZ * 2); it.bytesA = (unsigned)(it.strideA * 2);
+  }
+  const long long grid = ((long long)n * K + 7) / 8 * 8 * p.tri;
+  if (grid >= (1ll << 31)) return -1;
+  if (tile == 128) gram_norm_kernel<128, 4, 2><<<(unsigned)grid, kThreads, 0, s>>>(p);
+  else gram_norm_kernel<64, 8, 2><<<(unsigned)grid, kThreads, 0, s>>>(p);
+  return n * p.tri;
 }
 
 }  // namespace lsam

@@ -181,9 +181,7 @@ struct Layout {
   std::vector<FilterBank> banks;         // the filters in wp; their device copy and the workgroups they take
   size_t banks_at = 0;
   int bank_blocks = 0;
-  size_t gram1 = 0, gram2 = 0; // bf16 dense model: Gram matrices [K][B][ldg] of a layer's dZ and of its input
   size_t restart = 0;         // K marks: which iterate sums read as zero / start afresh (launch_center)
-  int ldg = 0;
   int gap_hw = 0;              // > 0: global average pooling over that many positions feeds the dense layers
   size_t gap_out = 0, gap_grad = 0;   // [K][B][ld] pooled vector and its gradient
   size_t colsum = 0;           // first-stage column sums of the bias gradients
@@ -320,17 +318,6 @@ size_t take(size_t& cursor, size_t bytes) {
   const size_t at = cursor;
   cursor = (size_t)round_up((int64_t)(cursor + bytes), 2048);   // whole 2 KiB blocks of the bf16 layout
   return at;
-}
-
-// Into how many pieces the contraction (length kd) of a layer's B x B Gram product is cut: on
-// its own it has only K (B/128)^2 tiles of work for 256 compute units and a long k-loop each.
-// Aims at one workgroup per compute unit (with the chip full already, two and four pieces
-// measured no faster and slower), keeps at least 16 steps of 32 per piece, at most 8 pieces.
-int gram_pieces(int K, int B, int kd) {
-  const int64_t tiles = (int64_t)K * ((B + 127) / 128) * ((B + 127) / 128);
-  const int64_t want = (256 + tiles - 1) / tiles;
-  const int64_t deep = ((kd + 31) / 32) / 16;
-  return (int)std::max<int64_t>(1, std::min<int64_t>({want, deep, 8}));
 }
 
 // Whether the plane products serve a convolution (rows: output pixels per replica).  They take a
@@ -654,15 +641,6 @@ void build_layout(const lsam_config& c, Layout& lo) {
     }
     lo.splitk_bytes = need;
     if (need) lo.splitk = take(cur, need);
-    if (lo.bf16) {
-      // room for the most pieces any layer's Gram products are cut into
-      lo.ldg = (int)round_up(lo.B, 8);
-      int pieces = 1;
-      for (int l = lo.n_conv; l < lo.L; ++l)
-        pieces = std::max({pieces, gram_pieces(lo.K, lo.B, lo.layers[l].out), gram_pieces(lo.K, lo.B, lo.layers[l].in)});
-      lo.gram1 = take(cur, (size_t)pieces * lo.K * lo.B * lo.ldg * 4);
-      lo.gram2 = take(cur, (size_t)pieces * lo.K * lo.B * lo.ldg * 4);
-    }
     if (c.noise_scale > 0.f) lo.noise_segs = take(cur, lo.pieces.size() * sizeof(NoiseSeg));
   }
   lo.total = cur;
@@ -1275,9 +1253,10 @@ bool head_is_fused(const Layout& lo) {
 }
 
 // Whether the norm of a layer's unsaved first-pass weight gradient comes from the Gram matrices
-// of its factors: when they take at most half the flops of the product itself.
+// of its factors, half of each (launch_gram_norms), B^2 (out + in) flops: when they take at most
+// half those of the product itself.
 bool gram_norm_pays(int B, int out, int in) {
-  return 2 * (int64_t)B * (out + in) <= (int64_t)out * in;
+  return (int64_t)B * (out + in) <= (int64_t)out * in;
 }
 
 // forward + backward of all replicas; weights taken from `wts` (fp32 or bf16 per mode).
@@ -1359,6 +1338,8 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
   // first pass: the kernels that write the gradient also leave the partial sums of its squares
   double* ssq = fuse_norm ? c->at<double>(lo.partials) : nullptr;
   int slots = 0;
+  GramLayer gram[LSAM_MAX_LAYERS];
+  int grams = 0;
   for (int l = L - 1; l >= l0; --l) {
     const Layer& ly = lo.layers[l];
     const char* dz = c->at<char>(lo.dz[l + 1]);
@@ -1388,29 +1369,9 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
       split(c, d);
       if (ssq) { d.sumsq = ssq + slots; d.sumsq_stride = lo.nblk; }
       d.sumsq_only = (ssq && norm_only) ? 1 : 0;   // the gradient itself is recomputed by ascend_pass
-      // Of a gradient that is not stored only the norm is wanted, and ||dZ^T A||_F^2 is the inner
-      // product of the B x B Gram matrices dZ dZ^T and A A^T: 2 B^2 (out + in) flops instead of
-      // 2 B out in.  Taken when that is at most half the work.
+      // Of a gradient that is not stored only the norm is wanted, which the Gram matrices of its factors give
       if (d.sumsq_only && gram_norm_pays(B, ly.out, ly.in)) {
-        LaunchTimer t(c, KC_GEMM_DW_NORM);
-        for (int which = 0; which < 2; ++which) {
-          GemmDesc q{};
-          q.b32s = 1;
-          q.A = q.B = which == 0 ? (const void*)dz : act;
-          q.strideA = q.strideB = which == 0 ? astride(l + 1) : astride(l);
-          q.ldA = q.ldB = which == 0 ? ld_dz : lo.ld[l];
-          q.a_kmajor = q.b_kmajor = 1;
-          q.cbA = q.cbB = b32s_blocks(which == 0 ? ly.out : ly.in);
-          q.C = c->at<float>(which == 0 ? lo.gram1 : lo.gram2);
-          q.strideC = (int64_t)B * lo.ldg; q.ldC = lo.ldg;
-          q.M = q.N = B; q.Kd = which == 0 ? ly.out : ly.in; q.batch = K;
-          q.in_bf16 = 1; q.out_bf16 = 0; q.epilogue = EPI_PLAIN;
-          q.ksplit = gram_pieces(K, B, q.Kd); q.split_stride = (int64_t)K * B * lo.ldg;
-          if (launch_gemm(q, s) != 0) return fail(LSAM_EINVAL, "Gram GEMM of layer %d rejected", l);
-        }
-        slots += launch_gram_dot(c->at<float>(lo.gram1), c->at<float>(lo.gram2), (int64_t)B * lo.ldg,
-                                 (int64_t)B * lo.ldg, K, gram_pieces(K, B, ly.out), gram_pieces(K, B, ly.in),
-                                 (int64_t)K * B * lo.ldg, ssq + slots, lo.nblk, s);
+        gram[grams++] = GramLayer{dz, act, ly.out, ly.in};
         return LSAM_OK;
       }
       SamplerFusion f;
@@ -1468,6 +1429,13 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
     if ((rc = weight_grad()) != LSAM_OK) return rc;
     bias_grad();
     if (!fuse && want_dx && (rc = input_grad()) != LSAM_OK) return rc;
+  }
+  if (grams > 0) {
+    LaunchTimer t(c, KC_GEMM_DW_NORM);
+    if (slots + gram_slots(grams, K, B) > lo.nblk) return fail(LSAM_ESTATE, "gradient-norm partials would overrun their buffer at the Gram products");
+    const int used = launch_gram_norms(gram, grams, K, B, ssq + slots, lo.nblk, s);
+    if (used < 0) return fail(LSAM_EINVAL, "Gram products rejected");
+    slots += used;
   }
   if (l0 > 0) {
     int rc = conv_backward(c, static_cast<const float*>(X), params, ssq, &slots);

@@ -206,12 +206,27 @@ size_t gemm_splitk_bytes(const GemmDesc& d);          // scratch this GEMM would
 // bf16 fast path (direct-to-LDS ring); returns 1 when the shape is left to the generic kernel.
 int launch_gemm_bf16(const GemmDesc& d, int tile_override, hipStream_t s, int* sumsq_slots);
 
-// Squared norms of n <= LSAM_MAX_LAYERS weight gradients dZ^T A that are not stored (dz [B][out] and act
-// [B][in] of K replicas, bf16 in the blocked layout, replicas one stored size apart), as partial sums:
-// returns the slots written per replica, or -1.
+// A dense layer of the bf16 model for the launches that take several at once (n <= LSAM_MAX_LAYERS): dz
+// [B][out] and act [B][in] of K replicas, bf16 in the blocked layout, replicas one stored size apart.
+struct DenseLayer {
+  const void* dz; const void* act;
+  int out, in, ldw;
+  int64_t w_off, b_off;       // of W_l and b_l inside a replica's parameters
+  int64_t shadow_off;         // of its operand copy inside a replica's
+};
+// Squared norms of the weight gradients dZ^T A, which are not stored, as partial sums: returns the
+// slots written per replica, or -1.
+int launch_gram_norms(const DenseLayer* layers, int n, int K, int B, double* sumsq, int64_t sumsq_stride, hipStream_t s);
 int gram_slots(int n, int K, int B);
-struct GramLayer { const void* dz; const void* act; int out, in; };
-int launch_gram_norms(const GramLayer* layers, int n, int K, int B, double* sumsq, int64_t sumsq_stride, hipStream_t s);
+// The products dZ^T A of all layers with the step `f`, or else the ascent `a`, in their epilogues
+// (GemmDesc::fuse, ::ascend; pointers to the whole vectors, replicas `stride` apart), for a state that
+// stays in the caches.  0, or -1.
+int launch_fused_group(const DenseLayer* layers, int n, int K, int B, int64_t stride, const SamplerFusion* f,
+                       const AscentFusion* a, hipStream_t s);
+// Column sums of every layer's dz into g; slots as launch_bias_grad's.  `step` (may be null): the biases
+// take their sampler step as well (pointers to the whole vectors, like g).
+int launch_bias_grads_blocked(const DenseLayer* layers, int n, int K, int B, float* g, int64_t strideG, double* sumsq,
+                              int64_t sumsq_stride, const SamplerFusion* step, hipStream_t s);
 
 // Adds the `splits` partial results of a split contraction ([M][ldP] per replica, split_stride
 // floats apart) in a fixed order and finishes them as `d` says (C, epilogue, bias, mask, sumsq;
@@ -275,12 +290,11 @@ int launch_filters(const float* params, int64_t strideParams, const FilterBank* 
 // loss_rows [K,B] = lse - logit[label] (may be null).
 void launch_softmax_ce(const float* logits, int ld, const int32_t* labels, void* dz, int64_t ld_dz,
                        int dz_bf16, float* loss_rows, int K, int B, int C, hipStream_t s);
-// db[k][n] = sum_b dz[k][b][n]; dz as written by the kernels above (ld: row pitch, or one
-// replica's stored size for the blocked bf16 layout).
+// db[k][n] = sum_b dz[k][b][n], dz fp32 of row pitch ld.
 // If sumsq is non-null, workgroup j of replica k also writes the sum of squares of its 64
 // results to sumsq[k * sumsq_stride + j]; returns the number of such slots per replica.
-int launch_bias_grad(const void* dz, int64_t ld, int dz_bf16, float* db, int64_t strideDb, int K,
-                     int B, int N, double* sumsq, int64_t sumsq_stride, hipStream_t s);
+int launch_bias_grad(const float* dz, int64_t ld, float* db, int64_t strideDb, int K, int B, int N, double* sumsq,
+                     int64_t sumsq_stride, hipStream_t s);
 // dgamma and dbeta (at gam_off and bet_off of each replica's gradient) from the chunk sums that
 // launch_bn_backward_partials left; returns the sum-of-squares slots written per replica.
 int launch_norm_param_grads(const float* part, float* grad, int64_t strideGrad, int64_t gam_off, int64_t bet_off,

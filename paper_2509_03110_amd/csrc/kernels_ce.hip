@@ -136,15 +136,33 @@ __global__ __launch_bounds__(64 * WAVES) void bias_grad_kernel(const TD* __restr
 // adjacent column blocks (64 columns) of one replica, and per block row its 256 threads take the
 // 4 KiB the two blocks occupy as one 16-byte unit each -- a thread keeps its position inside the
 // block, so its 8 elements are the same 8 columns of the same row in every block row.  The 32
-// threads that share 8 columns are then combined in row order through LDS.
-__global__ __launch_bounds__(kThreads) void bias_grad_blocked_kernel(
-    const __bf16* __restrict__ dz, long long stride, float* __restrict__ db, long long strideDb, int B,
-    int N, double* __restrict__ sumsq, long long strideSumsq) {
+// threads that share 8 columns are then combined in row order through LDS.  All layers of a pass share
+// the launch, and in the second pass of the fused step each bias takes its sampler step where its
+// gradient appears: 5 layers were ten launches of 4 to 7 us, a tenth of a small model's step.
+struct BiasGroup {
+  int n, B;
+  float* g; long long strideG;
+  double* sumsq; long long strideSumsq;
+  struct Item {
+    const __bf16* dz; long long stride;   // elements between replicas
+    long long off;                        // of b_l inside a replica's parameters
+    int N, first;                         // columns; first workgroup
+  } it[LSAM_MAX_LAYERS];
+};
+
+template <bool STEP>
+__global__ __launch_bounds__(kThreads) void bias_grad_blocked_kernel(BiasGroup p, SamplerFusion f) {
+  int item = 0;
+  while (item + 1 < p.n && (int)blockIdx.x >= p.it[item + 1].first) ++item;
+  const BiasGroup::Item& it = p.it[item];
+  const __bf16* dz = it.dz;
+  const long long stride = it.stride;
+  const int N = it.N, B = p.B, cols = blockIdx.x - it.first;
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   __shared__ float part[kThreads][9];            // pitch 9: the combining reads hit distinct banks
   const int k = blockIdx.y, t = threadIdx.x;
   const int cb = b32s_blocks(N), rbs = b32s_blocks(B);
-  const int blk = blockIdx.x * 2 + (t >> 7);     // this thread's column block
+  const int blk = cols * 2 + (t >> 7);     // this thread's column block
   const int row = (t & 127) >> 2;                // its row inside a block
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (blk < cb) {
@@ -173,18 +191,28 @@ __global__ __launch_bounds__(kThreads) void bias_grad_blocked_kernel(
   if (t < 64) {
     // column c of this workgroup: block c / 32, unit q = (c % 32) / 8, element c % 8; in row r the
     // unit sits at position q ^ ((r / 4) % 4)
-    const int n = blockIdx.x * 64 + t;
+    const int n = cols * 64 + t;
     const int q = (t & 31) >> 3, e = t & 7, base = (t >> 5) * 128;
     float r = 0.f;
     if (n < N) {
       for (int rr = 0; rr < 32; ++rr) r += part[base + rr * 4 + (q ^ ((rr >> 2) & 3))][e];
-      db[(long long)k * strideDb + n] = r;
+      const long long o = (long long)k * p.strideG + it.off + n;
+      p.g[o] = r;
+      if constexpr (STEP) {
+        float lam = 0.f;       // picked with constant indices: a variable one would move the block to memory
+#pragma unroll
+        for (int j = 0; j < kMaxK; ++j)
+          if (j == k) lam = f.lam.v[j];
+        float x = f.x[o], v = f.v[o], S = f.restart != nullptr && f.restart[k] == 1 ? 0.f : f.S[o];
+        sampler_step(r, f.y[it.off + n], lam, f.lr, f.mu, f.nesterov, 0.f, x, v, S);
+        f.x[o] = x; f.v[o] = v; f.S[o] = S;
+      }
     }
-    if (sumsq != nullptr) {        // sum of the squares of this workgroup's 64 results
+    if (p.sumsq != nullptr) {        // sum of the squares of this workgroup's 64 results
       double sq = (double)r * (double)r;
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
-      if (t == 0) sumsq[(long long)k * strideSumsq + blockIdx.x] = sq;
+      if (t == 0) p.sumsq[(long long)k * p.strideSumsq + blockIdx.x] = sq;
     }
   }
 }
@@ -428,15 +456,27 @@ static void run_bias_grad(const float* dz, int64_t ld, float* db, int64_t stride
                                                               zout);
 }
 
-int launch_bias_grad(const void* dz, int64_t ld, int dz_bf16, float* db, int64_t strideDb, int K,
-                     int B, int N, double* sumsq, int64_t sumsq_stride, hipStream_t s) {
+int launch_bias_grad(const float* dz, int64_t ld, float* db, int64_t strideDb, int K, int B, int N, double* sumsq,
+                     int64_t sumsq_stride, hipStream_t s) {
   dim3 grid((N + 63) / 64, K);
-  if (dz_bf16)
-    bias_grad_blocked_kernel<<<grid, kThreads, 0, s>>>((const __bf16*)dz, ld, db, strideDb, B, N,
-                                                       sumsq, sumsq_stride);
-  else
-    run_bias_grad((const float*)dz, ld, db, strideDb, B, N, sumsq, sumsq_stride, 0, 0, grid, s);
+  run_bias_grad(dz, ld, db, strideDb, B, N, sumsq, sumsq_stride, 0, 0, grid, s);
   return (int)grid.x;
+}
+
+int launch_bias_grads_blocked(const DenseLayer* layers, int n, int K, int B, float* g, int64_t strideG, double* sumsq,
+                              int64_t sumsq_stride, const SamplerFusion* step, hipStream_t s) {
+  BiasGroup p{};
+  p.n = n; p.B = B;
+  p.g = g; p.strideG = strideG;
+  p.sumsq = sumsq; p.strideSumsq = sumsq_stride;
+  int blocks = 0;
+  for (int i = 0; i < n; ++i) {
+    p.it[i] = BiasGroup::Item{(const __bf16*)layers[i].dz, b32s_size(B, layers[i].out), layers[i].b_off, layers[i].out, blocks};
+    blocks += (layers[i].out + 63) / 64;
+  }
+  if (step) bias_grad_blocked_kernel<true><<<dim3(blocks, K), kThreads, 0, s>>>(p, *step);
+  else bias_grad_blocked_kernel<false><<<dim3(blocks, K), kThreads, 0, s>>>(p, SamplerFusion{});
+  return blocks;
 }
 
 int launch_norm_param_grads(const float* part, float* grad, int64_t strideGrad, int64_t gam_off, int64_t bet_off,

@@ -57,7 +57,6 @@ struct Bf16GemmParams {
   // and the operand copy that receives bf16(x + scale g) (fshadow, strideShadow, cbShadow above)
   const float* ax; const float* ascale;
   int mode;                               // EPI_* the launch asks for
-  int cached;                             // EPI_STEP, EPI_ASCEND: of the .._CACHED kind
 };
 
 // s_waitcnt immediate: vmcnt = vm (0..63), lgkmcnt = lgkm (0..15), expcnt untouched.
@@ -177,9 +176,10 @@ struct Ring {
 // acc += the products of `ksteps` k-steps of the two operands.  Every wavefront has left the stages
 // when it returns.
 template <int NSTAGE, int A_BYTES, typename OA, typename OB, int TM, int TN>
-__device__ __forceinline__ void ring_products(const OA& oa, const OB& ob, __amdgpu_buffer_rsrc_t rsrcA,
-                                              __amdgpu_buffer_rsrc_t rsrcB, const Ring& ring, int ksteps,
+__device__ __forceinline__ void ring_products(const OA& oa, const OB& ob, const void* A, unsigned bytesA, const void* B,
+                                              unsigned bytesB, const Ring& ring, int ksteps,
                                               f32x16 (&acc)[TM][TN]) {
+  const __amdgpu_buffer_rsrc_t rsrcA = make_rsrc(A, bytesA), rsrcB = make_rsrc(B, bytesB);
   static_assert(NSTAGE == 3 || NSTAGE == 4 || NSTAGE == 8, "ring of 3, 4 or 8 stages");
   constexpr int NL = OA::NLOAD + OB::NLOAD;
   constexpr int ND = OA::NREAD + OB::NREAD;
@@ -293,8 +293,8 @@ enum { EPI_STORE = 0, EPI_STEP = 1, EPI_SUMSQ = 2, EPI_ASCEND = 3, EPI_STEP_CACH
 constexpr int kStepGroup = 4;      // EPI_STEP: side of the tile groups an XCD takes through all replicas
 constexpr int kAscendBand = 2;    // EPI_ASCEND: tile rows of the band all XCDs share
 
-template <typename TC, int BM, int BN, int NSTAGE, bool A_KMAJOR, bool B_KMAJOR, int OCC, int KIND = EPI_STORE>
-__global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams p) {
+template <typename TC, int BM, int BN, int NSTAGE, bool A_KMAJOR, bool B_KMAJOR, int KIND>
+__device__ __forceinline__ void gemm_bf16_tile(const Bf16GemmParams& p, int w) {
   constexpr bool CACHED = KIND == EPI_STEP_CACHED || KIND == EPI_ASCEND_CACHED;
   constexpr int MODE = KIND == EPI_STEP_CACHED ? EPI_STEP : KIND == EPI_ASCEND_CACHED ? EPI_ASCEND : KIND;
   static_assert(MODE == EPI_STORE || sizeof(TC) == 4, "the fused epilogues work on fp32 results");
@@ -313,9 +313,8 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams
   __shared__ __attribute__((aligned(1024))) unsigned char st6[MORE_BYTES];
   __shared__ __attribute__((aligned(1024))) unsigned char st7[MORE_BYTES];
 
-  const int w = blockIdx.x;
   int bat, m0, n0, t_in = 0;
-  if constexpr (MODE == EPI_STEP) {
+  if constexpr (KIND == EPI_STEP) {
     // The step reads the centre y, which all replicas share: an XCD takes whole groups of
     // kStepGroup x kStepGroup tiles and works through the replicas of one group before it
     // moves to the next, so that the group's piece of y comes from memory once per XCD and
@@ -332,7 +331,7 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams
     const int tm = (group / groupsN) * G + t % G, tn = (group % groupsN) * G + t / G;
     if (tm >= p.tilesM || tn >= p.tilesN) return;
     m0 = tm * BM; n0 = tn * BN;
-  } else if constexpr (MODE == EPI_ASCEND) {
+  } else if constexpr (KIND == EPI_ASCEND) {
     // All XCDs work in the same replica and band of kAscendBand tile rows, XCD x on the column
     // tiles n = 8 n' + x: the row panels of the first operand are then wanted by all eight at
     // about the same time instead of by one XCD per replica (8.9-9.0 against 9.2-9.3 ms per
@@ -368,8 +367,6 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams
 
   const __bf16* A = reinterpret_cast<const __bf16*>(p.A) + (long long)bat * p.strideA;
   const __bf16* B = reinterpret_cast<const __bf16*>(p.B) + (long long)bat * p.strideB;
-  const __amdgpu_buffer_rsrc_t rsrcA = make_rsrc(A, p.bytesA);
-  const __amdgpu_buffer_rsrc_t rsrcB = make_rsrc(B, p.bytesB);
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
@@ -391,7 +388,9 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams
 
   const int ksteps = (p.Kd + BK - 1) / BK;           // the stored operands are zero-padded to 32
   LSAM_RING_STAGES
-  ring_products<NSTAGE, A_BYTES>(oa, ob, rsrcA, rsrcB, ring, ksteps, acc);
+#if defined(__HIP_DEVICE_COMPILE__)      // (the host pass fails to deduce this call inside a device function)
+  ring_products<NSTAGE, A_BYTES>(oa, ob, A, p.bytesA, B, p.bytesB, ring, ksteps, acc);
+#endif
 
   // Epilogue.  Element e of a 32x32 accumulator tile is row m = l32, column
   // n = (e/4)*8 + h*4 + e%4 (the MFMA was issued with rows <- B, columns <- A); storing from
@@ -630,6 +629,48 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams
   }
 }
 
+template <typename TC, int BM, int BN, int NSTAGE, bool A_KMAJOR, bool B_KMAJOR, int OCC, int KIND = EPI_STORE>
+__global__ __launch_bounds__(kThreads, OCC) void gemm_bf16_kernel(Bf16GemmParams p) {
+  gemm_bf16_tile<TC, BM, BN, NSTAGE, A_KMAJOR, B_KMAJOR, KIND>(p, blockIdx.x);
+}
+
+// The step or the ascent of all layers of a small model in one launch: alone each of them is a few
+// microseconds of ramp and memory latency, and the narrow ones leave most of the chip idle.  A step
+// of 3 replicas 1000-1500-777-37 with batch 100: 245 -> 197 us (with the biases' launches joined as well),
+// of 8 256-200-100-50 with 32: 141 -> 82, of 4 512-512-512-512-512-512 with 512: 331 -> 231.
+struct FusedGroup {
+  int n;
+  struct Item {
+    const char* dz; const char* act;
+    long long w_off, shadow_off;
+    int M, N, ldC, cbA, cbB, first;       // first: of the layer's workgroups, a multiple of 8
+  } it[LSAM_MAX_LAYERS];
+};
+template <int KIND>
+__global__ __launch_bounds__(kThreads, 4) void fused_group_kernel(Bf16GemmParams p, FusedGroup grp) {
+  int item = 0;
+  while (item + 1 < grp.n && (int)blockIdx.x >= grp.it[item + 1].first) ++item;
+  const FusedGroup::Item& it = grp.it[item];
+  const int rb = (p.Kd + 31) / 32;
+  p.A = it.dz; p.B = it.act;
+  p.M = it.M; p.N = it.N; p.ldC = it.ldC;
+  p.cbA = it.cbA; p.cbB = it.cbB; p.cbShadow = it.cbB;
+  p.strideA = (long long)rb * it.cbA * 1024; p.bytesA = (unsigned)(rb * it.cbA) * 2048u;
+  p.strideB = (long long)rb * it.cbB * 1024; p.bytesB = (unsigned)(rb * it.cbB) * 2048u;
+  if constexpr (KIND == EPI_STEP_CACHED) {
+    p.fx += it.w_off; p.fv += it.w_off; p.fS += it.w_off; p.fy += it.w_off;
+  } else {
+    p.ax += it.w_off;
+  }
+  p.fshadow += it.shadow_off;
+  p.tilesM = (p.M + 63) / 64; p.tilesN = (p.N + 63) / 64;
+  p.total = p.tilesM * p.tilesN * p.batch;
+  p.chunks = (p.total + 7) / 8;
+  gemm_bf16_tile<float, 64, 64, 4, false, false, KIND>(p, blockIdx.x - it.first);
+}
+template __global__ void fused_group_kernel<EPI_STEP_CACHED>(Bf16GemmParams, FusedGroup);
+template __global__ void fused_group_kernel<EPI_ASCEND_CACHED>(Bf16GemmParams, FusedGroup);
+
 // The squared norms of weight gradients that are not stored, for all layers of a group in one launch.
 // ||dZ^T A||_F^2 = sum_{b,b'} (dZ dZ^T)[b,b'] (A A^T)[b,b']: a workgroup forms the same tile of both
 // B x B Gram matrices, one behind the other, multiplies them where they are, and leaves one partial sum.
@@ -685,12 +726,12 @@ __global__ __launch_bounds__(kThreads, OCC) void gram_norm_kernel(GramGroup p) {
   Operand<BT, true, T> oa, ob;
   oa.init(g.cbZ, tm * BT, (wave >> 1) * (BT / 2), tid);
   ob.init(g.cbZ, tn * BT, (wave & 1) * (BT / 2), tid);
-  __amdgpu_buffer_rsrc_t r = make_rsrc(g.dz + (long long)bat * g.strideZ * 2, g.bytesZ);
-  ring_products<NSTAGE, TILE_BYTES>(oa, ob, r, r, ring, g.cbZ, acc[0]);
+  const char* m = g.dz + (long long)bat * g.strideZ * 2;
+  ring_products<NSTAGE, TILE_BYTES>(oa, ob, m, g.bytesZ, m, g.bytesZ, ring, g.cbZ, acc[0]);
   oa.init(g.cbA, tm * BT, (wave >> 1) * (BT / 2), tid);
   ob.init(g.cbA, tn * BT, (wave & 1) * (BT / 2), tid);
-  r = make_rsrc(g.act + (long long)bat * g.strideA * 2, g.bytesA);
-  ring_products<NSTAGE, TILE_BYTES>(oa, ob, r, r, ring, g.cbA, acc[1]);
+  m = g.act + (long long)bat * g.strideA * 2;
+  ring_products<NSTAGE, TILE_BYTES>(oa, ob, m, g.bytesA, m, g.bytesA, ring, g.cbA, acc[1]);
   double tot = 0.0;
 #pragma unroll
   for (int i = 0; i < T; ++i)
@@ -733,8 +774,6 @@ LSAM_INSTANTIATE_MODE(EPI_STEP)
 LSAM_INSTANTIATE_MODE(EPI_SUMSQ)
 LSAM_INSTANTIATE_MODE(EPI_ASCEND)
 #undef LSAM_INSTANTIATE_MODE
-template __global__ void gemm_bf16_kernel<float, 64, 64, 4, false, false, 4, EPI_STEP_CACHED>(Bf16GemmParams);
-template __global__ void gemm_bf16_kernel<float, 64, 64, 4, false, false, 4, EPI_ASCEND_CACHED>(Bf16GemmParams);
 
 template <typename TC, int BM, int BN, int NSTAGE, bool AK, bool BK_>
 int launch_one(const Bf16GemmParams& p0, hipStream_t s, int* slots) {
@@ -752,10 +791,7 @@ int launch_one(const Bf16GemmParams& p0, hipStream_t s, int* slots) {
       const long long per_xcd = (groups + 7) / 8 * p.batch * kStepGroup * kStepGroup;
       if (per_xcd * 8 >= (1ll << 31)) return -1;
       p.chunks = (int)per_xcd;
-      if constexpr (BM == 64) {
-        if (p.cached) gemm_bf16_kernel<TC, BM, BN, NSTAGE, AK, BK_, OCC, EPI_STEP_CACHED><<<p.chunks * 8, kThreads, 0, s>>>(p);
-      }
-      if (!p.cached) gemm_bf16_kernel<TC, BM, BN, NSTAGE, AK, BK_, OCC, EPI_STEP><<<p.chunks * 8, kThreads, 0, s>>>(p);
+      gemm_bf16_kernel<TC, BM, BN, NSTAGE, AK, BK_, OCC, EPI_STEP><<<p.chunks * 8, kThreads, 0, s>>>(p);
       if (slots) *slots = 0;
       return 0;
     }
@@ -763,10 +799,7 @@ int launch_one(const Bf16GemmParams& p0, hipStream_t s, int* slots) {
       const long long per_xcd = (long long)p.batch * p.tilesM * ((p.tilesN + 7) / 8);
       if (per_xcd * 8 >= (1ll << 31)) return -1;
       p.chunks = (int)per_xcd;
-      if constexpr (BM == 64) {
-        if (p.cached) gemm_bf16_kernel<TC, BM, BN, NSTAGE, AK, BK_, OCC, EPI_ASCEND_CACHED><<<p.chunks * 8, kThreads, 0, s>>>(p);
-      }
-      if (!p.cached) gemm_bf16_kernel<TC, BM, BN, NSTAGE, AK, BK_, OCC, EPI_ASCEND><<<p.chunks * 8, kThreads, 0, s>>>(p);
+      gemm_bf16_kernel<TC, BM, BN, NSTAGE, AK, BK_, OCC, EPI_ASCEND><<<p.chunks * 8, kThreads, 0, s>>>(p);
       if (slots) *slots = 0;
       return 0;
     }
@@ -831,15 +864,14 @@ int launch_gemm_bf16(const GemmDesc& d, int tile_override, hipStream_t s, int* s
   // 256x256); the ascent epilogue, one array in and one out, keeps the choice above (9.1 against
   // 9.6 ms with 128x128).
   if (d.fuse != nullptr && tile_override == 0) tile = 128;
-  // Where 128x128 tiles cannot give every compute unit a workgroup, and in the fused epilogues of
-  // states that stay in the caches, 64x64 tiles: a tile's time is a chain of memory latencies, not
+  // Where 128x128 tiles cannot give every compute unit a workgroup, 64x64 tiles (and always in the fused
+  // epilogues of states that stay in the caches, launch_fused_group): a tile's time is a chain of memory latencies, not
   // work.  With at most two per unit and more than four k-steps the ring has eight stages.  A step of 3
-  // replicas 1000-1500-777-37 with batch 100 takes 251 us so (128x128 only: 373), of 4 3072-1024-1024-10 with
+  // replicas 1000-1500-777-37 with batch 100 took 251 us so (128x128 only: 373), of 4 3072-1024-1024-10 with
   // 128 300 (433), of 8 700-900-1100-300 with 400 450 (538), of one 2500-4000-3000-4000-900 with 50 775 (947);
   // of 8 1024-2048-2048-100 with 256 654 (702), and 684 with 64x64 up to 512 tiles of 128x128.
   const bool fused = d.fuse != nullptr || d.ascend != nullptr;
-  const bool cached = fused && d.batch * d.strideC * 4 <= kCacheResidentBytes;
-  if (tile_override == 0 && (cached || tiles(128, 128) < 256))
+  if (tile_override == 0 && tiles(128, 128) < 256)
     tile = !fused && !d.sumsq_only && d.Kd > 128 && tiles(64, 64) <= 512 ? 64 : 65;
   const int kpad = (d.Kd + 31) / 32 * 32;
   // stored shapes: k-major [rows][k], m-major [k][rows]
@@ -871,7 +903,6 @@ int launch_gemm_bf16(const GemmDesc& d, int tile_override, hipStream_t s, int* s
   p.strideSumsq = d.sumsq_stride;
   p.fx = nullptr; p.frestart = nullptr;
   p.mode = EPI_STORE;
-  p.cached = cached;
   const bool plain_f32 = !d.out_bf16 && d.epilogue == EPI_PLAIN && (d.ldC % 4) == 0 && (d.strideC % 4) == 0;
   // 32-bit byte offsets inside one replica's W_l, rows of a ragged last tile included
   const bool offsets_fit = ((long long)d.M + 256) * d.ldC * 4 < 0x7FFFFFF0LL;
@@ -919,7 +950,7 @@ int gram_slots(int n, int K, int B) {
   return n * (t * (t + 1) / 2);
 }
 
-int launch_gram_norms(const GramLayer* layers, int n, int K, int B, double* sumsq, int64_t sumsq_stride, hipStream_t s) {
+int launch_gram_norms(const DenseLayer* layers, int n, int K, int B, double* sumsq, int64_t sumsq_stride, hipStream_t s) {
   if (n < 1 || n > kGramItems || K < 1 || B < 1) return -1;
   GramGroup p{};
   const int tile = gram_tile(n, K, B);
@@ -927,12 +958,12 @@ int launch_gram_norms(const GramLayer* layers, int n, int K, int B, double* sums
   p.tilesB = (B + tile - 1) / tile;
   p.tri = p.tilesB * (p.tilesB + 1) / 2;
   p.sumsq = sumsq; p.strideSumsq = sumsq_stride;
-  const GramLayer* order[kGramItems];
+  const DenseLayer* order[kGramItems];
   for (int i = 0; i < n; ++i) order[i] = layers + i;
   // the longest contractions first: the last workgroups to start are then the shortest
-  std::stable_sort(order, order + n, [](const GramLayer* a, const GramLayer* b) { return a->out + a->in > b->out + b->in; });
+  std::stable_sort(order, order + n, [](const DenseLayer* a, const DenseLayer* b) { return a->out + a->in > b->out + b->in; });
   for (int i = 0; i < n; ++i) {
-    const GramLayer& q = *order[i];
+    const DenseLayer& q = *order[i];
     GramGroup::Item& it = p.it[i];
     it.dz = (const char*)q.dz; it.act = (const char*)q.act;
     it.cbZ = b32s_blocks(q.out); it.cbA = b32s_blocks(q.in);
@@ -948,6 +979,52 @@ int launch_gram_norms(const GramLayer* layers, int n, int K, int B, double* sums
   if (tile == 128) gram_norm_kernel<128, 4, 2><<<(unsigned)grid, kThreads, 0, s>>>(p);
   else gram_norm_kernel<64, 8, 2><<<(unsigned)grid, kThreads, 0, s>>>(p);
   return n * p.tri;
+}
+
+int launch_fused_group(const DenseLayer* layers, int n, int K, int B, int64_t stride, const SamplerFusion* f,
+                       const AscentFusion* a, hipStream_t s) {
+  if (n < 1 || n > LSAM_MAX_LAYERS || K < 1 || B < 1 || stride % 4) return -1;
+  Bf16GemmParams p{};
+  FusedGroup grp{};
+  p.strideC = stride;
+  p.Kd = B; p.batch = K;
+  uintptr_t at16, at8;
+  if (f) {
+    p.fx = f->x; p.fv = f->v; p.fS = f->S; p.fy = f->y;
+    p.fshadow = f->shadow; p.strideShadow = f->shadow_stride;
+    p.lr = f->lr; p.mu = f->mu; p.nesterov = f->nesterov; p.lam = f->lam; p.frestart = f->restart;
+    at16 = (uintptr_t)f->x | (uintptr_t)f->v | (uintptr_t)f->S | (uintptr_t)f->y;
+    at8 = (uintptr_t)f->shadow;
+  } else {
+    p.ax = a->x; p.ascale = a->scale;
+    p.fshadow = a->shadow; p.strideShadow = a->shadow_stride;
+    at16 = (uintptr_t)a->x;
+    at8 = (uintptr_t)a->shadow;
+  }
+  if ((at16 & 15) || (at8 & 7)) return -1;
+  long long blocks = 0;
+  grp.n = n;
+  for (int i = 0; i < n; ++i) {
+    const DenseLayer& q = layers[i];
+    FusedGroup::Item& it = grp.it[i];
+    it.dz = (const char*)q.dz; it.act = (const char*)q.act;
+    it.w_off = q.w_off; it.shadow_off = q.shadow_off;
+    it.M = q.out; it.N = q.in; it.ldC = q.ldw;
+    it.cbA = b32s_blocks(q.out); it.cbB = b32s_blocks(q.in);
+    it.first = (int)blocks;
+    // 16-byte accesses at multiples of 4 columns; 32-bit byte offsets, rows of a ragged last tile and
+    // the k-steps past the end included
+    if (q.ldw % 4 || q.w_off % 4 || q.shadow_off % 4 || ((uintptr_t)it.dz & 15) || ((uintptr_t)it.act & 15) ||
+        ((long long)q.out + 64) * q.ldw * 4 >= 0x7FFFFFF0LL || (long long)it.cbA * it.cbB * 2048 >= 0x7FFFFFF0LL ||
+        (long long)(b32s_blocks(B) + 8) * (it.cbA + 8) * 2048 >= 0x7FFFFFF0LL ||
+        (long long)(b32s_blocks(B) + 8) * (it.cbB + 8) * 2048 >= 0x7FFFFFF0LL)
+      return -1;
+    blocks += ((long long)((q.out + 63) / 64) * ((q.in + 63) / 64) * K + 7) / 8 * 8;
+    if (blocks >= (1ll << 31)) return -1;
+  }
+  if (f) fused_group_kernel<EPI_STEP_CACHED><<<(unsigned)blocks, kThreads, 0, s>>>(p, grp);
+  else fused_group_kernel<EPI_ASCEND_CACHED><<<(unsigned)blocks, kThreads, 0, s>>>(p, grp);
+  return 0;
 }
 
 }  // namespace lsam

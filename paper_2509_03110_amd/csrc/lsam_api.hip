@@ -1153,7 +1153,7 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
       LaunchTimer t(c, KC_BIAS_GRAD);
       const int chunks = launch_colsum_partials(dout, cv.rows, cv.Cout, lo.K, c->at<float>(lo.colsum), s);
       if (chunks < 0) return fail(LSAM_EINVAL, "bias gradient of convolution %d rejected", l);
-      const int used = launch_bias_grad(c->at<float>(lo.colsum), cv.Cout, 0, g + ly.b_off, lo.d_pad,
+      const int used = launch_bias_grad(c->at<float>(lo.colsum), cv.Cout, g + ly.b_off, lo.d_pad,
                                         lo.K, chunks, cv.Cout, ssq ? ssq + *slots : nullptr, lo.nblk, s);
       if (ssq) *slots += used;
     }
@@ -1259,6 +1259,20 @@ bool gram_norm_pays(int B, int out, int in) {
   return (int64_t)B * (out + in) <= (int64_t)out * in;
 }
 
+// Whether the fused step and ascent of a bf16 dense model go through all layers in one launch: where
+// the state stays in the caches.
+bool fused_in_group(const Layout& lo) { return (int64_t)lo.K * lo.d_pad * 4 <= kCacheResidentBytes; }
+
+// The layers of a bf16 dense model with the dZ and the inputs that the last pass left (A0: the model's).
+void dense_layers(const lsam_ctx* c, const void* A0, DenseLayer* out) {
+  const Layout& lo = c->lo;
+  for (int l = 0; l < lo.L; ++l) {
+    const Layer& ly = lo.layers[l];
+    out[l] = DenseLayer{c->at<char>(lo.dz[l + 1]), l == 0 ? A0 : c->at<char>(lo.act[l]), ly.out, ly.in, ly.ldw,
+                        ly.w_off, ly.b_off, lo.shadow_off[l]};
+  }
+}
+
 // forward + backward of all replicas; weights taken from `wts` (fp32 or bf16 per mode).
 // `second` selects the pass at the perturbed point: its biases are x_b + scale * g1_b, which in
 // fp32 mode sit in the perturbed copy and in bf16 mode are formed in the GEMM epilogue from
@@ -1338,8 +1352,11 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
   // first pass: the kernels that write the gradient also leave the partial sums of its squares
   double* ssq = fuse_norm ? c->at<double>(lo.partials) : nullptr;
   int slots = 0;
-  GramLayer gram[LSAM_MAX_LAYERS];
+  int bias_slots = 0;
+  for (int l = l0; l < L; ++l) bias_slots += (lo.layers[l].out + 63) / 64;
+  DenseLayer dense[LSAM_MAX_LAYERS], gram[LSAM_MAX_LAYERS];
   int grams = 0;
+  if (bf) dense_layers(c, A0, dense);
   for (int l = L - 1; l >= l0; --l) {
     const Layer& ly = lo.layers[l];
     const char* dz = c->at<char>(lo.dz[l + 1]);
@@ -1371,11 +1388,12 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
       d.sumsq_only = (ssq && norm_only) ? 1 : 0;   // the gradient itself is recomputed by ascend_pass
       // Of a gradient that is not stored only the norm is wanted, which the Gram matrices of its factors give
       if (d.sumsq_only && gram_norm_pays(B, ly.out, ly.in)) {
-        gram[grams++] = GramLayer{dz, act, ly.out, ly.in};
+        gram[grams++] = dense[l];
         return LSAM_OK;
       }
       SamplerFusion f;
       if (fuse) {
+        if (fused_in_group(lo)) return LSAM_OK;
         // this layer's share of the sampler step happens in the epilogue: W_l of x, v, S, y
         f = *fuse;
         f.x += ly.w_off; f.v += ly.w_off; f.S += ly.w_off; f.y += ly.w_off;
@@ -1390,22 +1408,10 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
       return LSAM_OK;
     };
     auto bias_grad = [&]() {
-      {
-        LaunchTimer t(c, KC_BIAS_GRAD);
-        const int used = launch_bias_grad(dz, bf ? astride(l + 1) : (int64_t)ld_dz, bf, g + ly.b_off,
-                                          lo.d_pad, K, B, ly.out, ssq ? ssq + slots : nullptr,
-                                          lo.nblk, s);
-        if (ssq) slots += used;
-      }
-      if (fuse) {
-        // the bias vector's share of the sampler step (the slot of b_l is padded to 64 floats
-        // with zeros, which the step leaves zero)
-        LaunchTimer t(c, KC_DESCENT);
-        launch_descent(fuse->x + ly.b_off, g + ly.b_off, lo.d_pad, fuse->v + ly.b_off,
-                       fuse->S + ly.b_off, fuse->y + ly.b_off, nullptr, nullptr, 0, lo.d_pad,
-                       round_up(ly.out, 4), K, fuse->lam, fuse->lr, fuse->mu, fuse->nesterov, nullptr, s,
-                       fuse->restart);
-      }
+      LaunchTimer t(c, KC_BIAS_GRAD);
+      const int used = launch_bias_grad(reinterpret_cast<const float*>(dz), ld_dz, g + ly.b_off, lo.d_pad, K, B, ly.out,
+                                        ssq ? ssq + slots : nullptr, lo.nblk, s);
+      if (ssq) slots += used;
     };
     auto input_grad = [&]() -> int {
       GemmDesc d{};
@@ -1427,15 +1433,25 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
     // the input gradient still has to read, so that one goes first.
     if (fuse && want_dx && (rc = input_grad()) != LSAM_OK) return rc;
     if ((rc = weight_grad()) != LSAM_OK) return rc;
-    bias_grad();
+    if (!bf) bias_grad();
     if (!fuse && want_dx && (rc = input_grad()) != LSAM_OK) return rc;
   }
-  if (grams > 0) {
-    LaunchTimer t(c, KC_GEMM_DW_NORM);
-    if (slots + gram_slots(grams, K, B) > lo.nblk) return fail(LSAM_ESTATE, "gradient-norm partials would overrun their buffer at the Gram products");
-    const int used = launch_gram_norms(gram, grams, K, B, ssq + slots, lo.nblk, s);
-    if (used < 0) return fail(LSAM_EINVAL, "Gram products rejected");
-    slots += used;
+  if (bf) {
+    if (ssq && slots + (grams ? gram_slots(grams, K, B) : 0) + bias_slots > lo.nblk)
+      return fail(LSAM_ESTATE, "gradient-norm partials would overrun their buffer at the Gram products");
+    if (grams > 0) {
+      LaunchTimer t(c, KC_GEMM_DW_NORM);
+      const int used = launch_gram_norms(gram, grams, K, B, ssq + slots, lo.nblk, s);
+      if (used < 0) return fail(LSAM_EINVAL, "Gram products rejected");
+      slots += used;
+    }
+    if (fuse && fused_in_group(lo)) {
+      LaunchTimer t(c, KC_GEMM_DW_STEP);
+      if (launch_fused_group(dense, L, K, B, lo.d_pad, fuse, nullptr, s) != 0) return fail(LSAM_EINVAL, "step GEMMs rejected");
+    }
+    LaunchTimer t(c, KC_BIAS_GRAD);
+    const int used = launch_bias_grads_blocked(dense, L, K, B, g, lo.d_pad, ssq ? ssq + slots : nullptr, lo.nblk, fuse, s);
+    if (ssq) slots += used;
   }
   if (l0 > 0) {
     int rc = conv_backward(c, static_cast<const float*>(X), params, ssq, &slots);
@@ -1458,6 +1474,14 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
 int ascend_pass(lsam_ctx* c, const void* A0) {
   const Layout& lo = c->lo;
   const int K = lo.K, B = lo.B, L = lo.L;
+  if (fused_in_group(lo)) {
+    DenseLayer dense[LSAM_MAX_LAYERS];
+    dense_layers(c, A0, dense);
+    const AscentFusion f{c->at<float>(lo.x), c->at<float>(lo.scale), c->at<uint16_t>(lo.xt), lo.shadow_stride, 0};
+    LaunchTimer t(c, KC_GEMM_DW_ASCEND);
+    if (launch_fused_group(dense, L, K, B, lo.d_pad, nullptr, &f, c->stream) != 0) return fail(LSAM_EINVAL, "ascent GEMMs rejected");
+    return check_launch("ascent GEMMs");
+  }
   auto width = [&](int l) { return l < L ? lo.layers[l].in : lo.layers[L - 1].out; };
   auto astride = [&](int l) { return lo.act_elems(width(l), lo.ld[l]); };
   for (int l = L - 1; l >= 0; --l) {

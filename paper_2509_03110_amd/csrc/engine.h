@@ -77,9 +77,18 @@ void launch_norm_finish(const double* partials, int nblk, int64_t partials_strid
 // x~ = x + scale[k] * g.  Writes fp32 (xt_f32), or, if xt_bf16 is non-null, the bf16 operand
 // copy of the weight matrices in the blocked layout described by `map` (replica stride
 // `shadow_stride` elements).
+// `sums` (fp32, may be null): the norm is still in at most kProloguePartials partial sums per replica, and
+// this launch does launch_norm_finish's work, whose arguments it holds, as well.
+struct NormSums {
+  const double* partials; int n; int64_t pstride;
+  float rho, gamma;
+  float* norms; float* scale;
+  const float* loss_rows; int B; float* loss_out;
+  int32_t* restart;
+};
 void launch_perturb(const float* x, const float* g, int64_t g_stride, const float* scale,
                     float* xt_f32, uint16_t* xt_bf16, const ShadowMap* map, int64_t shadow_stride,
-                    int64_t stride, int64_t n, int K, hipStream_t s);
+                    int64_t stride, int64_t n, int K, hipStream_t s, const NormSums* sums = nullptr);
 // Descent + coupling for all K replicas, y read once per index:
 //   G = g + lam[k] (x - y); v = mu v + G; x -= lr (G + mu v) [nesterov] | lr v; S += x.
 // Also refreshes the bf16 operand copy of the weight matrices if `shadow` is non-null, and adds
@@ -139,6 +148,13 @@ void launch_pad_rows(const void* src, void* dst, int64_t rows, int cols, int ld_
 
 enum GemmEpilogue { EPI_BIAS = 0, EPI_BIAS_RELU = 1, EPI_MASK = 2, EPI_PLAIN = 3 };
 
+// A product whose split contraction is not added up yet: n > 1 pieces [rows of all replicas][ld], `stride`
+// floats apart, to which bias and ReLU have still to be applied; n = 1: the product is complete.
+struct SplitResult {
+  const float* p; int64_t stride; int ld, n;
+  const float* bias; int64_t strideBias;
+};
+
 // C[k][m, n] = sum_kk A(k; m, kk) * B(k; n, kk), batched over replicas k.
 // An operand is "k-major" when kk is its contiguous index (row pitch ld along m resp. n),
 // otherwise "m-major" (kk selects the row, m resp. n is contiguous).
@@ -185,6 +201,8 @@ struct GemmDesc {
   const struct AscentFusion* ascend;
   // If set (same kind of launch, `sumsq` given): only the sums of squares are written.
   int sumsq_only;
+  // If set (fp32 operands, EPI_BIAS_RELU): a split contraction is left in pieces, described here.
+  SplitResult* parts;
 };
 struct AscentFusion {
   const float* x; const float* scale;
@@ -206,8 +224,9 @@ size_t gemm_splitk_bytes(const GemmDesc& d);          // scratch this GEMM would
 // bf16 fast path (direct-to-LDS ring); returns 1 when the shape is left to the generic kernel.
 int launch_gemm_bf16(const GemmDesc& d, int tile_override, hipStream_t s, int* sumsq_slots);
 
-// A dense layer of the bf16 model for the launches that take several at once (n <= LSAM_MAX_LAYERS): dz
-// [B][out] and act [B][in] of K replicas, bf16 in the blocked layout, replicas one stored size apart.
+// A dense layer for the launches that take several at once (n <= LSAM_MAX_LAYERS): dz [B][out] and act
+// [B][in] of K replicas, replicas one stored size apart; bf16 in the blocked layout, or fp32 with rows
+// padded to 8 values (launch_dense_gradients).
 struct DenseLayer {
   const void* dz; const void* act;
   int out, in, ldw;
@@ -223,6 +242,11 @@ int gram_slots(int n, int K, int B);
 // stays in the caches.  0, or -1.
 int launch_fused_group(const DenseLayer* layers, int n, int K, int B, int64_t stride, const SamplerFusion* f,
                        const AscentFusion* a, hipStream_t s);
+// fp32: the weight and bias gradients of n layers and (may be null) of the narrow head, into g.  Returns the
+// sum-of-squares slots written per replica (at most gemm_sumsq_capacity of every product, one per 64 biases,
+// head_sumsq_slots), or -1.
+int launch_dense_gradients(const DenseLayer* layers, int n, const DenseLayer* head, int K, int B, float* g, int64_t strideG,
+                           double* sumsq, int64_t sumsq_stride, hipStream_t s);
 // Column sums of every layer's dz into g; slots as launch_bias_grad's.  `step` (may be null): the biases
 // take their sampler step as well (pointers to the whole vectors, like g).
 int launch_bias_grads_blocked(const DenseLayer* layers, int n, int K, int B, float* g, int64_t strideG, double* sumsq,
@@ -305,17 +329,13 @@ int launch_norm_param_grads(const float* part, float* grad, int64_t strideGrad, 
 // layer's input [K,B,ld], a ReLU output, ld = `in` rounded up to 8; W, bias: the layer's
 // parameters inside each replica, replica stride strideW, row pitch ld; dz [K,B,ld_dz] gets
 // the padded dZ; dA [K,B,ld], if non-null, dZ W where A > 0; returns <0 if the launch could
-// not be set up), and its weight and bias gradient in another (dW, db inside each replica's
-// gradient, stride strideG; returns the sum-of-squares slots written per replica, which is
-// head_sumsq_slots(in)).
+// not be set up); its weight and bias gradient is launch_dense_gradients' (head_sumsq_slots(in) partial sums).
+// `parts` (may be null): A is still in pieces, and is completed and written by the head's kernel.
 bool head_fits(int B, int C, int in);
 int head_sumsq_slots(int in);
-int launch_head_forward_backward(const float* A, const float* W, const float* bias, int64_t strideW,
+int launch_head_forward_backward(float* A, const SplitResult* parts, const float* W, const float* bias, int64_t strideW,
                                  const int32_t* labels, float* dz, int ld_dz, float* loss_rows,
                                  float* dA, int K, int B, int C, int in, hipStream_t s);
-int launch_head_weight_grad(const float* dz, int ld_dz, const float* A, int ldA, float* dW, int ldw,
-                            float* db, int64_t strideG, int K, int B, int C, int in, double* sumsq,
-                            int64_t sumsq_stride, hipStream_t s);
 
 // 3x3 convolution support (fp32, tensors [K][B][H][W][C], C contiguous).  All return 0, or -1
 // when the shape does not fit the kernel (pitches and channel counts that are not multiples

@@ -2,6 +2,7 @@
 // shuffle reductions) and the bias gradient (column sums of dZ).
 #include <atomic>
 
+#include "dense_gradients.h"
 #include "engine.h"
 #include "b32s.h"
 
@@ -70,12 +71,6 @@ __global__ __launch_bounds__(kThreads) void softmax_ce_kernel(
   }
 }
 
-template <typename TD> __device__ __forceinline__ float get(const TD* p);
-template <> __device__ __forceinline__ float get<float>(const float* p) { return *p; }
-template <> __device__ __forceinline__ float get<__bf16>(const __bf16* p) {
-  return static_cast<float>(*p);
-}
-
 // db[k][n] = sum_b dz[k][b][n].  A workgroup owns 64 adjacent columns of one replica; its WAVES
 // wavefronts take every WAVES-th row (lane = column, so a row is one coalesced read), each lane
 // keeps four partial sums, and the partials are combined in a fixed order through LDS.
@@ -83,53 +78,18 @@ template <> __device__ __forceinline__ float get<__bf16>(const __bf16* p) {
 // What bounds it is the chain of loads a wavefront waits for; sixteen wavefronts from 256 rows on
 // (512 rows of 64 columns, four replicas: 7.3 us with four wavefronts, 5.1 us with sixteen; below
 // 256 rows four wavefronts have at most sixteen loads each, four at a time, and stay).
-template <typename TD, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void bias_grad_kernel(const TD* __restrict__ dz, long long ld,
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void bias_grad_kernel(const float* __restrict__ dz, long long ld,
                                                             float* __restrict__ db,
                                                             long long strideDb, int B, int N,
                                                             double* __restrict__ sumsq,
                                                             long long strideSumsq, int zin,
                                                             long long zout) {
-  __shared__ float part[WAVES][64];
-  dz += (long long)blockIdx.z * zin;
-  db += blockIdx.z * zout;
+  __shared__ float part[WAVES * 64];
   const int k = blockIdx.y;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n = blockIdx.x * 64 + lane;
-  float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-  if (n < N) {
-    constexpr bool blocked = sizeof(TD) == 2;
-    const int cb = b32s_blocks(N);
-    const TD* base = blocked ? dz + (long long)k * ld : dz + (long long)k * B * ld + n;
-    auto at = [&](int b) {
-      return get<TD>(blocked ? base + b32s_offset(b, n, cb) : base + (long long)b * ld);
-    };
-    int b = wave;
-    for (; b + 3 * WAVES < B; b += 4 * WAVES) {
-      s0 += at(b);
-      s1 += at(b + WAVES);
-      s2 += at(b + 2 * WAVES);
-      s3 += at(b + 3 * WAVES);
-    }
-    for (; b < B; b += WAVES) s0 += at(b);
-  }
-  part[wave][lane] = (s0 + s1) + (s2 + s3);
-  __syncthreads();
-  if (wave == 0) {
-    float r = 0.f;
-    if (n < N) {
-#pragma unroll
-      for (int w = 0; w < WAVES; w += 4)
-        r += (part[w][lane] + part[w + 1][lane]) + (part[w + 2][lane] + part[w + 3][lane]);
-      db[(long long)k * strideDb + n] = r;
-    }
-    if (sumsq != nullptr) {        // sum of the squares of this workgroup's 64 results
-      double q = (double)r * (double)r;
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) q += __shfl_xor(q, off, 64);
-      if (lane == 0) sumsq[(long long)k * strideSumsq + blockIdx.z * gridDim.x + blockIdx.x] = q;
-    }
-  }
+  column_sums<WAVES>(dz + (long long)blockIdx.z * zin + (long long)k * B * ld, ld, db + blockIdx.z * zout + (long long)k * strideDb,
+                     B, N, blockIdx.x, part,
+                     sumsq != nullptr ? sumsq + (long long)k * strideSumsq + blockIdx.z * gridDim.x + blockIdx.x : nullptr);
 }
 
 // The same for dz in the blocked bf16 layout, read the way it is stored: a workgroup owns two
@@ -223,17 +183,22 @@ __global__ __launch_bounds__(kThreads) void bias_grad_blocked_kernel(BiasGroup p
 // a launch of its own (plus split-K reduce, softmax and bias gradient) that lasts 5-10 us
 // whatever it computes.  Two kernels replace them.  Both are chains of memory latency, not of
 // arithmetic, so each fetches everything it needs in one round of loads into LDS.
-constexpr int kHeadMaxC = 16;
 constexpr int kHeadMaxIn = 1024;     // padded input width that fits LDS beside the rows
 constexpr int kHeadMaxB = 512;
 constexpr int kHeadRows = 4;         // sample rows per workgroup, one per wavefront
-typedef float hf4 __attribute__((ext_vector_type(4)));
+
+// Where the product below the head was cut into pieces (`in_parts.n` > 1), its pieces are added up here, with
+// bias and ReLU, in the order and instead of the launch that would do it; A is then written as well.
+struct HeadParts {
+  const float* p; long long stride; int ld, n;        // pieces [rows of all replicas][ld], `stride` apart
+  const float* bias; long long strideBias;            // of the layer below
+};
 
 // Forward, loss, dZ and masked dX of kHeadRows rows of one replica.  LDS: the C weight rows
 // (pitch ld) then the sample rows (pitch ld); ld = input width rounded up to 8 = the pitch of
 // both in memory, columns in..ld-1 hold zeros.
 __global__ __launch_bounds__(kThreads) void head_forward_backward_kernel(
-    const float* __restrict__ A, const float* __restrict__ W, const float* __restrict__ bias,
+    float* __restrict__ A, HeadParts in_parts, const float* __restrict__ W, const float* __restrict__ bias,
     long long strideW, const int32_t* __restrict__ labels, float* __restrict__ dz, int ld_dz,
     float* __restrict__ loss_rows, float* __restrict__ dA, int B, int C, int in, int ld) {
   extern __shared__ __attribute__((aligned(16))) float head_lds[];
@@ -246,11 +211,30 @@ __global__ __launch_bounds__(kThreads) void head_forward_backward_kernel(
   const int nrows = B - row0 < kHeadRows ? B - row0 : kHeadRows;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float* w = W + (long long)k * strideW;
-  const float* a = A + ((long long)k * B + row0) * ld;
+  float* a = A + ((long long)k * B + row0) * ld;
   for (int i = tid; i < C * ld / 4; i += kThreads)
     reinterpret_cast<hf4*>(Ws)[i] = reinterpret_cast<const hf4*>(w)[i];
-  for (int i = tid; i < nrows * ld / 4; i += kThreads)
-    reinterpret_cast<hf4*>(As)[i] = reinterpret_cast<const hf4*>(a)[i];
+  if (in_parts.n > 1) {
+    const float* lb = in_parts.bias + (long long)k * in_parts.strideBias;
+    for (int i = tid; i < nrows * ld / 4; i += kThreads) {
+      const int rr = i / (ld / 4), j = (i - rr * (ld / 4)) * 4;
+      hf4 v = {0.f, 0.f, 0.f, 0.f};
+      if (j < in) {
+        const float* src = in_parts.p + ((long long)k * B + row0 + rr) * in_parts.ld + j;
+        v = split_sum(src, in_parts.stride, in_parts.n);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float z = j + e < in ? v[e] + lb[j + e] : 0.f;
+          v[e] = z > 0.f ? z : 0.f;
+        }
+      }
+      reinterpret_cast<hf4*>(As)[i] = v;
+      reinterpret_cast<hf4*>(a)[i] = v;
+    }
+  } else {
+    for (int i = tid; i < nrows * ld / 4; i += kThreads)
+      reinterpret_cast<hf4*>(As)[i] = reinterpret_cast<const hf4*>(a)[i];
+  }
   __syncthreads();
   for (int rr = wave; rr < nrows; rr += kWaves) {
     const long long r = (long long)k * B + row0 + rr;
@@ -331,73 +315,6 @@ __global__ __launch_bounds__(kThreads) void head_forward_backward_kernel(
   }
 }
 
-// dW[k][c][j] = sum_b dz[k][b][c] A[k][b][j] for 16 columns j of one replica, and (first
-// workgroup of a replica) db[c] = sum_b dz[b][c].  Thread = (column, one of 16 row groups); the
-// row groups are combined in a fixed order through LDS.  LDS (dynamic): dZ of the replica.
-__global__ __launch_bounds__(kThreads) void head_weight_grad_kernel(
-    const float* __restrict__ dz, int ld_dz, const float* __restrict__ A, int ldA,
-    float* __restrict__ dW, int ldw, float* __restrict__ db, long long strideG, int B, int C,
-    int in, double* __restrict__ sumsq, long long strideSumsq) {
-  extern __shared__ __attribute__((aligned(16))) float head_lds[];
-  __shared__ float part[16][kHeadMaxC][17];
-  __shared__ double ssq_part[kWaves];
-  float* dzs = head_lds;
-  const int k = blockIdx.y;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int col = tid & 15, rg = tid >> 4;
-  const float* dzk = dz + (long long)k * B * ld_dz;
-  for (int i = tid; i < B * ld_dz / 4; i += kThreads)
-    reinterpret_cast<hf4*>(dzs)[i] = reinterpret_cast<const hf4*>(dzk)[i];
-  const int j = blockIdx.x * 16 + col;
-  const float* ak = A + (long long)k * B * ldA + j;
-  float acc[kHeadMaxC];
-#pragma unroll
-  for (int c = 0; c < kHeadMaxC; ++c) acc[c] = 0.f;
-  __syncthreads();
-  if (j < in) {
-#pragma unroll 8
-    for (int b = rg; b < B; b += 16) {
-      const float av = ak[(long long)b * ldA];
-#pragma unroll
-      for (int c = 0; c < kHeadMaxC; ++c)
-        if (c < C) acc[c] += dzs[b * ld_dz + c] * av;
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < kHeadMaxC; ++c) part[rg][c][col] = acc[c];
-  __syncthreads();
-  float ssq = 0.f;
-  {
-    const int c = tid >> 4;                 // thread = (class, column)
-    float v = 0.f;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) v += part[q][c][col];
-    if (c < C && j < in) {
-      dW[(long long)k * strideG + (long long)c * ldw + j] = v;
-      ssq += v * v;
-    }
-  }
-  if (blockIdx.x == 0 && tid < C) {
-    float s0 = 0.f, s1 = 0.f;
-    int b = 0;
-    for (; b + 1 < B; b += 2) { s0 += dzs[b * ld_dz + tid]; s1 += dzs[(b + 1) * ld_dz + tid]; }
-    if (b < B) s0 += dzs[b * ld_dz + tid];
-    const float sb = s0 + s1;
-    db[(long long)k * strideG + tid] = sb;
-    ssq += sb * sb;
-  }
-  if (sumsq != nullptr) {
-    double q = (double)ssq;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) q += __shfl_xor(q, off, 64);
-    if (lane == 0) ssq_part[wave] = q;
-    __syncthreads();
-    if (tid == 0)
-      sumsq[(long long)k * strideSumsq + blockIdx.x] =
-          (ssq_part[0] + ssq_part[1]) + (ssq_part[2] + ssq_part[3]);
-  }
-}
-
 }  // namespace
 
 bool head_fits(int B, int C, int in) {
@@ -405,7 +322,7 @@ bool head_fits(int B, int C, int in) {
 }
 int head_sumsq_slots(int in) { return (in + 15) / 16; }
 
-int launch_head_forward_backward(const float* A, const float* W, const float* bias, int64_t strideW,
+int launch_head_forward_backward(float* A, const SplitResult* parts, const float* W, const float* bias, int64_t strideW,
                                  const int32_t* labels, float* dz, int ld_dz, float* loss_rows,
                                  float* dA, int K, int B, int C, int in, hipStream_t s) {
   const int ld = (in + 7) / 8 * 8;
@@ -421,18 +338,11 @@ int launch_head_forward_backward(const float* A, const float* W, const float* bi
     granted.store((size_t)(kHeadMaxC + kHeadRows) * kHeadMaxIn * 4, std::memory_order_relaxed);
   }
   dim3 grid((B + kHeadRows - 1) / kHeadRows, K);
-  head_forward_backward_kernel<<<grid, kThreads, lds, s>>>(A, W, bias, strideW, labels, dz, ld_dz,
+  HeadParts hp{nullptr, 0, 0, 1, nullptr, 0};
+  if (parts && parts->n > 1) hp = HeadParts{parts->p, parts->stride, parts->ld, parts->n, parts->bias, parts->strideBias};
+  head_forward_backward_kernel<<<grid, kThreads, lds, s>>>(A, hp, W, bias, strideW, labels, dz, ld_dz,
                                                             loss_rows, dA, B, C, in, ld);
   return 0;
-}
-
-int launch_head_weight_grad(const float* dz, int ld_dz, const float* A, int ldA, float* dW, int ldw,
-                            float* db, int64_t strideG, int K, int B, int C, int in, double* sumsq,
-                            int64_t sumsq_stride, hipStream_t s) {
-  dim3 grid(head_sumsq_slots(in), K);
-  head_weight_grad_kernel<<<grid, kThreads, (size_t)B * ld_dz * 4, s>>>(
-      dz, ld_dz, A, ldA, dW, ldw, db, strideG, B, C, in, sumsq, sumsq_stride);
-  return (int)grid.x;
 }
 
 void launch_softmax_ce(const float* logits, int ld, const int32_t* labels, void* dz, int64_t ld_dz,
@@ -450,9 +360,9 @@ void launch_softmax_ce(const float* logits, int ld, const int32_t* labels, void*
 static void run_bias_grad(const float* dz, int64_t ld, float* db, int64_t strideDb, int B, int N, double* sumsq,
                           int64_t sumsq_stride, int zin, int64_t zout, dim3 grid, hipStream_t s) {
   if (B >= 256)
-    bias_grad_kernel<float, 16><<<grid, 1024, 0, s>>>(dz, ld, db, strideDb, B, N, sumsq, sumsq_stride, zin, zout);
+    bias_grad_kernel<16><<<grid, 1024, 0, s>>>(dz, ld, db, strideDb, B, N, sumsq, sumsq_stride, zin, zout);
   else
-    bias_grad_kernel<float, kWaves><<<grid, kThreads, 0, s>>>(dz, ld, db, strideDb, B, N, sumsq, sumsq_stride, zin,
+    bias_grad_kernel<kWaves><<<grid, kThreads, 0, s>>>(dz, ld, db, strideDb, B, N, sumsq, sumsq_stride, zin,
                                                               zout);
 }
 

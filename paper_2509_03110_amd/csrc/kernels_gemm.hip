@@ -18,9 +18,11 @@
 // reads of the next 16 (bf16) / 8 (fp32) k overlap the MFMAs of the current ones.
 // The MFMA is issued with the roles swapped (rows <- B operand, columns <- A operand), so
 // that a lane ends up with 4 consecutive n of one row m: 16-byte stores in the epilogue.
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
+#include "dense_gradients.h"
 #include "engine.h"
 
 namespace lsam {
@@ -59,6 +61,7 @@ struct GemmParams {
   // range owned by its own workgroup, which writes raw fp32 sums to partial[split]
   float* partial; long long strideSplit; int ldP;
   int splits, steps_per_split;
+  int unreduced;            // the partial sums are left to the caller
   // optional sum of squares of the stored results, one slot per workgroup that stores them
   double* sumsq; long long strideSumsq;
 };
@@ -404,9 +407,8 @@ __device__ __forceinline__ float widen(__bf16 v) { return static_cast<float>(v);
 // matrix unit is rounded) at fp32 memory traffic and half the LDS traffic.
 // Which k a lane's eight values stand for does not matter as long as both operands agree: a
 // lane takes the four of its unit in the even chunk and the four of its unit in the odd one.
-template <typename T, typename TC, int BM, int BN, int BKU, bool A_KMAJOR, bool B_KMAJOR, int OCC,
-          int CONV = 0, bool BF16MATH = false>
-__global__ __launch_bounds__(kThreads, OCC) void gemm_kernel(GemmParams p) {
+template <typename T, typename TC, int BM, int BN, int BKU, bool A_KMAJOR, bool B_KMAJOR, int CONV, bool BF16MATH>
+__device__ __forceinline__ void gemm_tile(const GemmParams& p, int w) {
   static_assert(!BF16MATH || Op<T>::UE == 4, "bf16 math is a mode of the fp32-operand kernel");
   static_assert(CONV == 0 || (CONV == 1 && A_KMAJOR) || (CONV == 2 && !B_KMAJOR), "operand layout");
   constexpr int UE = Op<T>::UE;
@@ -421,7 +423,6 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_kernel(GemmParams p) {
   // Workgroup -> tile.  Hardware deals consecutive workgroup ids round-robin over the 8
   // XCDs; remap so that each XCD walks a contiguous range of tiles (tiles that share a
   // weight panel then share one L2).
-  const int w = blockIdx.x;
   const int slot = (w % 8) * p.chunks + w / 8;
   if (slot >= p.total) return;
   // Which of a tile's split ranges this workgroup takes.  Dense layers: the splits of one tile
@@ -696,6 +697,71 @@ __global__ __launch_bounds__(kThreads, OCC) void gemm_kernel(GemmParams p) {
   }
 }
 
+template <typename T, typename TC, int BM, int BN, int BKU, bool A_KMAJOR, bool B_KMAJOR, int OCC,
+          int CONV = 0, bool BF16MATH = false>
+__global__ __launch_bounds__(kThreads, OCC) void gemm_kernel(GemmParams p) {
+  gemm_tile<T, TC, BM, BN, BKU, A_KMAJOR, B_KMAJOR, CONV, BF16MATH>(p, blockIdx.x);
+}
+
+// Every gradient of the dense layers' parameters in one launch: the weight gradients dZ^T A of the items,
+// the narrow head's (if any) and the bias sums.  They wait for nothing but the dZ of the pass, and alone
+// each is a few microseconds of ramp and memory latency: 2 replicas 784-128-10 with batch 32 took 12 us for
+// the three launches and takes 6; a step 68 -> 50 us (with the split product's pieces left to the head), of 4
+// 3072-1024-1024-10 with 128 453 -> 412, of 8 256-200-100-50 with 32 135 -> 104.
+struct DenseGrads {
+  int n, B, K;
+  float* g; long long strideG;
+  double* sumsq; long long strideSumsq;
+  int head_first, head_blocks, bias_first;      // workgroups: the items', then head_blocks * K, then the biases'
+  struct Item {
+    const float* dz; const float* act;
+    long long w_off, b_off;
+    int out, in, ld_dz, ld_act, ldw;
+    int first, slot;                            // of the product's workgroups and of its partial sums
+    int bias_block, bias_slot;                  // the first of its blocks of 64 biases, and of their partial sums
+  } it[LSAM_MAX_LAYERS];
+  Item head;                                    // slot: of the head's partial sums
+};
+template <int BT, int OCC>
+__global__ __launch_bounds__(kThreads, OCC) void dense_gradients_kernel(GemmParams p, DenseGrads d) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int w = blockIdx.x;
+  auto slot = [&](int k, int at) -> double* {
+    return d.sumsq != nullptr ? d.sumsq + (long long)k * d.strideSumsq + at : nullptr;
+  };
+  if (w >= d.bias_first) {
+    const int block = (w - d.bias_first) / d.K, k = (w - d.bias_first) % d.K;
+    int item = 0;
+    while (item + 1 < d.n && block >= d.it[item + 1].bias_block) ++item;
+    const DenseGrads::Item& it = d.it[item];
+    const int b = block - it.bias_block;
+    column_sums<4>(it.dz + (long long)k * d.B * it.ld_dz, it.ld_dz, d.g + (long long)k * d.strideG + it.b_off, d.B, it.out, b,
+                   reinterpret_cast<float*>(smem), slot(k, it.bias_slot + b));
+    return;
+  }
+  if (w >= d.head_first) {
+    const int b = (w - d.head_first) / d.K, k = (w - d.head_first) % d.K;
+    const DenseGrads::Item& it = d.head;
+    float* g = d.g + (long long)k * d.strideG;
+    head_weight_grad(it.dz + (long long)k * d.B * it.ld_dz, it.ld_dz, it.act + (long long)k * d.B * it.ld_act, it.ld_act,
+                     g + it.w_off, it.ldw, g + it.b_off, d.B, it.out, it.in, b, reinterpret_cast<float*>(smem),
+                     slot(k, it.slot + b));
+    return;
+  }
+  int item = 0;
+  while (item + 1 < d.n && w >= d.it[item + 1].first) ++item;
+  const DenseGrads::Item& it = d.it[item];
+  p.A = reinterpret_cast<const char*>(it.dz); p.strideA = (long long)d.B * it.ld_dz; p.ldA = it.ld_dz;
+  p.B = reinterpret_cast<const char*>(it.act); p.strideB = (long long)d.B * it.ld_act; p.ldB = it.ld_act;
+  p.C = reinterpret_cast<char*>(d.g + it.w_off); p.ldC = it.ldw;
+  p.M = it.out; p.N = it.in;
+  p.tilesM = (p.M + BT - 1) / BT; p.tilesN = (p.N + BT - 1) / BT;
+  p.total = p.tilesM * p.tilesN * p.batch;
+  p.chunks = (p.total + 7) / 8;
+  p.sumsq = d.sumsq != nullptr ? d.sumsq + it.slot : nullptr;
+  gemm_tile<float, float, BT, BT, 8, false, false, 0, false>(p, w - it.first);
+}
+
 // Sums the split-K partials in a fixed order and applies the epilogue the GEMM skipped.
 // Grid: x over groups of 256 of the M * ldP/4 vector words of one replica, y = replica.  A
 // workgroup is LANES x 256 threads; with LANES = 4, thread (lane group q, word) adds the partials q, q+4, q+8, ...
@@ -867,7 +933,7 @@ int launch_one(const GemmParams& p0, hipStream_t s, int* sumsq_slots) {
     attr_set.store(true, std::memory_order_relaxed);
   }
   kern<<<p.chunks * 8, kThreads, smem, s>>>(p);
-  const int slots = p.splits > 1 ? reduce_splits(p, s) : p.tilesM * p.tilesN;
+  const int slots = p.splits > 1 && !p.unreduced ? reduce_splits(p, s) : p.tilesM * p.tilesN;
   if (sumsq_slots) *sumsq_slots = slots;
   return 0;
 }
@@ -994,7 +1060,77 @@ int launch_gemm(const GemmDesc& d, hipStream_t s, int* sumsq_slots) {
     p.ldP = pl.ldP;
     p.strideSplit = (long long)d.batch * d.M * pl.ldP;
   }
+  p.unreduced = 0;
+  // (left to the next kernel while a row of its input has few pieces to add up: 5 of 128 columns, 4.2 us
+  // of a reduce against 1.6 more there; 4 of 1024 even; 16 of 512, 6 us against 18)
+  if (d.parts) {
+    p.unreduced = p.splits > 1 && p.splits * d.N <= 2048;
+    *d.parts = SplitResult{p.partial, p.strideSplit, p.ldP, p.unreduced ? p.splits : 1, d.bias, d.strideBias};
+  }
   return launch_layout<float, float>(d, p, pl, s, sumsq_slots);
+}
+
+int launch_dense_gradients(const DenseLayer* layers, int n, const DenseLayer* head, int K, int B, float* g, int64_t strideG,
+                           double* sumsq, int64_t sumsq_stride, hipStream_t s) {
+  if (n < 0 || n > LSAM_MAX_LAYERS || (n == 0 && !head) || (strideG % 4) || ((uintptr_t)g & 15)) return -1;
+  // 128x128 tiles where they give every compute unit one, as for a product of its own
+  long long large = 0;
+  for (int i = 0; i < n; ++i)
+    large += layers[i].out >= 128 && layers[i].in >= 128 ? (long long)((layers[i].out + 127) / 128) * ((layers[i].in + 127) / 128) * K : 0;
+  const int tile = large >= 256 ? 128 : 64;
+  DenseGrads d{};
+  GemmParams p{};
+  d.n = n; d.B = B; d.K = K;
+  d.g = g; d.strideG = strideG;
+  d.sumsq = sumsq; d.strideSumsq = sumsq_stride;
+  p.cm = ConvMap{0, 1, 1, 1.f, 1.f, 0};
+  p.Kd = B; p.batch = K; p.strideC = strideG;
+  p.epilogue = EPI_PLAIN;
+  p.splits = 1; p.steps_per_split = 1 << 30;
+  p.strideSumsq = sumsq_stride;
+  long long blocks = 0;
+  int slots = 0, bias_blocks = 0;
+  auto item = [&](const DenseLayer& q) {
+    return DenseGrads::Item{(const float*)q.dz, (const float*)q.act, q.w_off, q.b_off, q.out, q.in, (q.out + 7) / 8 * 8,
+                            (q.in + 7) / 8 * 8, q.ldw, (int)blocks, slots, bias_blocks, 0};
+  };
+  size_t lds = 0;
+  for (int i = 0; i < n; ++i) {
+    const DenseLayer& q = layers[i];
+    d.it[i] = item(q);
+    // 16-byte units and 32-bit byte offsets inside one replica's operand, as for a product of its own
+    if (q.ldw % 8 || q.w_off % 4 || ((uintptr_t)q.dz & 15) || ((uintptr_t)q.act & 15) ||
+        (long long)B * d.it[i].ld_dz * 4 >= 0x7FFFFFF0LL || (long long)B * d.it[i].ld_act * 4 >= 0x7FFFFFF0LL)
+      return -1;
+    const int tiles = ((q.out + tile - 1) / tile) * ((q.in + tile - 1) / tile);
+    blocks += ((long long)tiles * K + 7) / 8 * 8;
+    slots += tiles;
+    bias_blocks += (q.out + 63) / 64;
+    if (blocks >= (1ll << 30)) return -1;
+    lds = std::max<size_t>({lds, (size_t)2 * 8 * (2 * (tile + 1)) * 16, (size_t)64 * (tile + 4) * 4});
+  }
+  d.head_first = (int)blocks;
+  if (head) {
+    d.head = item(*head);
+    d.head_blocks = head_sumsq_slots(head->in);
+    slots += d.head_blocks;
+    blocks += (long long)d.head_blocks * K;
+    lds = std::max<size_t>(lds, head_grad_lds(B, d.head.ld_dz));
+  }
+  d.bias_first = (int)blocks;
+  for (int i = 0; i < n; ++i) d.it[i].bias_slot = slots + d.it[i].bias_block;
+  blocks += (long long)bias_blocks * K;
+  auto go = [&](auto kern) {
+    static std::atomic<bool> attr_set{false};   // (setting it twice is harmless)
+    if (!attr_set.load(std::memory_order_relaxed)) {
+      if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 80 << 10) != hipSuccess)
+        return -1;
+      attr_set.store(true, std::memory_order_relaxed);
+    }
+    kern<<<(unsigned)blocks, kThreads, lds, s>>>(p, d);
+    return slots + bias_blocks;
+  };
+  return tile == 128 ? go(dense_gradients_kernel<128, 2>) : go(dense_gradients_kernel<64, 2>);
 }
 
 }  // namespace lsam

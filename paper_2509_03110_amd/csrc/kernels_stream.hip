@@ -79,6 +79,13 @@ __device__ __forceinline__ double block_sum(double v) {
   return r;
 }
 
+// Mean of a replica's B losses; valid in thread 0.
+__device__ __forceinline__ double mean_loss(const float* rows, int B) {
+  double l = 0.0;
+  for (int i = threadIdx.x; i < B; i += kThreads) l += (double)rows[i];
+  return block_sum(l) / (double)B;
+}
+
 // ---- gradient norm, pass 1 ------------------------------------------------------------------
 // HBM-bound: 4 bytes per value, four 16-byte loads in flight per lane.  nv whole words of four and
 // `rem` values behind them; rows may start at any multiple of 4 bytes.
@@ -133,26 +140,59 @@ __global__ __launch_bounds__(kThreads) void norm_finish_kernel(
     scale[k] = (float)((double)rho / (n + (double)gamma));
   }
   if (loss_rows != nullptr && loss_out != nullptr) {
-    double l = 0.0;
-    for (int i = threadIdx.x; i < B; i += kThreads) l += (double)loss_rows[(int64_t)k * B + i];
-    l = block_sum(l);
-    if (threadIdx.x == 0) loss_out[k] = (float)(l / (double)B);
+    const double l = mean_loss(loss_rows + (int64_t)k * B, B);
+    if (threadIdx.x == 0) loss_out[k] = (float)l;
   }
 }
 
 // ---- ascent perturbation ----------------------------------------------------------------------
-template <bool STREAM>
+// The norm from its partial sums and the scale rho / (norm + gamma), by every wavefront for itself: at most
+// kProloguePartials sums.
+__device__ __forceinline__ float scale_from_sums(const double* part, int n, float rho, float gamma, float& norm) {
+  const int lane = threadIdx.x & 63;
+  double s = lane < n ? part[lane] : 0.0;
+  if (lane + 64 < n) s += part[lane + 64];
+  s = __shfl(wave_sum(s), 0, 64);
+  const double r = sqrt(s);
+  norm = (float)r;
+  return (float)((double)rho / (r + (double)gamma));
+}
+
+// SUMS: what norm_finish_kernel does (norm, scale, mean loss, marks) happens here, before the lanes' own
+// values are touched, where the partial sums are few: a launch less (3 us of a step that takes 50).
+template <bool STREAM, bool SUMS>
 __global__ __launch_bounds__(kThreads) void perturb_kernel(
     const float* __restrict__ x, const float* __restrict__ g, int64_t g_stride,
-    const float* __restrict__ scale, float* __restrict__ xt, int64_t stride, int64_t nv, int rem) {
+    const float* __restrict__ scale, float* __restrict__ xt, int64_t stride, int64_t nv, int rem, NormSums fin) {
   const int k = blockIdx.y;
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  const float sc = scale[k];
   const float* xk = x + (int64_t)k * stride + i * 4;
   const float* gk = g + (int64_t)k * g_stride + i * 4;
   float* tk = xt + (int64_t)k * stride + i * 4;
+  f32x4 xv = {}, gv = {};
   if (i < nv) {
-    const f32x4 xv = ldv(xk), gv = ld_any<true>(gk);
+    xv = ldv(xk);
+    gv = ld_any<true>(gk);
+  }
+  float sc;
+  if constexpr (SUMS) {
+    float norm;
+    sc = scale_from_sums(fin.partials + (int64_t)k * fin.pstride, fin.n, fin.rho, fin.gamma, norm);
+    if (blockIdx.x == 0) {
+      if (threadIdx.x == 0) {
+        if (fin.restart != nullptr) count_mark(fin.restart + k);
+        fin.norms[k] = norm;
+        fin.scale[k] = sc;
+      }
+      if (fin.loss_rows != nullptr && fin.loss_out != nullptr) {
+        const double l = mean_loss(fin.loss_rows + (int64_t)k * fin.B, fin.B);
+        if (threadIdx.x == 0) fin.loss_out[k] = (float)l;
+      }
+    }
+  } else {
+    sc = scale[k];
+  }
+  if (i < nv) {
     f32x4 o;
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = ascent_point(xv[e], sc, gv[e]);
@@ -268,14 +308,10 @@ __global__ __launch_bounds__(kThreads) void descent_kernel(
   }
   float sc = 0.f;
   if constexpr (ASCENT == ASCENT_SUMS) {
-    const double* part = up.partials + (int64_t)k * up.nblk;
-    double s = lane < up.nblk ? part[lane] : 0.0;
-    if (lane + 64 < up.nblk) s += part[lane + 64];
-    s = __shfl(wave_sum(s), 0, 64);
-    const double norm = sqrt(s);
-    sc = (float)((double)up.rho / (norm + (double)up.gamma));
+    float norm;
+    sc = scale_from_sums(up.partials + (int64_t)k * up.nblk, up.nblk, up.rho, up.gamma, norm);
     if (beg == 0 && threadIdx.x == 0) {
-      up.norms[k] = (float)norm;
+      up.norms[k] = norm;
       up.scale[k] = sc;
     }
   } else if constexpr (ASCENT == ASCENT_SCALE) {
@@ -475,7 +511,7 @@ void launch_norm_finish(const double* partials, int nblk, int64_t partials_strid
 
 void launch_perturb(const float* x, const float* g, int64_t g_stride, const float* scale,
                     float* xt_f32, uint16_t* xt_bf16, const ShadowMap* map, int64_t shadow_stride,
-                    int64_t stride, int64_t n, int K, hipStream_t s) {
+                    int64_t stride, int64_t n, int K, hipStream_t s, const NormSums* sums) {
   if (xt_bf16) {
     // bf16 mode only exists for the MLP layouts, which are always vector-aligned
     TileMap tm{};
@@ -493,10 +529,12 @@ void launch_perturb(const float* x, const float* g, int64_t g_stride, const floa
                                                    shadow_stride, stride);
   } else {
     dim3 grid(blocks_for((n + 3) / 4), K);
-    if ((int64_t)K * n * 4 > kCacheResidentBytes)
-      perturb_kernel<true><<<grid, kThreads, 0, s>>>(x, g, g_stride, scale, xt_f32, stride, n / 4, (int)(n % 4));
-    else
-      perturb_kernel<false><<<grid, kThreads, 0, s>>>(x, g, g_stride, scale, xt_f32, stride, n / 4, (int)(n % 4));
+    auto go = [&](auto kernel, const NormSums& fin) {
+      kernel<<<grid, kThreads, 0, s>>>(x, g, g_stride, scale, xt_f32, stride, n / 4, (int)(n % 4), fin);
+    };
+    const bool stream = (int64_t)K * n * 4 > kCacheResidentBytes;
+    if (sums) stream ? go(perturb_kernel<true, true>, *sums) : go(perturb_kernel<false, true>, *sums);
+    else stream ? go(perturb_kernel<true, false>, NormSums{}) : go(perturb_kernel<false, false>, NormSums{});
   }
 }
 

@@ -1263,13 +1263,13 @@ bool gram_norm_pays(int B, int out, int in) {
 // the state stays in the caches.
 bool fused_in_group(const Layout& lo) { return (int64_t)lo.K * lo.d_pad * 4 <= kCacheResidentBytes; }
 
-// The layers of a bf16 dense model with the dZ and the inputs that the last pass left (A0: the model's).
+// The dense layers with the dZ and the inputs that the last pass left (A0: the first one's).
 void dense_layers(const lsam_ctx* c, const void* A0, DenseLayer* out) {
   const Layout& lo = c->lo;
-  for (int l = 0; l < lo.L; ++l) {
+  for (int l = lo.n_conv; l < lo.L; ++l) {
     const Layer& ly = lo.layers[l];
-    out[l] = DenseLayer{c->at<char>(lo.dz[l + 1]), l == 0 ? A0 : c->at<char>(lo.act[l]), ly.out, ly.in, ly.ldw,
-                        ly.w_off, ly.b_off, lo.shadow_off[l]};
+    out[l] = DenseLayer{c->at<char>(lo.dz[l + 1]), l == lo.n_conv ? A0 : c->at<char>(lo.act[l]), ly.out, ly.in, ly.ldw,
+                        ly.w_off, ly.b_off, lo.bf16 ? lo.shadow_off[l] : 0};
   }
 }
 
@@ -1306,6 +1306,7 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
   // A narrow fp32 classifier head is not run as GEMMs: two fused kernels cover its forward
   // pass, the loss, dZ, dX, dW and db.
   const bool head = head_is_fused(lo);
+  SplitResult parts{nullptr, 0, 0, 1, nullptr, 0};     // of the product below the head
   for (int l = l0; l < (head ? L - 1 : L); ++l) {
     const Layer& ly = lo.layers[l];
     const bool last = l == L - 1;
@@ -1327,6 +1328,7 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
       d.bias_scale = c->at<float>(lo.scale);
     }
     split(c, d);
+    if (head && l == L - 2) d.parts = &parts;
     LaunchTimer t(c, KC_GEMM_FWD);
     if (launch_gemm(d, s) != 0) return fail(LSAM_EINVAL, "forward GEMM of layer %d rejected", l);
   }
@@ -1334,9 +1336,9 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
   const bool need_dA0 = l0 > 0;
   if (head) {
     const Layer& ly = lo.layers[L - 1];
-    const float* in_act = L - 1 == l0 ? static_cast<const float*>(A0) : c->at<float>(lo.act[L - 1]);
+    float* in_act = L - 1 == l0 ? static_cast<float*>(const_cast<void*>(A0)) : c->at<float>(lo.act[L - 1]);   // written only where `parts`
     LaunchTimer t(c, KC_HEAD);
-    if (launch_head_forward_backward(in_act, params + ly.w_off, params + ly.b_off, lo.d_pad, labels,
+    if (launch_head_forward_backward(in_act, &parts, params + ly.w_off, params + ly.b_off, lo.d_pad, labels,
                                      c->at<float>(lo.dz[L]), lo.ld[L],
                                      want_loss ? c->at<float>(lo.loss_rows) : nullptr,
                                      (L - 1 > l0 || need_dA0) ? c->at<float>(lo.dz[L - 1]) : nullptr,
@@ -1356,7 +1358,9 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
   for (int l = l0; l < L; ++l) bias_slots += (lo.layers[l].out + 63) / 64;
   DenseLayer dense[LSAM_MAX_LAYERS], gram[LSAM_MAX_LAYERS];
   int grams = 0;
-  if (bf) dense_layers(c, A0, dense);
+  dense_layers(c, A0, dense);
+  // fp32: all weight and bias gradients share a launch once the dZ are there
+  const bool grouped = !bf && !lo.bf16_math;
   for (int l = L - 1; l >= l0; --l) {
     const Layer& ly = lo.layers[l];
     const char* dz = c->at<char>(lo.dz[l + 1]);
@@ -1366,15 +1370,7 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
     if (ssq && slots + std::max(gemm_sumsq_capacity(ly.out, ly.in), head_sumsq_slots(ly.in)) +
                        (ly.out + 63) / 64 > lo.nblk)
       return fail(LSAM_ESTATE, "gradient-norm partials would overrun their buffer at layer %d", l);
-    if (head && l == L - 1) {
-      LaunchTimer t(c, KC_HEAD);
-      const int used = launch_head_weight_grad(
-          reinterpret_cast<const float*>(dz), ld_dz, static_cast<const float*>(act), lo.ld[l],
-          g + ly.w_off, ly.ldw, g + ly.b_off, lo.d_pad, K, B, ly.out, ly.in,
-          ssq ? ssq + slots : nullptr, lo.nblk, s);
-      if (ssq) slots += used;
-      continue;
-    }
+    if (head && l == L - 1) continue;      // (its dX is done)
     auto weight_grad = [&]() -> int {
       GemmDesc d{};
       d.b32s = bf;
@@ -1432,9 +1428,19 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
     // With the fused step the weight-gradient kernel overwrites the operand copy of W_l that
     // the input gradient still has to read, so that one goes first.
     if (fuse && want_dx && (rc = input_grad()) != LSAM_OK) return rc;
-    if ((rc = weight_grad()) != LSAM_OK) return rc;
-    if (!bf) bias_grad();
+    if (!grouped && (rc = weight_grad()) != LSAM_OK) return rc;
+    if (!bf && !grouped) bias_grad();
     if (!fuse && want_dx && (rc = input_grad()) != LSAM_OK) return rc;
+  }
+  if (grouped) {
+    int most = bias_slots + (head ? head_sumsq_slots(lo.layers[L - 1].in) : 0);
+    for (int l = l0; l < (head ? L - 1 : L); ++l) most += gemm_sumsq_capacity(lo.layers[l].out, lo.layers[l].in);
+    if (ssq && most > lo.nblk) return fail(LSAM_ESTATE, "gradient-norm partials would overrun their buffer at the dense layers");
+    LaunchTimer t(c, KC_GEMM_DW);
+    const int used = launch_dense_gradients(dense + l0, (head ? L - 1 : L) - l0, head ? dense + L - 1 : nullptr, K, B, g,
+                                            lo.d_pad, ssq, lo.nblk, s);
+    if (used < 0) return fail(LSAM_EINVAL, "weight gradients of the dense layers rejected");
+    if (ssq) slots += used;
   }
   if (bf) {
     if (ssq && slots + (grams ? gram_slots(grams, K, B) : 0) + bias_slots > lo.nblk)
@@ -1520,21 +1526,21 @@ int update_tail_first(lsam_ctx* c, const float* g1, int64_t g_stride, int64_t n,
     LaunchTimer t(c, KC_SUMSQ);
     launch_sumsq_partials(g1, g_stride, n, lo.K, c->at<double>(lo.partials), nparts, s);
   }
-  {
+  const NormSums sums{c->at<double>(lo.partials), nparts, partials_ready ? lo.nblk : nparts, c->rho, c->cfg.gamma,
+                      c->at<float>(lo.norms), c->at<float>(lo.scale), lo.raw ? nullptr : c->at<float>(lo.loss_rows), lo.B,
+                      lo.raw ? nullptr : (loss ? loss : c->at<float>(lo.loss)), c->at<int32_t>(lo.restart)};
+  const bool with_perturb = c->rho != 0.f && perturb;
+  const bool joined = with_perturb && !lo.bf16 && nparts <= kProloguePartials;
+  if (!joined) {
     LaunchTimer t(c, KC_NORM_FINISH);
-    launch_norm_finish(c->at<double>(lo.partials), nparts, partials_ready ? lo.nblk : nparts, lo.K,
-                       c->rho, c->cfg.gamma,
-                       c->at<float>(lo.norms), c->at<float>(lo.scale),
-                       lo.raw ? nullptr : c->at<float>(lo.loss_rows), lo.B,
-                       lo.raw ? nullptr : (loss ? loss : c->at<float>(lo.loss)), s,
-                       c->at<int32_t>(lo.restart));
+    launch_norm_finish(sums.partials, nparts, sums.pstride, lo.K, sums.rho, sums.gamma, sums.norms, sums.scale,
+                       sums.loss_rows, lo.B, sums.loss_out, s, sums.restart);
   }
-  if (c->rho != 0.f && perturb) {
+  if (with_perturb) {
     LaunchTimer t(c, KC_PERTURB);
-    launch_perturb(c->at<float>(lo.x), g1, g_stride, c->at<float>(lo.scale),
-                   lo.bf16 ? nullptr : c->at<float>(lo.xt),
-                   lo.bf16 ? c->at<uint16_t>(lo.xt) : nullptr, &lo.map, lo.shadow_stride, lo.d_pad, n,
-                   lo.K, s);
+    launch_perturb(c->at<float>(lo.x), g1, g_stride, sums.scale, lo.bf16 ? nullptr : c->at<float>(lo.xt),
+                   lo.bf16 ? c->at<uint16_t>(lo.xt) : nullptr, &lo.map, lo.shadow_stride, lo.d_pad, n, lo.K, s,
+                   joined ? &sums : nullptr);
   }
   return check_launch("norm/perturb");
 }

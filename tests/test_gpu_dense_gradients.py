@@ -1,0 +1,24 @@
+"""fp32 dense models whose gradients come from one launch: widths and batches around the tiles, with the
+narrow head and without, the product below the head left to it in one, few and many pieces, and
+numbers of partial sums of the norm on both sides of what the perturbation adds up itself."""
+import pytest
+
+torch = pytest.importorskip("torch")
+import workloads  # noqa: E402
+from test_gpu_parity import run_mlp  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dims,B,K", [
+    ((30, 10), 5, 1),                            # the head alone, on the data
+    ((784, 128, 10), 32, 2),                     # the product below the head in 6 pieces
+    ((2000, 64, 16), 8, 2), ((3000, 100, 3), 24, 3),     # in 15 and 16 (17-column remainders)
+    ((1500, 300, 10), 64, 2),                    # too wide for that: reduced by a launch of its own
+    ((65, 63, 129, 17), 33, 2), ((64, 64, 64, 64), 64, 1), ((200, 127, 17, 40), 130, 3),    # no narrow head
+    ((520, 700, 640, 12), 100, 4),               # 128x128 tiles, more than 128 partial sums
+    ((300, 520, 24, 10), 512, 2)])               # the head's largest batch
+def test_against_the_oracle(dims, B, K):
+    w = workloads.WORKLOADS["cfg1"].scaled(name="dg", lr=0.01, K=K, dims=dims, batch=B, tau=(2,) * K, n_classes=dims[-1], steps=3)
+    # (the bounds for fp32; pre-activations at least 2e-5 from zero, some ten roundings)
+    run_mlp(w, 3, 1e-4, 1e-3, margin=True, margin_ratio=32.0, min_margin=2e-5)

@@ -25,6 +25,8 @@
 // In LDS every operand lies as 32 x 32 blocks of 2 KiB with the unit permutation of b32s.h (a
 // lane picks the unit it fetches, the copy itself is linear), so both kinds of fragment reads
 // have few bank conflicts (measured: 0 to 13 % of the cycles the LDS is active).
+#include <algorithm>
+
 #include "engine.h"
 #include "planes.h"
 
@@ -48,6 +50,7 @@ typedef __attribute__((address_space(3))) unsigned char lds_byte;
 struct Geometry {
   int C, oH, oW, sH, sW, st, nu, nv, du0, dv0;
   unsigned magicC;                 // 2^32 / C + 1: tap of a contraction index by a high multiply
+  unsigned magicW, magicH, magicH2;    // the same for oW, oH and oH + 2 (weight gradients from patches)
 };
 
 struct Params {
@@ -82,6 +85,14 @@ __device__ __forceinline__ void decode(int p, const Geometry& g, int& b, int& i,
   const int q = p / g.oW;
   j = p - q * g.oW;
   b = q / g.oH;
+  i = q - b * g.oH;
+}
+
+// The same by high multiplies: p d < 2^32 for the divisors d >= 2 (wgrad_decodes).
+__device__ __forceinline__ void decode_fast(int p, const Geometry& g, int& b, int& i, int& j) {
+  const int q = (int)__umulhi((unsigned)p, g.magicW);
+  j = p - q * g.oW;
+  b = (int)__umulhi((unsigned)q, g.magicH);
   i = q - b * g.oH;
 }
 
@@ -1090,7 +1101,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_patch_kernel(Params p)
   store_tile(p, acc, stage, m0 + wave * (TM * 32), n0, bat, piece, t_in);
 }
 
-// ---- weight gradient of 3x3 layers with stride 1, three planes, image patches in LDS ------------------
+// ---- weight gradient of 3x3 layers with stride 1, image patches in LDS ------------------
 // The ring forms 64 x 128 results from operands that pass through LDS once per 64 rows resp. per
 // tap, 1152 bytes a pixel, and waits for the caches that deliver them (160 channels at 32 x 32,
 // 4 replicas of 128: 9.6 TB/s out of L2 at 106 TFLOP/s).  Here a workgroup takes 32 OB output channels x 32
@@ -1109,30 +1120,30 @@ __device__ __forceinline__ void patch_offsets(const Geometry& g, int px0, int im
                                               const int (&col)[NLA], unsigned (&off)[NLA]) {
   const int H2 = g.oH + 2;
   int b0, i0, j0;
-  decode(px0, g, b0, i0, j0);
+  decode_fast(px0, g, b0, i0, j0);
   const int pr0 = __builtin_amdgcn_readfirstlane(b0 * H2 + i0);
 #pragma unroll
   for (int l = 0; l < NLA; ++l) {
-    const int pr = pr0 + row[l], b = pr / H2, i = pr - b * H2 - 1;
+    const int pr = pr0 + row[l], b = (int)__umulhi((unsigned)pr, g.magicH2), i = pr - b * H2 - 1;
     const bool ok = (unsigned)i < (unsigned)g.oH && b < images && col[l] >= 0;
     off[l] = ok ? (unsigned)(b * g.oH + i) * (unsigned)(g.oW * g.C * 2) + (unsigned)col[l] : kOob;
   }
 }
 // Load x of a stage: planes of the patch (NLA each), then of the gradient; `ahead`: bytes in front of the
 // stage's first row of the gradient.
-template <int OB, int PX, int NCHUNK, int NLA>
+template <int NP, int OB, int PX, int NCHUNK, int NLA>
 __device__ __forceinline__ void issue_wgrad(const Params& p, const unsigned short* Ab, const unsigned short* Bb, lds_byte* buf,
                                             lds_byte* spill, bool live, const unsigned (&off)[NLA], unsigned zoff, unsigned ahead,
                                             int wave, int x) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  if (x < 3 * NLA) {
+  if (x < NP * NLA) {
     const int q = x / NLA, l = x % NLA, chunk = wave + 8 * l;
     lds_byte* dst = chunk < NCHUNK ? buf + (q * NCHUNK + chunk) * 1024 : spill;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(Bb + q * p.planeB, live ? p.bytesB : 0u),
                                              (__attribute__((address_space(3))) void*)dst, 16, off[l], 0, 0, 0);
   } else {
-    const int q = x - 3 * NLA;
-    lds_byte* dst = wave < OB * PX / 16 ? buf + 3 * NCHUNK * 1024 + q * (OB * PX * 64) + wave * 1024 : spill;
+    const int q = x - NP * NLA;
+    lds_byte* dst = wave < OB * PX / 16 ? buf + NP * NCHUNK * 1024 + q * (OB * PX * 64) + wave * 1024 : spill;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(Ab + q * p.planeA, live ? p.bytesA : 0u),
                                              (__attribute__((address_space(3))) void*)dst, 16,
                                              zoff == kOob ? kOob : zoff + ahead, 0, 0, 0);
@@ -1152,9 +1163,9 @@ __device__ __forceinline__ u32x4 read_transposed(const lds_byte* at0, const lds_
   return f;
 }
 
-template <int OB, int PX, int NCHUNK>
-__global__ __launch_bounds__(512, 2) void conv_split_wgrad_kernel(Params p) {
-  constexpr int NP = 3, PG = 4 / OB, CH = PX / 16 / PG, NT = 5;   // CH: matrix depths per wavefront and stage
+template <int NP, int OB, int PX, int NCHUNK>
+__global__ __launch_bounds__(512, 2) void conv_wgrad_kernel(Params p) {
+  constexpr int PG = 4 / OB, CH = PX / 16 / PG, NT = 5;   // CH: matrix depths per wavefront and stage
   constexpr int NLA = (NCHUNK + 7) / 8, NL = NP * (NLA + 1);
   constexpr int X_BYTES = NP * NCHUNK * 1024, Z_PLANE = OB * PX * 64, USED = X_BYTES + NP * Z_PLANE;
   constexpr int SUMS = NT * 16 * 64;                       // floats of a wavefront's sums
@@ -1194,7 +1205,8 @@ __global__ __launch_bounds__(512, 2) void conv_split_wgrad_kernel(Params p) {
     const int slot = (wave + 8 * l) * 16 + (lane >> 2);
     row[l] = slot / W2;
     const int x = slot - row[l] * W2 - 1;
-    col[l] = (unsigned)x < (unsigned)g.oW && wave + 8 * l < NCHUNK ? (x * g.C + c0 + (lane & 3) * 8) * 2 : -1;
+    col[l] = (unsigned)x < (unsigned)g.oW && wave + 8 * l < NCHUNK && c0 + (lane & 3) * 8 < g.C
+                 ? (x * g.C + c0 + (lane & 3) * 8) * 2 : -1;
   }
   unsigned zoff;
   {
@@ -1218,11 +1230,14 @@ __global__ __launch_bounds__(512, 2) void conv_split_wgrad_kernel(Params p) {
     shift[i] = (tap / 3 * W2 + tap % 3) * 64;
   }
 
-  f32x16 acc[NT], low[NT];
+  f32x16 acc[NT], low[NP == 3 ? NT : 1];                   // low: the small products of a split
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[t][e] = low[t][e] = 0.f;
+    for (int e = 0; e < 16; ++e) {
+      acc[t][e] = 0.f;
+      if constexpr (NP == 3) low[t][e] = 0.f;
+    }
 
   // What a stage needs in addresses is worked out under the products of the stages before it: the
   // offsets of its patch two stages ahead, its pixels' slots (of tap (0, 0)) one.
@@ -1230,13 +1245,13 @@ __global__ __launch_bounds__(512, 2) void conv_split_wgrad_kernel(Params p) {
   int xs[CH][2], zs[CH][2];
   auto slots_of = [&](int px0) {
     int b, y, x;
-    decode(px0, g, b, y, x);
+    decode_fast(px0, g, b, y, x);
     const int pr0 = b * H2 + y;
 #pragma unroll
     for (int cc = 0; cc < CH; ++cc)
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
-        decode(px0 + (pg + PG * cc) * 16 + kr + kk * 4, g, b, y, x);
+        decode_fast(px0 + (pg + PG * cc) * 16 + kr + kk * 4, g, b, y, x);
         xs[cc][kk] = ((b * H2 + y - pr0) * W2 + x) * 64 + colb;
       }
   };
@@ -1247,10 +1262,10 @@ __global__ __launch_bounds__(512, 2) void conv_split_wgrad_kernel(Params p) {
   const unsigned step = (unsigned)(p.ldA * 2) * PX;        // bytes of a stage's rows of the gradient
   patch_offsets(g, first * PX, images, row, col, off);
 #pragma unroll
-  for (int x = 0; x < NL; ++x) issue_wgrad<OB, PX, NCHUNK>(p, Ab, Bb, s0, sp, true, off, zoff, first * step, wave, x);
+  for (int x = 0; x < NL; ++x) issue_wgrad<NP, OB, PX, NCHUNK>(p, Ab, Bb, s0, sp, true, off, zoff, first * step, wave, x);
   patch_offsets(g, (first + 1) * PX, images, row, col, off);
 #pragma unroll
-  for (int x = 0; x < NL; ++x) issue_wgrad<OB, PX, NCHUNK>(p, Ab, Bb, s1, sp, 1 < n, off, zoff, (first + 1) * step, wave, x);
+  for (int x = 0; x < NL; ++x) issue_wgrad<NP, OB, PX, NCHUNK>(p, Ab, Bb, s1, sp, 1 < n, off, zoff, (first + 1) * step, wave, x);
   patch_offsets(g, (first + 2) * PX, images, row, col, off);
   slots_of(first * PX);
   constexpr int LPS = (NL + CH * (NT - 1) - 1) / (CH * (NT - 1));   // loads under a step's products
@@ -1281,16 +1296,18 @@ __global__ __launch_bounds__(512, 2) void conv_split_wgrad_kernel(Params p) {
 #pragma unroll
         for (int x = x0; x < x0 + LPS; ++x)
           if (x < NL)
-            issue_wgrad<OB, PX, NCHUNK>(p, Ab, Bb, fill, sp, st + 2 < n, off, zoff, (first + st + 2) * step, wave, x);
-      constexpr int xa[6] = {2, 0, 1, 1, 0, 0}, xb[6] = {0, 2, 1, 0, 1, 0};
+            issue_wgrad<NP, OB, PX, NCHUNK>(p, Ab, Bb, fill, sp, st + 2 < n, off, zoff, (first + st + 2) * step, wave, x);
       if (i < NT - 1 || tg == 0) {
+        if constexpr (NP == 3) {
+          constexpr int xa[5] = {2, 0, 1, 1, 0}, xb[5] = {0, 2, 1, 0, 1};
 #pragma unroll
-        for (int q = 0; q < 6; ++q) {
-          f32x16& to = q < 5 ? low[i] : acc[i];
-          to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb[t & 1][xb[q]]),
-                                                       __builtin_bit_cast(bf16x8, fa[cc & 1][xa[q]]), to, 0, 0, 0);
+          for (int q = 0; q < 5; ++q)
+            low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb[t & 1][xb[q]]),
+                                                             __builtin_bit_cast(bf16x8, fa[cc & 1][xa[q]]), low[i], 0, 0, 0);
         }
-        if (i < NT - 1) Interleave<0x120, 2 * NP + LPS, 6, 0>::run();
+        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb[t & 1][0]),
+                                                         __builtin_bit_cast(bf16x8, fa[cc & 1][0]), acc[i], 0, 0, 0);
+        if (i < NT - 1) Interleave<0x120, 2 * NP + LPS, NP == 3 ? 6 : 1, 0>::run();
       }
     }
   };
@@ -1318,9 +1335,10 @@ __global__ __launch_bounds__(512, 2) void conv_split_wgrad_kernel(Params p) {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
+  if constexpr (NP == 3) {
 #pragma unroll
-  for (int t = 0; t < NT; ++t)
-    join_sums(acc[t], low[t]);
+    for (int t = 0; t < NT; ++t) join_sums(acc[t], low[t]);
+  }
   // the sums of pixel groups half.. to those of groups 0..half - 1
 #pragma unroll
   for (int half = PG / 2; half >= 1; half /= 2) {
@@ -1349,9 +1367,9 @@ __global__ __launch_bounds__(512, 2) void conv_split_wgrad_kernel(Params p) {
       if (tg * NT + t >= 9) continue;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int c = (tg * NT + t) * g.C + c0 + q * 8 + (lane >> 5) * 4;
+        const int c = c0 + q * 8 + (lane >> 5) * 4;
         f32x4 v = {acc[t][q * 4], acc[t][q * 4 + 1], acc[t][q * 4 + 2], acc[t][q * 4 + 3]};
-        *reinterpret_cast<f32x4*>(C + c) = v;
+        if (c < g.C) *reinterpret_cast<f32x4*>(C + (tg * NT + t) * g.C + c) = v;
       }
     }
   }
@@ -1384,8 +1402,10 @@ template __global__ void conv_split_patch_kernel<2, 2, 11>(Params);
 template __global__ void conv_split_patch_kernel<1, 2, 10>(Params);
 template __global__ void conv_split_patch_kernel<2, 1, 11>(Params);
 template __global__ void conv_split_patch_kernel<1, 1, 10>(Params);
-template __global__ void conv_split_wgrad_kernel<2, 64, 9>(Params);
-template __global__ void conv_split_wgrad_kernel<1, 64, 9>(Params);
+template __global__ void conv_wgrad_kernel<3, 2, 64, 9>(Params);
+template __global__ void conv_wgrad_kernel<3, 1, 64, 9>(Params);
+template __global__ void conv_wgrad_kernel<1, 2, 64, 9>(Params);
+template __global__ void conv_wgrad_kernel<1, 1, 64, 9>(Params);
 
 // ---- planes --------------------------------------------------------------------------------------
 // dst planes of n values (a multiple of 4), 4 to a thread.  Bound by its (4 + 2 NP) bytes a value.
@@ -1520,13 +1540,15 @@ int run_weight_grad(Params& p, const Tile& t, int np, hipStream_t s) {
   return run<3, kWeightGrad, 32, 128, 1, 2, 2>(p, s);
 }
 
-enum PatchKind { kNoPatch = 0, kPatch22, kPatch26, kSplitPatch256, kSplitPatch128, kSplitNarrow256, kSplitNarrow128, kSplitWgrad64, kSplitWgrad32 };
-int run_patch(Params& p, int kind, hipStream_t s) {
-  if (kind == kSplitWgrad64 || kind == kSplitWgrad32) {
-    tiled(p, kind == kSplitWgrad64 ? 64 : 32, 9 * 32);       // N = 9 C, C a multiple of 32
+enum PatchKind { kNoPatch = 0, kPatch22, kPatch26, kSplitPatch256, kSplitPatch128, kSplitNarrow256, kSplitNarrow128, kWgrad64, kWgrad32 };
+int run_patch(Params& p, int kind, int np, hipStream_t s) {
+  if (kind == kWgrad64 || kind == kWgrad32) {
+    tiled(p, kind == kWgrad64 ? 64 : 32, 9 * 32);            // N = 9 C: a column of tiles per 32 channels
     const unsigned grid = (unsigned)p.chunks * 8;
-    if (kind == kSplitWgrad64) conv_split_wgrad_kernel<2, 64, 9><<<grid, 512, 0, s>>>(p);
-    else conv_split_wgrad_kernel<1, 64, 9><<<grid, 512, 0, s>>>(p);
+    if (np == 1 && kind == kWgrad64) conv_wgrad_kernel<1, 2, 64, 9><<<grid, 512, 0, s>>>(p);
+    else if (np == 1) conv_wgrad_kernel<1, 1, 64, 9><<<grid, 512, 0, s>>>(p);
+    else if (kind == kWgrad64) conv_wgrad_kernel<3, 2, 64, 9><<<grid, 512, 0, s>>>(p);
+    else conv_wgrad_kernel<3, 1, 64, 9><<<grid, 512, 0, s>>>(p);
     return 0;                                                // partial sums only
   }
   const int slots = tiled(p, kind == kSplitPatch128 || kind == kSplitNarrow128 ? 128 : 256,
@@ -1564,6 +1586,12 @@ int patch_slots(int bm, int H, int W) {
   return (rows + 2 + 2 * inside) * (W + 2);
 }
 
+// Whether decode_fast finds the pixels of a weight gradient, and of the stages that its loads reach past the end.
+bool wgrad_decodes(const ConvGemmDesc& d) {
+  const long long px = (long long)d.Kd + 1024, side = std::max(d.image.oW, d.image.oH + 2);
+  return d.image.oW >= 2 && d.image.oH >= 2 && 2 * px * side < (1ll << 32);     // (rimmed rows: at most twice the pixels)
+}
+
 ConvPlan conv_plan(const ConvGemmDesc& d) {
   ConvPlan pl{{128, 128}, 0, 1, 0, 0, 0};
   auto count = [&](int bm, int bn) { return (long long)((d.M + bm - 1) / bm) * ((d.N + bn - 1) / bn) * d.batch; };
@@ -1592,10 +1620,10 @@ ConvPlan conv_plan(const ConvGemmDesc& d) {
   // Weight gradients: the patch kernel always leaves partial sums.  Its workgroups have a compute unit to
   // themselves and equal work, so the contraction is cut for one, two or four full rounds of 256,
   // the first that keeps 93 % of the units busy.
-  if (d.wgrad && d.np == 3 && im.nu == 3 && im.nv == 3 && im.st == 1 && im.C % 32 == 0) {
+  if (d.wgrad && im.nu == 3 && im.nv == 3 && im.st == 1 && wgrad_decodes(d)) {
     const bool wide = d.M > 32;
     const int px = 64;
-    const long long tiles = (long long)((d.M + (wide ? 63 : 31)) / (wide ? 64 : 32)) * (im.C / 32) * d.batch;
+    const long long tiles = (long long)((d.M + (wide ? 63 : 31)) / (wide ? 64 : 32)) * ((im.C + 31) / 32) * d.batch;
     const int stages = (d.Kd + px - 1) / px;
     long long pieces = 0;
     for (int r = 1; r <= 4; r *= 2) {
@@ -1605,7 +1633,7 @@ ConvPlan conv_plan(const ConvGemmDesc& d) {
     if (pieces > 64) pieces = 64;
     if (pieces > stages / 4) pieces = stages / 4;
     if (patch_slots(px, im.oH, im.oW) <= 9 * 16 && pieces >= 2) {
-      pl.patch = wide ? kSplitWgrad64 : kSplitWgrad32;
+      pl.patch = wide ? kWgrad64 : kWgrad32;
       pl.steps = (int)((stages + pieces - 1) / pieces);
       pl.splits = (stages + pl.steps - 1) / pl.steps;
       pl.ldP = d.N;
@@ -1676,7 +1704,8 @@ int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots) {
   p.C = d.C; p.strideC = d.strideC; p.ldC = d.ldC;
   p.M = d.M; p.N = d.N; p.Kd = d.Kd; p.batch = d.batch;
   p.g = Geometry{im.C, im.oH, im.oW, im.sH, im.sW, im.st, im.nu, im.nv, im.du0, im.dv0,
-                 (unsigned)((1ull << 32) / (unsigned)im.C + 1)};
+                 (unsigned)((1ull << 32) / (unsigned)im.C + 1), (unsigned)((1ull << 32) / (unsigned)im.oW + 1),
+                 (unsigned)((1ull << 32) / (unsigned)im.oH + 1), (unsigned)((1ull << 32) / (unsigned)(im.oH + 2) + 1)};
   p.epilogue = d.epilogue;
   p.out_step = d.out_step;
   p.bias = d.bias; p.strideBias = d.strideBias;
@@ -1691,7 +1720,7 @@ int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots) {
     p.partial = d.splitk_ws; p.ldP = pl.ldP;
     p.stridePartial = (long long)d.batch * d.M * pl.ldP;
   }
-  int slots = pl.patch ? run_patch(p, pl.patch, s)
+  int slots = pl.patch ? run_patch(p, pl.patch, d.np, s)
               : d.wgrad ? run_weight_grad(p, pl.tile, d.np, s)
               : scalar_tap ? run_forward<kForward>(p, pl.tile, d.np, s) : run_forward<kForwardAnyC>(p, pl.tile, d.np, s);
   if (p.ksplit > 1) {

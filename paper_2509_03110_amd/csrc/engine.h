@@ -201,6 +201,7 @@ struct GemmDesc {
   const struct AscentFusion* ascend;
   // If set (same kind of launch, `sumsq` given): only the sums of squares are written.
   int sumsq_only;
+  const float* add; int64_t strideAdd; int ldAdd;   // launch_splitk_reduce only: ConvGemmDesc::add
   // If set (fp32 operands, EPI_BIAS_RELU): a split contraction is left in pieces, described here.
   SplitResult* parts;
 };
@@ -281,6 +282,9 @@ struct ConvGemmDesc {
   const float* mask; int64_t strideMask; int ldMask;
   float* splitk_ws; size_t splitk_bytes;
   double* sumsq; int64_t sumsq_stride;
+  // If set: [M][ldAdd] of every replica, added to the results behind the bias and in front of ReLU or mask (with
+  // out_step 2 its pixels are those of even row and column, [oH][oW]).  Not for weight gradients.
+  const float* add = nullptr; int64_t strideAdd = 0; int ldAdd = 0;
   // 2: the input gradient of a stride-2 convolution.  The image is the output gradient [oH][oW], C and
   // the mask are images of [2 oH][2 oW].  An input pixel meets the taps of its row's and its
   // column's parity only: four classes of pixels, each a convolution of 1, 2, 2 or 4 taps whose filters

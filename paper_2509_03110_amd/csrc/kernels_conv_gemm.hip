@@ -66,6 +66,7 @@ struct Params {
   double* sumsq; long long strideSumsq;
   int out_step, out_i, out_j;                          // see ConvGemmDesc
   int ksplit, steps_per_piece; float* partial; long long stridePartial; int ldP;
+  const float* add; long long strideAdd; int ldAdd;        // added to the results (may be null)
 };
 
 constexpr int waitcnt(int vm, int lgkm) {
@@ -407,10 +408,14 @@ __device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[
   const bool relu = !split_mode && p.epilogue == EPI_BIAS_RELU;
   const bool masked = !split_mode && p.epilogue == EPI_MASK;
   const float* mask = masked ? p.mask + (long long)bat * p.strideMask : nullptr;
+  // (of a stride-2 input gradient, the class of even rows and columns)
+  const bool adds = !split_mode && p.add != nullptr && p.out_i == 0 && p.out_j == 0;
+  const float* add = adds ? p.add + (long long)bat * p.strideAdd : nullptr;
   constexpr int PITCH = TN * 32 + 4;
   constexpr int LANES_PER_ROW = TN * 8;
   constexpr int ROWS_PER_PASS = 64 / LANES_PER_ROW;
   constexpr int PASSES = (32 + ROWS_PER_PASS - 1) / ROWS_PER_PASS;
+  constexpr int GRP = PASSES < 4 ? PASSES : 4;
   const int c4 = (lane % LANES_PER_ROW) * 4;
   const int rsub = lane / LANES_PER_ROW;
   const int n = n0 + c4;
@@ -432,30 +437,41 @@ __device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[
         for (int r = 0; r < 4; ++r) v[r] = acc[i][j][q * 4 + r];
         *reinterpret_cast<f32x4*>(stage + l32 * PITCH + j * 32 + q * 8 + h * 4) = v;
       }
-#pragma unroll 4
-    for (int pass = 0; pass < PASSES; ++pass) {
-      const int rr = pass * ROWS_PER_PASS + rsub;
-      const int m = m0 + i * 32 + rr;
-      if (rr < 32 && rsub < ROWS_PER_PASS && m < p.M && n < p.N) {       // N is a multiple of 4
-        f32x4 v = *reinterpret_cast<const f32x4*>(stage + rr * PITCH + c4);
-        v += bv;
-        int row = m;
+    // What the results meet in memory (addend, mask) is requested for GRP passes at a time: a load after a
+    // pass's stores is waited for together with them.
+#pragma unroll
+    for (int p0 = 0; p0 < PASSES; p0 += GRP) {
+      f32x4 mk[GRP], ad[GRP];
+      int row[GRP];
+#pragma unroll
+      for (int u = 0; u < GRP; ++u) {
+        const int rr = (p0 + u) * ROWS_PER_PASS + rsub, m = m0 + i * 32 + rr;
+        row[u] = p0 + u < PASSES && rr < 32 && rsub < ROWS_PER_PASS && m < p.M && n < p.N ? m : -1;    // N is a multiple of 4
+        if (row[u] < 0) continue;
+        if (adds) ad[u] = *reinterpret_cast<const f32x4*>(add + (long long)m * p.ldAdd + n);
         if (p.out_step > 1) {
           int b, oi, oj;
           decode(m, p.g, b, oi, oj);
-          row = ((b * p.g.oH + oi) * 2 + p.out_i) * (2 * p.g.oW) + 2 * oj + p.out_j;
+          row[u] = ((b * p.g.oH + oi) * 2 + p.out_i) * (2 * p.g.oW) + 2 * oj + p.out_j;
         }
+        if (masked) mk[u] = *reinterpret_cast<const f32x4*>(mask + (long long)row[u] * p.ldMask + n);
+      }
+#pragma unroll
+      for (int u = 0; u < GRP; ++u) {
+        if (row[u] < 0) continue;
+        f32x4 v = *reinterpret_cast<const f32x4*>(stage + ((p0 + u) * ROWS_PER_PASS + rsub) * PITCH + c4);
+        v += bv;
+        if (adds) v += ad[u];
         if (relu) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) v[r] = v[r] > 0.f ? v[r] : 0.f;
         }
         if (masked) {
-          const f32x4 mk = *reinterpret_cast<const f32x4*>(mask + (long long)row * p.ldMask + n);
 #pragma unroll
           for (int r = 0; r < 4; ++r)
-            if (!(mk[r] > 0.f)) v[r] = 0.f;
+            if (!(mk[u][r] > 0.f)) v[r] = 0.f;
         }
-        *reinterpret_cast<f32x4*>(C + (long long)row * ldC + n) = v;
+        *reinterpret_cast<f32x4*>(C + (long long)row[u] * ldC + n) = v;
         ssq += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
       }
     }
@@ -1691,6 +1707,7 @@ int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots) {
       (d.other_plane % 8) || ((uintptr_t)d.C & 15))
     return -1;
   if (d.epilogue == EPI_MASK && (d.ldMask % 4 || d.strideMask % 4 || ((uintptr_t)d.mask & 15))) return -1;
+  if (d.add && (d.wgrad || d.ldAdd % 4 || d.strideAdd % 4 || ((uintptr_t)d.add & 15))) return -1;
   if ((d.epilogue == EPI_BIAS || d.epilogue == EPI_BIAS_RELU) && (((uintptr_t)d.bias & 15) || d.strideBias % 4)) return -1;
   Params p{};
   const unsigned image_bytes = (unsigned)(img_elems * 2), other_bytes = (unsigned)(rows * d.ld * 2);
@@ -1710,6 +1727,7 @@ int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots) {
   p.out_step = d.out_step;
   p.bias = d.bias; p.strideBias = d.strideBias;
   p.mask = d.mask; p.strideMask = d.strideMask; p.ldMask = d.ldMask;
+  p.add = d.add; p.strideAdd = d.strideAdd; p.ldAdd = d.ldAdd;
   p.sumsq = d.sumsq; p.strideSumsq = d.sumsq_stride;
   ConvPlan pl = conv_plan(d);
   const bool room = d.splitk_ws != nullptr && d.splitk_bytes >= pl.ws_bytes && ((uintptr_t)d.splitk_ws & 15) == 0;
@@ -1728,6 +1746,7 @@ int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots) {
     r.C = d.C; r.strideC = d.strideC; r.ldC = d.ldC; r.M = d.M; r.N = d.N; r.batch = d.batch;
     r.epilogue = d.epilogue; r.bias = d.bias; r.strideBias = d.strideBias;
     r.mask = d.mask; r.strideMask = d.strideMask; r.ldMask = d.ldMask;
+    r.add = d.add; r.strideAdd = d.strideAdd; r.ldAdd = d.ldAdd;
     r.sumsq = d.sumsq; r.sumsq_stride = d.sumsq_stride;
     slots = launch_splitk_reduce(r, p.partial, p.ksplit, p.stridePartial, p.ldP, s);
   }

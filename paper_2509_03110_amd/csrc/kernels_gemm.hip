@@ -62,6 +62,7 @@ struct GemmParams {
   float* partial; long long strideSplit; int ldP;
   int splits, steps_per_split;
   int unreduced;            // the partial sums are left to the caller
+  const float* add; long long strideAdd; int ldAdd;    // the reduce adds it to the results (may be null)
   // optional sum of squares of the stored results, one slot per workgroup that stores them
   double* sumsq; long long strideSumsq;
 };
@@ -809,6 +810,7 @@ __global__ __launch_bounds__(kThreads * LANES) void splitk_reduce_kernel(GemmPar
         if (p.bias_dir) bv = bv + p.bias_scale[bat] * p.bias_dir[(long long)bat * p.strideBias + n];
         o += bv;
       }
+      if (p.add) o += p.add[(long long)bat * p.strideAdd + (long long)m * p.ldAdd + n];
       if (p.epilogue == EPI_BIAS_RELU) o = o > 0.f ? o : 0.f;
       if (p.epilogue == EPI_MASK && !(mask[n] > 0.f)) o = 0.f;
       C[n] = o;
@@ -996,6 +998,7 @@ int launch_splitk_reduce(const GemmDesc& d, const float* partial, int splits, in
   p.epilogue = d.epilogue;
   p.bias = d.bias; p.strideBias = d.strideBias;
   p.mask = (const char*)d.mask; p.strideMask = d.strideMask; p.ldMask = d.ldMask;
+  p.add = d.add; p.strideAdd = d.strideAdd; p.ldAdd = d.ldAdd;
   p.partial = const_cast<float*>(partial); p.strideSplit = split_stride; p.ldP = ldP; p.splits = splits;
   p.sumsq = d.sumsq; p.strideSumsq = d.sumsq_stride;
   return reduce_splits(p, s);
@@ -1061,6 +1064,7 @@ int launch_gemm(const GemmDesc& d, hipStream_t s, int* sumsq_slots) {
     p.strideSplit = (long long)d.batch * d.M * pl.ldP;
   }
   p.unreduced = 0;
+  p.add = nullptr; p.strideAdd = 0; p.ldAdd = 0;
   // (left to the next kernel while a row of its input has few pieces to add up: 5 of 128 columns, 4.2 us
   // of a reduce against 1.6 more there; 4 of 1024 even; 16 of 512, 6 us against 18)
   if (d.parts) {

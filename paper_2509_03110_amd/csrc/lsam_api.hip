@@ -850,6 +850,17 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
                            (int64_t)lo.K * cv.rows * cv.ldc, cv.ldc, lo.K, lo.B, cv.H, cv.W, cv.Cin, cv.stride, s) != 0)
         return fail(LSAM_EINVAL, "unfold of convolution %d rejected", l);
     }
+    if (cv.proj && cv.fast) {
+      // projection shortcut: the block input's pixels (every second one if the block halved
+      // the image) through a 1x1 convolution
+      LaunchTimer t(c, KC_GEMM_FWD);
+      ConvGemmDesc d = plane_desc(c, projection_image(c, lo.conv[l - 1], cv), 0, cv.pwf, (int)cv.rows, cv.Cout, ly.proj_in);
+      d.C = c->at<float>(cv.pz); d.strideC = cv.rows * cv.Cout; d.ldC = cv.Cout;
+      d.epilogue = EPI_BIAS;
+      d.bias = params + ly.pb_off; d.strideBias = lo.d_pad;
+      if (launch_conv_gemm(d, s) != 0)
+        return fail(LSAM_EINVAL, "projection of convolution %d rejected", l);
+    }
     if (!cv.first && cv.fast) {
       // filters of ldw columns: 9 C_in, and zeros up to the unfolded image's pitch where that is stored
       LaunchTimer t(c, KC_GEMM_FWD);
@@ -858,6 +869,10 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
       d.C = c->at<float>(cv.bn ? cv.z : cv.out); d.strideC = cv.rows * cv.Cout; d.ldC = cv.Cout;
       d.epilogue = cv.bn ? EPI_BIAS : EPI_BIAS_RELU;
       d.bias = params + ly.b_off; d.strideBias = lo.d_pad;
+      if (cv.skip && lo.preact) {
+        // a pre-activation block's sum: the bare projection, or the sum two convolutions below
+        d.add = c->at<float>(cv.proj ? cv.pz : lo.conv[l - 2].z); d.strideAdd = cv.rows * cv.Cout; d.ldAdd = cv.Cout;
+      }
       if (launch_conv_gemm(d, s) != 0)
         return fail(LSAM_EINVAL, "forward product of convolution %d rejected", l);
     } else if (!cv.first) {
@@ -877,17 +892,7 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
       if (launch_gemm(d, s) != 0) return fail(LSAM_EINVAL, "forward GEMM of convolution %d rejected", l);
     }
     if (cv.proj) {
-      // projection shortcut: the block input's pixels (every second one if the block halved
-      // the image) through a 1x1 convolution, then that output's own statistics
-      if (cv.fast) {
-        LaunchTimer t(c, KC_GEMM_FWD);
-        ConvGemmDesc d = plane_desc(c, projection_image(c, lo.conv[l - 1], cv), 0, cv.pwf, (int)cv.rows, cv.Cout, ly.proj_in);
-        d.C = c->at<float>(cv.pz); d.strideC = cv.rows * cv.Cout; d.ldC = cv.Cout;
-        d.epilogue = EPI_BIAS;
-        d.bias = params + ly.pb_off; d.strideBias = lo.d_pad;
-        if (launch_conv_gemm(d, s) != 0)
-          return fail(LSAM_EINVAL, "projection of convolution %d rejected", l);
-      } else {
+      if (!cv.fast) {
         const ConvLayer& src = lo.conv[l - 2];
         const float* sub = c->at<float>(src.out);
         if (cv.skip_step == 2) {
@@ -909,7 +914,9 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
           if (launch_gemm(d, s) != 0) return fail(LSAM_EINVAL, "projection of convolution %d rejected", l);
         }
       }
-      if (lo.preact) {
+      if (lo.preact && cv.fast) {
+        // (the sum is taken where the convolution's product is written)
+      } else if (lo.preact) {
         // the bare projection joins the convolution's output in front of the normalisation
         LaunchTimer t(c, KC_POOL);
         if (launch_add_into(c->at<float>(cv.z), c->at<float>(cv.pz), (int64_t)lo.K * cv.rows * cv.Cout, s) != 0)
@@ -920,7 +927,7 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
                             cv.rows, cv.Cout, c->cfg.bn_eps, s) != 0)
           return fail(LSAM_EINVAL, "projection of convolution %d: statistics rejected", l);
       }
-    } else if (cv.skip && lo.preact) {
+    } else if (cv.skip && lo.preact && !cv.fast) {
       // identity shortcut of a pre-activation block: the sum two convolutions below
       LaunchTimer t(c, KC_POOL);
       if (launch_add_into(c->at<float>(cv.z), c->at<float>(lo.conv[l - 2].z), (int64_t)lo.K * cv.rows * cv.Cout,
@@ -1157,6 +1164,11 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
                                         lo.K, chunks, cv.Cout, ssq ? ssq + *slots : nullptr, lo.nblk, s);
       if (ssq) *slots += used;
     }
+    // If this convolution opened a residual block, the gradient of the block output (kept by the closing
+    // convolution) also reaches the block input through the shortcut: where the product of this one
+    // writes that gradient, or by a launch of its own
+    const bool opens = l + 1 < lo.n_conv && lo.conv[l + 1].skip && (lo.conv[l + 1].proj || !lo.preact);
+    bool shortcut_done = false;
     if (l > 0 && cv.direct_dx) {
       // dX as a convolution of the output gradient with the mirrored filters, written straight
       // into the gradient of the image this layer read (masked by the ReLU output it came
@@ -1176,6 +1188,13 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
         d.epilogue = below.pool ? EPI_PLAIN : EPI_MASK;
         if (!below.pool) {
           d.mask = c->at<float>(below.out); d.strideMask = image; d.ldMask = cv.Cin;
+        }
+        // (the product and the shortcut halve the image in the same step)
+        if (opens && !below.pool && lo.conv[l + 1].H == cv.H && lo.conv[l + 1].W == cv.W && lo.conv[l + 1].skip_step == cv.stride) {
+          const ConvLayer& top = lo.conv[l + 1];
+          d.ldAdd = top.proj ? top.skip_C : top.Cout;
+          d.add = c->at<float>(top.proj ? top.psub : top.dout); d.strideAdd = top.rows * d.ldAdd;
+          shortcut_done = true;
         }
         if (launch_conv_gemm(d, s) != 0)
           return fail(LSAM_EINVAL, "dX product of convolution %d rejected", l);
@@ -1230,9 +1249,7 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
                          cv.stride, s) != 0)
         return fail(LSAM_EINVAL, "fold of convolution %d rejected", l);
     }
-    if (l + 1 < lo.n_conv && lo.conv[l + 1].skip && (lo.conv[l + 1].proj || !lo.preact)) {
-      // this convolution opened a residual block: the gradient of the block output (kept by the
-      // closing convolution) also reaches the block input through the shortcut
+    if (opens && !shortcut_done) {
       const ConvLayer& top = lo.conv[l + 1];
       const ConvLayer& below = lo.conv[l - 1];
       const ShortcutDesc sc{nullptr, below.rows * top.skip_C, top.H, top.W, top.skip_C, top.skip_step};

@@ -1270,10 +1270,10 @@ bool head_is_fused(const Layout& lo) {
 }
 
 // Whether the norm of a layer's unsaved first-pass weight gradient comes from the Gram matrices
-// of its factors, half of each (launch_gram_norms), B^2 (out + in) flops: when they take at most
-// half those of the product itself.
+// of its factors, half of each (launch_gram_norms): B^2 (out + in) flops, when they take at most a
+// quarter of those of the product itself.
 bool gram_norm_pays(int B, int out, int in) {
-  return (int64_t)B * (out + in) <= (int64_t)out * in;
+  return 2 * (int64_t)B * (out + in) <= (int64_t)out * in;
 }
 
 // Whether the fused step and ascent of a bf16 dense model go through all layers in one launch: where

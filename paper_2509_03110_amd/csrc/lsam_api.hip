@@ -144,7 +144,7 @@ struct ConvLayer {
   int ldc;             // pitch of the unfolded image, 9 Cin rounded up to 8
   // Which products serve the layer.  `fast`: the bf16 matrix units on plane tensors
   // (kernels_conv_gemm.hip); otherwise the fp32-storage GEMM (small layers and, in fp32 arithmetic, channel
-  // counts other than 8, 16 and multiples of 32; plane_products_pay).
+  // counts that are no multiples of 8; plane_products_pay).
   // Both can read an unfolded image straight from the image: `direct_in` for the layer's input
   // (forward and dW), `direct_dx` for its output gradient (dX, with the mirrored filters, `wt` for
   // the fp32-storage GEMM).  Otherwise the unfolded image (`col`, planes if fast) resp. its gradient
@@ -327,17 +327,22 @@ size_t take(size_t& cursor, size_t bytes) {
 // at 9e6, 0.90 at 1.5e8, 0.74 at 2.4e9; 16 channels 0.93 at 2e7, 0.60 at 6e8; 64 channels 1.13 at
 // 7.5e7, 0.98 at 6e8; 128 channels 0.87 at 1.2e9 (fp32 arithmetic; with bf16 products 1.0, 0.94, 0.78;
 // 0.92, 0.59; 1.02, 0.90; 0.91).  One plane leaves little to gain on few, small images: 256 channels on
-// 2048 pixels 0.95 in fp32, 1.07 with bf16 products, which therefore want 4096.  Other channel counts
-// (multiples of 8, but neither 8, 16 nor multiples of 32) are taken with a stored unfolded image here, nine
-// times the image either way: with three planes that was slower at every size (24 channels: 1.06 to
-// 1.16), with one plane it pays from 3e8 (0.88).  The loaders could unfold them by address as well; that
-// has not been measured.
+// 2048 pixels 0.95 in fp32, 1.07 with bf16 products, which therefore want 4096.  Channel counts that are no
+// multiples of 32 have a stored unfolded image to save: from 2e7, and above 32 channels 1e8 on at least
+// 4096 pixels (two equal layers, fp32 / bf16 products: 16 channels at 9e6 0.94 to 1.03 / 0.95, at 2e7 0.95 /
+// 0.91; 24 at 2e7 0.95, 4e8 0.72, 2.7e9 0.40 / 0.42; 40 at 1.2e8 0.97, 2.4e8 0.84 / 0.90; 72 at 1.9e8 0.99, 3e9
+// 0.50; 152 at 2.3e10 0.46; but 104 channels at 1e8 on 1024 pixels 1.16).  Counts that are no multiples of 8
+// are taken with a stored unfolded image, nine times the image either way: with one plane that pays from 3e8.
 bool plane_products_pay(int np, int K, int64_t rows, int Cin, int Cout) {
-  auto fits = [](int C) { return C % 32 == 0 || C == 8 || C == 16; };
   const double macs = (double)K * (double)rows * 9.0 * Cin * Cout;
   if (np == 1 && K * rows < 4096) return false;
-  if (fits(Cin) && fits(Cout)) return macs >= (std::max(Cin, Cout) <= 32 ? 1e8 : 3e8);
-  return np == 1 && macs >= 3e8;
+  if (Cin % 8 || Cout % 8) return np == 1 && macs >= 3e8;
+  // (in fp32 arithmetic 24 channels beside a multiple of 32 stay with the fp32-storage GEMM, not because it is
+  // faster, but because callers are told so: lsam_layer_info's answers for such layers are held to it)
+  if (np == 3 && std::min(Cin, Cout) == 24 && std::max(Cin, Cout) % 32 == 0) return false;
+  const bool stored = Cin % 32 || Cout % 32;       // on the fp32-storage GEMM
+  if (std::max(Cin, Cout) <= 32) return macs >= (stored ? 2e7 : 1e8);
+  return macs >= (stored && K * rows >= 4096 ? 1e8 : 3e8);
 }
 
 void build_layout(const lsam_config& c, Layout& lo) {
@@ -498,7 +503,7 @@ void build_layout(const lsam_config& c, Layout& lo) {
       cv.fast = plane_products_pay(lo.np, lo.K, cv.rows, cv.Cin, cv.Cout);
       // unfolding by address: whole taps or parts of one tap make up a 32-deep k-step; the
       // fp32-storage GEMM knows stride 1 and parts of taps only
-      auto fits = [&](int C) { return C % 32 == 0 || (cv.fast && (C == 8 || C == 16)); };
+      auto fits = [&](int C) { return C % (cv.fast ? 8 : 32) == 0; };
       cv.direct_in = small && fits(cv.Cin) && (cv.fast || cv.stride == 1);
       // (stride 2: with three planes the classes lose against the product with a stored gradient where
       // their columns fill the 64-wide tiles badly: 160 channels, a step 0.35 ms slower of 27)

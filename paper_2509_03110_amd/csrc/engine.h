@@ -243,11 +243,11 @@ int gram_slots(int n, int K, int B);
 // stays in the caches.  0, or -1.
 int launch_fused_group(const DenseLayer* layers, int n, int K, int B, int64_t stride, const SamplerFusion* f,
                        const AscentFusion* a, hipStream_t s);
-// fp32: the weight and bias gradients of n layers and (may be null) of the narrow head, into g.  Returns the
+// fp32 (bf16_math: operands of the products rounded): the weight and bias gradients of n layers and (may be null) of the narrow head, into g.  Returns the
 // sum-of-squares slots written per replica (at most gemm_sumsq_capacity of every product, one per 64 biases,
 // head_sumsq_slots), or -1.
 int launch_dense_gradients(const DenseLayer* layers, int n, const DenseLayer* head, int K, int B, float* g, int64_t strideG,
-                           double* sumsq, int64_t sumsq_stride, hipStream_t s);
+                           double* sumsq, int64_t sumsq_stride, int bf16_math, hipStream_t s);
 // Column sums of every layer's dz into g; slots as launch_bias_grad's.  `step` (may be null): the biases
 // take their sampler step as well (pointers to the whole vectors, like g).
 int launch_bias_grads_blocked(const DenseLayer* layers, int n, int K, int B, float* g, int64_t strideG, double* sumsq,

@@ -723,7 +723,7 @@ struct DenseGrads {
   } it[LSAM_MAX_LAYERS];
   Item head;                                    // slot: of the head's partial sums
 };
-template <int BT, int OCC>
+template <int BT, int OCC, bool BF16MATH>
 __global__ __launch_bounds__(kThreads, OCC) void dense_gradients_kernel(GemmParams p, DenseGrads d) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int w = blockIdx.x;
@@ -760,7 +760,7 @@ __global__ __launch_bounds__(kThreads, OCC) void dense_gradients_kernel(GemmPara
   p.total = p.tilesM * p.tilesN * p.batch;
   p.chunks = (p.total + 7) / 8;
   p.sumsq = d.sumsq != nullptr ? d.sumsq + it.slot : nullptr;
-  gemm_tile<float, float, BT, BT, 8, false, false, 0, false>(p, w - it.first);
+  gemm_tile<float, float, BT, BT, 8, false, false, 0, BF16MATH>(p, w - it.first);
 }
 
 // Sums the split-K partials in a fixed order and applies the epilogue the GEMM skipped.
@@ -1075,13 +1075,13 @@ int launch_gemm(const GemmDesc& d, hipStream_t s, int* sumsq_slots) {
 }
 
 int launch_dense_gradients(const DenseLayer* layers, int n, const DenseLayer* head, int K, int B, float* g, int64_t strideG,
-                           double* sumsq, int64_t sumsq_stride, hipStream_t s) {
+                           double* sumsq, int64_t sumsq_stride, int bf16_math, hipStream_t s) {
   if (n < 0 || n > LSAM_MAX_LAYERS || (n == 0 && !head) || (strideG % 4) || ((uintptr_t)g & 15)) return -1;
   // 128x128 tiles where they give every compute unit one, as for a product of its own
   long long large = 0;
   for (int i = 0; i < n; ++i)
     large += layers[i].out >= 128 && layers[i].in >= 128 ? (long long)((layers[i].out + 127) / 128) * ((layers[i].in + 127) / 128) * K : 0;
-  const int tile = large >= 256 ? 128 : 64;
+  const int tile = large >= (bf16_math ? 192 : 256) ? 128 : 64;
   DenseGrads d{};
   GemmParams p{};
   d.n = n; d.B = B; d.K = K;
@@ -1111,7 +1111,8 @@ int launch_dense_gradients(const DenseLayer* layers, int n, const DenseLayer* he
     slots += tiles;
     bias_blocks += (q.out + 63) / 64;
     if (blocks >= (1ll << 30)) return -1;
-    lds = std::max<size_t>({lds, (size_t)2 * 8 * (2 * (tile + 1)) * 16, (size_t)64 * (tile + 4) * 4});
+    lds = std::max<size_t>({lds, bf16_math ? (size_t)2 * 8 * (2 * (tile + 2)) * 8 : (size_t)2 * 8 * (2 * (tile + 1)) * 16,
+                            (size_t)64 * (tile + 4) * 4});
   }
   d.head_first = (int)blocks;
   if (head) {
@@ -1134,7 +1135,8 @@ int launch_dense_gradients(const DenseLayer* layers, int n, const DenseLayer* he
     kern<<<(unsigned)blocks, kThreads, lds, s>>>(p, d);
     return slots + bias_blocks;
   };
-  return tile == 128 ? go(dense_gradients_kernel<128, 2>) : go(dense_gradients_kernel<64, 2>);
+  if (bf16_math) return tile == 128 ? go(dense_gradients_kernel<128, 2, true>) : go(dense_gradients_kernel<64, 2, true>);
+  return tile == 128 ? go(dense_gradients_kernel<128, 2, false>) : go(dense_gradients_kernel<64, 2, false>);
 }
 
 }  // namespace lsam

@@ -1382,7 +1382,7 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
   int grams = 0;
   dense_layers(c, A0, dense);
   // fp32: all weight and bias gradients share a launch once the dZ are there
-  const bool grouped = !bf && !lo.bf16_math;
+  const bool grouped = !bf;
   for (int l = L - 1; l >= l0; --l) {
     const Layer& ly = lo.layers[l];
     const char* dz = c->at<char>(lo.dz[l + 1]);
@@ -1425,12 +1425,6 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
       if (ssq) slots += used;
       return LSAM_OK;
     };
-    auto bias_grad = [&]() {
-      LaunchTimer t(c, KC_BIAS_GRAD);
-      const int used = launch_bias_grad(reinterpret_cast<const float*>(dz), ld_dz, g + ly.b_off, lo.d_pad, K, B, ly.out,
-                                        ssq ? ssq + slots : nullptr, lo.nblk, s);
-      if (ssq) slots += used;
-    };
     auto input_grad = [&]() -> int {
       GemmDesc d{};
       d.b32s = bf;
@@ -1451,7 +1445,6 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
     // the input gradient still has to read, so that one goes first.
     if (fuse && want_dx && (rc = input_grad()) != LSAM_OK) return rc;
     if (!grouped && (rc = weight_grad()) != LSAM_OK) return rc;
-    if (!bf && !grouped) bias_grad();
     if (!fuse && want_dx && (rc = input_grad()) != LSAM_OK) return rc;
   }
   if (grouped) {
@@ -1460,7 +1453,7 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
     if (ssq && most > lo.nblk) return fail(LSAM_ESTATE, "gradient-norm partials would overrun their buffer at the dense layers");
     LaunchTimer t(c, KC_GEMM_DW);
     const int used = launch_dense_gradients(dense + l0, (head ? L - 1 : L) - l0, head ? dense + L - 1 : nullptr, K, B, g,
-                                            lo.d_pad, ssq, lo.nblk, s);
+                                            lo.d_pad, ssq, lo.nblk, lo.bf16_math, s);
     if (used < 0) return fail(LSAM_EINVAL, "weight gradients of the dense layers rejected");
     if (ssq) slots += used;
   }

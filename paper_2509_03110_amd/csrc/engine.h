@@ -355,19 +355,19 @@ int launch_unfold3x3(const float* X, int64_t strideX, void* col, int np, int64_t
 // set to zero where mask (same shape as dX, may be null) is not positive.  C % 4 == 0.
 int launch_fold3x3(const float* dcol, int64_t strideCol, int ld, float* dX, const float* mask,
                    int64_t strideX, int K, int B, int H, int W, int C, int stride, hipStream_t s);
-// A first convolution layer with C = 1..3 input channels and a multiple of 32 output channels
+// A first convolution layer with C = 1..3 input channels and a multiple of 8 output channels up to 256
 // (first_conv_fits) has kernels of its own that gather the image straight into the MFMA
 // operands.  Forward: out[k][p][o] = b[o] + conv, rectified if `relu`, parameters taken from
 // params + k * strideParams at w_off (row pitch ldw) and b_off.  Weight gradient: dW and db
 // into grad + k * strideParams at the same offsets, through `partial`
-// ([K][first_conv_chunks(rows)][Cout][32] floats of scratch), plus, if sumsq is non-null, the
+// ([K][first_conv_chunks(rows, Cout, K)][Cout][32] floats of scratch), plus, if sumsq is non-null, the
 // sums of their squares in sumsq[k * sumsq_stride + slot]; returns the slots written per
 // replica (Cout / 2), or -1.  `round`: both operands of every product are rounded to bfloat16
 // first.  `skip_bias`: the weight-gradient kernels leave db alone (with rounded operands they
 // would sum rounded values, the caller then takes the column sums of dout instead; below a
 // batch normalisation the bias gradient is zero).
-bool first_conv_fits(int C, int Cout, int64_t rows);
-int first_conv_chunks(int64_t rows);
+bool first_conv_fits(int C, int Cout, int64_t rows, int K, int round);
+int first_conv_chunks(int64_t rows, int Cout, int K);
 int launch_first_conv_forward(const float* X, const float* params, int64_t strideParams, int64_t w_off,
                               int64_t b_off, int ldw, float* out, int relu, int round, int K,
                               int64_t rows, int H, int W, int C, int Cout, hipStream_t s);

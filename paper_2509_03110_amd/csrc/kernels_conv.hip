@@ -333,19 +333,20 @@ __global__ __launch_bounds__(kThreads) void first_conv_forward_kernel(const floa
                                                                       const float* __restrict__ params,
                                                                       long long w_off, long long b_off,
                                                                       float* __restrict__ out,
-                                                                      FirstConv f, int relu, int round) {
+                                                                      FirstConv f, int group, int relu, int round) {
   constexpr int KS = (9 * C + 1) / 2;          // MFMA steps of depth 2
   constexpr int WP = 33;                       // LDS pitch of a filter: lanes o, o+1 on different banks
-  extern __shared__ float wl[];                // [Cout][WP]: the filters, zero for t >= 9 C
+  extern __shared__ float wl[];                // [group][WP]: the filters, zero for t >= 9 C
+  const int o0 = blockIdx.z * group;           // this workgroup's channels: `group`, a multiple of 32
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l32 = lane & 31, h = lane >> 5;
   const int k = blockIdx.y;
   {
     // rows of 32 floats (lanes along t: whole 128-byte lines of the filter bank)
     const float* Wg = params + (long long)k * f.strideParams + w_off;
-    for (int e = threadIdx.x; e < f.Cout * 32; e += kThreads) {
+    for (int e = threadIdx.x; e < group * 32; e += kThreads) {
       const int o = e >> 5, t = e & 31;
-      const float wv = t < 9 * C ? Wg[(long long)o * f.ldw + t] : 0.f;
+      const float wv = t < 9 * C && o0 + o < f.Cout ? Wg[(long long)(o0 + o) * f.ldw + t] : 0.f;
       wl[o * WP + t] = round ? to_bf16(wv) : wv;
     }
   }
@@ -365,62 +366,70 @@ __global__ __launch_bounds__(kThreads) void first_conv_forward_kernel(const floa
   // acc[e] of lane (l32, h): output channel ob + l32 of pixel tile*32 + (e/4)*8 + h*4 + e%4, so
   // that a store instruction writes two whole 128-byte rows
   const int tile0 = (blockIdx.x * 4 + wave) * 32;
-  for (int ob = 0; ob < f.Cout; ob += 32) {
+  for (int ob = o0; ob < o0 + group && ob < f.Cout; ob += 32) {
     f32x16 acc;
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] = 0.f;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      const float w = wl[(ob + l32) * WP + 2 * s + h];
+      const float w = wl[(ob - o0 + l32) * WP + 2 * s + h];
       acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[s], w, acc, 0, 0, 0);
     }
-    const float bv = bias[ob + l32];
+    const bool mine = ob + l32 < f.Cout;         // (the last block of 32 channels need not be full)
+    const float bv = mine ? bias[ob + l32] : 0.f;
     float* dst = out + ((long long)k * f.rows + tile0) * f.Cout + ob + l32;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const int pp = (e / 4) * 8 + h * 4 + e % 4;
       const float z = acc[e] + bv;
-      if (tile0 + pp < f.rows) dst[(long long)pp * f.Cout] = (relu && !(z > 0.f)) ? 0.f : z;
+      if (mine && tile0 + pp < f.rows) dst[(long long)pp * f.Cout] = (relu && !(z > 0.f)) ? 0.f : z;
     }
   }
 }
 
-// Weight and bias gradient, first stage: workgroup (chunk, k) covers kFirstChunk pixels, 128 per
+// Weight and bias gradient, first stage: workgroup (chunk, k) covers `chunk_px` pixels, a quarter per
 // wavefront; partial[k][chunk][o][t] = sum over its pixels of dout[p][o] unfolded(p, t), with
 // t = 9 C standing for the constant 1 (that column is the bias gradient).  The four
 // wavefronts' sums are added in wave order through LDS.  What bounds it is the work per pixel in
 // front of the matrix instruction (its row and column, the gather of its 27 neighbours), so two
 // blocks of 32 output channels share it where there are two: 64 channels at 32 x 32, 4 replicas of 128,
-// 87 us with one at a time, 57 with two.
-constexpr int kFirstChunk = 512;
+// 87 us with one at a time, 57 with two.  Few pixels leave it a chain of latencies: with 512 pixels a workgroup
+// a step of one 64-channel layer on 4096 pixels took 175 us, with 64 it takes 121.
+// (A workgroup takes 64 to 512 pixels, as few as give the launch a thousand workgroups, and 32 OB channels:
+// blockIdx.z.)
 template <int C, int OB>
 __global__ __launch_bounds__(kThreads) void first_conv_wgrad_kernel(const float* __restrict__ X,
                                                                     const float* __restrict__ dout,
                                                                     float* __restrict__ partial,
-                                                                    int chunks, FirstConv f, int round) {
+                                                                    int chunks, int chunk_px, FirstConv f, int round) {
   __shared__ float red[3][32 * 32];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l32 = lane & 31, h = lane >> 5;
   const int k = blockIdx.y;
   const float* img = X + (long long)k * f.rows * C;
   const float* dz = dout + (long long)k * f.rows * f.Cout;
-  const int p0 = blockIdx.x * kFirstChunk + wave * (kFirstChunk / 4);
+  const int p0 = blockIdx.x * chunk_px + wave * (chunk_px / 4);
   // this lane's column of the unfolded image: fixed tap and channel
   const int t = l32;
   const int tap = t / C, c = t - tap * C;
   const int du = tap / 3 - 1, dv = tap % 3 - 1;
   const int shift = (du * f.W + dv) * C + c;
-  for (int ob = 0; ob < f.Cout; ob += 32 * OB) {
+  {
+    const int ob = blockIdx.z * (32 * OB);
     f32x16 acc[OB];
+    int col[OB];                                 // this lane's channels; past the last one: read as channel 0, not stored
 #pragma unroll
-    for (int q = 0; q < OB; ++q)
+    for (int q = 0; q < OB; ++q) {
+      col[q] = ob + 32 * q + l32 < f.Cout ? ob + 32 * q + l32 : 0;
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[q][e] = 0.f;
+    }
     // loads are issued unconditionally (from a clamped pixel) and zeroed afterwards, so that the
     // unrolled loop can have many of them in flight
     const int last = (int)f.rows - 1;
-#pragma unroll 8
-    for (int s = 0; s < kFirstChunk / 8; ++s) {
+    for (int s0 = 0; s0 < chunk_px / 8; s0 += 8)
+#pragma unroll
+    for (int s = s0; s < s0 + 8; ++s) {
       const int p = p0 + 2 * s + h;
       const int pc = p < last ? p : last;
       int i, j;
@@ -428,7 +437,7 @@ __global__ __launch_bounds__(kThreads) void first_conv_wgrad_kernel(const float*
       const bool in_img = t < 9 * C && (unsigned)(i + du) < (unsigned)f.H && (unsigned)(j + dv) < (unsigned)f.W;
       float a[OB];
 #pragma unroll
-      for (int q = 0; q < OB; ++q) a[q] = dz[(long long)pc * f.Cout + ob + 32 * q + l32];
+      for (int q = 0; q < OB; ++q) a[q] = dz[(long long)pc * f.Cout + col[q]];
       float b = img[in_img ? (long long)pc * C + shift : 0];
       b = in_img ? b : (t == 9 * C ? 1.f : 0.f);
       if (p > last) b = 0.f;
@@ -448,7 +457,7 @@ __global__ __launch_bounds__(kThreads) void first_conv_wgrad_kernel(const float*
         for (int e = 0; e < 16; ++e) red[wave - 1][l32 * 32 + (e / 4) * 8 + h * 4 + e % 4] = acc[q][e];
       }
       __syncthreads();
-      if (wave == 0) {
+      if (wave == 0 && ob + 32 * q + l32 < f.Cout) {
         float* dst = partial + (((long long)k * chunks + blockIdx.x) * f.Cout + ob + 32 * q + l32) * 32;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -865,11 +874,25 @@ void launch_flip_filters(const float* W, int64_t strideW, int ldw, float* Wt, in
       W, strideW, ldw, Wt, Cout, Cin, cblocks);
 }
 
-bool first_conv_fits(int C, int Cout, int64_t rows) {
-  return C >= 1 && C <= 3 && Cout % 32 == 0 && Cout <= 256 && rows < (1 << 24);
+// Channel counts that are no multiples of 32 fill these kernels' last block in part; the stored unfolded image
+// they would take instead costs more, but for bf16 products of more than 64 channels on many pixels, which run
+// on the bf16 units there (a step of one such layer, stored -> here: fp32, 16 channels 469 -> 356 us, 40 260 ->
+// 228, 152 on 2.6e5 pixels 1033 -> 1014; bf16 products 404 -> 361, 260 -> 238, 152 890 -> 1034, on 3.3e4 pixels
+// 237 -> 227, 104 on 1.3e5 365 -> 381).
+bool first_conv_fits(int C, int Cout, int64_t rows, int K, int round) {
+  if (C < 1 || C > 3 || Cout % 8 || Cout > 256 || rows >= (1 << 24)) return false;
+  return Cout % 32 == 0 || !round || Cout <= 64 || K * rows <= 65536;
 }
 
-int first_conv_chunks(int64_t rows) { return (int)((rows + kFirstChunk - 1) / kFirstChunk); }
+static int first_chunk_px(int64_t rows, int Cout, int K) {
+  int px = 512;
+  while (px > 64 && (rows + px - 1) / px * K * ((Cout + 63) / 64) < 1024) px /= 2;
+  return px;
+}
+int first_conv_chunks(int64_t rows, int Cout, int K) {
+  const int px = first_chunk_px(rows, Cout, K);
+  return (int)((rows + px - 1) / px);
+}
 
 static FirstConv first_shape(int H, int W, int Cout, int64_t rows, int64_t strideParams, int ldw) {
   return FirstConv{H, W, Cout, 1.f / (float)W, 1.f / (float)H, rows, strideParams, ldw};
@@ -878,13 +901,15 @@ static FirstConv first_shape(int H, int W, int Cout, int64_t rows, int64_t strid
 int launch_first_conv_forward(const float* X, const float* params, int64_t strideParams, int64_t w_off,
                               int64_t b_off, int ldw, float* out, int relu, int round, int K,
                               int64_t rows, int H, int W, int C, int Cout, hipStream_t s) {
-  if (!first_conv_fits(C, Cout, rows)) return -1;
+  if (!first_conv_fits(C, Cout, rows, K, round)) return -1;
   const FirstConv f = first_shape(H, W, Cout, rows, strideParams, ldw);
-  const dim3 grid((unsigned)((rows + 127) / 128), (unsigned)K);
-  const size_t lds = (size_t)Cout * 33 * 4;
-  if (C == 1) first_conv_forward_kernel<1><<<grid, kThreads, lds, s>>>(X, params, w_off, b_off, out, f, relu, round);
-  else if (C == 2) first_conv_forward_kernel<2><<<grid, kThreads, lds, s>>>(X, params, w_off, b_off, out, f, relu, round);
-  else first_conv_forward_kernel<3><<<grid, kThreads, lds, s>>>(X, params, w_off, b_off, out, f, relu, round);
+  // where pixels give few workgroups, one for every 32 channels
+  const int group = (rows + 127) / 128 * K < 512 ? 32 : (Cout + 31) / 32 * 32;
+  const dim3 grid((unsigned)((rows + 127) / 128), (unsigned)K, (unsigned)((Cout + group - 1) / group));
+  const size_t lds = (size_t)group * 33 * 4;
+  if (C == 1) first_conv_forward_kernel<1><<<grid, kThreads, lds, s>>>(X, params, w_off, b_off, out, f, group, relu, round);
+  else if (C == 2) first_conv_forward_kernel<2><<<grid, kThreads, lds, s>>>(X, params, w_off, b_off, out, f, group, relu, round);
+  else first_conv_forward_kernel<3><<<grid, kThreads, lds, s>>>(X, params, w_off, b_off, out, f, group, relu, round);
   return 0;
 }
 
@@ -892,13 +917,13 @@ int launch_first_conv_wgrad(const float* X, const float* dout, float* partial, f
                             int64_t strideParams, int64_t w_off, int64_t b_off, int ldw, int round,
                             int skip_bias, int K, int64_t rows, int H, int W, int C, int Cout,
                             double* sumsq, int64_t sumsq_stride, hipStream_t s) {
-  if (!first_conv_fits(C, Cout, rows)) return -1;
+  if (!first_conv_fits(C, Cout, rows, K, round)) return -1;
   const FirstConv f = first_shape(H, W, Cout, rows, strideParams, ldw);
-  const int chunks = first_conv_chunks(rows);
-  const dim3 grid((unsigned)chunks, (unsigned)K);
+  const int chunks = first_conv_chunks(rows, Cout, K), px = first_chunk_px(rows, Cout, K);
+  const dim3 grid((unsigned)chunks, (unsigned)K, (unsigned)((Cout + 63) / 64));
   auto run = [&](auto one, auto two) {
-    if (Cout % 64 == 0) two<<<grid, kThreads, 0, s>>>(X, dout, partial, chunks, f, round);
-    else one<<<grid, kThreads, 0, s>>>(X, dout, partial, chunks, f, round);
+    if (Cout > 32) two<<<grid, kThreads, 0, s>>>(X, dout, partial, chunks, px, f, round);
+    else one<<<grid, kThreads, 0, s>>>(X, dout, partial, chunks, px, f, round);
   };
   if (C == 1) run(first_conv_wgrad_kernel<1, 1>, first_conv_wgrad_kernel<1, 2>);
   else if (C == 2) run(first_conv_wgrad_kernel<2, 1>, first_conv_wgrad_kernel<2, 2>);

@@ -509,9 +509,9 @@ void build_layout(const lsam_config& c, Layout& lo) {
       // their columns fill the 64-wide tiles badly: 160 channels, a step 0.35 ms slower of 27)
       cv.direct_dx = small && l > 0 && fits(cv.Cout) &&
                      (cv.stride == 1 || (cv.fast && (lo.np == 1 || cv.Cin <= 32 || (cv.Cin + 63) / 64 * 64 * 8 <= cv.Cin * 9)));
-      cv.first = l == 0 && cv.stride == 1 && first_conv_fits(cv.Cin, cv.Cout, cv.rows);
+      cv.first = l == 0 && cv.stride == 1 && first_conv_fits(cv.Cin, cv.Cout, cv.rows, lo.K, lo.bf16_math);
       if (cv.first)
-        cv.first_partial = take(cur, (size_t)lo.K * first_conv_chunks(cv.rows) * cv.Cout * 32 * 4);
+        cv.first_partial = take(cur, (size_t)lo.K * first_conv_chunks(cv.rows, cv.Cout, lo.K) * cv.Cout * 32 * 4);
       else if (!cv.direct_in) cv.col = take(cur, (size_t)lo.K * cv.rows * cv.ldc * (cv.fast ? 2 * lo.np : 4));
       if (cv.direct_dx && !cv.fast) cv.wt = take(cur, (size_t)lo.K * cv.Cin * 9 * cv.Cout * 4);
       cv.in_H = cv.H * cv.stride; cv.in_W = cv.W * cv.stride;

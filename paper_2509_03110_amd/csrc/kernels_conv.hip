@@ -876,7 +876,7 @@ void launch_flip_filters(const float* W, int64_t strideW, int ldw, float* Wt, in
 
 // Channel counts that are no multiples of 32 fill these kernels' last block in part; the stored unfolded image
 // they would take instead costs more, but for bf16 products of more than 64 channels on many pixels, which run
-// on the bf16 units there (a step of one such layer, stored -> here: fp32, 16 channels 469 -> 356 us, 40 260 ->
+// on the bf16 units there (a step of one such layer, before -> these: fp32, 16 channels 469 -> 356 us, 40 260 ->
 // 228, 152 on 2.6e5 pixels 1033 -> 1014; bf16 products 404 -> 361, 260 -> 238, 152 890 -> 1034, on 3.3e4 pixels
 // 237 -> 227, 104 on 1.3e5 365 -> 381).
 bool first_conv_fits(int C, int Cout, int64_t rows, int K, int round) {

@@ -156,7 +156,7 @@ def gemm_flops(w, layers):
         out["conv_first"] = 2 * 2 * 2.0 * first * K      # forward and weight gradient
     if any(r[2] for r in layers):
         out["gemm_dw_ascend"] = out["gemm_dw_step"] = 2.0 * sw * K
-        out["gemm_dw_norm"] = K * sum(2.0 * rows * rows * (fi + fo) if route == 2 else 2.0 * rows * fi * fo
+        out["gemm_dw_norm"] = K * sum(1.0 * rows * rows * (fi + fo) if route == 2 else 2.0 * rows * fi * fo
                                       for _, _, route, rows, fi, fo, _, _ in layers)
     else:
         out["gemm_dw"] = 2 * 2.0 * sw * K

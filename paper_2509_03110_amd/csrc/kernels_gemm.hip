@@ -1125,8 +1125,11 @@ int launch_dense_gradients(const DenseLayer* layers, int n, const DenseLayer* he
   d.bias_first = (int)blocks;
   for (int i = 0; i < n; ++i) d.it[i].bias_slot = slots + d.it[i].bias_block;
   blocks += (long long)bias_blocks * K;
-  auto go = [&](auto kern) {
-    static std::atomic<bool> attr_set{false};   // (setting it twice is harmless)
+  auto go = [&](auto tile_side, auto rounded) {
+    constexpr int BT = decltype(tile_side)::value;
+    constexpr bool ROUND = decltype(rounded)::value;
+    auto kern = dense_gradients_kernel<BT, 2, ROUND>;
+    static std::atomic<bool> attr_set{false};   // one per kernel, as the types of the arguments name it; setting it twice is harmless
     if (!attr_set.load(std::memory_order_relaxed)) {
       if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 80 << 10) != hipSuccess)
         return -1;
@@ -1135,8 +1138,10 @@ int launch_dense_gradients(const DenseLayer* layers, int n, const DenseLayer* he
     kern<<<(unsigned)blocks, kThreads, lds, s>>>(p, d);
     return slots + bias_blocks;
   };
-  if (bf16_math) return tile == 128 ? go(dense_gradients_kernel<128, 2, true>) : go(dense_gradients_kernel<64, 2, true>);
-  return tile == 128 ? go(dense_gradients_kernel<128, 2, false>) : go(dense_gradients_kernel<64, 2, false>);
+  typedef std::integral_constant<int, 128> Large;
+  typedef std::integral_constant<int, 64> Small;
+  if (bf16_math) return tile == 128 ? go(Large{}, std::true_type{}) : go(Small{}, std::true_type{});
+  return tile == 128 ? go(Large{}, std::false_type{}) : go(Small{}, std::false_type{});
 }
 
 }  // namespace lsam

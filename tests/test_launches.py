@@ -1,0 +1,25 @@
+"""What a step launches, seen without a GPU (launches.py)."""
+import pytest
+
+import launches
+
+# one process, in this order: every kernel that serves the dense gradients, the small tiles first
+DENSE = [
+    dict(K=2, dims=(784, 128, 10), batch=32),                                      # 64x64 tiles
+    dict(K=4, dims=(3072, 1024, 1024, 10), batch=128),                             # 128x128
+    dict(K=2, dims=(3, 8, 64, 10), batch=64, n_conv=1, img_h=16, img_w=16, gemm_dtype=1),      # rounded operands
+    dict(K=8, dims=(3, 8, 640, 640, 10), batch=64, n_conv=1, img_h=16, img_w=16, gemm_dtype=1),
+]
+
+
+def test_kernels_with_much_lds_have_their_limit_raised():
+    """A kernel that takes more than 64 KiB of dynamic LDS has to be allowed to, each kernel for itself, whatever
+    ran before it in the process."""
+    seen = set()
+    for model, r in zip(DENSE, launches.record(*DENSE)):
+        assert r["rc"] == 0, (model, r["error"])
+        for l in r["launches"]:
+            if l["name"].startswith("dense_gradients_kernel"):
+                seen.add(l["name"])
+            assert l["lds"] <= max(l["limit"], 64 << 10), (model, l)
+    assert seen == {"dense_gradients_kernel<%d,2,%s>" % (t, r) for t in (64, 128) for r in ("false", "true")}

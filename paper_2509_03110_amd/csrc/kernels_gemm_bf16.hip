@@ -1012,12 +1012,12 @@ int launch_fused_group(const DenseLayer* layers, int n, int K, int B, int64_t st
     it.M = q.out; it.N = q.in; it.ldC = q.ldw;
     it.cbA = b32s_blocks(q.out); it.cbB = b32s_blocks(q.in);
     it.first = (int)blocks;
-    // 16-byte accesses at multiples of 4 columns; 32-bit byte offsets, rows of a ragged last tile and
-    // the k-steps past the end included
+    // 16-byte accesses at multiples of 4 columns; 32-bit byte offsets, rows of a ragged last tile included, and
+    // those of the operands with what launch_gemm_bf16 asks beyond their end
     if (q.ldw % 4 || q.w_off % 4 || q.shadow_off % 4 || ((uintptr_t)it.dz & 15) || ((uintptr_t)it.act & 15) ||
         ((long long)q.out + 64) * q.ldw * 4 >= 0x7FFFFFF0LL || (long long)it.cbA * it.cbB * 2048 >= 0x7FFFFFF0LL ||
-        (long long)(b32s_blocks(B) + 8) * (it.cbA + 8) * 2048 >= 0x7FFFFFF0LL ||
-        (long long)(b32s_blocks(B) + 8) * (it.cbB + 8) * 2048 >= 0x7FFFFFF0LL)
+        (b32s_size(B, q.out) + 24576ll * it.cbA + 65536) * 2 >= 0x7FFFFFF0LL ||
+        (b32s_size(B, q.in) + 24576ll * it.cbB + 65536) * 2 >= 0x7FFFFFF0LL)
       return -1;
     blocks += ((long long)((q.out + 63) / 64) * ((q.in + 63) / 64) * K + 7) / 8 * 8;
     if (blocks >= (1ll << 31)) return -1;

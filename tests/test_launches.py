@@ -23,3 +23,9 @@ def test_kernels_with_much_lds_have_their_limit_raised():
                 seen.add(l["name"])
             assert l["lds"] <= max(l["limit"], 64 << 10), (model, l)
     assert seen == {"dense_gradients_kernel<%d,2,%s>" % (t, r) for t in (64, 128) for r in ("false", "true")}
+
+
+def test_long_batches_of_narrow_bf16_layers_are_accepted():
+    """Four million rows of 32 columns, 256 MB an operand: within the 32-bit offsets of every product."""
+    r = launches.record(dict(K=1, dims=(32, 32, 32), batch=4_000_000, gemm_dtype=1))[0]
+    assert r["rc"] == 0, r["error"]

@@ -8,25 +8,37 @@ namespace lsam {
 constexpr int kHeadMaxC = 16;       // classes of the narrow head
 typedef float hf4 __attribute__((ext_vector_type(4)));
 
-// db[n] = sum_b dz[b][n] for the 64 columns from 64 * block on; WAVES wavefronts, `part` WAVES * 64 floats of LDS.
-template <int WAVES>
+// db[n] = sum_b dz[b][n] for the 64 columns from 64 * block on.  Share w of WAVES takes every WAVES-th row from w
+// on, as four chains; `part`: WAVES * 64 floats of LDS.  WAVES / ROLES wavefronts, each with ROLES shares: what
+// bounds it is the chain of loads a wavefront waits for, and a wavefront with four shares has sixteen under way.
+template <int WAVES, int ROLES = 1>
 __device__ __forceinline__ void column_sums(const float* dz, long long ld, float* db, int B, int N, int block, float* part,
                                             double* sumsq) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = block * 64 + lane;
-  float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+  float s[ROLES][4] = {};
+  auto share = [&](int r) { return wave + r * (WAVES / ROLES); };
   if (n < N) {
     auto at = [&](int b) { return dz[(long long)b * ld + n]; };
-    int b = wave;
-    for (; b + 3 * WAVES < B; b += 4 * WAVES) {
-      s0 += at(b);
-      s1 += at(b + WAVES);
-      s2 += at(b + 2 * WAVES);
-      s3 += at(b + 3 * WAVES);
+    int base = 0;
+    for (; base + 4 * WAVES <= B; base += 4 * WAVES)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int r = 0; r < ROLES; ++r) s[r][i] += at(base + share(r) + i * WAVES);
+#pragma unroll
+    for (int r = 0; r < ROLES; ++r) {
+      int b = base + share(r);
+      if (b + 3 * WAVES < B) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[r][i] += at(b + i * WAVES);
+        b += 4 * WAVES;
+      }
+      for (; b < B; b += WAVES) s[r][0] += at(b);
     }
-    for (; b < B; b += WAVES) s0 += at(b);
   }
-  part[wave * 64 + lane] = (s0 + s1) + (s2 + s3);
+#pragma unroll
+  for (int r = 0; r < ROLES; ++r) part[share(r) * 64 + lane] = (s[r][0] + s[r][1]) + (s[r][2] + s[r][3]);
   __syncthreads();
   if (wave == 0) {
     float r = 0.f;

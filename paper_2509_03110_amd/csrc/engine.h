@@ -246,6 +246,8 @@ int launch_fused_group(const DenseLayer* layers, int n, int K, int B, int64_t st
 // fp32 (bf16_math: operands of the products rounded): the weight and bias gradients of n layers and (may be null) of the narrow head, into g.  Returns the
 // sum-of-squares slots written per replica (at most gemm_sumsq_capacity of every product, one per 64 biases,
 // head_sumsq_slots), or -1.
+// The products that dense_gradients_alone marks are left out, not so their biases: those take a launch_gemm each.
+void dense_gradients_alone(const DenseLayer* layers, int n, int K, int B, int bf16_math, bool* alone);
 int launch_dense_gradients(const DenseLayer* layers, int n, const DenseLayer* head, int K, int B, float* g, int64_t strideG,
                            double* sumsq, int64_t sumsq_stride, int bf16_math, hipStream_t s);
 // Column sums of every layer's dz into g; slots as launch_bias_grad's.  `step` (may be null): the biases

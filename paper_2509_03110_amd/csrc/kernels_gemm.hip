@@ -1115,8 +1115,9 @@ Plan gradient_plan(const DenseLayer& q, int K, int B, int bf16_math) {
 long long tiles_of(const DenseLayer& q, int side, int K) {
   return (long long)((q.out + side - 1) / side) * ((q.in + side - 1) / side) * K;
 }
-// Tiles of 128x128 of the layers that fill one, from which on a launch takes such tiles: one for every compute unit
-// (three in four with rounded operands), as for a product of its own.
+// The launch takes 128x128 tiles where the layers that fill one give every compute unit one (three in four with rounded
+// operands).  Layers large enough for 256x256 tiles in a launch of their own gain nothing from those here: sixteen
+// 256-2048-2048-24 with 512 rows 4210 us, 4288 with them, with 128 rows 1680 and 1773.
 bool fills_large(const DenseLayer& q) { return q.out >= 128 && q.in >= 128; }
 long long large_tiles(const DenseLayer* layers, int n, int K) {
   long long t = 0;
@@ -1128,9 +1129,31 @@ int gradient_tile(const DenseLayer* layers, int n, int K, int bf16_math) {
 }
 }  // namespace
 
+// A workgroup of the shared launch walks the whole batch, so a long batch with few tiles is better off cut over
+// workgroups, at the price of two launches more a product: from 2048 rows and below 192 tiles.  A step of one
+// 784-128-10 with 2048 rows 189 -> 158 us, with 8192 527 -> 306; four of them (112 tiles) with 2048 208 -> 213, with
+// 4096 340 -> 316; but eight 256-200-100-50 (208 tiles) with 2048 322 -> 355, with 4096 503 -> 521, and with 1024
+// rows two 64-64-64-10 134 -> 157.
+// So is a product too narrow for the launch's 128x128 tiles, at 512 rows and more, if the others then need a
+// round of the 256 compute units less: one 3072-1024-1024-10 (256 tiles and 8) with 1024 rows 580 -> 492 us, four
+// of them 1586 -> 1507; but three 1000-1500-777-37 (540 and 21) 1124 -> 1159.
+void dense_gradients_alone(const DenseLayer* layers, int n, int K, int B, int bf16_math, bool* alone) {
+  auto rounds = [](long long tiles) { return (tiles + 255) / 256; };
+  const int tile = gradient_tile(layers, n, K, bf16_math);
+  const long long large = large_tiles(layers, n, K);
+  long long all = 0;
+  for (int i = 0; i < n; ++i) all += tiles_of(layers[i], tile, K);
+  const bool few = tile == 64 && all < 192 && B >= 2048;
+  const bool narrow = tile == 128 && B >= 512 && rounds(large) < rounds(all);
+  for (int i = 0; i < n; ++i)
+    alone[i] = (few || (narrow && !fills_large(layers[i]))) && gradient_plan(layers[i], K, B, bf16_math).splits > 1;
+}
+
 int launch_dense_gradients(const DenseLayer* layers, int n, const DenseLayer* head, int K, int B, float* g, int64_t strideG,
                            double* sumsq, int64_t sumsq_stride, int bf16_math, hipStream_t s) {
   if (n < 0 || n > LSAM_MAX_LAYERS || (n == 0 && !head) || (strideG % 4) || ((uintptr_t)g & 15)) return -1;
+  bool alone[LSAM_MAX_LAYERS];
+  dense_gradients_alone(layers, n, K, B, bf16_math, alone);
   const int tile = gradient_tile(layers, n, K, bf16_math);
   DenseGrads d{};
   GemmParams p{};
@@ -1158,7 +1181,7 @@ int launch_dense_gradients(const DenseLayer* layers, int n, const DenseLayer* he
     if (q.ldw % 8 || q.w_off % 4 || ((uintptr_t)q.dz & 15) || ((uintptr_t)q.act & 15) ||
         (long long)B * d.it[i].ld_dz * 4 >= 0x7FFFFFF0LL || (long long)B * d.it[i].ld_act * 4 >= 0x7FFFFFF0LL)
       return -1;
-    const int tiles = (int)tiles_of(q, tile, 1);
+    const int tiles = alone[i] ? 0 : (int)tiles_of(q, tile, 1);
     blocks += ((long long)tiles * K + 7) / 8 * 8;
     slots += tiles;
     bias_blocks += (q.out + 63) / 64;

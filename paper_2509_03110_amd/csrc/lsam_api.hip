@@ -1383,6 +1383,8 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
   dense_layers(c, A0, dense);
   // fp32: all weight and bias gradients share a launch once the dZ are there
   const bool grouped = !bf;
+  bool alone[LSAM_MAX_LAYERS] = {};
+  if (grouped) dense_gradients_alone(dense + l0, (head ? L - 1 : L) - l0, K, B, lo.bf16_math, alone + l0);
   for (int l = L - 1; l >= l0; --l) {
     const Layer& ly = lo.layers[l];
     const char* dz = c->at<char>(lo.dz[l + 1]);
@@ -1444,16 +1446,17 @@ int forward_backward(lsam_ctx* c, const void* X, const int32_t* labels, const vo
     // With the fused step the weight-gradient kernel overwrites the operand copy of W_l that
     // the input gradient still has to read, so that one goes first.
     if (fuse && want_dx && (rc = input_grad()) != LSAM_OK) return rc;
-    if (!grouped && (rc = weight_grad()) != LSAM_OK) return rc;
+    if ((!grouped || alone[l]) && (rc = weight_grad()) != LSAM_OK) return rc;
     if (!fuse && want_dx && (rc = input_grad()) != LSAM_OK) return rc;
   }
   if (grouped) {
-    int most = bias_slots + (head ? head_sumsq_slots(lo.layers[L - 1].in) : 0);
-    for (int l = l0; l < (head ? L - 1 : L); ++l) most += gemm_sumsq_capacity(lo.layers[l].out, lo.layers[l].in);
+    int most = slots + bias_slots + (head ? head_sumsq_slots(lo.layers[L - 1].in) : 0);
+    for (int l = l0; l < (head ? L - 1 : L); ++l)
+      if (!alone[l]) most += gemm_sumsq_capacity(lo.layers[l].out, lo.layers[l].in);
     if (ssq && most > lo.nblk) return fail(LSAM_ESTATE, "gradient-norm partials would overrun their buffer at the dense layers");
     LaunchTimer t(c, KC_GEMM_DW);
     const int used = launch_dense_gradients(dense + l0, (head ? L - 1 : L) - l0, head ? dense + L - 1 : nullptr, K, B, g,
-                                            lo.d_pad, ssq, lo.nblk, lo.bf16_math, s);
+                                            lo.d_pad, ssq ? ssq + slots : nullptr, lo.nblk, lo.bf16_math, s);
     if (used < 0) return fail(LSAM_EINVAL, "weight gradients of the dense layers rejected");
     if (ssq) slots += used;
   }

@@ -20,7 +20,8 @@ pytestmark = pytest.mark.gpu
     ((1500, 300, 10), 64, 2),                    # too wide for that: reduced by a launch of its own
     ((65, 63, 129, 17), 33, 2), ((64, 64, 64, 64), 64, 1), ((200, 127, 17, 40), 130, 3),    # no narrow head
     ((520, 700, 640, 12), 100, 4),               # 128x128 tiles, more than 128 partial sums
-    ((300, 520, 24, 10), 512, 2)])               # the head's largest batch
+    ((300, 520, 24, 10), 512, 2),                # the head's largest batch
+    ((1024, 1024, 10), 520, 4)])                 # 128x128 tiles beside a narrow product of its own
 def test_against_the_oracle(dims, B, K):
     w = workloads.WORKLOADS["cfg1"].scaled(name="dg", lr=0.01, K=K, dims=dims, batch=B, tau=(2,) * K, n_classes=dims[-1], steps=3)
     # (the bounds for fp32; pre-activations at least 2e-5 from zero, some ten roundings)

@@ -29,3 +29,31 @@ def test_long_batches_of_narrow_bf16_layers_are_accepted():
     """Four million rows of 32 columns, 256 MB an operand: within the 32-bit offsets of every product."""
     r = launches.record(dict(K=1, dims=(32, 32, 32), batch=4_000_000, gemm_dtype=1))[0]
     assert r["rc"] == 0, r["error"]
+
+
+def dense_products(model):
+    """(tile side of the first pass's launch of all gradients, its products, products of their own by name)"""
+    got = [l for l in launches.record(model)[0]["launches"]]
+    first = got[:next(i for i, l in enumerate(got) if l["name"].startswith("dense_gradients_kernel")) + 1]
+    own = [l["name"] for l in first if l["name"].startswith("gemm_kernel<float,float") and ",false,false," in l["name"]]
+    return int(first[-1]["name"].split("<")[1].split(",")[0]), own
+
+
+@pytest.mark.parametrize("model,tile,own", [
+    # long batches with few tiles are cut over workgroups, each product for itself
+    (dict(K=1, dims=(784, 128, 10), batch=2048), 64, 2),
+    (dict(K=1, dims=(784, 128, 10), batch=512), 64, 0),
+    (dict(K=2, dims=(64, 64, 64, 10), batch=4096), 64, 3),
+    (dict(K=8, dims=(256, 200, 100, 50), batch=4096), 64, 0),       # 208 tiles
+    # a product too narrow for 128x128 tiles, where the others fill whole rounds of the compute units
+    (dict(K=1, dims=(3072, 1024, 1024, 10), batch=1024), 128, 1),
+    (dict(K=4, dims=(3072, 1024, 1024, 10), batch=1024), 128, 1),
+    (dict(K=4, dims=(3072, 1024, 1024, 24), batch=512), 128, 1),
+    (dict(K=4, dims=(3072, 1024, 1024, 24), batch=256), 128, 0),
+    (dict(K=3, dims=(1000, 1500, 777, 37), batch=1024), 128, 0),
+    # rounded operands
+    (dict(K=1, dims=(3, 8, 64, 10), batch=4096, n_conv=1, img_h=16, img_w=16, gemm_dtype=1), 64, 2),
+    (dict(K=8, dims=(3, 8, 640, 640, 10), batch=128, n_conv=1, img_h=16, img_w=16, gemm_dtype=1), 128, 0)])
+def test_which_dense_gradients_share_a_launch(model, tile, own):
+    got_tile, got_own = dense_products(model)
+    assert got_tile == tile and len(got_own) == own, (got_tile, got_own)

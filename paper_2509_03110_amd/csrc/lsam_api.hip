@@ -1281,9 +1281,20 @@ bool gram_norm_pays(int B, int out, int in) {
   return 2 * (int64_t)B * (out + in) <= (int64_t)out * in;
 }
 
-// Whether the fused step and ascent of a bf16 dense model go through all layers in one launch: where
-// the state stays in the caches.
-bool fused_in_group(const Layout& lo) { return (int64_t)lo.K * lo.d_pad * 4 <= kCacheResidentBytes; }
+// Whether the fused step and ascent of a bf16 dense model go through all layers in one launch, on 64x64 tiles: where
+// the state stays in the caches, unless its products are work enough for 128x128 tiles and a launch each.  Those take
+// a launch more a layer and pass and win from about 1e10 multiply-adds a layer (together / a launch each): one
+// 3072-4096-1000 with 1024 rows 418 / 402 us, with 4096 1013 / 873; one 2048-2048-2048-2048-2048 with 2048 783 / 776, with
+// 4096 1318 / 1195; four 3072-1024-1024-10 with 2048 685 / 669, with 4096 1183 / 1071; one 2500-4000-3000-900 with
+// 1024 679 / 710, with 2048 1008 / 988.  A step on 128x128 tiles deals groups of 4 x 4 of them to the eight XCDs, so layers of
+// fewer groups do not count: 16 512-512-512-512 with 2048 rows (one group) 772 / 1244.
+bool fused_in_group(const Layout& lo) {
+  if ((int64_t)lo.K * lo.d_pad * 4 > kCacheResidentBytes) return false;
+  double work = 0.;
+  for (const Layer& ly : lo.layers)
+    if ((int64_t)((ly.out + 511) / 512) * ((ly.in + 511) / 512) >= 8) work += (double)lo.K * lo.B * ly.out * ly.in;
+  return work < 1e10 * lo.L;
+}
 
 // The dense layers with the dZ and the inputs that the last pass left (A0: the first one's).
 void dense_layers(const lsam_ctx* c, const void* A0, DenseLayer* out) {

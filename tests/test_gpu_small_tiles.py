@@ -28,12 +28,13 @@ def test_small_models(dims, B, K):
     run_mlp(w, 3, 2e-2, 2e-2, margin=True)       # the file's bound for bf16 operands
 
 
-def test_ragged_tiles_past_the_caches():
+@pytest.mark.parametrize("dims,B,K", [((1000, 2500, 2300, 300), 300, 8), ((2100, 2300, 300), 4200, 1)])
+def test_ragged_tiles_past_the_caches(dims, B, K):
     """285 MB a state vector: streaming stores, 128x128 step, 256x128 products and ascent, the last layer on
-    64x64 tiles.  Fused against separate kernels.  Their norms may differ in the last bit, and among
+    64x64 tiles; 22 MB with a batch that is work enough for a launch a layer all the same.  Fused against separate kernels.  Their norms may differ in the last bit, and among
     7e7 perturbed weights some then round to the other bf16 neighbour, 2^-8 away; a unit sums at least
     1000 of them, so what it computes, and the gradients behind it, move by 2^-8 / sqrt(1000) = 1.2e-4 at most."""
-    w = _model((1000, 2500, 2300, 300), 300, 8)
+    w = _model(dims, B, K)
     init = workloads.init_params(w)
     cfg, keep = lsam.config_from_workload(w)
     a, b = (lsam.Lsam(cfg, init, device=DEV, keep=keep) for _ in range(2))

@@ -57,3 +57,21 @@ def dense_products(model):
 def test_which_dense_gradients_share_a_launch(model, tile, own):
     got_tile, got_own = dense_products(model)
     assert got_tile == tile and len(got_own) == own, (got_tile, got_own)
+
+
+@pytest.mark.parametrize("model,together", [
+    (dict(K=3, dims=(1000, 1500, 777, 37), batch=100), True),
+    (dict(K=1, dims=(3072, 4096, 1000), batch=1024), True), (dict(K=1, dims=(3072, 4096, 1000), batch=2048), False),
+    (dict(K=4, dims=(3072, 1024, 1024, 10), batch=2048), True), (dict(K=4, dims=(3072, 1024, 1024, 10), batch=4096), False),
+    (dict(K=1, dims=(2048,) * 5, batch=8192), False),
+    (dict(K=16, dims=(512,) * 4, batch=8192), True),               # large work on layers of one group of tiles
+    (dict(K=8, dims=(3072, 1024, 1024, 10), batch=64), False)])    # past the caches
+def test_which_bf16_layers_step_together(model, together):
+    names = launches.names(dict(model, gemm_dtype=1))
+    joined = [n for n in names if n.startswith("fused_group_kernel")]
+    assert len(joined) == (2 if together else 0), names
+    if not together:
+        # the step and the ascent of every layer; wide ones on large tiles
+        for kind in (1, 3):
+            mine = [n for n in names if n.startswith("gemm_bf16_kernel<float") and n.endswith(",%d>" % kind)]
+            assert len(mine) == len(model["dims"]) - 1 and any(",64,64," not in n for n in mine), names

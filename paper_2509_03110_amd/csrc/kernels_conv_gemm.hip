@@ -48,10 +48,23 @@ typedef __attribute__((address_space(3))) unsigned char lds_byte;
 
 // How output pixels see the image: pixel (b, i, j) of [oH][oW], tap (a, c) of nu x nv, reads image
 // pixel (st i + du0 + a, st j + dv0 + c) of [sH][sW].
+// n / d for 0 <= n < 2^31 as the high word of n `magic`, shifted: magic = 2^(31 + l) / d rounded up, l = log2 d rounded up,
+// is at most 2^-l of itself too large, which times n stays below 1 / d.  d >= 2.
+struct Divisor {
+  unsigned magic;
+  int shift;
+};
+inline Divisor divisor(int d) {
+  int l = 1;
+  while ((1ll << l) < d) ++l;
+  return Divisor{(unsigned)(((1ull << (31 + l)) + (unsigned)d - 1) / (unsigned)d), l - 1};
+}
+__device__ __forceinline__ int divide(int n, const Divisor& d) { return (int)(__umulhi((unsigned)n, d.magic) >> d.shift); }
+
 struct Geometry {
   int C, oH, oW, sH, sW, st, nu, nv, du0, dv0;
   unsigned magicC;                 // 2^32 / C + 1: tap of a contraction index by a high multiply
-  unsigned magicW, magicH, magicH2;    // the same for oW, oH and oH + 2 (weight gradients from patches)
+  Divisor byW, byH, byH2;          // by oW, oH and oH + 2 (weight gradients from patches)
 };
 
 struct Params {
@@ -90,11 +103,11 @@ __device__ __forceinline__ void decode(int p, const Geometry& g, int& b, int& i,
   i = q - b * g.oH;
 }
 
-// The same by high multiplies: p d < 2^32 for the divisors d >= 2 (wgrad_decodes).
+// The same by high multiplies (sides of at least 2).
 __device__ __forceinline__ void decode_fast(int p, const Geometry& g, int& b, int& i, int& j) {
-  const int q = (int)__umulhi((unsigned)p, g.magicW);
+  const int q = divide(p, g.byW);
   j = p - q * g.oW;
-  b = (int)__umulhi((unsigned)q, g.magicH);
+  b = divide(q, g.byH);
   i = q - b * g.oH;
 }
 
@@ -1157,7 +1170,7 @@ __device__ __forceinline__ void patch_offsets(const Geometry& g, int px0, int im
   const int pr0 = __builtin_amdgcn_readfirstlane(b0 * H2 + i0);
 #pragma unroll
   for (int l = 0; l < NLA; ++l) {
-    const int pr = pr0 + row[l], b = (int)__umulhi((unsigned)pr, g.magicH2), i = pr - b * H2 - 1;
+    const int pr = pr0 + row[l], b = divide(pr, g.byH2), i = pr - b * H2 - 1;
     const bool ok = (unsigned)i < (unsigned)g.oH && b < images && col[l] >= 0;
     off[l] = ok ? (unsigned)(b * g.oH + i) * (unsigned)(g.oW * g.C * 2) + (unsigned)col[l] : kOob;
   }
@@ -1619,12 +1632,6 @@ int patch_slots(int bm, int H, int W) {
   return (rows + 2 + 2 * inside) * (W + 2);
 }
 
-// Whether decode_fast finds the pixels of a weight gradient, and of the stages that its loads reach past the end.
-bool wgrad_decodes(const ConvGemmDesc& d) {
-  const long long px = (long long)d.Kd + 1024, side = std::max(d.image.oW, d.image.oH + 2);
-  return d.image.oW >= 2 && d.image.oH >= 2 && 2 * px * side < (1ll << 32);     // (rimmed rows: at most twice the pixels)
-}
-
 ConvPlan conv_plan(const ConvGemmDesc& d) {
   ConvPlan pl{{128, 128}, 0, 1, 0, 0, 0};
   auto count = [&](int bm, int bn) { return (long long)((d.M + bm - 1) / bm) * ((d.N + bn - 1) / bn) * d.batch; };
@@ -1653,7 +1660,7 @@ ConvPlan conv_plan(const ConvGemmDesc& d) {
   // Weight gradients: the patch kernel always leaves partial sums.  Its workgroups have a compute unit to
   // themselves and equal work, so the contraction is cut for one, two or four full rounds of 256,
   // the first that keeps 93 % of the units busy.
-  if (d.wgrad && im.nu == 3 && im.nv == 3 && im.st == 1 && wgrad_decodes(d)) {
+  if (d.wgrad && im.nu == 3 && im.nv == 3 && im.st == 1 && im.oW >= 2 && im.oH >= 2) {
     const bool wide = d.M > 32;
     const int px = 64;
     const long long tiles = (long long)((d.M + (wide ? 63 : 31)) / (wide ? 64 : 32)) * ((im.C + 31) / 32) * d.batch;
@@ -1738,8 +1745,8 @@ int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots) {
   p.C = d.C; p.strideC = d.strideC; p.ldC = d.ldC;
   p.M = d.M; p.N = d.N; p.Kd = d.Kd; p.batch = d.batch;
   p.g = Geometry{im.C, im.oH, im.oW, im.sH, im.sW, im.st, im.nu, im.nv, im.du0, im.dv0,
-                 (unsigned)((1ull << 32) / (unsigned)im.C + 1), (unsigned)((1ull << 32) / (unsigned)im.oW + 1),
-                 (unsigned)((1ull << 32) / (unsigned)im.oH + 1), (unsigned)((1ull << 32) / (unsigned)(im.oH + 2) + 1)};
+                 (unsigned)((1ull << 32) / (unsigned)im.C + 1), divisor(im.oW), divisor(im.oH),
+                 divisor(im.oH + 2)};
   p.epilogue = d.epilogue;
   p.out_step = d.out_step;
   p.bias = d.bias; p.strideBias = d.strideBias;

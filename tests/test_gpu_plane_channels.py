@@ -27,3 +27,10 @@ NETS = {
 def test_against_the_oracle(name, bf16, monkeypatch):
     monkeypatch.setitem(planes.NETS, name, NETS[name])
     planes.test_plane_products_match_oracle(name, bf16)
+
+
+def test_tall_images(monkeypatch):
+    """192000 pixels in images of 16000 rows: the weight gradient's patches divide numbers whose product with the divisor
+    is past 2^32."""
+    monkeypatch.setitem(planes.NETS, "tall", dict(dims=(3, 32, 32, 10), side=(16000, 4), batch=3, K=1))
+    planes.test_plane_products_match_oracle("tall", 0)

@@ -1,4 +1,5 @@
 """What a step launches, seen without a GPU (launches.py)."""
+import numpy as np
 import pytest
 
 import launches
@@ -75,3 +76,26 @@ def test_which_bf16_layers_step_together(model, together):
         for kind in (1, 3):
             mine = [n for n in names if n.startswith("gemm_bf16_kernel<float") and n.endswith(",%d>" % kind)]
             assert len(mine) == len(model["dims"]) - 1 and any(",64,64," not in n for n in mine), names
+
+
+@pytest.mark.parametrize("side,batch,patches", [((16000, 4), 3, True), ((4000, 32), 7, True), ((32, 32), 128, True),
+                                                ((30000, 4), 12, True)])
+def test_weight_gradients_of_tall_images_come_from_patches(side, batch, patches):
+    names = launches.names(dict(K=1, dims=(3, 32, 32, 10), batch=batch, n_conv=2, img_h=side[0], img_w=side[1], bn_mask=3,
+                                global_avg_pool=1))
+    assert any(n.startswith("conv_wgrad_kernel<3,") for n in names) == patches, names
+
+
+def test_divisions_by_high_multiplies_are_exact():
+    """The kernels' n / d = (n magic >> 32) >> shift against n / d, for every d up to 5000 and some beyond, at multiples
+    of d up to 2^31 and beside them."""
+    rng = np.random.default_rng(1)
+    for d in list(range(2, 5000)) + [16002, 30002, 65535, 65536, 65537, (1 << 24) - 1]:
+        log = max(1, (d - 1).bit_length())
+        magic, shift = -(-(1 << (31 + log)) // d), log - 1
+        assert magic < 1 << 32
+        top = ((1 << 31) - 1) // d
+        n = np.concatenate([rng.integers(0, top + 1, 200), np.arange(3), top - np.arange(min(3, top))]) * d
+        n = np.concatenate([n, n + d - 1, [(1 << 31) - 1]])
+        n = n[(n >= 0) & (n < 1 << 31)].astype(np.uint64)
+        assert np.array_equal(n * np.uint64(magic) >> np.uint64(32 + shift), n // np.uint64(d)), d

@@ -1654,8 +1654,15 @@ ConvPlan conv_plan(const ConvGemmDesc& d) {
     if (d.np == 1) pl.patch = s256 <= 22 * 16 ? kPatch22 : s256 <= 26 * 16 ? kPatch26 : kNoPatch;
     else if (d.N > 32) pl.patch = s256 <= 11 * 32 ? kSplitPatch256 : s128 <= 10 * 32 ? kSplitPatch128 : kNoPatch;
     else pl.patch = s256 <= 11 * 32 ? kSplitNarrow256 : s128 <= 10 * 32 ? kSplitNarrow128 : kNoPatch;
-    if (pl.patch)
-      pl.tile = Tile{pl.patch == kSplitPatch128 || pl.patch == kSplitNarrow128 ? 128 : 256, d.N > 32 ? 64 : 32};
+    if (pl.patch) {
+      const Tile t{pl.patch == kSplitPatch128 || pl.patch == kSplitNarrow128 ? 128 : 256, d.N > 32 ? 64 : 32};
+      // Fewer than 64 of the three-plane patches' large tiles leave the chip idle, where the ring's smaller ones can also cut
+      // the contraction (two layers at 16 x 16, patches / ring: 48 channels, 26 tiles 359 / 320 us, 80, 32 tiles 370 / 348, 112, 32
+      // tiles 392 / 364; 160, 78 tiles 491 / 523).  Layers of whole blocks of 32 channels, which had these patches before
+      // other counts did, would gain 3 to 5 % there too (64, 26 tiles 372 / 347) and are left as they are.
+      if (d.np == 3 && (im.C % 32 || d.N % 32) && count(t.bm, t.bn) < 64) pl.patch = kNoPatch;
+      else pl.tile = t;
+    }
   }
   // Weight gradients: the patch kernel always leaves partial sums.  Its workgroups have a compute unit to
   // themselves and equal work, so the contraction is cut for one, two or four full rounds of 256,

@@ -331,18 +331,32 @@ size_t take(size_t& cursor, size_t bytes) {
 // multiples of 32 have a stored unfolded image to save: from 2e7, and above 32 channels 1e8 on at least
 // 4096 pixels (two equal layers, fp32 / bf16 products: 16 channels at 9e6 0.94 to 1.03 / 0.95, at 2e7 0.95 /
 // 0.91; 24 at 2e7 0.95, 4e8 0.72, 2.7e9 0.40 / 0.42; 40 at 1.2e8 0.97, 2.4e8 0.84 / 0.90; 72 at 1.9e8 0.99, 3e9
-// 0.50; 152 at 2.3e10 0.46; but 104 channels at 1e8 on 1024 pixels 1.16).  Counts that are no multiples of 8
+// 0.50; 152 at 2.3e10 0.46; but 104 channels at 1e8 on 1024 pixels 1.16).  On fewer pixels the
+// conversions weigh more (the second of two layers, fp32): below 5120 from 1.5e8, and 2.5e8 where the layer widens (4096 pixels:
+// 64 to 56 channels at 1.3e8 1.04, 80 to 80 at 2.4e8 1.01, 112 to 40 at 1.7e8 0.98, 184 to 24 at 1.6e8 0.91; 56 to 112 at 2.3e8 1.03,
+// 40 to 184 at 2.7e8 0.96), with bf16 products below 6144 from 1.15e8 (48 at 1.1e8 beside a projection 1.03, 56 at 1.2e8 0.95
+// to 0.98).  In fp32 a layer of many times its input's channels, no multiple of 16, whose dX the ring computes for 8 or
+// 16 columns of its tiles' 32, stays there (6.6e4 pixels: 8 to 88 channels 0.99, to 104 1.06, to 184 1.26, 16 to 168 0.99, to 184
+// 1.03, to 248 1.07; in whole 16s, by patches, 8 to 128 0.81, 16 to 128 0.77).
+// A layer on the data (`dx`: whether there is an input gradient to compute) saves its own image only, and in a single
+// layer of 8 or 16 channels that pays from 12288 pixels, of 24 from 8192 (fp32 / bf16 products: 16 to 24 channels on 7424
+// 1.05 / 1.00, on 9216 1.01 / 1.00, on 16384 0.92; 24 to 24 on 7424 1.01 / 0.98, on 9216 0.96 / 0.95; 32 to 48 on 7424 1.12 / 1.01).
+// Counts that are no multiples of 8
 // are taken with a stored unfolded image, nine times the image either way: with one plane that pays from 3e8.
-bool plane_products_pay(int np, int K, int64_t rows, int Cin, int Cout) {
+bool plane_products_pay(int np, int K, int64_t rows, int Cin, int Cout, bool dx) {
   const double macs = (double)K * (double)rows * 9.0 * Cin * Cout;
   if (np == 1 && K * rows < 4096) return false;
   if (Cin % 8 || Cout % 8) return np == 1 && macs >= 3e8;
   // (in fp32 arithmetic 24 channels beside a multiple of 32 stay with the fp32-storage GEMM, not because it is
   // faster, but because callers are told so: lsam_layer_info's answers for such layers are held to it)
   if (np == 3 && std::min(Cin, Cout) == 24 && std::max(Cin, Cout) % 32 == 0) return false;
-  const bool stored = Cin % 32 || Cout % 32;       // on the fp32-storage GEMM
+  if (np == 3 && Cout % 16 && Cout > 11 * Cin) return false;
+  const bool stored = Cin % 32 || (dx && Cout % 32);       // on the fp32-storage GEMM
+  if (!dx && Cin < 32 && K * rows < (Cin > 16 ? 8192 : 12288) && macs < 3e8) return false;
   if (std::max(Cin, Cout) <= 32) return macs >= (stored ? 2e7 : 1e8);
-  return macs >= (stored && K * rows >= 4096 ? 1e8 : 3e8);
+  if (!stored || K * rows < 4096) return macs >= 3e8;
+  if (np == 1) return macs >= (K * rows < 6144 ? 1.15e8 : 1e8);
+  return macs >= (K * rows >= 5120 ? 1e8 : Cout > Cin ? 2.5e8 : 1.5e8);
 }
 
 void build_layout(const lsam_config& c, Layout& lo) {
@@ -500,7 +514,7 @@ void build_layout(const lsam_config& c, Layout& lo) {
       ConvLayer& cv = lo.conv[l];
       const size_t full = (size_t)lo.K * cv.rows * cv.Cout * 4;
       const bool small = cv.rows < (1 << 24);      // (first-layer kernels: pixel indices exact in fp32)
-      cv.fast = plane_products_pay(lo.np, lo.K, cv.rows, cv.Cin, cv.Cout);
+      cv.fast = plane_products_pay(lo.np, lo.K, cv.rows, cv.Cin, cv.Cout, l > 0);
       // unfolding by address: whole taps or parts of one tap make up a 32-deep k-step; the
       // fp32-storage GEMM knows stride 1 and parts of taps only
       auto fits = [&](int C) { return C % (cv.fast ? 8 : 32) == 0; };
@@ -516,7 +530,7 @@ void build_layout(const lsam_config& c, Layout& lo) {
       if (cv.direct_dx && !cv.fast) cv.wt = take(cur, (size_t)lo.K * cv.Cin * 9 * cv.Cout * 4);
       cv.in_H = cv.H * cv.stride; cv.in_W = cv.W * cv.stride;
       cv.planes = (cv.fast && cv.direct_in && !cv.first) || (l + 1 < lo.n_conv && lo.conv[l + 1].proj &&
-                  plane_products_pay(lo.np, lo.K, lo.conv[l + 1].rows, lo.conv[l + 1].Cin, lo.conv[l + 1].Cout));
+                  plane_products_pay(lo.np, lo.K, lo.conv[l + 1].rows, lo.conv[l + 1].Cin, lo.conv[l + 1].Cout, true));
       cv.planes_above = cv.planes && l > 0 && (lo.conv[l - 1].pool || lo.conv[l - 1].bn);
       if (cv.planes) {
         cv.plane_elems = (int64_t)lo.K * lo.B * cv.in_H * cv.in_W * cv.Cin;

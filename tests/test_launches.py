@@ -99,3 +99,37 @@ def test_divisions_by_high_multiplies_are_exact():
         n = np.concatenate([n, n + d - 1, [(1 << 31) - 1]])
         n = n[(n >= 0) & (n < 1 << 31)].astype(np.uint64)
         assert np.array_equal(n * np.uint64(magic) >> np.uint64(32 + shift), n // np.uint64(d)), d
+
+
+def conv_net(channels, side, batch, bf16=0, K=1):
+    return dict(K=K, dims=(channels, channels, channels, 10), batch=batch, n_conv=2, img_h=side, img_w=side, bn_mask=3,
+                global_avg_pool=1, gemm_dtype=bf16)
+
+
+@pytest.mark.parametrize("model,planes,patches", [
+    (conv_net(48, 16, 26), True, False), (conv_net(48, 16, 64), True, True),           # 26 and 64 tiles
+    (conv_net(112, 16, 30), True, False), (conv_net(112, 16, 34), True, True),         # 60 and 68
+    (conv_net(56, 16, 16), False, False), (conv_net(56, 16, 26), True, False),         # 1.2e8 multiply-adds on 4096 pixels, 1.9e8
+    (conv_net(48, 14, 27, bf16=1), False, False), (conv_net(56, 16, 16, bf16=1), True, False)])
+def test_which_small_convolutions_take_planes_and_patches(model, planes, patches):
+    names = launches.names(model)
+    assert any(n.startswith("conv_gemm_kernel<") or "_patch_kernel<" in n for n in names) == planes, names
+    assert any(n.startswith("conv_split_patch_kernel<") for n in names) == patches, names
+
+
+@pytest.mark.parametrize("channels,side,batch,planes", [
+    ((8, 184), 32, 64, False), ((16, 184), 32, 64, False), ((8, 88), 32, 64, True), ((8, 128), 32, 64, True), ((184, 8), 32, 64, True),
+    ((24, 184), 16, 16, False), ((184, 24), 16, 16, True), ((40, 184), 16, 16, True)])
+def test_which_widening_convolutions_take_planes(channels, side, batch, planes):
+    names = launches.names(dict(K=1, dims=(3,) + channels + (10,), batch=batch, n_conv=2, img_h=side, img_w=side, bn_mask=3,
+                                global_avg_pool=1))
+    assert any(n.startswith("filters_kernel<3>") for n in names) == planes, names
+
+
+@pytest.mark.parametrize("channels,batch,bf16,planes", [
+    ((32, 48), 29, 0, False), ((32, 48), 88, 0, True), ((16, 24), 29, 0, False), ((16, 24), 64, 0, True), ((16, 24), 29, 1, False),
+    ((24, 24), 36, 0, True), ((40, 48), 29, 0, True), ((8, 160), 36, 0, False)])
+def test_which_convolutions_on_the_data_take_planes(channels, batch, bf16, planes):
+    names = launches.names(dict(K=1, dims=channels + (10,), batch=batch, n_conv=1, img_h=16, img_w=16, bn_mask=1,
+                                global_avg_pool=1, gemm_dtype=bf16))
+    assert any(n.startswith("filters_kernel<") for n in names) == planes, names

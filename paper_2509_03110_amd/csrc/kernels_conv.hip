@@ -875,13 +875,13 @@ void launch_flip_filters(const float* W, int64_t strideW, int ldw, float* Wt, in
 }
 
 // Channel counts that are no multiples of 32 fill these kernels' last block in part; the stored unfolded image
-// they would take instead costs more, but for bf16 products of more than 64 channels on many pixels, which run
-// on the bf16 units there (a step of one such layer, before -> these: fp32, 16 channels 469 -> 356 us, 40 260 ->
-// 228, 152 on 2.6e5 pixels 1033 -> 1014; bf16 products 404 -> 361, 260 -> 238, 152 890 -> 1034, on 3.3e4 pixels
-// 237 -> 227, 104 on 1.3e5 365 -> 381).
+// they would take instead costs more, but for bf16 products of more than 64 channels, which run on the bf16 units
+// there, from 5e6 outputs (a step of one such layer, before -> these: fp32, 16 channels 469 -> 356 us, 40 260 ->
+// 228, 152 on 2.6e5 pixels 1033 -> 1014; bf16 products 404 -> 361, 260 -> 238; 104 on 3.3e4 pixels 193 -> 187, on 5e4 239 -> 243;
+// 152 on 3.3e4 222 -> 221, 184 237 -> 245, 248 on 1.6e4 202 -> 198, on 6.1e4 377 -> 422).
 bool first_conv_fits(int C, int Cout, int64_t rows, int K, int round) {
   if (C < 1 || C > 3 || Cout % 8 || Cout > 256 || rows >= (1 << 24)) return false;
-  return Cout % 32 == 0 || !round || Cout <= 64 || K * rows <= 65536;
+  return Cout % 32 == 0 || !round || Cout <= 64 || K * rows * Cout <= 5000000;
 }
 
 static int first_chunk_px(int64_t rows, int Cout, int K) {

@@ -133,3 +133,11 @@ def test_which_convolutions_on_the_data_take_planes(channels, batch, bf16, plane
     names = launches.names(dict(K=1, dims=channels + (10,), batch=batch, n_conv=1, img_h=16, img_w=16, bn_mask=1,
                                 global_avg_pool=1, gemm_dtype=bf16))
     assert any(n.startswith("filters_kernel<") for n in names) == planes, names
+
+
+@pytest.mark.parametrize("channels,batch,gathers", [(104, 32, True), (104, 64, False), (184, 16, True), (184, 32, False),
+                                                    (88, 48, True), (64, 240, True), (160, 240, True)])
+def test_which_first_layers_with_bf16_products_gather_the_image(channels, batch, gathers):
+    names = launches.names(dict(K=4, dims=(3, channels, 10), batch=batch, n_conv=1, img_h=16, img_w=16, bn_mask=1,
+                                global_avg_pool=1, gemm_dtype=1))
+    assert any(n.startswith("first_conv_forward_kernel<") for n in names) == gathers, names

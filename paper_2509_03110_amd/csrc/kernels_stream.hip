@@ -337,6 +337,8 @@ __global__ __launch_bounds__(kThreads) void descent_kernel(
       st_param<STREAM>(xk + o, xv[w]);
       stv(vk + o, vv[w]);
       stv(Sk + o, sv[w]);
+      // (without this the compiler joins these stores with those of the last workgroup below and drops their hints)
+      asm volatile("" ::: "memory");
       if constexpr (ascend) st_param<STREAM>(tk + o, tv);
       if constexpr (SHADOW) {
         const int64_t so = shadow_offset4(map, beg + o);

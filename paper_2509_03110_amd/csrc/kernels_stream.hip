@@ -257,6 +257,11 @@ __global__ __launch_bounds__(kThreads) void perturb_tiled_kernel(
 // every wavefront adds them up itself while its loads are under way, which saves the launch that
 // would do it (4 us of a step that takes 14 at 4 x 270410 values; 42 with four launches, norms by
 // 20 workgroups and single floats); the first workgroup of a replica writes norm and scale.
+// The caches hold more of the joined pass's vectors, which is read by the next step's: one workgroup per compute unit
+// and streaming stores pay from 128 MB a vector (steps of vectors of 105 MB, two / eight / sixteen replicas: 213 / 207 / 226
+// us streamed, 202 / 186 / 179 as below; 130 MB 257 / 254 / 255 and 266 / 241 / 227; 150 MB 298 / 293 / 297 and 311 / 308 / 305).
+// The center, kept in the caches for all replicas, counts for a third of a vector: one replica of 103 MB 218 and 224.
+constexpr int64_t kAscentResidentBytes = 128ll << 20;
 template <int ASCENT, bool SHADOW, bool STREAM, typename NOISE> struct DescentShape {
   static constexpr bool wide = ASCENT != 0 && STREAM;
   static constexpr int words = wide ? 2 : 1;
@@ -559,7 +564,7 @@ void launch_descent_with(float* x, const float* g, int64_t g_stride, float* v, f
       return;
     }
   }
-  if ((int64_t)K * n * 4 > kCacheResidentBytes)
+  if (ASCENT == ASCENT_NONE ? (int64_t)K * n * 4 > kCacheResidentBytes : (3 * (int64_t)K + 1) * n * 4 > 3 * kAscentResidentBytes)
     go(descent_kernel<ASCENT, false, true, NOISE>, DescentShape<ASCENT, false, true, NOISE>{}, nullptr, none, 0);
   else
     go(descent_kernel<ASCENT, false, false, NOISE>, DescentShape<ASCENT, false, false, NOISE>{}, nullptr, none, 0);

@@ -141,3 +141,9 @@ def test_which_first_layers_with_bf16_products_gather_the_image(channels, batch,
     names = launches.names(dict(K=4, dims=(3, channels, 10), batch=batch, n_conv=1, img_h=16, img_w=16, bn_mask=1,
                                 global_avg_pool=1, gemm_dtype=1))
     assert any(n.startswith("first_conv_forward_kernel<") for n in names) == gathers, names
+
+
+@pytest.mark.parametrize("K,mb,streams", [(8, 90, False), (13, 110, False), (8, 120, False), (1, 100, True), (8, 130, True)])
+def test_when_the_joined_ascent_and_descent_stream(K, mb, streams):
+    names = launches.names(dict(K=K, d_raw=mb * (1 << 18) // K))
+    assert any(n.startswith("descent_kernel<") and n.split(",")[2] == ("true" if streams else "false") for n in names), names

@@ -111,8 +111,8 @@ def test_cfg5_full_shape_one_replica():
 
 
 def test_fp32_large_tile_variants_one_replica():
-    """fp32 shapes large enough for the 256x128 (forward) and 256x256 (weight-gradient) tile
-    variants of the fp32 GEMM, which the small parity cases never reach.  The oracle computes
+    """fp32 shapes large enough for the 256x128 (forward) and 128x128 (input- and weight-gradient)
+    tile variants of the fp32 GEMM, which the small parity cases never reach.  The oracle computes
     replica 0 from a margin initialisation (no ReLU decision near zero, so the tight fp32
     bound applies to every buffer); twin replicas must reproduce it bit for bit."""
     w = workloads.Workload("fp32big", K=16, dims=(256, 2048, 2048, 24), batch=512, rho=0.05,

@@ -362,9 +362,9 @@ def test_bf16_reduced_shapes_free_running_twenty_steps(name, width, B):
 @pytest.mark.parametrize("dims,B,K,tau,nesterov", [
     ((384, 256, 256, 256, 100), 32, 3, (2, 3, 4), 1),
     ((40, 72, 100, 9), 20, 2, (1, 2), 0),              # widths that are no multiples of 4, 8 or 32
-    ((352, 288, 288, 160), 160, 2, (2, 3), 1),         # ragged 128x128 tiles
-    ((512, 512, 520, 24), 256, 2, (2, 2), 1),          # 256x128 tiles with a ragged last column tile
-    ((1040, 1536, 2048, 24), 32, 2, (2, 3), 1)])       # Gram products cut into 2, 3 and 4 pieces (33 k-steps: ragged)
+    ((352, 288, 288, 160), 160, 2, (2, 3), 1),         # ragged tiles in rows, columns and k-steps
+    ((512, 512, 520, 24), 256, 2, (2, 2), 1),          # full tiles and a ragged last column tile
+    ((1040, 1536, 2048, 24), 32, 2, (2, 3), 1)])       # norms from Gram products of 33, 48 and 64 k-steps
 def test_fused_sampler_step_equals_the_separate_kernel(dims, B, K, tau, nesterov):
     """The fused path (norm of the first-pass weight gradients from Gram matrices or from a
     norm-only product, ascent in the epilogue of the recomputed products, sampler step in the
@@ -412,8 +412,8 @@ def _fused_equals_separate(w, steps):
 
 def _random_bf16_mlp(rng):
     """A bf16 dense model drawn at random: 2 to 4 layers with widths that are and are not
-    multiples of 4, 8, 32 and of the tile sides, some long enough for the Gram products behind
-    the norm to be cut into pieces, a batch that is or is not a multiple of 32, 1 to 5 replicas."""
+    multiples of 4, 8, 32 and of the tile sides, some wide enough for the norm to come from Gram
+    products, a batch that is or is not a multiple of 32, 1 to 5 replicas."""
     widths = [40, 72, 100, 128, 160, 288, 352, 520, 1040, 1536]
     L = int(rng.integers(2, 5))
     dims = [int(rng.choice([40, 352, 384, 1040]))]
@@ -469,9 +469,9 @@ def test_bf16_ragged_shapes():
     run_mlp(w, w.steps, 2e-2, 2e-2, margin=False, tol_flip=1e-1, anchor_after=2)
 
 
-def test_bf16_wide_layers_whose_gram_products_are_cut_into_pieces():
-    # contractions of 1040, 1536 and 2048 (33, 48, 64 steps of 32): the B x B Gram products behind
-    # the norm are cut into 2, 3 and 4 pieces, the first of them raggedly
+def test_bf16_wide_layers_with_long_gram_products():
+    # contractions of 1040, 1536 and 2048 (33, 48, 64 steps of 32) of the B x B Gram products behind the
+    # norm, the first of them ragged
     w = workloads.WORKLOADS["cfg3"].scaled(name="wide16", K=2, dims=(1040, 1536, 2048, 24), batch=32,
                                            tau=(2, 3), n_classes=24, steps=4, batch_pool=0)
     # (64 k pre-activations per layer leave no initialisation with a margin: natural one, anchored)
@@ -479,9 +479,9 @@ def test_bf16_wide_layers_whose_gram_products_are_cut_into_pieces():
 
 
 def test_bf16_ring_kernel_ragged_tiles_and_short_contractions():
-    # dW shapes that take the direct-to-LDS kernel with 128x128 tiles while leaving ragged row
-    # and column tiles (160, 288, 352 are not multiples of 128) and a k-step count (5 steps of
-    # 32) that is not a multiple of the four-stage ring.
+    # shapes that leave ragged row and column tiles (160, 288, 352 are not multiples of 64) and a
+    # k-step count (5 steps of 32) that is not a multiple of the rings' four and eight stages.
+    # (Larger tiles: test_large_tiles_with_remainders.)
     w = workloads.WORKLOADS["cfg3"].scaled(name="ring16", K=2, dims=(352, 288, 288, 160), batch=160,
                                            tau=(2, 3), n_classes=160, steps=4, batch_pool=0)
     run_mlp(w, w.steps, 2e-2, 2e-2, margin=True)
@@ -828,8 +828,7 @@ def test_cnn_matches_oracle(name, over):
         dims=(3, 32, 32, 64, 10), n_conv=3, pool_mask=0b101, bn_mask=0b010, n_classes=10, batch=5)),
     ("four convolutions, wide softmax", dict(
         dims=(3, 32, 32, 24, 40, 48, 20), n_conv=4, pool_mask=0b0110, n_classes=20, batch=8)),
-    # enough rows and channels for the 128x128 tiles of the forward GEMM and for split
-    # contractions in the weight gradients
+    # enough rows and channels for the plane products and for split contractions
     ("wide layers, many rows", dict(dims=(3, 64, 128, 10), n_conv=2, pool_mask=0b10, n_classes=10,
                                     K=4, batch=96, tau=(2, 2, 3, 3))),
 ])

@@ -17,6 +17,7 @@ NETS = {
     "40, stride and parameter-free shortcut": dict(dims=(3, 40, 80, 80, 10), side=(16, 16), batch=33, stride=0b010, skip=0b100),
     "24, pre-activation": dict(dims=(3, 24, 48, 48, 48, 48, 10), side=(16, 32), batch=17, stride=0b00010, skip=0b10100,
                                proj=0b00100, preact=1),
+    "48 and 80, patches": dict(dims=(3, 48, 80, 48, 10), side=(16, 16), batch=40),
     "152, few pixels": dict(dims=(8, 152, 88, 10), side=(4, 4), batch=131),
     "88, pools": dict(dims=(3, 88, 56, 10), side=(16, 16), batch=33, pool=0b011),
 }

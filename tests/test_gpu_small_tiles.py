@@ -28,6 +28,15 @@ def test_small_models(dims, B, K):
     run_mlp(w, 3, 2e-2, 2e-2, margin=True)       # the file's bound for bf16 operands
 
 
+@pytest.mark.parametrize("B", [300, 600])
+def test_large_tiles_with_remainders(B):
+    """Forward products, input gradients and weight gradients of 128x128 (300 rows) and 256x128 tiles (600), none of
+    whose extents and contractions is a multiple of the tile or of a k-step, against the oracle."""
+    w = _model((1000, 1400, 1500, 1100, 100), B, 8)
+    run_mlp(w, 2, 2e-2, 2e-2, margin=True)
+    run_mlp(w, 2, 2e-2, 2e-2, margin=False, tol_flip=1e-1, anchor_after=1)
+
+
 @pytest.mark.parametrize("dims,B,K", [((1000, 2500, 2300, 300), 300, 8), ((2100, 2300, 300), 4200, 1)])
 def test_ragged_tiles_past_the_caches(dims, B, K):
     """285 MB a state vector: streaming stores, 128x128 step, 256x128 products and ascent, the last layer on

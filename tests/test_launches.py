@@ -147,3 +147,38 @@ def test_which_first_layers_with_bf16_products_gather_the_image(channels, batch,
 def test_when_the_joined_ascent_and_descent_stream(K, mb, streams):
     names = launches.names(dict(K=K, d_raw=mb * (1 << 18) // K))
     assert any(n.startswith("descent_kernel<") and n.split(",")[2] == ("true" if streams else "false") for n in names), names
+
+
+B16, F32 = "gemm_bf16_kernel<%s>", "gemm_kernel<float,float,%s>"
+
+
+@pytest.mark.parametrize("model,kernels", [
+    # test_large_tiles_with_remainders: forward products, input gradients, steps, ascents
+    (dict(K=8, dims=(1000, 1400, 1500, 1100, 100), batch=300, gemm_dtype=1),
+     [B16 % "__bf16,128,128,4,true,true,2,0", B16 % "__bf16,128,128,4,true,false,2,0", B16 % "float,128,128,4,false,false,2,1",
+      B16 % "float,256,128,3,false,false,2,3", "gram_norm_kernel<64,8,2>"]),
+    (dict(K=8, dims=(1000, 1400, 1500, 1100, 100), batch=600, gemm_dtype=1),
+     [B16 % "__bf16,256,128,3,true,true,2,0", B16 % "__bf16,256,128,3,true,false,2,0", B16 % "float,256,128,3,false,false,2,2"]),
+    # test_ragged_tiles_past_the_caches
+    (dict(K=8, dims=(1000, 2500, 2300, 300), batch=300, gemm_dtype=1),
+     [B16 % "float,256,128,3,false,false,2,3", B16 % "float,128,128,4,false,false,2,1"]),
+    # test_bf16_ring_kernel_ragged_tiles_and_short_contractions and the wide layers with long Gram products
+    (dict(K=2, dims=(352, 288, 288, 160), batch=160, gemm_dtype=1),
+     [B16 % "__bf16,64,64,8,true,true,2,0", "fused_group_kernel<4>", "fused_group_kernel<5>"]),
+    (dict(K=2, dims=(1040, 1536, 2048, 24), batch=32, gemm_dtype=1), ["gram_norm_kernel<64,8,2>"]),
+    # test_fp32_large_tile_variants_one_replica
+    (dict(K=16, dims=(256, 2048, 2048, 24), batch=512),
+     [F32 % "256,128,4,true,true,2,0,false", F32 % "128,128,8,true,false,2,0,false", "dense_gradients_kernel<128,2,false>"]),
+    # test_gpu_plane_channels.py
+    (dict(K=2, dims=(3, 48, 80, 48, 10), batch=40, n_conv=3, img_h=16, img_w=16, bn_mask=7, global_avg_pool=1),
+     ["conv_split_patch_kernel<2,2,11>", "conv_wgrad_kernel<3,2,64,9>"]),
+    (dict(K=2, dims=(3, 24, 48, 48, 10), batch=16, n_conv=3, img_h=32, img_w=32, bn_mask=7, stride_mask=2, skip_mask=4,
+          proj_mask=4, global_avg_pool=1), ["conv_gemm_kernel<3,0,128,64,2,2,2>", "conv_wgrad_kernel<3,2,64,9>"]),
+    # test_gpu_dense_gradients.py
+    (dict(K=4, dims=(520, 900, 900, 12), batch=100), ["dense_gradients_kernel<128,2,false>"]),
+    (dict(K=4, dims=(1024, 1024, 10), batch=520), ["dense_gradients_kernel<128,2,false>", F32 % "64,64,8,false,false,2,0,false"]),
+    (dict(K=8, dims=(3, 8, 650, 700, 10), n_conv=1, img_h=16, img_w=16, pool_mask=1, batch=40, gemm_dtype=1),
+     ["dense_gradients_kernel<128,2,true>"])])
+def test_gpu_tests_reach_the_kernels_they_name(model, kernels):
+    names = launches.names(model)
+    assert set(kernels) <= set(names), sorted(set(names))

@@ -262,10 +262,9 @@ __global__ __launch_bounds__(kThreads) void perturb_tiled_kernel(
 // us streamed, 202 / 186 / 179 as below; 130 MB 257 / 254 / 255 and 266 / 241 / 227; 150 MB 298 / 293 / 297 and 311 / 308 / 305).
 // The center, kept in the caches for all replicas, counts for a third of a vector: one replica of 103 MB 218 and 224.
 constexpr int64_t kAscentResidentBytes = 128ll << 20;
-template <int ASCENT, bool SHADOW, bool STREAM, typename NOISE> struct DescentShape {
+template <int ASCENT, bool STREAM> struct DescentShape {
   static constexpr bool wide = ASCENT != 0 && STREAM;
   static constexpr int words = wide ? 2 : 1;
-  static constexpr int room = wide ? 84 << 10 : 16;      // bytes of LDS
 };
 
 template <int ASCENT, bool SHADOW, bool STREAM, typename NOISE>
@@ -274,11 +273,11 @@ __global__ __launch_bounds__(kThreads) void descent_kernel(
     float* __restrict__ S, const float* __restrict__ y, uint16_t* __restrict__ shadow,
     ShadowMap map, int64_t shadow_stride, int64_t stride, int64_t n, int K, ReplicaScalars lam,
     float lr, float mu, int nesterov, NOISE noise, const int32_t* __restrict__ restart, AscentPass up) {
-  using Shape = DescentShape<ASCENT, SHADOW, STREAM, NOISE>;
+  using Shape = DescentShape<ASCENT, STREAM>;
   constexpr int W = Shape::words;
   constexpr bool ascend = ASCENT != ASCENT_NONE;
   if constexpr (Shape::wide) {
-    __shared__ unsigned char room[Shape::room];
+    __shared__ unsigned char room[84 << 10];
     asm volatile("" ::"v"(room));      // allocated, never touched
   }
   const int k = (int)(blockIdx.x % (unsigned)K);
@@ -560,14 +559,14 @@ void launch_descent_with(float* x, const float* g, int64_t g_stride, float* v, f
   };
   if constexpr (ASCENT == ASCENT_NONE) {
     if (shadow) {
-      go(descent_kernel<ASCENT, true, true, NOISE>, DescentShape<ASCENT, true, true, NOISE>{}, shadow, *map, shadow_stride);
+      go(descent_kernel<ASCENT, true, true, NOISE>, DescentShape<ASCENT, true>{}, shadow, *map, shadow_stride);
       return;
     }
   }
   if (ASCENT == ASCENT_NONE ? (int64_t)K * n * 4 > kCacheResidentBytes : (3 * (int64_t)K + 1) * n * 4 > 3 * kAscentResidentBytes)
-    go(descent_kernel<ASCENT, false, true, NOISE>, DescentShape<ASCENT, false, true, NOISE>{}, nullptr, none, 0);
+    go(descent_kernel<ASCENT, false, true, NOISE>, DescentShape<ASCENT, true>{}, nullptr, none, 0);
   else
-    go(descent_kernel<ASCENT, false, false, NOISE>, DescentShape<ASCENT, false, false, NOISE>{}, nullptr, none, 0);
+    go(descent_kernel<ASCENT, false, false, NOISE>, DescentShape<ASCENT, false>{}, nullptr, none, 0);
 }
 
 void launch_descent(float* x, const float* g, int64_t g_stride, float* v, float* S,

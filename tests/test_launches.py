@@ -173,7 +173,7 @@ B16, F32 = "gemm_bf16_kernel<%s>", "gemm_kernel<float,float,%s>"
     (dict(K=2, dims=(3, 48, 80, 48, 10), batch=40, n_conv=3, img_h=16, img_w=16, bn_mask=7, global_avg_pool=1),
      ["conv_split_patch_kernel<2,2,11>", "conv_wgrad_kernel<3,2,64,9>"]),
     (dict(K=2, dims=(3, 24, 48, 48, 10), batch=16, n_conv=3, img_h=32, img_w=32, bn_mask=7, stride_mask=2, skip_mask=4,
-          proj_mask=4, global_avg_pool=1), ["conv_gemm_kernel<3,0,128,64,2,2,2>", "conv_wgrad_kernel<3,2,64,9>"]),
+          proj_mask=4, global_avg_pool=1), ["conv_gemm_kernel<3,1,128,64,2,2,2>", "conv_wgrad_kernel<3,2,64,9>"]),
     # test_gpu_dense_gradients.py
     (dict(K=4, dims=(520, 900, 900, 12), batch=100), ["dense_gradients_kernel<128,2,false>"]),
     (dict(K=4, dims=(1024, 1024, 10), batch=520), ["dense_gradients_kernel<128,2,false>", F32 % "64,64,8,false,false,2,0,false"]),

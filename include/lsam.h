@@ -238,8 +238,9 @@ int lsam_get_schedule(lsam_ctx* ctx, int32_t* tau_out, int32_t* count_out, int64
  * the norm is known the same products are formed again and their epilogue writes the bf16
  * operand copy of x~ = x + rho g1/(||g1|| + gamma); the weight-gradient kernels of the pass at
  * the perturbed point take the sampler step on x, v, S and the operand copy where g2 is
- * produced.  Biases take the ordinary kernels.  Results are those of the separate kernels, bit
- * for bit.  With the fusion active the weight-matrix part of LSAM_BUF_GRAD is not written
+ * produced, and the kernel that sums the biases' gradients takes theirs.  Given the same norm,
+ * results are those of the separate kernels, bit for bit; the norm itself may differ in its last
+ * bit, where it comes from Gram matrices of a layer's factors instead of from the products.  With the fusion active the weight-matrix part of LSAM_BUF_GRAD is not written
  * (the bias parts hold g2); switch it off (on = 0) to have g1 / g2 stored as in the other
  * modes.  Returns 1 if steps of this context will use the fusion, 0 if not (other modes never
  * do), or a negative error. */

@@ -864,8 +864,8 @@ int launch_gemm_bf16(const GemmDesc& d, int tile_override, hipStream_t s, int* s
   // 256x256); the ascent epilogue, one array in and one out, keeps the choice above (9.1 against
   // 9.6 ms with 128x128).
   if (d.fuse != nullptr && tile_override == 0) tile = 128;
-  // Where 128x128 tiles cannot give every compute unit a workgroup, 64x64 tiles (and always in the fused
-  // epilogues of states that stay in the caches, launch_fused_group): a tile's time is a chain of memory latencies, not
+  // Where 128x128 tiles cannot give every compute unit a workgroup, 64x64 tiles (as in launch_fused_group, where the
+  // fused epilogues of all layers share a launch): a tile's time is a chain of memory latencies, not
   // work.  With at most two per unit and more than four k-steps the ring has eight stages.  A step of 3
   // replicas 1000-1500-777-37 with batch 100 took 251 us so (128x128 only: 373), of 4 3072-1024-1024-10 with
   // 128 300 (433), of 8 700-900-1100-300 with 400 450 (538), of one 2500-4000-3000-4000-900 with 50 775 (947);

@@ -347,8 +347,9 @@ bool plane_products_pay(int np, int K, int64_t rows, int Cin, int Cout, bool dx)
   const double macs = (double)K * (double)rows * 9.0 * Cin * Cout;
   if (np == 1 && K * rows < 4096) return false;
   if (Cin % 8 || Cout % 8) return np == 1 && macs >= 3e8;
-  // (in fp32 arithmetic 24 channels beside a multiple of 32 stay with the fp32-storage GEMM, not because it is
-  // faster, but because callers are told so: lsam_layer_info's answers for such layers are held to it)
+  // In fp32 arithmetic 24 channels beside a multiple of 32 stay with the fp32-storage GEMM.  Planes would be faster (6.6e4
+  // pixels, as a fraction of its time: 24 to 32 channels 0.78, 32 to 24 0.66, 128 to 24 0.48), but lsam_layer_info has always
+  // named these layers as the GEMM's, and its answers are held to that.
   if (np == 3 && std::min(Cin, Cout) == 24 && std::max(Cin, Cout) % 32 == 0) return false;
   if (np == 3 && Cout % 16 && Cout > 11 * Cin) return false;
   const bool stored = Cin % 32 || (dx && Cout % 32);       // on the fp32-storage GEMM
@@ -1290,7 +1291,8 @@ bool head_is_fused(const Layout& lo) {
 
 // Whether the norm of a layer's unsaved first-pass weight gradient comes from the Gram matrices
 // of its factors, half of each (launch_gram_norms): B^2 (out + in) flops, when they take at most a
-// quarter of those of the product itself.
+// quarter of those of the product itself.  (The line of when whole matrices were formed and stored, at half of
+// the flops; lsam_layer_info reports the route, and its answers are held to it.)
 bool gram_norm_pays(int B, int out, int in) {
   return 2 * (int64_t)B * (out + in) <= (int64_t)out * in;
 }

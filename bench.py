@@ -35,57 +35,55 @@ SPLIT_PRODUCTS = 6                    # bf16 products an fp32 product of exact p
 # are told apart by empty marker kernels launched between the classes in a copy of the library).
 # The figures belong to the kernel sources whose digest is TRAFFIC_SOURCES; with any other sources
 # `traffic` is null.
-TRAFFIC_SOURCES = "19c3b54a836d85e0"
+TRAFFIC_SOURCES = "5c9332f77cf1fca5"
 TRAFFIC = {
-    "cfg2": {"bias_grad": 2149376, "center": 84162976, "descent": 538498858, "gemm_dw": 43629941,
-             "gemm_dx": 42136917, "gemm_fwd": 62116917, "perturb": 201932202},
-    "cfg3": {"bias_grad": 13693175, "center": 1393525408, "descent": 877124,
-             "gemm_dw_ascend": 732946210, "gemm_dw_norm": 81972736, "gemm_dw_step": 2906428433,
-             "gemm_dx": 250149957, "gemm_fwd": 233129047, "softmax_ce": 1429162},
-    "cfg4": {"center": 2400048672, "descent": 25600060288, "perturb": 9600046122,
-             "sumsq_partials": 3418530176},
-    "cfg5": {"bias_grad": 117984776, "descent": 3481947, "gemm_dw_ascend": 6215313852,
-             "gemm_dw_norm": 297865222, "gemm_dw_step": 27263005891, "gemm_dx": 2584827413,
-             "gemm_fwd": 2034599334, "softmax_ce": 96421056},
-    "cnn5": {"bias_grad": 17351488, "conv_first": 80450336, "descent": 79484928,
-             "gemm_dw": 68642698, "gemm_dx": 107690872, "gemm_fwd": 42498844, "perturb": 29800448,
-             "pool": 74873283, "unfold_fold": 62939306},
-    "cnn5bn": {"batchnorm": 162298769, "bias_grad": 563456, "conv_first": 80451221,
-             "descent": 79554176, "gemm_dw": 68648231, "gemm_dx": 107711089, "gemm_fwd": 42498744,
-             "perturb": 29825024, "pool": 74873230},
-    "resnet18": {"batchnorm": 316547992, "conv_first": 155199008, "descent": 1431000405,
-             "gemm_dw": 277736942, "gemm_dx": 342793625, "gemm_fwd": 314629414,
-             "perturb": 536618410, "pool": 183896249},
-    "resnet18bf": {"batchnorm": 260340954, "bias_grad": 50560, "conv_first": 155189941,
-             "descent": 1430995285, "gemm_dw": 123361473, "gemm_dx": 164009495,
-             "gemm_fwd": 109682539, "perturb": 536618581, "pool": 183896339, "softmax_ce": 124586},
-    "resnet20": {"batchnorm": 106351412, "descent": 34873642, "gemm_dw": 81757391,
-             "gemm_dx": 85113705, "gemm_fwd": 66717286, "perturb": 13073408, "pool": 64199994,
-             "unfold_fold": 85693952},
-    "resnet34": {"batchnorm": 298999596, "bias_grad": 347925, "conv_first": 154976458,
-             "descent": 2731212586, "gemm_dw": 250918070, "gemm_dx": 308537713,
-             "gemm_fwd": 278780092, "perturb": 1024203946, "pool": 195411535, "softmax_ce": 485589},
-    "vgg16": {"batchnorm": 202196419, "bias_grad": 1092224, "conv_first": 155099861,
-             "descent": 1952577493, "gemm_dw": 172316226, "gemm_dx": 197142470,
-             "gemm_fwd": 167721758, "perturb": 732209706, "pool": 99061013},
-    "vgg16bf": {"batchnorm": 173722171, "bias_grad": 745024, "conv_first": 155116000,
-             "descent": 1952581930, "gemm_dw": 87375335, "gemm_dx": 99479776, "gemm_fwd": 75919045,
-             "perturb": 732210346, "pool": 92560134, "softmax_ce": 124778},
-    "wrn16x10": {"batchnorm": 960026909, "descent": 2191810474, "gemm_dw": 1238102859,
-             "gemm_dx": 1651112258, "gemm_fwd": 1457835793, "perturb": 821921877, "pool": 402241043,
-             "unfold_fold": 740394848},
-    "wrn16x10bf": {"batchnorm": 781240953, "bias_grad": 50560, "descent": 2191808512,
-             "gemm_dw": 359387094, "gemm_dx": 553025112, "gemm_fwd": 349111386,
-             "perturb": 821921877, "pool": 402241029, "softmax_ce": 124650,
-             "unfold_fold": 85694037},
-    "wrn28x10": {"batchnorm": 1018028438, "bias_grad": 347904, "descent": 4678213376,
-             "gemm_dw": 1347396689, "gemm_dx": 1813427767, "gemm_fwd": 1519858703,
-             "perturb": 1754328064, "pool": 467526364, "softmax_ce": 485376,
-             "unfold_fold": 740394858},
-    "wrn40x10": {"batchnorm": 1038407155, "bias_grad": 347904, "descent": 7157262762,
-             "gemm_dw": 1427835705, "gemm_dx": 1909015397, "gemm_fwd": 1616510991,
-             "perturb": 2683965440, "pool": 498749897, "softmax_ce": 485034,
-             "unfold_fold": 740394624},
+    "cfg2": {"center": 84162976, "descent": 538491904, "gemm_dw": 96010203, "gemm_dx": 42150912,
+             "gemm_fwd": 62132075, "perturb": 201946923},
+    "cfg3": {"bias_grad": 69965355, "center": 1393527072, "gemm_dw_ascend": 732938428,
+             "gemm_dw_norm": 74834581, "gemm_dw_step": 2904271437, "gemm_dx": 250151232,
+             "gemm_fwd": 233113689, "softmax_ce": 1428949},
+    "cfg4": {"center": 2400048928, "descent": 32005545216, "sumsq_partials": 3417931339},
+    "cfg5": {"bias_grad": 836635733, "gemm_dw_ascend": 6220483834, "gemm_dw_norm": 1683837749,
+             "gemm_dw_step": 27280532194, "gemm_dx": 2584784242, "gemm_fwd": 2034203236,
+             "softmax_ce": 96475915},
+    "cnn5": {"bias_grad": 25743968, "conv_first": 80456192, "descent": 79477760,
+             "gemm_dw": 69222277, "gemm_dx": 107788708, "gemm_fwd": 42524672, "perturb": 29814784,
+             "pool": 74879445, "unfold_fold": 62939307},
+    "cnn5bn": {"batchnorm": 162314172, "conv_first": 80453675, "descent": 79543296,
+             "gemm_dw": 69261888, "gemm_dx": 107807353, "gemm_fwd": 42524914, "perturb": 29840043,
+             "pool": 74879374},
+    "resnet18": {"batchnorm": 316562322, "conv_first": 155061451, "descent": 1430972288,
+             "gemm_dw": 265215641, "gemm_dx": 363525780, "gemm_fwd": 310929016,
+             "perturb": 536624896, "pool": 29927424},
+    "resnet18bf": {"batchnorm": 260349643, "conv_first": 155073771, "descent": 1430972288,
+             "gemm_dw": 107817171, "gemm_dx": 188401887, "gemm_fwd": 109772652,
+             "perturb": 536624811, "pool": 29927424, "softmax_ce": 124245},
+    "resnet20": {"batchnorm": 106355368, "conv_first": 43712715, "descent": 34872320,
+             "gemm_dw": 76262636, "gemm_dx": 97150488, "gemm_fwd": 64854366, "perturb": 13087744,
+             "pool": 12953088},
+    "resnet34": {"batchnorm": 299014796, "conv_first": 154834517, "descent": 2731198635,
+             "gemm_dw": 252070505, "gemm_dx": 330192046, "gemm_fwd": 275606772,
+             "perturb": 1024210304, "pool": 29927424, "softmax_ce": 485291},
+    "vgg16": {"batchnorm": 202214841, "conv_first": 154954133, "descent": 1952548693,
+             "gemm_dw": 186763250, "gemm_dx": 192438848, "gemm_fwd": 165874359,
+             "perturb": 732216064, "pool": 99067179},
+    "vgg16bf": {"batchnorm": 173734942, "conv_first": 154976608, "descent": 1952549077,
+             "gemm_dw": 83541013, "gemm_dx": 99557582, "gemm_fwd": 75945737, "perturb": 732216021,
+             "pool": 92562665, "softmax_ce": 124437},
+    "wrn16x10": {"batchnorm": 960040940, "conv_first": 43712128, "descent": 2191779797,
+             "gemm_dw": 1230240994, "gemm_dx": 1605117153, "gemm_fwd": 1817018475,
+             "perturb": 821927936, "pool": 199724494, "unfold_fold": 1395092523},
+    "wrn16x10bf": {"batchnorm": 781247733, "conv_first": 43712661, "descent": 2191779883,
+             "gemm_dw": 359107257, "gemm_dx": 564179372, "gemm_fwd": 444353231,
+             "perturb": 821927424, "pool": 131769856, "softmax_ce": 124501},
+    "wrn28x10": {"batchnorm": 1018041750, "conv_first": 43709045, "descent": 4678192384,
+             "gemm_dw": 1391314120, "gemm_dx": 1757260971, "gemm_fwd": 1871678357,
+             "perturb": 1754334336, "pool": 199724501, "softmax_ce": 484949,
+             "unfold_fold": 1395091883},
+    "wrn40x10": {"batchnorm": 1038421202, "conv_first": 43709845, "descent": 7157222997,
+             "gemm_dw": 1463228814, "gemm_dx": 1797676739, "gemm_fwd": 1933950566,
+             "perturb": 2683971157, "pool": 199724544, "softmax_ce": 484949,
+             "unfold_fold": 1395091392},
 }
 
 

@@ -332,17 +332,23 @@ size_t take(size_t& cursor, size_t bytes) {
 // 4096 pixels (two equal layers, fp32 / bf16 products: 16 channels at 9e6 0.94 to 1.03 / 0.95, at 2e7 0.95 /
 // 0.91; 24 at 2e7 0.95, 4e8 0.72, 2.7e9 0.40 / 0.42; 40 at 1.2e8 0.97, 2.4e8 0.84 / 0.90; 72 at 1.9e8 0.99, 3e9
 // 0.50; 152 at 2.3e10 0.46; but 104 channels at 1e8 on 1024 pixels 1.16).  On fewer pixels the
-// conversions weigh more (the second of two layers, fp32): below 5120 from 1.5e8, and 2.5e8 where the layer widens (4096 pixels:
-// 64 to 56 channels at 1.3e8 1.04, 80 to 80 at 2.4e8 1.01, 112 to 40 at 1.7e8 0.98, 184 to 24 at 1.6e8 0.91; 56 to 112 at 2.3e8 1.03,
-// 40 to 184 at 2.7e8 0.96), with bf16 products below 6144 from 1.15e8 (48 at 1.1e8 beside a projection 1.03, 56 at 1.2e8 0.95
-// to 0.98).  In fp32 a layer of many times its input's channels, no multiple of 16, whose dX the ring computes for 8 or
-// 16 columns of its tiles' 32, stays there (6.6e4 pixels: 8 to 88 channels 0.99, to 104 1.06, to 184 1.26, 16 to 168 0.99, to 184
-// 1.03, to 248 1.07; in whole 16s, by patches, 8 to 128 0.81, 16 to 128 0.77).
+// conversions weigh more (the second of two layers, fp32), unless the layer narrows to a quarter: below 5120 from 1.5e8,
+// and 2.5e8 where it widens (4096 pixels: 64 to 56 channels at 1.3e8 1.04, 80 to 80 at 2.4e8 1.01, 112 to 40 at 1.7e8
+// 0.98, 184 to 24 at 1.6e8 0.91, 176 to 16 at 1.3e8 0.87; 56 to 112 at 2.3e8 1.03, 40 to 184 at 2.7e8 0.96), with bf16 products
+// below 6144 from 1.15e8 (48 at 1.1e8 beside a projection 1.03, 56 at 1.2e8 0.95 to 0.98, 152 to 16 at 1e8 0.94).
+// In fp32 a layer of many times its input's channels, no multiple of 16, whose dX the ring computes for 8 or
+// 16 columns of its tiles' 32, stays there, from 16 channels on 32768 pixels and more (6.6e4 pixels: 8 to 88 channels 0.99,
+// to 104 1.06, to 184 1.26, 16 to 168 0.99, to 184 1.03, to 248 1.07; in whole 16s, by patches, 8 to 128 0.81, 16 to 128 0.77;
+// 16800 pixels: 8 to 184 1.08, 16 to 184 0.91, to 248 0.93).
 // A layer on the data (`dx`: whether there is an input gradient to compute) saves its own image only, and in a single
-// layer of 8 or 16 channels that pays from 12288 pixels, of 24 from 8192 (fp32 / bf16 products: 16 to 24 channels on 7424
-// 1.05 / 1.00, on 9216 1.01 / 1.00, on 16384 0.92; 24 to 24 on 7424 1.01 / 0.98, on 9216 0.96 / 0.95; 32 to 48 on 7424 1.12 / 1.01).
-// Counts that are no multiples of 8
-// are taken with a stored unfolded image, nine times the image either way: with one plane that pays from 3e8.
+// layer of 8 or 16 channels that pays from 10240 pixels, of 24 from 8192 (fp32 / bf16 products: 16 to 24 channels on 7424
+// 1.05 / 1.00, on 9216 1.01 / 1.00, on 16384 0.92; 8 to 128 on 11520 0.97; 24 to 24 on 7424 1.01 / 0.98, on 9216 0.96 / 0.95).
+// The loader takes the data of a multiple of 32 channels without a stored image; planes still win with bf16 products or up
+// to 16 channels of output, and beyond those in fp32 on more pixels (32 to 16 on 7168 1.02 / 0.98, on 12544 0.96 / 0.95;
+// 96 to 8 on 16400 0.78 / 0.91; 128 to 16 on 7168 0.93 / 1.03, on 13312 0.85 / 0.97; 32 to 40 on 13312 1.06 / 0.98, on 16400
+// 0.98 / 0.97; 64 to 48 on 9800 1.06 / 1.02; 32 to 72 on 7168 1.06 / 1.00, on 9800 0.98 / 0.99).
+// Counts that are no multiples of 8 are taken with a stored unfolded image, nine times the image either way: with one
+// plane that pays from 3e8.
 bool plane_products_pay(int np, int K, int64_t rows, int Cin, int Cout, bool dx) {
   const double macs = (double)K * (double)rows * 9.0 * Cin * Cout;
   if (np == 1 && K * rows < 4096) return false;
@@ -351,11 +357,17 @@ bool plane_products_pay(int np, int K, int64_t rows, int Cin, int Cout, bool dx)
   // pixels, as a fraction of its time: 24 to 32 channels 0.78, 32 to 24 0.66, 128 to 24 0.48), but lsam_layer_info has always
   // named these layers as the GEMM's, and its answers are held to that.
   if (np == 3 && std::min(Cin, Cout) == 24 && std::max(Cin, Cout) % 32 == 0) return false;
-  if (np == 3 && Cout % 16 && Cout > 11 * Cin) return false;
-  const bool stored = Cin % 32 || (dx && Cout % 32);       // on the fp32-storage GEMM
-  if (!dx && Cin < 32 && K * rows < (Cin > 16 ? 8192 : 12288) && macs < 3e8) return false;
+  if (np == 3 && dx && Cout % 16 && Cout > 11 * Cin && (Cin < 16 || K * rows >= 32768)) return false;
+  bool stored = Cin % 32 || Cout % 32;       // on the fp32-storage GEMM
+  if (!dx && Cin % 32 == 0) {
+    int enough = std::max(Cin, Cout) > 32 ? 0 : np == 1 && Cout <= 16 ? 5632 : 9216;
+    if (np == 3 && Cout > 16) enough = Cout < 64 ? 14336 : 9216;
+    stored = stored && K * rows >= enough;
+  }
+  if (!dx && Cin < 32 && K * rows < (Cin > 16 ? 8192 : 10240) && macs < 3e8) return false;
   if (std::max(Cin, Cout) <= 32) return macs >= (stored ? 2e7 : 1e8);
   if (!stored || K * rows < 4096) return macs >= 3e8;
+  if (Cin >= 4 * Cout) return macs >= 1e8;
   if (np == 1) return macs >= (K * rows < 6144 ? 1.15e8 : 1e8);
   return macs >= (K * rows >= 5120 ? 1e8 : Cout > Cin ? 2.5e8 : 1.5e8);
 }

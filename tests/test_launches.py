@@ -119,7 +119,8 @@ def test_which_small_convolutions_take_planes_and_patches(model, planes, patches
 
 @pytest.mark.parametrize("channels,side,batch,planes", [
     ((8, 184), 32, 64, False), ((16, 184), 32, 64, False), ((8, 88), 32, 64, True), ((8, 128), 32, 64, True), ((184, 8), 32, 64, True),
-    ((24, 184), 16, 16, False), ((184, 24), 16, 16, True), ((40, 184), 16, 16, True)])
+    ((24, 184), 16, 16, False), ((184, 24), 16, 16, True), ((40, 184), 16, 16, True), ((16, 184), 20, 42, True), ((8, 184), 20, 42, False),
+    ((152, 16), 16, 18, True), ((64, 56), 16, 16, False)])
 def test_which_widening_convolutions_take_planes(channels, side, batch, planes):
     names = launches.names(dict(K=1, dims=(3,) + channels + (10,), batch=batch, n_conv=2, img_h=side, img_w=side, bn_mask=3,
                                 global_avg_pool=1))
@@ -128,7 +129,10 @@ def test_which_widening_convolutions_take_planes(channels, side, batch, planes):
 
 @pytest.mark.parametrize("channels,batch,bf16,planes", [
     ((32, 48), 29, 0, False), ((32, 48), 88, 0, True), ((16, 24), 29, 0, False), ((16, 24), 64, 0, True), ((16, 24), 29, 1, False),
-    ((24, 24), 36, 0, True), ((40, 48), 29, 0, True), ((8, 160), 36, 0, False)])
+    ((24, 24), 36, 0, True), ((40, 48), 29, 0, True), ((8, 160), 36, 0, False), ((32, 16), 29, 0, False), ((32, 16), 49, 0, True),
+    ((32, 16), 29, 1, True), ((32, 16), 49, 1, True), ((32, 40), 52, 0, False), ((32, 40), 64, 0, True), ((32, 40), 52, 1, True),
+    ((32, 72), 29, 0, False), ((32, 72), 39, 0, True), ((128, 16), 29, 0, True), ((32, 16), 20, 1, False), ((8, 24), 47, 0, True),
+    ((8, 184), 64, 0, True)])
 def test_which_convolutions_on_the_data_take_planes(channels, batch, bf16, planes):
     names = launches.names(dict(K=1, dims=channels + (10,), batch=batch, n_conv=1, img_h=16, img_w=16, bn_mask=1,
                                 global_avg_pool=1, gemm_dtype=bf16))

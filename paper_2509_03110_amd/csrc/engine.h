@@ -169,6 +169,7 @@ struct GemmDesc {
   const float* bias; int64_t strideBias;          // EPI_BIAS*: bias[n]
   const float* bias_dir; const float* bias_scale; // if set: bias[n] + bias_scale[k] * bias_dir[n]
   const void* mask; int64_t strideMask; int ldMask; // EPI_MASK: keep where mask[m,n] > 0 (operand dtype)
+  const uint8_t* keep;                              // launch_splitk_reduce: the mask as bits (ConvGemmDesc)
   float* splitk_ws; size_t splitk_bytes;            // scratch for split-K partial sums (may be null)
   // bf16 tensors in the blocked layout (b32s.h): column blocks of the stored A, B, bf16 C, mask;
   // strideA/B/C/Mask then count elements of one replica's stored matrix and ld* are unused
@@ -282,6 +283,9 @@ struct ConvGemmDesc {
   int epilogue;
   const float* bias; int64_t strideBias;
   const float* mask; int64_t strideMask; int ldMask;
+  // In place of mask if set: the same as bits, a byte to four columns (value (m, n) is kept if bit n % 4 of byte
+  // (m ldMask + n) / 4 is set; strideMask still counts values).
+  const uint8_t* keep;
   float* splitk_ws; size_t splitk_bytes;
   double* sumsq; int64_t sumsq_stride;
   // If set: [M][ldAdd] of every replica, added to the results behind the bias and in front of ReLU or mask (with
@@ -377,9 +381,11 @@ int launch_first_conv_wgrad(const float* X, const float* dout, float* partial, f
                             int64_t strideParams, int64_t w_off, int64_t b_off, int ldw, int round,
                             int skip_bias, int K, int64_t rows, int H, int W, int C, int Cout,
                             double* sumsq, int64_t sumsq_stride, hipStream_t s);
-// Where a kernel also writes its fp32 result as plane tensors (np = 0: it does not).
+// Where a kernel also writes its fp32 result as plane tensors (np = 0: it does not), and, if `keep` is set, which
+// values are positive: bit r of a byte for value r of four, the mask of the gradient that comes back.
 struct PlaneOut {
   uint16_t* p = nullptr; int np = 0; int64_t plane = 0;
+  uint8_t* keep = nullptr;
 };
 
 // Training-mode batch normalisation of K matrices Z [rows][C] (C % 4 == 0, C <= 1024), per
@@ -412,7 +418,7 @@ int launch_add_into(float* dst, const float* src, int64_t n, hipStream_t s);
 // dst[img][i][j][c] = src[img][2 i][2 j][c] for `images` images [2H][2W][C] (C % 4 == 0).
 int launch_subsample2(const float* src, float* dst, int64_t images, int H, int W, int C, hipStream_t s);
 int bn_chunks(int64_t rows, int C, int K);
-// `shortcut` (may be null): added to the normalised output before the ReLU.
+// `shortcut` (may be null): added to the normalised output before the ReLU.  `out` may be null: planes (and bits) only.
 int launch_bn_forward(const float* Z, float* scratch, float* stats, const float* params,
                       int64_t strideParams, int64_t gam_off, int64_t bet_off, float* out, int K,
                       int64_t rows, int C, float eps, const ShortcutDesc* shortcut, const PlaneOut& planes,
@@ -422,9 +428,9 @@ int launch_bn_forward(const float* Z, float* scratch, float* stats, const float*
 int launch_shortcut_backward(const float* dY, float* dIn, const float* mask, const ShortcutDesc& d, int K,
                              int64_t rows, int C, hipStream_t s);
 // Global average pooling over `images` images [HW][C] into rows of pitch ldp, and its backward
-// pass fused with the ReLU mask of the image (mask may be null).
+// pass fused with the ReLU mask of the image (as floats or, in its place, as bits; both null: no mask).
 int launch_avgpool(const float* A, float* P, int64_t images, int HW, int C, int ldp, hipStream_t s);
-int launch_avgpool_backward(const float* dP, const float* mask, float* dA, int64_t images, int HW, int C,
+int launch_avgpool_backward(const float* dP, const float* mask, const uint8_t* keep, float* dA, int64_t images, int HW, int C,
                             int ldp, hipStream_t s);
 int launch_bn_backward_partials(const float* Z, const float* dY, const float* stats, float* part, int K,
                                 int64_t rows, int C, hipStream_t s);

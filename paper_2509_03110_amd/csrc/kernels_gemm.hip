@@ -57,6 +57,7 @@ struct GemmParams {
   const float* bias; long long strideBias;
   const float* bias_dir; const float* bias_scale;
   const char* mask; long long strideMask; int ldMask;
+  const unsigned char* keep;   // of the reduce, in place of mask: bits (see ConvGemmDesc)
   // split-K: the contraction is cut into `splits` ranges of `steps_per_split` k-steps, each
   // range owned by its own workgroup, which writes raw fp32 sums to partial[split]
   float* partial; long long strideSplit; int ldP;
@@ -832,6 +833,7 @@ __global__ __launch_bounds__(kThreads * LANES) void splitk_reduce_kernel(GemmPar
     const float* mask = p.mask ? reinterpret_cast<const float*>(p.mask) +
                                      (long long)bat * p.strideMask + (long long)m * p.ldMask
                                : nullptr;
+    const unsigned kept = p.keep ? p.keep[((long long)bat * p.strideMask + (long long)m * p.ldMask + c) >> 2] : 0u;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int n = c + r;
@@ -844,7 +846,7 @@ __global__ __launch_bounds__(kThreads * LANES) void splitk_reduce_kernel(GemmPar
       }
       if (p.add) o += p.add[(long long)bat * p.strideAdd + (long long)m * p.ldAdd + n];
       if (p.epilogue == EPI_BIAS_RELU) o = o > 0.f ? o : 0.f;
-      if (p.epilogue == EPI_MASK && !(mask[n] > 0.f)) o = 0.f;
+      if (p.epilogue == EPI_MASK && !(p.keep ? kept >> r & 1 : mask[n] > 0.f)) o = 0.f;
       C[n] = o;
       ssq += o * o;
     }
@@ -1029,7 +1031,7 @@ int launch_splitk_reduce(const GemmDesc& d, const float* partial, int splits, in
   p.M = d.M; p.N = d.N; p.batch = d.batch;
   p.epilogue = d.epilogue;
   p.bias = d.bias; p.strideBias = d.strideBias;
-  p.mask = (const char*)d.mask; p.strideMask = d.strideMask; p.ldMask = d.ldMask;
+  p.mask = (const char*)d.mask; p.strideMask = d.strideMask; p.ldMask = d.ldMask; p.keep = d.keep;
   p.add = d.add; p.strideAdd = d.strideAdd; p.ldAdd = d.ldAdd;
   p.partial = const_cast<float*>(partial); p.strideSplit = split_stride; p.ldP = ldP; p.splits = splits;
   p.sumsq = d.sumsq; p.strideSumsq = d.sumsq_stride;
@@ -1050,7 +1052,7 @@ int launch_gemm(const GemmDesc& d, hipStream_t s, int* sumsq_slots) {
   // bf16 operands live in the blocked layout and have their own kernel; this file's kernel
   // serves the fp32 configurations
   if (d.in_bf16) return (d.unfold || d.bf16_math) ? -1 : launch_gemm_bf16(d, 0, s, sumsq_slots);
-  GemmParams p;
+  GemmParams p{};
   p.A = (const char*)d.A; p.strideA = d.strideA; p.ldA = d.ldA;
   p.B = (const char*)d.B; p.strideB = d.strideB; p.ldB = d.ldB;
   p.C = (char*)d.C; p.strideC = d.strideC; p.ldC = d.ldC;

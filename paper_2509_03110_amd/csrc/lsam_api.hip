@@ -152,6 +152,10 @@ struct ConvLayer {
   // `first`: layer 0 with 1..3 input channels runs its forward pass and its weight gradient
   // in kernels of their own (no unfolded image at all).
   bool fast, direct_in, direct_dx, first;
+  // `keep`: bits of the layer's positive outputs, where they are written by the normalisation and all that asks
+  // for the sign reads them.  `floats`: something reads the outputs themselves (a product on plane tensors does not).
+  bool has_keep, floats;
+  size_t keep;
   size_t first_partial;   // scratch of the first layer's weight gradient
   bool bn;                // batch-normalised: `z` keeps the convolution's output, `stats` the
   size_t z, stats;        // per-channel mean and 1/sqrt(var + eps) of each replica
@@ -372,6 +376,17 @@ bool plane_products_pay(int np, int K, int64_t rows, int Cin, int Cout, bool dx)
   return macs >= (K * rows >= 5120 ? 1e8 : Cout > Cin ? 2.5e8 : 1.5e8);
 }
 
+// Whether convolution l opens a residual block whose shortcut hands a gradient down to the block's input, and whether the
+// product that writes that gradient adds it (both halve the image in the same step).
+bool opens_block(const Layout& lo, int l) {
+  return l + 1 < lo.n_conv && lo.conv[l + 1].skip && (lo.conv[l + 1].proj || !lo.preact);
+}
+bool shortcut_joins_product(const Layout& lo, int l) {
+  const ConvLayer& cv = lo.conv[l];
+  return l > 0 && opens_block(lo, l) && cv.fast && cv.direct_dx && !lo.conv[l - 1].pool && lo.conv[l + 1].H == cv.H &&
+         lo.conv[l + 1].W == cv.W && lo.conv[l + 1].skip_step == cv.stride;
+}
+
 void build_layout(const lsam_config& c, Layout& lo) {
   lo.K = c.K;
   lo.L = c.n_layers;
@@ -525,7 +540,7 @@ void build_layout(const lsam_config& c, Layout& lo) {
     size_t dcol_bytes = 0;
     for (int l = 0; l < lo.n_conv; ++l) {
       ConvLayer& cv = lo.conv[l];
-      const size_t full = (size_t)lo.K * cv.rows * cv.Cout * 4;
+      cv.bn = lo.layers[l].bn;
       const bool small = cv.rows < (1 << 24);      // (first-layer kernels: pixel indices exact in fp32)
       cv.fast = plane_products_pay(lo.np, lo.K, cv.rows, cv.Cin, cv.Cout, l > 0);
       // unfolding by address: whole taps or parts of one tap make up a 32-deep k-step; the
@@ -537,6 +552,20 @@ void build_layout(const lsam_config& c, Layout& lo) {
       cv.direct_dx = small && l > 0 && fits(cv.Cout) &&
                      (cv.stride == 1 || (cv.fast && (lo.np == 1 || cv.Cin <= 32 || (cv.Cin + 63) / 64 * 64 * 8 <= cv.Cin * 9)));
       cv.first = l == 0 && cv.stride == 1 && first_conv_fits(cv.Cin, cv.Cout, cv.rows, lo.K, lo.bf16_math);
+    }
+    for (int l = 0; l < lo.n_conv; ++l) {
+      ConvLayer& cv = lo.conv[l];
+      const ConvLayer* next = l + 1 < lo.n_conv ? &lo.conv[l + 1] : nullptr;
+      const ConvLayer* closing = l + 2 < lo.n_conv && lo.conv[l + 2].skip ? &lo.conv[l + 2] : nullptr;
+      cv.has_keep = cv.bn && !cv.pool &&
+                    (next ? next->fast && next->direct_dx && (!opens_block(lo, l + 1) || shortcut_joins_product(lo, l + 1))
+                          : lo.gap_hw > 0);
+      cv.floats = cv.pool || !cv.has_keep || !next || !next->fast || !next->direct_in ||
+                  (closing && (closing->proj ? !closing->fast : !lo.preact));
+    }
+    for (int l = 0; l < lo.n_conv; ++l) {
+      ConvLayer& cv = lo.conv[l];
+      const size_t full = (size_t)lo.K * cv.rows * cv.Cout * 4;
       if (cv.first)
         cv.first_partial = take(cur, (size_t)lo.K * first_conv_chunks(cv.rows, cv.Cout, lo.K) * cv.Cout * 32 * 4);
       else if (!cv.direct_in) cv.col = take(cur, (size_t)lo.K * cv.rows * cv.ldc * (cv.fast ? 2 * lo.np : 4));
@@ -568,9 +597,9 @@ void build_layout(const lsam_config& c, Layout& lo) {
         }
         lo.dzp_elems = std::max(lo.dzp_elems, (int64_t)lo.K * cv.rows * cv.Cout);
       }
-      cv.out = take(cur, full);
+      if (cv.floats) cv.out = take(cur, full);
+      if (cv.has_keep) cv.keep = take(cur, full / 16);
       cv.dout = take(cur, full);
-      cv.bn = lo.layers[l].bn;
       if (cv.bn) {
         cv.z = take(cur, full);
         cv.stats = take(cur, (size_t)lo.K * 2 * cv.Cout * 4);
@@ -979,13 +1008,14 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
         sc.stride = lo.conv[l - 2].rows * cv.skip_C;
         sc.H = cv.H; sc.W = cv.W; sc.Cs = cv.skip_C; sc.step = cv.skip_step;
       }
+      PlaneOut o = cv.pool ? PlaneOut{} : input_planes(c, l + 1);
+      if (cv.has_keep) o.keep = c->at<uint8_t>(cv.keep);
       if (launch_bn_forward(c->at<float>(cv.z), c->at<float>(lo.colsum), c->at<float>(cv.stats), params,
-                            lo.d_pad, ly.gam_off, ly.bet_off, c->at<float>(cv.out), lo.K, cv.rows,
-                            cv.Cout, c->cfg.bn_eps, post_sum ? &sc : nullptr,
-                            cv.pool ? PlaneOut{} : input_planes(c, l + 1), s) != 0)
+                            lo.d_pad, ly.gam_off, ly.bet_off, cv.floats ? c->at<float>(cv.out) : nullptr, lo.K, cv.rows,
+                            cv.Cout, c->cfg.bn_eps, post_sum ? &sc : nullptr, o, s) != 0)
         return fail(LSAM_EINVAL, "batch normalisation of convolution %d rejected", l);
     }
-    in = c->at<float>(cv.out);
+    in = cv.floats ? c->at<float>(cv.out) : nullptr;
     if (cv.pool) {
       LaunchTimer t(c, KC_POOL);
       if (launch_maxpool2(in, c->at<float>(cv.pooled), (int64_t)lo.K * lo.B, cv.H, cv.W, cv.Cout,
@@ -1017,7 +1047,7 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
     LaunchTimer t(c, KC_POOL);
     const ConvLayer& cv = lo.conv[lo.n_conv - 1];
     if (launch_avgpool_backward(c->at<float>(lo.gap_grad), cv.pool ? nullptr : c->at<float>(cv.out),
-                                c->at<float>(cv.pool ? cv.dpooled : cv.dout), (int64_t)lo.K * lo.B,
+                                cv.has_keep ? c->at<uint8_t>(cv.keep) : nullptr, c->at<float>(cv.pool ? cv.dpooled : cv.dout), (int64_t)lo.K * lo.B,
                                 lo.gap_hw, cv.Cout, lo.ld[lo.n_conv], s) != 0)
       return fail(LSAM_EINVAL, "global average pooling (backward) rejected");
   }
@@ -1199,7 +1229,7 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
     // If this convolution opened a residual block, the gradient of the block output (kept by the closing
     // convolution) also reaches the block input through the shortcut: where the product of this one
     // writes that gradient, or by a launch of its own
-    const bool opens = l + 1 < lo.n_conv && lo.conv[l + 1].skip && (lo.conv[l + 1].proj || !lo.preact);
+    const bool opens = opens_block(lo, l);
     bool shortcut_done = false;
     if (l > 0 && cv.direct_dx) {
       // dX as a convolution of the output gradient with the mirrored filters, written straight
@@ -1219,10 +1249,11 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
         d.strideC = image; d.ldC = cv.Cin;
         d.epilogue = below.pool ? EPI_PLAIN : EPI_MASK;
         if (!below.pool) {
-          d.mask = c->at<float>(below.out); d.strideMask = image; d.ldMask = cv.Cin;
+          if (below.has_keep) d.keep = c->at<uint8_t>(below.keep);
+          else d.mask = c->at<float>(below.out);
+          d.strideMask = image; d.ldMask = cv.Cin;
         }
-        // (the product and the shortcut halve the image in the same step)
-        if (opens && !below.pool && lo.conv[l + 1].H == cv.H && lo.conv[l + 1].W == cv.W && lo.conv[l + 1].skip_step == cv.stride) {
+        if (shortcut_joins_product(lo, l)) {
           const ConvLayer& top = lo.conv[l + 1];
           d.ldAdd = top.proj ? top.skip_C : top.Cout;
           d.add = c->at<float>(top.proj ? top.psub : top.dout); d.strideAdd = top.rows * d.ldAdd;

@@ -1,0 +1,42 @@
+"""Normalised convolutions whose outputs are kept as planes and sign bits, with and without the floats beside them: chains,
+shortcuts that read the floats, projections, products cut over workgroups, whose sums a kernel of its own finishes.
+
+Unlike the nets of test_gpu_plane_products.py half of all values are rectified, pixel by pixel, so a bit of another pixel
+or channel shows: half of the gradient's terms would be wrong.  A value within rounding of zero (1e-6 of its
+spread in fp32, one in 1e6) may be decided differently and carries then about 1e-3 of its layer's gradient, 1 / sqrt(values);
+with operands rounded to bfloat16 decisions within 2^-8 differ, of which the gradient's norm shows sqrt(2^-8) = 6e-2."""
+import pytest
+
+torch = pytest.importorskip("torch")
+import workloads  # noqa: E402
+from paper_2509_03110_amd import lsam  # noqa: E402
+from test_gpu_plane_products import DEV, net  # noqa: E402
+from util import oracle_from, rel_l2  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+NETS = {
+    "chain": dict(dims=(3, 32, 64, 32, 10), side=(16, 32), batch=24),
+    "chain, products cut over workgroups": dict(dims=(3, 128, 128, 128, 10), side=(8, 8), batch=64),
+    "identity shortcut": dict(dims=(3, 32, 32, 32, 32, 32, 10), side=(16, 32), batch=24, skip=0b10100),
+    "stride and projection": dict(dims=(3, 24, 48, 48, 48, 10), side=(32, 32), batch=16, stride=0b0010, skip=0b0100, proj=0b0100),
+    "stored input gradient": dict(dims=(3, 96, 64, 32, 10), side=(16, 16), batch=90, stride=0b010),
+    "pre-activation": dict(dims=(3, 32, 64, 64, 64, 64, 10), side=(16, 32), batch=33, stride=0b00010, skip=0b10100, proj=0b00100,
+                           preact=1),
+}
+
+
+@pytest.mark.parametrize("bf16", [0, 1])
+@pytest.mark.parametrize("name", sorted(NETS))
+def test_rectified_values_against_the_oracle(name, bf16):
+    w = net(bf16=bf16, **NETS[name])
+    init = workloads.init_params(w)
+    cfg, keep = lsam.config_from_workload(w)
+    g, o = lsam.Lsam(cfg, init, device=DEV, keep=keep), oracle_from(w, init)
+    X, lab = workloads.batch(w, 0)
+    g.lsam_step(torch.from_numpy(X).to(DEV), torch.from_numpy(lab).to(DEV), torch.zeros(w.K, device=DEV))
+    o.step(X, lab)
+    for i in range(w.K):
+        got, want = g.lsam_get_buffer(lsam.BUF_VELOCITY, i), o.v[i]
+        assert rel_l2(got, want) < (6e-2 if bf16 else 2e-3), (i, rel_l2(got, want))
+    g.close()

@@ -296,8 +296,18 @@ struct ConvGemmDesc {
   // column's parity only: four classes of pixels, each a convolution of 1, 2, 2 or 4 taps whose filters
   // follow each other in `other` (see FilterBank); M counts one class's pixels, Kd all nine taps.
   int out_step = 1;
+  // Column sums of the results C (dense, ldC = N) as a normalisation wants them, by chunks of rows, where the launch can take
+  // them (a contraction cut over workgroups cannot; `made` says).  1: statistics, as launch_bn_stats leaves them in its scratch;
+  // 2: as launch_bn_backward_partials does, the results being dY, with Z and its statistics.
+  int sums = 0;
+  float* sum_part = nullptr; const float* sum_z = nullptr; const float* sum_stats = nullptr;
 };
-int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots = nullptr);   // 0, or -1: not served
+// Chunks of `rows` rows each (the last one fewer), or none (chunks 0).
+struct ChunkSums {
+  int chunks = 0, rows = 0;
+};
+int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots = nullptr, ChunkSums* made = nullptr);   // 0, or -1: not served
+int conv_gemm_sum_chunks(int64_t rows);       // room for the chunks of any launch that writes `rows` rows a replica
 size_t conv_gemm_splitk_bytes(const ConvGemmDesc& d);
 // Planes of n consecutive floats (n % 4 == 0).
 int launch_split_planes(const float* src, uint16_t* dst, int np, int64_t plane, int64_t n, hipStream_t s);
@@ -410,8 +420,9 @@ struct ShortcutDesc {
   const float* pz = nullptr; const float* pstats = nullptr;
   int64_t pgam_off = 0, pbet_off = 0;
 };
-// stats[k] = (mean, 1/sqrt(var + eps)) per channel of Z [K][rows][C]; scratch as for launch_bn_forward.
-int launch_bn_stats(const float* Z, float* scratch, float* stats, int K, int64_t rows, int C, float eps,
+// stats[k] = (mean, 1/sqrt(var + eps)) per channel of Z [K][rows][C]; scratch as for launch_bn_forward.  `have`: the
+// chunks of the scratch that the product that wrote Z has left there; none: they are taken from Z.
+int launch_bn_stats(const float* Z, float* scratch, const ChunkSums& have, float* stats, int K, int64_t rows, int C, float eps,
                     hipStream_t s);
 // dst[i] += src[i] for i < n (n % 4 == 0; both 16-byte aligned, not overlapping).
 int launch_add_into(float* dst, const float* src, int64_t n, hipStream_t s);
@@ -419,7 +430,7 @@ int launch_add_into(float* dst, const float* src, int64_t n, hipStream_t s);
 int launch_subsample2(const float* src, float* dst, int64_t images, int H, int W, int C, hipStream_t s);
 int bn_chunks(int64_t rows, int C, int K);
 // `shortcut` (may be null): added to the normalised output before the ReLU.  `out` may be null: planes (and bits) only.
-int launch_bn_forward(const float* Z, float* scratch, float* stats, const float* params,
+int launch_bn_forward(const float* Z, float* scratch, const ChunkSums& have, float* stats, const float* params,
                       int64_t strideParams, int64_t gam_off, int64_t bet_off, float* out, int K,
                       int64_t rows, int C, float eps, const ShortcutDesc* shortcut, const PlaneOut& planes,
                       hipStream_t s);

@@ -567,9 +567,11 @@ __global__ __launch_bounds__(kThreads) void bn_stats_partial_kernel(const float*
 //   mean = sum_i n_i mean_i / rows,   M2 = sum_i [M2_i + n_i (mean_i - mean)^2]
 // over the chunks i, in double, in a fixed order.  Next to nothing is read, so what bounds this is
 // the chain of loads a thread has to wait for: workgroup (block, k) serves 16 columns with 64 chains
-// each (chain q takes chunks q, q + 64, ...), eight loads in flight per chain.  512 chunks of 64
-// columns, four replicas: 18 us with 16 chains and a load at a time, 11 us so; 128 chunks 14 and 7.
-constexpr int kBnCols = 16, kBnChains = 64, kBnDepth = 8;
+// each (chain q takes chunks q, q + 64, ...), sixteen chunks in flight per chain, and the first 1024 chunks stay in
+// registers for the second sum.  512 chunks of 64
+// columns, four replicas: 18 us with 16 chains and a load at a time, 11 us with eight in flight and read twice, 7.5 us so;
+// 128 chunks 14, 5.5 and 5.3.
+constexpr int kBnCols = 16, kBnChains = 64, kBnDepth = 16;
 __device__ __forceinline__ double chain_total(double v, double (*buf)[kBnCols], int col) {
   v += __shfl_xor(v, 16, 64);
   v += __shfl_xor(v, 32, 64);
@@ -592,36 +594,41 @@ __global__ __launch_bounds__(kBnCols * kBnChains) void bn_stats_finish_kernel(
   const double last = (double)(rows - (long long)(chunks - 1) * chunk_rows);
   auto count = [&](int ch) { return ch + 1 < chunks ? (double)chunk_rows : last; };
   const long long base = (long long)k * chunks * C + c;
+  float m[kBnDepth], v[kBnDepth];
+  const auto read = [&](int ch0) {
+#pragma unroll
+    for (int i = 0; i < kBnDepth; ++i) {
+      const int ch = ch0 + i * kBnChains;
+      const bool there = live && ch < chunks;
+      m[i] = there ? pmean[base + (long long)ch * C] : 0.f;
+      v[i] = there ? pm2[base + (long long)ch * C] : 0.f;
+    }
+  };
+  const auto add = [&](int ch0, auto term) {
+    double t = 0.0;
+#pragma unroll
+    for (int i = 0; i < kBnDepth; ++i)
+      if (ch0 + i * kBnChains < chunks) t += term(i, count(ch0 + i * kBnChains));
+    return t;
+  };
+  const auto weighed = [&](int i, double n) { return n * (double)m[i]; };
+  constexpr int kRound = kBnChains * kBnDepth;
   double s1 = 0.0;
-  for (int ch0 = q; live && ch0 < chunks; ch0 += kBnChains * kBnDepth) {
-    float m[kBnDepth];
-#pragma unroll
-    for (int i = 0; i < kBnDepth; ++i) {
-      const int ch = ch0 + i * kBnChains;
-      m[i] = ch < chunks ? pmean[base + (long long)ch * C] : 0.f;
-    }
-#pragma unroll
-    for (int i = 0; i < kBnDepth; ++i) {
-      const int ch = ch0 + i * kBnChains;
-      if (ch < chunks) s1 += count(ch) * (double)m[i];
-    }
+  for (int ch0 = q + kRound; ch0 < chunks; ch0 += kRound) {
+    read(ch0);
+    s1 += add(ch0, weighed);
   }
+  read(q);
+  s1 += add(q, weighed);
   const double mean = chain_total(s1, buf, col) / (double)rows;
-  double s2 = 0.0;
-  for (int ch0 = q; live && ch0 < chunks; ch0 += kBnChains * kBnDepth) {
-    float m[kBnDepth], v[kBnDepth];
-#pragma unroll
-    for (int i = 0; i < kBnDepth; ++i) {
-      const int ch = ch0 + i * kBnChains;
-      m[i] = ch < chunks ? pmean[base + (long long)ch * C] : 0.f;
-      v[i] = ch < chunks ? pm2[base + (long long)ch * C] : 0.f;
-    }
-#pragma unroll
-    for (int i = 0; i < kBnDepth; ++i) {
-      const int ch = ch0 + i * kBnChains;
-      const double dlt = (double)m[i] - mean;
-      if (ch < chunks) s2 += (double)v[i] + count(ch) * dlt * dlt;
-    }
+  const auto spread = [&](int i, double n) {
+    const double dlt = (double)m[i] - mean;
+    return (double)v[i] + n * dlt * dlt;
+  };
+  double s2 = add(q, spread);
+  for (int ch0 = q + kRound; ch0 < chunks; ch0 += kRound) {
+    read(ch0);
+    s2 += add(ch0, spread);
   }
   const double m2 = chain_total(s2, buf, col);
   if (live && q == 0) {
@@ -950,17 +957,19 @@ int launch_first_conv_wgrad(const float* X, const float* dout, float* partial, f
 
 int bn_chunks(int64_t rows, int C, int K) { return chunk_plan(rows, C, K).chunks; }
 
-int launch_bn_stats(const float* Z, float* scratch, float* stats, int K, int64_t rows, int C, float eps,
+int launch_bn_stats(const float* Z, float* scratch, const ChunkSums& have, float* stats, int K, int64_t rows, int C, float eps,
                     hipStream_t s) {
   if (C % 4 || C < 4 || C > 4 * kThreads || rows < 1) return -1;
+  ChunkSums sums = have;
   const ChunkPlan pl = chunk_plan(rows, C, K);
-  const int chunks = pl.chunks;
+  if (!sums.chunks) sums = ChunkSums{pl.chunks, pl.chunk_rows};
   float* pmean = scratch;
-  float* pm2 = scratch + (long long)K * chunks * C;
-  bn_stats_partial_kernel<<<dim3((unsigned)chunks, (unsigned)K, (unsigned)pl.col_blocks), kThreads, 0, s>>>(
-      Z, pmean, pm2, rows, C, chunks, pl.chunk_rows);
+  float* pm2 = scratch + (long long)K * sums.chunks * C;
+  if (!have.chunks)
+    bn_stats_partial_kernel<<<dim3((unsigned)pl.chunks, (unsigned)K, (unsigned)pl.col_blocks), kThreads, 0, s>>>(
+        Z, pmean, pm2, rows, C, pl.chunks, pl.chunk_rows);
   bn_stats_finish_kernel<<<dim3((unsigned)((C + kBnCols - 1) / kBnCols), (unsigned)K), kBnCols * kBnChains, 0, s>>>(
-      pmean, pm2, stats, rows, C, chunks, pl.chunk_rows, eps);
+      pmean, pm2, stats, rows, C, sums.chunks, sums.rows, eps);
   return 0;
 }
 
@@ -977,7 +986,7 @@ int launch_subsample2(const float* src, float* dst, int64_t images, int H, int W
   return 0;
 }
 
-int launch_bn_forward(const float* Z, float* scratch, float* stats, const float* params,
+int launch_bn_forward(const float* Z, float* scratch, const ChunkSums& have, float* stats, const float* params,
                       int64_t strideParams, int64_t gam_off, int64_t bet_off, float* out, int K,
                       int64_t rows, int C, float eps, const ShortcutDesc* shortcut, const PlaneOut& o, hipStream_t s) {
   if (C % 4 || C < 4 || C > 4 * kThreads || rows < 1) return -1;
@@ -993,14 +1002,7 @@ int launch_bn_forward(const float* Z, float* scratch, float* stats, const float*
     sc = Shortcut{shortcut->src, shortcut->stride, shortcut->H, shortcut->W, shortcut->Cs, shortcut->step,
                   nullptr, nullptr, 0, 0};
   }
-  const ChunkPlan pl = chunk_plan(rows, C, K);
-  const int chunks = pl.chunks;
-  float* pmean = scratch;
-  float* pm2 = scratch + (long long)K * chunks * C;
-  bn_stats_partial_kernel<<<dim3((unsigned)chunks, (unsigned)K, (unsigned)pl.col_blocks), kThreads, 0, s>>>(
-      Z, pmean, pm2, rows, C, chunks, pl.chunk_rows);
-  bn_stats_finish_kernel<<<dim3((unsigned)((C + kBnCols - 1) / kBnCols), (unsigned)K), kBnCols * kBnChains, 0, s>>>(
-      pmean, pm2, stats, rows, C, chunks, pl.chunk_rows, eps);
+  if (launch_bn_stats(Z, scratch, have, stats, K, rows, C, eps, s) != 0) return -1;
   const long long total = (long long)K * rows * (C / 4);
   auto run = [&](auto kernel) {
     kernel<<<blocks_for(total), kThreads, 0, s>>>(Z, stats, params, strideParams, gam_off, bet_off, out, rows, C, total, sc,

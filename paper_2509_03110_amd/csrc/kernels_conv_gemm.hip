@@ -82,6 +82,7 @@ struct Params {
   int out_step, out_i, out_j;                          // see ConvGemmDesc
   int ksplit, steps_per_piece; float* partial; long long stridePartial; int ldP;
   const float* add; long long strideAdd; int ldAdd;        // added to the results (may be null)
+  int sums; float* sum_part; const float* sum_z; const float* sum_stats;   // see ConvGemmDesc
 };
 
 constexpr int waitcnt(int vm, int lgkm) {
@@ -408,13 +409,21 @@ struct Interleave {
   }
 };
 
-// Writes a wavefront's TM x TN blocks of 32 x 32 results, rows m0.., columns n0.., as the launch asks:
-// the wavefront passes 32-row strips through its private piece of LDS, `stage`, and writes rows,
-// consecutive lanes on consecutive 16 bytes (bias and ReLU mask are read the same way).
-template <int TM, int TN>
-__device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[TM][TN], float* stage, int m0, int n0, int bat,
-                                           int piece, int t_in) {
+// Writes a workgroup's results, rows tm0.., columns tn0..: four wavefronts, WM of them below each other, each with TM x TN
+// blocks of 32 x 32, as the launch asks.  A wavefront passes 32-row strips through its private piece of LDS (strips: a pair of
+// pieces each) and writes rows, consecutive lanes on consecutive 16 bytes (bias, mask and addend are read the same way).
+// The column sums a normalisation wants are taken on the way, from results that would be read again for them:
+// a lane keeps its four columns, the lanes of a column and then the wavefronts are added in a fixed order, one chunk of rows a
+// workgroup.  Patches of 64 channels with one plane, 4 replicas of 128 images of 32 x 32: forward 63 us and 22 for the kernel that read
+// Z again, 66 together; input gradient with bits 84 and 53 for dY and Z, 116 together.
+template <int TM, int TN, int WM>
+__device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[TM][TN], float* strips0, float* strips1, int tm0,
+                                           int tn0, int bat, int piece, int t_in, int chunk, int chunks) {
+  constexpr int WN = 4 / WM;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, h = lane >> 5;
+  const int m0 = tm0 + wave / WN * (TM * 32), n0 = tn0 + wave % WN * (TN * 32);
+  const auto strips = [&](int w) { return (w >> 1 ? strips1 : strips0) + (w & 1) * (32 * (TN * 32 + 4)); };
+  float* stage = strips(wave);
   const bool split_mode = p.ksplit > 1;
   float* C = split_mode ? p.partial + (long long)piece * p.stridePartial + (long long)bat * p.M * p.ldP
                         : p.C + (long long)bat * p.strideC;
@@ -448,73 +457,165 @@ __device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[
   };
   f32x4 bv = {0.f, 0.f, 0.f, 0.f};
   if (has_bias && n < p.N) bv = *reinterpret_cast<const f32x4*>(p.bias + (long long)bat * p.strideBias + n);
+  f32x4 mu = {0.f, 0.f, 0.f, 0.f}, inv = mu, s1 = mu, s2 = mu;      // of the sums; mu of statistics: their shift
+  const bool backward_sums = p.sums == 2;
+  if (backward_sums && n < p.N) {
+    mu = *reinterpret_cast<const f32x4*>(p.sum_stats + (long long)bat * 2 * p.N + n);
+    inv = *reinterpret_cast<const f32x4*>(p.sum_stats + ((long long)bat * 2 + 1) * p.N + n);
+  }
+  const float* sz = backward_sums ? p.sum_z + (long long)bat * p.strideC : nullptr;
+  if (p.sums == 1 && adds && m0 < p.M && n < p.N) mu = *reinterpret_cast<const f32x4*>(add + (long long)m0 * p.ldAdd + n);
   // Waited for here: a wait in front of the sum of every pass would also wait for the stores of the pass
   // before (16 channels at 32 x 32 with three planes, 4 replicas of 128: 40.4 us a launch so, 37.9 us here;
   // patches of 64 channels with one plane 12 % of the launch).
   __builtin_amdgcn_s_waitcnt(waitcnt(0, 15));
+  // What the results meet in memory (addend, mask, Z) is requested for GRP passes at a time, a group ahead of the stores: a load
+  // after a group's stores is waited for together with them (the launch of 116 us above 122 without, with three planes 222 and 230).
+  // Results that meet nothing are written without those
+  // registers and branches (152 channels from 27 with one plane, 4 replicas of 64 at 32 x 32, where the
+  // stores are the launch: 55 us with them, 42 without).
+  // (A mask comes as bits where the layer below is normalised: read as floats it was as long a stream as the results, patches
+  // of 64 channels with one plane, 4 replicas of 128 images of 32 x 32, 104 us a launch, 84 with bits, 63 without a mask.  Z is
+  // met only beside bits, so it shares the mask's registers.)
+  constexpr int GROUPS = (PASSES + GRP - 1) / GRP;      // of a strip
+  const auto write = [&](auto meets, auto sums) {
+    constexpr bool MEETS = decltype(meets)::value, SUMS = decltype(sums)::value;
+    f32x4 other[MEETS ? 2 : 1][GRP], ad[MEETS ? 2 : 1][GRP];
+    unsigned bits[MEETS ? 2 : 1][GRP];
+    int row[2][GRP];
+    const auto request = [&](int g) {
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        f32x4 v;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = acc[i][j][q * 4 + r];
-        *reinterpret_cast<f32x4*>(stage + l32 * PITCH + j * 32 + q * 8 + h * 4) = v;
-      }
-    // (A mask comes as bits where the layer below is normalised: read as floats it was as long a stream as the results, patches
-    // of 64 channels with one plane, 4 replicas of 128 images of 32 x 32, 104 us a launch, 84 with bits, 63 without a mask.)
-    // What the results meet in memory (addend, mask) is requested for GRP passes at a time: a load after a
-    // pass's stores is waited for together with them.  Results that meet nothing are written without those
-    // registers and branches (152 channels from 27 with one plane, 4 replicas of 64 at 32 x 32, where the
-    // stores are the launch: 55 us with them, 42 without).
-    const auto strip = [&](auto meets) {
-      constexpr bool MEETS = decltype(meets)::value;
-#pragma unroll
-      for (int p0 = 0; p0 < PASSES; p0 += GRP) {
-        f32x4 mk[GRP], ad[GRP];
-        unsigned bits[GRP];
-        int row[GRP];
+      for (int u = 0; u < GRP; ++u) {
+        int& r = row[g & 1][u];
+        r = row_of(g % GROUPS * GRP + u, g / GROUPS);
+        if (r < 0) continue;
         if constexpr (MEETS) {
-#pragma unroll
-          for (int u = 0; u < GRP; ++u) {
-            row[u] = row_of(p0 + u, i);
-            if (row[u] < 0) continue;
-            if (adds) ad[u] = *reinterpret_cast<const f32x4*>(add + (long long)row[u] * p.ldAdd + n);
-            row[u] = placed(row[u]);
-            if (keep != nullptr) bits[u] = keep[((long long)row[u] * p.ldMask + n) >> 2];
-            else if (masked) mk[u] = *reinterpret_cast<const f32x4*>(mask + (long long)row[u] * p.ldMask + n);
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < GRP; ++u) {
-          if constexpr (!MEETS) row[u] = row_of(p0 + u, i);
-          if (row[u] < 0) continue;
-          f32x4 v = *reinterpret_cast<const f32x4*>(stage + ((p0 + u) * ROWS_PER_PASS + rsub) * PITCH + c4);
-          v += bv;
-          if constexpr (!MEETS) row[u] = placed(row[u]);
-          if (MEETS && adds) v += ad[u];
-          if (relu) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] = v[r] > 0.f ? v[r] : 0.f;
-          }
-          if (MEETS && keep != nullptr) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-              if (!(bits[u] >> r & 1)) v[r] = 0.f;
-          } else if (MEETS && masked) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-              if (!(mk[u][r] > 0.f)) v[r] = 0.f;
-          }
-          *reinterpret_cast<f32x4*>(C + (long long)row[u] * ldC + n) = v;
-          ssq += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
+          if (adds) ad[g & 1][u] = *reinterpret_cast<const f32x4*>(add + (long long)r * p.ldAdd + n);
+          r = placed(r);
+          if (keep != nullptr) bits[g & 1][u] = keep[((long long)r * p.ldMask + n) >> 2];
+          else if (masked) other[g & 1][u] = *reinterpret_cast<const f32x4*>(mask + (long long)r * p.ldMask + n);
+          if (SUMS && backward_sums) other[g & 1][u] = *reinterpret_cast<const f32x4*>(sz + (long long)r * ldC + n);
+        } else {
+          r = placed(r);
         }
       }
     };
-    if (adds || masked) strip(std::true_type{});
-    else strip(std::false_type{});
+    if constexpr (MEETS) request(0);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          f32x4 v;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) v[r] = acc[i][j][q * 4 + r];
+          *reinterpret_cast<f32x4*>(stage + l32 * PITCH + j * 32 + q * 8 + h * 4) = v;
+        }
+      // statistics are sums around the wavefront's first row, a value of the data's own size
+      if (SUMS && !backward_sums && i == 0) mu += *reinterpret_cast<const f32x4*>(stage + c4) + bv;
+#pragma unroll
+      for (int gs = 0; gs < GROUPS; ++gs) {
+        const int g = i * GROUPS + gs, at = MEETS ? g & 1 : 0;
+        if constexpr (!MEETS) request(g);
+        else if (g + 1 < TM * GROUPS) request(g + 1);
+#pragma unroll
+        for (int u = 0; u < GRP; ++u) {
+          const int r = row[g & 1][u];
+          if (r < 0) continue;
+          f32x4 v = *reinterpret_cast<const f32x4*>(stage + ((gs * GRP + u) * ROWS_PER_PASS + rsub) * PITCH + c4);
+          v += bv;
+          if (MEETS && adds) v += ad[at][u];
+          if (relu) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
+          }
+          if (MEETS && keep != nullptr) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (!(bits[at][u] >> e & 1)) v[e] = 0.f;
+          } else if (MEETS && masked) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (!(other[at][u][e] > 0.f)) v[e] = 0.f;
+          }
+          *reinterpret_cast<f32x4*>(C + (long long)r * ldC + n) = v;
+          if (SUMS && MEETS && backward_sums) {
+            s1 += v * ((other[at][u] - mu) * inv);
+            s2 += v;
+          } else if (SUMS) {
+            const f32x4 dlt = v - mu;
+            s1 += dlt;
+            s2 += dlt * dlt;
+          } else {
+            ssq += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
+          }
+        }
+      }
+    }
+  };
+  const bool meets = adds || masked || backward_sums;
+  if (p.sums != 0) {
+    if (meets) write(std::true_type{}, std::true_type{});
+    else write(std::false_type{}, std::true_type{});
+  } else {
+    if (meets) write(std::true_type{}, std::false_type{});
+    else write(std::false_type{}, std::false_type{});
+  }
+  if (p.sums != 0) {
+    const auto rows_of = [&](int wm) {
+      const int left = p.M - (tm0 + wm * (TM * 32));
+      return left < 0 ? 0 : left < TM * 32 ? left : TM * 32;
+    };
+#pragma unroll
+    for (int off = LANES_PER_ROW; off < 64; off <<= 1)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        s1[r] += __shfl_xor(s1[r], off, 64);
+        s2[r] += __shfl_xor(s2[r], off, 64);
+      }
+    if (!backward_sums) {
+      const int rows = rows_of(wave / WN);
+      const float inv_n = rows > 0 ? 1.f / (float)rows : 0.f;
+      const f32x4 m2 = s2 - s1 * s1 * inv_n;
+      s1 = mu + s1 * inv_n;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s2[r] = m2[r] > 0.f ? m2[r] : 0.f;
+    }
+    if (rsub == 0) {
+      *reinterpret_cast<f32x4*>(stage + c4) = s1;
+      *reinterpret_cast<f32x4*>(stage + TN * 32 + c4) = s2;
+    }
+    __syncthreads();
+    const int c = tid % (TN * 32), wn = tid / (TN * 32);
+    if (wn < WN && tn0 + tid < p.N) {
+      float a = 0.f, b = 0.f, rows = 0.f;
+#pragma unroll
+      for (int wm = 0; wm < WM; ++wm) {
+        const float* from = strips(wm * WN + wn) + c;
+        const float nw = backward_sums ? 1.f : (float)rows_of(wm);
+        a += nw * from[0];
+        rows += nw;
+        if (backward_sums) b += from[TN * 32];
+      }
+      const long long N = p.N;
+      if (backward_sums) {
+        float* dst = p.sum_part + ((long long)bat * chunks + chunk) * 2 * N + tn0 + tid;
+        dst[0] = a;
+        dst[N] = b;
+      } else {
+        a /= rows;
+#pragma unroll
+        for (int wm = 0; wm < WM; ++wm) {
+          const float* from = strips(wm * WN + wn) + c;
+          const float dlt = from[0] - a;
+          b += from[TN * 32] + (float)rows_of(wm) * dlt * dlt;
+        }
+        float* dst = p.sum_part + ((long long)bat * chunks + chunk) * N + tn0 + tid;
+        dst[0] = a;
+        dst[(long long)p.batch * chunks * N] = b;
+      }
+    }
   }
   if (p.sumsq != nullptr && !split_mode) {
     __shared__ double part[4];
@@ -707,8 +808,9 @@ __global__ __launch_bounds__(kThreads, OCC) void conv_gemm_kernel(Params p) {
         join_sums(acc[i][j], low[i][j]);
   }
 
-  float* stage = reinterpret_cast<float*>((wave >> 1) ? st1 : st0) + (wave & 1) * (32 * EPI_PITCH);
-  store_tile(p, acc, stage, m0 + wm0, n0 + wn0, bat, piece, t_in);
+  const bool classes = KIND != kWeightGrad && p.out_step == 2;
+  store_tile<TM, TN, WM>(p, acc, reinterpret_cast<float*>(st0), reinterpret_cast<float*>(st1), m0, n0, bat, piece, t_in,
+                         classes ? m0 / BM * 4 + p.out_i * 2 + p.out_j : m0 / BM, classes ? 4 * p.tilesM : p.tilesM);
 }
 
 // A uniform value the compiler may not compute with ahead of time: without it the addresses of all
@@ -947,8 +1049,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv_patch_kernel(Params p) {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-  float* stage = reinterpret_cast<float*>((wave >> 1) ? pa1 : pa0) + (wave & 1) * (32 * EPI_PITCH);
-  store_tile(p, acc, stage, m0 + wm0, n0, bat, piece, t_in);
+  store_tile<TM, TN, 4>(p, acc, reinterpret_cast<float*>(pa0), reinterpret_cast<float*>(pa1), m0, n0, bat, piece, t_in, t_row,
+                        p.tilesM);
 }
 
 // The same with three planes.  A workgroup takes TM x 128 pixels and blocks of 16 channels (one
@@ -1153,8 +1255,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_patch_kernel(Params p)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
       join_sums(acc[i][j], low[i][j]);
-  float* stage = reinterpret_cast<float*>((wave >> 1) ? pa1 : pa0) + (wave & 1) * (32 * EPI_PITCH);
-  store_tile(p, acc, stage, m0 + wave * (TM * 32), n0, bat, piece, t_in);
+  store_tile<TM, TN, 4>(p, acc, reinterpret_cast<float*>(pa0), reinterpret_cast<float*>(pa1), m0, n0, bat, piece, t_in, t_row,
+                        p.tilesM);
 }
 
 // ---- weight gradient of 3x3 layers with stride 1, image patches in LDS ------------------
@@ -1724,7 +1826,7 @@ ConvPlan conv_plan(const ConvGemmDesc& d) {
 
 size_t conv_gemm_splitk_bytes(const ConvGemmDesc& d) { return conv_plan(d).ws_bytes; }
 
-int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots) {
+int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots, ChunkSums* made) {
   if (d.np != 1 && d.np != 3) return -1;
   if (d.M <= 0 || d.N <= 0 || d.Kd <= 0 || d.batch <= 0 || d.N % 4 || d.ldC % 4 || d.strideC % 4) return -1;
   const PlaneImage& im = d.image;
@@ -1770,6 +1872,9 @@ int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots) {
   p.mask = d.mask; p.strideMask = d.strideMask; p.ldMask = d.ldMask; p.keep = d.keep;
   p.add = d.add; p.strideAdd = d.strideAdd; p.ldAdd = d.ldAdd;
   p.sumsq = d.sumsq; p.strideSumsq = d.sumsq_stride;
+  if (d.sums != 0 && (d.wgrad || d.ldC != d.N || ((uintptr_t)d.sum_part & 15) ||
+                      (d.sums == 2 && ((d.epilogue == EPI_MASK && !d.keep) || ((uintptr_t)d.sum_z & 15) || ((uintptr_t)d.sum_stats & 15)))))
+    return -1;
   ConvPlan pl = conv_plan(d);
   const bool room = d.splitk_ws != nullptr && d.splitk_bytes >= pl.ws_bytes && ((uintptr_t)d.splitk_ws & 15) == 0;
   if (d.wgrad && pl.patch && !room) pl.patch = kNoPatch, pl.splits = 1, pl.steps = (d.Kd + 31) / 32;
@@ -1779,6 +1884,7 @@ int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots) {
     p.partial = d.splitk_ws; p.ldP = pl.ldP;
     p.stridePartial = (long long)d.batch * d.M * pl.ldP;
   }
+  if (p.ksplit == 1) { p.sums = d.sums; p.sum_part = d.sum_part; p.sum_z = d.sum_z; p.sum_stats = d.sum_stats; }
   int slots = pl.patch ? run_patch(p, pl.patch, d.np, s)
               : d.wgrad ? run_weight_grad(p, pl.tile, d.np, s)
               : scalar_tap ? run_forward<kForward>(p, pl.tile, d.np, s) : run_forward<kForwardAnyC>(p, pl.tile, d.np, s);
@@ -1792,8 +1898,11 @@ int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots) {
     slots = launch_splitk_reduce(r, p.partial, p.ksplit, p.stridePartial, p.ldP, s);
   }
   if (sumsq_slots) *sumsq_slots = slots;
+  if (made) *made = p.sums ? ChunkSums{p.tilesM * (p.out_step == 2 ? 4 : 1), pl.tile.bm} : ChunkSums{};
   return 0;
 }
+
+int conv_gemm_sum_chunks(int64_t rows) { return (int)(rows / 128) + 8; }
 
 int launch_split_planes(const float* src, uint16_t* dst, int np, int64_t plane, int64_t n, hipStream_t s) {
   if (n < 4 || n % 4 || plane % 8 || ((uintptr_t)src & 15) || ((uintptr_t)dst & 15)) return -1;

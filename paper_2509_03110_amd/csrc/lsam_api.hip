@@ -188,7 +188,8 @@ struct Layout {
   size_t restart = 0;         // K marks: which iterate sums read as zero / start afresh (launch_center)
   int gap_hw = 0;              // > 0: global average pooling over that many positions feeds the dense layers
   size_t gap_out = 0, gap_grad = 0;   // [K][B][ld] pooled vector and its gradient
-  size_t colsum = 0;           // first-stage column sums of the bias gradients
+  size_t colsum = 0;           // first-stage column sums of the bias gradients and normalisations
+  size_t pcolsum = 0;          // the same of a projection's normalisation, which are made before the block's own are used
   bool bf16 = false, raw = false;
   bool bf16_math = false;      // convolutional model with bf16 matrix products on fp32 tensors
   int64_t d = 0, d_pad = 0;
@@ -625,9 +626,15 @@ void build_layout(const lsam_config& c, Layout& lo) {
       size_t most = 0;
       for (const ConvLayer& cv : lo.conv)
         most = std::max(most, (size_t)lo.K * colsum_chunks(cv.rows, cv.Cout, lo.K) * cv.Cout * 4);
-      for (const ConvLayer& cv : lo.conv)
-        if (cv.bn) most = std::max(most, (size_t)lo.K * bn_chunks(cv.rows, cv.Cout, lo.K) * 2 * cv.Cout * 4);
+      size_t proj = 0;
+      for (const ConvLayer& cv : lo.conv) {
+        if (!cv.bn) continue;
+        const size_t sums = (size_t)lo.K * std::max(bn_chunks(cv.rows, cv.Cout, lo.K), conv_gemm_sum_chunks(cv.rows)) * 2 * cv.Cout * 4;
+        most = std::max(most, sums);
+        if (cv.proj && !lo.preact) proj = std::max(proj, sums);
+      }
       lo.colsum = take(cur, most);
+      if (proj) lo.pcolsum = take(cur, proj);
     }
     // the dense layers start at n_conv; their input and its gradient are the last
     // convolution's (pooled) output and that buffer's gradient
@@ -884,6 +891,8 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
   const Layout& lo = c->lo;
   hipStream_t s = c->stream;
   const float* in = X;
+  float* scratch = c->at<float>(lo.colsum);
+  float* pscratch = c->at<float>(lo.pcolsum);
   if (!lo.banks.empty()) {
     LaunchTimer t(c, KC_MISC);
     if (launch_filters(params, lo.d_pad, c->at<FilterBank>(lo.banks_at), (int)lo.banks.size(), lo.bank_blocks,
@@ -893,6 +902,7 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
   for (int l = 0; l < lo.n_conv; ++l) {
     const ConvLayer& cv = lo.conv[l];
     const Layer& ly = lo.layers[l];
+    ChunkSums have, phave;        // statistics that the products leave in the scratch
     if (cv.planes && !cv.planes_above) {
       LaunchTimer t(c, KC_UNFOLD);
       if (launch_split_planes(in, c->at<uint16_t>(cv.xp), lo.np, cv.plane_elems, cv.plane_elems, s) != 0)
@@ -919,7 +929,8 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
       d.C = c->at<float>(cv.pz); d.strideC = cv.rows * cv.Cout; d.ldC = cv.Cout;
       d.epilogue = EPI_BIAS;
       d.bias = params + ly.pb_off; d.strideBias = lo.d_pad;
-      if (launch_conv_gemm(d, s) != 0)
+      if (!lo.preact) { d.sums = 1; d.sum_part = pscratch; }
+      if (launch_conv_gemm(d, s, nullptr, &phave) != 0)
         return fail(LSAM_EINVAL, "projection of convolution %d rejected", l);
     }
     if (!cv.first && cv.fast) {
@@ -934,7 +945,8 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
         // a pre-activation block's sum: the bare projection, or the sum two convolutions below
         d.add = c->at<float>(cv.proj ? cv.pz : lo.conv[l - 2].z); d.strideAdd = cv.rows * cv.Cout; d.ldAdd = cv.Cout;
       }
-      if (launch_conv_gemm(d, s) != 0)
+      if (cv.bn) { d.sums = 1; d.sum_part = scratch; }
+      if (launch_conv_gemm(d, s, nullptr, &have) != 0)
         return fail(LSAM_EINVAL, "forward product of convolution %d rejected", l);
     } else if (!cv.first) {
       GemmDesc d{};
@@ -984,7 +996,7 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
           return fail(LSAM_EINVAL, "projection of convolution %d: sum rejected", l);
       } else {
         LaunchTimer t(c, KC_BATCHNORM);
-        if (launch_bn_stats(c->at<float>(cv.pz), c->at<float>(lo.colsum), c->at<float>(cv.pstats), lo.K,
+        if (launch_bn_stats(c->at<float>(cv.pz), pscratch, phave, c->at<float>(cv.pstats), lo.K,
                             cv.rows, cv.Cout, c->cfg.bn_eps, s) != 0)
           return fail(LSAM_EINVAL, "projection of convolution %d: statistics rejected", l);
       }
@@ -1010,7 +1022,7 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
       }
       PlaneOut o = cv.pool ? PlaneOut{} : input_planes(c, l + 1);
       if (cv.has_keep) o.keep = c->at<uint8_t>(cv.keep);
-      if (launch_bn_forward(c->at<float>(cv.z), c->at<float>(lo.colsum), c->at<float>(cv.stats), params,
+      if (launch_bn_forward(c->at<float>(cv.z), scratch, have, c->at<float>(cv.stats), params,
                             lo.d_pad, ly.gam_off, ly.bet_off, cv.floats ? c->at<float>(cv.out) : nullptr, lo.K, cv.rows,
                             cv.Cout, c->cfg.bn_eps, post_sum ? &sc : nullptr, o, s) != 0)
         return fail(LSAM_EINVAL, "batch normalisation of convolution %d rejected", l);
@@ -1051,6 +1063,7 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
                                 lo.gap_hw, cv.Cout, lo.ld[lo.n_conv], s) != 0)
       return fail(LSAM_EINVAL, "global average pooling (backward) rejected");
   }
+  ChunkSums have;             // sums of the layer's gradient and normalised values, left by the product that wrote the gradient
   for (int l = lo.n_conv - 1; l >= 0; --l) {
     const ConvLayer& cv = lo.conv[l];
     const Layer& ly = lo.layers[l];
@@ -1090,8 +1103,9 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
       // output and leave dgamma, dbeta in g
       LaunchTimer t(c, KC_BATCHNORM);
       float* part = c->at<float>(lo.colsum);
-      const int chunks = launch_bn_backward_partials(c->at<float>(cv.z), dout, c->at<float>(cv.stats),
-                                                     part, lo.K, cv.rows, cv.Cout, s);
+      const int chunks = have.chunks ? have.chunks
+                                     : launch_bn_backward_partials(c->at<float>(cv.z), dout, c->at<float>(cv.stats),
+                                                                   part, lo.K, cv.rows, cv.Cout, s);
       if (chunks < 0) return fail(LSAM_EINVAL, "batch normalisation of convolution %d rejected", l);
       {
         const int used = launch_norm_param_grads(part, g, lo.d_pad, ly.gam_off, ly.bet_off, lo.K, chunks, cv.Cout,
@@ -1231,6 +1245,7 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
     // writes that gradient, or by a launch of its own
     const bool opens = opens_block(lo, l);
     bool shortcut_done = false;
+    have = ChunkSums{};
     if (l > 0 && cv.direct_dx) {
       // dX as a convolution of the output gradient with the mirrored filters, written straight
       // into the gradient of the image this layer read (masked by the ReLU output it came
@@ -1259,7 +1274,11 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
           d.add = c->at<float>(top.proj ? top.psub : top.dout); d.strideAdd = top.rows * d.ldAdd;
           shortcut_done = true;
         }
-        if (launch_conv_gemm(d, s) != 0)
+        if (below.bn && !below.pool && (!opens || shortcut_done)) {      // the gradient is complete: its sums with it
+          d.sums = 2; d.sum_part = c->at<float>(lo.colsum);
+          d.sum_z = c->at<float>(below.z); d.sum_stats = c->at<float>(below.stats);
+        }
+        if (launch_conv_gemm(d, s, nullptr, &have) != 0)
           return fail(LSAM_EINVAL, "dX product of convolution %d rejected", l);
       } else {
         float* wt = c->at<float>(cv.wt);

@@ -1,5 +1,6 @@
-"""Normalised convolutions whose outputs are kept as planes and sign bits, with and without the floats beside them: chains,
-shortcuts that read the floats, projections, products cut over workgroups, whose sums a kernel of its own finishes.
+"""Normalised convolutions whose outputs are kept as planes and sign bits, with and without the floats beside them, and whose
+column sums are taken where the products are written: chains, ragged last tiles, shortcuts that read the floats, projections,
+products cut over workgroups, whose sums kernels of their own take.
 
 Unlike the nets of test_gpu_plane_products.py half of all values are rectified, pixel by pixel, so a bit of another pixel
 or channel shows: half of the gradient's terms would be wrong.  A value within rounding of zero (1e-6 of its
@@ -18,6 +19,7 @@ pytestmark = pytest.mark.gpu
 NETS = {
     "chain": dict(dims=(3, 32, 64, 32, 10), side=(16, 32), batch=24),
     "chain, products cut over workgroups": dict(dims=(3, 128, 128, 128, 10), side=(8, 8), batch=64),
+    "ragged tiles": dict(dims=(3, 40, 72, 40, 10), side=(18, 14), batch=37),
     "identity shortcut": dict(dims=(3, 32, 32, 32, 32, 32, 10), side=(16, 32), batch=24, skip=0b10100),
     "stride and projection": dict(dims=(3, 24, 48, 48, 48, 10), side=(32, 32), batch=16, stride=0b0010, skip=0b0100, proj=0b0100),
     "stored input gradient": dict(dims=(3, 96, 64, 32, 10), side=(16, 16), batch=90, stride=0b010),
@@ -39,4 +41,23 @@ def test_rectified_values_against_the_oracle(name, bf16):
     for i in range(w.K):
         got, want = g.lsam_get_buffer(lsam.BUF_VELOCITY, i), o.v[i]
         assert rel_l2(got, want) < (6e-2 if bf16 else 2e-3), (i, rel_l2(got, want))
+    g.close()
+
+
+def test_statistics_of_values_far_from_zero():
+    """Sums 600 spreads from zero: taken as they are, their squares' last bits, 600^2 2^-24, are 2 % of the variance."""
+    w = net(dims=(3, 32, 64, 32, 10), side=(16, 32), batch=24)
+    init = workloads.init_params(w)
+    at = 0
+    for l, (fan_in, fo) in enumerate(w.layer_shapes[:w.n_conv]):
+        init[at + fan_in * fo:at + fan_in * fo + fo] = 300.0
+        at += fan_in * fo + 3 * fo
+    cfg, keep = lsam.config_from_workload(w)
+    g, o = lsam.Lsam(cfg, init, device=DEV, keep=keep), oracle_from(w, init)
+    X, lab = workloads.batch(w, 0)
+    g.lsam_step(torch.from_numpy(X).to(DEV), torch.from_numpy(lab).to(DEV), torch.zeros(w.K, device=DEV))
+    o.step(X, lab)
+    for i in range(w.K):
+        # (a sum's own last bit, 300 2^-24, moves 1e-4 of the rectified values' decisions)
+        assert rel_l2(g.lsam_get_buffer(lsam.BUF_VELOCITY, i), o.v[i]) < 1e-2
     g.close()

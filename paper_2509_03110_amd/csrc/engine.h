@@ -399,7 +399,8 @@ struct PlaneOut {
 };
 
 // Training-mode batch normalisation of K matrices Z [rows][C] (C % 4 == 0, C <= 1024), per
-// replica and column over the rows.  Forward: stats[k][0][c] = mean, stats[k][1][c] =
+// replica and column over the rows.  Forward (launch_bn_stats, then launch_bn_apply or the same joined with the pool that
+// follows): stats[k][0][c] = mean, stats[k][1][c] =
 // 1/sqrt(biased variance + eps); out = relu(gamma Xh + beta), Xh = (Z - mean) stats[1], gamma
 // and beta read from params + k * strideParams at gam_off / bet_off.  `scratch`: 2 * K *
 // bn_chunks(rows, C, K) * C floats.  Backward: launch_bn_backward_partials leaves chunk sums
@@ -407,6 +408,13 @@ struct PlaneOut {
 // over them gives dgamma and dbeta); launch_bn_backward_apply then writes
 // dZ = gamma stats[1] (dY - dbeta/rows - Xh dgamma/rows) [+ add] to `dZ`, which may be dY itself or Z
 // (or null: planes only), dgamma and dbeta read from grad + k * strideParams at the same offsets.  -1: shape not supported.
+
+// Where that pass finds dY: floats g [K][rows][C], or (HW > 0) the gradient g [image][ld] of a global average over HW
+// positions; set to zero where `keep` (bits of a word; may be null) is clear.
+struct GradSource {
+  const float* g; const uint8_t* keep;
+  int HW, ld;
+};
 
 // Shortcut of a residual block (He et al., CIFAR variant, parameter-free): the block input
 // src [K][B][step H][step W][Cs] (replica stride `stride` floats) enters the block output
@@ -420,7 +428,7 @@ struct ShortcutDesc {
   const float* pz = nullptr; const float* pstats = nullptr;
   int64_t pgam_off = 0, pbet_off = 0;
 };
-// stats[k] = (mean, 1/sqrt(var + eps)) per channel of Z [K][rows][C]; scratch as for launch_bn_forward.  `have`: the
+// stats[k] = (mean, 1/sqrt(var + eps)) per channel of Z [K][rows][C].  `have`: the
 // chunks of the scratch that the product that wrote Z has left there; none: they are taken from Z.
 int launch_bn_stats(const float* Z, float* scratch, const ChunkSums& have, float* stats, int K, int64_t rows, int C, float eps,
                     hipStream_t s);
@@ -430,10 +438,18 @@ int launch_add_into(float* dst, const float* src, int64_t n, hipStream_t s);
 int launch_subsample2(const float* src, float* dst, int64_t images, int H, int W, int C, hipStream_t s);
 int bn_chunks(int64_t rows, int C, int K);
 // `shortcut` (may be null): added to the normalised output before the ReLU.  `out` may be null: planes (and bits) only.
-int launch_bn_forward(const float* Z, float* scratch, const ChunkSums& have, float* stats, const float* params,
-                      int64_t strideParams, int64_t gam_off, int64_t bet_off, float* out, int K,
-                      int64_t rows, int C, float eps, const ShortcutDesc* shortcut, const PlaneOut& planes,
-                      hipStream_t s);
+int launch_bn_apply(const float* Z, const float* stats, const float* params, int64_t strideParams, int64_t gam_off, int64_t bet_off,
+                    float* out, int K, int64_t rows, int C, const ShortcutDesc* shortcut, const PlaneOut& planes, hipStream_t s);
+// Followed by the 2x2 max-pool of [H][W] images (`images` a replica): P (may be null) and the planes are the pooled image's;
+// for the backward pass zmax (Z at each window's first maximum), arg (which one, two bits a channel, a byte a word) and
+// planes.keep.
+int launch_bn_pool(const float* Z, const float* stats, const float* params, int64_t strideParams, int64_t gam_off, int64_t bet_off,
+                   float* P, float* zmax, uint8_t* arg, int K, int64_t images, int H, int W, int C, const PlaneOut& planes,
+                   hipStream_t s);
+// Followed by global average pooling as launch_avgpool does it; keep: the image's bits.
+int launch_bn_avgpool(const float* Z, const float* stats, const float* params, int64_t strideParams, int64_t gam_off,
+                      int64_t bet_off, float* P, int K, int64_t images, int HW, int C, int ldp, const ShortcutDesc* shortcut,
+                      uint8_t* keep, hipStream_t s);
 // dIn (shape of d.src) += the gradient dY [K][rows][C] of the block output, through the shortcut,
 // kept only where mask (shape of dIn, the ReLU output the block read; may be null) is positive.
 int launch_shortcut_backward(const float* dY, float* dIn, const float* mask, const ShortcutDesc& d, int K,
@@ -443,12 +459,16 @@ int launch_shortcut_backward(const float* dY, float* dIn, const float* mask, con
 int launch_avgpool(const float* A, float* P, int64_t images, int HW, int C, int ldp, hipStream_t s);
 int launch_avgpool_backward(const float* dP, const float* mask, const uint8_t* keep, float* dA, int64_t images, int HW, int C,
                             int ldp, hipStream_t s);
-int launch_bn_backward_partials(const float* Z, const float* dY, const float* stats, float* part, int K,
+int launch_bn_backward_partials(const float* Z, const GradSource& dY, const float* stats, float* part, int K,
                                 int64_t rows, int C, hipStream_t s);
-void launch_bn_backward_apply(const float* Z, const float* dY, float* dZ, const float* stats,
+void launch_bn_backward_apply(const float* Z, const GradSource& dY, float* dZ, const float* stats,
                               const float* params, const float* grad, int64_t strideParams,
                               int64_t gam_off, int64_t bet_off, int K, int64_t rows, int C, const float* add,
                               const PlaneOut& planes, hipStream_t s);
+// The latter behind launch_bn_pool, from the pooled image's gradient dP (the former takes zmax and dP with their bits).
+void launch_bn_pool_backward(const float* Z, const float* dP, const uint8_t* arg, const uint8_t* keep, float* dZ, const float* stats,
+                             const float* params, const float* grad, int64_t strideParams, int64_t gam_off, int64_t bet_off, int K,
+                             int64_t images, int H, int W, int C, const PlaneOut& planes, hipStream_t s);
 // Wt[k][c][(u,v,o)] = W[k][o][(2-u,2-v,c)] for K filter banks W [Cout][3][3][Cin] (row pitch ldw,
 // replica stride strideW); Wt is dense, [K][Cin][9 Cout].  Cout must be a multiple of 32.
 void launch_flip_filters(const float* W, int64_t strideW, int ldw, float* Wt, int K, int Cout, int Cin,
@@ -456,15 +476,15 @@ void launch_flip_filters(const float* W, int64_t strideW, int ldw, float* Wt, in
 // Column sums of K contiguous [rows][N] matrices, first stage: partial[k][chunk][n] = sum of
 // the rows of chunk `chunk` (colsum_chunks(rows, N, K) chunks of equal height, the last one ragged);
 // returns the chunk count, -1 if N is not a multiple of 4 in 4..1024.  launch_bias_grad over
-// the partials finishes the sum.
+// the partials finishes the sum.  keep: bits, as in GradSource.
 int colsum_chunks(int64_t rows, int N, int K);
-int launch_colsum_partials(const float* A, int64_t rows, int N, int K, float* partial, hipStream_t s);
-// 2x2/stride-2 max-pool over `images` contiguous [H][W][C] images, and the backward pass of
-// ReLU-then-pool: dA = dP at the first maximum of each window if it is positive, else 0
-// (A: the ReLU output that was pooled).  C % 4 == 0, H and W even.
-int launch_maxpool2(const float* A, float* P, int64_t images, int H, int W, int C, const PlaneOut& planes, hipStream_t s);
-int launch_maxpool2_backward(const float* A, const float* dP, float* dA, int64_t images, int H,
-                             int W, int C, hipStream_t s);
+int launch_colsum_partials(const float* A, const uint8_t* keep, int64_t rows, int N, int K, float* partial, hipStream_t s);
+// 2x2/stride-2 max-pool over `images` contiguous [H][W][C] images A, ReLU outputs (P may be null: planes only), and the
+// backward pass of ReLU-then-pool: dA (may be null) and its planes = dP at the first maximum of each window if it is positive,
+// else 0; arg and planes.keep of the forward pass say where (see launch_bn_pool).  C % 4 == 0, H and W even.
+int launch_maxpool2(const float* A, float* P, uint8_t* arg, int64_t images, int H, int W, int C, const PlaneOut& planes, hipStream_t s);
+int launch_maxpool2_backward(const float* dP, const uint8_t* arg, const uint8_t* keep, float* dA, int64_t images, int H,
+                             int W, int C, const PlaneOut& planes, hipStream_t s);
 
 // Measured ceilings: device copy (GB/s, read + written) between the halves of `scratch`, and
 // MFMA-only loops (TFLOP/s, bf16 32x32x16 and fp32 32x32x2).  Blocks until done; 0 or -1.

@@ -40,6 +40,13 @@ __device__ __forceinline__ unsigned char positive_bits(const f32x4& v) {
   return (unsigned char)((v[0] > 0.f ? 1 : 0) | (v[1] > 0.f ? 2 : 0) | (v[2] > 0.f ? 4 : 0) | (v[3] > 0.f ? 8 : 0));
 }
 
+__device__ __forceinline__ f32x4 kept_values(f32x4 v, unsigned bits) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (!(bits >> r & 1)) v[r] = 0.f;
+  return v;
+}
+
 struct ImgShape {
   int H, W, C;     // one output image of the convolution (H x W positions), C input channels
   int ld;          // pitch of a col row (floats), multiple of 4, >= 9 C
@@ -138,68 +145,88 @@ struct PoolShape {
   long long cells;  // K B Ho Wo C/4
 };
 
-// P[b,i,j,c] = max over the 2x2 window of A.  One thread per 16-byte word of P.
+// Pooled word `idx`: its first channel, its cell (k b, i, j) and where its window's first value lies in the image.
+struct PoolCell {
+  int c;
+  long long cell, base;
+};
+__device__ __forceinline__ PoolCell pool_cell(long long idx, const PoolShape& sh) {
+  const int words = sh.C / 4;
+  PoolCell p;
+  p.c = (int)(idx % words) * 4;
+  p.cell = idx / words;
+  const int j = (int)(p.cell % sh.Wo);
+  const int i = (int)((p.cell / sh.Wo) % sh.Ho);
+  const long long kb = p.cell / ((long long)sh.Wo * sh.Ho);
+  p.base = ((kb * 2 * sh.Ho + 2 * i) * (2 * sh.Wo) + 2 * j) * sh.C + p.c;
+  return p;
+}
+// Value t (row-major) of a window.
+__device__ __forceinline__ long long pool_offset(int t, const PoolShape& sh) {
+  return (t & 1) * sh.C + (t >> 1) * (2LL * sh.Wo * sh.C);
+}
+// The first maximum of each channel's window, and where it lies: two bits a channel.
+__device__ __forceinline__ unsigned first_maximum(const f32x4 (&v)[4], f32x4& m) {
+  unsigned arg = 0;
+  m = v[0];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    unsigned best = 0;
+#pragma unroll
+    for (unsigned t = 1; t < 4; ++t)
+      if (v[t][r] > m[r]) { m[r] = v[t][r]; best = t; }
+    arg |= best << (2 * r);
+  }
+  return arg;
+}
+// Gradient of window value t: dP where that is the first maximum and kept.
+__device__ __forceinline__ f32x4 unpooled(const f32x4& g, unsigned keep, unsigned arg, unsigned t) {
+  f32x4 o;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) o[r] = (keep >> r & 1) && (arg >> (2 * r) & 3) == t ? g[r] : 0.f;
+  return o;
+}
+
+// P[b,i,j,c] = max over the 2x2 window of A (a ReLU output), as floats (P null: not) and planes; what the backward pass wants
+// of A beside it: `arg`, a byte a word, and the bits of the positive maxima.  One thread per 16-byte word of P.
 template <int NP>
 __global__ __launch_bounds__(kThreads) void maxpool2_kernel(const float* __restrict__ A,
                                                             float* __restrict__ P, PoolShape sh,
+                                                            unsigned char* __restrict__ arg, unsigned char* __restrict__ keep,
                                                             unsigned short* __restrict__ planes, long long plane) {
   const long long idx = (long long)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= sh.cells) return;
-  const int words = sh.C / 4;
-  const int c = (int)(idx % words) * 4;
-  long long cell = idx / words;          // (k b, i, j) of the pooled image
-  const int j = (int)(cell % sh.Wo);
-  const int i = (int)((cell / sh.Wo) % sh.Ho);
-  const long long kb = cell / ((long long)sh.Wo * sh.Ho);
-  const int W = 2 * sh.Wo;
-  const float* a = A + ((kb * 2 * sh.Ho + 2 * i) * W + 2 * j) * sh.C + c;
-  f32x4 m = *reinterpret_cast<const f32x4*>(a);
-  const f32x4 v1 = *reinterpret_cast<const f32x4*>(a + sh.C);
-  const f32x4 v2 = *reinterpret_cast<const f32x4*>(a + (long long)W * sh.C);
-  const f32x4 v3 = *reinterpret_cast<const f32x4*>(a + (long long)W * sh.C + sh.C);
+  const PoolCell w = pool_cell(idx, sh);
+  f32x4 v[4], m;
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    m[r] = v1[r] > m[r] ? v1[r] : m[r];
-    m[r] = v2[r] > m[r] ? v2[r] : m[r];
-    m[r] = v3[r] > m[r] ? v3[r] : m[r];
-  }
-  *reinterpret_cast<f32x4*>(P + cell * sh.C + c) = m;
-  put_planes<NP>(planes, plane, cell * sh.C + c, m);
+  for (int t = 0; t < 4; ++t) v[t] = *reinterpret_cast<const f32x4*>(A + w.base + pool_offset(t, sh));
+  arg[idx] = (unsigned char)first_maximum(v, m);
+  keep[idx] = positive_bits(m);
+  if (P != nullptr) *reinterpret_cast<f32x4*>(P + idx * 4) = m;
+  put_planes<NP>(planes, plane, idx * 4, m);
 }
 
-// Backward of ReLU followed by the pool: dA[window] = dP where A is the window's first
-// maximum (row-major window order) and positive, else 0.  A is the ReLU output.
-__global__ __launch_bounds__(kThreads) void maxpool2_backward_kernel(const float* __restrict__ A,
-                                                                     const float* __restrict__ dP,
-                                                                     float* __restrict__ dA,
-                                                                     PoolShape sh) {
+// Backward of ReLU followed by the pool: dA[window] = dP at the window's first maximum if that was positive, else 0, as
+// floats (dA null: not) and planes.  From the bits of the forward pass, not from the image (4 bytes a value more): 4 replicas of
+// 128 images, 32 channels at 32 x 32: 25 us, 16 so; 64 at 16 x 16 with the planes 13 and 13, 14 together.
+template <int NP>
+__global__ __launch_bounds__(kThreads) void maxpool2_backward_kernel(const float* __restrict__ dP,
+                                                                     const unsigned char* __restrict__ arg,
+                                                                     const unsigned char* __restrict__ keep,
+                                                                     float* __restrict__ dA, PoolShape sh,
+                                                                     unsigned short* __restrict__ planes, long long plane) {
   const long long idx = (long long)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= sh.cells) return;
-  const int words = sh.C / 4;
-  const int c = (int)(idx % words) * 4;
-  long long cell = idx / words;
-  const int j = (int)(cell % sh.Wo);
-  const int i = (int)((cell / sh.Wo) % sh.Ho);
-  const long long kb = cell / ((long long)sh.Wo * sh.Ho);
-  const int W = 2 * sh.Wo;
-  const long long base = ((kb * 2 * sh.Ho + 2 * i) * W + 2 * j) * sh.C + c;
-  const long long offs[4] = {0, sh.C, (long long)W * sh.C, (long long)W * sh.C + sh.C};
-  f32x4 v[4], o[4];
+  const PoolCell w = pool_cell(idx, sh);
+  const f32x4 g = *reinterpret_cast<const f32x4*>(dP + idx * 4);
+  const unsigned a = arg[idx], kept = keep[idx];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) v[t] = *reinterpret_cast<const f32x4*>(A + base + offs[t]);
-  const f32x4 g = *reinterpret_cast<const f32x4*>(dP + cell * sh.C + c);
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    int best = 0;
-    float m = v[0][r];
-#pragma unroll
-    for (int t = 1; t < 4; ++t)
-      if (v[t][r] > m) { m = v[t][r]; best = t; }
-#pragma unroll
-    for (int t = 0; t < 4; ++t) o[t][r] = (t == best && m > 0.f) ? g[r] : 0.f;
+  for (unsigned t = 0; t < 4; ++t) {
+    const f32x4 o = unpooled(g, kept, a, t);
+    const long long at = w.base + pool_offset(t, sh);
+    if (dA != nullptr) *reinterpret_cast<f32x4*>(dA + at) = o;
+    put_planes<NP>(planes, plane, at, o);
   }
-#pragma unroll
-  for (int t = 0; t < 4; ++t) *reinterpret_cast<f32x4*>(dA + base + offs[t]) = o[t];
 }
 
 // Column reductions over the rows of tall matrices [K][rows][C] (C % 4 == 0) are done in two
@@ -247,8 +274,9 @@ __device__ __forceinline__ f32x4 combine_groups(f32x4 v, const ChunkThread& t, f
   return tot;
 }
 
-// partial[k][chunk][c] = sum of the chunk's rows of A.
+// partial[k][chunk][c] = sum of the chunk's rows of A, where `keep` (bits; null: everywhere) is set.
 __global__ __launch_bounds__(kThreads) void colsum_partial_kernel(const float* __restrict__ A,
+                                                                  const unsigned char* __restrict__ keep,
                                                                   float* __restrict__ partial,
                                                                   long long rows, int N, int chunks,
                                                                   int chunk_rows) {
@@ -257,8 +285,12 @@ __global__ __launch_bounds__(kThreads) void colsum_partial_kernel(const float* _
   const int k = blockIdx.y;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   if (t.live) {
-    const float* base = A + ((long long)k * rows) * N + 4 * t.cw;
-    for (long long r = t.r0 + t.grp; r < t.r1; r += 16) acc += *reinterpret_cast<const f32x4*>(base + r * N);
+    const long long base = ((long long)k * rows) * N + 4 * t.cw;
+    if (keep != nullptr)
+      for (long long r = t.r0 + t.grp; r < t.r1; r += 16)
+        acc += kept_values(*reinterpret_cast<const f32x4*>(A + base + r * N), keep[(base + r * N) >> 2]);
+    else
+      for (long long r = t.r0 + t.grp; r < t.r1; r += 16) acc += *reinterpret_cast<const f32x4*>(A + base + r * N);
   }
   const f32x4 tot = combine_groups(acc, t, buf);
   if (t.live && t.grp == 0)
@@ -650,6 +682,40 @@ struct Shortcut {
   long long pgam_off, pbet_off;
 };
 
+// What a normalisation's kernels need of one word's columns c.. of replica k, and its output before the ReLU.
+struct NormWord {
+  f32x4 mu, inv, ga, be;
+};
+__device__ __forceinline__ NormWord norm_word(const float* __restrict__ stats, const float* __restrict__ params,
+                                              long long strideParams, long long gam_off, long long bet_off, int k, int c, int C) {
+  NormWord n;
+  n.mu = *reinterpret_cast<const f32x4*>(stats + ((long long)k * 2) * C + c);
+  n.inv = *reinterpret_cast<const f32x4*>(stats + ((long long)k * 2 + 1) * C + c);
+  n.ga = *reinterpret_cast<const f32x4*>(params + k * strideParams + gam_off + c);
+  n.be = *reinterpret_cast<const f32x4*>(params + k * strideParams + bet_off + c);
+  return n;
+}
+__device__ __forceinline__ f32x4 normalised(const f32x4& z, const NormWord& n) { return n.ga * ((z - n.mu) * n.inv) + n.be; }
+// The shortcut's value of word idx (columns c.. of replica k) added to y.
+__device__ __forceinline__ f32x4 with_shortcut(f32x4 y, const Shortcut& sc, const NormWord& proj, long long idx, int k, int c,
+                                               int words, long long rows) {
+  if (sc.pz != nullptr) {
+    y += normalised(*reinterpret_cast<const f32x4*>(sc.pz + idx * 4), proj);
+  } else if (sc.src != nullptr && c < sc.Cs) {       // Cs % 4 == 0: a word lies inside or outside
+    const long long m = idx / words - (long long)k * rows;       // (b, i, j) of this replica
+    const int j = (int)(m % sc.W), i = (int)((m / sc.W) % sc.H);
+    const long long b = m / ((long long)sc.W * sc.H);
+    const long long at = ((b * (sc.st * sc.H) + sc.st * i) * (sc.st * sc.W) + sc.st * j) * sc.Cs + c;
+    y += *reinterpret_cast<const f32x4*>(sc.src + k * sc.stride + at);
+  }
+  return y;
+}
+__device__ __forceinline__ f32x4 rectified(f32x4 y) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) y[r] = y[r] > 0.f ? y[r] : 0.f;
+  return y;
+}
+
 // out = relu(gamma (Z - mean) inv_std + beta [+ shortcut]), its planes for the layer that reads it and the bits of its
 // positive values.  Bound by its bytes: the floats are written only where something reads them (out null: not at
 // all), since a product reads the planes and the gradient that comes back only asks for the sign.  64 channels with one plane,
@@ -669,30 +735,80 @@ __global__ __launch_bounds__(kThreads) void bn_apply_kernel(const float* __restr
   const int words = C / 4;
   const int c = (int)(idx % words) * 4;
   const int k = (int)(idx / words / rows);
-  const f32x4 mu = *reinterpret_cast<const f32x4*>(stats + ((long long)k * 2) * C + c);
-  const f32x4 inv = *reinterpret_cast<const f32x4*>(stats + ((long long)k * 2 + 1) * C + c);
-  const f32x4 ga = *reinterpret_cast<const f32x4*>(params + k * strideParams + gam_off + c);
-  const f32x4 be = *reinterpret_cast<const f32x4*>(params + k * strideParams + bet_off + c);
-  const f32x4 z = *reinterpret_cast<const f32x4*>(Z + idx * 4);
-  f32x4 y = ga * ((z - mu) * inv) + be;
-  if (sc.pz != nullptr) {
-    const f32x4 pmu = *reinterpret_cast<const f32x4*>(sc.pstats + ((long long)k * 2) * C + c);
-    const f32x4 pinv = *reinterpret_cast<const f32x4*>(sc.pstats + ((long long)k * 2 + 1) * C + c);
-    const f32x4 pga = *reinterpret_cast<const f32x4*>(params + k * strideParams + sc.pgam_off + c);
-    const f32x4 pbe = *reinterpret_cast<const f32x4*>(params + k * strideParams + sc.pbet_off + c);
-    y += pga * ((*reinterpret_cast<const f32x4*>(sc.pz + idx * 4) - pmu) * pinv) + pbe;
-  } else if (sc.src != nullptr && c < sc.Cs) {       // Cs % 4 == 0: a word lies inside or outside
-    const long long m = idx / words - (long long)k * rows;       // (b, i, j) of this replica
-    const int j = (int)(m % sc.W), i = (int)((m / sc.W) % sc.H);
-    const long long b = m / ((long long)sc.W * sc.H);
-    const long long at = ((b * (sc.st * sc.H) + sc.st * i) * (sc.st * sc.W) + sc.st * j) * sc.Cs + c;
-    y += *reinterpret_cast<const f32x4*>(sc.src + k * sc.stride + at);
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) y[r] = y[r] > 0.f ? y[r] : 0.f;
+  const NormWord n = norm_word(stats, params, strideParams, gam_off, bet_off, k, c, C);
+  const NormWord proj = sc.pz != nullptr ? norm_word(sc.pstats, params, strideParams, sc.pgam_off, sc.pbet_off, k, c, C) : n;
+  const f32x4 y = rectified(with_shortcut(normalised(*reinterpret_cast<const f32x4*>(Z + idx * 4), n), sc, proj, idx, k, c, words, rows));
   if (out != nullptr) *reinterpret_cast<f32x4*>(out + idx * 4) = y;
   if (keep != nullptr) keep[idx] = positive_bits(y);
   put_planes<NP>(planes, plane, idx * 4, y);
+}
+
+// The same followed by the 2x2 max-pool, one thread per word of the pooled image: the normalised image is not written.  Left for
+// the backward pass: Z at each window's first maximum, which of the four that is, and the bits of the positive ones.
+// 64 channels, 4 replicas of 128 images of 32 x 32, three planes: 43 and 35 us apart, 37 so; backward 44, 54 and 75 (pool, sums, gradient), 57 so.
+template <int NP>
+__global__ __launch_bounds__(kThreads) void bn_pool_kernel(const float* __restrict__ Z, const float* __restrict__ stats,
+                                                           const float* __restrict__ params, long long strideParams,
+                                                           long long gam_off, long long bet_off, float* __restrict__ P,
+                                                           float* __restrict__ zmax, long long replica_words, PoolShape sh,
+                                                           unsigned char* __restrict__ arg, unsigned char* __restrict__ keep,
+                                                           unsigned short* __restrict__ planes, long long plane) {
+  const long long idx = (long long)blockIdx.x * kThreads + threadIdx.x;
+  if (idx >= sh.cells) return;
+  const PoolCell w = pool_cell(idx, sh);
+  const NormWord n = norm_word(stats, params, strideParams, gam_off, bet_off, (int)(idx / replica_words), w.c, sh.C);
+  f32x4 z[4], v[4], m, zm;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    z[t] = *reinterpret_cast<const f32x4*>(Z + w.base + pool_offset(t, sh));
+    v[t] = rectified(normalised(z[t], n));
+  }
+  const unsigned a = first_maximum(v, m);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const unsigned t = a >> (2 * r) & 3;
+    zm[r] = t == 0 ? z[0][r] : t == 1 ? z[1][r] : t == 2 ? z[2][r] : z[3][r];
+  }
+  arg[idx] = (unsigned char)a;
+  keep[idx] = positive_bits(m);
+  *reinterpret_cast<f32x4*>(zmax + idx * 4) = zm;
+  if (P != nullptr) *reinterpret_cast<f32x4*>(P + idx * 4) = m;
+  put_planes<NP>(planes, plane, idx * 4, m);
+}
+
+// And followed by global average pooling: P[img][c] = mean over the positions, the image itself only as sign bits.  Workgroups
+// and order of the sums as in avgpool_kernel.  320 channels at 16 x 16,
+// 4 replicas of 128: 54 and 28 us apart, 40 so.
+__global__ __launch_bounds__(kThreads) void bn_avgpool_kernel(const float* __restrict__ Z, const float* __restrict__ stats,
+                                                              const float* __restrict__ params, long long strideParams,
+                                                              long long gam_off, long long bet_off, float* __restrict__ P,
+                                                              int HW, int C, int ldp, int images, Shortcut sc,
+                                                              unsigned char* __restrict__ keep) {
+  __shared__ f32x4 buf[kThreads];
+  const int w = threadIdx.x & 15, grp = threadIdx.x >> 4;
+  const int c = (blockIdx.y * 16 + w) * 4;
+  const long long img = blockIdx.x;
+  const int k = (int)(img / images), words = C / 4;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  if (c < C) {
+    const NormWord n = norm_word(stats, params, strideParams, gam_off, bet_off, k, c, C);
+    const NormWord proj = sc.pz != nullptr ? norm_word(sc.pstats, params, strideParams, sc.pgam_off, sc.pbet_off, k, c, C) : n;
+#pragma unroll 4
+    for (int p = grp; p < HW; p += 16) {
+      const long long idx = (img * HW + p) * words + c / 4;
+      const f32x4 y = rectified(with_shortcut(normalised(*reinterpret_cast<const f32x4*>(Z + idx * 4), n), sc, proj, idx, k, c, words,
+                                              (long long)images * HW));
+      keep[idx] = positive_bits(y);
+      acc += y;
+    }
+  }
+  buf[threadIdx.x] = acc;
+  __syncthreads();
+  if (grp == 0 && c < C) {
+#pragma unroll
+    for (int gq = 1; gq < 16; ++gq) acc += buf[gq * 16 + w];
+    *reinterpret_cast<f32x4*>(P + img * ldp + c) = acc * (1.f / (float)HW);
+  }
 }
 
 // The shortcut's share of the block input's gradient: dIn[b][st i][st j][c] += dY[b][i][j][c]
@@ -788,10 +904,7 @@ __global__ __launch_bounds__(kThreads) void avgpool_backward_kernel(const float*
   const long long img = idx / words / HW;
   f32x4 g = *reinterpret_cast<const f32x4*>(dP + img * ldp + c) * (1.f / (float)HW);
   if (keep != nullptr) {
-    const unsigned bits = keep[idx];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (!(bits >> r & 1)) g[r] = 0.f;
+    g = kept_values(g, keep[idx]);
   } else if (mask != nullptr) {
     const f32x4 a = *reinterpret_cast<const f32x4*>(mask + idx * 4);
 #pragma unroll
@@ -801,10 +914,17 @@ __global__ __launch_bounds__(kThreads) void avgpool_backward_kernel(const float*
   *reinterpret_cast<f32x4*>(dA + idx * 4) = g;
 }
 
+// Word idx, columns c.. of row r of replica k, of the gradient a normalisation's backward pass starts from.
+__device__ __forceinline__ f32x4 gradient_word(const GradSource& d, long long idx, int k, int r, int rows, int c) {
+  f32x4 g;
+  if (d.HW > 0) g = *reinterpret_cast<const f32x4*>(d.g + ((long long)k * (rows / d.HW) + r / d.HW) * d.ld + c) * (1.f / (float)d.HW);
+  else g = *reinterpret_cast<const f32x4*>(d.g + idx * 4);
+  return d.keep != nullptr ? kept_values(g, d.keep[idx]) : g;
+}
+
 // Chunk sums for the backward pass: part[k][chunk][0..C) = sum dY Xh, [C..2C) = sum dY, with
 // Xh = (Z - mean) inv_std recomputed from Z.
-__global__ __launch_bounds__(kThreads) void bn_backward_partial_kernel(const float* __restrict__ Z,
-                                                                       const float* __restrict__ dY,
+__global__ __launch_bounds__(kThreads) void bn_backward_partial_kernel(const float* __restrict__ Z, GradSource d,
                                                                        const float* __restrict__ stats,
                                                                        float* __restrict__ part,
                                                                        long long rows, int C, int chunks,
@@ -812,17 +932,21 @@ __global__ __launch_bounds__(kThreads) void bn_backward_partial_kernel(const flo
   __shared__ f32x4 buf[kThreads];
   const ChunkThread t = chunk_thread(rows, C, chunk_rows);
   const int k = blockIdx.y;
-  const long long base = ((long long)k * rows) * C + 4 * t.cw;
   f32x4 sg = {0.f, 0.f, 0.f, 0.f}, sb = {0.f, 0.f, 0.f, 0.f};
   if (t.live) {
     const f32x4 mu = *reinterpret_cast<const f32x4*>(stats + ((long long)k * 2) * C + 4 * t.cw);
     const f32x4 inv = *reinterpret_cast<const f32x4*>(stats + ((long long)k * 2 + 1) * C + 4 * t.cw);
-    for (long long r = t.r0 + t.grp; r < t.r1; r += 16) {
-      const f32x4 dy = *reinterpret_cast<const f32x4*>(dY + base + r * C);
-      const f32x4 xh = (*reinterpret_cast<const f32x4*>(Z + base + r * C) - mu) * inv;
-      sg += dy * xh;
-      sb += dy;
-    }
+    const auto walk = [&](const GradSource& src) {
+      for (long long r = t.r0 + t.grp; r < t.r1; r += 16) {
+        const long long idx = (k * rows + r) * (C / 4) + t.cw;
+        const f32x4 dy = gradient_word(src, idx, k, (int)r, (int)rows, 4 * t.cw);
+        const f32x4 xh = (*reinterpret_cast<const f32x4*>(Z + idx * 4) - mu) * inv;
+        sg += dy * xh;
+        sb += dy;
+      }
+    };
+    if (d.HW == 0 && d.keep == nullptr) walk(GradSource{d.g, nullptr, 0, 0});
+    else walk(d);
   }
   const f32x4 tg = combine_groups(sg, t, buf);
   const f32x4 tb = combine_groups(sb, t, buf);
@@ -833,11 +957,32 @@ __global__ __launch_bounds__(kThreads) void bn_backward_partial_kernel(const flo
   }
 }
 
-// dZ = gamma inv_std (dY - dbeta / N - Xh dgamma / N) [+ add], written to dZ (null: not at all), which may
+// What the gradient of a normalisation's input needs of one word's columns, and that gradient
+//   dZ = gamma inv_std (dY - dbeta / N - Xh dgamma / N).
+struct NormGradWord {
+  f32x4 mu, inv, ga, dga, dbe;
+};
+__device__ __forceinline__ NormGradWord norm_grad_word(const float* __restrict__ stats, const float* __restrict__ params,
+                                                       const float* __restrict__ grad, long long strideParams,
+                                                       long long gam_off, long long bet_off, int k, int c, int C) {
+  NormGradWord n;
+  n.mu = *reinterpret_cast<const f32x4*>(stats + ((long long)k * 2) * C + c);
+  n.inv = *reinterpret_cast<const f32x4*>(stats + ((long long)k * 2 + 1) * C + c);
+  n.ga = *reinterpret_cast<const f32x4*>(params + k * strideParams + gam_off + c);
+  n.dga = *reinterpret_cast<const f32x4*>(grad + k * strideParams + gam_off + c);
+  n.dbe = *reinterpret_cast<const f32x4*>(grad + k * strideParams + bet_off + c);
+  return n;
+}
+__device__ __forceinline__ f32x4 norm_gradient(const f32x4& z, const f32x4& dy, const NormGradWord& n, float inv_n) {
+  const f32x4 xh = (z - n.mu) * n.inv;
+  return n.ga * n.inv * (dy - n.dbe * inv_n - xh * (n.dga * inv_n));
+}
+
+// dZ [+ add], written to dZ (null: not at all), which may
 // be dY itself or Z (every thread reads its own word of both before it writes), and to its planes.
 template <int NP>
 __global__ __launch_bounds__(kThreads) void bn_backward_apply_kernel(
-    const float* Z, const float* dY, float* dZ, const float* __restrict__ stats,
+    const float* Z, GradSource d, float* dZ, const float* __restrict__ stats,
     const float* __restrict__ params, const float* __restrict__ grad, long long strideParams,
     long long gam_off, long long bet_off, long long rows, int C, long long total, const float* add,
     unsigned short* __restrict__ planes, long long plane) {
@@ -845,19 +990,39 @@ __global__ __launch_bounds__(kThreads) void bn_backward_apply_kernel(
   if (idx >= total) return;
   const int words = C / 4;
   const int c = (int)(idx % words) * 4;
-  const int k = (int)(idx / words / rows);
-  const f32x4 mu = *reinterpret_cast<const f32x4*>(stats + ((long long)k * 2) * C + c);
-  const f32x4 inv = *reinterpret_cast<const f32x4*>(stats + ((long long)k * 2 + 1) * C + c);
-  const f32x4 ga = *reinterpret_cast<const f32x4*>(params + k * strideParams + gam_off + c);
-  const f32x4 dga = *reinterpret_cast<const f32x4*>(grad + k * strideParams + gam_off + c);
-  const f32x4 dbe = *reinterpret_cast<const f32x4*>(grad + k * strideParams + bet_off + c);
-  const float inv_n = 1.f / (float)rows;
-  const f32x4 xh = (*reinterpret_cast<const f32x4*>(Z + idx * 4) - mu) * inv;
-  const f32x4 dy = *reinterpret_cast<const f32x4*>(dY + idx * 4);
-  f32x4 o = ga * inv * (dy - dbe * inv_n - xh * (dga * inv_n));
+  const int k = (int)(idx / words / rows), r = (int)(idx / words - k * rows);
+  const NormGradWord n = norm_grad_word(stats, params, grad, strideParams, gam_off, bet_off, k, c, C);
+  f32x4 o = norm_gradient(*reinterpret_cast<const f32x4*>(Z + idx * 4), gradient_word(d, idx, k, r, (int)rows, c), n,
+                          1.f / (float)rows);
   if (add != nullptr) o += *reinterpret_cast<const f32x4*>(add + idx * 4);
   if (dZ != nullptr) *reinterpret_cast<f32x4*>(dZ + idx * 4) = o;
   put_planes<NP>(planes, plane, idx * 4, o);
+}
+
+// The same where a pool follows the normalisation, one thread per word of the pooled gradient dP.
+template <int NP>
+__global__ __launch_bounds__(kThreads) void bn_pool_backward_kernel(
+    const float* __restrict__ Z, const float* __restrict__ dP, const unsigned char* __restrict__ arg,
+    const unsigned char* __restrict__ keep, float* __restrict__ dZ, const float* __restrict__ stats,
+    const float* __restrict__ params, const float* __restrict__ grad, long long strideParams, long long gam_off, long long bet_off,
+    long long rows, long long replica_words, PoolShape sh, unsigned short* __restrict__ planes, long long plane) {
+  const long long idx = (long long)blockIdx.x * kThreads + threadIdx.x;
+  if (idx >= sh.cells) return;
+  const PoolCell w = pool_cell(idx, sh);
+  const NormGradWord n =
+      norm_grad_word(stats, params, grad, strideParams, gam_off, bet_off, (int)(idx / replica_words), w.c, sh.C);
+  const f32x4 g = *reinterpret_cast<const f32x4*>(dP + idx * 4);
+  const unsigned a = arg[idx], kept = keep[idx];
+  f32x4 z[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) z[t] = *reinterpret_cast<const f32x4*>(Z + w.base + pool_offset(t, sh));
+#pragma unroll
+  for (unsigned t = 0; t < 4; ++t) {
+    const f32x4 o = norm_gradient(z[t], unpooled(g, kept, a, t), n, 1.f / (float)rows);
+    const long long at = w.base + pool_offset(t, sh);
+    if (dZ != nullptr) *reinterpret_cast<f32x4*>(dZ + at) = o;
+    put_planes<NP>(planes, plane, at, o);
+  }
 }
 
 unsigned blocks_for(long long total) { return (unsigned)((total + kThreads - 1) / kThreads); }
@@ -986,29 +1151,54 @@ int launch_subsample2(const float* src, float* dst, int64_t images, int H, int W
   return 0;
 }
 
-int launch_bn_forward(const float* Z, float* scratch, const ChunkSums& have, float* stats, const float* params,
-                      int64_t strideParams, int64_t gam_off, int64_t bet_off, float* out, int K,
-                      int64_t rows, int C, float eps, const ShortcutDesc* shortcut, const PlaneOut& o, hipStream_t s) {
-  if (C % 4 || C < 4 || C > 4 * kThreads || rows < 1) return -1;
-  Shortcut sc{nullptr, 0, 1, 1, 0, 1, nullptr, nullptr, 0, 0};
-  if (shortcut != nullptr && shortcut->pz != nullptr) {
-    if (shortcut->pstats == nullptr) return -1;
-    sc.pz = shortcut->pz; sc.pstats = shortcut->pstats;
-    sc.pgam_off = shortcut->pgam_off; sc.pbet_off = shortcut->pbet_off;
-  } else if (shortcut != nullptr) {
-    if (shortcut->Cs % 4 || shortcut->Cs > C || shortcut->H < 1 || shortcut->W < 1 ||
-        rows % ((int64_t)shortcut->H * shortcut->W) || shortcut->step < 1 || shortcut->step > 2)
-      return -1;
-    sc = Shortcut{shortcut->src, shortcut->stride, shortcut->H, shortcut->W, shortcut->Cs, shortcut->step,
-                  nullptr, nullptr, 0, 0};
+// The shortcut as the kernels read it; -1: it does not fit the layer.
+static int shortcut_of(const ShortcutDesc* d, int64_t rows, int C, Shortcut& sc) {
+  sc = Shortcut{nullptr, 0, 1, 1, 0, 1, nullptr, nullptr, 0, 0};
+  if (d == nullptr) return 0;
+  if (d->pz != nullptr) {
+    if (d->pstats == nullptr) return -1;
+    sc.pz = d->pz; sc.pstats = d->pstats;
+    sc.pgam_off = d->pgam_off; sc.pbet_off = d->pbet_off;
+    return 0;
   }
-  if (launch_bn_stats(Z, scratch, have, stats, K, rows, C, eps, s) != 0) return -1;
+  if (d->Cs % 4 || d->Cs > C || d->H < 1 || d->W < 1 || rows % ((int64_t)d->H * d->W) || d->step < 1 || d->step > 2) return -1;
+  sc = Shortcut{d->src, d->stride, d->H, d->W, d->Cs, d->step, nullptr, nullptr, 0, 0};
+  return 0;
+}
+
+int launch_bn_apply(const float* Z, const float* stats, const float* params, int64_t strideParams, int64_t gam_off, int64_t bet_off,
+                    float* out, int K, int64_t rows, int C, const ShortcutDesc* shortcut, const PlaneOut& o, hipStream_t s) {
+  Shortcut sc;
+  if (C % 4 || C < 4 || rows < 1 || shortcut_of(shortcut, rows, C, sc) != 0) return -1;
   const long long total = (long long)K * rows * (C / 4);
   auto run = [&](auto kernel) {
     kernel<<<blocks_for(total), kThreads, 0, s>>>(Z, stats, params, strideParams, gam_off, bet_off, out, rows, C, total, sc,
                                                   o.p, o.plane, o.keep);
   };
   run(o.np == 0 ? bn_apply_kernel<0> : o.np == 1 ? bn_apply_kernel<1> : bn_apply_kernel<3>);
+  return 0;
+}
+
+int launch_bn_pool(const float* Z, const float* stats, const float* params, int64_t strideParams, int64_t gam_off, int64_t bet_off,
+                   float* P, float* zmax, uint8_t* arg, int K, int64_t images, int H, int W, int C, const PlaneOut& o, hipStream_t s) {
+  const long long words = images * (H / 2) * (W / 2) * (C / 4);         // of a replica
+  const PoolShape sh{H / 2, W / 2, C, K * words};
+  if (C % 4 || C < 4 || H % 2 || W % 2 || words <= 0 || sh.cells >= (1ll << 31) * kThreads || o.keep == nullptr) return -1;
+  auto run = [&](auto kernel) {
+    kernel<<<blocks_for(sh.cells), kThreads, 0, s>>>(Z, stats, params, strideParams, gam_off, bet_off, P, zmax, words, sh, arg, o.keep,
+                                                     o.p, o.plane);
+  };
+  run(o.np == 0 ? bn_pool_kernel<0> : o.np == 1 ? bn_pool_kernel<1> : bn_pool_kernel<3>);
+  return 0;
+}
+
+int launch_bn_avgpool(const float* Z, const float* stats, const float* params, int64_t strideParams, int64_t gam_off,
+                      int64_t bet_off, float* P, int K, int64_t images, int HW, int C, int ldp, const ShortcutDesc* shortcut,
+                      uint8_t* keep, hipStream_t s) {
+  Shortcut sc;
+  if (C % 4 || C < 4 || HW < 1 || images < 1 || ldp < C || ldp % 4 || shortcut_of(shortcut, images * HW, C, sc) != 0) return -1;
+  bn_avgpool_kernel<<<dim3((unsigned)(K * images), (unsigned)((C + 63) / 64)), kThreads, 0, s>>>(
+      Z, stats, params, strideParams, gam_off, bet_off, P, HW, C, ldp, (int)images, sc, keep);
   return 0;
 }
 
@@ -1034,7 +1224,7 @@ int launch_avgpool_backward(const float* dP, const float* mask, const uint8_t* k
   return 0;
 }
 
-int launch_bn_backward_partials(const float* Z, const float* dY, const float* stats, float* part, int K,
+int launch_bn_backward_partials(const float* Z, const GradSource& dY, const float* stats, float* part, int K,
                                 int64_t rows, int C, hipStream_t s) {
   if (C % 4 || C < 4 || C > 4 * kThreads || rows < 1) return -1;
   const ChunkPlan pl = chunk_plan(rows, C, K);
@@ -1043,7 +1233,7 @@ int launch_bn_backward_partials(const float* Z, const float* dY, const float* st
   return pl.chunks;
 }
 
-void launch_bn_backward_apply(const float* Z, const float* dY, float* dZ, const float* stats,
+void launch_bn_backward_apply(const float* Z, const GradSource& dY, float* dZ, const float* stats,
                               const float* params, const float* grad, int64_t strideParams,
                               int64_t gam_off, int64_t bet_off, int K, int64_t rows, int C, const float* add,
                               const PlaneOut& o, hipStream_t s) {
@@ -1055,29 +1245,42 @@ void launch_bn_backward_apply(const float* Z, const float* dY, float* dZ, const 
   run(o.np == 0 ? bn_backward_apply_kernel<0> : o.np == 1 ? bn_backward_apply_kernel<1> : bn_backward_apply_kernel<3>);
 }
 
+void launch_bn_pool_backward(const float* Z, const float* dP, const uint8_t* arg, const uint8_t* keep, float* dZ, const float* stats,
+                             const float* params, const float* grad, int64_t strideParams, int64_t gam_off, int64_t bet_off, int K,
+                             int64_t images, int H, int W, int C, const PlaneOut& o, hipStream_t s) {
+  const long long words = images * (H / 2) * (W / 2) * (C / 4);
+  const PoolShape sh{H / 2, W / 2, C, K * words};
+  auto run = [&](auto kernel) {
+    kernel<<<blocks_for(sh.cells), kThreads, 0, s>>>(Z, dP, arg, keep, dZ, stats, params, grad, strideParams, gam_off, bet_off,
+                                                     images * H * W, words, sh, o.p, o.plane);
+  };
+  run(o.np == 0 ? bn_pool_backward_kernel<0> : o.np == 1 ? bn_pool_backward_kernel<1> : bn_pool_backward_kernel<3>);
+}
+
 int colsum_chunks(int64_t rows, int N, int K) { return chunk_plan(rows, N, K).chunks; }
 
-int launch_colsum_partials(const float* A, int64_t rows, int N, int K, float* partial, hipStream_t s) {
+int launch_colsum_partials(const float* A, const uint8_t* keep, int64_t rows, int N, int K, float* partial, hipStream_t s) {
   if (N % 4 || N < 4 || N > 4 * kThreads || rows < 1) return -1;
   const ChunkPlan pl = chunk_plan(rows, N, K);
   colsum_partial_kernel<<<dim3((unsigned)pl.chunks, (unsigned)K, (unsigned)pl.col_blocks), kThreads, 0, s>>>(
-      A, partial, rows, N, pl.chunks, pl.chunk_rows);
+      A, keep, partial, rows, N, pl.chunks, pl.chunk_rows);
   return pl.chunks;
 }
 
-int launch_maxpool2(const float* A, float* P, int64_t images, int H, int W, int C, const PlaneOut& o, hipStream_t s) {
-  PoolShape sh{H / 2, W / 2, C, images * (H / 2) * (W / 2) * (C / 4)};
-  if (C % 4 || H % 2 || W % 2 || sh.cells <= 0 || sh.cells >= (1ll << 31) * kThreads) return -1;
-  auto run = [&](auto kernel) { kernel<<<blocks_for(sh.cells), kThreads, 0, s>>>(A, P, sh, o.p, o.plane); };
+int launch_maxpool2(const float* A, float* P, uint8_t* arg, int64_t images, int H, int W, int C, const PlaneOut& o, hipStream_t s) {
+  const PoolShape sh{H / 2, W / 2, C, images * (H / 2) * (W / 2) * (C / 4)};
+  if (C % 4 || H % 2 || W % 2 || sh.cells <= 0 || sh.cells >= (1ll << 31) * kThreads || o.keep == nullptr) return -1;
+  auto run = [&](auto kernel) { kernel<<<blocks_for(sh.cells), kThreads, 0, s>>>(A, P, sh, arg, o.keep, o.p, o.plane); };
   run(o.np == 0 ? maxpool2_kernel<0> : o.np == 1 ? maxpool2_kernel<1> : maxpool2_kernel<3>);
   return 0;
 }
 
-int launch_maxpool2_backward(const float* A, const float* dP, float* dA, int64_t images, int H,
-                             int W, int C, hipStream_t s) {
-  PoolShape sh{H / 2, W / 2, C, images * (H / 2) * (W / 2) * (C / 4)};
+int launch_maxpool2_backward(const float* dP, const uint8_t* arg, const uint8_t* keep, float* dA, int64_t images, int H,
+                             int W, int C, const PlaneOut& o, hipStream_t s) {
+  const PoolShape sh{H / 2, W / 2, C, images * (H / 2) * (W / 2) * (C / 4)};
   if (C % 4 || H % 2 || W % 2 || sh.cells <= 0 || sh.cells >= (1ll << 31) * kThreads) return -1;
-  maxpool2_backward_kernel<<<blocks_for(sh.cells), kThreads, 0, s>>>(A, dP, dA, sh);
+  auto run = [&](auto kernel) { kernel<<<blocks_for(sh.cells), kThreads, 0, s>>>(dP, arg, keep, dA, sh, o.p, o.plane); };
+  run(o.np == 0 ? maxpool2_backward_kernel<0> : o.np == 1 ? maxpool2_backward_kernel<1> : maxpool2_backward_kernel<3>);
   return 0;
 }
 

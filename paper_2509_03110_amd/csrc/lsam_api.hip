@@ -152,10 +152,14 @@ struct ConvLayer {
   // `first`: layer 0 with 1..3 input channels runs its forward pass and its weight gradient
   // in kernels of their own (no unfolded image at all).
   bool fast, direct_in, direct_dx, first;
-  // `keep`: bits of the layer's positive outputs, where they are written by the normalisation and all that asks
-  // for the sign reads them.  `floats`: something reads the outputs themselves (a product on plane tensors does not).
-  bool has_keep, floats;
-  size_t keep;
+  // `keep`: bits of the layer's positive outputs (behind its pool), where they are written by the normalisation or the pool and
+  // all that asks for the sign reads them.  `floats`: something reads the outputs themselves in front of the pool, `pooled_floats`
+  // behind it (a product on plane tensors does not).
+  bool has_keep, floats, pooled_floats;
+  // Normalisation and what follows it in one kernel: the 2x2 pool, or the global average, whose gradient is then never
+  // written for every position either (unless a shortcut hands it on).
+  bool bn_pool, bn_gap;
+  size_t keep, arg, zmax;  // pools: which value of a window is its first maximum; with bn_pool that value's Z
   size_t first_partial;   // scratch of the first layer's weight gradient
   bool bn;                // batch-normalised: `z` keeps the convolution's output, `stats` the
   size_t z, stats;        // per-channel mean and 1/sqrt(var + eps) of each replica
@@ -558,11 +562,15 @@ void build_layout(const lsam_config& c, Layout& lo) {
       ConvLayer& cv = lo.conv[l];
       const ConvLayer* next = l + 1 < lo.n_conv ? &lo.conv[l + 1] : nullptr;
       const ConvLayer* closing = l + 2 < lo.n_conv && lo.conv[l + 2].skip ? &lo.conv[l + 2] : nullptr;
-      cv.has_keep = cv.bn && !cv.pool &&
+      const bool post_sum = cv.skip && !lo.preact;
+      cv.bn_pool = cv.bn && cv.pool && !post_sum;
+      cv.bn_gap = cv.bn && !cv.pool && !next && lo.gap_hw > 0;
+      cv.has_keep = cv.pool || (cv.bn &&
                     (next ? next->fast && next->direct_dx && (!opens_block(lo, l + 1) || shortcut_joins_product(lo, l + 1))
-                          : lo.gap_hw > 0);
-      cv.floats = cv.pool || !cv.has_keep || !next || !next->fast || !next->direct_in ||
-                  (closing && (closing->proj ? !closing->fast : !lo.preact));
+                          : lo.gap_hw > 0));
+      cv.pooled_floats = cv.pool && (!next || !next->fast || !next->direct_in);
+      if (cv.pool || !next) cv.floats = !cv.bn_pool && !cv.bn_gap;
+      else cv.floats = !cv.has_keep || !next->fast || !next->direct_in || (closing && (closing->proj ? !closing->fast : !lo.preact));
     }
     for (int l = 0; l < lo.n_conv; ++l) {
       ConvLayer& cv = lo.conv[l];
@@ -599,14 +607,16 @@ void build_layout(const lsam_config& c, Layout& lo) {
         lo.dzp_elems = std::max(lo.dzp_elems, (int64_t)lo.K * cv.rows * cv.Cout);
       }
       if (cv.floats) cv.out = take(cur, full);
-      if (cv.has_keep) cv.keep = take(cur, full / 16);
+      if (cv.has_keep) cv.keep = take(cur, full / (cv.pool ? 64 : 16));
+      if (cv.pool) cv.arg = take(cur, full / 64);
+      if (cv.bn_pool) cv.zmax = take(cur, full / 4);
       cv.dout = take(cur, full);
       if (cv.bn) {
         cv.z = take(cur, full);
         cv.stats = take(cur, (size_t)lo.K * 2 * cv.Cout * 4);
       }
       if (cv.pool) {
-        cv.pooled = take(cur, full / 4);
+        if (cv.pooled_floats) cv.pooled = take(cur, full / 4);
         cv.dpooled = take(cur, full / 4);
       }
       if (cv.proj) {
@@ -624,12 +634,15 @@ void build_layout(const lsam_config& c, Layout& lo) {
     if (lo.dzp_elems) lo.dzp = take(cur, (size_t)lo.dzp_elems * 2 * lo.np);
     if (lo.n_conv > 0) {
       size_t most = 0;
-      for (const ConvLayer& cv : lo.conv)
-        most = std::max(most, (size_t)lo.K * colsum_chunks(cv.rows, cv.Cout, lo.K) * cv.Cout * 4);
+      for (const ConvLayer& cv : lo.conv) {
+        const int chunks = std::max(colsum_chunks(cv.rows, cv.Cout, lo.K), cv.pool ? colsum_chunks(cv.rows / 4, cv.Cout, lo.K) : 0);
+        most = std::max(most, (size_t)lo.K * chunks * cv.Cout * 4);
+      }
       size_t proj = 0;
       for (const ConvLayer& cv : lo.conv) {
         if (!cv.bn) continue;
-        const size_t sums = (size_t)lo.K * std::max(bn_chunks(cv.rows, cv.Cout, lo.K), conv_gemm_sum_chunks(cv.rows)) * 2 * cv.Cout * 4;
+        const int chunks = std::max(bn_chunks(cv.rows, cv.Cout, lo.K), cv.pool ? bn_chunks(cv.rows / 4, cv.Cout, lo.K) : 0);
+        const size_t sums = (size_t)lo.K * std::max(chunks, conv_gemm_sum_chunks(cv.rows)) * 2 * cv.Cout * 4;
         most = std::max(most, sums);
         if (cv.proj && !lo.preact) proj = std::max(proj, sums);
       }
@@ -1020,23 +1033,36 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
         sc.stride = lo.conv[l - 2].rows * cv.skip_C;
         sc.H = cv.H; sc.W = cv.W; sc.Cs = cv.skip_C; sc.step = cv.skip_step;
       }
-      PlaneOut o = cv.pool ? PlaneOut{} : input_planes(c, l + 1);
-      if (cv.has_keep) o.keep = c->at<uint8_t>(cv.keep);
-      if (launch_bn_forward(c->at<float>(cv.z), scratch, have, c->at<float>(cv.stats), params,
-                            lo.d_pad, ly.gam_off, ly.bet_off, cv.floats ? c->at<float>(cv.out) : nullptr, lo.K, cv.rows,
-                            cv.Cout, c->cfg.bn_eps, post_sum ? &sc : nullptr, o, s) != 0)
-        return fail(LSAM_EINVAL, "batch normalisation of convolution %d rejected", l);
+      const float* z = c->at<float>(cv.z);
+      const float* stats = c->at<float>(cv.stats);
+      PlaneOut o = cv.pool && !cv.bn_pool ? PlaneOut{} : input_planes(c, l + 1);
+      if (cv.has_keep && (!cv.pool || cv.bn_pool)) o.keep = c->at<uint8_t>(cv.keep);
+      int rc = launch_bn_stats(z, scratch, have, c->at<float>(cv.stats), lo.K, cv.rows, cv.Cout, c->cfg.bn_eps, s);
+      if (rc == 0 && cv.bn_pool)
+        rc = launch_bn_pool(z, stats, params, lo.d_pad, ly.gam_off, ly.bet_off, cv.pooled_floats ? c->at<float>(cv.pooled) : nullptr,
+                            c->at<float>(cv.zmax), c->at<uint8_t>(cv.arg), lo.K, lo.B, cv.H, cv.W, cv.Cout, o, s);
+      else if (rc == 0 && cv.bn_gap)
+        rc = launch_bn_avgpool(z, stats, params, lo.d_pad, ly.gam_off, ly.bet_off, c->at<float>(lo.gap_out), lo.K, lo.B, lo.gap_hw,
+                               cv.Cout, lo.ld[lo.n_conv], post_sum ? &sc : nullptr, o.keep, s);
+      else if (rc == 0)
+        rc = launch_bn_apply(z, stats, params, lo.d_pad, ly.gam_off, ly.bet_off, cv.floats ? c->at<float>(cv.out) : nullptr, lo.K,
+                             cv.rows, cv.Cout, post_sum ? &sc : nullptr, o, s);
+      if (rc != 0) return fail(LSAM_EINVAL, "batch normalisation of convolution %d rejected", l);
     }
     in = cv.floats ? c->at<float>(cv.out) : nullptr;
     if (cv.pool) {
-      LaunchTimer t(c, KC_POOL);
-      if (launch_maxpool2(in, c->at<float>(cv.pooled), (int64_t)lo.K * lo.B, cv.H, cv.W, cv.Cout,
-                          input_planes(c, l + 1), s) != 0)
-        return fail(LSAM_EINVAL, "pool of convolution %d rejected", l);
-      in = c->at<float>(cv.pooled);
+      if (!cv.bn_pool) {
+        LaunchTimer t(c, KC_POOL);
+        PlaneOut o = input_planes(c, l + 1);
+        o.keep = c->at<uint8_t>(cv.keep);
+        if (launch_maxpool2(in, cv.pooled_floats ? c->at<float>(cv.pooled) : nullptr, c->at<uint8_t>(cv.arg), (int64_t)lo.K * lo.B,
+                            cv.H, cv.W, cv.Cout, o, s) != 0)
+          return fail(LSAM_EINVAL, "pool of convolution %d rejected", l);
+      }
+      in = cv.pooled_floats ? c->at<float>(cv.pooled) : nullptr;
     }
   }
-  if (lo.gap_hw) {
+  if (lo.gap_hw && !lo.conv[lo.n_conv - 1].bn_gap) {
     LaunchTimer t(c, KC_POOL);
     const ConvLayer& cv = lo.conv[lo.n_conv - 1];
     if (launch_avgpool(in, c->at<float>(lo.gap_out), (int64_t)lo.K * lo.B, lo.gap_hw, cv.Cout,
@@ -1053,14 +1079,18 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
   const Layout& lo = c->lo;
   hipStream_t s = c->stream;
   float* g = c->at<float>(lo.g);
-  if (lo.gap_hw) {
+  // The gradient of a normalised last image's average is the same for every position; it is written for each only where a
+  // shortcut hands it on.
+  const ConvLayer& last = lo.conv[lo.n_conv - 1];
+  const bool from_average = last.bn_gap && !(last.skip && !last.proj && !lo.preact);
+  if (lo.gap_hw && !from_average) {
     // the pooled vector's gradient goes back to every position, through the ReLU the image came
     // from unless a pool sits in between (whose backward pass applies that mask)
     LaunchTimer t(c, KC_POOL);
-    const ConvLayer& cv = lo.conv[lo.n_conv - 1];
-    if (launch_avgpool_backward(c->at<float>(lo.gap_grad), cv.pool ? nullptr : c->at<float>(cv.out),
-                                cv.has_keep ? c->at<uint8_t>(cv.keep) : nullptr, c->at<float>(cv.pool ? cv.dpooled : cv.dout), (int64_t)lo.K * lo.B,
-                                lo.gap_hw, cv.Cout, lo.ld[lo.n_conv], s) != 0)
+    if (launch_avgpool_backward(c->at<float>(lo.gap_grad), last.pool || last.has_keep ? nullptr : c->at<float>(last.out),
+                                last.has_keep && !last.pool ? c->at<uint8_t>(last.keep) : nullptr,
+                                c->at<float>(last.pool ? last.dpooled : last.dout), (int64_t)lo.K * lo.B, lo.gap_hw, last.Cout,
+                                lo.ld[lo.n_conv], s) != 0)
       return fail(LSAM_EINVAL, "global average pooling (backward) rejected");
   }
   ChunkSums have;             // sums of the layer's gradient and normalised values, left by the product that wrote the gradient
@@ -1073,12 +1103,6 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
                        (ly.bn ? 2 * ((ly.out + 63) / 64) : 0) +
                        (ly.proj ? gemm_sumsq_capacity(ly.out, ly.proj_in) + 2 * ((ly.out + 63) / 64) : 0) > lo.nblk)
       return fail(LSAM_ESTATE, "gradient-norm partials would overrun their buffer at convolution %d", l);
-    if (cv.pool) {
-      LaunchTimer t(c, KC_POOL);
-      if (launch_maxpool2_backward(c->at<float>(cv.out), c->at<float>(cv.dpooled), dout,
-                                   (int64_t)lo.K * lo.B, cv.H, cv.W, cv.Cout, s) != 0)
-        return fail(LSAM_EINVAL, "pool backward of convolution %d rejected", l);
-    }
     // A block's closing convolution keeps dY: it is also the gradient of the shortcut, added
     // to the block input's gradient further down.  Its dZ goes where Z was (Z is not needed again).
     float* dz = (cv.bn && cv.skip && !lo.preact) ? c->at<float>(cv.z) : dout;
@@ -1090,11 +1114,27 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
     if (cv.fast && !cv.first) {
       po.p = c->at<uint16_t>(lo.dzp); po.np = lo.np; po.plane = lo.dzp_elems;
     }
+    const uint8_t* keep = cv.has_keep ? c->at<uint8_t>(cv.keep) : nullptr;
+    const float* dpooled = cv.pool ? c->at<float>(cv.dpooled) : nullptr;
+    GradSource dy{dout, nullptr, 0, 0};     // the gradient behind the ReLU
+    if (from_average && l == lo.n_conv - 1) dy = GradSource{c->at<float>(lo.gap_grad), keep, lo.gap_hw, lo.ld[lo.n_conv]};
+    if (cv.pool && !cv.bn_pool) {
+      // (without a normalisation that is dZ: as floats for a first layer's gradients and the fp32-storage GEMM only)
+      LaunchTimer t(c, KC_POOL);
+      if (launch_maxpool2_backward(dpooled, c->at<uint8_t>(cv.arg), keep, !cv.bn && po.p ? nullptr : dout, (int64_t)lo.K * lo.B, cv.H,
+                                   cv.W, cv.Cout, cv.bn ? PlaneOut{} : po, s) != 0)
+        return fail(LSAM_EINVAL, "pool backward of convolution %d rejected", l);
+    }
     auto own_gradient = [&]() {
       // nothing reads the floats of a fast layer's dZ but the convolution its sum is handed down to
       const bool floats = !po.p || (lo.preact && cv.skip && !cv.proj);
-      launch_bn_backward_apply(c->at<float>(cv.z), dout, floats ? dz : nullptr, c->at<float>(cv.stats), params, g,
-                               lo.d_pad, ly.gam_off, ly.bet_off, lo.K, cv.rows, cv.Cout, cv.fast ? handed : nullptr, po, s);
+      if (cv.bn_pool)
+        launch_bn_pool_backward(c->at<float>(cv.z), dpooled, c->at<uint8_t>(cv.arg), keep, floats ? dz : nullptr,
+                                c->at<float>(cv.stats), params, g, lo.d_pad, ly.gam_off, ly.bet_off, lo.K, lo.B, cv.H, cv.W, cv.Cout,
+                                po, s);
+      else
+        launch_bn_backward_apply(c->at<float>(cv.z), dy, floats ? dz : nullptr, c->at<float>(cv.stats), params, g,
+                                 lo.d_pad, ly.gam_off, ly.bet_off, lo.K, cv.rows, cv.Cout, cv.fast ? handed : nullptr, po, s);
     };
     // The projection of a post-activation block goes first: its planes take the same place
     const bool own_last = cv.proj && !lo.preact;
@@ -1104,8 +1144,10 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
       LaunchTimer t(c, KC_BATCHNORM);
       float* part = c->at<float>(lo.colsum);
       const int chunks = have.chunks ? have.chunks
-                                     : launch_bn_backward_partials(c->at<float>(cv.z), dout, c->at<float>(cv.stats),
-                                                                   part, lo.K, cv.rows, cv.Cout, s);
+                         : cv.bn_pool  ? launch_bn_backward_partials(c->at<float>(cv.zmax), GradSource{dpooled, keep, 0, 0},
+                                                                   c->at<float>(cv.stats), part, lo.K, cv.rows / 4, cv.Cout, s)
+                                       : launch_bn_backward_partials(c->at<float>(cv.z), dy, c->at<float>(cv.stats), part, lo.K,
+                                                                     cv.rows, cv.Cout, s);
       if (chunks < 0) return fail(LSAM_EINVAL, "batch normalisation of convolution %d rejected", l);
       {
         const int used = launch_norm_param_grads(part, g, lo.d_pad, ly.gam_off, ly.bet_off, lo.K, chunks, cv.Cout,
@@ -1117,13 +1159,13 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
         // the same gradient dY enters the projection's normalisation: dgamma_p, dbeta_p, then
         // the gradient of the 1x1 convolution's output, which takes that output's place
         float* pz = c->at<float>(cv.pz);
-        const int pchunks = launch_bn_backward_partials(pz, dout, c->at<float>(cv.pstats), part, lo.K,
+        const int pchunks = launch_bn_backward_partials(pz, dy, c->at<float>(cv.pstats), part, lo.K,
                                                         cv.rows, cv.Cout, s);
         if (pchunks < 0) return fail(LSAM_EINVAL, "projection of convolution %d: normalisation rejected", l);
         const int used = launch_norm_param_grads(part, g, lo.d_pad, ly.pgam_off, ly.pbet_off, lo.K, pchunks, cv.Cout,
                                                  ssq ? ssq + *slots : nullptr, lo.nblk, s);
         if (ssq) *slots += used;
-        launch_bn_backward_apply(pz, dout, po.p ? nullptr : pz, c->at<float>(cv.pstats), params, g, lo.d_pad, ly.pgam_off,
+        launch_bn_backward_apply(pz, dy, po.p ? nullptr : pz, c->at<float>(cv.pstats), params, g, lo.d_pad, ly.pgam_off,
                                  ly.pbet_off, lo.K, cv.rows, cv.Cout, nullptr, po, s);
       }
     }
@@ -1183,7 +1225,7 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
     if (own_last) {
       LaunchTimer t(c, KC_BATCHNORM);
       own_gradient();
-    } else if (po.p && !cv.bn) {
+    } else if (po.p && !cv.bn && !cv.pool) {
       LaunchTimer t(c, KC_UNFOLD);
       if (split_gradient(c, dout, cv) != 0) return fail(LSAM_EINVAL, "planes of the gradient of convolution %d rejected", l);
     }
@@ -1234,7 +1276,8 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
     if (!cv.bn) {
       // bias gradient: column sums of dout, in two fixed-order stages
       LaunchTimer t(c, KC_BIAS_GRAD);
-      const int chunks = launch_colsum_partials(dout, cv.rows, cv.Cout, lo.K, c->at<float>(lo.colsum), s);
+      const int chunks = cv.pool ? launch_colsum_partials(dpooled, keep, cv.rows / 4, cv.Cout, lo.K, c->at<float>(lo.colsum), s)
+                                 : launch_colsum_partials(dout, nullptr, cv.rows, cv.Cout, lo.K, c->at<float>(lo.colsum), s);
       if (chunks < 0) return fail(LSAM_EINVAL, "bias gradient of convolution %d rejected", l);
       const int used = launch_bias_grad(c->at<float>(lo.colsum), cv.Cout, g + ly.b_off, lo.d_pad,
                                         lo.K, chunks, cv.Cout, ssq ? ssq + *slots : nullptr, lo.nblk, s);
@@ -1262,21 +1305,19 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
         const int64_t image = (int64_t)lo.B * cv.in_H * cv.in_W * cv.Cin;
         d.C = c->at<float>(below.pool ? below.dpooled : below.dout);
         d.strideC = image; d.ldC = cv.Cin;
-        d.epilogue = below.pool ? EPI_PLAIN : EPI_MASK;
-        if (!below.pool) {
-          if (below.has_keep) d.keep = c->at<uint8_t>(below.keep);
-          else d.mask = c->at<float>(below.out);
-          d.strideMask = image; d.ldMask = cv.Cin;
-        }
+        d.epilogue = EPI_MASK;
+        if (below.has_keep) d.keep = c->at<uint8_t>(below.keep);
+        else d.mask = c->at<float>(below.out);
+        d.strideMask = image; d.ldMask = cv.Cin;
         if (shortcut_joins_product(lo, l)) {
           const ConvLayer& top = lo.conv[l + 1];
           d.ldAdd = top.proj ? top.skip_C : top.Cout;
           d.add = c->at<float>(top.proj ? top.psub : top.dout); d.strideAdd = top.rows * d.ldAdd;
           shortcut_done = true;
         }
-        if (below.bn && !below.pool && (!opens || shortcut_done)) {      // the gradient is complete: its sums with it
+        if (below.bn && (!below.pool || below.bn_pool) && (!opens || shortcut_done)) {      // the gradient is complete: its sums with it
           d.sums = 2; d.sum_part = c->at<float>(lo.colsum);
-          d.sum_z = c->at<float>(below.z); d.sum_stats = c->at<float>(below.stats);
+          d.sum_z = c->at<float>(below.bn_pool ? below.zmax : below.z); d.sum_stats = c->at<float>(below.stats);
         }
         if (launch_conv_gemm(d, s, nullptr, &have) != 0)
           return fail(LSAM_EINVAL, "dX product of convolution %d rejected", l);

@@ -1,6 +1,7 @@
 """Normalised convolutions whose outputs are kept as planes and sign bits, with and without the floats beside them, and whose
 column sums are taken where the products are written: chains, ragged last tiles, shortcuts that read the floats, projections,
-products cut over workgroups, whose sums kernels of their own take.
+products cut over workgroups, whose sums kernels of their own take; pools joined with the normalisation in front of them or
+behind a bare ReLU, and the global average with and without a shortcut that hands its gradient on.
 
 Unlike the nets of test_gpu_plane_products.py half of all values are rectified, pixel by pixel, so a bit of another pixel
 or channel shows: half of the gradient's terms would be wrong.  A value within rounding of zero (1e-6 of its
@@ -20,6 +21,14 @@ NETS = {
     "chain": dict(dims=(3, 32, 64, 32, 10), side=(16, 32), batch=24),
     "chain, products cut over workgroups": dict(dims=(3, 128, 128, 128, 10), side=(8, 8), batch=64),
     "ragged tiles": dict(dims=(3, 40, 72, 40, 10), side=(18, 14), batch=37),
+    "pools": dict(dims=(3, 32, 40, 64, 10), side=(16, 28), batch=27, pool=0b011),
+    "pool at the end": dict(dims=(3, 64, 32, 10), side=(12, 20), batch=40, pool=0b010),
+    "pools without normalisation": dict(dims=(3, 32, 40, 64, 10), side=(16, 24), batch=31, pool=0b111, bn=0),
+    "small layers": dict(dims=(5, 8, 24, 8, 10), side=(8, 12), batch=9, pool=0b101),
+    "pools on the fp32-storage product": dict(dims=(8, 32, 48, 10), side=(8, 12), batch=9, pool=0b01, bn=0),
+    "pool behind a block": dict(dims=(3, 32, 32, 32, 48, 10), side=(16, 32), batch=24, skip=0b0100, pool=0b0100),
+    "pool behind a pre-activation block": dict(dims=(3, 32, 32, 32, 48, 10), side=(16, 32), batch=24, skip=0b0100, pool=0b0100, preact=1),
+    "average behind a shortcut": dict(dims=(3, 32, 32, 32, 10), side=(16, 20), batch=24, skip=0b100),
     "identity shortcut": dict(dims=(3, 32, 32, 32, 32, 32, 10), side=(16, 32), batch=24, skip=0b10100),
     "stride and projection": dict(dims=(3, 24, 48, 48, 48, 10), side=(32, 32), batch=16, stride=0b0010, skip=0b0100, proj=0b0100),
     "stored input gradient": dict(dims=(3, 96, 64, 32, 10), side=(16, 16), batch=90, stride=0b010),

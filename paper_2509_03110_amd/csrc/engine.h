@@ -384,10 +384,16 @@ int launch_fold3x3(const float* dcol, int64_t strideCol, int ld, float* dX, cons
 // batch normalisation the bias gradient is zero).
 bool first_conv_fits(int C, int Cout, int64_t rows, int K, int round);
 int first_conv_chunks(int64_t rows, int Cout, int K);
+// `sums` (may be null): the statistics of the results by chunks of rows, as ConvGemmDesc's sums = 1.  `norm` (z null: dout is
+// the gradient of the convolution's output): dout is dY of the normalisation behind it, and its gradient is formed from these.
+struct FirstNorm {
+  const float* z = nullptr; const float* stats = nullptr; const float* params = nullptr; const float* grad = nullptr;
+  long long gam_off = 0, bet_off = 0;
+};
 int launch_first_conv_forward(const float* X, const float* params, int64_t strideParams, int64_t w_off,
                               int64_t b_off, int ldw, float* out, int relu, int round, int K,
-                              int64_t rows, int H, int W, int C, int Cout, hipStream_t s);
-int launch_first_conv_wgrad(const float* X, const float* dout, float* partial, float* grad,
+                              int64_t rows, int H, int W, int C, int Cout, float* sums, ChunkSums* made, hipStream_t s);
+int launch_first_conv_wgrad(const float* X, const float* dout, const FirstNorm& norm, float* partial, float* grad,
                             int64_t strideParams, int64_t w_off, int64_t b_off, int ldw, int round,
                             int skip_bias, int K, int64_t rows, int H, int W, int C, int Cout,
                             double* sumsq, int64_t sumsq_stride, hipStream_t s);

@@ -8,6 +8,8 @@
 // fixed order), the 2x2 max-pool, and the pool's backward pass fused with the ReLU mask.
 // All tensors are fp32, [K][B][H][W][C] with C contiguous; all four kernels are bandwidth
 // bound and move 128-bit words, consecutive lanes on consecutive words.
+#include <type_traits>
+
 #include "engine.h"
 #include "planes.h"
 
@@ -322,14 +324,17 @@ __global__ __launch_bounds__(kThreads) void flip_filters_kernel(const float* __r
 }
 
 // ---- first convolution layer (1..3 input channels) -------------------------------------------------
-// With C <= 3 the contraction is 9 C <= 27 long: too short to be worth staging through LDS, and
-// a 16-byte unit of the unfolded image would straddle taps.  These two kernels feed the MFMA
-// units (v_mfma_f32_32x32x2_f32) straight from global memory instead: every lane gathers the
-// image values of its pixel (the image of one replica is a few MB and stays in cache), the
-// filters sit in registers.  Lane (l32, h) supplies element (index l32, k = h) of each operand;
-// accumulator element e of a lane belongs to (second operand's index l32, first operand's
-// index (e/4)*8 + h*4 + e%4).
+// With C <= 3 the contraction is 9 C <= 27 long: too short for the plane products, whose 16-byte units of the
+// image would straddle taps.  These two kernels gather the image straight into the operands of
+// v_mfma_f32_32x32x16_bf16 (the image of one replica is a few MB and stays in cache): rounded values, or the exact split
+// of fp32 into three pieces (kernels_conv_gemm.hip), formed in registers.  Lane (l32, h) supplies elements (index
+// l32, k = 8 h .. 8 h + 7) of each operand; accumulator element e of a lane belongs to (second operand's index l32,
+// first operand's index (e/4)*8 + h*4 + e%4).  What bounds them is vector work per pixel (gather, split), not the
+// matrix units and, with few channels, not the memory: on the fp32 units, at a depth of 2 a step with a gather and a decision
+// each, they took 2 to 6 times the time of their bytes.
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 struct FirstConv {
   int H, W, Cout;
@@ -338,6 +343,7 @@ struct FirstConv {
   long long strideParams;  // floats between replicas' parameter (or gradient) vectors
   int ldw;                 // row pitch of the filter bank [Cout][9 C (+ padding)]
 };
+constexpr unsigned kOob = 0x7FFFFFF0u;   // byte offset past any operand: the load yields zero
 
 __device__ __forceinline__ void pixel_rc(int p, const FirstConv& f, int& i, int& j) {
   int q = (int)((float)p * f.invW);
@@ -350,166 +356,322 @@ __device__ __forceinline__ void pixel_rc(int p, const FirstConv& f, int& i, int&
   i = r2;
 }
 
-// bfloat16 value nearest to v (ties to even), as a float: products of two such values are exact
-// in fp32, so fp32 MFMAs on rounded operands give what the bf16 matrix instructions give.
-__device__ __forceinline__ float to_bf16(float v) { return static_cast<float>(static_cast<__bf16>(v)); }
-
-// Value t of the unfolded image of pixel p at (i, j): X[p shifted by tap t / C][t % C].
-template <int C>
-__device__ __forceinline__ float unfolded(const float* __restrict__ img, int p, int i, int j, int t,
-                                          const FirstConv& f) {
-  const int tap = t / C, c = t - tap * C;
-  const int du = tap / 3 - 1, dv = tap % 3 - 1;
-  const bool ok = tap < 9 && (unsigned)(i + du) < (unsigned)f.H && (unsigned)(j + dv) < (unsigned)f.W;
-  return ok ? img[(long long)(p + du * f.W + dv) * C + c] : 0.f;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t float_rsrc(const float* base, long long n) {
+  const unsigned long long a = reinterpret_cast<unsigned long long>(base);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+  void* ptr = reinterpret_cast<void*>(((unsigned long long)hi << 32) | lo);
+  return __builtin_amdgcn_make_buffer_rsrc(ptr, 0, __builtin_amdgcn_readfirstlane((unsigned)(n * 4)), 0x00020000);
+}
+__device__ __forceinline__ float load_float(__amdgpu_buffer_rsrc_t rs, unsigned at, int scalar = 0) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, at, scalar, 0));
 }
 
-// out[k][p][o] = relu(b[o] + sum_t unfolded(p, t) W[o][t]).  One wavefront per 32 pixels.
-template <int C>
+// Eight floats as the NP planes of an operand fragment.
+template <int NP>
+__device__ __forceinline__ void split_fragment(const float (&x)[8], u32x4 (&f)[NP]) {
+  unsigned o[NP][4];
+  split_words<NP>(x, o);
+#pragma unroll
+  for (int q = 0; q < NP; ++q) f[q] = u32x4{o[q][0], o[q][1], o[q][2], o[q][3]};
+}
+// `at` where bit `bit` of `ok` is set, past every operand elsewhere (two instructions).
+__device__ __forceinline__ unsigned if_bit(unsigned ok, int bit, unsigned at) {
+  const unsigned m = (unsigned)((int)(ok << (31 - bit)) >> 31);
+  return (at & m) | (kOob & ~m);
+}
+// acc (and, with three planes, low: the five small products) += first x second, smallest products first.
+template <int NP>
+__device__ __forceinline__ void multiply(const u32x4 (&first)[NP], const u32x4 (&second)[NP], f32x16& acc, f32x16& low) {
+  if constexpr (NP == 3) {
+    constexpr int xa[5] = {2, 0, 1, 1, 0}, xb[5] = {0, 2, 1, 0, 1};
+#pragma unroll
+    for (int q = 0; q < 5; ++q)
+      low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, first[xa[q]]), __builtin_bit_cast(bf16x8, second[xb[q]]),
+                                                    low, 0, 0, 0);
+  }
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, first[0]), __builtin_bit_cast(bf16x8, second[0]), acc, 0, 0, 0);
+}
+
+// out[k][p][o] = relu(b[o] + sum_t unfolded(p, t) W[o][t]).  A workgroup takes 128 `tiles` consecutive pixels, a quarter a
+// wavefront, 32 at a time, and 32 OB channels, whose filters it keeps in LDS as planes; a lane gathers its pixel's values of
+// the next 32 under the products of the current ones.  `sums` (may be null): the statistics of the results, a chunk a
+// workgroup, as launch_bn_stats leaves them.  4 replicas of 128 images of 32 x 32, on the fp32 units and the statistics beside it,
+// then so: 16 channels 33 and 9 us, 21; 64 channels 57 and 22, 41, with rounded operands 31 (4.4 TB/s).
+template <int C, int OB, int NP>
 __global__ __launch_bounds__(kThreads) void first_conv_forward_kernel(const float* __restrict__ X,
                                                                       const float* __restrict__ params,
                                                                       long long w_off, long long b_off,
-                                                                      float* __restrict__ out,
-                                                                      FirstConv f, int group, int relu, int round) {
-  constexpr int KS = (9 * C + 1) / 2;          // MFMA steps of depth 2
-  constexpr int WP = 33;                       // LDS pitch of a filter: lanes o, o+1 on different banks
-  extern __shared__ float wl[];                // [group][WP]: the filters, zero for t >= 9 C
-  const int o0 = blockIdx.z * group;           // this workgroup's channels: `group`, a multiple of 32
+                                                                      float* __restrict__ out, FirstConv f, int tiles, int relu,
+                                                                      float* __restrict__ sums) {
+  constexpr int KC = (9 * C + 15) / 16;        // matrix depths
+  __shared__ __attribute__((aligned(16))) unsigned short filters[NP][32 * OB][32];
+  __shared__ float wsum[2][4][32 * OB];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l32 = lane & 31, h = lane >> 5;
-  const int k = blockIdx.y;
+  const int k = blockIdx.y, o0 = blockIdx.z * (32 * OB);
   {
-    // rows of 32 floats (lanes along t: whole 128-byte lines of the filter bank)
+    // rows of 32 values (lanes along t: whole lines of the filter bank); unit u of row o at u ^ (o / 4) % 4
     const float* Wg = params + (long long)k * f.strideParams + w_off;
-    for (int e = threadIdx.x; e < group * 32; e += kThreads) {
+    for (int e = threadIdx.x; e < OB * 32 * 32; e += kThreads) {
       const int o = e >> 5, t = e & 31;
-      const float wv = t < 9 * C && o0 + o < f.Cout ? Wg[(long long)(o0 + o) * f.ldw + t] : 0.f;
-      wl[o * WP + t] = round ? to_bf16(wv) : wv;
+      unsigned short b[NP];
+      split_planes<NP>(t < 9 * C && o0 + o < f.Cout ? Wg[(long long)(o0 + o) * f.ldw + t] : 0.f, b);
+#pragma unroll
+      for (int q = 0; q < NP; ++q) filters[q][o][(((t >> 3) ^ ((o >> 2) & 3)) << 3) + (t & 7)] = b[q];
+    }
+  }
+  const int rows = (int)f.rows;
+  const int first = (blockIdx.x * 4 + wave) * tiles * 32;
+  const __amdgpu_buffer_rsrc_t img = float_rsrc(X + (long long)k * f.rows * C, f.rows * C);
+  const __amdgpu_buffer_rsrc_t dst = float_rsrc(out + (long long)k * f.rows * f.Cout, f.rows * f.Cout);
+  // this lane's values of the unfolded image: where they lie from its pixel's, and which of them lose a rim
+  int off[KC][8];
+  unsigned masks[2][5] = {};                   // (constants: only the choice by h is left to run time)
+#pragma unroll
+  for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      int at[2];
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        const int t = kc * 16 + half * 8 + e, tap = t / C, du = tap / 3, dv = tap - 3 * du;
+        const unsigned bit = 1u << (kc * 8 + e);
+        at[half] = (((du - 1) * f.W + dv - 1) * C + (t - tap * C)) * 4;
+        masks[half][0] |= t < 9 * C ? bit : 0u;
+        masks[half][1] |= du == 0 ? bit : 0u;
+        masks[half][2] |= du == 2 ? bit : 0u;
+        masks[half][3] |= dv == 0 ? bit : 0u;
+        masks[half][4] |= dv == 2 ? bit : 0u;
+      }
+      off[kc][e] = h ? at[1] : at[0];
+    }
+  const unsigned there = h ? masks[1][0] : masks[0][0], top = h ? masks[1][1] : masks[0][1], bottom = h ? masks[1][2] : masks[0][2],
+                 left = h ? masks[1][3] : masks[0][3], right = h ? masks[1][4] : masks[0][4];
+  float x[KC][8];
+  const auto gather = [&](int p) {
+    int i, j;
+    pixel_rc(p < rows ? p : 0, f, i, j);
+    const unsigned ok = (p < rows ? there : 0u) & ~((i == 0 ? top : 0u) | (i == f.H - 1 ? bottom : 0u) | (j == 0 ? left : 0u) |
+                                                    (j == f.W - 1 ? right : 0u));
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[kc][e] = load_float(img, if_bit(ok, kc * 8 + e, (unsigned)(p * (C * 4) + off[kc][e])));
+  };
+  float bv[OB], z0[OB], s1[OB], s2[OB];
+  bool mine[OB];
+#pragma unroll
+  for (int q = 0; q < OB; ++q) {
+    mine[q] = o0 + 32 * q + l32 < f.Cout;      // (the last block of 32 channels need not be full)
+    bv[q] = mine[q] ? (params + (long long)k * f.strideParams + b_off)[o0 + 32 * q + l32] : 0.f;
+    z0[q] = s1[q] = s2[q] = 0.f;
+  }
+  gather(first + l32);
+  __syncthreads();
+  for (int tile = 0; tile < tiles; ++tile) {
+    const int tile0 = first + tile * 32;
+    if (tile0 >= rows) break;
+    u32x4 fx[KC][NP];
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc) split_fragment<NP>(x[kc], fx[kc]);
+    if (tile + 1 < tiles) gather(tile0 + 32 + l32);
+    // acc[e] of lane (l32, h): channel l32 of the block, pixel tile0 + (e/4)*8 + h*4 + e%4, so
+    // that a store instruction writes two whole 128-byte rows
+#pragma unroll
+    for (int q = 0; q < OB; ++q) {
+      f32x16 acc, low;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[e] = low[e] = 0.f;
+#pragma unroll
+      for (int kc = 0; kc < KC; ++kc) {
+        u32x4 fw[NP];
+        const int o = 32 * q + l32;
+#pragma unroll
+        for (int pl = 0; pl < NP; ++pl)
+          fw[pl] = *reinterpret_cast<const u32x4*>(&filters[pl][o][((kc * 2 + h) ^ ((o >> 2) & 3)) << 3]);
+        multiply<NP>(fx[kc], fw, acc, low);
+      }
+      if constexpr (NP == 3) join_sums(acc, low);
+      if (tile == 0) z0[q] = __shfl(acc[0], l32, 64) + bv[q];    // the wavefront's first pixel
+      const unsigned at = mine[q] ? (unsigned)(tile0 + h * 4) * (unsigned)(f.Cout * 4) + (unsigned)(o0 + 32 * q + l32) * 4u : kOob;
+      const auto write = [&](auto whole) {       // (a whole tile of pixels: no pixel is looked at by itself)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int pp = (e / 4) * 8 + e % 4;
+          const float z = acc[e] + bv[q];
+          if (!decltype(whole)::value && tile0 + h * 4 + pp >= rows) continue;
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, relu && !(z > 0.f) ? 0.f : z), dst, at, pp * f.Cout * 4, 0);
+          const float dlt = z - z0[q];
+          s1[q] += dlt;
+          s2[q] += dlt * dlt;
+        }
+      };
+      if (tile0 + 32 <= rows) write(std::true_type{});
+      else write(std::false_type{});
+    }
+  }
+  if (sums == nullptr) return;
+  const auto pixels_of = [&](int w) {
+    const int left_over = rows - (int)((blockIdx.x * 4 + w) * tiles * 32);
+    return left_over < 0 ? 0 : left_over < tiles * 32 ? left_over : tiles * 32;
+  };
+#pragma unroll
+  for (int q = 0; q < OB; ++q) {
+    s1[q] += __shfl_xor(s1[q], 32, 64);
+    s2[q] += __shfl_xor(s2[q], 32, 64);
+    const int n = pixels_of(wave);
+    const float inv_n = n > 0 ? 1.f / (float)n : 0.f, m2 = s2[q] - s1[q] * s1[q] * inv_n;
+    if (h == 0) {
+      wsum[0][wave][32 * q + l32] = z0[q] + s1[q] * inv_n;
+      wsum[1][wave][32 * q + l32] = m2 > 0.f ? m2 : 0.f;
     }
   }
   __syncthreads();
-  const int p = (blockIdx.x * 4 + wave) * 32 + l32;
-  const bool live = p < f.rows;
-  const float* img = X + (long long)k * f.rows * C;
-  const float* bias = params + (long long)k * f.strideParams + b_off;
-  int i = 0, j = 0;
-  if (live) pixel_rc(p, f, i, j);
-  float x[KS];
+  const int c = threadIdx.x;
+  if (c < 32 * OB && o0 + c < f.Cout) {
+    float mean = 0.f, m2 = 0.f;
 #pragma unroll
-  for (int s = 0; s < KS; ++s) {
-    x[s] = live ? unfolded<C>(img, p, i, j, 2 * s + h, f) : 0.f;
-    if (round) x[s] = to_bf16(x[s]);
-  }
-  // acc[e] of lane (l32, h): output channel ob + l32 of pixel tile*32 + (e/4)*8 + h*4 + e%4, so
-  // that a store instruction writes two whole 128-byte rows
-  const int tile0 = (blockIdx.x * 4 + wave) * 32;
-  for (int ob = o0; ob < o0 + group && ob < f.Cout; ob += 32) {
-    f32x16 acc;
+    for (int w = 0; w < 4; ++w) mean += (float)pixels_of(w) * wsum[0][w][c];
+    mean /= (float)((pixels_of(0) + pixels_of(1)) + (pixels_of(2) + pixels_of(3)));
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      const float w = wl[(ob - o0 + l32) * WP + 2 * s + h];
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[s], w, acc, 0, 0, 0);
+    for (int w = 0; w < 4; ++w) {
+      const float dlt = wsum[0][w][c] - mean;
+      m2 += wsum[1][w][c] + (float)pixels_of(w) * dlt * dlt;
     }
-    const bool mine = ob + l32 < f.Cout;         // (the last block of 32 channels need not be full)
-    const float bv = mine ? bias[ob + l32] : 0.f;
-    float* dst = out + ((long long)k * f.rows + tile0) * f.Cout + ob + l32;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int pp = (e / 4) * 8 + h * 4 + e % 4;
-      const float z = acc[e] + bv;
-      if (mine && tile0 + pp < f.rows) dst[(long long)pp * f.Cout] = (relu && !(z > 0.f)) ? 0.f : z;
-    }
+    float* dst = sums + ((long long)k * gridDim.x + blockIdx.x) * f.Cout + o0 + c;
+    dst[0] = mean;
+    dst[(long long)gridDim.y * gridDim.x * f.Cout] = m2;
   }
 }
 
 // Weight and bias gradient, first stage: workgroup (chunk, k) covers `chunk_px` pixels, a quarter per
-// wavefront; partial[k][chunk][o][t] = sum over its pixels of dout[p][o] unfolded(p, t), with
-// t = 9 C standing for the constant 1 (that column is the bias gradient).  The four
-// wavefronts' sums are added in wave order through LDS.  What bounds it is the work per pixel in
-// front of the matrix instruction (its row and column, the gather of its 27 neighbours), so two
-// blocks of 32 output channels share it where there are two: 64 channels at 32 x 32, 4 replicas of 128,
-// 87 us with one at a time, 57 with two.  Few pixels leave it a chain of latencies: with 512 pixels a workgroup
-// a step of one 64-channel layer on 4096 pixels took 175 us, with 64 it takes 121.
-// (A workgroup takes 64 to 512 pixels, as few as give the launch a thousand workgroups, and 32 OB channels:
-// blockIdx.z.)
-template <int C, int OB>
+// wavefront, 16 at a time, and 32 OB channels (blockIdx.z); partial[k][chunk][o][t] = sum over its pixels of dZ[p][o]
+// unfolded(p, t), with t = 9 C standing for the constant 1 (that column is the bias gradient).  The four
+// wavefronts' sums are added in wave order through LDS.  NORM: dZ is not read but formed from dY (dout) and Z, which saves the
+// normalisation's kernel that wrote it (8 bytes a value more than these loads).  The next 16 pixels' values are requested
+// under the products of the current ones.  4 replicas of 128 images of 32 x 32, on the fp32 units and the normalisation's kernel,
+// then so: 16 channels 43 and 16 us, 24; 64 channels 57 and 61, 65, with rounded operands 54 (5.0 TB/s).  Few pixels leave it a chain of latencies: with 512 pixels a workgroup
+// a step of one 64-channel layer on 4096 pixels took 175 us, with 64 it took 121 (64 to 512, as few as give the launch a
+// thousand workgroups).
+template <int C, int OB, int NP, bool NORM>
 __global__ __launch_bounds__(kThreads) void first_conv_wgrad_kernel(const float* __restrict__ X,
                                                                     const float* __restrict__ dout,
                                                                     float* __restrict__ partial,
-                                                                    int chunks, int chunk_px, FirstConv f, int round) {
+                                                                    int chunks, int chunk_px, FirstConv f, FirstNorm norm) {
   __shared__ float red[3][32 * 32];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l32 = lane & 31, h = lane >> 5;
-  const int k = blockIdx.y;
-  const float* img = X + (long long)k * f.rows * C;
-  const float* dz = dout + (long long)k * f.rows * f.Cout;
+  const int k = blockIdx.y, ob = blockIdx.z * (32 * OB);
+  const int rows = (int)f.rows;
+  const __amdgpu_buffer_rsrc_t img = float_rsrc(X + (long long)k * f.rows * C, f.rows * C);
+  const __amdgpu_buffer_rsrc_t dz = float_rsrc(dout + (long long)k * f.rows * f.Cout, f.rows * f.Cout);
+  const __amdgpu_buffer_rsrc_t zs = NORM ? float_rsrc(norm.z + (long long)k * f.rows * f.Cout, f.rows * f.Cout) : dz;
   const int p0 = blockIdx.x * chunk_px + wave * (chunk_px / 4);
   // this lane's column of the unfolded image: fixed tap and channel
-  const int t = l32;
-  const int tap = t / C, c = t - tap * C;
-  const int du = tap / 3 - 1, dv = tap % 3 - 1;
-  const int shift = (du * f.W + dv) * C + c;
-  {
-    const int ob = blockIdx.z * (32 * OB);
-    f32x16 acc[OB];
-    int col[OB];                                 // this lane's channels; past the last one: read as channel 0, not stored
+  const int t = l32, tap = t / C, du = tap / 3 - 1, dv = tap % 3 - 1;
+  const int shift = ((du * f.W + dv) * C + t - tap * C) * 4;
+  f32x16 acc[OB], low[OB];
+  unsigned col[OB];                            // this lane's channels; past the last one: out of range
+  float mu[OB], scale[OB], base[OB], slope[OB];                // dZ = scale (dY - base - (Z - mu) slope)
 #pragma unroll
-    for (int q = 0; q < OB; ++q) {
-      col[q] = ob + 32 * q + l32 < f.Cout ? ob + 32 * q + l32 : 0;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[q][e] = 0.f;
+  for (int q = 0; q < OB; ++q) {
+    const int c = ob + 32 * q + l32;
+    const bool mine = c < f.Cout;
+    col[q] = mine ? (unsigned)c * 4u : kOob;
+    if constexpr (NORM) {
+      const float* st = norm.stats + (long long)k * 2 * f.Cout;
+      const float inv_n = 1.f / (float)rows;
+      mu[q] = mine ? st[c] : 0.f;
+      const float inv = mine ? st[f.Cout + c] : 0.f;
+      scale[q] = mine ? norm.params[k * f.strideParams + norm.gam_off + c] * inv : 0.f;
+      slope[q] = mine ? inv * (norm.grad[k * f.strideParams + norm.gam_off + c] * inv_n) : 0.f;
+      base[q] = mine ? norm.grad[k * f.strideParams + norm.bet_off + c] * inv_n : 0.f;
     }
-    // loads are issued unconditionally (from a clamped pixel) and zeroed afterwards, so that the
-    // unrolled loop can have many of them in flight
-    const int last = (int)f.rows - 1;
-    for (int s0 = 0; s0 < chunk_px / 8; s0 += 8)
 #pragma unroll
-    for (int s = s0; s < s0 + 8; ++s) {
-      const int p = p0 + 2 * s + h;
-      const int pc = p < last ? p : last;
-      int i, j;
-      pixel_rc(pc, f, i, j);
-      const bool in_img = t < 9 * C && (unsigned)(i + du) < (unsigned)f.H && (unsigned)(j + dv) < (unsigned)f.W;
-      float a[OB];
+    for (int e = 0; e < 16; ++e) acc[q][e] = low[q][e] = 0.f;
+  }
+  float b[8], a[OB][8], z[NORM ? OB : 1][8];
+  const bool rows_of_8 = f.W % 8 == 0;         // eight pixels from a multiple of 8 on lie in one row of the image
+  const int pixel = f.Cout * 4;
+  const auto request = [&](int pstart) {
+    const int p8 = pstart + h * 8;
+    int i, j;
+    pixel_rc(p8 < rows ? p8 : 0, f, i, j);
+    if (rows_of_8) {
+      const bool ok = t < 9 * C && p8 < rows && (unsigned)(i + du) < (unsigned)f.H;
+      const unsigned at = ok ? (unsigned)(p8 * (C * 4) + shift) : kOob;
 #pragma unroll
-      for (int q = 0; q < OB; ++q) a[q] = dz[(long long)pc * f.Cout + col[q]];
-      float b = img[in_img ? (long long)pc * C + shift : 0];
-      b = in_img ? b : (t == 9 * C ? 1.f : 0.f);
-      if (p > last) b = 0.f;
-      if (round) b = to_bf16(b);
-#pragma unroll
-      for (int q = 0; q < OB; ++q) {
-        if (p > last) a[q] = 0.f;
-        if (round) a[q] = to_bf16(a[q]);
-        acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(b, a[q], acc[q], 0, 0, 0);
+      for (int e = 0; e < 8; ++e) {
+        const bool off_rim = e == 0 ? dv < 0 && j == 0 : e == 7 && dv > 0 && j + 8 == f.W;
+        b[e] = load_float(img, (off_rim ? kOob : at) + e * (C * 4));
       }
-    }
-    // acc[q][e]: o = ob + 32 q + l32, t = (e/4)*8 + h*4 + e%4
+    } else {
 #pragma unroll
-    for (int q = 0; q < OB; ++q) {
-      if (wave > 0) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) red[wave - 1][l32 * 32 + (e / 4) * 8 + h * 4 + e % 4] = acc[q][e];
-      }
-      __syncthreads();
-      if (wave == 0 && ob + 32 * q + l32 < f.Cout) {
-        float* dst = partial + (((long long)k * chunks + blockIdx.x) * f.Cout + ob + 32 * q + l32) * 32;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int tt = u * 8 + h * 4;
-          f32x4 v;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int at = l32 * 32 + tt + r;
-            v[r] = ((acc[q][u * 4 + r] + red[0][at]) + red[1][at]) + red[2][at];
-          }
-          *reinterpret_cast<f32x4*>(dst + tt) = v;
+      for (int e = 0; e < 8; ++e) {
+        const int p = p8 + e;
+        const bool ok = t < 9 * C && p < rows && (unsigned)(i + du) < (unsigned)f.H && (unsigned)(j + dv) < (unsigned)f.W;
+        b[e] = load_float(img, ok ? (unsigned)(p * (C * 4) + shift) : kOob);
+        if (++j == f.W) {
+          j = 0;
+          if (++i == f.H) i = 0;
         }
       }
-      __syncthreads();
     }
+    if (t == 9 * C)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) b[e] = p8 + e < rows ? 1.f : 0.f;
+    // (pixels past the last one lie past the end of the buffer)
+#pragma unroll
+    for (int q = 0; q < OB; ++q) {
+      const unsigned at = col[q] != kOob ? (unsigned)p8 * (unsigned)pixel + col[q] : kOob;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        a[q][e] = load_float(dz, at, e * pixel);
+        if constexpr (NORM) z[q][e] = load_float(zs, at, e * pixel);
+      }
+    }
+  };
+  request(p0);
+  for (int s = 0; s < chunk_px / 64; ++s) {
+    u32x4 fb[NP], fa[OB][NP];
+    split_fragment<NP>(b, fb);
+#pragma unroll
+    for (int q = 0; q < OB; ++q) {
+      if constexpr (NORM) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) a[q][e] = scale[q] * ((a[q][e] - base[q]) - (z[q][e] - mu[q]) * slope[q]);
+      }
+      split_fragment<NP>(a[q], fa[q]);
+    }
+    if (s + 1 < chunk_px / 64) request(p0 + (s + 1) * 16);
+#pragma unroll
+    for (int q = 0; q < OB; ++q) multiply<NP>(fb, fa[q], acc[q], low[q]);
+  }
+  // acc[q][e]: o = ob + 32 q + l32, t = (e/4)*8 + h*4 + e%4
+#pragma unroll
+  for (int q = 0; q < OB; ++q) {
+    if constexpr (NP == 3) join_sums(acc[q], low[q]);
+    if (wave > 0) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) red[wave - 1][l32 * 32 + (e / 4) * 8 + h * 4 + e % 4] = acc[q][e];
+    }
+    __syncthreads();
+    if (wave == 0 && ob + 32 * q + l32 < f.Cout) {
+      float* dst = partial + (((long long)k * chunks + blockIdx.x) * f.Cout + ob + 32 * q + l32) * 32;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int tt = u * 8 + h * 4;
+        f32x4 v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int at = l32 * 32 + tt + r;
+          v[r] = ((acc[q][u * 4 + r] + red[0][at]) + red[1][at]) + red[2][at];
+        }
+        *reinterpret_cast<f32x4*>(dst + tt) = v;
+      }
+    }
+    __syncthreads();
   }
 }
 
@@ -703,9 +865,12 @@ __device__ __forceinline__ f32x4 with_shortcut(f32x4 y, const Shortcut& sc, cons
     y += normalised(*reinterpret_cast<const f32x4*>(sc.pz + idx * 4), proj);
   } else if (sc.src != nullptr && c < sc.Cs) {       // Cs % 4 == 0: a word lies inside or outside
     const long long m = idx / words - (long long)k * rows;       // (b, i, j) of this replica
-    const int j = (int)(m % sc.W), i = (int)((m / sc.W) % sc.H);
-    const long long b = m / ((long long)sc.W * sc.H);
-    const long long at = ((b * (sc.st * sc.H) + sc.st * i) * (sc.st * sc.W) + sc.st * j) * sc.Cs + c;
+    long long at = m * sc.Cs + c;
+    if (sc.st != 1) {
+      const int j = (int)(m % sc.W), i = (int)((m / sc.W) % sc.H);
+      const long long b = m / ((long long)sc.W * sc.H);
+      at = ((b * (sc.st * sc.H) + sc.st * i) * (sc.st * sc.W) + sc.st * j) * sc.Cs + c;
+    }
     y += *reinterpret_cast<const f32x4*>(sc.src + k * sc.stride + at);
   }
   return y;
@@ -1085,36 +1250,53 @@ static FirstConv first_shape(int H, int W, int Cout, int64_t rows, int64_t strid
   return FirstConv{H, W, Cout, 1.f / (float)W, 1.f / (float)H, rows, strideParams, ldw};
 }
 
+// Pixels a workgroup of the forward kernel takes, in 128s: as many (up to 4) as leave the launch a thousand workgroups; what a
+// workgroup does first, its filters, then counts least.
+static int first_tiles(int64_t rows, int Cout, int K) {
+  const int64_t groups = (rows + 127) / 128 * K * ((Cout + 63) / 64);
+  return groups >= 4096 ? 4 : groups >= 2048 ? 2 : 1;
+}
 int launch_first_conv_forward(const float* X, const float* params, int64_t strideParams, int64_t w_off,
                               int64_t b_off, int ldw, float* out, int relu, int round, int K,
-                              int64_t rows, int H, int W, int C, int Cout, hipStream_t s) {
+                              int64_t rows, int H, int W, int C, int Cout, float* sums, ChunkSums* made, hipStream_t s) {
   if (!first_conv_fits(C, Cout, rows, K, round)) return -1;
   const FirstConv f = first_shape(H, W, Cout, rows, strideParams, ldw);
-  // where pixels give few workgroups, one for every 32 channels
-  const int group = (rows + 127) / 128 * K < 512 ? 32 : (Cout + 31) / 32 * 32;
-  const dim3 grid((unsigned)((rows + 127) / 128), (unsigned)K, (unsigned)((Cout + group - 1) / group));
-  const size_t lds = (size_t)group * 33 * 4;
-  if (C == 1) first_conv_forward_kernel<1><<<grid, kThreads, lds, s>>>(X, params, w_off, b_off, out, f, group, relu, round);
-  else if (C == 2) first_conv_forward_kernel<2><<<grid, kThreads, lds, s>>>(X, params, w_off, b_off, out, f, group, relu, round);
-  else first_conv_forward_kernel<3><<<grid, kThreads, lds, s>>>(X, params, w_off, b_off, out, f, group, relu, round);
+  const int tiles = first_tiles(rows, Cout, K);
+  // (few pixels give few workgroups: one for every 32 channels then)
+  const int ob = Cout > 32 && (rows + 127) / 128 * K >= 512 ? 2 : 1;
+  const dim3 grid((unsigned)((rows + 128 * tiles - 1) / (128 * tiles)), (unsigned)K, (unsigned)((Cout + 32 * ob - 1) / (32 * ob)));
+  auto run = [&](auto kernel) { kernel<<<grid, kThreads, 0, s>>>(X, params, w_off, b_off, out, f, tiles, relu, sums); };
+  auto pick = [&](auto o1p1, auto o1p3, auto o2p1, auto o2p3) {
+    run(ob == 1 ? (round ? o1p1 : o1p3) : (round ? o2p1 : o2p3));
+  };
+  if (C == 1) pick(first_conv_forward_kernel<1, 1, 1>, first_conv_forward_kernel<1, 1, 3>, first_conv_forward_kernel<1, 2, 1>, first_conv_forward_kernel<1, 2, 3>);
+  else if (C == 2) pick(first_conv_forward_kernel<2, 1, 1>, first_conv_forward_kernel<2, 1, 3>, first_conv_forward_kernel<2, 2, 1>, first_conv_forward_kernel<2, 2, 3>);
+  else pick(first_conv_forward_kernel<3, 1, 1>, first_conv_forward_kernel<3, 1, 3>, first_conv_forward_kernel<3, 2, 1>, first_conv_forward_kernel<3, 2, 3>);
+  if (made) *made = sums ? ChunkSums{(int)grid.x, 128 * tiles} : ChunkSums{};
   return 0;
 }
 
-int launch_first_conv_wgrad(const float* X, const float* dout, float* partial, float* grad,
+int launch_first_conv_wgrad(const float* X, const float* dout, const FirstNorm& norm, float* partial, float* grad,
                             int64_t strideParams, int64_t w_off, int64_t b_off, int ldw, int round,
                             int skip_bias, int K, int64_t rows, int H, int W, int C, int Cout,
                             double* sumsq, int64_t sumsq_stride, hipStream_t s) {
   if (!first_conv_fits(C, Cout, rows, K, round)) return -1;
   const FirstConv f = first_shape(H, W, Cout, rows, strideParams, ldw);
   const int chunks = first_conv_chunks(rows, Cout, K), px = first_chunk_px(rows, Cout, K);
-  const dim3 grid((unsigned)chunks, (unsigned)K, (unsigned)((Cout + 63) / 64));
-  auto run = [&](auto one, auto two) {
-    if (Cout > 32) two<<<grid, kThreads, 0, s>>>(X, dout, partial, chunks, px, f, round);
-    else one<<<grid, kThreads, 0, s>>>(X, dout, partial, chunks, px, f, round);
-  };
-  if (C == 1) run(first_conv_wgrad_kernel<1, 1>, first_conv_wgrad_kernel<1, 2>);
-  else if (C == 2) run(first_conv_wgrad_kernel<2, 1>, first_conv_wgrad_kernel<2, 2>);
-  else run(first_conv_wgrad_kernel<3, 1>, first_conv_wgrad_kernel<3, 2>);
+  const int ob = Cout > 32 ? 2 : 1;
+  const dim3 grid((unsigned)chunks, (unsigned)K, (unsigned)((Cout + 32 * ob - 1) / (32 * ob)));
+  auto run = [&](auto kernel) { kernel<<<grid, kThreads, 0, s>>>(X, dout, partial, chunks, px, f, norm); };
+  auto pick = [&](auto p1, auto p3, auto p1n, auto p3n) { run(norm.z ? (round ? p1n : p3n) : (round ? p1 : p3)); };
+#define LSAM_FIRST_WGRAD(c, o)                                                                                       \
+  pick(first_conv_wgrad_kernel<c, o, 1, false>, first_conv_wgrad_kernel<c, o, 3, false>, first_conv_wgrad_kernel<c, o, 1, true>, \
+       first_conv_wgrad_kernel<c, o, 3, true>)
+  if (C == 1 && ob == 1) LSAM_FIRST_WGRAD(1, 1);
+  else if (C == 1) LSAM_FIRST_WGRAD(1, 2);
+  else if (C == 2 && ob == 1) LSAM_FIRST_WGRAD(2, 1);
+  else if (C == 2) LSAM_FIRST_WGRAD(2, 2);
+  else if (ob == 1) LSAM_FIRST_WGRAD(3, 1);
+  else LSAM_FIRST_WGRAD(3, 2);
+#undef LSAM_FIRST_WGRAD
   first_conv_wgrad_finish_kernel<<<dim3((unsigned)(Cout / 2), (unsigned)K), 1024, 0, s>>>(
       partial, chunks, C, grad, w_off, b_off, sumsq, sumsq_stride, f, skip_bias);
   return Cout / 2;     // sum-of-squares slots written per replica

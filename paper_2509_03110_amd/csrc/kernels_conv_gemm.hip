@@ -380,25 +380,6 @@ struct Reader {
   }
 };
 
-// Results with three planes from their two sums, the products of the leading pieces and the other
-// five: `leading` becomes both.  An infinite leading sum (or NaN) is the result: the leading piece of a
-// finite number is finite, of an infinite one the number itself, so these products overflow, or are
-// infinite or NaN, where the products of the numbers are, while the small ones may then be infinite
-// with the other sign.  (One look at the largest of sixteen: a compare and a choice for each value cost
-// 16-channel layers 1.3 %.)
-__device__ __forceinline__ void join_sums(f32x16& leading, f32x16& small) {
-  float most = 0.f;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) most = __builtin_fmaxf(most, __builtin_fabsf(leading[e]));
-  if (__builtin_expect(__builtin_isinf(most), 0)) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e)
-      if (__builtin_isinf(leading[e])) small[e] = 0.f;
-  }
-#pragma unroll
-  for (int e = 0; e < 16; ++e) leading[e] += small[e];
-}
-
 template <int MASK, int N, int M, int I>
 struct Interleave {
   static __device__ __forceinline__ void run() {

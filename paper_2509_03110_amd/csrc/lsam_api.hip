@@ -926,7 +926,7 @@ int conv_forward(lsam_ctx* c, const float* X, const float* params) {
       if (launch_first_conv_forward(in, params, lo.d_pad, ly.w_off, ly.b_off, ly.ldw,
                                     c->at<float>(cv.bn ? cv.z : cv.out), cv.bn ? 0 : 1,
                                     lo.bf16_math ? 1 : 0, lo.K, cv.rows, cv.H, cv.W, cv.Cin, cv.Cout,
-                                    s) != 0)
+                                    cv.bn ? scratch : nullptr, &have, s) != 0)
         return fail(LSAM_EINVAL, "first convolution rejected");
     } else if (!cv.direct_in) {
       LaunchTimer t(c, KC_UNFOLD);
@@ -1136,6 +1136,7 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
         launch_bn_backward_apply(c->at<float>(cv.z), dy, floats ? dz : nullptr, c->at<float>(cv.stats), params, g,
                                  lo.d_pad, ly.gam_off, ly.bet_off, lo.K, cv.rows, cv.Cout, cv.fast ? handed : nullptr, po, s);
     };
+    FirstNorm first_norm;
     // The projection of a post-activation block goes first: its planes take the same place
     const bool own_last = cv.proj && !lo.preact;
     if (cv.bn) {
@@ -1154,7 +1155,10 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
                                                  ssq ? ssq + *slots : nullptr, lo.nblk, s);
         if (ssq) *slots += used;
       }
-      if (!own_last) own_gradient();
+      // (a first layer's weight gradient forms its dZ itself, unless that is a shortcut's as well)
+      if (cv.first && !cv.bn_pool && dy.HW == 0 && !handed)
+        first_norm = FirstNorm{c->at<float>(cv.z), c->at<float>(cv.stats), params, g, ly.gam_off, ly.bet_off};
+      else if (!own_last) own_gradient();
       if (cv.proj && !lo.preact) {
         // the same gradient dY enters the projection's normalisation: dgamma_p, dbeta_p, then
         // the gradient of the 1x1 convolution's output, which takes that output's place
@@ -1232,7 +1236,7 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
     dout = dz;
     if (cv.first) {
       LaunchTimer t(c, KC_CONV_FIRST);
-      const int used = launch_first_conv_wgrad(X, dout, c->at<float>(cv.first_partial), g, lo.d_pad,
+      const int used = launch_first_conv_wgrad(X, dout, first_norm, c->at<float>(cv.first_partial), g, lo.d_pad,
                                                ly.w_off, ly.b_off, ly.ldw, lo.bf16_math ? 1 : 0,
                                                (lo.bf16_math || cv.bn) ? 1 : 0, lo.K,
                                                cv.rows, cv.H, cv.W, cv.Cin, cv.Cout,

@@ -5,8 +5,10 @@ behind a bare ReLU, and the global average with and without a shortcut that hand
 
 Unlike the nets of test_gpu_plane_products.py half of all values are rectified, pixel by pixel, so a bit of another pixel
 or channel shows: half of the gradient's terms would be wrong.  A value within rounding of zero (1e-6 of its
-spread in fp32, one in 1e6) may be decided differently and carries then about 1e-3 of its layer's gradient, 1 / sqrt(values);
-with operands rounded to bfloat16 decisions within 2^-8 differ, of which the gradient's norm shows sqrt(2^-8) = 6e-2."""
+spread in fp32, one in 1e6) may be decided differently from the oracle.  Of the smallest image's V = 1.5e5 values (135000
+behind the pre-activation blocks) half carry gradient, one of them (2 / V)^(1/2) = 3.7e-3 of its norm on average; four times
+that for the largest is 1.5e-2, the bound (measured: 2e-7 to 5e-7, with one such decision 8e-5, 4.5e-4 and 4.8e-3).  With operands
+rounded to bfloat16 decisions within 2^-8 differ, of which the gradient's norm shows sqrt(2^-8) = 6e-2."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -49,7 +51,7 @@ def test_rectified_values_against_the_oracle(name, bf16):
     o.step(X, lab)
     for i in range(w.K):
         got, want = g.lsam_get_buffer(lsam.BUF_VELOCITY, i), o.v[i]
-        assert rel_l2(got, want) < (6e-2 if bf16 else 2e-3), (i, rel_l2(got, want))
+        assert rel_l2(got, want) < (6e-2 if bf16 else 1.5e-2), (i, rel_l2(got, want))
     g.close()
 
 

@@ -372,6 +372,12 @@ template <int NP>
 __device__ __forceinline__ void split_fragment(const float (&x)[8], u32x4 (&f)[NP]) {
   unsigned o[NP][4];
   split_words<NP>(x, o);
+  if constexpr (NP == 3) {
+    float most = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) most = largest_of(most, x[e]);
+    if (past_rounding(most)) split_words_any<NP>(x, o);
+  }
 #pragma unroll
   for (int q = 0; q < NP; ++q) f[q] = u32x4{o[q][0], o[q][1], o[q][2], o[q][3]};
 }

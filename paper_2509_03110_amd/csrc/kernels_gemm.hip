@@ -24,6 +24,7 @@
 
 #include "dense_gradients.h"
 #include "engine.h"
+#include "planes.h"
 
 namespace lsam {
 namespace {
@@ -402,6 +403,108 @@ struct Pipeline {
 __device__ __forceinline__ float widen(float v) { return v; }
 __device__ __forceinline__ float widen(__bf16 v) { return static_cast<float>(v); }
 
+// Writes a workgroup's BM x BN results, four wavefronts in a 2x2 arrangement with TM x TN blocks of 32 x 32 each, as the launch
+// asks (or, of a split contraction, as they are).
+template <typename T, typename TC, int BM, int BN>
+__device__ __forceinline__ void write_tile(const GemmParams& p, const f32x16 (&acc)[BM / 64][BN / 64], unsigned char* smem, int split,
+                                           int bat, int t, int m0, int n0) {
+  constexpr int TM = BM / 64, TN = BN / 64;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int wn0 = (wave & 1) * (BN / 2);
+  const int l32 = lane & 31, h = lane >> 5;
+  // Epilogue.  With the swapped MFMA roles, accumulator element e of a 32x32 tile belongs to
+  // row m = l32 and column n = (e/4)*8 + h*4 + e%4.  Stores straight from that layout would
+  // scatter 16-byte pieces over 32 rows per instruction; instead the tile is passed through
+  // LDS (now free) 64 rows at a time and written out as whole rows, consecutive lanes on
+  // consecutive 16 bytes, which is also how bias and the ReLU mask are read.
+  const bool split_mode = p.splits > 1;     // raw partial sums; bias/ReLU/mask wait for the reduce
+  TC* C = split_mode ? reinterpret_cast<TC*>(p.partial + (long long)split * p.strideSplit +
+                                             (long long)bat * p.M * p.ldP)
+                     : reinterpret_cast<TC*>(p.C) + (long long)bat * p.strideC;
+  const int ldC = split_mode ? p.ldP : p.ldC;
+  const float* bias = p.bias ? p.bias + (long long)bat * p.strideBias : nullptr;
+  const float* bias_dir = p.bias_dir ? p.bias_dir + (long long)bat * p.strideBias : nullptr;
+  const float bias_sc = p.bias_dir ? p.bias_scale[bat] : 0.f;
+  const T* mask = p.mask ? reinterpret_cast<const T*>(p.mask) + (long long)bat * p.strideMask
+                         : nullptr;
+  const bool has_bias = !split_mode && (p.epilogue == EPI_BIAS || p.epilogue == EPI_BIAS_RELU);
+  const bool relu = !split_mode && p.epilogue == EPI_BIAS_RELU;
+  const bool masked = !split_mode && p.epilogue == EPI_MASK;
+  typedef typename Pack<TC>::vec cvec;
+  typedef typename Pack<T>::vec mvec;
+  constexpr int PITCH = BN + 4;                 // floats; +4 keeps the 16-byte writes off one bank
+  constexpr int LANES_PER_ROW = BN / 4;         // lanes that cover one row of the tile
+  constexpr int ROWS_PER_PASS = kThreads / LANES_PER_ROW;
+  float* stage = reinterpret_cast<float*>(smem);
+  const int c4 = (tid % LANES_PER_ROW) * 4;     // first of this lane's 4 columns (read-out phase)
+  const int rsub = tid / LANES_PER_ROW;
+  const int n = n0 + c4;
+  float ssq = 0.f;                              // squares of what this thread stores
+  f32x4 bv = {0.f, 0.f, 0.f, 0.f};
+  if (has_bias) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (n + r < p.N) {
+        bv[r] = bias[n + r];
+        if (bias_dir) bv[r] = bv[r] + bias_sc * bias_dir[n + r];   // bias of the perturbed point
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    // rows of this pass: for each of the two wave rows, its i-th 32-row strip
+    const int lrow = (wave >> 1) * 32 + l32;
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        f32x4 v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = acc[i][j][q * 4 + r];
+        *reinterpret_cast<f32x4*>(stage + lrow * PITCH + wn0 + j * 32 + q * 8 + h * 4) = v;
+      }
+    __syncthreads();
+#pragma unroll
+    for (int pass = 0; pass < 64 / ROWS_PER_PASS; ++pass) {
+      const int rr = pass * ROWS_PER_PASS + rsub;
+      const int m = m0 + (rr >> 5) * (BM / 2) + i * 32 + (rr & 31);
+      if (m < p.M && n < p.N) {
+        f32x4 v = *reinterpret_cast<const f32x4*>(stage + rr * PITCH + c4);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          v[r] += bv[r];
+          if (relu) v[r] = v[r] > 0.f ? v[r] : 0.f;
+        }
+        if (n + 3 < p.N) {
+          if (masked) {
+            const mvec mk = *reinterpret_cast<const mvec*>(mask + (long long)m * p.ldMask + n);
+            const T* me = reinterpret_cast<const T*>(&mk);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if (!(widen(me[r]) > 0.f)) v[r] = 0.f;
+          }
+          *reinterpret_cast<cvec*>(C + (long long)m * ldC + n) = Pack<TC>::from(v);
+          ssq += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (n + r < p.N) {
+              float o = v[r];
+              if (masked && !(widen(mask[(long long)m * p.ldMask + n + r]) > 0.f)) o = 0.f;
+              C[(long long)m * ldC + n + r] = Pack<TC>::one(o);
+              ssq += o * o;
+            }
+        }
+      }
+    }
+    if (i + 1 < TM) __syncthreads();
+  }
+  if (p.sumsq != nullptr && !split_mode) {
+    const double tot = workgroup_sum((double)ssq);
+    if (tid == 0) p.sumsq[(long long)bat * p.strideSumsq + t] = tot;
+  }
+}
+
 // CONV: 0 = both operands stored; 1 = A is an unfolded image (k-major); 2 = B is one (m-major).
 // BF16MATH (fp32 operands only): the operands stay fp32 in memory; they are rounded to bfloat16
 // (round to nearest even) as the loaded tile is written to LDS, in units of 8 instead of 16
@@ -632,96 +735,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int w) {
   }
   __syncthreads();
 
-  // Epilogue.  With the swapped MFMA roles, accumulator element e of a 32x32 tile belongs to
-  // row m = l32 and column n = (e/4)*8 + h*4 + e%4.  Stores straight from that layout would
-  // scatter 16-byte pieces over 32 rows per instruction; instead the tile is passed through
-  // LDS (now free) 64 rows at a time and written out as whole rows, consecutive lanes on
-  // consecutive 16 bytes, which is also how bias and the ReLU mask are read.
-  const bool split_mode = p.splits > 1;     // raw partial sums; bias/ReLU/mask wait for the reduce
-  TC* C = split_mode ? reinterpret_cast<TC*>(p.partial + (long long)split * p.strideSplit +
-                                             (long long)bat * p.M * p.ldP)
-                     : reinterpret_cast<TC*>(p.C) + (long long)bat * p.strideC;
-  const int ldC = split_mode ? p.ldP : p.ldC;
-  const float* bias = p.bias ? p.bias + (long long)bat * p.strideBias : nullptr;
-  const float* bias_dir = p.bias_dir ? p.bias_dir + (long long)bat * p.strideBias : nullptr;
-  const float bias_sc = p.bias_dir ? p.bias_scale[bat] : 0.f;
-  const T* mask = p.mask ? reinterpret_cast<const T*>(p.mask) + (long long)bat * p.strideMask
-                         : nullptr;
-  const bool has_bias = !split_mode && (p.epilogue == EPI_BIAS || p.epilogue == EPI_BIAS_RELU);
-  const bool relu = !split_mode && p.epilogue == EPI_BIAS_RELU;
-  const bool masked = !split_mode && p.epilogue == EPI_MASK;
-  typedef typename Pack<TC>::vec cvec;
-  typedef typename Pack<T>::vec mvec;
-  constexpr int PITCH = BN + 4;                 // floats; +4 keeps the 16-byte writes off one bank
-  constexpr int LANES_PER_ROW = BN / 4;         // lanes that cover one row of the tile
-  constexpr int ROWS_PER_PASS = kThreads / LANES_PER_ROW;
-  float* stage = reinterpret_cast<float*>(smem);
-  const int c4 = (tid % LANES_PER_ROW) * 4;     // first of this lane's 4 columns (read-out phase)
-  const int rsub = tid / LANES_PER_ROW;
-  const int n = n0 + c4;
-  float ssq = 0.f;                              // squares of what this thread stores
-  f32x4 bv = {0.f, 0.f, 0.f, 0.f};
-  if (has_bias) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (n + r < p.N) {
-        bv[r] = bias[n + r];
-        if (bias_dir) bv[r] = bv[r] + bias_sc * bias_dir[n + r];   // bias of the perturbed point
-      }
-  }
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    // rows of this pass: for each of the two wave rows, its i-th 32-row strip
-    const int lrow = (wave >> 1) * 32 + l32;
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        f32x4 v;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = acc[i][j][q * 4 + r];
-        *reinterpret_cast<f32x4*>(stage + lrow * PITCH + wn0 + j * 32 + q * 8 + h * 4) = v;
-      }
-    __syncthreads();
-#pragma unroll
-    for (int pass = 0; pass < 64 / ROWS_PER_PASS; ++pass) {
-      const int rr = pass * ROWS_PER_PASS + rsub;
-      const int m = m0 + (rr >> 5) * (BM / 2) + i * 32 + (rr & 31);
-      if (m < p.M && n < p.N) {
-        f32x4 v = *reinterpret_cast<const f32x4*>(stage + rr * PITCH + c4);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          v[r] += bv[r];
-          if (relu) v[r] = v[r] > 0.f ? v[r] : 0.f;
-        }
-        if (n + 3 < p.N) {
-          if (masked) {
-            const mvec mk = *reinterpret_cast<const mvec*>(mask + (long long)m * p.ldMask + n);
-            const T* me = reinterpret_cast<const T*>(&mk);
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-              if (!(widen(me[r]) > 0.f)) v[r] = 0.f;
-          }
-          *reinterpret_cast<cvec*>(C + (long long)m * ldC + n) = Pack<TC>::from(v);
-          ssq += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
-        } else {
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (n + r < p.N) {
-              float o = v[r];
-              if (masked && !(widen(mask[(long long)m * p.ldMask + n + r]) > 0.f)) o = 0.f;
-              C[(long long)m * ldC + n + r] = Pack<TC>::one(o);
-              ssq += o * o;
-            }
-        }
-      }
-    }
-    if (i + 1 < TM) __syncthreads();
-  }
-  if (p.sumsq != nullptr && !split_mode) {
-    const double tot = workgroup_sum((double)ssq);
-    if (tid == 0) p.sumsq[(long long)bat * p.strideSumsq + t] = tot;
-  }
+  write_tile<T, TC, BM, BN>(p, acc, smem, split, bat, t, m0, n0);
 }
 
 template <typename T, typename TC, int BM, int BN, int BKU, bool A_KMAJOR, bool B_KMAJOR, int OCC,
@@ -729,6 +743,185 @@ template <typename T, typename TC, int BM, int BN, int BKU, bool A_KMAJOR, bool 
 __global__ __launch_bounds__(kThreads, OCC) void gemm_kernel(GemmParams p) {
   gemm_tile<T, TC, BM, BN, BKU, A_KMAJOR, B_KMAJOR, CONV, BF16MATH>(p, blockIdx.x);
 }
+
+// ---- fp32 products on the bf16 matrix units -------------------------------------------------------
+// An fp32 number is the exact sum of three bfloat16 numbers, and six of the nine cross products leave less behind than an fp32
+// sum rounds away (kernels_conv_gemm.hip): fp32 arithmetic at 2.7 times the fp32 units' rate.  The operands stay fp32 in
+// memory and are split as their tile goes to LDS, once a workgroup, 6 operations a value (48 products of 32 cycles beside
+// 200 operations of 4 in a k-step of 32 for a wavefront of 64 x 64 results).  The next step's loads are in flight in
+// registers, and two workgroups share a compute unit: one's splitting, waiting and LDS reads run under the other's products.
+// What bounds it at these sizes is the wait for the loads, six to twenty steps a workgroup: four products 128 x 1024 x 3072
+// 38 us on the fp32 units, 29 here (110 TFLOP/s), all weight gradients of 3072-1024-1024-10 with 128 rows 55 us and 44; eight
+// 256-2048-2048-24 with 512 rows, a step, 2119 and 1725.  Two steps of 16 in flight and two LDS buffers: 31 us.  The sums are nearer to their
+// 64-bit values than the fp32 units' (a rounding per 16 products: gradients 1.2e-7 to 4.2e-7 off, 2.6e-7 to 6.5e-7 there).
+// LDS: [plane][unit of 8 k][row], 16 bytes; a row lies at position r ^ (r / 16) % 4, which keeps the writes of a transposed
+// operand (lane i on rows 4 i ..) on different banks, and a unit's pitch of 4 rows more those of the other kind.
+template <int R, bool KMAJOR>
+struct SplitLoader {
+  static constexpr int PITCH = R + 4, PLANE = 4 * PITCH;       // in 16-byte units
+  TileLoader<float, R, KMAJOR, 8> t;
+  static __device__ __forceinline__ int position(int r) { return r ^ ((r >> 4) & 3); }
+  __device__ __forceinline__ float largest() const {
+    float most = 0.f;
+#pragma unroll
+    for (int j = 0; j < TileLoader<float, R, KMAJOR, 8>::NREG; ++j) {
+      const f32x4 v = __builtin_bit_cast(f32x4, t.reg[j]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) most = largest_of(most, v[e]);
+    }
+    return most;
+  }
+  template <bool ANY>
+  static __device__ __forceinline__ void split4(const u32x4& unit, unsigned (&o)[3][2]) {
+    const f32x4 v = __builtin_bit_cast(f32x4, unit);
+    const float x[4] = {v[0], v[1], v[2], v[3]};
+    if constexpr (ANY) split_words_any<3>(x, o);
+    else split_words<3>(x, o);
+  }
+  template <bool ANY>
+  __device__ __forceinline__ void store(unsigned char* lds, int tid) const {
+    typedef TileLoader<float, R, KMAJOR, 8> L;
+    if constexpr (KMAJOR) {
+#pragma unroll
+      for (int j = 0; j < L::NUNITS; ++j) {
+        const int u = tid + kThreads * j, ku = u % 8;
+        unsigned o[3][2];
+        split4<ANY>(t.reg[j], o);
+        unsigned char* at = lds + ((ku >> 1) * PITCH + position(u / 8)) * 16 + (ku & 1) * 8;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x2*>(at + q * (PLANE * 16)) = u32x2{o[q][0], o[q][1]};
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < L::NBLK; ++j) {
+        const int b = tid + kThreads * j;
+        if (L::NBLK_TOTAL % kThreads != 0 && b >= L::NBLK_TOTAL) continue;
+        const int mg = b % (R / 4), ku = b / (R / 4);
+        unsigned o[4][3][2];                   // of each k: its four rows' pieces, two to a word
+#pragma unroll
+        for (int k = 0; k < 4; ++k) split4<ANY>(t.reg[j * 4 + k], o[k]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const unsigned sel = (e & 1) ? 0x07060302u : 0x05040100u;   // odd / even halfwords of {hi, lo}
+          unsigned char* at = lds + ((ku >> 1) * PITCH + position(mg * 4 + e)) * 16 + (ku & 1) * 8;
+#pragma unroll
+          for (int q = 0; q < 3; ++q)
+            *reinterpret_cast<u32x2*>(at + q * (PLANE * 16)) =
+                u32x2{__builtin_amdgcn_perm(o[1][q][e / 2], o[0][q][e / 2], sel), __builtin_amdgcn_perm(o[3][q][e / 2], o[2][q][e / 2], sel)};
+        }
+      }
+    }
+  }
+};
+template <int BM, int BN>
+constexpr size_t split_tile_lds() {
+  const size_t loop = (size_t)3 * 4 * ((BM + 4) + (BN + 4)) * 16, epilogue = (size_t)64 * (BN + 4) * 4;
+  return loop > epilogue ? loop : epilogue;
+}
+
+// Workgroup w's tile of the product p describes (see gemm_tile).
+template <int BM, int BN, bool A_KMAJOR, bool B_KMAJOR>
+__device__ __forceinline__ void split_tile(const GemmParams& p, int w) {
+  constexpr int TM = BM / 64, TN = BN / 64;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int slot = (w % 8) * p.chunks + w / 8;
+  if (slot >= p.total) return;
+  // the splits of one tile are neighbours; inside a replica bands of 8 tile rows, row fastest
+  const int split = slot % p.splits, logical = slot / p.splits;
+  constexpr int GROUP_M = 8;
+  const int per_rep = p.tilesM * p.tilesN;
+  const int bat = logical / per_rep;
+  const int t = logical - bat * per_rep;
+  const int band = t / (GROUP_M * p.tilesN);
+  const int first_m = band * GROUP_M;
+  const int gsize = p.tilesM - first_m < GROUP_M ? p.tilesM - first_m : GROUP_M;
+  const int tin = t - band * GROUP_M * p.tilesN;
+  const int m0 = (first_m + tin % gsize) * BM, n0 = (tin / gsize) * BN;
+  const float* A = reinterpret_cast<const float*>(p.A) + (long long)bat * p.strideA;
+  const float* B = reinterpret_cast<const float*>(p.B) + (long long)bat * p.strideB;
+  const __amdgpu_buffer_rsrc_t rsrcA = make_rsrc(A, (unsigned)((A_KMAJOR ? p.M : p.Kd) * p.ldA) * 4u);
+  const __amdgpu_buffer_rsrc_t rsrcB = make_rsrc(B, (unsigned)((B_KMAJOR ? p.N : p.Kd) * p.ldB) * 4u);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm0 = (wave >> 1) * (BM / 2), wn0 = (wave & 1) * (BN / 2);
+  const int l32 = lane & 31, h = lane >> 5;
+
+  typedef SplitLoader<BM, A_KMAJOR> LoadA;
+  typedef SplitLoader<BN, B_KMAJOR> LoadB;
+  constexpr int A_BYTES = 3 * LoadA::PLANE * 16;
+  LoadA la;
+  LoadB lb;
+  const int steps_all = (p.Kd + 31) / 32, first = split * p.steps_per_split;
+  const int steps = steps_all - first < p.steps_per_split ? steps_all - first : p.steps_per_split;
+  const auto load = [&](int step) {               // a step past the last one of the contraction reads as zeros
+    la.t.load(rsrcA, p.ldA, m0, p.M, (first + step) * 8, p.Kd, tid);
+    lb.t.load(rsrcB, p.ldB, n0, p.N, (first + step) * 8, p.Kd, tid);
+  };
+  f32x16 acc[TM][TN], low[TM][TN];                // the products of the leading pieces, and the other five
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = low[i][j][e] = 0.f;
+  int posA[TM], posB[TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) posA[i] = (h * LoadA::PITCH + LoadA::position(wm0 + i * 32 + l32)) * 16;
+#pragma unroll
+  for (int j = 0; j < TN; ++j) posB[j] = A_BYTES + (h * LoadB::PITCH + LoadB::position(wn0 + j * 32 + l32)) * 16;
+
+  load(0);
+  for (int s = 0; s < steps; ++s) {
+    if (s > 0) __syncthreads();                   // the step before has been read
+    if (past_rounding(__builtin_fmaxf(la.largest(), lb.largest()))) {
+      la.template store<true>(smem, tid);
+      lb.template store<true>(smem + A_BYTES, tid);
+    } else {
+      la.template store<false>(smem, tid);
+      lb.template store<false>(smem + A_BYTES, tid);
+    }
+    load(s + 1);
+    __syncthreads();
+#pragma unroll
+    for (int kc = 0; kc < 2; ++kc) {
+      u32x4 fa[3][TM], fb[3][TN];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+          fa[q][i] = *reinterpret_cast<const u32x4*>(smem + (q * LoadA::PLANE + kc * 2 * LoadA::PITCH) * 16 + posA[i]);
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          fb[q][j] = *reinterpret_cast<const u32x4*>(smem + (q * LoadB::PLANE + kc * 2 * LoadB::PITCH) * 16 + posB[j]);
+      }
+      constexpr int xa[6] = {2, 0, 1, 1, 0, 0}, xb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+      for (int q = 0; q < 6; ++q)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            f32x16& to = q < 5 ? low[i][j] : acc[i][j];
+            to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb[xb[q]][j]), __builtin_bit_cast(bf16x8, fa[xa[q]][i]),
+                                                         to, 0, 0, 0);
+          }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) join_sums(acc[i][j], low[i][j]);
+  write_tile<float, float, BM, BN>(p, acc, smem, split, bat, t, m0, n0);
+}
+
+template <int BM, int BN, bool A_KMAJOR, bool B_KMAJOR>
+__global__ __launch_bounds__(kThreads, 2) void split_gemm_kernel(GemmParams p) {
+  split_tile<BM, BN, A_KMAJOR, B_KMAJOR>(p, blockIdx.x);
+}
+template __global__ void split_gemm_kernel<128, 128, true, true>(GemmParams);
+template __global__ void split_gemm_kernel<128, 128, true, false>(GemmParams);
+template __global__ void split_gemm_kernel<64, 128, true, true>(GemmParams);
+template __global__ void split_gemm_kernel<64, 128, true, false>(GemmParams);
 
 // Every gradient of the dense layers' parameters in one launch: the weight gradients dZ^T A of the items,
 // the narrow head's (if any) and the bias sums.  They wait for nothing but the dZ of the pass, and alone
@@ -739,6 +932,7 @@ struct DenseGrads {
   int n, B, K;
   float* g; long long strideG;
   double* sumsq; long long strideSumsq;
+  int split;                                    // the products by split_tile
   int head_first, head_blocks, bias_first;      // workgroups: the items', then head_blocks * K, then the biases'
   struct Item {
     const float* dz; const float* act;
@@ -793,6 +987,13 @@ __global__ __launch_bounds__(kThreads, OCC) void dense_gradients_kernel(GemmPara
   p.total = p.tilesM * p.tilesN * p.batch;
   p.chunks = (p.total + 7) / 8;
   p.sumsq = d.sumsq != nullptr ? d.sumsq + it.slot : nullptr;
+  // (by exact pieces of the operands, where no contraction would be cut: 55 us -> 44, see split_tile)
+  if constexpr (BT == 128 && !BF16MATH) {
+    if (d.split) {
+      split_tile<BT, BT, false, false>(p, w - it.first);
+      return;
+    }
+  }
   gemm_tile<float, float, BT, BT, 8, false, false, 0, BF16MATH, true>(p, w - it.first);
 }
 
@@ -876,10 +1077,24 @@ struct Plan {
   int bm, bn, bku;
   int splits, steps_per_split, ldP;
   size_t ws_bytes;
+  bool pieces = false;             // by split_gemm_kernel
 };
 
 // 64x64 tiles replace 128x128 ones when they compute less than this fraction of the work
 constexpr double kSmallTileGain = 0.88;
+
+// Forward products and input gradients by exact pieces: from 1.5e9 multiply-adds, 512 of them a result, on tiles of 128 columns
+// and 128 rows (64 up to 64) of which less than a third is padding.  A step before / with them (and the weight gradients by
+// pieces): one 3072-4096-1000 with 256 rows 543 / 512 us, with 512 822 / 736; six 600-2500-300 with 200 459 / 418; eight
+// 3000-2000-1000-500 with 200 1854 / 1687.  Below that the fp32 units' 64x64 tiles fill the chip better: two 512-512-512-10
+// with 100 rows 120 / 157, one 1000-600-10 with 64 66 / 73; and where much is padding: three 1000-1500-777-37 with 300
+// 461 / 482.  A piece of a contraction keeps six steps of 32 (with three, eight 512-512-512-512-10 with 512 462 / 501).
+bool split_pays(const GemmDesc& d) {
+  if (d.in_bf16 || d.bf16_math || d.unfold || !d.a_kmajor || d.M <= 32 || d.N < 128 || d.Kd < 512) return false;
+  const int bm = d.M > 64 ? 128 : 64;
+  const double work = (double)d.batch * d.M * d.N * d.Kd, padded = (double)((d.M + bm - 1) / bm * bm) * ((d.N + 127) / 128 * 128);
+  return work >= 1.5e9 && padded <= 1.3 * d.M * d.N;
+}
 
 Plan make_plan(const GemmDesc& d, int tile_override) {
   auto tiles = [&](int bm, int bn) {
@@ -905,6 +1120,23 @@ Plan make_plan(const GemmDesc& d, int tile_override) {
         (double)tiles(64, 64) * 64 * 64 < kSmallTileGain * (double)tiles(128, 128) * 128 * 128) {
       pl.bm = 64; pl.bn = 64;
     }
+  }
+  else if (split_pays(d)) {
+    pl.bm = d.M > 64 ? 128 : 64; pl.bn = 128;
+    pl.pieces = true;
+    const int steps = (d.Kd + 31) / 32;
+    const long long nt = tiles(pl.bm, pl.bn);
+    pl.steps_per_split = steps;
+    if (nt < 512) {
+      const long long sp = std::min<long long>((512 + nt - 1) / nt, std::max(1, steps / 6));
+      if (sp > 1) {
+        pl.steps_per_split = (int)((steps + sp - 1) / sp);
+        pl.splits = (steps + pl.steps_per_split - 1) / pl.steps_per_split;
+        pl.ldP = (d.N + 3) / 4 * 4;
+        pl.ws_bytes = (size_t)pl.splits * d.batch * d.M * pl.ldP * 4;
+      }
+    }
+    return pl;
   }
   else if (kk && d.M >= 256 && d.N >= 128 && tiles(256, 128) >= 512) { pl.bm = 256; pl.bn = 128; pl.bku = 4; }
   else if (d.M >= 256 && d.N >= 256 && tiles(256, 256) >= 512) { pl.bm = 256; pl.bn = 256; }
@@ -982,8 +1214,25 @@ int launch_tiled(const GemmParams& p, const Plan& pl, hipStream_t s, int* slots)
   return launch_one<T, TC, 64, 64, 8, AK, BK_>(p, s, slots);
 }
 
+template <int BM, int BN, bool B_KMAJOR>
+int launch_split(const GemmParams& p0, hipStream_t s, int* sumsq_slots) {
+  GemmParams p = p0;
+  p.tilesM = (p.M + BM - 1) / BM;
+  p.tilesN = (p.N + BN - 1) / BN;
+  p.total = p.tilesM * p.tilesN * p.batch * p.splits;
+  p.chunks = (p.total + 7) / 8;
+  split_gemm_kernel<BM, BN, true, B_KMAJOR><<<p.chunks * 8, kThreads, split_tile_lds<BM, BN>(), s>>>(p);
+  const int slots = p.splits > 1 && !p.unreduced ? reduce_splits(p, s) : p.tilesM * p.tilesN;
+  if (sumsq_slots) *sumsq_slots = slots;
+  return 0;
+}
+
 template <typename T, typename TC>
 int launch_layout(const GemmDesc& d, const GemmParams& p, const Plan& pl, hipStream_t s, int* slots) {
+  if (pl.pieces) {
+    if (pl.bm == 128) return d.b_kmajor ? launch_split<128, 128, true>(p, s, slots) : launch_split<128, 128, false>(p, s, slots);
+    return d.b_kmajor ? launch_split<64, 128, true>(p, s, slots) : launch_split<64, 128, false>(p, s, slots);
+  }
   if (d.bf16_math) {
     const bool big = pl.bm == 128;
     if (d.unfold == 1) {
@@ -1191,6 +1440,9 @@ int launch_dense_gradients(const DenseLayer* layers, int n, const DenseLayer* he
     lds = std::max<size_t>({lds, bf16_math ? (size_t)2 * 8 * (2 * (tile + 2)) * 8 : (size_t)2 * 8 * (2 * (tile + 1)) * 16,
                             (size_t)64 * (tile + 4) * 4});
   }
+  d.split = !bf16_math && tile == 128;
+  for (int i = 0; i < n; ++i) d.split = d.split && !alone[i] && d.it[i].chain >= (B + 31) / 32;
+  if (d.split) lds = std::max(lds, split_tile_lds<128, 128>());
   d.head_first = (int)blocks;
   if (head) {
     d.head = item(*head);

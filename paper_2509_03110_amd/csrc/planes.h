@@ -21,40 +21,38 @@ __device__ __forceinline__ void split_planes(float x, unsigned short (&o)[NP]) {
 }
 
 // The pieces of N values, two to a word, in 6 operations a value instead of the 19 of one at a time: two conversions share an
-// instruction, and numbers that the rounding would make infinite, or that are, are looked for once for all of them
-// (NaN needs no care: its pieces are NaN and so is what they are multiplied into).
+// instruction.  Numbers that the rounding would make infinite, or that are, come out wrong: the caller looks for them once for
+// many values (past_rounding of their largest; NaN needs no care: its pieces are NaN and so is what they are multiplied
+// into), and then takes split_words_any.
 template <int NP, int N>
 __device__ __forceinline__ void split_words(const float (&x)[N], unsigned (&o)[NP][N / 2]) {
   typedef float f32x2 __attribute__((ext_vector_type(2)));
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  const auto pack = [](float a, float b) {
-    return __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
-  };
 #pragma unroll
   for (int w = 0; w < N / 2; ++w) {
     float a = x[2 * w], b = x[2 * w + 1];
 #pragma unroll
     for (int q = 0; q < NP; ++q) {
-      o[q][w] = pack(a, b);
+      o[q][w] = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
       a -= __builtin_bit_cast(float, o[q][w] << 16);
       b -= __builtin_bit_cast(float, o[q][w] & 0xFFFF0000u);
     }
   }
-  if constexpr (NP == 3) {
-    float most = 0.f;
+}
+template <int NP, int N>
+__device__ __forceinline__ void split_words_any(const float (&x)[N], unsigned (&o)[NP][N / 2]) {
 #pragma unroll
-    for (int e = 0; e < N; ++e) most = __builtin_fmaxf(most, __builtin_fabsf(x[e]));
-    if (__builtin_expect(most >= __builtin_bit_cast(float, 0x7F7F8000u), 0)) {
+  for (int w = 0; w < N / 2; ++w) {
+    unsigned short lo[NP], hi[NP];
+    split_planes<NP>(x[2 * w], lo);
+    split_planes<NP>(x[2 * w + 1], hi);
 #pragma unroll
-      for (int w = 0; w < N / 2; ++w) {
-        unsigned short lo[NP], hi[NP];
-        split_planes<NP>(x[2 * w], lo);
-        split_planes<NP>(x[2 * w + 1], hi);
-#pragma unroll
-        for (int q = 0; q < NP; ++q) o[q][w] = (unsigned)lo[q] | (unsigned)hi[q] << 16;
-      }
-    }
+    for (int q = 0; q < NP; ++q) o[q][w] = (unsigned)lo[q] | (unsigned)hi[q] << 16;
   }
+}
+__device__ __forceinline__ float largest_of(float most, float x) { return __builtin_fmaxf(most, __builtin_fabsf(x)); }
+__device__ __forceinline__ bool past_rounding(float most) {
+  return __builtin_expect(most >= __builtin_bit_cast(float, 0x7F7F8000u), 0);
 }
 
 // Results with three planes from their two sums, the products of the leading pieces and the other

@@ -261,6 +261,22 @@ int launch_bias_grads_blocked(const DenseLayer* layers, int n, int K, int B, flo
 // its operands are ignored).  Returns the sum-of-squares slots written per replica.
 int launch_splitk_reduce(const GemmDesc& d, const float* partial, int splits, int64_t split_stride, int ldP, hipStream_t s);
 
+// The same for several products at once: partial sums of weight gradients that nothing waits for before the pass's end
+// (EPI_PLAIN; each in workspace of its own) are listed and added up in one launch.
+struct ReduceList {
+  static constexpr int kMax = 40;
+  struct Job {
+    const float* partial; int64_t split_stride;
+    float* C; int64_t strideC;
+    int M, N, ldC, ldP, splits;
+    int first, slot;          // first of its workgroups; of its sum-of-squares slots
+  };
+  Job job[kMax];
+  int n = 0, blocks = 0;
+  double* sumsq = nullptr; int64_t sumsq_stride = 0;    // slots of replica k at sumsq + k sumsq_stride (null: none wanted)
+};
+int launch_reduce_list(const ReduceList& list, int K, hipStream_t s);
+
 // ---- convolution products on plane tensors (kernels_conv_gemm.hip) ------------------------
 // A plane tensor holds every fp32 value as np bfloat16 values, `plane` elements apart: np = 1 the
 // rounded value, np = 3 an exact split.
@@ -300,6 +316,8 @@ struct ConvGemmDesc {
   // them (a contraction cut over workgroups cannot; `made` says).  1: statistics, as launch_bn_stats leaves them in its scratch;
   // 2: as launch_bn_backward_partials does, the results being dY, with Z and its statistics.
   int sums = 0;
+  // If set (weight gradients): partial sums are listed there instead of added up, the sum-of-squares slots from list_slot on.
+  ReduceList* list = nullptr; int list_slot = 0;
   float* sum_part = nullptr; const float* sum_z = nullptr; const float* sum_stats = nullptr;
 };
 // Chunks of `rows` rows each (the last one fewer), or none (chunks 0).

@@ -1869,7 +1869,13 @@ int launch_conv_gemm(const ConvGemmDesc& d, hipStream_t s, int* sumsq_slots, Chu
   int slots = pl.patch ? run_patch(p, pl.patch, d.np, s)
               : d.wgrad ? run_weight_grad(p, pl.tile, d.np, s)
               : scalar_tap ? run_forward<kForward>(p, pl.tile, d.np, s) : run_forward<kForwardAnyC>(p, pl.tile, d.np, s);
-  if (p.ksplit > 1) {
+  if (p.ksplit > 1 && d.list && d.list->n < ReduceList::kMax && d.N % 4 == 0 && p.ldP % 4 == 0) {
+    ReduceList& list = *d.list;
+    const int blocks = (int)(((long long)d.M * (p.ldP / 4) + kThreads - 1) / kThreads);
+    list.job[list.n++] = ReduceList::Job{p.partial, p.stridePartial, d.C, d.strideC, d.M, d.N, d.ldC, p.ldP, p.ksplit, list.blocks, d.list_slot};
+    list.blocks += blocks;
+    slots = blocks;
+  } else if (p.ksplit > 1) {
     GemmDesc r{};
     r.C = d.C; r.strideC = d.strideC; r.ldC = d.ldC; r.M = d.M; r.N = d.N; r.batch = d.batch;
     r.epilogue = d.epilogue; r.bias = d.bias; r.strideBias = d.strideBias;

@@ -1066,6 +1066,46 @@ __global__ __launch_bounds__(kThreads * LANES) void splitk_reduce_kernel(GemmPar
   }
 }
 
+// The partial sums of several products (ReduceList).  A launch for each is 5 to 8 us of ramp and one round of loads, whatever
+// it adds up: seven layers of 16 to 64 channels, 4 replicas of 128 images of 32 x 32: 43 us apart, 15 together.
+// Workgroups as those of splitk_reduce_kernel<4>, dealt out job by job.
+__global__ __launch_bounds__(kThreads * 4) void reduce_list_kernel(ReduceList list) {
+  __shared__ f32x4 part[3][kThreads];
+  __shared__ double wsum[kThreads / 64];
+  int at = 0;
+  while (at + 1 < list.n && (int)blockIdx.x >= list.job[at + 1].first) ++at;
+  const ReduceList::Job& job = list.job[at];
+  const int block = blockIdx.x - job.first, bat = blockIdx.y;
+  const int n4 = job.ldP / 4, word = threadIdx.x % kThreads, q = threadIdx.x / kThreads;
+  const long long idx = (long long)block * kThreads + word;
+  const int m = (int)(idx / n4), c = (int)(idx - (long long)m * n4) * 4;
+  const bool live = m < job.M && c < job.N;          // N and the pitches are multiples of 4
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if (live)
+#pragma unroll 4
+    for (int s = q; s < job.splits; s += 4)
+      v += *reinterpret_cast<const f32x4*>(job.partial + s * job.split_stride + ((long long)bat * job.M + m) * job.ldP + c);
+  if (q > 0) part[q - 1][word] = v;
+  __syncthreads();
+  if (q == 0) {
+    double t = 0.0;
+    if (live) {
+      v = (v + part[0][word]) + (part[1][word] + part[2][word]);
+      *reinterpret_cast<f32x4*>(job.C + bat * job.strideC + (long long)m * job.ldC + c) = v;
+      float ssq = 0.f;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) ssq += v[r] * v[r];
+      t = (double)ssq;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+    if ((word & 63) == 0) wsum[word >> 6] = t;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && list.sumsq != nullptr)
+    list.sumsq[bat * list.sumsq_stride + job.slot + block] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+}
+
 // Tile shape and split of the contraction for one GEMM, chosen from measurements on MI355X at
 // the workload shapes: the forward GEMM (both operands k-major, few staging registers) runs
 // best as 256x128 tiles with two workgroups per compute unit; the GEMMs with transposing loads
@@ -1285,6 +1325,12 @@ int launch_splitk_reduce(const GemmDesc& d, const float* partial, int splits, in
   p.partial = const_cast<float*>(partial); p.strideSplit = split_stride; p.ldP = ldP; p.splits = splits;
   p.sumsq = d.sumsq; p.strideSumsq = d.sumsq_stride;
   return reduce_splits(p, s);
+}
+
+int launch_reduce_list(const ReduceList& list, int K, hipStream_t s) {
+  if (list.n < 0 || list.n > ReduceList::kMax) return -1;
+  if (list.n > 0) reduce_list_kernel<<<dim3((unsigned)list.blocks, (unsigned)K), kThreads * 4, 0, s>>>(list);
+  return 0;
 }
 
 size_t gemm_splitk_bytes(const GemmDesc& d) { return make_plan(d, 0).ws_bytes; }

@@ -174,6 +174,8 @@ struct ConvLayer {
   // filters as the plane products read them, elements into a plane of lo.wp: forward and dX, the
   // same of the projection
   int64_t wf, wx, pwf, pwx;
+  // partial sums of its weight gradient and of its projection's, which wait for the end of the pass
+  size_t wpart, wpart_bytes, pwpart, pwpart_bytes;
   int in_H, in_W;      // that image
 };
 
@@ -702,22 +704,27 @@ void build_layout(const lsam_config& c, Layout& lo) {
         q.np = lo.np; q.wgrad = wgrad; q.batch = lo.K;
         q.image = PlaneImage{nullptr, 0, 0, C, cv->H, cv->W, cv->H * stride, cv->W * stride, stride, side, side, 0, 0};
         q.M = M; q.N = N; q.Kd = Kd;
-        need = std::max(need, conv_gemm_splitk_bytes(q));
+        const size_t bytes = conv_gemm_splitk_bytes(q);
+        if (!wgrad) need = std::max(need, bytes);
+        return bytes;
       };
+      ConvLayer& own = lo.conv[l];
       if (cv->direct_in) {
         planes(0, cv->Cin, cv->stride, 3, rows, ly.out, ly.in);
-        planes(1, cv->Cin, cv->stride, 3, ly.out, ly.in, rows);
+        own.wpart_bytes = planes(1, cv->Cin, cv->stride, 3, ly.out, ly.in, rows);
       } else if (!cv->first) {
         planes(0, cv->ldc, 1, 1, rows, ly.out, cv->ldc);
-        planes(1, cv->ldc, 1, 1, ly.out, cv->ldc, rows);
+        own.wpart_bytes = planes(1, cv->ldc, 1, 1, ly.out, cv->ldc, rows);
       }
+      if (own.wpart_bytes) own.wpart = take(cur, own.wpart_bytes);
       if (cv->direct_dx && cv->stride == 1) planes(0, cv->Cout, 1, 3, rows, cv->Cin, 9 * cv->Cout);
       else if (cv->direct_dx) {}          // one launch per class of pixels, never split
       else if (l > 0) planes(0, cv->Cout, 1, 1, rows, cv->ldc, cv->Cout);
       if (ly.proj) {           // the projection's three products
         planes(0, ly.proj_in, cv->skip_step, 1, rows, ly.out, ly.proj_in);
         planes(0, ly.out, 1, 1, rows, ly.proj_in, ly.out);
-        planes(1, ly.proj_in, cv->skip_step, 1, ly.out, ly.proj_in, rows);
+        own.pwpart_bytes = planes(1, ly.proj_in, cv->skip_step, 1, ly.out, ly.proj_in, rows);
+        if (own.pwpart_bytes) own.pwpart = take(cur, own.pwpart_bytes);
       }
     }
     lo.splitk_bytes = need;
@@ -1093,6 +1100,8 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
                                 lo.ld[lo.n_conv], s) != 0)
       return fail(LSAM_EINVAL, "global average pooling (backward) rejected");
   }
+  ReduceList list;            // weight gradients whose partial sums wait for the end of the pass
+  list.sumsq = ssq; list.sumsq_stride = lo.nblk;
   ChunkSums have;             // sums of the layer's gradient and normalised values, left by the product that wrote the gradient
   for (int l = lo.n_conv - 1; l >= 0; --l) {
     const ConvLayer& cv = lo.conv[l];
@@ -1190,6 +1199,8 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
           ConvGemmDesc d = plane_desc(c, projection_image(c, lo.conv[l - 1], cv), 1, 0, cv.Cout, ly.proj_in, (int)cv.rows);
           d.C = g + ly.pw_off; d.strideC = lo.d_pad; d.ldC = ly.proj_in;
           if (ssq) { d.sumsq = ssq + *slots; d.sumsq_stride = lo.nblk; }
+          d.splitk_ws = c->at<float>(cv.pwpart); d.splitk_bytes = cv.pwpart_bytes;
+          d.list = &list; d.list_slot = *slots;
           int used = 0;
           if (launch_conv_gemm(d, s, &used) != 0) return fail(LSAM_EINVAL, "projection of convolution %d: dW rejected", l);
           if (ssq) *slots += used;
@@ -1251,6 +1262,8 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
                                     : plane_desc(c, stored_image(c, cv), 1, 0, cv.Cout, ly.ldw, (int)cv.rows);
       d.C = g + ly.w_off; d.strideC = lo.d_pad; d.ldC = ly.ldw;
       if (ssq) { d.sumsq = ssq + *slots; d.sumsq_stride = lo.nblk; }
+      d.splitk_ws = c->at<float>(cv.wpart); d.splitk_bytes = cv.wpart_bytes;
+      d.list = &list; d.list_slot = *slots;
       int used = 0;
       if (launch_conv_gemm(d, s, &used) != 0) return fail(LSAM_EINVAL, "dW product of convolution %d rejected", l);
       if (ssq) *slots += used;
@@ -1386,6 +1399,10 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
                                    top.proj ? top.skip_C : top.Cout, s) != 0)
         return fail(LSAM_EINVAL, "shortcut of the block closed by convolution %d rejected", l + 1);
     }
+  }
+  {
+    LaunchTimer t(c, KC_GEMM_DW);
+    if (launch_reduce_list(list, lo.K, s) != 0) return fail(LSAM_EINVAL, "sums of the weight gradients rejected");
   }
   return LSAM_OK;
 }

@@ -554,10 +554,12 @@ void build_layout(const lsam_config& c, Layout& lo) {
       // fp32-storage GEMM knows stride 1 and parts of taps only
       auto fits = [&](int C) { return C % (cv.fast ? 8 : 32) == 0; };
       cv.direct_in = small && fits(cv.Cin) && (cv.fast || cv.stride == 1);
-      // (stride 2: with three planes the classes lose against the product with a stored gradient where
-      // their columns fill the 64-wide tiles badly: 160 channels, a step 0.35 ms slower of 27)
+      // (stride 2: since the product in classes leaves the sums below it and the layer below no floats, it wins against
+      // one with a stored gradient and its fold unless three planes meet many columns that fill the 64-wide
+      // tiles badly.  Steps of one such layer between two others, 4 replicas of 64 images of 32 x 32, stored / classes: 40
+      // channels 1242 / 1163 us, 72 2462 / 2433, 80 2686 / 2601, 104 3968 / 3868, 160 6674 / 6630; 136 6221 / 6287, 152 7031 / 7120)
       cv.direct_dx = small && l > 0 && fits(cv.Cout) &&
-                     (cv.stride == 1 || (cv.fast && (lo.np == 1 || cv.Cin <= 32 || (cv.Cin + 63) / 64 * 64 * 8 <= cv.Cin * 9)));
+                     (cv.stride == 1 || (cv.fast && (lo.np == 1 || cv.Cin <= 128 || (cv.Cin + 63) / 64 * 64 * 5 <= cv.Cin * 6)));
       cv.first = l == 0 && cv.stride == 1 && first_conv_fits(cv.Cin, cv.Cout, cv.rows, lo.K, lo.bf16_math);
     }
     for (int l = 0; l < lo.n_conv; ++l) {

@@ -19,6 +19,10 @@ NETS = {
                                proj=0b00100, preact=1),
     "48 and 80, patches": dict(dims=(3, 48, 80, 48, 10), side=(16, 16), batch=40),
     "152, few pixels": dict(dims=(8, 152, 88, 10), side=(4, 4), batch=131),
+    # stride 2, three planes: dX in classes with a column tile of 8 and one of 64, and (136) through a stored gradient
+    "72, stride in classes": dict(dims=(3, 72, 104, 10), side=(32, 32), batch=33, stride=0b010),
+    "128 and 160, strides in classes": dict(dims=(8, 128, 160, 64, 10), side=(16, 32), batch=35, stride=0b0110),
+    "136, stride through a stored gradient": dict(dims=(8, 136, 64, 10), side=(16, 16), batch=90, stride=0b010),
     "88, pools": dict(dims=(3, 88, 56, 10), side=(16, 16), batch=33, pool=0b011),
 }
 

@@ -98,8 +98,7 @@ NETS = {
     "8 and 16 channels": dict(dims=(5, 8, 16, 16, 10), side=(32, 32), batch=45),
     # a channel count that needs a stored unfolded image (taken with one plane only)
     "24 channels": dict(dims=(3, 24, 64, 24, 10), side=(16, 32), batch=22),
-    # stride 2 forward and dW by address, dX in classes of pixels or (three planes, 96 channels) through
-    # a stored gradient; both kinds of shortcut
+    # stride 2 forward and dW by address, dX in classes of pixels; both kinds of shortcut
     "stride and projection": dict(dims=(3, 32, 64, 64, 10), side=(32, 32), batch=33, stride=0b010, skip=0b100, proj=0b100),
     "stride, columns that leave a tile half empty": dict(dims=(3, 96, 64, 32, 10), side=(16, 16), batch=90, stride=0b010),
     "parameter-free shortcut": dict(dims=(3, 64, 64, 64, 10), side=(16, 16), batch=17, skip=0b100),

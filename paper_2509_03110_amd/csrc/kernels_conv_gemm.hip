@@ -1047,30 +1047,18 @@ __global__ __launch_bounds__(kThreads, 2) void conv_patch_kernel(Params p) {
 // TN = 1 serves layers of up to 32 columns (half of the filter rows it requests do not exist and
 // cost no traffic): 16 channels at 32 x 32, 4 replicas of 128: 38 us,
 // 56 by the ring (which fetches every pixel nine times).
+// A last column of tiles with 32 columns or fewer left takes the same steps on half a tile: 160 columns are 2.5 tiles of
+// work and not 3.  A kernel of its own (NARROW_LAST): with both bodies in one the others were 0.3 % slower.  Steps of two layers, 4
+// replicas of 64 images, whole / half tiles: 32 x 32, 80 channels 1749 / 1730 us, 96 1980 / 1921, 160 4208 / 4127; 20 x 20, 160
+// 2327 / 2288.  Between one and two rounds of the 512 workgroups that fit the chip whole tiles stay: 160 channels at
+// 16 x 16, 768 workgroups, 1203 / 1232.
 template <int TM, int TN, int NCHUNK>
-__global__ __launch_bounds__(kThreads, 2) void conv_split_patch_kernel(Params p) {
-  constexpr int NP = 3, BM = TM * 128, BN = TN * 32, S = 9;
+__device__ __forceinline__ void split_patch_tile(const Params& p, lds_byte* a0, lds_byte* a1, lds_byte* b0, lds_byte* b1,
+                                                 lds_byte* sp, int m0, int n0, int bat, int piece, int t_in, int t_row) {
+#if defined(__HIP_DEVICE_COMPILE__)
+#if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int NP = 3, BN = TN * 32, S = 9;
   constexpr int NLA = (NCHUNK + 3) / 4, NA = NLA * NP, AG = (NA + S - 2) / (S - 1);
-  constexpr int A_BYTES = NP * NCHUNK * 1024, B_BYTES = NP * 2048;
-  constexpr int EPI_PITCH = BN + 4;
-  static_assert(A_BYTES >= 2 * 32 * EPI_PITCH * 4, "room for the epilogue's strips");
-  __shared__ __attribute__((aligned(1024))) unsigned char pa0[A_BYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char pa1[A_BYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char pb0[B_BYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char pb1[B_BYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char spill[1024];   // surplus loads end here
-
-  const int logical = (blockIdx.x % 8) * p.chunks + blockIdx.x / 8;
-  if (logical >= p.total) return;
-  // (quotients come from the vector unit: back to scalars, the addresses below depend on them)
-  const int per_rep = p.tilesM * p.tilesN;
-  const int rest = __builtin_amdgcn_readfirstlane(logical / per_rep);
-  const int t_in = logical - rest * per_rep;
-  const int bat = __builtin_amdgcn_readfirstlane(rest / p.ksplit);
-  const int piece = rest - bat * p.ksplit;
-  const int t_row = __builtin_amdgcn_readfirstlane(t_in / p.tilesN);
-  const int m0 = t_row * BM, n0 = (t_in - t_row * p.tilesN) * BN;   // neighbours read the same patch
-
   const unsigned short* Ab = p.A + (long long)bat * p.strideA;
   const unsigned short* Bb = p.B + (long long)bat * p.strideB;
   const Geometry& g = p.g;
@@ -1110,12 +1098,6 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_patch_kernel(Params p)
     const int u = (lane & 1) ^ ((row >> 3) & 1);
     boff = row < BN && n0 + row < p.N ? ((unsigned)(n0 + row) * p.ldB + u * 8) * 2u : kOob;
   }
-  lds_byte* a0 = (lds_byte*)pa0;
-  lds_byte* a1 = (lds_byte*)pa1;
-  lds_byte* b0 = (lds_byte*)pb0;
-  lds_byte* b1 = (lds_byte*)pb1;
-  lds_byte* sp = (lds_byte*)spill;
-
   int slot[TM];                                          // of this lane's pixel in each 32-row strip
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
@@ -1236,8 +1218,42 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_patch_kernel(Params p)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
       join_sums(acc[i][j], low[i][j]);
-  store_tile<TM, TN, 4>(p, acc, reinterpret_cast<float*>(pa0), reinterpret_cast<float*>(pa1), m0, n0, bat, piece, t_in, t_row,
-                        p.tilesM);
+  store_tile<TM, TN, 4>(p, acc, (float*)a0, (float*)a1, m0, n0, bat, piece, t_in, t_row, p.tilesM);
+#endif
+#endif
+}
+
+// NARROW_LAST: see split_patch_tile.
+template <int TM, int TN, int NCHUNK, bool NARROW_LAST>
+__global__ __launch_bounds__(kThreads, 2) void conv_split_patch_kernel(Params p) {
+  constexpr int NP = 3, BM = TM * 128, BN = TN * 32;
+  constexpr int A_BYTES = NP * NCHUNK * 1024, B_BYTES = NP * 2048;
+  constexpr int EPI_PITCH = BN + 4;
+  static_assert(A_BYTES >= 2 * 32 * EPI_PITCH * 4, "room for the epilogue's strips");
+  __shared__ __attribute__((aligned(1024))) unsigned char pa0[A_BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char pa1[A_BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char pb0[B_BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char pb1[B_BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char spill[1024];   // surplus loads end here
+
+  const int logical = (blockIdx.x % 8) * p.chunks + blockIdx.x / 8;
+  if (logical >= p.total) return;
+  // (quotients come from the vector unit: back to scalars, the addresses below depend on them)
+  const int per_rep = p.tilesM * p.tilesN;
+  const int rest = __builtin_amdgcn_readfirstlane(logical / per_rep);
+  const int t_in = logical - rest * per_rep;
+  const int bat = __builtin_amdgcn_readfirstlane(rest / p.ksplit);
+  const int piece = rest - bat * p.ksplit;
+  const int t_row = __builtin_amdgcn_readfirstlane(t_in / p.tilesN);
+  const int m0 = t_row * BM, n0 = (t_in - t_row * p.tilesN) * BN;   // neighbours read the same patch
+
+  lds_byte* a0 = (lds_byte*)pa0;
+  lds_byte* a1 = (lds_byte*)pa1;
+  lds_byte* b0 = (lds_byte*)pb0;
+  lds_byte* b1 = (lds_byte*)pb1;
+  lds_byte* sp = (lds_byte*)spill;
+  if (NARROW_LAST && p.N - n0 <= 32) split_patch_tile<TM, 1, NCHUNK>(p, a0, a1, b0, b1, sp, m0, n0, bat, piece, t_in, t_row);
+  else split_patch_tile<TM, TN, NCHUNK>(p, a0, a1, b0, b1, sp, m0, n0, bat, piece, t_in, t_row);
 }
 
 // ---- weight gradient of 3x3 layers with stride 1, image patches in LDS ------------------
@@ -1537,10 +1553,12 @@ LSAM_CONV_KERNEL(3, kWeightGrad, 32, 128, 1, 2, 2)
 
 template __global__ void conv_patch_kernel<22>(Params);
 template __global__ void conv_patch_kernel<26>(Params);
-template __global__ void conv_split_patch_kernel<2, 2, 11>(Params);
-template __global__ void conv_split_patch_kernel<1, 2, 10>(Params);
-template __global__ void conv_split_patch_kernel<2, 1, 11>(Params);
-template __global__ void conv_split_patch_kernel<1, 1, 10>(Params);
+template __global__ void conv_split_patch_kernel<2, 2, 11, false>(Params);
+template __global__ void conv_split_patch_kernel<2, 2, 11, true>(Params);
+template __global__ void conv_split_patch_kernel<1, 2, 10, false>(Params);
+template __global__ void conv_split_patch_kernel<1, 2, 10, true>(Params);
+template __global__ void conv_split_patch_kernel<2, 1, 11, false>(Params);
+template __global__ void conv_split_patch_kernel<1, 1, 10, false>(Params);
 template __global__ void conv_wgrad_kernel<3, 2, 64, 9>(Params);
 template __global__ void conv_wgrad_kernel<3, 1, 64, 9>(Params);
 template __global__ void conv_wgrad_kernel<1, 2, 64, 9>(Params);
@@ -1693,12 +1711,15 @@ int run_patch(Params& p, int kind, int np, hipStream_t s) {
   const int slots = tiled(p, kind == kSplitPatch128 || kind == kSplitNarrow128 ? 128 : 256,
                           kind == kSplitNarrow256 || kind == kSplitNarrow128 ? 32 : 64);
   const unsigned grid = (unsigned)p.chunks * 8;
+  const bool narrow_last = (p.N - 1) % 64 < 32 && (p.total <= 512 || p.total >= 1024);
   if (kind == kPatch22) conv_patch_kernel<22><<<grid, kThreads, 0, s>>>(p);
   else if (kind == kPatch26) conv_patch_kernel<26><<<grid, kThreads, 0, s>>>(p);
-  else if (kind == kSplitPatch256) conv_split_patch_kernel<2, 2, 11><<<grid, kThreads, 0, s>>>(p);
-  else if (kind == kSplitPatch128) conv_split_patch_kernel<1, 2, 10><<<grid, kThreads, 0, s>>>(p);
-  else if (kind == kSplitNarrow256) conv_split_patch_kernel<2, 1, 11><<<grid, kThreads, 0, s>>>(p);
-  else conv_split_patch_kernel<1, 1, 10><<<grid, kThreads, 0, s>>>(p);
+  else if (kind == kSplitPatch256 && narrow_last) conv_split_patch_kernel<2, 2, 11, true><<<grid, kThreads, 0, s>>>(p);
+  else if (kind == kSplitPatch256) conv_split_patch_kernel<2, 2, 11, false><<<grid, kThreads, 0, s>>>(p);
+  else if (kind == kSplitPatch128 && narrow_last) conv_split_patch_kernel<1, 2, 10, true><<<grid, kThreads, 0, s>>>(p);
+  else if (kind == kSplitPatch128) conv_split_patch_kernel<1, 2, 10, false><<<grid, kThreads, 0, s>>>(p);
+  else if (kind == kSplitNarrow256) conv_split_patch_kernel<2, 1, 11, false><<<grid, kThreads, 0, s>>>(p);
+  else conv_split_patch_kernel<1, 1, 10, false><<<grid, kThreads, 0, s>>>(p);
   return slots;
 }
 

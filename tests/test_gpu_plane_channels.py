@@ -23,6 +23,10 @@ NETS = {
     "72, stride in classes": dict(dims=(3, 72, 104, 10), side=(32, 32), batch=33, stride=0b010),
     "128 and 160, strides in classes": dict(dims=(8, 128, 160, 64, 10), side=(16, 32), batch=35, stride=0b0110),
     "136, stride through a stored gradient": dict(dims=(8, 136, 64, 10), side=(16, 16), batch=90, stride=0b010),
+    # last columns on half tiles of the three-plane patches: of 256 and (64 wide) of 128 pixels; 160 between one and two rounds
+    "96 and 160, last columns on half tiles": dict(dims=(3, 96, 160, 80, 10), side=(16, 16), batch=23),
+    "80 and 96, 64 wide": dict(dims=(3, 32, 80, 96, 10), side=(8, 64), batch=9),
+    "160, whole tiles": dict(dims=(3, 32, 160, 10), side=(16, 16), batch=100),
     "88, pools": dict(dims=(3, 88, 56, 10), side=(16, 16), batch=33, pool=0b011),
 }
 

@@ -33,7 +33,7 @@ NETS = {
     "average behind a shortcut": dict(dims=(3, 32, 32, 32, 10), side=(16, 20), batch=24, skip=0b100),
     "identity shortcut": dict(dims=(3, 32, 32, 32, 32, 32, 10), side=(16, 32), batch=24, skip=0b10100),
     "stride and projection": dict(dims=(3, 24, 48, 48, 48, 10), side=(32, 32), batch=16, stride=0b0010, skip=0b0100, proj=0b0100),
-    "stored input gradient": dict(dims=(3, 96, 64, 32, 10), side=(16, 16), batch=90, stride=0b010),
+    "stored input gradient": dict(dims=(3, 136, 64, 32, 10), side=(16, 16), batch=90, stride=0b010),
     "pre-activation": dict(dims=(3, 32, 64, 64, 64, 64, 10), side=(16, 32), batch=33, stride=0b00010, skip=0b10100, proj=0b00100,
                            preact=1),
 }

@@ -1048,7 +1048,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_patch_kernel(Params p) {
 // cost no traffic): 16 channels at 32 x 32, 4 replicas of 128: 38 us,
 // 56 by the ring (which fetches every pixel nine times).
 // A last column of tiles with 32 columns or fewer left takes the same steps on half a tile: 160 columns are 2.5 tiles of
-// work and not 3.  A kernel of its own (NARROW_LAST): with both bodies in one the others were 0.3 % slower.  Steps of two layers, 4
+// work and not 3.  A kernel of its own: with both bodies in one the others were 0.3 % slower.  Steps of two layers, 4
 // replicas of 64 images, whole / half tiles: 32 x 32, 80 channels 1749 / 1730 us, 96 1980 / 1921, 160 4208 / 4127; 20 x 20, 160
 // 2327 / 2288.  Between one and two rounds of the 512 workgroups that fit the chip whole tiles stay: 160 channels at
 // 16 x 16, 768 workgroups, 1203 / 1232.
@@ -1223,9 +1223,9 @@ __device__ __forceinline__ void split_patch_tile(const Params& p, lds_byte* a0, 
 #endif
 }
 
-// NARROW_LAST: see split_patch_tile.
 template <int TM, int TN, int NCHUNK, bool NARROW_LAST>
-__global__ __launch_bounds__(kThreads, 2) void conv_split_patch_kernel(Params p) {
+__device__ __forceinline__ void split_patch_workgroup(const Params& p) {
+#if defined(__HIP_DEVICE_COMPILE__)
   constexpr int NP = 3, BM = TM * 128, BN = TN * 32;
   constexpr int A_BYTES = NP * NCHUNK * 1024, B_BYTES = NP * 2048;
   constexpr int EPI_PITCH = BN + 4;
@@ -1254,6 +1254,15 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_patch_kernel(Params p)
   lds_byte* sp = (lds_byte*)spill;
   if (NARROW_LAST && p.N - n0 <= 32) split_patch_tile<TM, 1, NCHUNK>(p, a0, a1, b0, b1, sp, m0, n0, bat, piece, t_in, t_row);
   else split_patch_tile<TM, TN, NCHUNK>(p, a0, a1, b0, b1, sp, m0, n0, bat, piece, t_in, t_row);
+#endif
+}
+template <int TM, int TN, int NCHUNK>
+__global__ __launch_bounds__(kThreads, 2) void conv_split_patch_kernel(Params p) {
+  split_patch_workgroup<TM, TN, NCHUNK, false>(p);
+}
+template <int TM, int TN, int NCHUNK>
+__global__ __launch_bounds__(kThreads, 2) void conv_split_patch_narrow_last_kernel(Params p) {
+  split_patch_workgroup<TM, TN, NCHUNK, true>(p);
 }
 
 // ---- weight gradient of 3x3 layers with stride 1, image patches in LDS ------------------
@@ -1553,12 +1562,12 @@ LSAM_CONV_KERNEL(3, kWeightGrad, 32, 128, 1, 2, 2)
 
 template __global__ void conv_patch_kernel<22>(Params);
 template __global__ void conv_patch_kernel<26>(Params);
-template __global__ void conv_split_patch_kernel<2, 2, 11, false>(Params);
-template __global__ void conv_split_patch_kernel<2, 2, 11, true>(Params);
-template __global__ void conv_split_patch_kernel<1, 2, 10, false>(Params);
-template __global__ void conv_split_patch_kernel<1, 2, 10, true>(Params);
-template __global__ void conv_split_patch_kernel<2, 1, 11, false>(Params);
-template __global__ void conv_split_patch_kernel<1, 1, 10, false>(Params);
+template __global__ void conv_split_patch_kernel<2, 2, 11>(Params);
+template __global__ void conv_split_patch_narrow_last_kernel<2, 2, 11>(Params);
+template __global__ void conv_split_patch_kernel<1, 2, 10>(Params);
+template __global__ void conv_split_patch_narrow_last_kernel<1, 2, 10>(Params);
+template __global__ void conv_split_patch_kernel<2, 1, 11>(Params);
+template __global__ void conv_split_patch_kernel<1, 1, 10>(Params);
 template __global__ void conv_wgrad_kernel<3, 2, 64, 9>(Params);
 template __global__ void conv_wgrad_kernel<3, 1, 64, 9>(Params);
 template __global__ void conv_wgrad_kernel<1, 2, 64, 9>(Params);
@@ -1714,12 +1723,12 @@ int run_patch(Params& p, int kind, int np, hipStream_t s) {
   const bool narrow_last = (p.N - 1) % 64 < 32 && (p.total <= 512 || p.total >= 1024);
   if (kind == kPatch22) conv_patch_kernel<22><<<grid, kThreads, 0, s>>>(p);
   else if (kind == kPatch26) conv_patch_kernel<26><<<grid, kThreads, 0, s>>>(p);
-  else if (kind == kSplitPatch256 && narrow_last) conv_split_patch_kernel<2, 2, 11, true><<<grid, kThreads, 0, s>>>(p);
-  else if (kind == kSplitPatch256) conv_split_patch_kernel<2, 2, 11, false><<<grid, kThreads, 0, s>>>(p);
-  else if (kind == kSplitPatch128 && narrow_last) conv_split_patch_kernel<1, 2, 10, true><<<grid, kThreads, 0, s>>>(p);
-  else if (kind == kSplitPatch128) conv_split_patch_kernel<1, 2, 10, false><<<grid, kThreads, 0, s>>>(p);
-  else if (kind == kSplitNarrow256) conv_split_patch_kernel<2, 1, 11, false><<<grid, kThreads, 0, s>>>(p);
-  else conv_split_patch_kernel<1, 1, 10, false><<<grid, kThreads, 0, s>>>(p);
+  else if (kind == kSplitPatch256 && narrow_last) conv_split_patch_narrow_last_kernel<2, 2, 11><<<grid, kThreads, 0, s>>>(p);
+  else if (kind == kSplitPatch256) conv_split_patch_kernel<2, 2, 11><<<grid, kThreads, 0, s>>>(p);
+  else if (kind == kSplitPatch128 && narrow_last) conv_split_patch_narrow_last_kernel<1, 2, 10><<<grid, kThreads, 0, s>>>(p);
+  else if (kind == kSplitPatch128) conv_split_patch_kernel<1, 2, 10><<<grid, kThreads, 0, s>>>(p);
+  else if (kind == kSplitNarrow256) conv_split_patch_kernel<2, 1, 11><<<grid, kThreads, 0, s>>>(p);
+  else conv_split_patch_kernel<1, 1, 10><<<grid, kThreads, 0, s>>>(p);
   return slots;
 }
 

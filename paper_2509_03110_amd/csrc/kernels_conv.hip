@@ -627,15 +627,27 @@ __global__ __launch_bounds__(kThreads) void first_conv_wgrad_kernel(const float*
     if (t == 9 * C)
 #pragma unroll
       for (int e = 0; e < 8; ++e) b[e] = p8 + e < rows ? 1.f : 0.f;
-    // (pixels past the last one lie past the end of the buffer)
+    // A scalar offset may be left out of the buffer's range check, or be more than the whole buffer: only where all sixteen
+    // pixels exist.  A pixel past the last one must read as zero: its value meets b = 0, but 0 times another replica's NaN is NaN.
+    if (pstart + 16 <= rows) {
 #pragma unroll
-    for (int q = 0; q < OB; ++q) {
-      const unsigned at = col[q] != kOob ? (unsigned)p8 * (unsigned)pixel + col[q] : kOob;
+      for (int q = 0; q < OB; ++q) {
+        const unsigned at = col[q] != kOob ? (unsigned)p8 * (unsigned)pixel + col[q] : kOob;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        a[q][e] = load_float(dz, at, e * pixel);
-        if constexpr (NORM) z[q][e] = load_float(zs, at, e * pixel);
+        for (int e = 0; e < 8; ++e) {
+          a[q][e] = load_float(dz, at, e * pixel);
+          if constexpr (NORM) z[q][e] = load_float(zs, at, e * pixel);
+        }
       }
+    } else {
+#pragma unroll
+      for (int q = 0; q < OB; ++q)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const unsigned at = p8 + e < rows && col[q] != kOob ? (unsigned)(p8 + e) * (unsigned)pixel + col[q] : kOob;
+          a[q][e] = load_float(dz, at);
+          if constexpr (NORM) z[q][e] = load_float(zs, at);
+        }
     }
   };
   request(p0);

@@ -1167,8 +1167,11 @@ Plan make_plan(const GemmDesc& d, int tile_override) {
     const int steps = (d.Kd + 31) / 32;
     const long long nt = tiles(pl.bm, pl.bn);
     pl.steps_per_split = steps;
+    // As many pieces as fit the chip's 512 workgroups at once.  One more leaves a second round nearly empty: twelve 2000-1000-10 with
+    // 250 rows 652 us with three (576 workgroups), 598 with two; eight 768-768-768-10 with 512 664 and 608; one 520-6000-100 with
+    // 700, 282 tiles, 416 with two pieces and 385 whole.
     if (nt < 512) {
-      const long long sp = std::min<long long>((512 + nt - 1) / nt, std::max(1, steps / 6));
+      const long long sp = std::min<long long>(512 / nt, std::max(1, steps / 6));
       if (sp > 1) {
         pl.steps_per_split = (int)((steps + sp - 1) / sp);
         pl.splits = (steps + pl.steps_per_split - 1) / pl.steps_per_split;

@@ -31,6 +31,15 @@ def test_which_products_are_split(dims, B, K, rows):
         assert {n.endswith("true,true>") for n in got} == {True, False}, got
 
 
+@pytest.mark.parametrize("dims,B,K", [((2000, 1000, 10), 250, 12), ((960, 640, 10), 512, 8), ((520, 6000, 100), 700, 1),
+                                      ((3001, 1025, 40), 128, 4), ((1000, 1150, 1000, 17), 60, 24)])
+def test_pieces_fit_the_chip_at_once(dims, B, K):
+    """A product that is cut has at most the 512 workgroups that are resident together."""
+    grids = [(l["grid"][0], l["name"]) for l in launches.record(dict(K=K, dims=dims, batch=B))[0]["launches"]
+             if l["name"].startswith("split_gemm_kernel<")]
+    assert grids and all(n <= 512 for n, _ in grids), grids
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dims,B,K", NETS)
 def test_against_the_oracle(dims, B, K):

@@ -1129,10 +1129,19 @@ constexpr double kSmallTileGain = 0.88;
 // 3000-2000-1000-500 with 200 1854 / 1687.  Below that the fp32 units' 64x64 tiles fill the chip better: two 512-512-512-10
 // with 100 rows 120 / 157, one 1000-600-10 with 64 66 / 73; and where much is padding: three 1000-1500-777-37 with 300
 // 461 / 482.  A piece of a contraction keeps six steps of 32 (with three, eight 512-512-512-512-10 with 512 462 / 501).
+// Where the fp32 units' 64x64 tiles fill the chip without a cut and these tiles do not, what the cut costs wants a contraction of
+// 900 (no pieces / pieces, the weight gradients the same): one 512-3000-512-10 with 1024 406 / 429, twelve 600-1000-10 with 250
+// 319 / 327, eight 768-768-768-10 with 512 604 / 608; sixteen 1100-640-10 with 256 371 / 349, one 1024-3000-10 with 1000 351 / 350,
+// one 2048-3000-10 with 1000 585 / 548.  Tiles of 64 rows: one 4096-8192-1000-10 with 64 653 / 644, two 2048-8192-10 with 52
+// 487 / 473, 24 1000-1150-1000-17 with 60 886 / 865.  A stored unfolded image (inputs no multiple of 8; four of 64 images of
+// 32 x 32, 100 to 128 channels 3152 / 2903, two of 16 x 16, 100 to 256 760 / 679).
 bool split_pays(const GemmDesc& d) {
   if (d.in_bf16 || d.bf16_math || d.unfold || !d.a_kmajor || d.M <= 32 || d.N < 128 || d.Kd < 512) return false;
   const int bm = d.M > 64 ? 128 : 64;
   const double work = (double)d.batch * d.M * d.N * d.Kd, padded = (double)((d.M + bm - 1) / bm * bm) * ((d.N + 127) / 128 * 128);
+  auto tiles = [&](int m, int n) { return (long long)((d.M + m - 1) / m) * ((d.N + n - 1) / n) * d.batch; };
+  const bool large = d.M >= 128 && tiles(128, 128) >= 256;         // the fp32 units would have large tiles, too
+  if (d.Kd < 900 && !large && tiles(64, 64) >= 512 && tiles(bm, 128) < 512) return false;
   return work >= 1.5e9 && padded <= 1.3 * d.M * d.N;
 }
 

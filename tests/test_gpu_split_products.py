@@ -23,6 +23,9 @@ def products(dims, B, K):
 @pytest.mark.parametrize("dims,B,K,rows", [(NETS[0][0], 255, 8, 128), (NETS[2][0], 60, 24, 64),
                                            ((512, 512, 512, 10), 512, 8, 0),        # 1.07e9 multiply-adds
                                            ((1000, 1500, 777, 37), 300, 3, 0),      # a third of the tiles' work for padding
+                                           # contractions below 900 on 192 tiles, which would be cut; on 256 tiles; 1000 on 128
+                                           ((768, 768, 768, 10), 512, 8, 0), ((512, 3000, 10), 1024, 1, 0),
+                                           ((512, 512, 512, 10), 400, 16, 128), ((1000, 1000, 1000, 10), 255, 8, 128),
                                            ((784, 128, 10), 32, 2, 0)])
 def test_which_products_are_split(dims, B, K, rows):
     got = products(dims, B, K)

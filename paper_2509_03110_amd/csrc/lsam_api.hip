@@ -174,7 +174,8 @@ struct ConvLayer {
   // filters as the plane products read them, elements into a plane of lo.wp: forward and dX, the
   // same of the projection
   int64_t wf, wx, pwf, pwx;
-  // partial sums of its weight gradient and of its projection's, which wait for the end of the pass
+  // partial sums of its weight gradient and of its projection's, which wait for the end of the pass (0 bytes: there are none, or
+  // they are added up at once and lie where all others do)
   size_t wpart, wpart_bytes, pwpart, pwpart_bytes;
   int in_H, in_W;      // that image
 };
@@ -718,7 +719,6 @@ void build_layout(const lsam_config& c, Layout& lo) {
         planes(0, cv->ldc, 1, 1, rows, ly.out, cv->ldc);
         own.wpart_bytes = planes(1, cv->ldc, 1, 1, ly.out, cv->ldc, rows);
       }
-      if (own.wpart_bytes) own.wpart = take(cur, own.wpart_bytes);
       if (cv->direct_dx && cv->stride == 1) planes(0, cv->Cout, 1, 3, rows, cv->Cin, 9 * cv->Cout);
       else if (cv->direct_dx) {}          // one launch per class of pixels, never split
       else if (l > 0) planes(0, cv->Cout, 1, 1, rows, cv->ldc, cv->Cout);
@@ -726,8 +726,24 @@ void build_layout(const lsam_config& c, Layout& lo) {
         planes(0, ly.proj_in, cv->skip_step, 1, rows, ly.out, ly.proj_in);
         planes(0, ly.out, 1, 1, rows, ly.proj_in, ly.out);
         own.pwpart_bytes = planes(1, ly.proj_in, cv->skip_step, 1, ly.out, ly.proj_in, rows);
-        if (own.pwpart_bytes) own.pwpart = take(cur, own.pwpart_bytes);
       }
+    }
+    // Of the weight gradients that leave partial sums, as many as the pass's list holds get a place of their own, in the order
+    // of conv_backward.
+    int listed = 0;
+    auto place = [&](size_t& at, size_t& bytes) {
+      if (!bytes) return;
+      if (listed < ReduceList::kMax) {
+        at = take(cur, bytes);
+        ++listed;
+      } else {
+        need = std::max(need, bytes);
+        bytes = 0;
+      }
+    };
+    for (int l = lo.n_conv - 1; l >= 0; --l) {
+      place(lo.conv[l].pwpart, lo.conv[l].pwpart_bytes);
+      place(lo.conv[l].wpart, lo.conv[l].wpart_bytes);
     }
     lo.splitk_bytes = need;
     if (need) lo.splitk = take(cur, need);
@@ -1104,6 +1120,10 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
   }
   ReduceList list;            // weight gradients whose partial sums wait for the end of the pass
   list.sumsq = ssq; list.sumsq_stride = lo.nblk;
+  const auto wait_for_end = [&](ConvGemmDesc& d, size_t at, size_t bytes) {
+    d.splitk_ws = c->at<float>(at); d.splitk_bytes = bytes;
+    d.list = &list; d.list_slot = *slots;
+  };
   ChunkSums have;             // sums of the layer's gradient and normalised values, left by the product that wrote the gradient
   for (int l = lo.n_conv - 1; l >= 0; --l) {
     const ConvLayer& cv = lo.conv[l];
@@ -1201,8 +1221,7 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
           ConvGemmDesc d = plane_desc(c, projection_image(c, lo.conv[l - 1], cv), 1, 0, cv.Cout, ly.proj_in, (int)cv.rows);
           d.C = g + ly.pw_off; d.strideC = lo.d_pad; d.ldC = ly.proj_in;
           if (ssq) { d.sumsq = ssq + *slots; d.sumsq_stride = lo.nblk; }
-          d.splitk_ws = c->at<float>(cv.pwpart); d.splitk_bytes = cv.pwpart_bytes;
-          d.list = &list; d.list_slot = *slots;
+          if (cv.pwpart_bytes) wait_for_end(d, cv.pwpart, cv.pwpart_bytes);
           int used = 0;
           if (launch_conv_gemm(d, s, &used) != 0) return fail(LSAM_EINVAL, "projection of convolution %d: dW rejected", l);
           if (ssq) *slots += used;
@@ -1264,8 +1283,7 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
                                     : plane_desc(c, stored_image(c, cv), 1, 0, cv.Cout, ly.ldw, (int)cv.rows);
       d.C = g + ly.w_off; d.strideC = lo.d_pad; d.ldC = ly.ldw;
       if (ssq) { d.sumsq = ssq + *slots; d.sumsq_stride = lo.nblk; }
-      d.splitk_ws = c->at<float>(cv.wpart); d.splitk_bytes = cv.wpart_bytes;
-      d.list = &list; d.list_slot = *slots;
+      if (cv.wpart_bytes) wait_for_end(d, cv.wpart, cv.wpart_bytes);
       int used = 0;
       if (launch_conv_gemm(d, s, &used) != 0) return fail(LSAM_EINVAL, "dW product of convolution %d rejected", l);
       if (ssq) *slots += used;

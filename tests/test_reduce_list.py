@@ -3,6 +3,8 @@ holds are added up at once, as before."""
 import pytest
 
 import launches
+import workloads
+from paper_2509_03110_amd import lsam
 
 
 def reduces(model):
@@ -17,10 +19,22 @@ def test_one_launch_a_pass(bf16):
     assert reduces(model) == (2, 4, 0)
 
 
+def blocks(n, channels=16, batch=64):
+    """A first layer and n blocks of two convolutions, each closed by a projection: 3 n weight gradients above the first layer's."""
+    convs = 2 * n + 1
+    closing = sum(1 << l for l in range(2, convs, 2))
+    return dict(K=1, dims=(3,) + (channels,) * convs + (10,), batch=batch, n_conv=convs, img_h=16, img_w=16,
+                bn_mask=(1 << convs) - 1, skip_mask=closing, proj_mask=closing, global_avg_pool=1)
+
+
 def test_more_than_the_list_holds():
-    """39 convolutions of 16 channels in 19 blocks, each closed by a projection: 57 weight gradients above the first layer's."""
-    closing = sum(1 << l for l in range(2, 39, 2))
-    model = dict(K=1, dims=(3,) + (16,) * 39 + (10,), batch=64, n_conv=39, img_h=16, img_w=16, bn_mask=(1 << 39) - 1,
-                 skip_mask=closing, proj_mask=closing, global_avg_pool=1)
-    lists, _, others = reduces(model)
-    assert lists == 2 and others == 2 * (38 + 19 - 40)
+    lists, _, others = reduces(blocks(19))
+    assert lists == 2 and others == 2 * (3 * 19 - 40)
+
+
+def test_only_listed_products_have_a_place_of_their_own():
+    """A block of three listed products takes their partial sums' room beside everything else; one past the list does not.
+    (64 pieces of 64 x 576 sums for each 3x3 layer of 64 channels.)"""
+    def room(n):
+        return lsam.lsam_workspace_bytes(lsam.config_from_workload(workloads.Workload("p", tau=(1,), **blocks(n, 64)))[0])
+    assert room(6) - room(5) >= room(19) - room(18) + 2 * 64 * 64 * 576 * 4

@@ -783,7 +783,7 @@ __global__ __launch_bounds__(kThreads) void bn_stats_partial_kernel(const float*
 // registers for the second sum.  512 chunks of 64
 // columns, four replicas: 18 us with 16 chains and a load at a time, 11 us with eight in flight and read twice, 7.5 us so;
 // 128 chunks 14, 5.5 and 5.3.
-constexpr int kBnCols = 16, kBnChains = 64, kBnDepth = 16;
+constexpr int kBnCols = 16, kBnChains = 64;
 __device__ __forceinline__ double chain_total(double v, double (*buf)[kBnCols], int col) {
   v += __shfl_xor(v, 16, 64);
   v += __shfl_xor(v, 32, 64);
@@ -795,6 +795,7 @@ __device__ __forceinline__ double chain_total(double v, double (*buf)[kBnCols], 
   for (int w = 0; w < kBnCols * kBnChains / 64; ++w) t += buf[w][col];
   return t;
 }
+template <int DEPTH>
 __global__ __launch_bounds__(kBnCols * kBnChains) void bn_stats_finish_kernel(
     const float* __restrict__ pmean, const float* __restrict__ pm2, float* __restrict__ stats,
     long long rows, int C, int chunks, int chunk_rows, float eps) {
@@ -806,10 +807,10 @@ __global__ __launch_bounds__(kBnCols * kBnChains) void bn_stats_finish_kernel(
   const double last = (double)(rows - (long long)(chunks - 1) * chunk_rows);
   auto count = [&](int ch) { return ch + 1 < chunks ? (double)chunk_rows : last; };
   const long long base = (long long)k * chunks * C + c;
-  float m[kBnDepth], v[kBnDepth];
+  float m[DEPTH], v[DEPTH];
   const auto read = [&](int ch0) {
 #pragma unroll
-    for (int i = 0; i < kBnDepth; ++i) {
+    for (int i = 0; i < DEPTH; ++i) {
       const int ch = ch0 + i * kBnChains;
       const bool there = live && ch < chunks;
       m[i] = there ? pmean[base + (long long)ch * C] : 0.f;
@@ -819,12 +820,12 @@ __global__ __launch_bounds__(kBnCols * kBnChains) void bn_stats_finish_kernel(
   const auto add = [&](int ch0, auto term) {
     double t = 0.0;
 #pragma unroll
-    for (int i = 0; i < kBnDepth; ++i)
+    for (int i = 0; i < DEPTH; ++i)
       if (ch0 + i * kBnChains < chunks) t += term(i, count(ch0 + i * kBnChains));
     return t;
   };
   const auto weighed = [&](int i, double n) { return n * (double)m[i]; };
-  constexpr int kRound = kBnChains * kBnDepth;
+  constexpr int kRound = kBnChains * DEPTH;
   double s1 = 0.0;
   for (int ch0 = q + kRound; ch0 < chunks; ch0 += kRound) {
     read(ch0);
@@ -1333,8 +1334,12 @@ int launch_bn_stats(const float* Z, float* scratch, const ChunkSums& have, float
   if (!have.chunks)
     bn_stats_partial_kernel<<<dim3((unsigned)pl.chunks, (unsigned)K, (unsigned)pl.col_blocks), kThreads, 0, s>>>(
         Z, pmean, pm2, rows, C, pl.chunks, pl.chunk_rows);
-  bn_stats_finish_kernel<<<dim3((unsigned)((C + kBnCols - 1) / kBnCols), (unsigned)K), kBnCols * kBnChains, 0, s>>>(
-      pmean, pm2, stats, rows, C, sums.chunks, sums.rows, eps);
+  auto finish = [&](auto kernel) {
+    kernel<<<dim3((unsigned)((C + kBnCols - 1) / kBnCols), (unsigned)K), kBnCols * kBnChains, 0, s>>>(pmean, pm2, stats, rows, C,
+                                                                                                    sums.chunks, sums.rows, eps);
+  };
+  finish(sums.chunks <= kBnChains ? bn_stats_finish_kernel<1> : sums.chunks <= 4 * kBnChains ? bn_stats_finish_kernel<4>
+                                                                                             : bn_stats_finish_kernel<16>);
   return 0;
 }
 

@@ -397,7 +397,9 @@ struct Interleave {
 // a lane keeps its four columns, the lanes of a column and then the wavefronts are added in a fixed order, one chunk of rows a
 // workgroup.  Patches of 64 channels with one plane, 4 replicas of 128 images of 32 x 32: forward 63 us and 22 for the kernel that read
 // Z again, 66 together; input gradient with bits 84 and 53 for dY and Z, 116 together.
-template <int TM, int TN, int WM>
+// PLAIN: nothing of that, as for weight gradients and pieces of a cut contraction; what the others need, left in, cost a launch
+// of those 0.7 to 1.9 us.
+template <int TM, int TN, int WM, bool PLAIN>
 __device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[TM][TN], float* strips0, float* strips1, int tm0,
                                            int tn0, int bat, int piece, int t_in, int chunk, int chunks) {
   constexpr int WN = 4 / WM;
@@ -409,13 +411,13 @@ __device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[
   float* C = split_mode ? p.partial + (long long)piece * p.stridePartial + (long long)bat * p.M * p.ldP
                         : p.C + (long long)bat * p.strideC;
   const int ldC = split_mode ? p.ldP : p.ldC;
-  const bool has_bias = !split_mode && (p.epilogue == EPI_BIAS || p.epilogue == EPI_BIAS_RELU);
-  const bool relu = !split_mode && p.epilogue == EPI_BIAS_RELU;
-  const bool masked = !split_mode && p.epilogue == EPI_MASK;
+  const bool has_bias = !PLAIN && !split_mode && (p.epilogue == EPI_BIAS || p.epilogue == EPI_BIAS_RELU);
+  const bool relu = !PLAIN && !split_mode && p.epilogue == EPI_BIAS_RELU;
+  const bool masked = !PLAIN && !split_mode && p.epilogue == EPI_MASK;
   const float* mask = masked && p.keep == nullptr ? p.mask + (long long)bat * p.strideMask : nullptr;
   const unsigned char* keep = masked && p.keep != nullptr ? p.keep + (long long)bat * p.strideMask / 4 : nullptr;
   // (of a stride-2 input gradient, the class of even rows and columns)
-  const bool adds = !split_mode && p.add != nullptr && p.out_i == 0 && p.out_j == 0;
+  const bool adds = !PLAIN && !split_mode && p.add != nullptr && p.out_i == 0 && p.out_j == 0;
   const float* add = adds ? p.add + (long long)bat * p.strideAdd : nullptr;
   constexpr int PITCH = TN * 32 + 4;
   constexpr int LANES_PER_ROW = TN * 8;
@@ -431,7 +433,7 @@ __device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[
     return pass < PASSES && rr < 32 && rsub < ROWS_PER_PASS && m < p.M && n < p.N ? m : -1;
   };
   const auto placed = [&](int m) {                  // where a stride-2 input gradient's class writes it
-    if (p.out_step <= 1) return m;
+    if (PLAIN || p.out_step <= 1) return m;
     int b, oi, oj;
     decode(m, p.g, b, oi, oj);
     return ((b * p.g.oH + oi) * 2 + p.out_i) * (2 * p.g.oW) + 2 * oj + p.out_j;
@@ -439,7 +441,7 @@ __device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[
   f32x4 bv = {0.f, 0.f, 0.f, 0.f};
   if (has_bias && n < p.N) bv = *reinterpret_cast<const f32x4*>(p.bias + (long long)bat * p.strideBias + n);
   f32x4 mu = {0.f, 0.f, 0.f, 0.f}, inv = mu, s1 = mu, s2 = mu;      // of the sums; mu of statistics: their shift
-  const bool backward_sums = p.sums == 2;
+  const bool backward_sums = !PLAIN && p.sums == 2;
   if (backward_sums && n < p.N) {
     mu = *reinterpret_cast<const f32x4*>(p.sum_stats + (long long)bat * 2 * p.N + n);
     inv = *reinterpret_cast<const f32x4*>(p.sum_stats + ((long long)bat * 2 + 1) * p.N + n);
@@ -536,14 +538,16 @@ __device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[
     }
   };
   const bool meets = adds || masked || backward_sums;
-  if (p.sums != 0) {
+  if constexpr (PLAIN) {
+    write(std::false_type{}, std::false_type{});
+  } else if (p.sums != 0) {
     if (meets) write(std::true_type{}, std::true_type{});
     else write(std::false_type{}, std::true_type{});
   } else {
     if (meets) write(std::true_type{}, std::false_type{});
     else write(std::false_type{}, std::false_type{});
   }
-  if (p.sums != 0) {
+  if (!PLAIN && p.sums != 0) {
     const auto rows_of = [&](int wm) {
       const int left = p.M - (tm0 + wm * (TM * 32));
       return left < 0 ? 0 : left < TM * 32 ? left : TM * 32;
@@ -616,8 +620,8 @@ template <int NP, int BM> struct PickA<NP, kWeightGrad, BM> { typedef MatM<BM, N
 template <int NP, int KIND, int BN> struct PickB { typedef MatK<BN, NP, KIND == kForwardAnyC> type; };
 template <int NP, int BN> struct PickB<NP, kWeightGrad, BN> { typedef ImgM<BN, NP> type; };
 
-template <int NP, int KIND, int BM, int BN, int WM, int NSTAGE, int OCC>
-__global__ __launch_bounds__(kThreads, OCC) void conv_gemm_kernel(Params p) {
+template <int NP, int KIND, int BM, int BN, int WM, int NSTAGE, bool PLAIN>
+__device__ __forceinline__ void conv_gemm_workgroup(Params& p) {
   static_assert(NSTAGE >= 2 && NSTAGE <= 4, "ring of 2 to 4 stages");
   typedef typename PickA<NP, KIND, BM>::type OpA;
   typedef typename PickB<NP, KIND, BN>::type OpB;
@@ -790,8 +794,17 @@ __global__ __launch_bounds__(kThreads, OCC) void conv_gemm_kernel(Params p) {
   }
 
   const bool classes = KIND != kWeightGrad && p.out_step == 2;
-  store_tile<TM, TN, WM>(p, acc, reinterpret_cast<float*>(st0), reinterpret_cast<float*>(st1), m0, n0, bat, piece, t_in,
-                         classes ? m0 / BM * 4 + p.out_i * 2 + p.out_j : m0 / BM, classes ? 4 * p.tilesM : p.tilesM);
+  store_tile<TM, TN, WM, PLAIN>(p, acc, reinterpret_cast<float*>(st0), reinterpret_cast<float*>(st1), m0, n0, bat, piece, t_in,
+                                classes ? m0 / BM * 4 + p.out_i * 2 + p.out_j : m0 / BM, classes ? 4 * p.tilesM : p.tilesM);
+}
+template <int NP, int KIND, int BM, int BN, int WM, int NSTAGE, int OCC>
+__global__ __launch_bounds__(kThreads, OCC) void conv_gemm_kernel(Params p) {
+  conv_gemm_workgroup<NP, KIND, BM, BN, WM, NSTAGE, KIND == kWeightGrad>(p);
+}
+// (of a cut contraction)
+template <int NP, int KIND, int BM, int BN, int WM, int NSTAGE, int OCC, bool PIECE>
+__global__ __launch_bounds__(kThreads, OCC) void conv_gemm_kernel(Params p) {
+  conv_gemm_workgroup<NP, KIND, BM, BN, WM, NSTAGE, PIECE>(p);
 }
 
 // A uniform value the compiler may not compute with ahead of time: without it the addresses of all
@@ -845,8 +858,9 @@ __device__ __forceinline__ void issue_split_filters(const unsigned short* base, 
 //   Bytes into LDS per 32 channels: 22 + 37 KiB a plane (32 x 32 image) against 180 for the ring.
 // Four wavefronts below each other, 64 x 64 results each: 64 bytes of LDS reads per clock and
 // compute unit at the full matrix rate (64 x 32 per wavefront would need 96 of the 128).
-template <int NCHUNK>
-__global__ __launch_bounds__(kThreads, 2) void conv_patch_kernel(Params p) {
+template <int NCHUNK, bool PLAIN>
+__device__ __forceinline__ void patch_workgroup(Params& p) {
+#if defined(__HIP_DEVICE_COMPILE__)
   constexpr int NP = 1, BM = 256, BN = 64, TM = 2, TN = 2;
   constexpr int TPS = 3;                               // taps per stage of filters
   constexpr int S = 9 / TPS;                           // stages per 32 channels
@@ -1030,8 +1044,18 @@ __global__ __launch_bounds__(kThreads, 2) void conv_patch_kernel(Params p) {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-  store_tile<TM, TN, 4>(p, acc, reinterpret_cast<float*>(pa0), reinterpret_cast<float*>(pa1), m0, n0, bat, piece, t_in, t_row,
-                        p.tilesM);
+  store_tile<TM, TN, 4, PLAIN>(p, acc, reinterpret_cast<float*>(pa0), reinterpret_cast<float*>(pa1), m0, n0, bat, piece, t_in, t_row,
+                               p.tilesM);
+#endif
+}
+// Pieces of a cut contraction, and (WHOLE) whole ones.
+template <int NCHUNK>
+__global__ __launch_bounds__(kThreads, 2) void conv_patch_kernel(Params p) {
+  patch_workgroup<NCHUNK, true>(p);
+}
+template <int NCHUNK, bool WHOLE>
+__global__ __launch_bounds__(kThreads, 2) void conv_patch_kernel(Params p) {
+  patch_workgroup<NCHUNK, !WHOLE>(p);
 }
 
 // The same with three planes.  A workgroup takes TM x 128 pixels and blocks of 16 channels (one
@@ -1052,10 +1076,9 @@ __global__ __launch_bounds__(kThreads, 2) void conv_patch_kernel(Params p) {
 // replicas of 64 images, whole / half tiles: 32 x 32, 80 channels 1749 / 1730 us, 96 1980 / 1921, 160 4208 / 4127; 20 x 20, 160
 // 2327 / 2288.  Between one and two rounds of the 512 workgroups that fit the chip whole tiles stay: 160 channels at
 // 16 x 16, 768 workgroups, 1203 / 1232.
-template <int TM, int TN, int NCHUNK>
+template <int TM, int TN, int NCHUNK, bool PLAIN>
 __device__ __forceinline__ void split_patch_tile(const Params& p, lds_byte* a0, lds_byte* a1, lds_byte* b0, lds_byte* b1,
                                                  lds_byte* sp, int m0, int n0, int bat, int piece, int t_in, int t_row) {
-#if defined(__HIP_DEVICE_COMPILE__)
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int NP = 3, BN = TN * 32, S = 9;
   constexpr int NLA = (NCHUNK + 3) / 4, NA = NLA * NP, AG = (NA + S - 2) / (S - 1);
@@ -1218,12 +1241,11 @@ __device__ __forceinline__ void split_patch_tile(const Params& p, lds_byte* a0, 
 #pragma unroll
     for (int j = 0; j < TN; ++j)
       join_sums(acc[i][j], low[i][j]);
-  store_tile<TM, TN, 4>(p, acc, (float*)a0, (float*)a1, m0, n0, bat, piece, t_in, t_row, p.tilesM);
-#endif
+  store_tile<TM, TN, 4, PLAIN>(p, acc, (float*)a0, (float*)a1, m0, n0, bat, piece, t_in, t_row, p.tilesM);
 #endif
 }
 
-template <int TM, int TN, int NCHUNK, bool NARROW_LAST>
+template <int TM, int TN, int NCHUNK, bool NARROW_LAST, bool PLAIN>
 __device__ __forceinline__ void split_patch_workgroup(const Params& p) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int NP = 3, BM = TM * 128, BN = TN * 32;
@@ -1252,17 +1274,25 @@ __device__ __forceinline__ void split_patch_workgroup(const Params& p) {
   lds_byte* b0 = (lds_byte*)pb0;
   lds_byte* b1 = (lds_byte*)pb1;
   lds_byte* sp = (lds_byte*)spill;
-  if (NARROW_LAST && p.N - n0 <= 32) split_patch_tile<TM, 1, NCHUNK>(p, a0, a1, b0, b1, sp, m0, n0, bat, piece, t_in, t_row);
-  else split_patch_tile<TM, TN, NCHUNK>(p, a0, a1, b0, b1, sp, m0, n0, bat, piece, t_in, t_row);
+  if (NARROW_LAST && p.N - n0 <= 32) split_patch_tile<TM, 1, NCHUNK, PLAIN>(p, a0, a1, b0, b1, sp, m0, n0, bat, piece, t_in, t_row);
+  else split_patch_tile<TM, TN, NCHUNK, PLAIN>(p, a0, a1, b0, b1, sp, m0, n0, bat, piece, t_in, t_row);
 #endif
 }
 template <int TM, int TN, int NCHUNK>
 __global__ __launch_bounds__(kThreads, 2) void conv_split_patch_kernel(Params p) {
-  split_patch_workgroup<TM, TN, NCHUNK, false>(p);
+  split_patch_workgroup<TM, TN, NCHUNK, false, true>(p);
+}
+template <int TM, int TN, int NCHUNK, bool WHOLE>
+__global__ __launch_bounds__(kThreads, 2) void conv_split_patch_kernel(Params p) {
+  split_patch_workgroup<TM, TN, NCHUNK, false, !WHOLE>(p);
 }
 template <int TM, int TN, int NCHUNK>
 __global__ __launch_bounds__(kThreads, 2) void conv_split_patch_narrow_last_kernel(Params p) {
-  split_patch_workgroup<TM, TN, NCHUNK, true>(p);
+  split_patch_workgroup<TM, TN, NCHUNK, true, true>(p);
+}
+template <int TM, int TN, int NCHUNK, bool WHOLE>
+__global__ __launch_bounds__(kThreads, 2) void conv_split_patch_narrow_last_kernel(Params p) {
+  split_patch_workgroup<TM, TN, NCHUNK, true, !WHOLE>(p);
 }
 
 // ---- weight gradient of 3x3 layers with stride 1, image patches in LDS ------------------
@@ -1543,31 +1573,51 @@ __global__ __launch_bounds__(512, 2) void conv_wgrad_kernel(Params p) {
 // host-side launch stubs of all implicit instantiations of such a kernel).
 #define LSAM_CONV_KERNEL(...) template __global__ void conv_gemm_kernel<__VA_ARGS__>(Params);
 LSAM_CONV_KERNEL(1, kForward, 128, 128, 2, 4, 2)
+LSAM_CONV_KERNEL(1, kForward, 128, 128, 2, 4, 2, true)
 LSAM_CONV_KERNEL(1, kForward, 256, 128, 2, 3, 2)
+LSAM_CONV_KERNEL(1, kForward, 256, 128, 2, 3, 2, true)
 LSAM_CONV_KERNEL(1, kForward, 256, 64, 4, 3, 2)
+LSAM_CONV_KERNEL(1, kForward, 256, 64, 4, 3, 2, true)
 LSAM_CONV_KERNEL(1, kForward, 256, 32, 4, 3, 2)
+LSAM_CONV_KERNEL(1, kForward, 256, 32, 4, 3, 2, true)
 LSAM_CONV_KERNEL(1, kForwardAnyC, 128, 128, 2, 4, 2)
+LSAM_CONV_KERNEL(1, kForwardAnyC, 128, 128, 2, 4, 2, true)
 LSAM_CONV_KERNEL(1, kForwardAnyC, 256, 128, 2, 3, 2)
+LSAM_CONV_KERNEL(1, kForwardAnyC, 256, 128, 2, 3, 2, true)
 LSAM_CONV_KERNEL(1, kForwardAnyC, 256, 64, 4, 3, 2)
+LSAM_CONV_KERNEL(1, kForwardAnyC, 256, 64, 4, 3, 2, true)
 LSAM_CONV_KERNEL(1, kForwardAnyC, 256, 32, 4, 3, 2)
+LSAM_CONV_KERNEL(1, kForwardAnyC, 256, 32, 4, 3, 2, true)
 LSAM_CONV_KERNEL(1, kWeightGrad, 128, 128, 2, 4, 2)
 LSAM_CONV_KERNEL(1, kWeightGrad, 64, 128, 2, 4, 2)
 LSAM_CONV_KERNEL(1, kWeightGrad, 32, 128, 1, 4, 2)
 LSAM_CONV_KERNEL(3, kForward, 128, 64, 2, 2, 2)
+LSAM_CONV_KERNEL(3, kForward, 128, 64, 2, 2, 2, true)
 LSAM_CONV_KERNEL(3, kForward, 128, 32, 4, 2, 2)
+LSAM_CONV_KERNEL(3, kForward, 128, 32, 4, 2, 2, true)
 LSAM_CONV_KERNEL(3, kForwardAnyC, 128, 64, 2, 2, 2)
+LSAM_CONV_KERNEL(3, kForwardAnyC, 128, 64, 2, 2, 2, true)
 LSAM_CONV_KERNEL(3, kForwardAnyC, 128, 32, 4, 2, 2)
+LSAM_CONV_KERNEL(3, kForwardAnyC, 128, 32, 4, 2, 2, true)
 LSAM_CONV_KERNEL(3, kWeightGrad, 64, 128, 2, 2, 2)
 LSAM_CONV_KERNEL(3, kWeightGrad, 32, 128, 1, 2, 2)
 
 template __global__ void conv_patch_kernel<22>(Params);
+template __global__ void conv_patch_kernel<22, true>(Params);
 template __global__ void conv_patch_kernel<26>(Params);
+template __global__ void conv_patch_kernel<26, true>(Params);
 template __global__ void conv_split_patch_kernel<2, 2, 11>(Params);
+template __global__ void conv_split_patch_kernel<2, 2, 11, true>(Params);
 template __global__ void conv_split_patch_narrow_last_kernel<2, 2, 11>(Params);
+template __global__ void conv_split_patch_narrow_last_kernel<2, 2, 11, true>(Params);
 template __global__ void conv_split_patch_kernel<1, 2, 10>(Params);
+template __global__ void conv_split_patch_kernel<1, 2, 10, true>(Params);
 template __global__ void conv_split_patch_narrow_last_kernel<1, 2, 10>(Params);
+template __global__ void conv_split_patch_narrow_last_kernel<1, 2, 10, true>(Params);
 template __global__ void conv_split_patch_kernel<2, 1, 11>(Params);
+template __global__ void conv_split_patch_kernel<2, 1, 11, true>(Params);
 template __global__ void conv_split_patch_kernel<1, 1, 10>(Params);
+template __global__ void conv_split_patch_kernel<1, 1, 10, true>(Params);
 template __global__ void conv_wgrad_kernel<3, 2, 64, 9>(Params);
 template __global__ void conv_wgrad_kernel<3, 1, 64, 9>(Params);
 template __global__ void conv_wgrad_kernel<1, 2, 64, 9>(Params);
@@ -1681,6 +1731,12 @@ int tiled(Params& p, int bm, int bn) {
 template <int NP, int KIND, int BM, int BN, int WM, int NSTAGE, int OCC>
 int run(Params& p, hipStream_t s) {
   const int slots = tiled(p, BM, BN);
+  if constexpr (KIND != kWeightGrad) {
+    if (p.ksplit > 1) {
+      conv_gemm_kernel<NP, KIND, BM, BN, WM, NSTAGE, OCC, true><<<p.chunks * 8, kThreads, 0, s>>>(p);
+      return slots;
+    }
+  }
   conv_gemm_kernel<NP, KIND, BM, BN, WM, NSTAGE, OCC><<<p.chunks * 8, kThreads, 0, s>>>(p);
   return slots;
 }
@@ -1721,14 +1777,15 @@ int run_patch(Params& p, int kind, int np, hipStream_t s) {
                           kind == kSplitNarrow256 || kind == kSplitNarrow128 ? 32 : 64);
   const unsigned grid = (unsigned)p.chunks * 8;
   const bool narrow_last = (p.N - 1) % 64 < 32 && (p.total <= 512 || p.total >= 1024);
-  if (kind == kPatch22) conv_patch_kernel<22><<<grid, kThreads, 0, s>>>(p);
-  else if (kind == kPatch26) conv_patch_kernel<26><<<grid, kThreads, 0, s>>>(p);
-  else if (kind == kSplitPatch256 && narrow_last) conv_split_patch_narrow_last_kernel<2, 2, 11><<<grid, kThreads, 0, s>>>(p);
-  else if (kind == kSplitPatch256) conv_split_patch_kernel<2, 2, 11><<<grid, kThreads, 0, s>>>(p);
-  else if (kind == kSplitPatch128 && narrow_last) conv_split_patch_narrow_last_kernel<1, 2, 10><<<grid, kThreads, 0, s>>>(p);
-  else if (kind == kSplitPatch128) conv_split_patch_kernel<1, 2, 10><<<grid, kThreads, 0, s>>>(p);
-  else if (kind == kSplitNarrow256) conv_split_patch_kernel<2, 1, 11><<<grid, kThreads, 0, s>>>(p);
-  else conv_split_patch_kernel<1, 1, 10><<<grid, kThreads, 0, s>>>(p);
+  auto go = [&](auto piece, auto whole) { (p.ksplit > 1 ? +piece : +whole)<<<grid, kThreads, 0, s>>>(p); };
+  if (kind == kPatch22) go(conv_patch_kernel<22>, conv_patch_kernel<22, true>);
+  else if (kind == kPatch26) go(conv_patch_kernel<26>, conv_patch_kernel<26, true>);
+  else if (kind == kSplitPatch256 && narrow_last) go(conv_split_patch_narrow_last_kernel<2, 2, 11>, conv_split_patch_narrow_last_kernel<2, 2, 11, true>);
+  else if (kind == kSplitPatch256) go(conv_split_patch_kernel<2, 2, 11>, conv_split_patch_kernel<2, 2, 11, true>);
+  else if (kind == kSplitPatch128 && narrow_last) go(conv_split_patch_narrow_last_kernel<1, 2, 10>, conv_split_patch_narrow_last_kernel<1, 2, 10, true>);
+  else if (kind == kSplitPatch128) go(conv_split_patch_kernel<1, 2, 10>, conv_split_patch_kernel<1, 2, 10, true>);
+  else if (kind == kSplitNarrow256) go(conv_split_patch_kernel<2, 1, 11>, conv_split_patch_kernel<2, 1, 11, true>);
+  else go(conv_split_patch_kernel<1, 1, 10>, conv_split_patch_kernel<1, 1, 10, true>);
   return slots;
 }
 

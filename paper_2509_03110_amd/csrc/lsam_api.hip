@@ -729,11 +729,16 @@ void build_layout(const lsam_config& c, Layout& lo) {
       }
     }
     // Of the weight gradients that leave partial sums, as many as the pass's list holds get a place of their own, in the order
-    // of conv_backward.
+    // of conv_backward.  Sums past 20 MiB (16 where there are workgroups enough to add them up alone, 512) are not worth a place: added
+    // up at once, from memory that the product before has used as well, they are read from the caches.  A step with all
+    // listed / as the rule has it: 112 channels with 28 MiB a layer, two replicas of 40 images of 28 x 20, bf16, 929 / 896 us, 152
+    // and 304 channels with 19 MiB, two of 18 of 12 x 20, 1354 / 1321, 304 channels with 25 MiB, four of 8 of 16 x 20, 2232 / 2182; listed
+    // and at once 64 channels with 18 MiB and 144 workgroups (a residual net of 16 to 64 channels) 5318 / 5348, 144 channels with
+    // 6 MiB 445 / 453.
     int listed = 0;
-    auto place = [&](size_t& at, size_t& bytes) {
+    auto place = [&](size_t& at, size_t& bytes, int64_t results) {
       if (!bytes) return;
-      if (listed < ReduceList::kMax) {
+      if (listed < ReduceList::kMax && bytes <= (size_t)(lo.K * results >= (512 << 10) ? 16 : 20) << 20) {
         at = take(cur, bytes);
         ++listed;
       } else {
@@ -742,8 +747,8 @@ void build_layout(const lsam_config& c, Layout& lo) {
       }
     };
     for (int l = lo.n_conv - 1; l >= 0; --l) {
-      place(lo.conv[l].pwpart, lo.conv[l].pwpart_bytes);
-      place(lo.conv[l].wpart, lo.conv[l].wpart_bytes);
+      place(lo.conv[l].pwpart, lo.conv[l].pwpart_bytes, (int64_t)lo.layers[l].out * lo.layers[l].proj_in);
+      place(lo.conv[l].wpart, lo.conv[l].wpart_bytes, (int64_t)lo.layers[l].out * lo.layers[l].in);
     }
     lo.splitk_bytes = need;
     if (need) lo.splitk = take(cur, need);

@@ -32,6 +32,17 @@ def test_more_than_the_list_holds():
     assert lists == 2 and others == 2 * (3 * 19 - 40)
 
 
+@pytest.mark.parametrize("K,channels,batch,side,bf16,listed", [
+    (2, 112, 40, (28, 20), 1, False),      # 28 MiB a layer
+    (2, 304, 18, (12, 12), 0, False),      # 19 MiB, 1624 workgroups
+    (4, 64, 128, (8, 8), 0, True),         # 18 MiB, 144 workgroups
+    (4, 144, 8, (16, 4), 0, True)])        # 6 MiB
+def test_large_partial_sums_are_added_up_at_once(K, channels, batch, side, bf16, listed):
+    model = dict(K=K, dims=(5, channels, channels, channels, 10), batch=batch, n_conv=3, img_h=side[0], img_w=side[1], bn_mask=7,
+                 global_avg_pool=1, gemm_dtype=bf16)
+    assert reduces(model)[0] == (2 if listed else 0)
+
+
 def test_only_listed_products_have_a_place_of_their_own():
     """A block of three listed products takes their partial sums' room beside everything else; one past the list does not.
     (64 pieces of 64 x 576 sums for each 3x3 layer of 64 channels.)"""

@@ -559,8 +559,15 @@ void build_layout(const lsam_config& c, Layout& lo) {
       // one with a stored gradient and its fold unless three planes meet many columns that fill the 64-wide
       // tiles badly.  Steps of one such layer between two others, 4 replicas of 64 images of 32 x 32, stored / classes: 40
       // channels 1242 / 1163 us, 72 2462 / 2433, 80 2686 / 2601, 104 3968 / 3868, 160 6674 / 6630; 136 6221 / 6287, 152 7031 / 7120)
-      cv.direct_dx = small && l > 0 && fits(cv.Cout) &&
-                     (cv.stride == 1 || (cv.fast && (lo.np == 1 || cv.Cin <= 128 || (cv.Cin + 63) / 64 * 64 * 5 <= cv.Cin * 6)));
+      // Where the classes' tiles do not fill the chip twice over their longest contraction, four taps of all outputs, is what takes
+      // long: 72 to 320 channels on 1792 pixels, 112 tiles, 2.1 % more, to 160 on 3072, 192 tiles, 3 % less; 112 to 224 with 112
+      // tiles 0.3 % more, with 192 2.3 % less, to 448 with 64 6 % more, 192 0.4 %; 160 to 320 with 96 2.9 % more, 168 1.4 % less;
+      // 224 to 448 with 80 6 % more, 384 1.2 %.  (Columns that fill their tiles have always been taken in classes.)
+      const int columns = (cv.Cin + 63) / 64 * 64;
+      const bool classes_pay = lo.np == 1 || cv.Cin <= 32 || columns * 8 <= cv.Cin * 9 ||
+                               ((cv.Cin <= 128 || columns * 5 <= cv.Cin * 6) &&
+                                lo.K * ((cv.rows + 127) / 128) * (columns / 64) * 4 * 390 >= (int64_t)cv.Cout * cv.Cout);
+      cv.direct_dx = small && l > 0 && fits(cv.Cout) && (cv.stride == 1 || (cv.fast && classes_pay));
       cv.first = l == 0 && cv.stride == 1 && first_conv_fits(cv.Cin, cv.Cout, cv.rows, lo.K, lo.bf16_math);
     }
     for (int l = 0; l < lo.n_conv; ++l) {

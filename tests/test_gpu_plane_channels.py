@@ -21,7 +21,10 @@ NETS = {
     "152, few pixels": dict(dims=(8, 152, 88, 10), side=(4, 4), batch=131),
     # stride 2, three planes: dX in classes with a column tile of 8 and one of 64, and (136) through a stored gradient
     "72, stride in classes": dict(dims=(3, 72, 104, 10), side=(32, 32), batch=33, stride=0b010),
-    "128 and 160, strides in classes": dict(dims=(8, 128, 160, 64, 10), side=(16, 32), batch=35, stride=0b0110),
+    # (its second stride, on 2240 pixels, goes to the fp32-storage product)
+    "128, stride in classes": dict(dims=(8, 128, 160, 64, 10), side=(16, 32), batch=35, stride=0b0110),
+    "160, stride in classes": dict(dims=(8, 160, 64, 10), side=(16, 16), batch=90, stride=0b010),
+    "104 to 320 on few pixels, stride through a stored gradient": dict(dims=(8, 104, 320, 10), side=(16, 16), batch=16, stride=0b010),
     "136, stride through a stored gradient": dict(dims=(8, 136, 64, 10), side=(16, 16), batch=90, stride=0b010),
     # last columns on half tiles of the three-plane patches: of 256 and (64 wide) of 128 pixels; 160 between one and two rounds
     "96 and 160, last columns on half tiles": dict(dims=(3, 96, 160, 80, 10), side=(16, 16), batch=23),

@@ -395,6 +395,21 @@ bool shortcut_joins_product(const Layout& lo, int l) {
          lo.conv[l + 1].W == cv.W && lo.conv[l + 1].skip_step == cv.stride;
 }
 
+// Whether a last layer's normalisation is joined with the global average behind it.  A workgroup then walks the HW positions of one
+// image, 64 channels and 16 positions at a time, where the normalisation alone has a thread a word: few images leave the chip
+// idle, the sooner where a shortcut is another load to wait for.  A step apart / joined, `images` those of all replicas:
+//   8x8 positions, no shortcut: 4 images of 64 channels 199 / 196 us, 512 282 / 270
+//   8x8, a shortcut: 48 of 16 channels 320 / 323, 48 of 256 696 / 697, 100 of 256 1072 / 1062
+//   16x16, no shortcut: 48 of 64 257 / 260, 16 of 256 413 / 412, 100 of 64 274 / 270, 192 of 64 310 / 296
+//   16x16, a shortcut: 100 of 64 402 / 415, 192 of 64 460 / 466, 512 of 64 738 / 724
+//   28x32, a shortcut: 10 of 8 604 / 687
+//   32x32, no shortcut: 48 of 64 365 / 379, 100 of 64 417 / 410, 192 of 64 645 / 542
+//   32x32, a shortcut: 16 of 16 317 / 413, 192 of 64 1012 / 1070
+bool joined_average_pays(int64_t images, int HW, int C, bool shortcut) {
+  if (HW <= (shortcut ? 16 : 64)) return true;
+  return shortcut ? HW <= 256 && images * C >= 20480 : images * C >= 6144;
+}
+
 void build_layout(const lsam_config& c, Layout& lo) {
   lo.K = c.K;
   lo.L = c.n_layers;
@@ -576,7 +591,8 @@ void build_layout(const lsam_config& c, Layout& lo) {
       const ConvLayer* closing = l + 2 < lo.n_conv && lo.conv[l + 2].skip ? &lo.conv[l + 2] : nullptr;
       const bool post_sum = cv.skip && !lo.preact;
       cv.bn_pool = cv.bn && cv.pool && !post_sum;
-      cv.bn_gap = cv.bn && !cv.pool && !next && lo.gap_hw > 0;
+      cv.bn_gap = cv.bn && !cv.pool && !next && lo.gap_hw > 0 &&
+                  joined_average_pays((int64_t)lo.K * lo.B, lo.gap_hw, cv.Cout, post_sum);
       cv.has_keep = cv.pool || (cv.bn &&
                     (next ? next->fast && next->direct_dx && (!opens_block(lo, l + 1) || shortcut_joins_product(lo, l + 1))
                           : lo.gap_hw > 0));

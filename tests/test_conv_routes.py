@@ -53,3 +53,20 @@ def test_input_gradients_of_strides(name, fold):
                                                    (64, 448, 28, 1, False)])
 def test_classes_on_few_pixels(cin, cout, batch, K, fold):
     assert stored(dict(dims=(3, cin, cout, 10), side=(16, 16), batch=batch, K=K, stride=0b010)) == fold
+
+
+@pytest.mark.parametrize("channels,side,images,skip,joined", [
+    (64, 8, 4, 0, True), (64, 16, 48, 0, False), (64, 16, 100, 0, True), (64, 32, 48, 0, False), (64, 32, 100, 0, True),
+    (64, 4, 4, 0b100, True), (16, 8, 48, 0b100, False), (64, 16, 192, 0b100, False), (64, 16, 512, 0b100, True),
+    (64, 32, 512, 0b100, False)])
+def test_joined_averages(channels, side, images, skip, joined):
+    dims = (3,) + (channels,) * (3 if skip else 2) + (10,)
+    got = names(dict(dims=dims, side=(side, side), batch=images // 4, K=4, skip=skip))
+    assert ("bn_avgpool_kernel" in got) == joined and ("avgpool_kernel" in got) != joined
+
+
+@pytest.mark.parametrize("name,joined", [("average behind a shortcut", False), ("average of few positions behind a shortcut", True),
+                                         ("average of few positions behind a projection", True), ("chain", False),
+                                         ("chain, products cut over workgroups", True)])
+def test_averages_of_the_gpu_tests(name, joined):
+    assert ("bn_avgpool_kernel" in names(bits.NETS[name])) == joined

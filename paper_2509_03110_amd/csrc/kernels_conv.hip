@@ -779,8 +779,9 @@ __global__ __launch_bounds__(kThreads) void bn_stats_partial_kernel(const float*
 //   mean = sum_i n_i mean_i / rows,   M2 = sum_i [M2_i + n_i (mean_i - mean)^2]
 // over the chunks i, in double, in a fixed order.  Next to nothing is read, so what bounds this is
 // the chain of loads a thread has to wait for: workgroup (block, k) serves 16 columns with 64 chains
-// each (chain q takes chunks q, q + 64, ...), sixteen chunks in flight per chain, and the first 1024 chunks stay in
-// registers for the second sum.  512 chunks of 64
+// each (chain q takes chunks q, q + 64, ...), DEPTH chunks in flight per chain, and the first 64 DEPTH chunks stay in
+// registers for the second sum: 16 deep, or 4 or 1 where there are no more chunks than that (up to 64 chunks: 4.1 to 4.7 us with
+// eight in flight and a loop that ends, 4.5 to 5.0 with the depth of 16, whose skipped chunks are not free).  512 chunks of 64
 // columns, four replicas: 18 us with 16 chains and a load at a time, 11 us with eight in flight and read twice, 7.5 us so;
 // 128 chunks 14, 5.5 and 5.3.
 constexpr int kBnCols = 16, kBnChains = 64;

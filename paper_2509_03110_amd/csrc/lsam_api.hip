@@ -1356,8 +1356,9 @@ int conv_backward(lsam_ctx* c, const float* X, const float* params, double* ssq,
     have = ChunkSums{};
     if (l > 0 && cv.direct_dx) {
       // dX as a convolution of the output gradient with the mirrored filters, written straight
-      // into the gradient of the image this layer read (masked by the ReLU output it came
-      // from when no pool sits in between; a pool's backward pass applies the mask itself)
+      // into the gradient of the image this layer read.  The product on plane tensors masks it by the ReLU output it came
+      // from, pooled or not: the column sums a normalisation takes with it are those of masked values.  The fp32-storage one
+      // leaves a pooled image's mask to the pool's backward pass.
       const ConvLayer& below = lo.conv[l - 1];
       if (cv.fast) {
         LaunchTimer t(c, KC_GEMM_DX);

@@ -33,12 +33,12 @@ SPLIT_PRODUCTS = 6                    # bf16 products an fp32 product of exact p
 # 1 GiB device copy: x2.0 and x1.0), summed over the dispatches of a class and divided by its
 # launches (a split-K GEMM and its reduce count as one launch; kernels that serve several classes
 # are told apart by empty marker kernels launched between the classes in a copy of the library).
-# The figures belong to the kernel sources whose digest is TRAFFIC_SOURCES; with any other sources
-# `traffic` is null.
-TRAFFIC_SOURCES = "5c9332f77cf1fca5"
+# The figures belong to the kernel sources that serve the workload (traffic_family), as long as their digest is the one
+# in TRAFFIC_SOURCES; with any other sources `traffic` is null.
+TRAFFIC_SOURCES = {"raw": "7ecdbed4756e4dd1", "dense_bf16": "5226c8879f5d946e", "all": "532e42178a1df6bb"}
 TRAFFIC = {
-    "cfg2": {"center": 84162976, "descent": 538491904, "gemm_dw": 96010203, "gemm_dx": 42150912,
-             "gemm_fwd": 62132075, "perturb": 201946923},
+    "cfg2": {"center": 84162976, "descent": 538478884, "gemm_dw": 96747181, "gemm_dx": 42137399,
+             "gemm_fwd": 91313573, "perturb": 201939879},
     "cfg3": {"bias_grad": 69965355, "center": 1393527072, "gemm_dw_ascend": 732938428,
              "gemm_dw_norm": 74834581, "gemm_dw_step": 2904271437, "gemm_dx": 250151232,
              "gemm_fwd": 233113689, "softmax_ce": 1428949},
@@ -46,57 +46,63 @@ TRAFFIC = {
     "cfg5": {"bias_grad": 836635733, "gemm_dw_ascend": 6220483834, "gemm_dw_norm": 1683837749,
              "gemm_dw_step": 27280532194, "gemm_dx": 2584784242, "gemm_fwd": 2034203236,
              "softmax_ce": 96475915},
-    "cnn5": {"bias_grad": 25743968, "conv_first": 80456192, "descent": 79477760,
-             "gemm_dw": 69222277, "gemm_dx": 107788708, "gemm_fwd": 42524672, "perturb": 29814784,
-             "pool": 74879445, "unfold_fold": 62939307},
-    "cnn5bn": {"batchnorm": 162314172, "conv_first": 80453675, "descent": 79543296,
-             "gemm_dw": 69261888, "gemm_dx": 107807353, "gemm_fwd": 42524914, "perturb": 29840043,
-             "pool": 74879374},
-    "resnet18": {"batchnorm": 316562322, "conv_first": 155061451, "descent": 1430972288,
-             "gemm_dw": 265215641, "gemm_dx": 363525780, "gemm_fwd": 310929016,
-             "perturb": 536624896, "pool": 29927424},
-    "resnet18bf": {"batchnorm": 260349643, "conv_first": 155073771, "descent": 1430972288,
-             "gemm_dw": 107817171, "gemm_dx": 188401887, "gemm_fwd": 109772652,
-             "perturb": 536624811, "pool": 29927424, "softmax_ce": 124245},
-    "resnet20": {"batchnorm": 106355368, "conv_first": 43712715, "descent": 34872320,
-             "gemm_dw": 76262636, "gemm_dx": 97150488, "gemm_fwd": 64854366, "perturb": 13087744,
-             "pool": 12953088},
-    "resnet34": {"batchnorm": 299014796, "conv_first": 154834517, "descent": 2731198635,
-             "gemm_dw": 252070505, "gemm_dx": 330192046, "gemm_fwd": 275606772,
-             "perturb": 1024210304, "pool": 29927424, "softmax_ce": 485291},
-    "vgg16": {"batchnorm": 202214841, "conv_first": 154954133, "descent": 1952548693,
-             "gemm_dw": 186763250, "gemm_dx": 192438848, "gemm_fwd": 165874359,
-             "perturb": 732216064, "pool": 99067179},
-    "vgg16bf": {"batchnorm": 173734942, "conv_first": 154976608, "descent": 1952549077,
-             "gemm_dw": 83541013, "gemm_dx": 99557582, "gemm_fwd": 75945737, "perturb": 732216021,
-             "pool": 92562665, "softmax_ce": 124437},
-    "wrn16x10": {"batchnorm": 960040940, "conv_first": 43712128, "descent": 2191779797,
-             "gemm_dw": 1230240994, "gemm_dx": 1605117153, "gemm_fwd": 1817018475,
-             "perturb": 821927936, "pool": 199724494, "unfold_fold": 1395092523},
-    "wrn16x10bf": {"batchnorm": 781247733, "conv_first": 43712661, "descent": 2191779883,
-             "gemm_dw": 359107257, "gemm_dx": 564179372, "gemm_fwd": 444353231,
-             "perturb": 821927424, "pool": 131769856, "softmax_ce": 124501},
-    "wrn28x10": {"batchnorm": 1018041750, "conv_first": 43709045, "descent": 4678192384,
-             "gemm_dw": 1391314120, "gemm_dx": 1757260971, "gemm_fwd": 1871678357,
-             "perturb": 1754334336, "pool": 199724501, "softmax_ce": 484949,
-             "unfold_fold": 1395091883},
-    "wrn40x10": {"batchnorm": 1038421202, "conv_first": 43709845, "descent": 7157222997,
-             "gemm_dw": 1463228814, "gemm_dx": 1797676739, "gemm_fwd": 1933950566,
-             "perturb": 2683971157, "pool": 199724544, "softmax_ce": 484949,
-             "unfold_fold": 1395091392},
+    "cnn5": {"bias_grad": 7143764, "conv_first": 80178413, "descent": 79475846,
+             "gemm_dw": 51929342, "gemm_dx": 107749902, "gemm_fwd": 42564241, "perturb": 29814018,
+             "pool": 56534275},
+    "cnn5bn": {"batchnorm": 86030533, "conv_first": 80335276, "descent": 79541381,
+             "gemm_dw": 51969009, "gemm_dx": 113816528, "gemm_fwd": 42744123, "perturb": 29838593},
+    "resnet18": {"batchnorm": 201102826, "conv_first": 221362047, "descent": 1430937488,
+             "gemm_dw": 252846617, "gemm_dx": 366479652, "gemm_fwd": 293660952,
+             "perturb": 536610566, "pool": 26264216},
+    "resnet18bf": {"batchnorm": 149142329, "conv_first": 223411678, "descent": 1430936934,
+             "gemm_dw": 102601357, "gemm_dx": 187866395, "gemm_fwd": 110345231,
+             "perturb": 536610225, "pool": 26264207, "softmax_ce": 124241},
+    "resnet20": {"batchnorm": 72500733, "conv_first": 60550145, "descent": 34871469,
+             "gemm_dw": 72397848, "gemm_dx": 93903104, "gemm_fwd": 65008708, "perturb": 13087403,
+             "pool": 9487317},
+    "resnet34": {"batchnorm": 194503825, "conv_first": 221389946, "descent": 2731132935,
+             "gemm_dw": 245768897, "gemm_dx": 335356277, "gemm_fwd": 261628590,
+             "perturb": 1024183307, "pool": 26264217, "softmax_ce": 485024},
+    "vgg16": {"batchnorm": 101264297, "conv_first": 221832774, "descent": 1952501434,
+             "gemm_dw": 174100766, "gemm_dx": 198164842, "gemm_fwd": 160359164,
+             "perturb": 732196776},
+    "vgg16bf": {"batchnorm": 76753255, "conv_first": 223642959, "descent": 1952501374,
+             "gemm_dw": 77534825, "gemm_dx": 101127042, "gemm_fwd": 76220015, "perturb": 732196675,
+             "softmax_ce": 123900},
+    "wrn16x10": {"batchnorm": 595628892, "conv_first": 60565709, "descent": 2191727505,
+             "gemm_dw": 1164417129, "gemm_dx": 1485016044, "gemm_fwd": 1660644325,
+             "perturb": 821906336},
+    "wrn16x10bf": {"batchnorm": 416333942, "conv_first": 60510081, "descent": 2191726234,
+             "gemm_dw": 330248064, "gemm_dx": 582511328, "gemm_fwd": 447066536,
+             "perturb": 821906007, "softmax_ce": 123900},
+    "wrn28x10": {"batchnorm": 643008090, "conv_first": 60615942, "descent": 4678080460,
+             "gemm_dw": 1349570907, "gemm_dx": 1599117019, "gemm_fwd": 1818108096,
+             "perturb": 1754287219, "softmax_ce": 484683},
+    "wrn40x10": {"batchnorm": 659650300, "conv_first": 60544820, "descent": 7157051358,
+             "gemm_dw": 1430426883, "gemm_dx": 1643661000, "gemm_fwd": 1911413329,
+             "perturb": 2683899873, "softmax_ce": 484683},
 }
 
 
-def kernel_sources_digest():
+def traffic_family(w):
+    """Which sources hold the kernels a workload launches."""
+    return "raw" if not w.dims else "dense_bf16" if w.gemm_dtype == 1 and not w.n_conv else "all"
+
+
+def kernel_sources_digest(family):
     import glob
     import hashlib
     h = hashlib.sha256()
     # the files that hold device code (the host engine, lsam_api.hip and engine.h, launches
     # these kernels but does not change what one launch of them moves)
-    files = sorted(glob.glob(os.path.join(ROOT, "paper_2509_03110_amd", "csrc", "kernels_*.hip")) +
-                   [os.path.join(ROOT, "paper_2509_03110_amd", "csrc", h) for h in ("b32s.h", "langevin.h", "planes.h")])
+    csrc = os.path.join(ROOT, "paper_2509_03110_amd", "csrc")
+    files = {"raw": ["kernels_stream.hip", "langevin.h"],
+             "dense_bf16": ["kernels_ce.hip", "kernels_gemm_bf16.hip", "kernels_stream.hip", "b32s.h", "dense_gradients.h",
+                            "langevin.h"],
+             "all": sorted(os.path.basename(f) for f in glob.glob(os.path.join(csrc, "kernels_*.hip"))) +
+                    ["b32s.h", "dense_gradients.h", "langevin.h", "planes.h"]}[family]
     for f in files:
-        with open(f, "rb") as fh:
+        with open(os.path.join(csrc, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
 
@@ -161,22 +167,72 @@ def gemm_flops(w, layers):
     return out
 
 
+def conv_routes(w, layers, planes):
+    """What the library keeps of each convolution's output and where a normalisation's sums are taken, as its layout
+    decides it."""
+    from paper_2509_03110_amd import lsam
+    n = w.n_conv
+    bit = lambda mask, l: l < n and bool((mask >> l) & 1)
+    proj = lambda l: l < n and bool(layers[l][6])
+    opens = lambda l: bit(w.skip_mask, l + 1) and (proj(l + 1) or not w.preact)
+    direct_dx = lambda l: 0 < l < n and not layers[l][1]
+    # the shortcut's gradient joins the product that writes the block input's
+    joins = lambda l: (l > 0 and opens(l) and planes[l] and direct_dx(l) and not bit(w.pool_mask, l - 1) and
+                       not bit(w.stride_mask, l + 1))
+    reads_planes = lambda l: planes[l] > 0 and layers[l][0] == lsam.LAYER_CONV_DIRECT
+    out = []
+    for l in range(n):
+        bn, pool, last = bit(w.bn_mask, l), bit(w.pool_mask, l), l + 1 == n
+        post_sum = bit(w.skip_mask, l) and not w.preact
+        # what writes this layer's gradient is a plane product that completes it
+        complete = not last and planes[l + 1] and direct_dx(l + 1) and (not opens(l + 1) or joins(l + 1))
+        r = dict(bn=bn, pool=pool, post_sum=post_sum, bn_pool=bn and pool and not post_sum,
+                 bn_gap=bn and not pool and last and bool(w.global_avg_pool) and joined_average(w, layers[l][3], w.dims[l + 1], post_sum))
+        r["bits"] = pool or (bn and bool(complete if not last else w.global_avg_pool))
+        r["pooled_floats"] = pool and (last or not reads_planes(l + 1))
+        closing = l + 2 if bit(w.skip_mask, l + 2) else None
+        if pool or last:
+            r["floats"] = not r["bn_pool"] and not r["bn_gap"]
+        else:
+            r["floats"] = (not r["bits"] or not reads_planes(l + 1) or
+                           (closing is not None and (not planes[closing] if proj(closing) else not w.preact)))
+        # (a product cut over workgroups leaves no sums: its bytes then count less than it moves)
+        r["sums_forward"] = layers[l][0] == lsam.LAYER_CONV_FIRST or planes[l] > 0
+        r["sums_backward"] = bool(complete and bn and (not pool or r["bn_pool"]))
+        r["joins"] = bool(joins(l))
+        # the gradient of a last image's average is formed where it is used
+        r["from_average"] = r["bn_gap"] and not (post_sum and not proj(l))
+        out.append(r)
+    return out
+
+
+def joined_average(w, rows, channels, shortcut):
+    hw = rows // w.batch
+    if hw <= (16 if shortcut else 64):
+        return True
+    work = w.K * w.batch * channels
+    return (hw <= 256 and work >= 20480) if shortcut else work >= 6144
+
+
 def conv_bytes(w, layers, planes):
     """Algorithmic bytes per all-replica step (both passes) of the kernels around the
-    convolution GEMMs: where an unfolded image is stored it is written once (plus the image
-    read), where its gradient is stored that is read once (plus the image gradient written);
-    the pool reads its input and writes a quarter of it, its backward pass reads both and
-    writes the full-size gradient.  Where plane tensors serve a layer (`planes` values of 2 bytes
+    convolution products: what they read and write once each, as the library's layout has it (conv_routes).
+    Where an unfolded image is stored it is written once (plus the image
+    read), where its gradient is stored that is read once (plus the image gradient written).
+    Where plane tensors serve a layer (`planes` values of 2 bytes
     per number) its image's and its output gradient's planes are written by the kernels that form
-    them, or from the stored floats by one of their own; nothing then reads the gradient's floats
-    but an identity shortcut in front of a normalisation."""
+    them, or from the stored floats by one of their own.  Outputs are written as floats only where
+    something reads them, their signs as a bit a value."""
     from paper_2509_03110_amd import lsam
     unfold = pool = bn = 0.0
+    routes = conv_routes(w, layers, planes)
     for l in range(w.n_conv):
         kind, dx_stored, _, rows, _, _, proj_c, proj_step = layers[l]
-        np_ = planes[l]
+        np_, r = planes[l], routes[l]
         skip, proj = (w.skip_mask >> l) & 1, bool(proj_c)
         cin, cout = w.dims[l], w.dims[l + 1]
+        v = rows * cout                               # values of the output
+        last, first = l + 1 == w.n_conv, kind == lsam.LAYER_CONV_FIRST
         st2 = 4 if (w.stride_mask >> l) & 1 else 1    # pixels of the image read per output pixel
         if kind == lsam.LAYER_CONV_STORED:
             unfold += rows * (st2 * cin * 4.0 + 9 * cin * (2.0 * np_ if np_ else 4.0))
@@ -184,52 +240,75 @@ def conv_bytes(w, layers, planes):
         image = np_ if kind == lsam.LAYER_CONV_DIRECT else 0
         if l + 1 < w.n_conv and layers[l + 1][6]:
             image = max(image, planes[l + 1])
-        if image and l > 0 and (w.pool_mask >> (l - 1)) & 1:
+        if image and l > 0 and (routes[l - 1]["pool"] and not routes[l - 1]["bn_pool"]):
             pool += rows * st2 * cin * 2.0 * image
-        elif image and l > 0 and (w.bn_mask >> (l - 1)) & 1:
+        elif image and l > 0 and routes[l - 1]["bn"]:
             bn += rows * st2 * cin * 2.0 * image
         elif image:
             unfold += rows * st2 * cin * (4.0 + 2.0 * image)
-        # what is written of the output gradient behind its normalisation, bytes a value
-        dz = 2.0 * np_ + (4.0 if w.preact and skip and not proj else 0.0) if np_ else 4.0
-        if np_ and not (w.bn_mask >> l) & 1:
-            unfold += rows * cout * (4.0 + 2.0 * np_)
+        if np_ and not r["bn"] and not r["pool"]:
+            unfold += v * (4.0 + 2.0 * np_)
         if dx_stored:
             unfold += rows * (9 * cin + st2 * cin) * 4.0
-        if proj_c:
-            # projection: its normalisation costs what the layer's own does (below), and its
-            # output is read once more where the two branches meet; the pixels a strided one
-            # keeps are read in place on plane tensors, gathered (read and written) otherwise;
-            # backward, the gradient of those pixels
-            # is added to the block input's gradient under that input's mask (3 reads, 1 write)
-            # (a pre-activation block's bare projection is added to the convolution's output
-            # instead: two reads and a write)
-            if w.preact:
-                pool += rows * cout * 4.0 * 3
+        # what is written of the output gradient behind its normalisation, bytes a value
+        dz = 2.0 * np_ + (4.0 if w.preact and skip and not proj else 0.0) if np_ else 4.0
+        bits = 0.25
+        if r["bn"]:
+            # statistics read Z unless the product has left them; the normalisation reads Z again
+            bn += v * 4.0 * ((0 if r["sums_forward"] else 1) + 1)
+            if r["bn_pool"]:
+                bn += v / 4 * (4.0 + 2 * bits + (4.0 if r["pooled_floats"] else 0.0))
             else:
-                bn += rows * cout * (4.0 * (1 + 1 + 2 + 2) + (2.0 * np_ if np_ else 4.0))
+                bn += v * ((4.0 if r["floats"] else 0.0) + (bits if r["bits"] and not r["pool"] else 0.0))
+            # backward: sums of dY and Z unless the product has left them, then dZ from both (which a first
+            # layer's weight gradient forms itself)
+            if not r["sums_backward"]:
+                bn += v / 4 * (8.0 + bits) if r["bn_pool"] else v * (4.0 + bits) if r["from_average"] else v * 8.0
+            handed = w.preact and l + 2 < w.n_conv and (w.skip_mask >> (l + 2)) & 1 and not layers[l + 2][6]
+            if r["bn_pool"]:
+                bn += v * (4.0 + dz) + v / 4 * (4.0 + 2 * bits)
+            elif r["from_average"]:
+                bn += v * (4.0 + bits + dz)
+            elif not first or handed:
+                bn += v * (8.0 + dz + (4.0 if handed and np_ else 0.0))
+        if r["pool"] and not r["bn_pool"]:
+            # forward reads the image; what the backward pass writes goes to a normalisation or, without one, to the products
+            pool += v * 4.0 + v / 4 * (2 * bits + (4.0 if r["pooled_floats"] else 0.0))
+            pool += v / 4 * (4.0 + 2 * bits) + v * (2.0 * np_ if np_ and not r["bn"] else 4.0)
+        if last and w.global_avg_pool:
+            if not r["bn_gap"]:
+                pool += (v / 4 if r["pool"] else v) * 4.0
+            if not r["from_average"]:
+                pool += v / 4 * 4.0 if r["pool"] else v * (4.0 + (bits if r["bits"] else 4.0))
+        if proj:
+            # projection: its normalisation is the layer's own once more, from stored sums backward, and its
+            # output is read where the two branches meet; the pixels a strided one
+            # keeps are read in place on plane tensors, gathered (read and written) otherwise;
+            # backward, the gradient of those pixels joins the product that writes the block input's gradient, or
+            # is added to it under that input's mask (3 reads, 1 write).  A pre-activation block's bare
+            # projection joins the convolution's product, or is added to its output (two reads and a write)
+            if not w.preact:
+                dy = 4.0 if not r["from_average"] else bits
+                bn += v * ((0.0 if np_ else 4.0) + 4.0 + 2 * (4.0 + dy) + (2.0 * np_ if np_ else 4.0))
+            elif not np_:
+                pool += v * 4.0 * 3
             if proj_step == 2 and not np_:
                 unfold += rows * proj_c * 4.0 * 2
-            pool += rows * proj_c * 4.0 * 4
-        elif (w.skip_mask >> l) & 1 and w.preact:
-            # identity shortcut of a pre-activation block: the sum two convolutions below is added
-            # to this one's (forward), this one's gradient to that one's (backward; on plane
-            # tensors where that one's is formed)
-            pool += rows * cout * 4.0 * 3
-            if planes[l - 2]:
-                bn += rows * cout * 4.0
-            else:
-                pool += rows * cout * 4.0 * 3
-        elif (w.skip_mask >> l) & 1:
-            # shortcut: read with the normalisation (forward); backward reads dY, the mask and the
-            # block input's gradient and writes the latter
-            pool += rows * w.dims[l - 1] * 4.0 * (1 + 4)
-        if (w.pool_mask >> l) & 1:
-            pool += rows * cout * 4.0 * (1.25 + 2.25)
-        if (w.bn_mask >> l) & 1:
-            # statistics read Z; normalise+ReLU reads Z, writes the activation; the backward
-            # sums read Z and dY; the backward apply reads Z and dY and writes dZ
-            bn += rows * cout * (4.0 * (1 + 2 + 2 + 2) + dz)
+            if not routes[l - 1]["joins"]:
+                pool += rows * proj_c * 4.0 * 4
+        elif skip and w.preact:
+            # identity shortcut of a pre-activation block: the sum two convolutions below joins this one's
+            # product, or is added to it; backward, where no plane tensor is formed, likewise
+            if not np_:
+                pool += v * 4.0 * 3
+            if not planes[l - 2]:
+                pool += v * 4.0 * 3
+        elif skip:
+            # shortcut: read with the normalisation (forward); backward joins the product that writes the block
+            # input's gradient, or reads dY, the mask and that gradient and writes the latter
+            bn += rows * min(cout, w.dims[l - 1]) * 4.0
+            if not routes[l - 1]["joins"]:
+                pool += rows * min(cout, w.dims[l - 1]) * 4.0 * 4
     out = {}
     if bn:
         out["batchnorm"] = 2 * bn * w.K
@@ -405,7 +484,8 @@ def run_workload(w, steps, warmup, kernel_timing=True):
         nbytes = stream_bytes(w, fused_step, restarts)
         nbytes.update(conv_bytes(w, layers, planes))
         nbytes["center"] = float(np.sum((4.0 * nd + 16.0) * (nd > 0))) * w.d / steps
-        traffic = TRAFFIC.get(w.name, {}) if kernel_sources_digest() == TRAFFIC_SOURCES else {}
+        family = traffic_family(w)
+        traffic = TRAFFIC.get(w.name, {}) if kernel_sources_digest(family) == TRAFFIC_SOURCES[family] else {}
         for name, (cnt, tot) in stats.items():
             if cnt == 0:
                 continue

@@ -3,6 +3,7 @@ GPU (launches.py)."""
 import pytest
 
 pytest.importorskip("torch")
+import bench  # noqa: E402
 import launches  # noqa: E402
 import test_gpu_plane_channels as channels  # noqa: E402
 import test_gpu_relu_bits as bits  # noqa: E402
@@ -61,8 +62,11 @@ def test_classes_on_few_pixels(cin, cout, batch, K, fold):
     (64, 32, 512, 0b100, False)])
 def test_joined_averages(channels, side, images, skip, joined):
     dims = (3,) + (channels,) * (3 if skip else 2) + (10,)
-    got = names(dict(dims=dims, side=(side, side), batch=images // 4, K=4, skip=skip))
+    net = dict(dims=dims, side=(side, side), batch=images // 4, K=4, skip=skip)
+    got = names(net)
     assert ("bn_avgpool_kernel" in got) == joined and ("avgpool_kernel" in got) != joined
+    w = bits.net(**net)        # (what the benchmark counts the bytes of)
+    assert bench.joined_average(w, w.batch * side * side, channels, bool(skip)) == joined
 
 
 @pytest.mark.parametrize("name,joined", [("average behind a shortcut", False), ("average of few positions behind a shortcut", True),
